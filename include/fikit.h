@@ -193,9 +193,8 @@ size_t fikit_profile_gapfill_workspace_bytes(uint64_t n_records, uint32_t n_task
  * required here; the profile's outputs are the gap fill's inputs), and every output equals what the two calls give
  * one after the other.  The difference is inside: a task that one workgroup profiles whole has its launches'
  * predicted durations and idle times written by that workgroup while the launches are still in its registers, so
- * the gap fill need not read the Kernel IDs again and look every one up (with at least 4096 scenarios and
- * predictions below 2^32 - 1 ns; otherwise, and for the tasks that take other paths, exactly the kernels of the two
- * calls run).
+ * the gap fill need not read the Kernel IDs again and look every one up (with predictions below 2^32 - 1 ns;
+ * otherwise, and for the tasks that take other paths, exactly the kernels of the two calls run).
  *
  *   d_workspace   256-byte aligned, at least fikit_profile_gapfill_workspace_bytes(...) bytes.
  *

@@ -22,7 +22,6 @@ namespace {
 using namespace fikit;
 
 constexpr uint64_t MAX_ELEMS = (1ull << 32) - (1ull << 24);
-constexpr int WALK_GW = 64;   // lanes that share a scenario in the few-scenario walk
 
 #define FIKIT_HIP(expr)                           \
   do {                                            \
@@ -538,8 +537,10 @@ int fikit_profile(const fikit_launch* d_records, uint64_t n_records, const uint6
 
 // The per-launch arrays of the gap fill are read in 64-byte pieces that may reach past the last launch.
 constexpr uint64_t GF_PAD = 256;
-// One lane per scenario pays off once there are about as many scenarios as the GPU has lanes to run at a time.
-constexpr uint64_t GF_LANES_MIN_SCENARIOS = 4096;
+// From this many scenarios on, one lane steps through a scenario (k_gf_walk_lanes), below it a wave (k_gf_walk_wave).  The
+// lanes take about 3.3 ms for traces of 4096 and queues of 16,384 launches, however many they are (to 65,536); the waves 0.1 ms
+// per 1024 scenarios of that shape once the chip is full (1.55 ms against 3.2 ms at 16,384).
+constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
 
 }  // extern "C"
 
@@ -547,85 +548,124 @@ namespace {
 
 constexpr uint64_t ws_align(uint64_t v) { return (v + 255) / 256 * 256; }
 
-// Workspace of the gap fill: control block, task roles, two work lists, queue totals, three per-launch arrays.
+// Workspace of the gap fill: control block, task roles, queue totals, three per-launch arrays.
 constexpr uint64_t gapfill_ws_bytes(uint64_t n_ids, uint64_t n_tasks) {
-  return 256 + ws_align(n_tasks * 4) + ws_align(n_tasks * 4 * 2) + ws_align(n_tasks * 8) + 2 * ws_align(n_ids * 8 + GF_PAD) +
-         ws_align(n_ids * 8);
+  return 256 + ws_align(n_tasks * 4) + ws_align(n_tasks * 8) + 2 * ws_align(n_ids * 8 + GF_PAD) + ws_align(n_ids * 8);
 }
+
+struct GapfillBuffers {
+  Ctrl* ctrl;
+  uint32_t* role;
+  uint64_t* lp_total;
+  int64_t *pe, *pg, *open;   // 64-bit predictions (k_gf_predict)
+  uint32_t* lp_e;            // 32-bit predictions (k_gf_predict32): they share the space of pe and pg
+  uint2* hp_eg;
+  GapfillBuffers(unsigned char* ws, uint64_t n_ids, uint32_t n_tasks) {
+    Carver c;
+    ctrl = reinterpret_cast<Ctrl*>(ws + c.take(256));
+    role = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4));
+    lp_total = reinterpret_cast<uint64_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 8));
+    pe = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
+    pg = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
+    open = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8));
+    lp_e = reinterpret_cast<uint32_t*>(pe);
+    hp_eg = reinterpret_cast<uint2*>(pg);
+  }
+};
 
 bool gapfill_params_ok(const fikit_gapfill_params* p) {
   return p && p->margin_ns >= 0 && p->min_gap_ns >= 0 && p->reserved == 0 && p->predictor >= FIKIT_PREDICT_P50 &&
          p->predictor <= FIKIT_PREDICT_MEAN;
 }
 
-// The gap fill in two parts: what has to come before the predictions (checks, task roles, work lists) and the rest.
-enum GfPart { GF_ALL, GF_SETUP, GF_REST };
+// Workgroups per task of k_gf_predict32: about PRED_PART launches each, and with few tasks as many as give the chip a few
+// workgroups per compute unit (a workgroup whose part is empty leaves at once).
+uint32_t predict_parts(uint64_t n_ids, uint32_t n_tasks) {
+  constexpr uint64_t PRED_PART = 8192, PRED_WORKGROUPS = 2048;
+  const uint64_t tasks = n_tasks ? n_tasks : 1;
+  uint64_t parts = n_ids / tasks / PRED_PART + 1;
+  if (parts * tasks < PRED_WORKGROUPS) parts = PRED_WORKGROUPS / tasks;
+  const uint64_t most = n_ids / (2 * PRED_THREADS) + 1;
+  if (parts > most) parts = most;
+  return static_cast<uint32_t>(parts > 64 ? 64 : parts);
+}
 
-// Enqueues every kernel of the gap fill on `st`; `ws` holds gapfill_ws_bytes(n_ids, n_tasks) bytes whose first 64
-// are the control block.  Nothing is read back and nothing is allocated here.
-int gapfill_enqueue(hipStream_t st, Tracer& tr, const uint64_t* d_ids, uint64_t n_ids, const uint64_t* d_task_offsets,
-                    uint32_t n_tasks, const fikit_row* d_rows, const uint64_t* d_task_row_offsets, const uint32_t* d_hp_task,
-                    const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
-                    const uint64_t* d_gap_offsets, uint64_t n_gaps, uint32_t* d_fill_count, int64_t* d_filled_ns,
-                    int64_t* d_lp_completion_ns, uint64_t* d_lp_placed, unsigned char* ws, bool set_attributes,
-                    GfPart part = GF_ALL, PredEmit* emit = nullptr) {
-  Carver c;
-  Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + c.take(256));
-  uint32_t* role = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4));
-  uint32_t* glists = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4 * 2));
-  uint64_t* lp_total = reinterpret_cast<uint64_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 8));
-  int64_t* pe = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
-  int64_t* pg = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
-  int64_t* open = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8));
-  // the 32-bit arrays of the one-lane-per-scenario kernels share the space of the 64-bit ones
-  uint32_t* lp_e = reinterpret_cast<uint32_t*>(pe);
-  uint2* hp_eg = reinterpret_cast<uint2*>(pg);
+// What every gap fill starts with: a cleared control block, checked arguments, task roles.
+void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_task_offsets, uint64_t n_ids, uint32_t n_tasks,
+                           const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets,
+                           uint64_t n_gaps) {
+  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, n_tasks);
+  hipLaunchKernelGGL(k_gf_check, dim3(blocks_for(n_scenarios > n_tasks ? n_scenarios : n_tasks, 256)), dim3(256), 0, st, d_task_offsets,
+                     n_tasks, n_ids, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, b.role, b.ctrl);
+}
 
-  const bool lanes = n_scenarios >= GF_LANES_MIN_SCENARIOS && n_gaps < MAX_ELEMS;
-  if (emit) {   // (what a profile that runs between the two parts may fill in; only the lane kernels read this form)
-    emit->role = lanes ? role : nullptr;
-    emit->lp_e = lp_e; emit->hp_eg = hp_eg; emit->lp_total = lp_total; emit->predictor = static_cast<uint32_t>(h_params->predictor);
-  }
-  if (part != GF_REST) {
-  tr.mark("gf_setup");
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, role, static_cast<uint64_t>(n_tasks), 0u);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
-  hipLaunchKernelGGL(k_gf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
-                     d_lp_task, n_scenarios, d_gap_offsets, n_gaps, role, ctrl);
-  tr.mark("gf_lists");
-  hipLaunchKernelGGL(k_gf_lists, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, role, 8192u, glists,
-                     ctrl);
-  FIKIT_HIP(hipGetLastError());
-  }
-  if (part == GF_SETUP) return FIKIT_OK;
-  // Many scenarios: one lane per scenario on 32-bit predictions; the 64-bit kernels then only run if a
-  // prediction did not fit (they check Ctrl::wide).  Few scenarios: the 64-bit kernels, a group of lanes each.
-  if (lanes) {
-    tr.mark("k_gf_predict32");
-    hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
-                       d_task_row_offsets, role, glists, static_cast<const int64_t*>(nullptr), lp_e, hp_eg, lp_total,
-                       static_cast<uint32_t>(h_params->predictor), emit ? emit->done : static_cast<const uint32_t*>(nullptr), ctrl);
-    tr.mark("k_gf_walk_lanes");
+// The walk on 32-bit predictions in one of its modes; `result`: completion times, or delays in the replay modes.
+template <int MODE>
+int walk_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_task_offsets, const uint32_t* d_hp_task,
+                 const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets, uint64_t n_gaps, int64_t margin,
+                 int64_t min_gap, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* result, uint64_t* d_lp_placed,
+                 bool set_attributes) {
+  if (n_scenarios >= GF_LANES_MIN_SCENARIOS && n_gaps < MAX_ELEMS) {
     if (set_attributes)
-      FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gf_walk_lanes<LW_PLAN>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizeof(LaneWalkSmem))));
+      FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gf_walk_lanes<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    static_cast<int>(sizeof(LaneWalkSmem))));
     const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
-    hipLaunchKernelGGL(k_gf_walk_lanes<LW_PLAN>, dim3(blocks_for(n_scenarios, LW_THREADS)), dim3(LW_THREADS), sizeof(LaneWalkSmem), st,
-                       d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, lp_e, hp_eg, lp_total,
-                       h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
-                       vec_ok, ctrl);
+    hipLaunchKernelGGL(k_gf_walk_lanes<MODE>, dim3(blocks_for(n_scenarios, LW_THREADS)), dim3(LW_THREADS), sizeof(LaneWalkSmem), st,
+                       d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
+                       d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, b.ctrl);
+  } else {
+    hipLaunchKernelGGL(k_gf_walk_wave<MODE>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st, d_task_offsets,
+                       d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,
+                       d_filled_ns, result, d_lp_placed, b.ctrl);
   }
-  const uint32_t only_if_wide = lanes ? 1u : 0u;
-  tr.mark("k_gf_predict");
-  hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
-                     d_task_row_offsets, role, glists, pe, pg, open, only_if_wide, static_cast<uint32_t>(h_params->predictor), ctrl);
-  tr.mark("k_gf_walk");
-  hipLaunchKernelGGL((k_gf_walk<WALK_GW, true>), dim3(blocks_for(n_scenarios, 256 / WALK_GW)), dim3(256), 0, st, d_task_offsets, d_hp_task,
-                     d_lp_task, n_scenarios, d_gap_offsets, pe, pg, open, h_params->margin_ns, h_params->min_gap_ns,
-                     d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, only_if_wide, ctrl);
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
+}
+
+// Enqueues the predictions and the fill on `st` (gapfill_check_enqueue has been).  done (may be null): tasks whose predictions exist
+// already.  Nothing is read back and nothing is allocated here.
+int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_ids, uint64_t n_ids,
+                    const uint64_t* d_task_offsets, uint32_t n_tasks, const fikit_row* d_rows, const uint64_t* d_task_row_offsets,
+                    const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
+                    const uint64_t* d_gap_offsets, uint64_t n_gaps, uint32_t* d_fill_count, int64_t* d_filled_ns,
+                    int64_t* d_lp_completion_ns, uint64_t* d_lp_placed, bool set_attributes, const uint32_t* done) {
+  tr.mark("k_gf_predict32");
+  hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
+                     n_tasks, d_rows, d_task_row_offsets, b.role, static_cast<const int64_t*>(nullptr), b.lp_e, b.hp_eg, b.lp_total,
+                     static_cast<uint32_t>(h_params->predictor), done, b.ctrl);
+  tr.mark("k_gf_walk");
+  return walk_enqueue<LW_PLAN>(st, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
+                               h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, set_attributes);
+}
+
+// The 64-bit kernels, which do the call if a prediction did not fit 32 bits (they check Ctrl::wide).
+int gapfill_wide_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_ids, const uint64_t* d_task_offsets, uint32_t n_tasks,
+                         const fikit_row* d_rows, const uint64_t* d_task_row_offsets, const uint32_t* d_hp_task,
+                         const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
+                         const uint64_t* d_gap_offsets, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* d_lp_completion_ns,
+                         uint64_t* d_lp_placed) {
+  hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
+                     d_task_row_offsets, b.role, b.pe, b.pg, b.open, static_cast<uint32_t>(h_params->predictor), b.ctrl);
+  hipLaunchKernelGGL(k_gf_walk, dim3(blocks_for(n_scenarios, 256 / WAVE)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
+                     n_scenarios, d_gap_offsets, b.pe, b.pg, b.open, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,
+                     d_lp_completion_ns, d_lp_placed, b.ctrl);
+  FIKIT_HIP(hipGetLastError());
+  return FIKIT_OK;
+}
+
+// Ends a gap fill: its status, and the 64-bit kernels first if they are needed.
+template <typename Wide>
+int finish_gapfill(hipStream_t st, Tracer& tr, const Ctrl* ctrl, Wide enqueue_wide) {
+  tr.mark("host_sync");
+  Ctrl h{};
+  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+  if (int rc = status_from_bits(h.status)) return rc;
+  if (!h.wide) return FIKIT_OK;
+  tr.mark("gf_wide");
+  if (int rc = enqueue_wide()) return rc;
+  tr.mark("host_sync");
+  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+  return status_from_bits(h.status);
 }
 
 }  // namespace
@@ -665,16 +705,18 @@ int fikit_gapfill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint32_
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
   if (workspace_bytes < fikit_gapfill_workspace_bytes(n_ids, n_tasks, n_scenarios)) return FIKIT_WORKSPACE_TOO_SMALL;
 
-  unsigned char* ws = static_cast<unsigned char*>(d_workspace);
+  const GapfillBuffers b(static_cast<unsigned char*>(d_workspace), n_ids, n_tasks);
   Tracer tr(st);
-  if (int rc = gapfill_enqueue(st, tr, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
+  tr.mark("gf_setup");
+  gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+  if (int rc = gapfill_enqueue(st, tr, b, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
                                n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns, d_lp_completion_ns,
-                               d_lp_placed, ws, true))
+                               d_lp_placed, true, nullptr))
     return rc;
-  tr.mark("host_sync");
-  Ctrl h{};
-  if (int rc = read_ctrl(reinterpret_cast<const Ctrl*>(ws), &h, st)) return rc;
-  return status_from_bits(h.status);
+  return finish_gapfill(st, tr, b.ctrl, [&] {
+    return gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task, n_scenarios,
+                                h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed);
+  });
 }
 
 size_t fikit_profile_gapfill_workspace_bytes(uint64_t n_records, uint32_t n_tasks, uint64_t n_scenarios) {
@@ -718,28 +760,29 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
 
   // 1. the gap fill's checks and task roles; 2. the profile, whose one-workgroup kernels also write the predictions
   // of the tasks that the scenarios use; 3. the predictions of the remaining tasks, and the fill.
+  const GapfillBuffers b(gf_ws, n_records, n_tasks);
   PredEmit emit{};
-  emit.done = done;
+  emit.role = b.role; emit.lp_e = b.lp_e; emit.hp_eg = b.hp_eg; emit.lp_total = b.lp_total; emit.done = done;
+  emit.predictor = static_cast<uint32_t>(h_params->predictor);
   {
     Tracer tr(st);
+    tr.mark("gf_setup");
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, done, static_cast<uint64_t>(n_tasks), 0u);
-    if (int rc = gapfill_enqueue(st, tr, d_ids_out, n_records, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task,
-                                 d_lp_task, n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns,
-                                 d_lp_completion_ns, d_lp_placed, gf_ws, true, GF_SETUP, &emit))
-      return rc;
+    gapfill_check_enqueue(st, b, d_task_offsets, n_records, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+    FIKIT_HIP(hipGetLastError());
   }
   if (int rc = profile_run(d_records, n_records, d_task_offsets, n_tasks, d_ids_out, d_rows_out, row_capacity, d_task_row_offsets,
-                           h_n_rows, ws, prof_bytes, hip_stream, emit.role ? &emit : nullptr))
+                           h_n_rows, ws, prof_bytes, hip_stream, &emit))
     return rc;
   Tracer tr(st);
-  if (int rc = gapfill_enqueue(st, tr, d_ids_out, n_records, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task,
+  if (int rc = gapfill_enqueue(st, tr, b, d_ids_out, n_records, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task,
                                d_lp_task, n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns,
-                               d_lp_completion_ns, d_lp_placed, gf_ws, true, GF_REST, &emit))
+                               d_lp_completion_ns, d_lp_placed, true, done))
     return rc;
-  tr.mark("host_sync");
-  Ctrl h{};
-  if (int rc = read_ctrl(reinterpret_cast<const Ctrl*>(gf_ws), &h, st)) return rc;
-  return status_from_bits(h.status);
+  return finish_gapfill(st, tr, b.ctrl, [&] {
+    return gapfill_wide_enqueue(st, b, d_ids_out, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task, d_lp_task,
+                                n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed);
+  });
 }
 
 }  // extern "C"
@@ -811,12 +854,19 @@ int fikit_gapfill_static(const uint64_t* d_ids, uint64_t n_ids, const uint64_t* 
   if (int rc = static_scratch_of_current_device(&ws)) return rc;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   Tracer tr(st, false);   // (recording events would allocate)
+  const GapfillBuffers b(ws, n_ids, n_tasks);
   if (n_scenarios == 0) {
-    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, reinterpret_cast<Ctrl*>(ws));
-  } else if (int rc = gapfill_enqueue(st, tr, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task,
-                                      d_lp_task, n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns,
-                                      d_lp_completion_ns, d_lp_placed, ws, false)) {
-    return rc;
+    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, b.ctrl);
+  } else {
+    gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+    if (int rc = gapfill_enqueue(st, tr, b, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
+                                 n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns, d_lp_completion_ns,
+                                 d_lp_placed, false, nullptr))
+      return rc;
+    // (whether a prediction needs 64 bits is only known on the device, and nothing is waited for here)
+    if (int rc = gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
+                                      n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed))
+      return rc;
   }
   hipLaunchKernelGGL(k_publish_status, dim3(1), dim3(64), 0, st, reinterpret_cast<const Ctrl*>(ws), d_status);
   FIKIT_HIP(hipGetLastError());
@@ -887,61 +937,29 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
   if (workspace_bytes < fikit_replay_workspace_bytes(n_ids, n_tasks, n_scenarios)) return FIKIT_WORKSPACE_TOO_SMALL;
 
-  unsigned char* ws = static_cast<unsigned char*>(d_workspace);
-  Carver c;   // (same layout as fikit_gapfill: the 32-bit arrays share the space of the 64-bit ones)
-  Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + c.take(256));
-  uint32_t* role = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4));
-  uint32_t* glists = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4 * 2));
-  uint64_t* lp_total = reinterpret_cast<uint64_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 8));
-  int64_t* pe = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
-  int64_t* pg = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
-  uint32_t* lp_e = reinterpret_cast<uint32_t*>(pe);
-  uint2* hp_eg = reinterpret_cast<uint2*>(pg);
-
+  const GapfillBuffers b(static_cast<unsigned char*>(d_workspace), n_ids, n_tasks);
   Tracer tr(st);
   tr.mark("gf_setup");
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, role, static_cast<uint64_t>(n_tasks), 0u);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
-  hipLaunchKernelGGL(k_gf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
-                     d_lp_task, n_scenarios, d_gap_offsets, n_gaps, role, ctrl);
-  tr.mark("gf_lists");
-  hipLaunchKernelGGL(k_gf_lists, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, role, 8192u, glists,
-                     ctrl);
+  gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
   tr.mark("k_gf_predict32");
-  hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
-                     d_task_row_offsets, role, glists, d_actual_gap_ns, lp_e, hp_eg, lp_total,
-                     static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), ctrl);
-  const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
-  const dim3 grid(blocks_for(n_scenarios, LW_THREADS)), block(LW_THREADS);
-  if (h_params->feedback) {
-    tr.mark("k_gf_replay_feedback");
-    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gf_walk_lanes<LW_REPLAY_FEEDBACK>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizeof(LaneWalkSmem))));
-    hipLaunchKernelGGL(k_gf_walk_lanes<LW_REPLAY_FEEDBACK>, grid, block, sizeof(LaneWalkSmem), st, d_task_offsets, d_hp_task,
-                       d_lp_task, n_scenarios, d_gap_offsets, lp_e, hp_eg, lp_total, h_params->margin_ns, h_params->min_gap_ns,
-                       d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, vec_ok, ctrl);
-  } else {
-    tr.mark("k_gf_replay");
-    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gf_walk_lanes<LW_REPLAY>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(sizeof(LaneWalkSmem))));
-    hipLaunchKernelGGL(k_gf_walk_lanes<LW_REPLAY>, grid, block, sizeof(LaneWalkSmem), st, d_task_offsets, d_hp_task, d_lp_task,
-                       n_scenarios, d_gap_offsets, lp_e, hp_eg, lp_total, h_params->margin_ns, h_params->min_gap_ns,
-                       d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, vec_ok, ctrl);
-  }
-  // a prediction that did not fit 32 bits (Ctrl::wide): the walk above has not run; the 64-bit kernels do the call
-  tr.mark("k_gf_replay_wide");
-  hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
-                     d_task_row_offsets, role, glists, pe, pg, static_cast<int64_t*>(nullptr), 1u,
-                     static_cast<uint32_t>(h_params->predictor), ctrl);
-  hipLaunchKernelGGL(k_gf_replay_wide, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
-                     n_scenarios, d_gap_offsets, pe, pg, d_actual_gap_ns, h_params->margin_ns, h_params->min_gap_ns,
-                     h_params->feedback ? 1u : 0u, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, ctrl);
-  FIKIT_HIP(hipGetLastError());
-  tr.mark("host_sync");
-  Ctrl h{};
-  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
-  return status_from_bits(h.status);
+  hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
+                     n_tasks, d_rows, d_task_row_offsets, b.role, d_actual_gap_ns, b.lp_e, b.hp_eg, b.lp_total,
+                     static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), b.ctrl);
+  tr.mark(h_params->feedback ? "k_gf_replay_feedback" : "k_gf_replay");
+  auto walk = h_params->feedback ? walk_enqueue<LW_REPLAY_FEEDBACK> : walk_enqueue<LW_REPLAY>;
+  if (int rc = walk(st, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
+                    h_params->min_gap_ns, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, true))
+    return rc;
+  return finish_gapfill(st, tr, b.ctrl, [&]() -> int {
+    hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
+                       d_task_row_offsets, b.role, b.pe, b.pg, static_cast<int64_t*>(nullptr),
+                       static_cast<uint32_t>(h_params->predictor), b.ctrl);
+    hipLaunchKernelGGL(k_gf_replay_wide, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
+                       n_scenarios, d_gap_offsets, b.pe, b.pg, d_actual_gap_ns, h_params->margin_ns, h_params->min_gap_ns,
+                       h_params->feedback ? 1u : 0u, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, b.ctrl);
+    FIKIT_HIP(hipGetLastError());
+    return FIKIT_OK;
+  });
 }
 
 size_t fikit_prio_fill_workspace_bytes(uint64_t n_ids, uint32_t n_tasks, uint64_t n_scenarios) {
@@ -950,7 +968,6 @@ size_t fikit_prio_fill_workspace_bytes(uint64_t n_ids, uint32_t n_tasks, uint64_
   Carver c;
   c.take(256);
   c.take(static_cast<uint64_t>(n_tasks) * 4);
-  c.take(static_cast<uint64_t>(n_tasks) * 4 * 2);
   c.take(static_cast<uint64_t>(n_tasks) * 8);
   c.take(n_ids * 8 + GF_PAD);
   c.take(n_ids * 8 + GF_PAD);
@@ -992,7 +1009,6 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   Carver c;
   Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + c.take(256));
   uint32_t* role = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4));
-  uint32_t* glists = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4 * 2));
   uint64_t* lp_total = reinterpret_cast<uint64_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 8));
   int64_t* pe = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));   // the 32-bit arrays share the space of the 64-bit ones
   int64_t* pg = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
@@ -1001,13 +1017,10 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
 
   Tracer tr(st);
   tr.mark("pf_setup");
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, role, static_cast<uint64_t>(n_tasks), 0u);
+  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, ctrl, role, lp_total, n_tasks);
   hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
   hipLaunchKernelGGL(k_pf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
                      d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, n_entries, d_gap_offsets, role, ctrl);
-  hipLaunchKernelGGL(k_gf_lists, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, role, 8192u, glists,
-                     ctrl);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};
@@ -1019,8 +1032,8 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   const bool groups = widest <= PF_MAX_LP;
   if (groups) {
     tr.mark("k_gf_predict32");
-    hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
-                       d_task_row_offsets, role, glists, static_cast<const int64_t*>(nullptr), lp_e, hp_eg, lp_total,
+    hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
+                       n_tasks, d_rows, d_task_row_offsets, role, static_cast<const int64_t*>(nullptr), lp_e, hp_eg, lp_total,
                        static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), ctrl);
     const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
     tr.mark("k_pf_walk");
@@ -1039,18 +1052,20 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
 #undef FIKIT_PF_WALK
     if (rc) return rc;
   }
-  const uint32_t only_if_wide = groups ? 1u : 0u;
-  tr.mark("k_pf_walk_wide");
-  hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
-                     d_task_row_offsets, role, glists, pe, pg, static_cast<int64_t*>(nullptr), only_if_wide,
-                     static_cast<uint32_t>(h_params->predictor), ctrl);
-  hipLaunchKernelGGL(k_pf_walk_wide, dim3(blocks_for(n_scenarios, 64)), dim3(64), 0, st, d_task_offsets, d_hp_task, d_lp_offsets,
-                     d_lp_task, d_lp_prio, n_scenarios, d_gap_offsets, pe, pg, h_params->margin_ns, h_params->min_gap_ns,
-                     d_fill_count, d_filled_ns, d_lp_placed, d_lp_placed_ns, only_if_wide, ctrl);
-  FIKIT_HIP(hipGetLastError());
-  tr.mark("host_sync");
-  if (int rc2 = read_ctrl(ctrl, &h, st)) return rc2;
-  return status_from_bits(h.status);
+  if (!groups) {
+    // the 64-bit kernels, as if a prediction had not fitted
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->wide, static_cast<uint64_t>(1), 1u);
+  }
+  return finish_gapfill(st, tr, ctrl, [&]() -> int {
+    hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
+                       d_task_row_offsets, role, pe, pg, static_cast<int64_t*>(nullptr), static_cast<uint32_t>(h_params->predictor),
+                       ctrl);
+    hipLaunchKernelGGL(k_pf_walk_wide, dim3(blocks_for(n_scenarios, 64)), dim3(64), 0, st, d_task_offsets, d_hp_task, d_lp_offsets,
+                       d_lp_task, d_lp_prio, n_scenarios, d_gap_offsets, pe, pg, h_params->margin_ns, h_params->min_gap_ns,
+                       d_fill_count, d_filled_ns, d_lp_placed, d_lp_placed_ns, ctrl);
+    FIKIT_HIP(hipGetLastError());
+    return FIKIT_OK;
+  });
 }
 
 size_t fikit_pairing_workspace_bytes(uint32_t n_tasks) {

@@ -3,22 +3,34 @@
 // kernels into each predicted idle gap for as long as they fit.
 //
 // Because predicted durations are >= 0, "keep issuing the head of the queue while it fits into
-// what is left" is the same as "advance the queue pointer to the last position whose prefix sum
-// of durations does not exceed (consumed so far) + (gap - margin)".  The kernels therefore work
-// on per-task prefix sums and search them with ballots.
+// what is left" is the same as "advance the queue pointer to the last position whose running sum
+// of durations does not exceed (consumed so far) + (gap - margin)".  Predictions are looked up once per
+// launch (k_gf_predict32) and are 32-bit numbers of nanoseconds; calls with a prediction that does not fit take
+// the 64-bit kernels (k_gf_predict, k_gf_walk).
 #pragma once
 
 #include "common.hip.h"
 
 namespace fikit {
 
-// Checks scenario arguments (n_gaps: the number of per-gap output slots the host sized its buffers for) and
-// records in role[t] how each task is used.
-__global__ void k_gf_scenarios(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* __restrict__ hp_task,
-                               const uint32_t* __restrict__ lp_task, uint64_t n_scen,
-                               const uint64_t* __restrict__ gap_off, uint64_t n_gaps, uint32_t* __restrict__ role, Ctrl* ctrl) {
-  if (ctrl->status & ERR_OFFSETS) return;
+// Start values of a call: the control block, and per task no role and no queue total.
+__global__ void k_gf_clear(Ctrl* ctrl, uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t n_tasks) {
+  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[t] = 0;
+  if (t < n_tasks) { role[t] = 0; lp_total[t] = 0; }
+}
+
+// Checks the task offsets (first 0, non-decreasing, last == n_ids) and the scenario arguments (n_gaps: the number of
+// per-gap output slots the host sized its buffers for), and records in role[t] how each task is used.  One thread per
+// task and per scenario; nothing is looked up at an offset here, so the two checks need not wait for each other.
+__global__ void k_gf_check(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const uint32_t* __restrict__ hp_task,
+                           const uint32_t* __restrict__ lp_task, uint64_t n_scen, const uint64_t* __restrict__ gap_off,
+                           uint64_t n_gaps, uint32_t* __restrict__ role, Ctrl* ctrl) {
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (s < n_tasks) {
+    const uint64_t a = off[s], b = off[s + 1];
+    if (a > b || b > n_ids || (s == 0 && a != 0) || (s + 1 == n_tasks && b != n_ids)) atomicOr(&ctrl->status, ERR_OFFSETS);
+  }
   if (s >= n_scen) return;
   if (s + 1 == n_scen && gap_off[n_scen] != n_gaps) atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
   const uint32_t hp = hp_task[s], lp = lp_task[s];
@@ -27,22 +39,9 @@ __global__ void k_gf_scenarios(const uint64_t* __restrict__ off, uint32_t n_task
   const uint64_t want = H > 0 ? H - 1 : 0;
   if (gap_off[s + 1] < gap_off[s] || gap_off[s + 1] - gap_off[s] != want || (s == 0 && gap_off[0] != 0))
     atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
-  atomicOr(&role[hp], ROLE_HP);
-  atomicOr(&role[lp], ROLE_LP);
-}
-
-// Work list of the predict kernel: tasks that play a role, short traces first, long ones after, so
-// that workgroups started next to each other have work of similar size.
-__global__ void k_gf_lists(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* __restrict__ role,
-                           uint32_t split_len, uint32_t* __restrict__ lists, Ctrl* ctrl) {
-  if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
-  const uint64_t t = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  uint32_t c = 2;
-  if (t < n_tasks && role[t]) c = (off[t + 1] - off[t]) <= split_len ? 0u : 1u;
-  for (uint32_t k = 0; k < 2; ++k) {
-    const uint32_t pos = wave_append(&ctrl->n_class[k], c == k);
-    if (c == k) lists[static_cast<uint64_t>(k) * n_tasks + pos] = static_cast<uint32_t>(t);
-  }
+  // (a task heads or serves many scenarios: the word is only touched while a bit is still missing)
+  if (!(__hip_atomic_load(&role[hp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ROLE_HP)) atomicOr(&role[hp], ROLE_HP);
+  if (!(__hip_atomic_load(&role[lp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ROLE_LP)) atomicOr(&role[lp], ROLE_LP);
 }
 
 constexpr int PRED_THREADS = 256;
@@ -97,15 +96,12 @@ __device__ __forceinline__ bool predict_one(uint64_t id, bool in_lds, const Pred
 __global__ void __launch_bounds__(PRED_THREADS) __attribute__((amdgpu_waves_per_eu(5, 8)))
 k_gf_predict(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, uint32_t n_tasks,
              const fikit_row* __restrict__ rows, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role,
-             const uint32_t* __restrict__ lists, int64_t* __restrict__ pe, int64_t* __restrict__ pg,
-             int64_t* __restrict__ open, uint32_t only_if_wide, uint32_t predictor, Ctrl* ctrl) {
+             int64_t* __restrict__ pe, int64_t* __restrict__ pg, int64_t* __restrict__ open, uint32_t predictor, Ctrl* ctrl) {
   __shared__ PredTable tb;
   // only bits that earlier kernels set: the decision must be the same for the whole workgroup
   if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
-  if (only_if_wide && !ctrl->wide) return;
-  const uint32_t n_short = ctrl->n_class[0], n_longer = ctrl->n_class[1];   // final: set by an earlier kernel
-  if (blockIdx.x >= n_short + n_longer) return;
-  const uint32_t t = blockIdx.x < n_short ? lists[blockIdx.x] : lists[static_cast<uint64_t>(n_tasks) + (blockIdx.x - n_short)];
+  if (!ctrl->wide) return;
+  const uint32_t t = blockIdx.x;   // (one workgroup per task)
   const uint32_t rl = role[t];
   if (rl == 0) return;
   const uint64_t base = off[t], len = off[t + 1] - base;
@@ -202,31 +198,21 @@ k_gf_predict(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off,
   if (unknown) atomicOr(&ctrl->status, ERR_UNKNOWN_ID);
 }
 
-// The walk.  GW lanes cooperate on one scenario (GW divides 64): they read GW predicted gaps
-// at a time, and search the low-priority prefix sums GW candidates at a time with a ballot.
-// A value of the group's lane `idx`, where idx is the same in all lanes of the group (a whole wave: scalar lane select).
-template <int GW>
-__device__ __forceinline__ int64_t group_value(int64_t v, uint32_t gbase, uint32_t idx) {
-  if constexpr (GW == WAVE) return static_cast<int64_t>(read_lane_u64(static_cast<uint64_t>(v), idx));
-  else return static_cast<int64_t>(shfl_u64(static_cast<uint64_t>(v), gbase + idx));
+// The walk on 64-bit prefix sums, one wave per scenario: for calls with a prediction that does not fit 32 bits.
+__device__ __forceinline__ int64_t lane_value(int64_t v, uint32_t idx) {   // (idx: the same in all lanes)
+  return static_cast<int64_t>(read_lane_u64(static_cast<uint64_t>(v), idx));
 }
 
-template <int GW, bool WINDOW>
 __global__ void __launch_bounds__(256)
 k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
           uint64_t n_scen, const uint64_t* __restrict__ gap_off, const int64_t* __restrict__ pe,
           const int64_t* __restrict__ pg, const int64_t* __restrict__ open, int64_t margin, int64_t min_gap,
           uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
-          uint64_t* __restrict__ placed_out, uint32_t only_if_wide, const Ctrl* ctrl) {
-  if (ctrl->status) return;
-  if (only_if_wide && !ctrl->wide) return;
-  constexpr int GROUPS_PER_BLOCK = 256 / GW;
-  const uint64_t s = static_cast<uint64_t>(blockIdx.x) * GROUPS_PER_BLOCK + threadIdx.x / GW;
-  if (s >= n_scen) return;  // whole groups leave together
+          uint64_t* __restrict__ placed_out, const Ctrl* ctrl) {
+  if (ctrl->status || !ctrl->wide) return;
+  const uint64_t s = static_cast<uint64_t>(blockIdx.x) * (256 / WAVE) + threadIdx.x / WAVE;
+  if (s >= n_scen) return;  // whole waves leave together
   const uint32_t lane = lane_id();
-  const uint32_t gl = lane % GW;           // lane within the group
-  const uint32_t gbase = lane - gl;        // first lane of the group
-  const uint64_t gmask = (GW == 64) ? ~0ull : ((1ull << GW) - 1ull);
 
   const uint32_t hp = hp_task[s], lp = lp_task[s];
   const uint64_t h0 = off[hp], H = off[hp + 1] - h0;
@@ -238,80 +224,65 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
   int64_t consumed = 0;   // their total predicted duration = pe[l0 + p - 1]
   bool done = (L == 0);
   int64_t completion = 0;
-  // The group keeps 2 * GW consecutive prefix sums of the low-priority queue in registers (win0: entries
-  // wb .. wb+GW-1, win1: the next GW), with wb <= p < wb + GW, so that most gaps are searched without
+  // The wave keeps 128 consecutive prefix sums of the low-priority queue in registers (win0: entries
+  // wb .. wb+63, win1: the next 64), with wb <= p < wb + 64, so that most gaps are searched without
   // touching memory.
   uint64_t wb = 0;
-  int64_t win0 = INT64_MAX, win1 = INT64_MAX;
-  if (WINDOW) {
-    win0 = gl < L ? pe[l0 + gl] : INT64_MAX;
-    win1 = GW + gl < L ? pe[l0 + GW + gl] : INT64_MAX;
-  }
+  int64_t win0 = lane < L ? pe[l0 + lane] : INT64_MAX;
+  int64_t win1 = WAVE + lane < L ? pe[l0 + WAVE + lane] : INT64_MAX;
 
-  // The predicted gaps of the next round are read while this round is worked on; without the window the prefix
-  // sum at the head of the queue is read again only when the head has moved.
-  int64_t next_g = gl < n_gaps ? pg[h0 + gl] : 0;
-  int64_t head_pe = (!WINDOW && L > 0) ? pe[l0] : INT64_MAX;
-  for (uint64_t i0 = 0; i0 < n_gaps; i0 += GW) {
-    const uint64_t mine = i0 + gl;
+  // The predicted gaps of the next round are read while this round is worked on.
+  int64_t next_g = lane < n_gaps ? pg[h0 + lane] : 0;
+  for (uint64_t i0 = 0; i0 < n_gaps; i0 += WAVE) {
+    const uint64_t mine = i0 + lane;
     const int64_t my_g = next_g;
-    next_g = mine + GW < n_gaps ? pg[h0 + mine + GW] : 0;
+    next_g = mine + WAVE < n_gaps ? pg[h0 + mine + WAVE] : 0;
     uint32_t my_c = 0;
     int64_t my_f = 0;
-    const uint32_t steps = static_cast<uint32_t>(n_gaps - i0 < GW ? n_gaps - i0 : GW);
+    const uint32_t steps = static_cast<uint32_t>(n_gaps - i0 < WAVE ? n_gaps - i0 : WAVE);
     uint32_t k = 0;
     while (k < steps) {
       // Gaps that the head of the queue does not fit into take nothing and change nothing: every lane tests
-      // its own gap against the head, and the group goes straight to the first gap that takes something.
-      // (with the window the prefix sum at the head comes from the lane that holds entry p: wb <= p < wb + GW)
-      const int64_t head_abs = WINDOW ? group_value<GW>(win0, gbase, static_cast<uint32_t>(p - wb))
-                                      : head_pe;
+      // its own gap against the head, and the wave goes straight to the first gap that takes something.
+      const int64_t head_abs = lane_value(win0, static_cast<uint32_t>(p - wb));
       const int64_t head = p < L ? head_abs - consumed : INT64_MAX;
-      const bool takes = gl >= k && gl < steps && my_g >= min_gap && my_g >= margin && head <= my_g - margin;
-      const uint64_t tb = (ballot(takes) >> gbase) & gmask;
+      const bool takes = lane >= k && lane < steps && my_g >= min_gap && my_g >= margin && head <= my_g - margin;
+      const uint64_t tb = ballot(takes);
       if (tb == 0) break;
       k = static_cast<uint32_t>(__builtin_ctzll(tb));
-      const int64_t G = group_value<GW>(my_g, gbase, k);
+      const int64_t G = lane_value(my_g, k);
       uint32_t c = 0;
       int64_t f = 0;
       if (G >= min_gap && G >= margin && p < L) {
         const int64_t limit = consumed + (G - margin);
         int64_t last_fit = consumed;
         for (;;) {
-          // candidate of this lane: queue entry p + c + gl, which lives in the window at idx
-          int64_t val;
-          if (WINDOW) {
-            const uint32_t idx = static_cast<uint32_t>(p + c - wb) + gl;          // 0 .. 2 * GW - 2
-            const int64_t a0 = static_cast<int64_t>(shfl_u64(static_cast<uint64_t>(win0), gbase + (idx & (GW - 1))));
-            const int64_t a1 = static_cast<int64_t>(shfl_u64(static_cast<uint64_t>(win1), gbase + (idx & (GW - 1))));
-            val = idx < GW ? a0 : a1;    // INT64_MAX beyond the end of the queue
-          } else {
-            const uint64_t j = p + c + gl;
-            val = j < L ? pe[l0 + j] : INT64_MAX;
-          }
-          const bool fits = val <= limit;
-          const uint64_t b = (ballot(fits) >> gbase) & gmask;
-          const uint32_t cnt = (b == gmask) ? GW : static_cast<uint32_t>(__builtin_ctzll(~b));
-          if (cnt > 0) last_fit = group_value<GW>(val, gbase, cnt - 1);
+          // candidate of this lane: queue entry p + c + lane, which lives in the window at idx
+          const uint32_t idx = static_cast<uint32_t>(p + c - wb) + lane;          // 0 .. 126
+          const int64_t a0 = static_cast<int64_t>(shfl_u64(static_cast<uint64_t>(win0), idx & (WAVE - 1)));
+          const int64_t a1 = static_cast<int64_t>(shfl_u64(static_cast<uint64_t>(win1), idx & (WAVE - 1)));
+          const int64_t val = idx < WAVE ? a0 : a1;    // INT64_MAX beyond the end of the queue
+          const uint64_t b = ballot(val <= limit);
+          const uint32_t cnt = b == ~0ull ? WAVE : static_cast<uint32_t>(__builtin_ctzll(~b));
+          if (cnt > 0) last_fit = lane_value(val, cnt - 1);
           c += cnt;
           // keep the window under the search position
-          if (WINDOW && p + c >= wb + GW) {
-            wb += GW;
+          if (p + c >= wb + WAVE) {
+            wb += WAVE;
             win0 = win1;
-            win1 = wb + GW + gl < L ? pe[l0 + wb + GW + gl] : INT64_MAX;
+            win1 = wb + WAVE + lane < L ? pe[l0 + wb + WAVE + lane] : INT64_MAX;
           }
-          if (cnt < GW) break;
+          if (cnt < WAVE) break;
         }
         f = last_fit - consumed;
         consumed = last_fit;
         p += c;
-        if (!WINDOW && c > 0) head_pe = p < L ? pe[l0 + p] : INT64_MAX;
         if (p == L && c > 0 && !done) {
           completion = open[h0 + i0 + k] + f;
           done = true;
         }
       }
-      if (gl == k) { my_c = c; my_f = f; }
+      if (lane == k) { my_c = c; my_f = f; }
       ++k;
     }
     if (mine < n_gaps) {
@@ -324,7 +295,7 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
     const int64_t rest = L > 0 ? pe[l0 + L - 1] - consumed : 0;
     completion = t_end + rest;
   }
-  if (gl == 0) {
+  if (lane == 0) {
     completion_out[s] = completion;
     placed_out[s] = p;
   }
@@ -353,8 +324,9 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 
 constexpr uint32_t WIDE32 = 0xffffffffu;   // 32-bit predictions must be below this
 
-// Predicted values of every launch of the tasks that take part, in 32 bits:
-//   lp_e[i]  execution time, for tasks used as low-priority queue; lp_total[t] their sum
+// Predicted values of every launch of the tasks that take part, in 32 bits (gridDim.y workgroups per task, each a
+// part of its launches: with few tasks one workgroup per task leaves most of the chip idle; see predict_parts):
+//   lp_e[i]  execution time, for tasks used as low-priority queue; lp_total[t] their sum (zero at the start)
 //   hp_eg[i] (execution time, idle time), for tasks used as high-priority trace
 // For the replay against actual idle times (actual != nullptr) the first word of hp_eg[i] holds the idle
 // time that really followed launch i instead (clamped to WIDE32, which no filled time can reach).
@@ -362,19 +334,18 @@ constexpr uint32_t WIDE32 = 0xffffffffu;   // 32-bit predictions must be below t
 __global__ void __launch_bounds__(PRED_THREADS)
 k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, uint32_t n_tasks,
                const fikit_row* __restrict__ rows, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role,
-               const uint32_t* __restrict__ lists, const int64_t* __restrict__ actual, uint32_t* __restrict__ lp_e,
-               uint2* __restrict__ hp_eg, uint64_t* __restrict__ lp_total, uint32_t predictor,
-               const uint32_t* __restrict__ pred_done, Ctrl* ctrl) {
+               const int64_t* __restrict__ actual, uint32_t* __restrict__ lp_e, uint2* __restrict__ hp_eg,
+               uint64_t* __restrict__ lp_total, uint32_t predictor, const uint32_t* __restrict__ pred_done, Ctrl* ctrl) {
   __shared__ PredTable tb;
   __shared__ uint64_t wave_tot[PRED_THREADS / WAVE];
   if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
-  const uint32_t n_short = ctrl->n_class[0], n_longer = ctrl->n_class[1];   // final: set by an earlier kernel
-  if (blockIdx.x >= n_short + n_longer) return;
-  const uint32_t t = blockIdx.x < n_short ? lists[blockIdx.x] : lists[static_cast<uint64_t>(n_tasks) + (blockIdx.x - n_short)];
+  const uint32_t t = blockIdx.x;
+  const uint64_t part0 = static_cast<uint64_t>(blockIdx.y) * (2 * PRED_THREADS);   // first launch of this workgroup's part
   const uint32_t rl = role[t];
   if (rl == 0) return;
   if (pred_done && pred_done[t]) return;   // (the profile kernels wrote this task's predictions already)
   const uint64_t base = off[t], len = off[t + 1] - base;
+  if (part0 >= len) return;
   const uint64_t r0 = row_off[t], nr = row_off[t + 1] - r0;
   const uint32_t tid = threadIdx.x;
   const bool in_lds = nr <= PRED_ROWS && (nr == 0 || rows[r0 + nr - 1].kernel_id != ~0ull);
@@ -399,7 +370,7 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
   uint64_t total = 0;
   const bool even = ((base & 1) == 0);   // 16-byte accesses to the workspace arrays need an even first index
   const bool ids_vec = (reinterpret_cast<uintptr_t>(ids + base) & 15) == 0;   // and those to the caller's IDs an aligned address
-  for (uint64_t i0 = 2 * static_cast<uint64_t>(tid); i0 < len; i0 += 2 * PRED_THREADS) {
+  for (uint64_t i0 = part0 + 2 * static_cast<uint64_t>(tid); i0 < len; i0 += static_cast<uint64_t>(gridDim.y) * (2 * PRED_THREADS)) {
     uint64_t id0 = 0, id1 = 0;
     const bool two = i0 + 1 < len;
     if (ids_vec && two) {
@@ -439,7 +410,7 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
   if (tid == 0) {
     uint64_t sum = 0;
     for (int w = 0; w < PRED_THREADS / WAVE; ++w) sum += wave_tot[w];
-    lp_total[t] = sum;
+    if (rl & ROLE_LP) atomicAdd(reinterpret_cast<unsigned long long*>(&lp_total[t]), static_cast<unsigned long long>(sum));
   }
   if (unknown) atomicOr(&ctrl->status, ERR_UNKNOWN_ID);
   if (bad_actual) atomicOr(&ctrl->status, ERR_ACTUAL_GAP);
@@ -488,6 +459,219 @@ k_gf_replay_wide(const uint64_t* __restrict__ off, const uint32_t* __restrict__ 
   placed_out[s] = p;
 }
 
+// MODE 0: the plan on predictions (fill counts, filled time, completion time of the low-priority task).
+// MODE 1 / 2: the same decisions replayed against the idle times that occurred, without / with real-time
+// feedback (the runtime-feedback paragraph of the paper's scheduling section): the first word of a
+// high-priority entry is then the actual idle time; with feedback nothing more is issued into a gap once
+// the time filled has reached it; what runs past it delays the high-priority task, and the sum of these
+// delays is written in place of the completion time.
+enum : int { LW_PLAN = 0, LW_REPLAY = 1, LW_REPLAY_FEEDBACK = 2 };
+
+// ---------------------------------------------------------------------------------------------
+// One wave per scenario, on the same 32-bit predictions.
+//
+// What a gap takes depends on where the queue stands after the gap before it: a scenario is one chain of dependent
+// decisions, and with few scenarios the length of one link decides.  Here a link never leaves the registers.  The
+// wave's lanes hold 63 consecutive entries of the queue as running sums from the window's start (win) and 64
+// consecutive gaps (b1: one more than what may be filled, 0 for a gap that is skipped).  The position o in the window
+// and the consumed time C are scalars.  "How far does the queue get in this gap" is one comparison of all lanes with
+// C + b1 and a population count: entries already consumed compare true as well, so the count is the new position
+// itself.  "Which gap takes something next" is one comparison of all lanes' C + b1 with the head's running sum: gaps
+// that take nothing cost nothing.  The next entries of the queue and the next gaps are read ahead into registers.
+//
+// Running sums saturate at 2^32 - 1, which compares as "does not fit" (C + b1 saturates there too).  The lane behind
+// the window holds that value, and so do entries behind the queue's end: a walk that stops at it has to look closer,
+// at any other value it is done.  If the sums themselves passed 32 bits, the window is reloaded at the head, where
+// C = 0 and everything that can fit is exact.
+//
+// What bounds it: with few scenarios the chain of one gap (about 25 instructions, 120 cycles), with many the issue of
+// scalar instructions (the gap's fourteen scalar instructions go through one port per SIMD).  64 scenarios of 1500 gaps:
+// 0.06 ms (the 64-bit kernel below, which passes 64-bit sums through the LDS crossbar: 0.23 ms); 256 scenarios of 65,535
+// gaps of which few take anything: 0.5 ms (1.8 ms); 16,384 scenarios of 4095 gaps: 1.55 ms (one lane each: 3.2 ms).
+constexpr int WW_THREADS = 256;
+constexpr uint32_t WW_WIN = WAVE - 1;
+constexpr int WW_BLOCKS = 4;   // blocks of 64 gaps per round (their reads are one round ahead)
+
+__device__ __forceinline__ uint32_t wave_incl_scan_sat_u32(uint32_t v) {
+  v = __builtin_elementwise_add_sat(v, dpp_or_zero<0x111, 0xf>(v));   // (see wave_incl_scan_u32)
+  v = __builtin_elementwise_add_sat(v, dpp_or_zero<0x112, 0xf>(v));
+  v = __builtin_elementwise_add_sat(v, dpp_or_zero<0x114, 0xf>(v));
+  v = __builtin_elementwise_add_sat(v, dpp_or_zero<0x118, 0xf>(v));
+  v = __builtin_elementwise_add_sat(v, dpp_or_zero<0x142, 0xa>(v));
+  v = __builtin_elementwise_add_sat(v, dpp_or_zero<0x143, 0xc>(v));
+  return v;
+}
+
+__device__ __forceinline__ uint32_t read_lane_u32(uint32_t v, uint32_t src) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(src)));
+}
+__device__ int llvm_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint32_t write_lane_u32(uint32_t v, uint32_t value, uint32_t dst) {   // v with lane dst replaced
+  return static_cast<uint32_t>(llvm_writelane(static_cast<int>(value), static_cast<int>(dst), static_cast<int>(v)));
+}
+__device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t sat32(uint64_t v) { return v > WIDE32 ? WIDE32 : static_cast<uint32_t>(v); }
+__device__ __forceinline__ uint32_t popc64(uint64_t m) { return static_cast<uint32_t>(__popcll(m)); }
+
+// (completion_out receives the delay in the replay modes).
+template <int MODE>
+__global__ void __launch_bounds__(WW_THREADS)
+k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
+               uint64_t n_scen, const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e,
+               const uint2* __restrict__ hp_eg, const uint64_t* __restrict__ lp_total, int64_t margin, int64_t min_gap,
+               uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
+               uint64_t* __restrict__ placed_out, const Ctrl* ctrl) {
+  if (ctrl->status || ctrl->wide) return;
+  const uint32_t lane = lane_id();
+  // (everything that is the same in the whole wave is kept in scalar registers: the scenario number has to be seen as one)
+  const uint32_t s = static_cast<uint32_t>(
+      __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (WW_THREADS / WAVE) + threadIdx.x / WAVE)));
+  if (s >= n_scen) return;
+  const uint32_t hp = hp_task[s], lp = lp_task[s];
+  const uint32_t h0 = static_cast<uint32_t>(off[hp]), H = static_cast<uint32_t>(off[hp + 1]) - h0;
+  const uint32_t l0 = static_cast<uint32_t>(off[lp]), L = static_cast<uint32_t>(off[lp + 1]) - l0;
+  const uint64_t g0 = gap_off[s];
+  const uint32_t n_gaps = H > 0 ? H - 1 : 0;
+  const uint32_t* __restrict__ queue = lp_e + l0;
+  const uint2* __restrict__ trace = hp_eg + h0;
+  const int64_t floor64 = min_gap > margin ? min_gap : margin;   // (32-bit idle times are below WIDE32)
+  const uint32_t gap_floor = floor64 >= static_cast<int64_t>(WIDE32) ? WIDE32 : static_cast<uint32_t>(floor64);
+  const uint32_t margin32 = margin >= static_cast<int64_t>(WIDE32) ? WIDE32 : static_cast<uint32_t>(margin);
+
+  uint32_t wb = 0, o = 0, C = 0, sum = 0;    // window start, position in it, time consumed since its start, running sum of the head
+  uint32_t win = 0, r1 = 0, r2 = 0, r3 = 0;  // running sums of the window; the entries of the three windows after it
+  // (behind the end: saturates, never fits; read without a branch, so that the walk's loop stays free of divergent ones)
+  auto entry = [&](uint32_t j) -> uint32_t {
+    const uint32_t v = queue[j < L ? j : L - 1];
+    return j < L ? v : WIDE32;
+  };
+  auto set_window = [&](uint32_t r) { win = wave_incl_scan_sat_u32(lane == WW_WIN ? WIDE32 : r); };
+  auto load_window = [&](uint32_t at) {
+    wb = at; o = 0; C = 0;
+    const uint32_t r0 = entry(at + lane);
+    r1 = entry(at + WW_WIN + lane); r2 = entry(at + 2 * WW_WIN + lane); r3 = entry(at + 3 * WW_WIN + lane);
+    set_window(r0);
+  };
+  bool done = L == 0;    // the whole queue has been issued
+  uint32_t f_last = 0;   // time filled in the gap that took the last of it
+  if (!done) { load_window(0); sum = read_lane_u32(win, 0); }
+
+  uint64_t time_line = 0, consumed = 0, delay = 0;   // (per lane; summed over the lanes at the end)
+  // (launches are read without a branch too, so that what is in flight can be counted: the lane behind the trace's end
+  // reads its last launch again, and nothing of it is used)
+  uint2 ahead[WW_BLOCKS];
+#pragma unroll
+  for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(64 * j + lane, H - 1)] : make_uint2(0, 0);
+  uint32_t i0 = 0;
+  for (; i0 < H && !done; i0 += 64 * WW_BLOCKS) {
+    uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
+#pragma unroll
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+      E[j] = ahead[j].x; G[j] = ahead[j].y;
+      b1[j] = (i0 + 64 * j + lane < n_gaps && G[j] >= gap_floor) ? G[j] - margin32 + 1 : 0u;
+      if (MODE == LW_REPLAY_FEEDBACK) b1[j] = E[j] == 0 ? 0u : b1[j];   // (the next request is there at once: nothing is issued)
+      asm volatile("" : "+v"(E[j]), "+v"(G[j]), "+v"(b1[j]));           // (waited for here, before the next round's reads go out)
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
+#pragma unroll
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+      const uint32_t i = i0 + 64 * j + lane;
+      const bool has_gap = i < n_gaps;
+      uint32_t my_c = 0, my_f = 0;
+      if (!done) {
+        uint64_t todo = ~0ull, takes;
+        uint32_t k = 0, o2;
+        for (;;) {
+          // the common case: the gap ends inside the window, at an entry whose running sum is exact
+          for (;;) {
+            const uint32_t lim = __builtin_elementwise_add_sat(b1[j], C);
+            takes = ballot(lim > sum) & todo;
+            if (takes == 0) break;
+            k = static_cast<uint32_t>(__builtin_ctzll(takes));
+            todo = (~1ull) << k;
+            // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
+            // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
+            // the entries that end before that.
+            const uint32_t limit = read_lane_u32(lim, k);
+            o2 = popc64(ballot(win < limit));
+            if (MODE == LW_REPLAY_FEEDBACK) {
+              const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
+              const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
+              o2 = o3 < o2 ? o3 : o2;
+            }
+            const uint32_t C2 = read_lane_u32(win, o2 - 1), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
+            if (sum2 == WIDE32) break;
+            my_c = write_lane_u32(my_c, o2 - o, k);
+            my_f = write_lane_u32(my_f, C2 - C, k);
+            o = o2; C = C2; sum = sum2;
+          }
+          if (takes == 0) break;
+          // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
+          uint32_t left = read_lane_u32(b1[j], k), c = 0, f = 0;
+          const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
+          for (;;) {
+            if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
+            o2 = popc64(ballot(win < C + left));
+            bool stop = false;
+            if (MODE == LW_REPLAY_FEEDBACK) {
+              const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
+              stop = o3 <= o2;
+              o2 = stop ? o3 : o2;
+            }
+            const uint32_t C3 = o2 ? read_lane_u32(win, o2 - 1) : 0u;
+            c += o2 - o; f += C3 - C; left -= C3 - C;
+            o = o2; C = C3;
+            if (wb + o >= L) { done = true; break; }
+            bool again = false;
+            if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
+              wb += WW_WIN; o = 0; C = 0;
+              set_window(r1);
+              r1 = r2; r2 = r3; r3 = entry(wb + 3 * WW_WIN + lane);
+              again = !stop;
+            }
+            sum = read_lane_u32(win, o);
+            if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
+            if (!again) break;
+          }
+          my_c = write_lane_u32(my_c, c, k);
+          my_f = write_lane_u32(my_f, f, k);
+          if (done) { f_last = f; break; }
+        }
+        if (MODE == LW_PLAN) {
+          consumed += my_f;
+          // predicted time line: all launches of the block and the idle times after them, or, if the queue ran empty in
+          // gap k, up to the launch before it
+          const bool ran = !done || lane <= k, idled = !done || lane < k;
+          time_line += (i < H && ran ? static_cast<uint64_t>(E[j]) : 0ull) + (has_gap && idled ? static_cast<uint64_t>(G[j]) : 0ull);
+        } else {
+          delay += my_f > E[j] ? my_f - E[j] : 0u;
+        }
+      }
+      if (has_gap) {
+        fill_count[g0 + i] = my_c;
+        filled_ns[g0 + i] = static_cast<int64_t>(my_f);
+      }
+    }
+  }
+  for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queue ran empty)
+    fill_count[g0 + i] = 0;
+    filled_ns[g0 + i] = 0;
+  }
+  int64_t result;
+  if (MODE == LW_PLAN) {
+    const uint64_t line = wave_sum_u64(time_line), used = wave_sum_u64(consumed);
+    result = static_cast<int64_t>(done ? line + f_last : line + (lp_total[lp] - used));
+  } else {
+    result = static_cast<int64_t>(wave_sum_u64(delay));
+  }
+  if (lane == 0) {
+    completion_out[s] = result;
+    placed_out[s] = wb + o;
+  }
+}
+
 constexpr int LW_THREADS = 256;
 constexpr uint32_t LW_OPENS = 4, LW_TRIES = 4;     // per period (between two rounds of stream reads / result writes):
                                                    // gaps opened, and queue entries tried per gap opened
@@ -516,14 +700,6 @@ __device__ __forceinline__ void lw_store_scalar(const LaneWalkSmem& sm, uint32_t
     filled_ns[at] = static_cast<int64_t>(sm.out_f[at & (LW_OUT_CAP - 1)][tid]);
   }
 }
-
-// MODE 0: the plan on predictions (fill counts, filled time, completion time of the low-priority task).
-// MODE 1 / 2: the same decisions replayed against the idle times that occurred, without / with real-time
-// feedback (the runtime-feedback paragraph of the paper's scheduling section): the first word of a
-// high-priority entry is then the actual idle time; with feedback nothing more is issued into a gap once
-// the time filled has reached it; what runs past it delays the high-priority task, and the sum of these
-// delays is written in place of the completion time.
-enum : int { LW_PLAN = 0, LW_REPLAY = 1, LW_REPLAY_FEEDBACK = 2 };
 
 template <int MODE>
 __global__ void __launch_bounds__(LW_THREADS)

@@ -338,9 +338,8 @@ k_pf_walk_wide(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
                const uint32_t* __restrict__ lp_task, const uint32_t* __restrict__ lp_prio, uint64_t n_scen,
                const uint64_t* __restrict__ gap_off, const int64_t* __restrict__ pe, const int64_t* __restrict__ pg,
                int64_t margin, int64_t min_gap, uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns,
-               uint64_t* __restrict__ placed, int64_t* __restrict__ placed_ns, uint32_t only_if_wide, const Ctrl* ctrl) {
-  if (ctrl->status) return;
-  if (only_if_wide && !ctrl->wide) return;
+               uint64_t* __restrict__ placed, int64_t* __restrict__ placed_ns, const Ctrl* ctrl) {
+  if (ctrl->status || !ctrl->wide) return;
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (s >= n_scen) return;
   const uint32_t hp = hp_task[s];

@@ -1,0 +1,48 @@
+"""The walk of the gap fill and of the replay where its windows begin and end: queues and traces one launch shorter and longer
+than a window, gaps that take several windows, and running sums of the queue that pass 32 bits, against the CPU oracle."""
+import numpy as np
+import pytest
+
+from paper_2311_10359_amd import traces
+from parity_util import check_gapfill, check_profile
+from test_gpu_parity import all_pairs
+from test_gpu_replay import check_measure, check_replay
+
+pytestmark = pytest.mark.gpu
+
+
+def trace_of(seed, lens, exec_choices, gap_choices):
+    """Tasks whose Kernel IDs have one duration and one idle time each (so the predictions are these values)."""
+    rng = np.random.default_rng(seed)
+    total = int(sum(lens))
+    rec = np.zeros(total, dtype=traces.LAUNCH_DTYPE)
+    kid = rng.integers(0, 8, total)
+    rec["name_id"] = kid
+    rec["grid"], rec["block"] = 1, 64
+    ex = np.asarray(rng.choice(exec_choices, 8), dtype=np.int64)[kid]
+    gp = np.asarray(rng.choice(gap_choices, 8), dtype=np.int64)[kid]
+    rec["start_ns"] = np.cumsum(ex + gp) - (ex + gp)
+    rec["end_ns"] = rec["start_ns"] + ex
+    off = np.zeros(len(lens) + 1, dtype=np.uint64)
+    np.cumsum(lens, out=off[1:])
+    return rec, off
+
+
+@pytest.mark.parametrize("exec_choices,gap_choices", [
+    ([100, 250], [0, 90, 400, 900]),                            # a few kernels per gap
+    ([1], [0, 62, 63, 64, 200]),                                # whole windows per gap
+    ([0, 1, 7], [0, 3, 40]),                                    # kernels without duration
+    ([1 << 31, (1 << 32) - 2, 5], [0, 9, 1 << 31, (1 << 32) - 2]),   # running sums past 32 bits
+    ([1 << 26, 3 << 25, 1], [1 << 27, 1 << 30, 2]),             # ... after many launches
+])
+@pytest.mark.parametrize("copies", [1, 3])                      # 676 scenarios; 6084 in the second form
+def test_walk_edges(exec_choices, gap_choices, copies):
+    lens = [1, 2, 3, 8, 15, 16, 17, 31, 32, 33, 61, 62, 63, 64, 65, 125, 126, 127, 128, 129, 189, 190, 255, 256, 257, 700] * copies
+    rec, off = trace_of(copies + len(gap_choices), lens, exec_choices, gap_choices)
+    prof, d_off, o_prof = check_profile(rec, off)
+    hp, lp = all_pairs(range(len(lens)))
+    for margin, min_gap in ((0, 0), (3, 50)):
+        print(f"{hp.size} scenarios, durations {exec_choices}, margin {margin}", flush=True)
+        check_gapfill(prof, d_off, off, o_prof, hp, lp, margin, min_gap)
+    d_gap, gap = check_measure(rec, off)
+    check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 3, 0)
