@@ -41,10 +41,12 @@ struct Ctrl {
   uint64_t n_general;     // tasks that take the general sort-based path
   uint64_t n_long;        // tasks too long for the one-workgroup path
   uint64_t n_heads;       // rows found by the general path
-  uint32_t n_class[4];    // length of the work lists (small, mid, medium tasks or units); [3]: priority queues, the
-                          // largest number of low-priority tasks of a scenario
+  uint32_t n_class[6];    // length of the work lists: small, mid, medium tasks or units, and units that are streamed (huge from
+                          // the list's front, others from its back); priority queues: [3] holds the largest number of
+                          // low-priority tasks of a scenario
+  uint32_t reserved[2];
 };
-static_assert(sizeof(Ctrl) == 64, "control block is 64 bytes");
+static_assert(sizeof(Ctrl) == 80, "control block");
 
 __device__ __forceinline__ uint32_t lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 

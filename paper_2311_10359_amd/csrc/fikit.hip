@@ -13,6 +13,7 @@
 #include "stats_kernels.hip.h"
 #include "task_kernels.hip.h"
 #include "msd_kernels.hip.h"
+#include "stream_kernels.hip.h"
 #include "prio_kernels.hip.h"
 #include "pairing_kernels.hip.h"
 #include "merge_kernels.hip.h"
@@ -95,7 +96,7 @@ ProfileLayout profile_layout(uint64_t n, uint32_t n_tasks) {
   L.units = c.take(L.max_units * 4 * 6);   // start, length, task, row count, first row, buckets
   {
     const uint64_t longest_list = L.max_units > n_tasks ? L.max_units : n_tasks;
-    L.lists = c.take(longest_list * 4 * 3);
+    L.lists = c.take(longest_list * 4 * 4);
   }
   L.total = c.at;
   return L;
@@ -369,13 +370,24 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     hipLaunchKernelGGL(k_tile_partition, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(PT_THREADS), sizeof(PartSmem), st, d_records,
                        d_task_offsets, n_tasks, mtiles, is_long, ids, k1, part_kg, bound, bucket_size, wflag, ctrl);
     tr.mark("k_msd_units");
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->n_class[0], static_cast<uint64_t>(4), 0u);   // the lists are reused for units
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->n_class[0], static_cast<uint64_t>(6), 0u);   // the lists are reused for units
     hipLaunchKernelGGL(k_msd_units, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, d_task_offsets, n_tasks, is_long, mtiles, bucket_size, wflag,
                        ustart, ulen, utask, udcount, ubuckets, mflag, gflag, lists, static_cast<uint32_t>(n_units), ctrl);
     FusedArgs ua = fa;
     ua.pred_role = nullptr;   // (units are parts of tasks: their task's predictions are left to the gap fill)
     ua.ustart = ustart; ua.ulen = ulen; ua.utask = utask; ua.ubuckets = ubuckets; ua.tile_prefix = mtiles; ua.bound = bound;
     ua.tile_len = PT_TILE; ua.part_id = k1; ua.part_kg = part_kg; ua.mflag = mflag; ua.dcount = udcount;
+    // (first, because its largest units take longest; a unit has more than FUSE_MAX launches, or is one of the
+    // MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
+    tr.mark("k_unit_stream");
+    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  static_cast<int>(sizeof(StreamSmem))));
+    const uint64_t stream_most = n / (FUSE_MAX + 1) + n / (static_cast<uint64_t>(UNIT_RUNS_MAX) * PT_TILE) * MSD_SLOTS;
+    if (n >= STREAM_MIN) {
+      ua.list = lists + 3 * n_units; ua.count = &ctrl->n_class[3];
+      hipLaunchKernelGGL(k_unit_stream, dim3(static_cast<uint32_t>(stream_most < n_units ? stream_most : n_units)), dim3(SU_THREADS),
+                         sizeof(StreamSmem), st, ua, static_cast<uint32_t>(n_units), reinterpret_cast<uint2*>(e0), g0);
+    }
     tr.mark("k_unit_fused_small");
     ua.list = lists; ua.count = &ctrl->n_class[0]; ua.max_len = FUSE_SMALL_MAX;
     hipLaunchKernelGGL(small_u, dim3(static_cast<uint32_t>(n_units)), dim3(FUSE_S_THREADS), small_lds, st, ua);

@@ -24,22 +24,20 @@
 
 namespace fikit {
 
-constexpr uint32_t MSD_MAX_BITS = 8;
-constexpr uint32_t MSD_SLOTS = 1u << MSD_MAX_BITS;   // unit slots reserved per long task
+// Top ID bits that name a launch's bucket.  All tasks use as many: neighbouring buckets are packed into one unit anyway, and
+// the finer the buckets, the fewer IDs share one with a frequent ID (k_unit_stream).
+constexpr uint32_t MSD_BITS = 8;
+constexpr uint32_t MSD_SLOTS = 1u << MSD_BITS;       // buckets, and unit slots reserved per long task
 constexpr uint32_t PT_TILE = 4096;                   // launches per tile of the partition pass
 constexpr int PT_THREADS = 512, PT_WAVES = PT_THREADS / WAVE, PT_KPT = PT_TILE / PT_THREADS;
 constexpr int PT_LB = 2;                             // rounds of record loads in flight per lane
+// A bucket of more than FUSE_MAX launches (one frequent ID) is streamed by k_unit_stream if its task has at least this
+// many launches; otherwise the task is sorted.
+constexpr uint64_t STREAM_MIN = 1u << 18;
+constexpr uint32_t STREAM_HUGE = 1u << 16;           // streamed units beyond this are started first
 constexpr uint32_t PT_ROWS = MSD_SLOTS + 1;          // rows of a task's boundary table: bucket 0 .. 256 (= the tile's end)
 static_assert(PT_TILE <= 0xffffu, "bucket boundaries inside a tile are stored in 16 bits");
 static_assert(MSD_SLOTS * FUSE_MAX / PT_TILE <= UNIT_RUNS_MAX, "a unit's run table holds one run per tile of its task");
-
-// Top ID bits used to partition a task of m launches: buckets of about FUSE_SMALL_MAX launches.
-__host__ __device__ inline uint32_t msd_bits(uint64_t m) {
-  const uint64_t want = (m + FUSE_SMALL_MAX - 1) / FUSE_SMALL_MAX;
-  uint32_t b = 1;
-  while ((1ull << b) < want && b < MSD_MAX_BITS) ++b;
-  return b;
-}
 
 // is_long[t] = 1 for tasks that take this path, mtiles[t] = their number of tiles; both arrays have
 // n_tasks + 1 entries (last 0) and are turned into prefix sums by the caller.
@@ -55,25 +53,6 @@ __global__ void k_plan_msd(const uint64_t* __restrict__ off, uint32_t n_tasks, c
   }
   is_long[t] = l;
   mtiles[t] = tiles;
-}
-
-// Rank of this lane's key among the keys with the same `bits`-bit digit that the wave has seen so far (as
-// wave_rank_digit, for digits narrower than eight bits).
-__device__ __forceinline__ uint32_t wave_rank_bits(uint32_t digit, bool valid, uint32_t* cnt_w, uint32_t bits) {
-  uint64_t same = ballot(valid);
-  for (uint32_t b = 0; b < bits; ++b) {
-    const bool bit = (digit >> b) & 1u;
-    const uint64_t bal = ballot(bit);
-    same &= bit ? bal : ~bal;
-  }
-  uint32_t rank = 0;
-  if (valid) {
-    const uint32_t before = cnt_w[digit];
-    rank = before + popc_below(same);
-    if ((same >> lane_id()) == 1ull) cnt_w[digit] = before + static_cast<uint32_t>(__popcll(same));
-  }
-  __builtin_amdgcn_wave_barrier();
-  return rank;
 }
 
 struct PartSmem {
@@ -102,8 +81,7 @@ k_tile_partition(const fikit_launch* __restrict__ rec, const uint64_t* __restric
   const uint64_t task_start = off[t], task_end = off[t + 1];
   const uint64_t start = task_start + static_cast<uint64_t>(jl) * PT_TILE;
   const uint32_t m = static_cast<uint32_t>(task_end - start < PT_TILE ? task_end - start : PT_TILE);
-  const uint32_t bits = msd_bits(task_end - task_start);
-  const int shift = 64 - static_cast<int>(bits);
+  constexpr int shift = 64 - static_cast<int>(MSD_BITS);
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
   for (uint32_t d = lane; d < 256; d += WAVE) sm.cnt[w][d] = 0;
   __builtin_amdgcn_wave_barrier();
@@ -170,10 +148,10 @@ k_tile_partition(const fikit_launch* __restrict__ rec, const uint64_t* __restric
 #pragma unroll
   for (int r = 0; r < PT_KPT; ++r) {
     const uint32_t pos = wave_base + r * WAVE + lane;
-    rk[r] = wave_rank_bits(static_cast<uint32_t>(idr[r] >> shift), pos < m, sm.cnt[w], bits);
+    rk[r] = wave_rank_digit(static_cast<uint32_t>(idr[r] >> shift), pos < m, sm.cnt[w]);
   }
   tile_digit_offsets<PT_WAVES>(sm.cnt, sm.aux, nullptr);
-  // where each bucket starts inside the tile (buckets the task does not have start at the tile's end), and the
+  // where each bucket starts inside the tile, and the
   // tile's share of the task's bucket sizes (integer adds: the totals do not depend on the order of the tiles)
   if (tid < 256) {
     const uint32_t first = sm.cnt[0][tid], next = tid < 255 ? sm.cnt[0][tid + 1] : m;
@@ -211,9 +189,9 @@ k_tile_partition(const fikit_launch* __restrict__ rec, const uint64_t* __restric
   }
 }
 
-// One workgroup per task: packs a long task's ID buckets into units.  A task with a bucket of more than
-// FUSE_MAX launches, or with an execution or idle time that does not fit 32 bits, keeps the general path
-// (mflag 0); otherwise mflag 1 and gflag cleared.  Thread d sums bucket d over the task's tiles, one thread
+// One workgroup per task: packs a long task's ID buckets into units (a bucket of more than FUSE_MAX launches is a
+// unit of its own).  A task with such a bucket and fewer than STREAM_MIN launches, or with an execution or idle time
+// that does not fit 32 bits, keeps the general path (mflag 0); otherwise mflag 1 and gflag cleared.  Thread d sums bucket d over the task's tiles, one thread
 // packs (a short sequential pass over at most 256 buckets in LDS), and all threads together write the unit
 // slots and the work lists.  bucket_size: the task's bucket sizes as the tiles added them up.
 __global__ void __launch_bounds__(MSD_SLOTS)
@@ -232,9 +210,9 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
   if (long_prefix[t + 1] == long_prefix[t]) return;   // not a long task
   const uint32_t o = long_prefix[t];
   const uint64_t task_start = off[t], len = off[t + 1] - task_start;
-  const uint32_t nb = 1u << msd_bits(len);
+  constexpr uint32_t nb = MSD_SLOTS;
   const uint32_t tiles_t = tile_prefix[t + 1] - tile_prefix[t];
-  const uint32_t size = d < nb ? bucket_size[static_cast<uint64_t>(o) * MSD_SLOTS + d] : 0u;
+  const uint32_t size = bucket_size[static_cast<uint64_t>(o) * MSD_SLOTS + d];
   uint32_t total;
   const uint32_t before = block_excl_scan_256(size, aux, total);
   bstart[d] = before;
@@ -242,12 +220,14 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
   __syncthreads();
   if (d == 0) {
     uint32_t u = 0;
-    bool ok = total == len && tiles_t <= UNIT_RUNS_MAX && wflag[t] == 0;
+    const bool may_stream = len >= STREAM_MIN;
+    const bool single = tiles_t > UNIT_RUNS_MAX;   // more runs than a unit's table holds: every bucket is streamed
+    bool ok = total == len && (!single || may_stream) && wflag[t] == 0;
     uint32_t cur_first = 0, cur_len = 0;
     for (uint32_t k = 0; k < nb; ++k) {
       const uint32_t sz = bstart[k + 1] - bstart[k];
-      if (sz > FUSE_MAX) ok = false;
-      if (cur_len > 0 && cur_len + sz > FUSE_MID_MAX) {
+      if (sz > FUSE_MAX && !may_stream) ok = false;
+      if (cur_len > 0 && (cur_len + sz > FUSE_MID_MAX || single)) {
         us[u] = bstart[cur_first]; ul[u] = cur_len; ub[u] = cur_first | (k << 16);
         ++u;
         cur_first = k;
@@ -277,15 +257,17 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
   ubuckets[u] = live ? ub[d] : 0u;
   // work lists of units by size class (see k_classify): one reservation per task and class (a counter that every
   // unit bumped on its own would serialise the whole launch on one address)
-  const uint32_t c = !live ? 3u : (l <= FUSE_SMALL_MAX ? 0u : (l <= FUSE_MID_MAX ? 1u : 2u));
+  // (list 3: streamed units, huge ones from its front and the others from its back)
+  const bool streamed = live && (l > FUSE_MAX || tiles_t > UNIT_RUNS_MAX);
+  const uint32_t c = !live ? 5u : streamed ? (l > STREAM_HUGE ? 3u : 4u) : (l <= FUSE_SMALL_MAX ? 0u : (l <= FUSE_MID_MAX ? 1u : 2u));
   __syncthreads();   // (aux is reused)
-  for (uint32_t k = 0; k < 3; ++k) {
+  for (uint32_t k = 0; k < 5; ++k) {
     uint32_t total;
     const uint32_t at = block_excl_scan_256(c == k ? 1u : 0u, aux, total);
     __shared__ uint32_t list_base;
     if (d == 0) list_base = total ? atomicAdd(&ctrl->n_class[k], total) : 0u;
     __syncthreads();
-    if (c == k) lists[static_cast<uint64_t>(k) * list_stride + list_base + at] = u;
+    if (c == k) lists[k < 4 ? static_cast<uint64_t>(k) * list_stride + list_base + at : 4ull * list_stride - 1 - (list_base + at)] = u;
     __syncthreads();
   }
 }

@@ -1,0 +1,369 @@
+// Units too large for a workgroup's registers: an ID bucket of a long task that a few frequent Kernel IDs fill with more
+// launches than k_task_fused holds (skewed traces: some kernel is launched over and over).  One workgroup streams the
+// bucket's launches as often as it needs; nothing is sorted.
+//
+//   1. The bucket's runs (one per tile) are read once: IDs are found in an LDS table, count / sum / min / max per ID (Section
+//      3.2: sum / count = SK_j, SG_j) are gathered, and the launches are written back packed: (execution time, idle time) and
+//      the ID's table slot, 10 bytes each.
+//   2. Nearest-rank p50 / p95 (statistics of the same samples): a histogram per (ID, array) over the ID's own value range, on
+//      the scale of k_task_fused, gives the bin of each wanted rank; the samples of that bin only are counted again by their
+//      offset in the bin, finer and finer until a bin is one value wide.  Two passes over the packed launches as a rule.
+//
+// What bounds it: a compute unit's share of memory (the largest bucket is one workgroup's), and in the first pass the
+// same-address LDS atomics that one frequent ID causes: every wave therefore keeps the sums of the ID it meets most in
+// registers.
+#pragma once
+
+#include "common.hip.h"
+#include "task_kernels.hip.h"
+
+namespace fikit {
+
+constexpr int SU_THREADS = 1024, SU_WAVES = SU_THREADS / WAVE;
+constexpr uint32_t SU_DMAX = 256, SU_HT = 2 * SU_DMAX;   // IDs of a bucket, slots of its ID table
+constexpr uint32_t SU_HIST = 24576;                      // words of the histograms (96 KB of the 160 KB)
+constexpr uint32_t SU_RUNS = 8;                          // runs a wave reads at a time: 16 loads in flight per lane
+constexpr uint32_t SU_KPT = 4;                           // packed launches a lane reads at a time
+constexpr uint32_t SU_BITS_MAX = 11;
+
+struct StreamSmem {
+  uint64_t ht_key[SU_HT], esum[SU_HT], gsum[SU_HT];
+  uint32_t cnt[SU_HT], gcnt[SU_HT], emin[SU_HT], emax[SU_HT], gmin[SU_HT], gmax[SU_HT];
+  uint4 sel[2][SU_HT];          // by array and slot: low end of the ID's window (on the scale), shift | rank << 8, the bins of p50 and p95
+  uint32_t base[4][SU_DMAX];    // by 2 * array + percentile and rank: where the bin searched next begins (a value) ...
+  uint32_t rest[4][SU_DMAX];    // ... the wanted rank among the samples from there on ...
+  uint8_t fine[4][SU_DMAX];     // ... and the shift that cuts it into bins
+  uint16_t slot_of[SU_DMAX];    // rank -> slot
+  uint32_t aux[SU_WAVES];
+  uint32_t ndist, fallback, filled, again;
+  union {
+    uint32_t hist[SU_HIST];
+    struct { uint64_t ckey[SU_DMAX]; uint16_t cslot[SU_DMAX]; } tmp;
+  } u;
+};
+static_assert(sizeof(StreamSmem) <= 160 * 1024, "fits a compute unit's LDS");
+constexpr uint32_t SU_NO_BIN = ~0u;
+
+// log2 of the bins each of n histograms may have.
+__device__ __forceinline__ uint32_t su_bins_log2(uint32_t n) {
+  const uint32_t b = 31u - __builtin_clz(SU_HIST / n);
+  return b < SU_BITS_MAX ? b : SU_BITS_MAX;
+}
+
+// The bin of hist[0 .. bins) that holds the rank k (0-based; the bins' counts sum to more than k), and the rank inside it.  Called by
+// whole waves with the same arguments; the results are in all lanes.
+__device__ __forceinline__ void su_find(const uint32_t* hist, uint32_t bins, uint32_t k, uint32_t& bin, uint32_t& inside) {
+  const uint32_t lane = lane_id();
+  const uint32_t per = bins > WAVE ? bins / WAVE : 1u;   // (bins is a power of two)
+  uint32_t mine = 0;
+  if (lane * per < bins)
+    for (uint32_t b = 0; b < per; ++b) mine += hist[lane * per + b];
+  const uint32_t incl = wave_incl_scan_u32(mine);
+  const uint64_t holds = ballot(k < incl);
+  const int leader = holds ? __builtin_ctzll(holds) : WAVE - 1;
+  uint32_t at = 0, in = 0;
+  if (static_cast<int>(lane) == leader) {
+    uint32_t cum = incl - mine;
+    for (uint32_t b = 0; b < per; ++b) {
+      const uint32_t c = hist[lane * per + b];
+      if (k < cum + c) { at = lane * per + b; in = k - cum; break; }
+      cum += c;
+    }
+  }
+  bin = __shfl(at, leader, WAVE);
+  inside = __shfl(in, leader, WAVE);
+}
+
+// Slot of an ID in the table (entered if it is new), or SU_HT if the table is full.
+__device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
+  uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (SU_HT - 1);
+  if (id == HT_EMPTY) return SU_HT;
+  for (uint32_t probe = 0; probe < SU_HT; ++probe) {
+    const uint64_t k = __hip_atomic_load(&sm.ht_key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (k == id) return h;
+    if (k == HT_EMPTY) {
+      const uint64_t old = atomicCAS(reinterpret_cast<unsigned long long*>(&sm.ht_key[h]), HT_EMPTY, id);
+      if (old == HT_EMPTY) { atomicAdd(&sm.ndist, 1u); return h; }
+      if (old == id) return h;
+    }
+    h = (h + 1) & (SU_HT - 1);
+  }
+  return SU_HT;
+}
+
+// Work list: A.list[0 .. count[0]) from the front (the largest units first), then A.list[list_end - 1 - x] for x < count[1].
+// pack_kg, pack_slot: two 8-byte arrays that only the sort would use.  A unit writes the slices of both that belong to its own
+// launches (ustart, ulen) and nothing else: other tasks may have handed their values over to the sort there already.
+__global__ void __launch_bounds__(SU_THREADS)
+k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_all, int64_t* __restrict__ pack_slot_all) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  StreamSmem& sm = *reinterpret_cast<StreamSmem*>(smem_raw);
+  Ctrl* ctrl = A.ctrl;
+  if (ctrl->status & ERR_OFFSETS) return;
+  const uint32_t front = A.count[0], back = A.count[1];
+  if (blockIdx.x >= front + back) return;
+  const uint32_t unit = blockIdx.x < front ? A.list[blockIdx.x] : A.list[list_end - 1 - (blockIdx.x - front)];
+  const uint32_t m = A.ulen[unit], t = A.utask[unit];
+  const uint64_t base = A.ustart[unit];
+  uint2* __restrict__ pack_kg = pack_kg_all + base;
+  uint16_t* __restrict__ pack_slot = reinterpret_cast<uint16_t*>(pack_slot_all + base);
+  const uint32_t tid = threadIdx.x, lane = lane_id();
+  const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(tid / WAVE)));
+
+  for (uint32_t s = tid; s < SU_HT; s += SU_THREADS) {
+    sm.ht_key[s] = HT_EMPTY; sm.esum[s] = 0; sm.gsum[s] = 0; sm.cnt[s] = 0; sm.gcnt[s] = 0;
+    sm.emin[s] = ~0u; sm.emax[s] = 0; sm.gmin[s] = ~0u; sm.gmax[s] = 0;
+  }
+  if (tid == 0) { sm.ndist = 0; sm.fallback = 0; sm.filled = 0; }
+  __syncthreads();
+
+  // ---- 1. gather the bucket's runs --------------------------------------------------------------------------------
+  {
+    const uint32_t ub = A.ubuckets[unit], d0 = ub & 0xffffu, d1 = ub >> 16;
+    const uint32_t tp = A.tile_prefix[t], tiles_t = A.tile_prefix[t + 1] - tp;
+    const uint32_t task_start = static_cast<uint32_t>(A.off[t]);
+    const uint16_t* b_lo = A.bound + static_cast<uint64_t>(tp) * (256 + 1) + static_cast<uint64_t>(d0) * tiles_t;
+    const uint16_t* b_hi = A.bound + static_cast<uint64_t>(tp) * (256 + 1) + static_cast<uint64_t>(d1) * tiles_t;
+    uint64_t dom_id = HT_EMPTY, dom_es = 0, dom_gs = 0;   // the ID this wave met most at the start, and its sums so far
+    uint32_t dom_slot = SU_HT, dom_c = 0, dom_gc = 0, dom_en = ~0u, dom_ex = 0, dom_gn = ~0u, dom_gx = 0;
+    for (uint32_t j0 = w * SU_RUNS; j0 < tiles_t; j0 += SU_WAVES * SU_RUNS) {
+      if (__hip_atomic_load(&sm.fallback, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
+      uint32_t lo = 0, c = 0;
+      const uint32_t j = j0 + lane;
+      if (lane < SU_RUNS && j < tiles_t) { lo = b_lo[j]; c = static_cast<uint32_t>(b_hi[j]) - lo; }
+      const uint32_t incl = wave_incl_scan_u32(c);   // (lanes from SU_RUNS on add nothing)
+      const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), WAVE - 1));
+      uint32_t place = 0;
+      if (lane == 0) place = atomicAdd(&sm.filled, total);
+      place = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(place)));
+      uint32_t rc[SU_RUNS], rat[SU_RUNS], rto[SU_RUNS], longest = 0;
+#pragma unroll
+      for (uint32_t r = 0; r < SU_RUNS; ++r) {
+        rc[r] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(c), static_cast<int>(r)));
+        rat[r] = task_start + (j0 + r) * A.tile_len + static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), static_cast<int>(r)));
+        rto[r] = place + static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), static_cast<int>(r))) - rc[r];
+        longest = rc[r] > longest ? rc[r] : longest;
+      }
+      for (uint32_t x0 = 0; x0 < longest; x0 += WAVE) {
+        const uint32_t x = x0 + lane;
+        uint64_t id[SU_RUNS];
+        uint2 kg[SU_RUNS];
+#pragma unroll
+        for (uint32_t r = 0; r < SU_RUNS; ++r) {
+          id[r] = HT_EMPTY;
+          kg[r] = make_uint2(0, NONE32);
+          if (x < rc[r]) { id[r] = A.part_id[rat[r] + x]; kg[r] = A.part_kg[rat[r] + x]; }
+        }
+        if (dom_slot == SU_HT) {
+          // the most frequent among four of the first 64 launches (a guess that costs nothing if it is wrong)
+          uint32_t most = 0;
+          for (uint32_t q = 0; q < WAVE; q += WAVE / 4) {
+            const uint64_t cand = read_lane_u64(id[0], q);
+            const uint32_t have = cand == HT_EMPTY ? 0u : static_cast<uint32_t>(__popcll(ballot(id[0] == cand)));
+            if (have > most) { most = have; dom_id = cand; }
+          }
+          if (most > 0) dom_slot = su_slot(sm, dom_id);
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < SU_RUNS; ++r) {
+          if (x < rc[r]) {
+            const uint32_t e = kg[r].x, g = kg[r].y;
+            uint32_t s = dom_slot;
+            if (id[r] == dom_id && dom_slot != SU_HT) {
+              ++dom_c; dom_es += e;
+              dom_en = e < dom_en ? e : dom_en; dom_ex = e > dom_ex ? e : dom_ex;
+              if (g != NONE32) {
+                ++dom_gc; dom_gs += g;
+                dom_gn = g < dom_gn ? g : dom_gn; dom_gx = g > dom_gx ? g : dom_gx;
+              }
+            } else {
+              s = su_slot(sm, id[r]);
+              if (s == SU_HT) { atomicOr(&sm.fallback, 1u); s = 0; }
+              atomicAdd(&sm.cnt[s], 1u);
+              atomicAdd(reinterpret_cast<unsigned long long*>(&sm.esum[s]), static_cast<unsigned long long>(e));
+              atomicMin(&sm.emin[s], e); atomicMax(&sm.emax[s], e);
+              if (g != NONE32) {
+                atomicAdd(&sm.gcnt[s], 1u);
+                atomicAdd(reinterpret_cast<unsigned long long*>(&sm.gsum[s]), static_cast<unsigned long long>(g));
+                atomicMin(&sm.gmin[s], g); atomicMax(&sm.gmax[s], g);
+              }
+            }
+            if (rto[r] + x < m) {   // (always: the unit's length is the sum of its runs)
+              pack_kg[rto[r] + x] = kg[r];
+              pack_slot[rto[r] + x] = static_cast<uint16_t>(s);
+            }
+          }
+        }
+      }
+    }
+    if (dom_slot != SU_HT) {   // (the same in the whole wave)
+      const uint32_t c = wave_sum_u32(dom_c), gc = wave_sum_u32(dom_gc);
+      const uint64_t es = wave_sum_u64(dom_es), gs = wave_sum_u64(dom_gs);
+      const uint32_t ex = wave_max_u32(dom_ex), gx = wave_max_u32(dom_gx), en = ~wave_max_u32(~dom_en), gn = ~wave_max_u32(~dom_gn);
+      if (lane == 0 && c) {
+        atomicAdd(&sm.cnt[dom_slot], c);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sm.esum[dom_slot]), static_cast<unsigned long long>(es));
+        atomicMin(&sm.emin[dom_slot], en); atomicMax(&sm.emax[dom_slot], ex);
+        atomicAdd(&sm.gcnt[dom_slot], gc);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&sm.gsum[dom_slot]), static_cast<unsigned long long>(gs));
+        atomicMin(&sm.gmin[dom_slot], gn); atomicMax(&sm.gmax[dom_slot], gx);
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t D = sm.ndist;
+  if (sm.fallback || D > SU_DMAX || sm.filled != m) {
+    // the whole task goes to the general path (k_long_general_values hands its per-launch values over)
+    if (tid == 0 && atomicExch(&A.mflag[t], 0u) == 1u) {
+      A.gflag[t] = 1;
+      atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->n_general), 1ull);
+    }
+    return;
+  }
+
+  // ---- rank the distinct IDs; where each value range is searched --------------------------------------------------
+  {
+    uint32_t total;
+    const bool used = tid < SU_HT && sm.ht_key[tid < SU_HT ? tid : 0] != HT_EMPTY;
+    const uint32_t at = block_excl_scan<SU_THREADS>(used ? 1u : 0u, sm.aux, total);
+    if (used) { sm.u.tmp.ckey[at] = sm.ht_key[tid]; sm.u.tmp.cslot[at] = static_cast<uint16_t>(tid); }
+    __syncthreads();
+    if (tid < D) {
+      const uint64_t k = sm.u.tmp.ckey[tid];
+      uint32_t rank = 0;
+      for (uint32_t i = 0; i < D; ++i) rank += sm.u.tmp.ckey[i] < k;
+      sm.slot_of[rank] = sm.u.tmp.cslot[tid];
+    }
+    __syncthreads();
+  }
+  const uint32_t B1 = su_bins_log2(2 * D), B2 = su_bins_log2(4 * D);
+  if (tid < 2 * D) {
+    const uint32_t arr = tid >= D ? 1u : 0u, j = tid - arr * D, s = sm.slot_of[j];
+    const uint32_t n = arr ? sm.gcnt[s] : sm.cnt[s];
+    const uint32_t lo = scale_of(arr ? sm.gmin[s] : sm.emin[s]), range = n ? scale_of(arr ? sm.gmax[s] : sm.emax[s]) - lo : 0u;
+    const uint32_t bits = range ? 32 - __builtin_clz(range) : 0u;
+    sm.sel[arr][s] = make_uint4(lo, (bits > B1 ? bits - B1 : 0u) | (j << 8), SU_NO_BIN, SU_NO_BIN);
+  }
+  for (uint32_t i = tid; i < ((2 * D) << B1); i += SU_THREADS) sm.u.hist[i] = 0;
+  __syncthreads();
+
+  // ---- 2. nearest-rank percentiles -------------------------------------------------------------------------------
+  for (uint32_t i0 = 0; i0 < m; i0 += SU_KPT * SU_THREADS) {
+    uint2 kg[SU_KPT];
+    uint32_t sl[SU_KPT];
+#pragma unroll
+    for (uint32_t u = 0; u < SU_KPT; ++u) {
+      const uint32_t i = i0 + u * SU_THREADS + tid;
+      kg[u] = make_uint2(0, 0); sl[u] = 0;
+      if (i < m) { kg[u] = pack_kg[i]; sl[u] = pack_slot[i]; }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < SU_KPT; ++u) {
+      if (i0 + u * SU_THREADS + tid < m) {
+        const uint4 se = sm.sel[0][sl[u]];
+        atomicAdd(&sm.u.hist[((se.y >> 8) << B1) + ((scale_of(kg[u].x) - se.x) >> (se.y & 0xffu))], 1u);
+        if (kg[u].y != NONE32) {
+          const uint4 sg = sm.sel[1][sl[u]];
+          atomicAdd(&sm.u.hist[((D + (sg.y >> 8)) << B1) + ((scale_of(kg[u].y) - sg.x) >> (sg.y & 0xffu))], 1u);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (uint32_t q = w; q < 4 * D; q += SU_WAVES) {   // (2 * array + percentile, rank); a wave each
+    const uint32_t ap = q / D, j = q - ap * D, arr = ap >> 1, s = sm.slot_of[j];
+    const uint32_t n = arr ? sm.gcnt[s] : sm.cnt[s];
+    if (n == 0) {
+      if (lane == 0) sm.base[ap][j] = 0;
+      continue;
+    }
+    const uint32_t k = static_cast<uint32_t>(rank_index(ap & 1u ? 95 : 50, n));
+    uint32_t bin, inside;
+    su_find(sm.u.hist + ((arr * D + j) << B1), 1u << B1, k, bin, inside);
+    if (lane == 0) {
+      const uint4 sel = sm.sel[arr][s];
+      const uint32_t sh = sel.y & 0xffu, t_lo = sel.x + (bin << sh), t_end = t_lo + (1u << sh);
+      // The values of the bin: the scale's float rounds to nearest, so the lowest of them may lie half a unit in the
+      // last place below the bin's own low end.
+      const uint32_t v_lo = value_of_scale(t_lo), mn = arr ? sm.gmin[s] : sm.emin[s], mx = arr ? sm.gmax[s] : sm.emax[s];
+      uint32_t vb = v_lo - (v_lo >> 23) - (v_lo ? 1u : 0u);
+      vb = vb < mn ? mn : vb;
+      uint32_t vt = t_end < scale_of(~0u) ? value_of_scale(t_end) : ~0u;
+      vt = vt > mx ? mx : vt;
+      const uint32_t width = vt - vb, bits = width ? 32 - __builtin_clz(width) : 0u;
+      sm.base[ap][j] = vb;
+      sm.rest[ap][j] = inside;
+      sm.fine[ap][j] = static_cast<uint8_t>(bits > B2 ? bits - B2 : 0u);
+      (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) = bin;
+    }
+  }
+  __syncthreads();
+  for (;;) {
+    for (uint32_t i = tid; i < ((4 * D) << B2); i += SU_THREADS) sm.u.hist[i] = 0;
+    if (tid == 0) sm.again = 0;
+    __syncthreads();
+    // a sample of a bin that is searched: counted by its offset from where the search has got to
+    auto count = [&](uint32_t arr, uint32_t v, uint32_t slot) {
+      const uint4 sel = sm.sel[arr][slot];
+      const uint32_t bin = (scale_of(v) - sel.x) >> (sel.y & 0xffu), j = sel.y >> 8;
+#pragma unroll
+      for (uint32_t p = 0; p < 2; ++p) {
+        if (bin == (p ? sel.w : sel.z)) {
+          const uint32_t ap = 2 * arr + p, d = (v - sm.base[ap][j]) >> sm.fine[ap][j];
+          if (v >= sm.base[ap][j] && d < (1u << B2)) atomicAdd(&sm.u.hist[((ap * D + j) << B2) + d], 1u);
+        }
+      }
+    };
+    for (uint32_t i0 = 0; i0 < m; i0 += SU_KPT * SU_THREADS) {
+      uint2 kg[SU_KPT];
+      uint32_t sl[SU_KPT];
+#pragma unroll
+      for (uint32_t u = 0; u < SU_KPT; ++u) {
+        const uint32_t i = i0 + u * SU_THREADS + tid;
+        kg[u] = make_uint2(0, 0); sl[u] = 0;
+        if (i < m) { kg[u] = pack_kg[i]; sl[u] = pack_slot[i]; }
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < SU_KPT; ++u) {
+        if (i0 + u * SU_THREADS + tid < m) {
+          count(0, kg[u].x, sl[u]);
+          if (kg[u].y != NONE32) count(1, kg[u].y, sl[u]);
+        }
+      }
+    }
+    __syncthreads();
+    for (uint32_t q = w; q < 4 * D; q += SU_WAVES) {
+      const uint32_t ap = q / D, j = q - ap * D, arr = ap >> 1, s = sm.slot_of[j];
+      const uint32_t searched = ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z;
+      if (searched == SU_NO_BIN) continue;
+      uint32_t bin, inside;
+      su_find(sm.u.hist + ((ap * D + j) << B2), 1u << B2, sm.rest[ap][j], bin, inside);
+      if (lane == 0) {
+        const uint32_t sh = sm.fine[ap][j];
+        sm.base[ap][j] += bin << sh;
+        sm.rest[ap][j] = inside;
+        sm.fine[ap][j] = static_cast<uint8_t>(sh > B2 ? sh - B2 : 0u);
+        if (sh == 0) (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) = SU_NO_BIN;   // one value wide: found
+        else atomicOr(&sm.again, 1u);
+      }
+    }
+    __syncthreads();
+    if (!sm.again) break;
+    __syncthreads();   // (again is cleared at the top)
+  }
+
+  if (tid < D) {
+    const uint32_t s = sm.slot_of[tid];
+    uint64_t* row = staged_row(A.stage_a, A.stage_b, base, m, tid);
+    const uint32_t gc = sm.gcnt[s];
+    row[0] = sm.ht_key[s]; row[1] = t;
+    row[2] = sm.cnt[s]; row[3] = sm.esum[s]; row[4] = sm.emin[s]; row[5] = sm.emax[s];
+    row[6] = sm.base[0][tid]; row[7] = sm.base[1][tid];
+    row[8] = gc; row[9] = sm.gsum[s]; row[10] = gc ? sm.gmin[s] : 0; row[11] = gc ? sm.gmax[s] : 0;
+    row[12] = sm.base[2][tid]; row[13] = sm.base[3][tid];
+    row[14] = 0; row[15] = 0;
+  }
+  if (tid == 0) A.dcount[unit] = D;
+}
+
+}  // namespace fikit

@@ -1,0 +1,63 @@
+"""Long tasks in which a few Kernel IDs are so frequent that no workgroup holds all their launches: every output of the
+profile against the CPU oracle, and whether the sort was needed."""
+import numpy as np
+import pytest
+
+from paper_2311_10359_amd import binding, traces
+from parity_util import check_profile
+
+pytestmark = pytest.mark.gpu
+LONG = 1 << 18      # tasks from this length on are not sorted for a frequent ID
+
+
+def skewed(seed, lens, n_ids, heavy, times):
+    """Tasks of the given lengths; a launch is kernel 0 with probability `heavy`, else one of n_ids."""
+    rng = np.random.default_rng(seed)
+    n = sum(lens)
+    rec = np.zeros(n, dtype=traces.LAUNCH_DTYPE)
+    kid = np.where(rng.random(n) < heavy, 0, rng.integers(0, n_ids, n)).astype(np.uint32)
+    rec["name_id"], rec["grid"], rec["block"] = kid * 7919, 1, 64
+    if times == "lognormal":
+        ex = np.maximum(1, np.rint(rng.lognormal(8.5 + (kid % 5), 1.5, n))).astype(np.int64)
+        gp = np.where(rng.random(n) < 0.3, 0, np.rint(rng.lognormal(9.6, 1.2, n))).astype(np.int64)
+    elif times == "ties":
+        ex, gp = np.full(n, 12345, np.int64), (kid % 3).astype(np.int64)
+    elif times == "wide":           # the whole range of 32 bits, clustered at both ends
+        ex = np.where(rng.random(n) < 0.5, rng.integers(0, 9, n), (1 << 32) - 2 - rng.integers(0, 9, n)).astype(np.int64)
+        gp = (np.int64(1) << rng.integers(0, 32, n)) - rng.integers(0, 2, n)
+    else:                           # one value in a thousand beyond 32 bits
+        ex = rng.integers(1, 100000, n) + np.where(rng.random(n) < 0.001, 1 << 33, 0)
+        gp = rng.integers(0, 1000, n)
+    start = np.cumsum(ex + gp) - (ex + gp)
+    rec["start_ns"], rec["end_ns"] = start, start + ex
+    rec["run"] = np.arange(n) // 100003
+    off = np.zeros(len(lens) + 1, dtype=np.uint64)
+    np.cumsum(lens, out=off[1:])
+    return rec, off
+
+
+@pytest.mark.parametrize("lens,n_ids,heavy,times,sorts", [
+    ([LONG], 1, 1.0, "lognormal", False),                        # one ID, the shortest such task
+    ([LONG + 1, 17, LONG + 4095], 3, 0.9, "ties", False),
+    ([LONG - 1], 40, 0.5, "lognormal", True),                    # one launch shorter: sorted
+    ([16385, 5000, LONG + 777, 300], 90, 0.3, "wide", False),    # beside tasks of every other shape
+    ([500000, 600, 300001], 4096, 0.2, "lognormal", False),
+    ([700001], 60000, 0.4, "lognormal", True),                   # more IDs in a bucket than its table holds
+    ([LONG, LONG], 50, 0.5, "beyond", True),
+])
+def test_frequent_ids(lens, n_ids, heavy, times, sorts):
+    print(f"lengths {lens}, {n_ids} IDs, share of the first {heavy}, {times}", flush=True)
+    rec, off = skewed(len(lens) + n_ids, lens, n_ids, heavy, times)
+    binding.fikit_trace_enable(True)
+    try:
+        check_profile(rec, off)
+        names = binding.fikit_trace_read()
+    finally:
+        binding.fikit_trace_enable(False)
+    assert ("k_onesweep_pass" in names) == sorts, sorted(names)
+
+
+def test_more_tiles_than_a_unit_can_list():
+    """A task of more than 1024 tiles: all of its buckets are streamed, small ones too."""
+    rec, off = skewed(5, [4_200_000, 900], 300, 0.1, "lognormal")
+    check_profile(rec, off)
