@@ -1039,7 +1039,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   if (int rc = read_ctrl(ctrl, &h, st)) return rc;   // the widest scenario decides how many lanes share one
   if (int rc = status_from_bits(h.status)) return rc;
   const uint32_t widest = h.n_class[3];
-  // Up to 64 low-priority tasks per scenario: a group of lanes per scenario on 32-bit predictions; the 64-bit
+  // Up to 64 low-priority tasks per scenario: a wave or a group of lanes per scenario on 32-bit predictions; the 64-bit
   // kernels then only run if a prediction did not fit (they check Ctrl::wide).  More tasks: the 64-bit kernels.
   const bool groups = widest <= PF_MAX_LP;
   if (groups) {
@@ -1054,7 +1054,24 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   rc = launch_prio_walk<W>(st, d_task_offsets, d_hp_task, d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, d_gap_offsets, \
                            lp_e, hp_eg, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_placed, \
                            d_lp_placed_ns, vec_ok, ctrl)
-    if (widest <= 1) FIKIT_PF_WALK(1);
+#define FIKIT_PF_WAVE(K)                                                                                                      \
+  hipLaunchKernelGGL(k_pf_walk_wave<K>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st,            \
+                     d_task_offsets, d_hp_task, d_lp_offsets, d_lp_task, d_lp_prio, static_cast<uint32_t>(n_scenarios),       \
+                     d_gap_offsets, lp_e, hp_eg, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,        \
+                     d_lp_placed, d_lp_placed_ns, ctrl)
+    // One wave per scenario up to this many scenarios, beyond it a group of lanes per scenario.  The waves' time grows with
+    // the scenarios, the groups' hardly does; traces of 1024 launches, queues of 2048, waves / groups in ms for the call:
+    //   1 task   4096: 0.41 / 1.22   12,288: 0.80 / 1.37   32,768: 1.78 / 1.69
+    //   3 tasks  64: 0.94 / 2.2   4096: 1.39 / 2.34   6144: 1.78 / 2.38   8192: 2.19 / 2.40   12,288: 3.08 / 2.74
+    //   4 tasks  6144: 2.28 / 2.71   8192: 2.86 / 2.74   6 tasks  6144: 2.62 / 3.67   12,288: 4.07 / 3.91
+    //   9 tasks  6144: 2.64 / 3.90   12,288: 4.08 / 5.30   16,384: 5.47 / 5.42
+    const bool waves = n_scenarios <= (widest <= 1 || widest > 8 ? 16384u : 6144u);
+    if (waves && widest <= 1) FIKIT_PF_WAVE(64);
+    else if (waves && widest <= 2) FIKIT_PF_WAVE(32);
+    else if (waves && widest <= 4) FIKIT_PF_WAVE(16);
+    else if (waves && widest <= 8) FIKIT_PF_WAVE(8);
+    else if (waves && widest <= 16) FIKIT_PF_WAVE(4);
+    else if (widest <= 1) FIKIT_PF_WALK(1);
     else if (widest <= 2) FIKIT_PF_WALK(2);
     else if (widest <= 4) FIKIT_PF_WALK(4);
     else if (widest <= 8) FIKIT_PF_WALK(8);
@@ -1062,6 +1079,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
     else if (widest <= 32) FIKIT_PF_WALK(32);
     else FIKIT_PF_WALK(64);
 #undef FIKIT_PF_WALK
+#undef FIKIT_PF_WAVE
     if (rc) return rc;
   }
   if (!groups) {

@@ -327,6 +327,165 @@ k_pf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
   for (; z < g_end; ++z) { fill_count[z] = 0; filled_ns[z] = 0; }
 }
 
+// One wave per scenario with up to 64 / SEG low-priority tasks, on the same 32-bit predictions.
+//
+// The first lanes hold the waiting requests in the order in which BestPrioFit prefers them: by level, within a level the
+// longest first, equal ones by age.  A decision is then one comparison of all lanes with what is left of the gap, and the
+// first lane that fits.  The request that takes the place of the issued one is the youngest: its place is behind the
+// requests of its level that are at least as long, and the ones between move up or down by a lane.  (Levels keep their
+// lanes; no enqueue stamps are needed.)  SEG lanes per queue hold its next durations, so that the following request is
+// one lane read; the SEG durations after them are read ahead.  Which gap takes something next is one comparison of all
+// lanes with the shortest request: gaps that take nothing cost nothing.
+// What bounds it: with few scenarios the chain of one decision (compare, first lane, three lane reads, compare, lane write:
+// about 320 cycles), with many the issue of its thirty instructions.  4096 scenarios of 1023 gaps and three queues of 2048:
+// 1.15 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
+template <int SEG>
+__global__ void __launch_bounds__(WW_THREADS)
+k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint64_t* __restrict__ lp_off,
+               const uint32_t* __restrict__ lp_task, const uint32_t* __restrict__ lp_prio, uint32_t n_scen,
+               const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e, const uint2* __restrict__ hp_eg,
+               int64_t margin, int64_t min_gap, uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns,
+               uint64_t* __restrict__ placed_out, int64_t* __restrict__ placed_ns_out, const Ctrl* ctrl) {
+  constexpr uint32_t K = WAVE / SEG;
+  static_assert(K <= 16, "the requests fit a row of lanes");
+  if (ctrl->status || ctrl->wide) return;
+  const uint32_t lane = lane_id(), mine = lane / SEG, place = lane % SEG;   // the queue this lane belongs to
+  const uint32_t s = static_cast<uint32_t>(
+      __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (WW_THREADS / WAVE) + threadIdx.x / WAVE)));
+  if (s >= n_scen) return;
+  const uint32_t hp = hp_task[s];
+  const uint32_t h0 = static_cast<uint32_t>(off[hp]), H = static_cast<uint32_t>(off[hp + 1]) - h0;
+  const uint32_t g0 = static_cast<uint32_t>(gap_off[s]), n_gaps = H > 0 ? H - 1 : 0;
+  const uint32_t e0 = static_cast<uint32_t>(lp_off[s]), listed = static_cast<uint32_t>(lp_off[s + 1]) - e0;   // (at most K)
+  const int64_t floor64 = min_gap > margin ? min_gap : margin;
+  const uint32_t gap_floor = floor64 >= static_cast<int64_t>(WIDE32) ? WIDE32 : static_cast<uint32_t>(floor64);
+  const uint32_t margin32 = margin >= static_cast<int64_t>(WIDE32) ? WIDE32 : static_cast<uint32_t>(margin);
+
+  // the queues: window raw = entries [start, start + SEG), WIDE32 behind the end; next = the SEG entries after it
+  const uint32_t* __restrict__ queue = lp_e;
+  uint32_t len = 0, start = 0;
+  if (mine < listed) {
+    const uint32_t lp = lp_task[e0 + mine];
+    const uint32_t first = static_cast<uint32_t>(off[lp]);
+    len = static_cast<uint32_t>(off[lp + 1]) - first;
+    queue = lp_e + first;
+  }
+  uint32_t raw = WIDE32, next = 0;
+  if (place < len) raw = queue[place];
+  if (SEG + place < len) next = queue[SEG + place];
+  uint64_t issued_ns = 0;      // of the windows this lane has seen pass
+
+  // the waiting requests in their order: duration, lane of the window it stands in, lanes of its level (as bits)
+  uint32_t hd = WIDE32, ho = 0, seg = 0;
+  {
+    const uint32_t level = lane < listed ? lp_prio[e0 + lane] : WIDE32;
+    const uint32_t head = static_cast<uint32_t>(__shfl(static_cast<int>(raw), static_cast<int>(lane * SEG & (WAVE - 1)), WAVE));
+    uint32_t rank = 0, at_level = WIDE32;
+    for (uint32_t j = 0; j < listed; ++j) {
+      const uint32_t lj = read_lane_u32(level, j), dj = read_lane_u32(head, j);
+      rank += lj < level || (lj == level && (dj > head || (dj == head && j < lane))) ? 1u : 0u;
+    }
+    for (uint32_t j = 0; j < listed; ++j) {
+      const uint32_t r = read_lane_u32(rank, j);
+      hd = write_lane_u32(hd, read_lane_u32(head, j), r);
+      ho = write_lane_u32(ho, j * SEG, r);
+      at_level = write_lane_u32(at_level, read_lane_u32(level, j), r);
+    }
+    for (uint32_t j = 0; j < listed; ++j) seg |= read_lane_u32(at_level, j) == at_level ? 1u << j : 0u;
+  }
+  auto shortest = [&]() {      // (the lanes behind the requests hold WIDE32)
+    uint32_t m = hd;
+    if (K >= 2) m = min_u32(m, dpp_move<0xB1>(m));    // quad_perm [1,0,3,2]
+    if (K >= 4) m = min_u32(m, dpp_move<0x4E>(m));    // quad_perm [2,3,0,1]
+    if (K >= 8) m = min_u32(m, dpp_move<0x141>(m));   // row_half_mirror
+    if (K >= 16) m = min_u32(m, dpp_move<0x140>(m));  // row_mirror
+    return read_lane_u32(m, 0);
+  };
+  uint32_t least = shortest();
+
+  const uint2* __restrict__ trace = hp_eg + h0;
+  auto idle_time = [&](uint32_t i) { return trace[i < n_gaps ? i : 0u].y; };
+  uint32_t G0 = n_gaps ? idle_time(lane) : 0u, G1 = n_gaps ? idle_time(WAVE + lane) : 0u;
+  uint32_t i0 = 0;
+  for (; i0 < n_gaps && least != WIDE32; i0 += WAVE) {
+    const uint32_t i = i0 + lane, G = G0;
+    G0 = G1;
+    G1 = idle_time(i + 2 * WAVE);
+    const uint32_t b1 = (i < n_gaps && G >= gap_floor) ? G - margin32 + 1 : 0u;   // one more than what may be filled
+    uint32_t my_c = 0, my_f = 0;
+    uint64_t todo = ~0ull;
+    for (;;) {
+      const uint64_t takes = ballot(b1 > least) & todo;
+      if (takes == 0) break;
+      const uint32_t j = static_cast<uint32_t>(__builtin_ctzll(takes));
+      todo = (~1ull) << j;
+      const uint32_t budget = read_lane_u32(b1, j) - 1;
+      uint32_t rem = budget, c = 0;
+      uint64_t fit = ballot(hd <= rem);   // (never empty here)
+      do {
+        const uint32_t p = static_cast<uint32_t>(__builtin_ctzll(fit));
+        rem -= read_lane_u32(hd, p);
+        ++c;
+        uint32_t w = read_lane_u32(ho, p) + 1;
+        const uint32_t level = read_lane_u32(seg, p);
+        if (__builtin_expect(w % SEG == 0, 0)) {   // the queue's window is used up
+          w -= SEG;
+          if (mine == w / SEG) {
+            issued_ns += raw;
+            start += SEG;
+            raw = start + place < len ? next : WIDE32;
+            const uint32_t at = start + SEG + place;
+            next = queue[at < len ? at : 0u];   // (a queue with a window to use up is not empty)
+          }
+        }
+        const uint32_t n = read_lane_u32(raw, w);
+        uint32_t to = p;
+        if (K > 1 && (level & (level - 1))) {
+          const uint32_t ahead = static_cast<uint32_t>(ballot(hd >= n)) & level & ~(1u << p);
+          to = static_cast<uint32_t>(__builtin_ctz(level)) + static_cast<uint32_t>(__builtin_popcount(ahead));
+          if (to > p) {
+            const uint32_t d1 = dpp_move<0x101>(hd), o1 = dpp_move<0x101>(ho);   // row_shl:1, from the lane above
+            const bool moves = lane - p < to - p;
+            hd = moves ? d1 : hd;
+            ho = moves ? o1 : ho;
+          } else if (to < p) {
+            const uint32_t d1 = dpp_move<0x111>(hd), o1 = dpp_move<0x111>(ho);   // row_shr:1, from the lane below
+            const bool moves = lane - to - 1 < p - to;
+            hd = moves ? d1 : hd;
+            ho = moves ? o1 : ho;
+          }
+        }
+        hd = write_lane_u32(hd, n, to);
+        ho = write_lane_u32(ho, w, to);
+        fit = ballot(hd <= rem);
+      } while (fit);
+      my_c = write_lane_u32(my_c, c, j);
+      my_f = write_lane_u32(my_f, budget - rem, j);
+      least = shortest();
+    }
+    if (i < n_gaps) {
+      fill_count[g0 + i] = my_c;
+      filled_ns[g0 + i] = static_cast<int64_t>(my_f);
+    }
+  }
+  for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queues ran empty)
+    fill_count[g0 + i] = 0;
+    filled_ns[g0 + i] = 0;
+  }
+  uint32_t gone = 0;           // entries of this lane's window that have been issued
+  for (uint32_t r = 0; r < listed; ++r) {
+    const uint32_t w = read_lane_u32(ho, r);
+    if (mine == w / SEG) gone = w % SEG;
+  }
+  if (place < gone) issued_ns += raw;
+#pragma unroll
+  for (int m = 1; m < SEG; m <<= 1) issued_ns += shfl_xor_u64(issued_ns, m);
+  if (place == 0 && mine < listed) {
+    placed_out[e0 + mine] = start + gone;
+    placed_ns_out[e0 + mine] = static_cast<int64_t>(issued_ns);
+  }
+}
+
 // Algorithm 1 with the whole of Algorithm 2 for the scenarios the group kernels do not take: predictions that do not
 // fit 32 bits (Ctrl::wide), or more low-priority tasks in a scenario than a wave has lanes.  One lane per scenario
 // steps through the gaps literally on the 64-bit arrays of k_gf_predict; every decision looks at all the scenario's
