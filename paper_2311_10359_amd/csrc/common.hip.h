@@ -82,6 +82,25 @@ __device__ __forceinline__ uint4 load_once(const uint4* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// Stores to `bytes` bytes from p on (the same in the whole wave): what a lane writes behind them is dropped by the
+// hardware, without a branch.
+typedef __amdgpu_buffer_rsrc_t bounded;
+__device__ __forceinline__ bounded bounded_at(void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a)));
+  const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32)));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(lo | hi << 32), 0,
+                                           __builtin_amdgcn_readfirstlane(static_cast<int>(bytes)), 0x00027000);
+}
+__device__ __forceinline__ void store_below(bounded b, uint32_t at, uint32_t v) {
+  __builtin_amdgcn_raw_buffer_store_b32(v, b, static_cast<int>(at), 0, 0);
+}
+typedef uint32_t u32x2_native __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void store_below(bounded b, uint32_t at, uint32_t lo, uint32_t hi) {
+  const u32x2_native v = {lo, hi};
+  __builtin_amdgcn_raw_buffer_store_b64(v, b, static_cast<int>(at), 0, 0);
+}
+
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
   uint32_t lo = __shfl_xor(static_cast<uint32_t>(v), m, WAVE);
   uint32_t hi = __shfl_xor(static_cast<uint32_t>(v >> 32), m, WAVE);

@@ -539,17 +539,16 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   const uint32_t margin32 = margin >= static_cast<int64_t>(WIDE32) ? WIDE32 : static_cast<uint32_t>(margin);
 
   uint32_t wb = 0, o = 0, C = 0, sum = 0;    // window start, position in it, time consumed since its start, running sum of the head
-  uint32_t win = 0, r1 = 0, r2 = 0, r3 = 0;  // running sums of the window; the entries of the three windows after it
-  // (behind the end: saturates, never fits; read without a branch, so that the walk's loop stays free of divergent ones)
-  auto entry = [&](uint32_t j) -> uint32_t {
-    const uint32_t v = queue[j < L ? j : L - 1];
-    return j < L ? v : WIDE32;
-  };
-  auto set_window = [&](uint32_t r) { win = wave_incl_scan_sat_u32(lane == WW_WIN ? WIDE32 : r); };
+  uint32_t win = 0, r1 = 0;                  // running sums of the window; the entries of the window after it
+  // (read without a branch, so that the walk's loop stays free of divergent ones; what lies behind the end is told apart
+  // when the entries are used, so that nothing waits for a read where it is issued)
+  auto entry = [&](uint32_t j) -> uint32_t { return queue[j < L ? j : L - 1]; };
+  // (behind the end: saturates, never fits)
+  auto set_window = [&](uint32_t r) { win = wave_incl_scan_sat_u32(lane == WW_WIN || wb + lane >= L ? WIDE32 : r); };
   auto load_window = [&](uint32_t at) {
     wb = at; o = 0; C = 0;
     const uint32_t r0 = entry(at + lane);
-    r1 = entry(at + WW_WIN + lane); r2 = entry(at + 2 * WW_WIN + lane); r3 = entry(at + 3 * WW_WIN + lane);
+    r1 = entry(at + WW_WIN + lane);
     set_window(r0);
   };
   bool done = L == 0;    // the whole queue has been issued
@@ -562,6 +561,8 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   uint2 ahead[WW_BLOCKS];
 #pragma unroll
   for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(64 * j + lane, H - 1)] : make_uint2(0, 0);
+#pragma unroll
+  for (uint32_t j = 0; j < WW_BLOCKS; ++j) asm volatile("" : "+v"(ahead[j].x), "+v"(ahead[j].y));   // (the loop starts with nothing in flight)
   uint32_t i0 = 0;
   for (; i0 < H && !done; i0 += 64 * WW_BLOCKS) {
     uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
@@ -573,6 +574,10 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
       asm volatile("" : "+v"(E[j]), "+v"(G[j]), "+v"(b1[j]));           // (waited for here, before the next round's reads go out)
     }
     __builtin_amdgcn_sched_barrier(0);
+    // (the results of a round are stored without a branch, so that the wait for the next round's reads can leave them in
+    // flight: lanes behind the last gap fall outside the buffer)
+    const uint32_t left = n_gaps - min_u32(i0, n_gaps), gaps_here = min_u32(left, 64 * WW_BLOCKS);
+    const bounded out_c = bounded_at(fill_count + g0 + i0, 4 * gaps_here), out_f = bounded_at(filled_ns + g0 + i0, 8 * gaps_here);
 #pragma unroll
     for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
 #pragma unroll
@@ -628,7 +633,7 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
             if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
               wb += WW_WIN; o = 0; C = 0;
               set_window(r1);
-              r1 = r2; r2 = r3; r3 = entry(wb + 3 * WW_WIN + lane);
+              r1 = entry(wb + WW_WIN + lane);
               again = !stop;
             }
             sum = read_lane_u32(win, o);
@@ -649,10 +654,8 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
           delay += my_f > E[j] ? my_f - E[j] : 0u;
         }
       }
-      if (has_gap) {
-        fill_count[g0 + i] = my_c;
-        filled_ns[g0 + i] = static_cast<int64_t>(my_f);
-      }
+      store_below(out_c, 256u * j + 4u * lane, my_c);
+      store_below(out_f, 512u * j + 8u * lane, my_f, 0u);
     }
   }
   for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queue ran empty)
