@@ -196,6 +196,19 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t* ld
   return base + incl - v;
 }
 
+// The same across a 1024-thread block; `lds` needs 16 words.
+__device__ __forceinline__ uint32_t block_excl_scan_1024(uint32_t v, uint32_t* lds, uint32_t& total) {
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  const uint32_t incl = wave_incl_scan_u32(v);
+  __syncthreads();  // protect lds reuse
+  if (lane == 63) lds[w] = incl;
+  __syncthreads();
+  const uint32_t sums = wave_incl_scan_u32(lane < 16 ? lds[lane] : 0u);   // (every wave scans the waves' totals for itself)
+  total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sums), 15));
+  const uint32_t base = w ? static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sums), static_cast<int>(w - 1))) : 0u;
+  return base + incl - v;
+}
+
 // Nearest rank: the ceil(K * count / 100)-th smallest, as a 0-based index (count >= 1).
 __device__ __forceinline__ uint64_t rank_index(uint64_t k, uint64_t count) { return (k * count + 99) / 100 - 1; }
 __device__ __forceinline__ uint32_t rank_index_u32(uint32_t k, uint32_t count) { return (k * count + 99) / 100 - 1; }

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <mutex>
 
 #include "common.hip.h"
@@ -112,6 +113,20 @@ int scan_u32(uint32_t* d_data, uint64_t count, uint32_t* d_sums, uint64_t* d_tot
   return FIKIT_OK;
 }
 
+// 64-bit offsets and their total (ctrl->n_rows) from `count` 32-bit row counts, the last of which is 0; see k_row_offsets.
+int row_offsets_enqueue(const uint32_t* d_counts, uint64_t count, uint32_t* d_sums, uint64_t* d_out, Ctrl* ctrl, hipStream_t st) {
+  if (count <= ROW_SCAN_ONE) {
+    hipLaunchKernelGGL(k_row_offsets, dim3(1), dim3(1024), 0, st, d_counts, count, d_out, ctrl);
+  } else {
+    const uint32_t nb = blocks_for(count, SCAN_TILE);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums);
+    hipLaunchKernelGGL(k_scan_spine, dim3(1), dim3(SCAN_BLOCK), 0, st, d_sums, static_cast<uint64_t>(nb), &ctrl->n_rows);
+    hipLaunchKernelGGL(k_row_offsets_apply, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums, d_out, ctrl);
+  }
+  FIKIT_HIP(hipGetLastError());
+  return FIKIT_OK;
+}
+
 // ---- optional per-kernel timing (fikit_trace_*) ---------------------------------------------
 // When enabled, every launch site records a HIP event on the caller's stream; at the end of
 // the call the time between consecutive events is added to the entry of the launch that
@@ -167,10 +182,56 @@ int status_from_bits(uint32_t bits) {
   return FIKIT_OK;
 }
 
+// Where device words arrive on the host: a few pinned bytes per calling thread, allocated on its first call and freed when
+// it ends.  A copy to memory that is not pinned goes through a staging buffer of the runtime: kernel, copy of 80 bytes and
+// wait take 22 us that way and 14.5 us this way, every further copy 11 us against 3 us.
+struct Mailbox {
+  static constexpr size_t BYTES = 256;
+  unsigned char* at = nullptr;
+  ~Mailbox() { if (at) (void)hipHostFree(at); }
+  unsigned char* get() {
+    if (!at) {
+      // (another thread may be capturing a graph, which an allocation in the default mode would break)
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, BYTES, hipHostMallocPortable) == hipSuccess) at = static_cast<unsigned char*>(p);
+      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+      (void)hipGetLastError();
+    }
+    return at;
+  }
+};
+thread_local Mailbox t_mailbox;
+
+// Up to four reads of device words; they have arrived once wait() returns.
+struct Reads {
+  hipStream_t st;
+  unsigned char* box = t_mailbox.get();
+  struct { void* to; size_t bytes, at; } item[4];
+  int n = 0;
+  size_t used = 0;
+  explicit Reads(hipStream_t s) : st(s) {}
+  int add(void* to, const void* from, size_t bytes) {
+    item[n].to = to; item[n].bytes = bytes; item[n].at = used;
+    FIKIT_HIP(hipMemcpyAsync(box ? box + used : to, from, bytes, hipMemcpyDeviceToHost, st));
+    used += (bytes + 15) / 16 * 16;
+    ++n;
+    return FIKIT_OK;
+  }
+  int wait() {
+    FIKIT_HIP(hipStreamSynchronize(st));
+    if (box)
+      for (int i = 0; i < n; ++i) std::memcpy(item[i].to, box + item[i].at, item[i].bytes);
+    return FIKIT_OK;
+  }
+};
+static_assert(sizeof(Ctrl) + 3 * 16 <= Mailbox::BYTES, "what one wait brings fits");
+
 int read_ctrl(const Ctrl* d_ctrl, Ctrl* h, hipStream_t st) {
-  FIKIT_HIP(hipMemcpyAsync(h, d_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipStreamSynchronize(st));
-  return FIKIT_OK;
+  Reads r(st);
+  if (int rc = r.add(h, d_ctrl, sizeof(Ctrl))) return rc;
+  return r.wait();
 }
 
 template <int W>
@@ -276,10 +337,10 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
 
   Tracer tr(st);
   tr.mark("setup");
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
   Ctrl h{};
   if (n == 0) {
+    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
+    hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(2 * (static_cast<uint64_t>(n_tasks) + 1), 256)), dim3(256), 0, st,
                        reinterpret_cast<uint32_t*>(d_task_row_offsets), 2 * (static_cast<uint64_t>(n_tasks) + 1), 0u);
     FIKIT_HIP(hipGetLastError());
@@ -296,8 +357,6 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   // Short tasks with few distinct IDs: one workgroup each, records read once, rows staged.
   tr.mark("plan");
   uint32_t* lists = reinterpret_cast<uint32_t*>(ws + L.lists);
-  hipLaunchKernelGGL(k_classify, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
-                     n_tasks, FUSE_SMALL_MAX, FUSE_MID_MAX, FUSE_MAX, gflag, dcount, lists, ctrl);
   uint32_t* is_long = reinterpret_cast<uint32_t*>(ws + L.is_long);
   uint32_t* mtiles = reinterpret_cast<uint32_t*>(ws + L.mtiles);
   uint32_t* mflag = reinterpret_cast<uint32_t*>(ws + L.mflag);
@@ -308,6 +367,26 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   uint32_t* urow = udcount + L.max_units;
   uint32_t* ubuckets = urow + L.max_units;
   uint32_t* wflag = reinterpret_cast<uint32_t*>(ws + L.wflag);
+  const bool few_tasks = n_tasks <= BEGIN_TASKS;
+  if (few_tasks) {
+    hipLaunchKernelGGL(k_profile_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n, FUSE_SMALL_MAX, FUSE_MID_MAX,
+                       FUSE_MAX, PT_TILE, gflag, dcount, lists, is_long, mtiles, wflag, ctrl);
+  } else {
+    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
+    hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
+    hipLaunchKernelGGL(k_classify, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
+                       n_tasks, FUSE_SMALL_MAX, FUSE_MID_MAX, FUSE_MAX, gflag, dcount, lists, ctrl);
+  }
+  FIKIT_HIP(hipGetLastError());
+  // Workgroups per class of task: their numbers if the host has to wait for them anyway (there may be long tasks, which are
+  // launched for by number), otherwise what the launches suffice for.
+  uint64_t n_class[3] = {n < n_tasks ? n : n_tasks, n / (FUSE_SMALL_MAX + 1), n / (FUSE_MID_MAX + 1)};
+  if (n > FUSE_MAX) {
+    tr.mark("host_sync");
+    if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+    if (int rc = status_from_bits(h.status)) return rc;
+    for (int k = 0; k < 3; ++k) n_class[k] = h.n_class[k];
+  }
   uint16_t* bound = reinterpret_cast<uint16_t*>(hist);
   uint2* part_kg = reinterpret_cast<uint2*>(k2);
   auto small = k_task_fused<FUSE_S_THREADS, FUSE_SMALL_MAX / FUSE_S_THREADS, 256, 7168, FUSE_S_LB, false, FUSE_S_WPE>;
@@ -332,45 +411,48 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     fa.pred_role = emit->role; fa.pred_lp_e = emit->lp_e; fa.pred_hp_eg = emit->hp_eg; fa.pred_lp_total = emit->lp_total;
     fa.pred_done = emit->done; fa.predictor = emit->predictor;
   }
-  {
+  if (n_class[0]) {
     tr.mark("k_task_fused_small");
     fa.list = lists; fa.count = &ctrl->n_class[0]; fa.max_len = FUSE_SMALL_MAX;
-    hipLaunchKernelGGL(small, dim3(n_tasks), dim3(FUSE_S_THREADS), small_lds, st, fa);
+    hipLaunchKernelGGL(small, dim3(static_cast<uint32_t>(n_class[0])), dim3(FUSE_S_THREADS), small_lds, st, fa);
+  }
+  if (n_class[1]) {
     tr.mark("k_task_fused_mid");
     fa.list = lists + n_tasks; fa.count = &ctrl->n_class[1]; fa.max_len = FUSE_MID_MAX;
-    hipLaunchKernelGGL(mid, dim3(n_tasks), dim3(512), mid_lds, st, fa);
+    hipLaunchKernelGGL(mid, dim3(static_cast<uint32_t>(n_class[1])), dim3(512), mid_lds, st, fa);
+  }
+  if (n_class[2]) {
     tr.mark("k_task_fused_medium");
     fa.list = lists + 2 * static_cast<uint64_t>(n_tasks); fa.count = &ctrl->n_class[2]; fa.max_len = FUSE_MAX;
-    hipLaunchKernelGGL(medium, dim3(n_tasks), dim3(FUSE_M_THREADS), medium_lds, st, fa);
-    FIKIT_HIP(hipGetLastError());
+    hipLaunchKernelGGL(medium, dim3(static_cast<uint32_t>(n_class[2])), dim3(FUSE_M_THREADS), medium_lds, st, fa);
   }
-  tr.mark("host_sync");
-  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
-  if (int rc = status_from_bits(h.status)) return rc;
-  uint64_t n_units = 0;
+  FIKIT_HIP(hipGetLastError());
+  uint64_t n_units = 0, n_msd_tiles = 0;
   if (h.n_long > 0) {
     // Long tasks: one pass over the records orders every tile by the top ID bits (IDs out in launch order on
     // the way), then the one-workgroup kernel on units of buckets, which gathers its launches from the tiles.
-    n_units = h.n_long * MSD_SLOTS;
+    const uint64_t n_long = h.n_long;
+    n_units = n_long * MSD_SLOTS;
     if (n_units > L.max_units) return FIKIT_HIP_ERROR;   // cannot happen: a long task has more than FUSE_MAX launches
-    tr.mark("plan");
-    hipLaunchKernelGGL(k_plan_msd, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
-                       n_tasks, gflag, is_long, mtiles, wflag);
-    if (int rc = scan_u32(is_long, static_cast<uint64_t>(n_tasks) + 1, sums, nullptr, st)) return rc;
-    if (int rc = scan_u32(mtiles, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_big_tiles, st)) return rc;
-    tr.mark("host_sync");
-    if (int rc = read_ctrl(ctrl, &h, st)) return rc;
-    const uint64_t n_msd_tiles = h.n_big_tiles;
+    if (!few_tasks) {
+      tr.mark("plan");
+      hipLaunchKernelGGL(k_plan_msd, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
+                         n_tasks, gflag, is_long, mtiles, wflag);
+      if (int rc = scan_u32(is_long, static_cast<uint64_t>(n_tasks) + 1, sums, nullptr, st)) return rc;
+      if (int rc = scan_u32(mtiles, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_big_tiles, st)) return rc;
+      tr.mark("host_sync");
+      if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+    }
+    n_msd_tiles = h.n_big_tiles;
     if (n_msd_tiles == 0 || n_msd_tiles > L.max_ptiles) return FIKIT_HIP_ERROR;
     tr.mark("k_tile_partition");
     uint32_t* bucket_size = reinterpret_cast<uint32_t*>(ws + L.bsize);
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(h.n_long * MSD_SLOTS, 256)), dim3(256), 0, st, bucket_size, h.n_long * MSD_SLOTS, 0u);
+    hipLaunchKernelGGL(k_msd_clear, dim3(blocks_for(n_units, 256)), dim3(256), 0, st, bucket_size, n_units, ctrl);
     FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tile_partition), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   static_cast<int>(sizeof(PartSmem))));
     hipLaunchKernelGGL(k_tile_partition, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(PT_THREADS), sizeof(PartSmem), st, d_records,
                        d_task_offsets, n_tasks, mtiles, is_long, ids, k1, part_kg, bound, bucket_size, wflag, ctrl);
     tr.mark("k_msd_units");
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->n_class[0], static_cast<uint64_t>(6), 0u);   // the lists are reused for units
     hipLaunchKernelGGL(k_msd_units, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, d_task_offsets, n_tasks, is_long, mtiles, bucket_size, wflag,
                        ustart, ulen, utask, udcount, ubuckets, mflag, gflag, lists, static_cast<uint32_t>(n_units), ctrl);
     FusedArgs ua = fa;
@@ -388,31 +470,54 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
       hipLaunchKernelGGL(k_unit_stream, dim3(static_cast<uint32_t>(stream_most < n_units ? stream_most : n_units)), dim3(SU_THREADS),
                          sizeof(StreamSmem), st, ua, static_cast<uint32_t>(n_units), reinterpret_cast<uint2*>(e0), g0);
     }
+    // (how many units of a class there can be: two neighbours of a task are longer than FUSE_MID_MAX together, or one of
+    // them would have taken the other's first bucket)
+    auto at_most = [&](uint64_t most) { return dim3(static_cast<uint32_t>(most < n_units ? most : n_units)); };
     tr.mark("k_unit_fused_small");
     ua.list = lists; ua.count = &ctrl->n_class[0]; ua.max_len = FUSE_SMALL_MAX;
-    hipLaunchKernelGGL(small_u, dim3(static_cast<uint32_t>(n_units)), dim3(FUSE_S_THREADS), small_lds, st, ua);
+    hipLaunchKernelGGL(small_u, at_most(2 * (n / FUSE_MID_MAX) + n_long), dim3(FUSE_S_THREADS), small_lds, st, ua);
     tr.mark("k_unit_fused_mid");
     ua.list = lists + n_units; ua.count = &ctrl->n_class[1]; ua.max_len = FUSE_MID_MAX;
-    hipLaunchKernelGGL(mid_u, dim3(static_cast<uint32_t>(n_units)), dim3(512), mid_lds, st, ua);
+    hipLaunchKernelGGL(mid_u, at_most(n / (FUSE_SMALL_MAX + 1)), dim3(512), mid_lds, st, ua);
     tr.mark("k_unit_fused_medium");
     ua.list = lists + 2 * n_units; ua.count = &ctrl->n_class[2]; ua.max_len = FUSE_MAX;
-    hipLaunchKernelGGL(medium_u, dim3(static_cast<uint32_t>(n_units)), dim3(FUSE_M_THREADS), medium_lds, st, ua);
+    hipLaunchKernelGGL(medium_u, at_most(n / (FUSE_MID_MAX + 1)), dim3(FUSE_M_THREADS), medium_lds, st, ua);
     tr.mark("plan");
     hipLaunchKernelGGL(k_msd_task_rows, dim3(blocks_for(n_tasks, 64)), dim3(64), 0, st, n_tasks, is_long, mflag, udcount, urow, dcount);
     FIKIT_HIP(hipGetLastError());
-    tr.mark("host_sync");
-    if (int rc = read_ctrl(ctrl, &h, st)) return rc;
-    if (int rc = status_from_bits(h.status)) return rc;
-    if (h.n_general > 0) {
-      tr.mark("k_long_general_values");
-      hipLaunchKernelGGL(k_long_general_values, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(256), 0, st, d_records, d_task_offsets,
-                         n_tasks, mtiles, gflag, wflag, ids, k1, part_kg, e0, g0);
-    }
   }
-  const bool any_general = h.n_general > 0;
+
+  // Row offsets and rows of the tasks so far.  They are the call's if no task is left to the general path, which is known
+  // when the host has waited: the kernels look at the control block and do nothing if there is one.
+  auto gather_rows = [&](uint64_t general_done) {
+    tr.mark("k_gather_rows");
+    hipLaunchKernelGGL(k_gather_rows, dim3(xcd_grid(n_tasks)), dim3(256), 0, st, d_task_offsets, d_task_row_offsets, gflag, is_long,
+                       n_units > 0 ? 1 : 0, e1, g1, n_tasks, d_rows_out, row_capacity, general_done, ctrl);
+    if (n_units > 0)
+      hipLaunchKernelGGL(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, ustart, ulen, utask,
+                         udcount, urow, mflag, d_task_row_offsets, e1, g1, static_cast<uint32_t>(n_units), d_rows_out, row_capacity,
+                         general_done, ctrl);
+  };
+  tr.mark("row_offsets");
+  if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets, ctrl, st)) return rc;
+  gather_rows(0);
+  FIKIT_HIP(hipGetLastError());
+  tr.mark("host_sync");
+  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+  if (int rc = status_from_bits(h.status)) return rc;
+  if (h.n_general == 0) {
+    *h_n_rows = h.n_rows;
+    return h.n_rows > row_capacity ? FIKIT_ROW_CAPACITY : FIKIT_OK;
+  }
+  const uint64_t n_general = h.n_general;
+  if (n_units > 0) {
+    tr.mark("k_long_general_values");
+    hipLaunchKernelGGL(k_long_general_values, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(256), 0, st, d_records, d_task_offsets,
+                       n_tasks, mtiles, gflag, wflag, ids, k1, part_kg, e0, g0);
+  }
   uint64_t n_heads = 0;
 
-  if (any_general) {
+  {
     // General path: per-launch values are in memory (written by whichever kernel gave the task up);
     // sort by ID, find the segment heads.
     tr.mark("plan");
@@ -501,13 +606,8 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   *h_n_rows = n_rows;
   if (n_rows > row_capacity) return FIKIT_ROW_CAPACITY;
 
-  tr.mark("k_gather_rows");
-  hipLaunchKernelGGL(k_gather_rows, dim3(xcd_grid(n_tasks)), dim3(256), 0, st, d_task_offsets, dcount, gflag, is_long,
-                     n_units > 0 ? 1 : 0, e1, g1, n_tasks, d_rows_out);
-  if (n_units > 0)
-    hipLaunchKernelGGL(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, ustart, ulen, utask,
-                       udcount, urow, mflag, dcount, e1, g1, static_cast<uint32_t>(n_units), d_rows_out);
-  if (any_general && n_heads > 0) {
+  gather_rows(n_general);
+  if (n_heads > 0) {
     tr.mark("seg_starts");
     hipLaunchKernelGGL(k_seg_starts, dim3(blocks_for(L.n_words, 256)), dim3(256), 0, st, bits, word_prefix, L.n_words, n, n_heads,
                        seg_start);
@@ -605,8 +705,13 @@ uint32_t predict_parts(uint64_t n_ids, uint32_t n_tasks) {
 // What every gap fill starts with: a cleared control block, checked arguments, task roles.
 void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_task_offsets, uint64_t n_ids, uint32_t n_tasks,
                            const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets,
-                           uint64_t n_gaps) {
-  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, n_tasks);
+                           uint64_t n_gaps, uint32_t* done) {
+  if (n_tasks <= GF_BEGIN_ITEMS && n_scenarios <= GF_BEGIN_ITEMS) {
+    hipLaunchKernelGGL(k_gf_begin, dim3(1), dim3(GF_BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n_ids, d_hp_task, d_lp_task,
+                       static_cast<uint32_t>(n_scenarios), d_gap_offsets, n_gaps, b.role, b.lp_total, done, b.ctrl);
+    return;
+  }
+  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, done, n_tasks);
   hipLaunchKernelGGL(k_gf_check, dim3(blocks_for(n_scenarios > n_tasks ? n_scenarios : n_tasks, 256)), dim3(256), 0, st, d_task_offsets,
                      n_tasks, n_ids, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, b.role, b.ctrl);
 }
@@ -655,12 +760,12 @@ int gapfill_wide_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t
                          const fikit_row* d_rows, const uint64_t* d_task_row_offsets, const uint32_t* d_hp_task,
                          const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
                          const uint64_t* d_gap_offsets, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* d_lp_completion_ns,
-                         uint64_t* d_lp_placed) {
+                         uint64_t* d_lp_placed, int32_t* d_status) {
   hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
                      d_task_row_offsets, b.role, b.pe, b.pg, b.open, static_cast<uint32_t>(h_params->predictor), b.ctrl);
   hipLaunchKernelGGL(k_gf_walk, dim3(blocks_for(n_scenarios, 256 / WAVE)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
                      n_scenarios, d_gap_offsets, b.pe, b.pg, b.open, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,
-                     d_lp_completion_ns, d_lp_placed, b.ctrl);
+                     d_lp_completion_ns, d_lp_placed, d_status, b.ctrl);
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
 }
@@ -709,9 +814,10 @@ int fikit_gapfill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint32_
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   // The element counts live on the device: total launches and total gaps.
   uint64_t n_ids = 0, n_gaps = 0;
-  FIKIT_HIP(hipMemcpyAsync(&n_ids, d_task_offsets + n_tasks, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipMemcpyAsync(&n_gaps, d_gap_offsets + n_scenarios, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipStreamSynchronize(st));
+  Reads counts(st);
+  if (int rc = counts.add(&n_ids, d_task_offsets + n_tasks, 8)) return rc;
+  if (int rc = counts.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
+  if (int rc = counts.wait()) return rc;
   if (n_ids >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if (n_ids > 0 && (!d_ids || !d_rows)) return FIKIT_INVALID_ARG;
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
@@ -720,14 +826,14 @@ int fikit_gapfill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint32_
   const GapfillBuffers b(static_cast<unsigned char*>(d_workspace), n_ids, n_tasks);
   Tracer tr(st);
   tr.mark("gf_setup");
-  gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+  gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, nullptr);
   if (int rc = gapfill_enqueue(st, tr, b, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
                                n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns, d_lp_completion_ns,
                                d_lp_placed, true, nullptr))
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&] {
     return gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task, n_scenarios,
-                                h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed);
+                                h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, nullptr);
   });
 }
 
@@ -765,10 +871,13 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
     return fikit_profile(d_records, n_records, d_task_offsets, n_tasks, d_ids_out, d_rows_out, row_capacity, d_task_row_offsets,
                          h_n_rows, ws, prof_bytes, hip_stream);
 
-  uint64_t n_gaps = 0;
-  FIKIT_HIP(hipMemcpyAsync(&n_gaps, d_gap_offsets + n_scenarios, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipStreamSynchronize(st));
-  if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
+  uint64_t n_gaps = ANY_GAPS;   // (the number matters only where a buffer is missing, or for the lane walk)
+  if (!d_fill_count || !d_filled_ns || n_scenarios >= GF_LANES_MIN_SCENARIOS) {
+    Reads r(st);
+    if (int rc = r.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
+    if (int rc = r.wait()) return rc;
+    if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
+  }
 
   // 1. the gap fill's checks and task roles; 2. the profile, whose one-workgroup kernels also write the predictions
   // of the tasks that the scenarios use; 3. the predictions of the remaining tasks, and the fill.
@@ -779,8 +888,7 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
   {
     Tracer tr(st);
     tr.mark("gf_setup");
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, done, static_cast<uint64_t>(n_tasks), 0u);
-    gapfill_check_enqueue(st, b, d_task_offsets, n_records, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+    gapfill_check_enqueue(st, b, d_task_offsets, n_records, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, done);
     FIKIT_HIP(hipGetLastError());
   }
   if (int rc = profile_run(d_records, n_records, d_task_offsets, n_tasks, d_ids_out, d_rows_out, row_capacity, d_task_row_offsets,
@@ -793,7 +901,7 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&] {
     return gapfill_wide_enqueue(st, b, d_ids_out, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task, d_lp_task,
-                                n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed);
+                                n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, nullptr);
   });
 }
 
@@ -830,14 +938,9 @@ int static_scratch_of_current_device(unsigned char** out) {
   return FIKIT_OK;
 }
 
-// The status a finished call would return, from the error bits its kernels left.
-__global__ void k_publish_status(const Ctrl* ctrl, int32_t* status_out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const uint32_t bits = ctrl->status;
-  int32_t st = FIKIT_OK;
-  if (bits & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) st = FIKIT_INVALID_ARG;
-  else if (bits & ERR_UNKNOWN_ID) st = FIKIT_UNKNOWN_ID;
-  *status_out = st;
+// The status of a call without scenarios.
+__global__ void k_publish_ok(int32_t* status_out) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) *status_out = FIKIT_OK;
 }
 
 }  // namespace
@@ -868,19 +971,19 @@ int fikit_gapfill_static(const uint64_t* d_ids, uint64_t n_ids, const uint64_t* 
   Tracer tr(st, false);   // (recording events would allocate)
   const GapfillBuffers b(ws, n_ids, n_tasks);
   if (n_scenarios == 0) {
-    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, b.ctrl);
+    hipLaunchKernelGGL(k_publish_ok, dim3(1), dim3(64), 0, st, d_status);
   } else {
-    gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+    gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, nullptr);
     if (int rc = gapfill_enqueue(st, tr, b, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
                                  n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns, d_lp_completion_ns,
                                  d_lp_placed, false, nullptr))
       return rc;
     // (whether a prediction needs 64 bits is only known on the device, and nothing is waited for here)
     if (int rc = gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
-                                      n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed))
+                                      n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
+                                      d_status))
       return rc;
   }
-  hipLaunchKernelGGL(k_publish_status, dim3(1), dim3(64), 0, st, reinterpret_cast<const Ctrl*>(ws), d_status);
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
 }
@@ -941,9 +1044,10 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint64_t n_ids = 0, n_gaps = 0;
-  FIKIT_HIP(hipMemcpyAsync(&n_ids, d_task_offsets + n_tasks, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipMemcpyAsync(&n_gaps, d_gap_offsets + n_scenarios, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipStreamSynchronize(st));
+  Reads counts(st);
+  if (int rc = counts.add(&n_ids, d_task_offsets + n_tasks, 8)) return rc;
+  if (int rc = counts.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
+  if (int rc = counts.wait()) return rc;
   if (n_ids >= MAX_ELEMS || n_gaps >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if (n_ids > 0 && (!d_ids || !d_rows || !d_actual_gap_ns)) return FIKIT_INVALID_ARG;
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
@@ -952,7 +1056,7 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   const GapfillBuffers b(static_cast<unsigned char*>(d_workspace), n_ids, n_tasks);
   Tracer tr(st);
   tr.mark("gf_setup");
-  gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps);
+  gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, nullptr);
   tr.mark("k_gf_predict32");
   hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                      n_tasks, d_rows, d_task_row_offsets, b.role, d_actual_gap_ns, b.lp_e, b.hp_eg, b.lp_total,
@@ -1007,10 +1111,11 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint64_t n_ids = 0, n_gaps = 0, n_entries = 0;
-  FIKIT_HIP(hipMemcpyAsync(&n_ids, d_task_offsets + n_tasks, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipMemcpyAsync(&n_gaps, d_gap_offsets + n_scenarios, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipMemcpyAsync(&n_entries, d_lp_offsets + n_scenarios, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipStreamSynchronize(st));
+  Reads counts(st);
+  if (int rc = counts.add(&n_ids, d_task_offsets + n_tasks, 8)) return rc;
+  if (int rc = counts.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
+  if (int rc = counts.add(&n_entries, d_lp_offsets + n_scenarios, 8)) return rc;
+  if (int rc = counts.wait()) return rc;
   if (n_ids >= MAX_ELEMS || n_gaps >= MAX_ELEMS || n_entries >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if (n_ids > 0 && (!d_ids || !d_rows)) return FIKIT_INVALID_ARG;
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
@@ -1029,7 +1134,8 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
 
   Tracer tr(st);
   tr.mark("pf_setup");
-  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, ctrl, role, lp_total, n_tasks);
+  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, ctrl, role, lp_total,
+                     static_cast<uint32_t*>(nullptr), n_tasks);
   hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
   hipLaunchKernelGGL(k_pf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
                      d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, n_entries, d_gap_offsets, role, ctrl);
@@ -1124,8 +1230,9 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint64_t n_gaps = 0;
   if (n_scenarios > 0) {
-    FIKIT_HIP(hipMemcpyAsync(&n_gaps, d_gap_offsets + n_scenarios, 8, hipMemcpyDeviceToHost, st));
-    FIKIT_HIP(hipStreamSynchronize(st));
+    Reads r(st);
+    if (int rc = r.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
+    if (int rc = r.wait()) return rc;
     if (n_gaps >= MAX_ELEMS || (n_gaps > 0 && !d_filled_ns)) return FIKIT_INVALID_ARG;
   }
   unsigned char* ws = static_cast<unsigned char*>(d_workspace);
@@ -1137,8 +1244,7 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
 
   Tracer tr(st);
   tr.mark("pair_setup");
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks, top_filled, soonest, best_scenario);
+  hipLaunchKernelGGL(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks, top_filled, soonest, best_scenario, ctrl);
   if (n_scenarios > 0) {
     tr.mark("k_pair_sum");
     hipLaunchKernelGGL(k_pair_sum, dim3(static_cast<uint32_t>(n_scenarios)), dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task,
@@ -1181,9 +1287,10 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint64_t na = 0, nb = 0;
-  FIKIT_HIP(hipMemcpyAsync(&na, d_task_row_offsets_a + n_tasks, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipMemcpyAsync(&nb, d_task_row_offsets_b + n_tasks, 8, hipMemcpyDeviceToHost, st));
-  FIKIT_HIP(hipStreamSynchronize(st));
+  Reads counts(st);
+  if (int rc = counts.add(&na, d_task_row_offsets_a + n_tasks, 8)) return rc;
+  if (int rc = counts.add(&nb, d_task_row_offsets_b + n_tasks, 8)) return rc;
+  if (int rc = counts.wait()) return rc;
   if (na >= MAX_ELEMS || nb >= MAX_ELEMS || na + nb >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if ((na > 0 && !d_rows_a) || (nb > 0 && !d_rows_b)) return FIKIT_INVALID_ARG;
 
@@ -1197,27 +1304,20 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   tr.mark("merge_count");
   const uint32_t grid = n_tasks < 65536u ? n_tasks : 65536u;
   hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_row_offsets_a, n_tasks, na, ctrl);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_row_offsets_b, n_tasks, nb, ctrl);
   hipLaunchKernelGGL(k_merge<0>, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
                      d_task_row_offsets_b, n_tasks, dcount, static_cast<const uint64_t*>(nullptr),
-                     static_cast<fikit_row*>(nullptr), ctrl);
-  if (int rc = scan_u32(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_rows, st)) return rc;
-  hipLaunchKernelGGL(k_widen_offsets, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, dcount,
-                     static_cast<uint64_t>(n_tasks) + 1, d_task_row_offsets_out);
+                     static_cast<fikit_row*>(nullptr), na, nb, row_capacity, ctrl);
+  if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets_out, ctrl, st)) return rc;
+  tr.mark("k_merge_rows");   // (does nothing if a check failed or the rows are too many)
+  hipLaunchKernelGGL(k_merge<1>, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
+                     d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, na, nb, row_capacity, ctrl);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};
   if (int rc = read_ctrl(ctrl, &h, st)) return rc;
   if (int rc = status_from_bits(h.status)) return rc;
   *h_n_rows = h.n_rows;
-  if (h.n_rows > row_capacity) return FIKIT_ROW_CAPACITY;
-  tr.mark("k_merge_rows");
-  hipLaunchKernelGGL(k_merge<1>, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
-                     d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, ctrl);
-  FIKIT_HIP(hipGetLastError());
-  FIKIT_HIP(hipStreamSynchronize(st));
-  return FIKIT_OK;
+  return h.n_rows > row_capacity ? FIKIT_ROW_CAPACITY : FIKIT_OK;
 }
 
 }  // extern "C"

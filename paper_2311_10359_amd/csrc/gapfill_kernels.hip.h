@@ -13,35 +13,80 @@
 
 namespace fikit {
 
-// Start values of a call: the control block, and per task no role and no queue total.
-__global__ void k_gf_clear(Ctrl* ctrl, uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t n_tasks) {
+// Start values of a call: the control block, and per task no role, no queue total and (done may be null) no predictions.
+__device__ __forceinline__ void gf_clear_task(uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t* __restrict__ done,
+                                              uint32_t t) {
+  role[t] = 0;
+  lp_total[t] = 0;
+  if (done) done[t] = 0;
+}
+__global__ void k_gf_clear(Ctrl* ctrl, uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t* __restrict__ done,
+                           uint32_t n_tasks) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[t] = 0;
-  if (t < n_tasks) { role[t] = 0; lp_total[t] = 0; }
+  if (t < n_tasks) gf_clear_task(role, lp_total, done, t);
 }
 
 // Checks the task offsets (first 0, non-decreasing, last == n_ids) and the scenario arguments (n_gaps: the number of
-// per-gap output slots the host sized its buffers for), and records in role[t] how each task is used.  One thread per
-// task and per scenario; nothing is looked up at an offset here, so the two checks need not wait for each other.
+// per-gap output slots the host sized its buffers for, ANY_GAPS if it does not look at it), and records in role[t] how each
+// task is used.  One thread per task and per scenario; nothing is looked up at an offset here, so the two checks need not
+// wait for each other.  Returns what is wrong.
+constexpr uint64_t ANY_GAPS = ~0ull;
+__device__ __forceinline__ uint32_t gf_check_item(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids,
+                                                  const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
+                                                  uint64_t n_scen, const uint64_t* __restrict__ gap_off, uint64_t n_gaps,
+                                                  uint32_t* __restrict__ role, uint64_t s) {
+  uint32_t wrong = 0;
+  if (s < n_tasks) {
+    const uint64_t a = off[s], b = off[s + 1];
+    if (a > b || b > n_ids || (s == 0 && a != 0) || (s + 1 == n_tasks && b != n_ids)) wrong |= ERR_OFFSETS;
+  }
+  if (s >= n_scen) return wrong;
+  if (s + 1 == n_scen && n_gaps != ANY_GAPS && gap_off[n_scen] != n_gaps) wrong |= ERR_GAP_OFFSETS;
+  const uint32_t hp = hp_task[s], lp = lp_task[s];
+  if (hp >= n_tasks || lp >= n_tasks) return wrong | ERR_TASK_INDEX;
+  const uint64_t H = off[hp + 1] - off[hp];
+  const uint64_t want = H > 0 ? H - 1 : 0;
+  if (gap_off[s + 1] < gap_off[s] || gap_off[s + 1] - gap_off[s] != want || (s == 0 && gap_off[0] != 0)) wrong |= ERR_GAP_OFFSETS;
+  // (a task heads or serves many scenarios: the word is only touched while a bit is still missing)
+  if (!(__hip_atomic_load(&role[hp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ROLE_HP)) atomicOr(&role[hp], ROLE_HP);
+  if (!(__hip_atomic_load(&role[lp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ROLE_LP)) atomicOr(&role[lp], ROLE_LP);
+  return wrong;
+}
 __global__ void k_gf_check(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const uint32_t* __restrict__ hp_task,
                            const uint32_t* __restrict__ lp_task, uint64_t n_scen, const uint64_t* __restrict__ gap_off,
                            uint64_t n_gaps, uint32_t* __restrict__ role, Ctrl* ctrl) {
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (s < n_tasks) {
-    const uint64_t a = off[s], b = off[s + 1];
-    if (a > b || b > n_ids || (s == 0 && a != 0) || (s + 1 == n_tasks && b != n_ids)) atomicOr(&ctrl->status, ERR_OFFSETS);
-  }
-  if (s >= n_scen) return;
-  if (s + 1 == n_scen && gap_off[n_scen] != n_gaps) atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
-  const uint32_t hp = hp_task[s], lp = lp_task[s];
-  if (hp >= n_tasks || lp >= n_tasks) { atomicOr(&ctrl->status, ERR_TASK_INDEX); return; }
-  const uint64_t H = off[hp + 1] - off[hp];
-  const uint64_t want = H > 0 ? H - 1 : 0;
-  if (gap_off[s + 1] < gap_off[s] || gap_off[s + 1] - gap_off[s] != want || (s == 0 && gap_off[0] != 0))
-    atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
-  // (a task heads or serves many scenarios: the word is only touched while a bit is still missing)
-  if (!(__hip_atomic_load(&role[hp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ROLE_HP)) atomicOr(&role[hp], ROLE_HP);
-  if (!(__hip_atomic_load(&role[lp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ROLE_LP)) atomicOr(&role[lp], ROLE_LP);
+  const uint32_t wrong = gf_check_item(off, n_tasks, n_ids, hp_task, lp_task, n_scen, gap_off, n_gaps, role, s);
+  if (wrong) atomicOr(&ctrl->status, wrong);
+}
+
+// Both of the above in one workgroup, for so few tasks and scenarios that a second launch costs more (4.5 us) than the
+// chip's other units save.
+constexpr uint32_t GF_BEGIN_ITEMS = 2048;
+constexpr int GF_BEGIN_THREADS = 1024;
+__global__ void __launch_bounds__(GF_BEGIN_THREADS)
+k_gf_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const uint32_t* __restrict__ hp_task,
+           const uint32_t* __restrict__ lp_task, uint32_t n_scen, const uint64_t* __restrict__ gap_off, uint64_t n_gaps,
+           uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t* __restrict__ done, Ctrl* ctrl) {
+  __shared__ uint32_t status;
+  const uint32_t tid = threadIdx.x, items = n_tasks > n_scen ? n_tasks : n_scen;
+  if (tid == 0) status = 0;
+  for (uint32_t t = tid; t < n_tasks; t += GF_BEGIN_THREADS) gf_clear_task(role, lp_total, done, t);
+  __threadfence();     // (the roles are set by atomics, which must not overtake the zeros)
+  __syncthreads();
+  uint32_t wrong = 0;
+  for (uint32_t s = tid; s < items; s += GF_BEGIN_THREADS)
+    wrong |= gf_check_item(off, n_tasks, n_ids, hp_task, lp_task, n_scen, gap_off, n_gaps, role, s);
+  if (wrong) atomicOr(&status, wrong);
+  __syncthreads();
+  if (tid < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[tid] = tid == 0 ? status : 0u;
+}
+
+// The status a finished call would return, from the error bits its kernels left (fikit_gapfill_static).
+__device__ __forceinline__ int32_t gf_status(uint32_t bits) {
+  if (bits & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return FIKIT_INVALID_ARG;
+  return bits & ERR_UNKNOWN_ID ? FIKIT_UNKNOWN_ID : FIKIT_OK;
 }
 
 constexpr int PRED_THREADS = 256;
@@ -208,7 +253,9 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
           uint64_t n_scen, const uint64_t* __restrict__ gap_off, const int64_t* __restrict__ pe,
           const int64_t* __restrict__ pg, const int64_t* __restrict__ open, int64_t margin, int64_t min_gap,
           uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
-          uint64_t* __restrict__ placed_out, const Ctrl* ctrl) {
+          uint64_t* __restrict__ placed_out, int32_t* __restrict__ status_out, const Ctrl* ctrl) {
+  // (status_out may be null: the call's status, which no kernel changes from here on)
+  if (status_out && blockIdx.x == 0 && threadIdx.x == 0) *status_out = gf_status(ctrl->status);
   if (ctrl->status || !ctrl->wide) return;
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * (256 / WAVE) + threadIdx.x / WAVE;
   if (s >= n_scen) return;  // whole waves leave together

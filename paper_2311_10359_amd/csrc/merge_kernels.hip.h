@@ -73,13 +73,14 @@ template <int MODE>
 __global__ void __launch_bounds__(MERGE_THREADS)
 k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, const fikit_row* __restrict__ b,
         const uint64_t* __restrict__ b_off, uint32_t n_tasks, uint32_t* __restrict__ dcount,
-        const uint64_t* __restrict__ row_off, fikit_row* __restrict__ out, Ctrl* ctrl) {
+        const uint64_t* __restrict__ row_off, fikit_row* __restrict__ out, uint64_t n_a, uint64_t n_b, uint64_t capacity, Ctrl* ctrl) {
   __shared__ MergeSmem sm;
-  if (ctrl->status) return;    // (the offsets have been checked by now: with valid offsets every row read is in bounds)
+  if (MODE == 1 && (ctrl->status || ctrl->n_rows > capacity)) return;   // (enqueued before the host knows)
   const uint32_t tid = threadIdx.x;
   for (uint32_t t = blockIdx.x; t < n_tasks; t += gridDim.x) {
     const uint64_t a0 = a_off[t], a1 = a_off[t + 1], b0 = b_off[t], b1 = b_off[t + 1];
-    if (a1 < a0 || b1 < b0 || a1 - a0 >= (1ull << 32) || b1 - b0 >= (1ull << 32) || (t == 0 && (a0 != 0 || b0 != 0))) {
+    // (n_a, n_b: the rows there are; with this every row read is in bounds, whatever the other offsets say)
+    if (a1 < a0 || b1 < b0 || a1 > n_a || b1 > n_b || a1 - a0 >= (1ull << 32) || b1 - b0 >= (1ull << 32) || (t == 0 && (a0 != 0 || b0 != 0))) {
       if (tid == 0) { atomicOr(&ctrl->status, ERR_OFFSETS); if (MODE == 0) dcount[t] = 0; }
       continue;    // (the same for all threads)
     }

@@ -55,6 +55,13 @@ __global__ void k_plan_msd(const uint64_t* __restrict__ off, uint32_t n_tasks, c
   mtiles[t] = tiles;
 }
 
+// What the partition pass adds up, and the work lists' lengths (which are reused for units).
+__global__ void k_msd_clear(uint32_t* __restrict__ bucket_size, uint64_t count, Ctrl* ctrl) {
+  const uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < count) bucket_size[i] = 0;
+  if (i < 6) ctrl->n_class[i] = 0;
+}
+
 struct PartSmem {
   uint64_t stage[PT_TILE];   // the tile's IDs in bucket order, then its values
   uint32_t cnt[PT_WAVES][256];
@@ -321,8 +328,9 @@ __global__ void k_msd_task_rows(uint32_t n_tasks, const uint32_t* __restrict__ l
 __global__ void __launch_bounds__(256)
 k_gather_units(const uint32_t* __restrict__ ustart, const uint32_t* __restrict__ ulen, const uint32_t* __restrict__ utask,
                const uint32_t* __restrict__ udcount, const uint32_t* __restrict__ urow, const uint32_t* __restrict__ mflag,
-               const uint32_t* __restrict__ row_off32, const int64_t* __restrict__ stage_a, const int64_t* __restrict__ stage_b,
-               uint32_t n_units, fikit_row* __restrict__ rows) {
+               const uint64_t* __restrict__ row_off, const int64_t* __restrict__ stage_a, const int64_t* __restrict__ stage_b,
+               uint32_t n_units, fikit_row* __restrict__ rows, uint64_t capacity, uint64_t general_done, const Ctrl* ctrl) {
+  if (!rows_final(ctrl, capacity, general_done)) return;
   const uint32_t u = xcd_item(blockIdx.x, n_units);
   if (u >= n_units) return;
   const uint32_t m = ulen[u];
@@ -330,7 +338,7 @@ k_gather_units(const uint32_t* __restrict__ ustart, const uint32_t* __restrict__
   const uint32_t t = utask[u];
   if (!mflag[t]) return;
   const uint32_t D = udcount[u];
-  uint64_t* out = reinterpret_cast<uint64_t*>(rows + row_off32[t] + urow[u]);
+  uint64_t* out = reinterpret_cast<uint64_t*>(rows + row_off[t] + urow[u]);
   const uint64_t base = ustart[u];
   for (uint32_t x = threadIdx.x; x < D * 16; x += 256) {
     const uint32_t j = x >> 4, f = x & 15;

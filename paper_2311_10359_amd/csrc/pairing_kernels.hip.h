@@ -69,10 +69,11 @@ __global__ void k_pair_first(const uint32_t* __restrict__ hp_task, uint64_t n_sc
   if (scen_filled[s] == top_filled[hp] && completion[s] == soonest[hp]) atomicMin(&best_scenario[hp], static_cast<unsigned long long>(s));
 }
 
-// Start values per task (no memset: the stream may be under graph capture).
+// The control block and start values per task (no memset: the stream may be under graph capture).
 __global__ void k_pair_init(uint32_t n_tasks, long long* __restrict__ top_filled, long long* __restrict__ soonest,
-                            unsigned long long* __restrict__ best_scenario) {
+                            unsigned long long* __restrict__ best_scenario, Ctrl* ctrl) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[t] = 0;
   if (t >= n_tasks) return;
   top_filled[t] = INT64_MIN;
   soonest[t] = INT64_MAX;

@@ -63,6 +63,66 @@ __global__ void k_classify(const uint64_t* __restrict__ off, uint32_t n_tasks, u
   }
 }
 
+// Everything that precedes the launches' own kernels, for up to BEGIN_TASKS tasks in one workgroup: what k_clear_ctrl,
+// k_validate_offsets, k_classify and (for the long tasks) k_plan_msd and its two prefix sums do.  With few tasks all of
+// these only wait for each other: a kernel that depends on the one before it costs 4.5 us however little it does (three
+// launches, ten with long tasks; this one takes 2.7 us for 2 tasks and 4.2 us for 256), and the number of the long tasks'
+// tiles is known a host round trip earlier.  With more tasks the calls are so long that it no longer matters.
+constexpr uint32_t BEGIN_TASKS = 2048;
+constexpr int BEGIN_THREADS = 1024;
+__global__ void __launch_bounds__(BEGIN_THREADS)
+k_profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n, uint32_t len_small, uint32_t len_mid, uint32_t len_max,
+                uint32_t tile, uint32_t* __restrict__ gflag, uint32_t* __restrict__ dcount, uint32_t* __restrict__ lists,
+                uint32_t* __restrict__ long_prefix, uint32_t* __restrict__ tile_prefix, uint32_t* __restrict__ wflag, Ctrl* ctrl) {
+  __shared__ uint32_t lds[16], listed[3], bad;
+  const uint32_t tid = threadIdx.x;
+  if (tid < 3) listed[tid] = 0;
+  if (tid == 3) bad = 0;
+  __syncthreads();
+  bool wrong = n_tasks == 0 && tid == 0 && (off[0] != 0 || n != 0);
+  for (uint32_t t = tid; t < n_tasks; t += BEGIN_THREADS) {
+    const uint64_t a = off[t], b = off[t + 1];
+    wrong |= a > b || b > n || (t == 0 && a != 0) || (t + 1 == n_tasks && b != n);
+  }
+  if (wrong) bad = 1;
+  __syncthreads();
+  uint32_t longs = 0, tiles = 0;
+  for (uint32_t t0 = 0; !bad && t0 <= n_tasks; t0 += BEGIN_THREADS) {   // (one entry more than tasks)
+    const uint32_t t = t0 + tid;
+    uint32_t c = 3, is_long = 0, my_tiles = 0;
+    if (t < n_tasks) {
+      const uint64_t len = off[t + 1] - off[t];
+      is_long = len > len_max ? 1u : 0u;
+      my_tiles = is_long ? static_cast<uint32_t>((len + tile - 1) / tile) : 0u;
+      gflag[t] = is_long;
+      wflag[t] = 0;
+      if (!is_long && len > 0) c = len <= len_small ? 0u : (len <= len_mid ? 1u : 2u);
+    }
+    for (uint32_t k = 0; k < 3; ++k) {
+      const uint32_t pos = wave_append(&listed[k], c == k);
+      if (c == k) lists[static_cast<uint64_t>(k) * n_tasks + pos] = t;
+    }
+    uint32_t more_longs, more_tiles;
+    const uint32_t l = block_excl_scan_1024(is_long, lds, more_longs), x = block_excl_scan_1024(my_tiles, lds, more_tiles);
+    if (t <= n_tasks) {
+      dcount[t] = 0;
+      long_prefix[t] = longs + l;
+      tile_prefix[t] = tiles + x;
+    }
+    longs += more_longs;
+    tiles += more_tiles;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    Ctrl c{};
+    c.status = bad ? ERR_OFFSETS : 0u;
+    c.n_big_tiles = tiles;
+    c.n_general = c.n_long = longs;
+    for (int k = 0; k < 3; ++k) c.n_class[k] = listed[k];
+    *ctrl = c;
+  }
+}
+
 // Execution time and idle time of every launch as they stand in the trace (Section 3.2, "Measuring the
 // execution and idle time of kernel"); task boundaries are put right by k_measure_task_ends afterwards.
 __global__ void __launch_bounds__(256)

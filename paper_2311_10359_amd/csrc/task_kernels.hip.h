@@ -1044,15 +1044,24 @@ k_task_fused(const FusedArgs A) {
   if (tid == 0) dcount[unit] = D;
 }
 
+// May rows be written?  Not for a call that has failed, with more rows than there is room for, or with tasks that are left to
+// the general path (general_done: how many of those have been counted): the host enqueues the gathers before it knows.
+__device__ __forceinline__ bool rows_final(const Ctrl* ctrl, uint64_t capacity, uint64_t general_done) {
+  return !ctrl->status && ctrl->n_general == general_done && ctrl->n_rows <= capacity;
+}
+
 // Moves a task's staged rows to their final place once the row offsets are known.
 __global__ void __launch_bounds__(256)
-k_gather_rows(const uint64_t* __restrict__ off, const uint32_t* __restrict__ row_off32, const uint32_t* __restrict__ gflag,
+k_gather_rows(const uint64_t* __restrict__ off, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ gflag,
               const uint32_t* __restrict__ long_prefix, int have_long, const int64_t* __restrict__ stage_a,
-              const int64_t* __restrict__ stage_b, uint32_t n_tasks, fikit_row* __restrict__ rows) {
+              const int64_t* __restrict__ stage_b, uint32_t n_tasks, fikit_row* __restrict__ rows, uint64_t capacity,
+              uint64_t general_done, const Ctrl* ctrl) {
+  if (!rows_final(ctrl, capacity, general_done)) return;
   const uint32_t t = xcd_item(blockIdx.x, n_tasks);
   if (t >= n_tasks || gflag[t]) return;
   if (have_long && long_prefix[t + 1] != long_prefix[t]) return;   // a long task: its units are gathered separately
-  const uint32_t r0 = row_off32[t], D = row_off32[t + 1] - r0;
+  const uint64_t r0 = row_off[t];
+  const uint32_t D = static_cast<uint32_t>(row_off[t + 1] - r0);
   if (D == 0) return;
   const uint64_t base = off[t];
   const uint32_t m = static_cast<uint32_t>(off[t + 1] - base);
