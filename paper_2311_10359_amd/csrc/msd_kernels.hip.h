@@ -11,7 +11,7 @@
 //                     inside the tile's own index range, with the tile's table of bucket boundaries.
 //                     Nothing depends on another tile: no counters, no waiting, one read of the records.
 //   k_msd_units       bucket sizes of a task (summed over its tiles) -> units of at most FUSE_MID_MAX
-//                     launches (or one larger bucket)
+//                     launches (FUSE_SMALL_MAX in shorter tasks; or one larger bucket)
 //   k_task_fused      (task_kernels.hip.h, unit form) reads a unit's launches as one run per tile
 //   k_msd_task_rows / k_gather_units   row counts and final placement of the units' rows
 //   k_long_general_values   per-launch values of long tasks that had to be left to the general path
@@ -34,9 +34,15 @@ constexpr int PT_LB = 2;                             // rounds of record loads i
 // A bucket of more than FUSE_MAX launches (one frequent ID) is streamed by k_unit_stream if its task has at least this
 // many launches; otherwise the task is sorted.
 constexpr uint64_t STREAM_MIN = 1u << 18;
+// Tasks of up to this many launches are cut into units of at most FUSE_SMALL_MAX launches, longer ones (whose buckets alone may
+// be longer) of FUSE_MID_MAX.  fikit_profile, uniform over 300 IDs, in ms with the smaller / the larger units:
+//   1024 tasks of 65,536 launches: 2.62 / 2.79   1000 of 100,000: 3.03 / 3.98   50 of 131,072: 0.298 / 0.386
+//   256 of 262,144: 2.03 / 2.01   16 of 1,048,576: 0.66 / 0.63
+constexpr uint64_t UNIT_SMALL_TASK = 1u << 17;
 constexpr uint32_t STREAM_HUGE = 1u << 16;           // streamed units beyond this are started first
 constexpr uint32_t PT_ROWS = MSD_SLOTS + 1;          // rows of a task's boundary table: bucket 0 .. 256 (= the tile's end)
 static_assert(PT_TILE <= 0xffffu, "bucket boundaries inside a tile are stored in 16 bits");
+static_assert(MSD_SLOTS == 256, "the scans over a task's slots are those of a 256-thread block");
 static_assert(MSD_SLOTS * FUSE_MAX / PT_TILE <= UNIT_RUNS_MAX, "a unit's run table holds one run per tile of its task");
 
 // is_long[t] = 1 for tasks that take this path, mtiles[t] = their number of tiles; both arrays have
@@ -198,9 +204,9 @@ k_tile_partition(const fikit_launch* __restrict__ rec, const uint64_t* __restric
 
 // One workgroup per task: packs a long task's ID buckets into units (a bucket of more than FUSE_MAX launches is a
 // unit of its own).  A task with such a bucket and fewer than STREAM_MIN launches, or with an execution or idle time
-// that does not fit 32 bits, keeps the general path (mflag 0); otherwise mflag 1 and gflag cleared.  Thread d sums bucket d over the task's tiles, one thread
-// packs (a short sequential pass over at most 256 buckets in LDS), and all threads together write the unit
-// slots and the work lists.  bucket_size: the task's bucket sizes as the tiles added them up.
+// that does not fit 32 bits, keeps the general path (mflag 0); otherwise mflag 1 and gflag cleared.  Every thread finds where a
+// unit that starts at its bucket would end and the next one start, one thread follows these from unit to unit, and all threads
+// together write the unit slots and the work lists.  bucket_size: the task's bucket sizes as the tiles added them up.
 __global__ void __launch_bounds__(MSD_SLOTS)
 k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* __restrict__ long_prefix,
             const uint32_t* __restrict__ tile_prefix, const uint32_t* __restrict__ bucket_size, const uint32_t* __restrict__ wflag,
@@ -208,44 +214,48 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
             uint32_t* __restrict__ udcount, uint32_t* __restrict__ ubuckets, uint32_t* __restrict__ mflag,
             uint32_t* __restrict__ gflag, uint32_t* __restrict__ lists, uint32_t list_stride, Ctrl* ctrl) {
   __shared__ uint32_t bstart[MSD_SLOTS + 1];   // where each bucket starts inside the task (in bucket order)
-  __shared__ uint32_t us[MSD_SLOTS], ul[MSD_SLOTS], ub[MSD_SLOTS];
+  __shared__ uint32_t after[MSD_SLOTS], follows[MSD_SLOTS + 1], ufirst[MSD_SLOTS];
   __shared__ uint32_t aux[8];
-  __shared__ uint32_t n_used, all_fit;
+  __shared__ uint32_t n_used, too_large;
   const uint32_t t = blockIdx.x, d = threadIdx.x;
   if (t >= n_tasks) return;
   if (d == 0) mflag[t] = 0;
   if (long_prefix[t + 1] == long_prefix[t]) return;   // not a long task
   const uint32_t o = long_prefix[t];
   const uint64_t task_start = off[t], len = off[t + 1] - task_start;
-  constexpr uint32_t nb = MSD_SLOTS;
   const uint32_t tiles_t = tile_prefix[t + 1] - tile_prefix[t];
   const uint32_t size = bucket_size[static_cast<uint64_t>(o) * MSD_SLOTS + d];
   uint32_t total;
   const uint32_t before = block_excl_scan_256(size, aux, total);
   bstart[d] = before;
-  if (d == 0) bstart[MSD_SLOTS] = total;
+  if (d == 0) { bstart[MSD_SLOTS] = total; too_large = 0; follows[MSD_SLOTS] = MSD_SLOTS; }
+  __syncthreads();
+  const bool may_stream = len >= STREAM_MIN;
+  const uint32_t unit_max = len <= UNIT_SMALL_TASK ? FUSE_SMALL_MAX : FUSE_MID_MAX;
+  const bool single = tiles_t > UNIT_RUNS_MAX;   // more runs than a unit's table holds: every bucket is streamed
+  if (size > FUSE_MAX && !may_stream) too_large = 1;
+  // first index in (lo, MSD_SLOTS] at which the buckets before it hold more than `most` launches, or MSD_SLOTS + 1
+  auto passes = [&](uint32_t lo, uint32_t most) {
+    uint32_t hi = MSD_SLOTS + 1;
+    while (hi - lo > 1) { const uint32_t mid = (lo + hi) >> 1; if (bstart[mid] > most) hi = mid; else lo = mid; }
+    return hi;
+  };
+  // A unit that starts at bucket d ends before the bucket that makes it longer than unit_max, but holds one bucket at least.
+  {
+    const uint32_t end = single ? d + 1 : passes(d, before + unit_max) - 1;
+    after[d] = end > d ? end : d + 1;
+  }
+  __syncthreads();
+  {   // the next unit starts at the first bucket from there on that is not empty
+    const uint32_t e = after[d];
+    follows[d] = e < MSD_SLOTS ? passes(e, bstart[e]) - 1 : MSD_SLOTS;
+  }
   __syncthreads();
   if (d == 0) {
     uint32_t u = 0;
-    const bool may_stream = len >= STREAM_MIN;
-    const bool single = tiles_t > UNIT_RUNS_MAX;   // more runs than a unit's table holds: every bucket is streamed
-    bool ok = total == len && (!single || may_stream) && wflag[t] == 0;
-    uint32_t cur_first = 0, cur_len = 0;
-    for (uint32_t k = 0; k < nb; ++k) {
-      const uint32_t sz = bstart[k + 1] - bstart[k];
-      if (sz > FUSE_MAX && !may_stream) ok = false;
-      if (cur_len > 0 && (cur_len + sz > FUSE_MID_MAX || single)) {
-        us[u] = bstart[cur_first]; ul[u] = cur_len; ub[u] = cur_first | (k << 16);
-        ++u;
-        cur_first = k;
-        cur_len = 0;
-      }
-      if (cur_len == 0) cur_first = k;
-      cur_len += sz;
-    }
-    if (cur_len > 0) { us[u] = bstart[cur_first]; ul[u] = cur_len; ub[u] = cur_first | (nb << 16); ++u; }
-    n_used = u;
-    all_fit = ok ? 1u : 0u;
+    for (uint32_t f = passes(0, 0) - 1; f < MSD_SLOTS; f = follows[f]) ufirst[u++] = f;
+    const bool ok = total == len && (!single || may_stream) && wflag[t] == 0 && !too_large;
+    n_used = ok ? u : 0;
     if (ok) {
       mflag[t] = 1;
       gflag[t] = 0;
@@ -253,15 +263,16 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
     }
   }
   __syncthreads();
-  const uint32_t used = all_fit ? n_used : 0;
+  const uint32_t used = n_used;
   const uint32_t u = o * MSD_SLOTS + d;
   utask[u] = t;
   udcount[u] = 0;
   const bool live = d < used;
-  const uint32_t l = live ? ul[d] : 0u;
-  ustart[u] = live ? static_cast<uint32_t>(task_start) + us[d] : 0u;
+  const uint32_t first = live ? ufirst[d] : 0u, past = live ? after[first] : 0u;
+  const uint32_t l = live ? bstart[past] - bstart[first] : 0u;
+  ustart[u] = live ? static_cast<uint32_t>(task_start) + bstart[first] : 0u;
   ulen[u] = l;
-  ubuckets[u] = live ? ub[d] : 0u;
+  ubuckets[u] = live ? first | (past << 16) : 0u;
   // work lists of units by size class (see k_classify): one reservation per task and class (a counter that every
   // unit bumped on its own would serialise the whole launch on one address)
   // (list 3: streamed units, huge ones from its front and the others from its back)
@@ -313,15 +324,17 @@ k_long_general_values(const fikit_launch* __restrict__ rec, const uint64_t* __re
   }
 }
 
-// Row count of every long task that went through units, and each unit's first row inside its task.
-__global__ void k_msd_task_rows(uint32_t n_tasks, const uint32_t* __restrict__ long_prefix, const uint32_t* __restrict__ mflag,
-                                const uint32_t* __restrict__ udcount, uint32_t* __restrict__ urow, uint32_t* __restrict__ dcount) {
-  const uint64_t t = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= n_tasks || long_prefix[t + 1] == long_prefix[t] || !mflag[t]) return;
-  const uint32_t u0 = long_prefix[t] * MSD_SLOTS;
-  uint32_t run = 0;
-  for (uint32_t k = 0; k < MSD_SLOTS; ++k) { urow[u0 + k] = run; run += udcount[u0 + k]; }
-  dcount[t] = run;
+// Row count of every long task that went through units, and each unit's first row inside its task.  One workgroup per task.
+__global__ void __launch_bounds__(MSD_SLOTS)
+k_msd_task_rows(uint32_t n_tasks, const uint32_t* __restrict__ long_prefix, const uint32_t* __restrict__ mflag,
+                const uint32_t* __restrict__ udcount, uint32_t* __restrict__ urow, uint32_t* __restrict__ dcount) {
+  __shared__ uint32_t aux[8];
+  const uint32_t t = blockIdx.x;
+  if (t >= n_tasks || long_prefix[t + 1] == long_prefix[t] || !mflag[t]) return;   // (the same for all threads)
+  const uint32_t u = long_prefix[t] * MSD_SLOTS + threadIdx.x;
+  uint32_t total;
+  urow[u] = block_excl_scan_256(udcount[u], aux, total);
+  if (threadIdx.x == 0) dcount[t] = total;
 }
 
 // Moves a unit's staged rows to their final place.
