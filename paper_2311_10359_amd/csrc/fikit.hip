@@ -1303,14 +1303,25 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   Tracer tr(st);
   tr.mark("merge_count");
   const uint32_t grid = n_tasks < 65536u ? n_tasks : 65536u;
+  // Tables of few rows on average: the kernel with the small LDS tables, and the tasks that do not fit them by list.
+  const bool small = (na + nb) / n_tasks <= MERGE_IDS_SMALL / 2;
+  const uint64_t most_large = small ? (na + nb) / (MERGE_IDS_SMALL + 1) : 0;
+  const uint32_t list_grid = static_cast<uint32_t>(most_large < grid ? most_large : grid);
+  // (the list lives where nothing else does at that time: in the row offsets before they exist, in the row counts after)
+  auto pass = [&](auto all, auto small_all, auto listed, uint32_t* list) {
+    hipLaunchKernelGGL(small ? small_all : all, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
+                       d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, na, nb, row_capacity,
+                       small ? list : static_cast<uint32_t*>(nullptr), ctrl);
+    if (list_grid > 0)
+      hipLaunchKernelGGL(listed, dim3(list_grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
+                         d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, na, nb, row_capacity, list, ctrl);
+  };
   hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_merge<0>, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
-                     d_task_row_offsets_b, n_tasks, dcount, static_cast<const uint64_t*>(nullptr),
-                     static_cast<fikit_row*>(nullptr), na, nb, row_capacity, ctrl);
+  pass(k_merge<0, MERGE_IDS, false>, k_merge<0, MERGE_IDS_SMALL, false>, k_merge<0, MERGE_IDS, true>,
+       reinterpret_cast<uint32_t*>(d_task_row_offsets_out));
   if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets_out, ctrl, st)) return rc;
   tr.mark("k_merge_rows");   // (does nothing if a check failed or the rows are too many)
-  hipLaunchKernelGGL(k_merge<1>, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
-                     d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, na, nb, row_capacity, ctrl);
+  pass(k_merge<1, MERGE_IDS, false>, k_merge<1, MERGE_IDS_SMALL, false>, k_merge<1, MERGE_IDS, true>, dcount);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};

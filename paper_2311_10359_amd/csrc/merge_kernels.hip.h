@@ -8,11 +8,16 @@
 namespace fikit {
 
 constexpr int MERGE_THREADS = 256;
-constexpr uint32_t MERGE_IDS = 3072;      // IDs of a task and input kept in LDS for the searches
+// IDs of a task and input kept in LDS for the searches.  A workgroup goes from one wait for memory to the next, so what
+// counts is how many of them a compute unit holds: three with the larger tables, seven with the smaller ones (writing the rows
+// of 20,000 tasks of 90 + 90 rows: 269 us with three, 182 us with seven; 146 us, 4.7 TB/s, since a lane moves 16 bytes and rows
+// that go nowhere are not read).  Tables beyond the larger number are searched in memory.
+constexpr uint32_t MERGE_IDS = 3072, MERGE_IDS_SMALL = 1024;
 
+template <uint32_t IDS>
 struct MergeSmem {
-  uint64_t ida[MERGE_IDS];
-  uint64_t idb[MERGE_IDS];
+  uint64_t ida[IDS];
+  uint64_t idb[IDS];
   uint32_t aux[8];
   uint32_t partner[MERGE_THREADS];   // per row of the round: its row in the other table, or MERGE_NONE
   uint32_t place[MERGE_THREADS];     // where it goes in the task's output, or MERGE_NONE: nowhere
@@ -48,20 +53,23 @@ __device__ __forceinline__ uint64_t merge_field(uint32_t f, uint64_t x, uint64_t
   return cy > cx ? y : x;   // the percentiles of the union are not known: those of the input with more samples stand in
 }
 
-// Writes the planned rows of a round (sm.place / sm.partner, `rows` of them, taken from src[first ..]): sixteen
-// lanes per row, one 8-byte field each, so that a wave reads and writes whole rows side by side.
-__device__ __forceinline__ void merge_write_round(const MergeSmem& sm, const fikit_row* __restrict__ src, uint32_t first,
+// Writes the planned rows of a round (sm.place / sm.partner, `rows` of them, taken from src[first ..]): eight
+// lanes per row, two 8-byte fields each, so that a wave reads and writes whole rows side by side.  Rows that go nowhere
+// (they went out with their partner) are not read.
+template <uint32_t IDS>
+__device__ __forceinline__ void merge_write_round(const MergeSmem<IDS>& sm, const fikit_row* __restrict__ src, uint32_t first,
                                                   uint32_t rows, const fikit_row* __restrict__ other, fikit_row* __restrict__ out) {
-  const uint32_t tid = threadIdx.x, f = tid & 15u;
-  const int row_lane0 = static_cast<int>(lane_id() - f);
-  for (uint32_t r = tid >> 4; r < rows; r += MERGE_THREADS / 16) {      // (the sixteen lanes of a row stay together)
+  const uint32_t tid = threadIdx.x, f = tid & 7u;
+  const int count_lane = static_cast<int>(lane_id() - f + (f < 4 ? 1 : 4));   // (fields 2 and 8)
+  for (uint32_t r = tid >> 3; r < rows; r += MERGE_THREADS / 8) {      // (the eight lanes of a row stay together)
     const uint32_t place = sm.place[r], partner = sm.partner[r];
-    const uint64_t x = reinterpret_cast<const uint64_t*>(src + first + r)[f];
-    const uint64_t y = partner != MERGE_NONE ? reinterpret_cast<const uint64_t*>(other + partner)[f] : 0;
-    const int count_lane = row_lane0 + (f < 8 ? 2 : 8);
-    const uint64_t cx = shfl_u64(x, count_lane), cy = shfl_u64(y, count_lane);
-    const uint64_t v = partner != MERGE_NONE ? merge_field(f, x, y, cx, cy) : x;
-    if (place != MERGE_NONE) reinterpret_cast<uint64_t*>(out + place)[f] = v;
+    if (place == MERGE_NONE) continue;
+    ulonglong2 v = reinterpret_cast<const ulonglong2*>(src + first + r)[f];
+    ulonglong2 y = make_ulonglong2(0, 0);
+    if (partner != MERGE_NONE) y = reinterpret_cast<const ulonglong2*>(other + partner)[f];
+    const uint64_t cx = shfl_u64(v.x, count_lane), cy = shfl_u64(y.x, count_lane);
+    if (partner != MERGE_NONE) v = make_ulonglong2(merge_field(2 * f, v.x, y.x, cx, cy), merge_field(2 * f + 1, v.y, y.y, cx, cy));
+    reinterpret_cast<ulonglong2*>(out + place)[f] = v;
   }
 }
 
@@ -69,15 +77,21 @@ __device__ __forceinline__ void merge_write_round(const MergeSmem& sm, const fik
 // union into dcount[t].  MODE 1: writes the union's rows at row_off[t].. in ID order.
 // One workgroup per task; rank of an ID in the union = IDs below it in a + IDs below it in b - IDs below
 // it that are in both (a running count of the matched rows seen so far).
-template <int MODE>
-__global__ void __launch_bounds__(MERGE_THREADS)
+// LIST: the tasks of list[0 .. ctrl->n_class[MODE]) only.  Otherwise all tasks; if list is not null, those with more than IDS
+// rows in a table are put on it instead.
+template <int MODE, uint32_t IDS, bool LIST>
+__global__ void __launch_bounds__(MERGE_THREADS, IDS == MERGE_IDS_SMALL ? 7 : 3)
 k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, const fikit_row* __restrict__ b,
-        const uint64_t* __restrict__ b_off, uint32_t n_tasks, uint32_t* __restrict__ dcount,
-        const uint64_t* __restrict__ row_off, fikit_row* __restrict__ out, uint64_t n_a, uint64_t n_b, uint64_t capacity, Ctrl* ctrl) {
-  __shared__ MergeSmem sm;
+        const uint64_t* __restrict__ b_off, uint32_t n_tasks, uint32_t* dcount,
+        const uint64_t* row_off, fikit_row* __restrict__ out, uint64_t n_a, uint64_t n_b, uint64_t capacity,
+        uint32_t* list, Ctrl* ctrl) {
+  __shared__ MergeSmem<IDS> sm;
   if (MODE == 1 && (ctrl->status || ctrl->n_rows > capacity)) return;   // (enqueued before the host knows)
   const uint32_t tid = threadIdx.x;
-  for (uint32_t t = blockIdx.x; t < n_tasks; t += gridDim.x) {
+  const uint32_t items = LIST ? ctrl->n_class[MODE] : n_tasks;
+  for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+    // (the rows are written from the last task to the first: what the counting pass read last is still in the cache)
+    const uint32_t t = LIST ? list[item] : MODE == 1 ? items - 1 - item : item;
     const uint64_t a0 = a_off[t], a1 = a_off[t + 1], b0 = b_off[t], b1 = b_off[t + 1];
     // (n_a, n_b: the rows there are; with this every row read is in bounds, whatever the other offsets say)
     if (a1 < a0 || b1 < b0 || a1 > n_a || b1 > n_b || a1 - a0 >= (1ull << 32) || b1 - b0 >= (1ull << 32) || (t == 0 && (a0 != 0 || b0 != 0))) {
@@ -87,16 +101,25 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
     const uint32_t na = static_cast<uint32_t>(a1 - a0), nb = static_cast<uint32_t>(b1 - b0);
     const fikit_row* ra = a + a0;
     const fikit_row* rb = b + b0;
-    const bool in_lds = na <= MERGE_IDS && nb <= MERGE_IDS;
+    const bool in_lds = na <= IDS && nb <= IDS;
+    if (!LIST && list && !in_lds) {   // (the same for all threads)
+      if (tid == 0) list[atomicAdd(&ctrl->n_class[MODE], 1u)] = t;
+      continue;
+    }
     __syncthreads();   // (the previous task's searches are over)
-    if (in_lds) {
-      for (uint32_t i = tid; i < na; i += MERGE_THREADS) sm.ida[i] = ra[i].kernel_id;
-      for (uint32_t i = tid; i < nb; i += MERGE_THREADS) sm.idb[i] = rb[i].kernel_id;
+    bool bad = false;
+    if (in_lds) {   // (ID and task are the first 16 bytes of a row: its line is touched once here)
+      auto take = [&](const fikit_row* r, uint64_t* ids, uint32_t i) {
+        const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(r + i);
+        ids[i] = v.x;
+        bad |= static_cast<uint32_t>(v.y) != t;
+      };
+      for (uint32_t i = tid; i < na; i += MERGE_THREADS) take(ra, sm.ida, i);
+      for (uint32_t i = tid; i < nb; i += MERGE_THREADS) take(rb, sm.idb, i);
     }
     __syncthreads();
     const uint64_t* ida = in_lds ? sm.ida : nullptr;
     const uint64_t* idb = in_lds ? sm.idb : nullptr;
-    bool bad = false;
     uint32_t carry = 0;      // matched rows of a before this round
     for (uint32_t i0 = 0; i0 < na; i0 += MERGE_THREADS) {
       const uint32_t i = i0 + tid;
@@ -106,7 +129,7 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
       if (i < na) {
         id = ida ? ida[i] : ra[i].kernel_id;
         below = ids_below(rb, idb, nb, id, &found);
-        if (MODE == 0) bad |= ra[i].task != t || (i > 0 && (ida ? ida[i - 1] : ra[i - 1].kernel_id) >= id);
+        if (MODE == 0) bad |= (!ida && ra[i].task != t) || (i > 0 && (ida ? ida[i - 1] : ra[i - 1].kernel_id) >= id);
       }
       uint32_t total;
       const uint32_t before = block_excl_scan_256(found ? 1u : 0u, sm.aux, total);
@@ -128,7 +151,7 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
       if (k < nb) {
         const uint64_t id = idb ? idb[k] : rb[k].kernel_id;
         if (MODE == 1) below = ids_below(ra, ida, na, id, &found);
-        if (MODE == 0) bad |= rb[k].task != t || (k > 0 && (idb ? idb[k - 1] : rb[k - 1].kernel_id) >= id);
+        if (MODE == 0) bad |= (!idb && rb[k].task != t) || (k > 0 && (idb ? idb[k - 1] : rb[k - 1].kernel_id) >= id);
       }
       if (MODE == 1) {
         uint32_t total;
@@ -146,7 +169,7 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
       if (tid == 0) dcount[t] = na + nb - matched;
     }
   }
-  if (MODE == 0 && blockIdx.x == 0 && tid == 0) dcount[n_tasks] = 0;   // (the scan leaves the total here)
+  if (MODE == 0 && !LIST && blockIdx.x == 0 && tid == 0) dcount[n_tasks] = 0;   // (the scan leaves the total here)
 }
 
 }  // namespace fikit
