@@ -8,15 +8,18 @@ namespace fikit {
 
 constexpr int PAIR_THREADS = 256;
 
-// One workgroup per scenario: checks the scenario, sums the time filled in its gaps (8 B read per gap)
-// and raises the largest filled time seen for its high-priority task.
+// One workgroup per scenario: checks the scenario, sums the time filled in its gaps (8 B read per gap) and raises the largest
+// filled time seen for its high-priority task.  Bound by HBM once enough bytes are in flight: a lane has up to eight 16-byte
+// reads out at a time.  16,384 scenarios of 2047 gaps: 62 us = 4.3 TB/s (four 8-byte reads at a time: 75 us).  A wave per
+// scenario is no faster (call 99 us against 97 us; 16,384 of 127 gaps 76 us against 77 us).  The atomic returns nothing, so
+// nothing waits for it; looking at the word first does wait, at a word that all scenarios of a task share (158 us).
 __global__ void __launch_bounds__(PAIR_THREADS)
 k_pair_sum(const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task, uint64_t n_scen, uint32_t n_tasks,
            const uint64_t* __restrict__ gap_off, uint64_t n_gaps, const int64_t* __restrict__ filled_ns,
            int64_t* __restrict__ scen_filled, long long* __restrict__ top_filled, Ctrl* ctrl) {
   __shared__ uint64_t part[PAIR_THREADS / WAVE];
-  const uint64_t s = blockIdx.x;
   const uint32_t tid = threadIdx.x;
+  const uint64_t s = blockIdx.x;
   const uint32_t hp = hp_task[s], lp = lp_task[s];
   const uint64_t g0 = gap_off[s], g1 = gap_off[s + 1];
   if (hp >= n_tasks || lp >= n_tasks) {
@@ -27,18 +30,40 @@ k_pair_sum(const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp
     if (tid == 0) atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
     return;
   }
-  uint64_t acc[4] = {0, 0, 0, 0};      // (sums wrap like the oracle's additions)
-  uint64_t i = g0 + tid;
-  for (; i + 3 * PAIR_THREADS < g1; i += 4 * PAIR_THREADS) {
+  constexpr int READS = 8;
+  uint64_t acc[2] = {0, 0};      // (sums wrap like the oracle's additions)
+  const uint64_t* f = reinterpret_cast<const uint64_t*>(filled_ns);
+  // pairs from the first gap on that lies on a 16-byte address; the gap before them and the one behind by one lane
+  const uint64_t p0 = g0 < g1 && (reinterpret_cast<uintptr_t>(f + g0) & 15) ? g0 + 1 : g0;
+  const uint64_t pairs = (g1 - p0) / 2;
+  const ulonglong2* v = reinterpret_cast<const ulonglong2*>(f + p0);
+  uint64_t i = tid;
+  for (; i + (READS - 1) * PAIR_THREADS < pairs; i += READS * PAIR_THREADS) {
+    ulonglong2 x[READS];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc[k] += static_cast<uint64_t>(filled_ns[i + k * PAIR_THREADS]);
+    for (int k = 0; k < READS; ++k) x[k] = v[i + k * PAIR_THREADS];
+#pragma unroll
+    for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
   }
-  for (; i < g1; i += PAIR_THREADS) acc[0] += static_cast<uint64_t>(filled_ns[i]);
-  const uint64_t mine = wave_sum_u64(acc[0] + acc[1] + acc[2] + acc[3]);
-  if (lane_id() == 0) part[tid >> 6] = mine;
+  {
+    ulonglong2 x[READS];
+#pragma unroll
+    for (int k = 0; k < READS; ++k) {
+      x[k] = make_ulonglong2(0, 0);
+      if (i + k * PAIR_THREADS < pairs) x[k] = v[i + k * PAIR_THREADS];
+    }
+#pragma unroll
+    for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
+  }
+  if (tid == 0) {
+    if (p0 > g0) acc[0] += f[g0];
+    if (p0 + 2 * pairs < g1) acc[1] += f[g1 - 1];
+  }
+  uint64_t total = wave_sum_u64(acc[0] + acc[1]);
+  if (lane_id() == 0) part[tid >> 6] = total;
   __syncthreads();
   if (tid == 0) {
-    uint64_t total = 0;
+    total = 0;
 #pragma unroll
     for (int w = 0; w < PAIR_THREADS / WAVE; ++w) total += part[w];
     scen_filled[s] = static_cast<int64_t>(total);

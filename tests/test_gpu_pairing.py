@@ -81,3 +81,20 @@ def test_pairing_argument_errors():
             run_pairing(bad_hp, lp, 2, np.array(bad_go, np.uint64), fn, comp)
         assert e.value.status == binding.FIKIT_INVALID_ARG, bad_go
     run_pairing(hp, lp, 2, np.array([0, 2, 5], np.uint64), fn, comp)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_pairing_sums_at_odd_gaps_and_addresses(shift):
+    rng = np.random.default_rng(21 + shift)
+    lens = np.array([0, 1, 2, 3, 511, 512, 513, 4094, 4095, 4096, 4097, 8191, 8193, 20001])
+    go = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
+    hp, lp = (rng.integers(0, 5, lens.size).astype(np.uint32) for _ in range(2))
+    fn = rng.integers(0, 10**12, int(go[-1]))
+    comp = rng.integers(0, 10**12, lens.size)
+    space = torch.zeros(fn.size + shift, dtype=torch.int64, device=DEV)      # (from a 16-byte address on, or 8 bytes behind one)
+    space[shift:] = torch.from_numpy(fn).to(DEV)
+    got = binding.fikit_pairing_best(binding.to_device_u32(hp, DEV), binding.to_device_u32(lp, DEV), 5, binding.to_device_u64(go, DEV),
+                                     space[shift:], torch.from_numpy(comp).to(DEV))
+    exp = oracle.pairing_best(hp, lp, 5, go, fn, comp)
+    assert np.array_equal(got.scenario_filled_ns.cpu().numpy(), exp[0])
+    assert np.array_equal(binding.u64_to_numpy(got.best_scenario), exp[1])
