@@ -651,7 +651,7 @@ int fikit_profile(const fikit_launch* d_records, uint64_t n_records, const uint6
 constexpr uint64_t GF_PAD = 256;
 // From this many scenarios on, one lane steps through a scenario (k_gf_walk_lanes), below it a wave (k_gf_walk_wave).  The
 // lanes take about 3.3 ms for traces of 4096 and queues of 16,384 launches, however many they are (to 65,536); the waves 0.1 ms
-// per 1024 scenarios of that shape once the chip is full (1.55 ms against 3.2 ms at 16,384).
+// per 1024 scenarios of that shape once the chip is full (1.44 ms against 3.2 ms at 16,384).
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
 
 }  // extern "C"

@@ -531,10 +531,10 @@ enum : int { LW_PLAN = 0, LW_REPLAY = 1, LW_REPLAY_FEEDBACK = 2 };
 // at any other value it is done.  If the sums themselves passed 32 bits, the window is reloaded at the head, where
 // C = 0 and everything that can fit is exact.
 //
-// What bounds it: with few scenarios the chain of one gap (about 25 instructions, 120 cycles), with many the issue of
+// What bounds it: with few scenarios the chain of one gap (about 22 instructions, 120 cycles), with many the issue of
 // scalar instructions (the gap's fourteen scalar instructions go through one port per SIMD).  64 scenarios of 1500 gaps:
-// 0.06 ms (the 64-bit kernel below, which passes 64-bit sums through the LDS crossbar: 0.23 ms); 256 scenarios of 65,535
-// gaps of which few take anything: 0.5 ms (1.8 ms); 16,384 scenarios of 4095 gaps: 1.55 ms (one lane each: 3.2 ms).
+// 0.076 ms (the 64-bit kernel above, which passes 64-bit sums through the LDS crossbar: 0.23 ms); 256 scenarios of 65,535
+// gaps of which few take anything: 0.52 ms (1.8 ms); 16,384 scenarios of 4095 gaps: 1.44 ms (one lane each: 3.2 ms).
 constexpr int WW_THREADS = 256;
 constexpr uint32_t WW_WIN = WAVE - 1;
 constexpr int WW_BLOCKS = 4;   // blocks of 64 gaps per round (their reads are one round ahead)
@@ -586,12 +586,15 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   const uint32_t margin32 = margin >= static_cast<int64_t>(WIDE32) ? WIDE32 : static_cast<uint32_t>(margin);
 
   uint32_t wb = 0, o = 0, C = 0, sum = 0;    // window start, position in it, time consumed since its start, running sum of the head
-  uint32_t win = 0, r1 = 0;                  // running sums of the window; the entries of the window after it
+  uint32_t win = 0, before = 0, r1 = 0;      // running sums of the window, and before each entry; the entries of the window after it
   // (read without a branch, so that the walk's loop stays free of divergent ones; what lies behind the end is told apart
   // when the entries are used, so that nothing waits for a read where it is issued)
   auto entry = [&](uint32_t j) -> uint32_t { return queue[j < L ? j : L - 1]; };
   // (behind the end: saturates, never fits)
-  auto set_window = [&](uint32_t r) { win = wave_incl_scan_sat_u32(lane == WW_WIN || wb + lane >= L ? WIDE32 : r); };
+  auto set_window = [&](uint32_t r) {
+    win = wave_incl_scan_sat_u32(lane == WW_WIN || wb + lane >= L ? WIDE32 : r);
+    before = dpp_or_zero<0x138, 0xf>(win);   // wave_shr:1
+  };
   auto load_window = [&](uint32_t at) {
     wb = at; o = 0; C = 0;
     const uint32_t r0 = entry(at + lane);
@@ -633,64 +636,64 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
       const bool has_gap = i < n_gaps;
       uint32_t my_c = 0, my_f = 0;
       if (!done) {
-        uint64_t todo = ~0ull, takes;
-        uint32_t k = 0, o2;
-        for (;;) {
-          // the common case: the gap ends inside the window, at an entry whose running sum is exact
-          for (;;) {
-            const uint32_t lim = __builtin_elementwise_add_sat(b1[j], C);
-            takes = ballot(lim > sum) & todo;
-            if (takes == 0) break;
-            k = static_cast<uint32_t>(__builtin_ctzll(takes));
-            todo = (~1ull) << k;
-            // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
-            // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
-            // the entries that end before that.
-            const uint32_t limit = read_lane_u32(lim, k);
-            o2 = popc64(ballot(win < limit));
-            if (MODE == LW_REPLAY_FEEDBACK) {
-              const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
-              const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
-              o2 = o3 < o2 ? o3 : o2;
-            }
-            const uint32_t C2 = read_lane_u32(win, o2 - 1), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
-            if (sum2 == WIDE32) break;
-            my_c = write_lane_u32(my_c, o2 - o, k);
-            my_f = write_lane_u32(my_f, C2 - C, k);
-            o = o2; C = C2; sum = sum2;
+        uint32_t k = 0, lim = __builtin_elementwise_add_sat(b1[j], C);
+        uint64_t takes = ballot(lim > sum);
+        // (one way out of the loop, at its end, and the rare case inside it: otherwise the compiler carries flags and copies
+        // through every gap)
+        if (takes) do {
+          k = static_cast<uint32_t>(__builtin_ctzll(takes));
+          uint64_t todo = (~1ull) << k;
+          // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
+          // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
+          // the entries that end before that.
+          const uint32_t limit = read_lane_u32(lim, k);
+          uint32_t o2 = popc64(ballot(win < limit));
+          if (MODE == LW_REPLAY_FEEDBACK) {
+            const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
+            const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
+            o2 = o3 < o2 ? o3 : o2;
           }
-          if (takes == 0) break;
-          // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
-          uint32_t left = read_lane_u32(b1[j], k), c = 0, f = 0;
-          const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
-          for (;;) {
-            if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
-            o2 = popc64(ballot(win < C + left));
-            bool stop = false;
-            if (MODE == LW_REPLAY_FEEDBACK) {
-              const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
-              stop = o3 <= o2;
-              o2 = stop ? o3 : o2;
+          const uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
+          // the common case: the gap ends inside the window, at an entry whose running sum is exact
+          uint32_t c = o2 - o, f = C2 - C;
+          if (__builtin_expect(sum2 != WIDE32, 1)) {
+            o = o2; C = C2; sum = sum2;
+          } else {
+            // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
+            uint32_t left = read_lane_u32(b1[j], k);
+            c = f = 0;
+            const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
+            for (;;) {
+              if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
+              o2 = popc64(ballot(win < C + left));
+              bool stop = false;
+              if (MODE == LW_REPLAY_FEEDBACK) {
+                const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
+                stop = o3 <= o2;
+                o2 = stop ? o3 : o2;
+              }
+              const uint32_t C3 = read_lane_u32(before, o2);
+              c += o2 - o; f += C3 - C; left -= C3 - C;
+              o = o2; C = C3;
+              if (wb + o >= L) { done = true; break; }
+              bool again = false;
+              if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
+                wb += WW_WIN; o = 0; C = 0;
+                set_window(r1);
+                r1 = entry(wb + WW_WIN + lane);
+                again = !stop;
+              }
+              sum = read_lane_u32(win, o);
+              if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
+              if (!again) break;
             }
-            const uint32_t C3 = o2 ? read_lane_u32(win, o2 - 1) : 0u;
-            c += o2 - o; f += C3 - C; left -= C3 - C;
-            o = o2; C = C3;
-            if (wb + o >= L) { done = true; break; }
-            bool again = false;
-            if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
-              wb += WW_WIN; o = 0; C = 0;
-              set_window(r1);
-              r1 = entry(wb + WW_WIN + lane);
-              again = !stop;
-            }
-            sum = read_lane_u32(win, o);
-            if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
-            if (!again) break;
+            if (done) { f_last = f; todo = 0; }
           }
           my_c = write_lane_u32(my_c, c, k);
           my_f = write_lane_u32(my_f, f, k);
-          if (done) { f_last = f; break; }
-        }
+          lim = __builtin_elementwise_add_sat(b1[j], C);
+          takes = ballot(lim > sum) & todo;
+        } while (takes);
         if (MODE == LW_PLAN) {
           consumed += my_f;
           // predicted time line: all launches of the block and the idle times after them, or, if the queue ran empty in
