@@ -1167,11 +1167,12 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
                      d_lp_placed, d_lp_placed_ns, ctrl)
     // One wave per scenario up to this many scenarios, beyond it a group of lanes per scenario.  The waves' time grows with
     // the scenarios, the groups' hardly does; traces of 1024 launches, queues of 2048, waves / groups in ms for the call:
-    //   1 task   4096: 0.41 / 1.22   12,288: 0.80 / 1.37   32,768: 1.78 / 1.69
-    //   3 tasks  64: 0.94 / 2.2   4096: 1.39 / 2.34   6144: 1.78 / 2.38   8192: 2.19 / 2.40   12,288: 3.08 / 2.74
-    //   4 tasks  6144: 2.28 / 2.71   8192: 2.86 / 2.74   6 tasks  6144: 2.62 / 3.67   12,288: 4.07 / 3.91
-    //   9 tasks  6144: 2.64 / 3.90   12,288: 4.08 / 5.30   16,384: 5.47 / 5.42
-    const bool waves = n_scenarios <= (widest <= 1 || widest > 8 ? 16384u : 6144u);
+    //   1 task   4096: 0.35 / 1.22   16,384: 0.94 / 1.42   24,576: 1.34 / 1.54
+    //   2 tasks  4096: 0.87 / 1.81   8192: 1.41 / 1.87   12,288: 1.93 / 1.96
+    //   3 tasks  64: 0.80 / 2.2   4096: 1.07 / 2.34   8192: 1.74 / 2.39   12,288: 2.41 / 2.76
+    //   4 tasks  4096: 1.42 / 2.64   12,288: 2.88 / 3.11   6 tasks  4096: 1.59 / 3.41   12,288: 3.14 / 3.99
+    //   9 tasks  4096: 1.71 / 3.75   16,384: 3.97 / 5.47   24,576: 5.51 / 7.75
+    const bool waves = n_scenarios <= (widest <= 1 || widest > 8 ? 24576u : 12288u);
     if (waves && widest <= 1) FIKIT_PF_WAVE(64);
     else if (waves && widest <= 2) FIKIT_PF_WAVE(32);
     else if (waves && widest <= 4) FIKIT_PF_WAVE(16);

@@ -337,8 +337,8 @@ k_pf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 // one lane read; the SEG durations after them are read ahead.  Which gap takes something next is one comparison of all
 // lanes with the shortest request: gaps that take nothing cost nothing.
 // What bounds it: with few scenarios the chain of one decision (compare, first lane, three lane reads, compare, lane write:
-// about 320 cycles), with many the issue of its thirty instructions.  4096 scenarios of 1023 gaps and three queues of 2048:
-// 1.15 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
+// about 260 cycles), with many the issue of its 25 to 35 instructions.  4096 scenarios of 1023 gaps and three queues of 2048:
+// 0.87 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
 template <int SEG>
 __global__ void __launch_bounds__(WW_THREADS)
 k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint64_t* __restrict__ lp_off,
@@ -375,8 +375,9 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   if (SEG + place < len) next = queue[SEG + place];
   uint64_t issued_ns = 0;      // of the windows this lane has seen pass
 
-  // the waiting requests in their order: duration, lane of the window it stands in, lanes of its level (as bits)
-  uint32_t hd = WIDE32, ho = 0, seg = 0;
+  // the waiting requests in their order: duration, lane of the window it stands in; the first lane of its level and the
+  // other lanes of it (as bits)
+  uint32_t hd = WIDE32, ho = 0, seg_first = 0, seg_others = 0;
   {
     const uint32_t level = lane < listed ? lp_prio[e0 + lane] : WIDE32;
     const uint32_t head = static_cast<uint32_t>(__shfl(static_cast<int>(raw), static_cast<int>(lane * SEG & (WAVE - 1)), WAVE));
@@ -391,7 +392,10 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
       ho = write_lane_u32(ho, j * SEG, r);
       at_level = write_lane_u32(at_level, read_lane_u32(level, j), r);
     }
+    uint32_t seg = 0;
     for (uint32_t j = 0; j < listed; ++j) seg |= read_lane_u32(at_level, j) == at_level ? 1u << j : 0u;
+    seg_first = static_cast<uint32_t>(__builtin_ctz(seg | 1u << 31));
+    seg_others = seg & ~(1u << (lane & 31));
   }
   auto shortest = [&]() {      // (the lanes behind the requests hold WIDE32)
     uint32_t m = hd;
@@ -413,12 +417,11 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
     G1 = idle_time(i + 2 * WAVE);
     const uint32_t b1 = (i < n_gaps && G >= gap_floor) ? G - margin32 + 1 : 0u;   // one more than what may be filled
     uint32_t my_c = 0, my_f = 0;
-    uint64_t todo = ~0ull;
-    for (;;) {
-      const uint64_t takes = ballot(b1 > least) & todo;
-      if (takes == 0) break;
+    // (one way out of every loop, at its end: see k_gf_walk_wave)
+    uint64_t takes = ballot(b1 > least);
+    if (takes) do {
       const uint32_t j = static_cast<uint32_t>(__builtin_ctzll(takes));
-      todo = (~1ull) << j;
+      const uint64_t todo = (~1ull) << j;
       const uint32_t budget = read_lane_u32(b1, j) - 1;
       uint32_t rem = budget, c = 0;
       uint64_t fit = ballot(hd <= rem);   // (never empty here)
@@ -427,7 +430,7 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
         rem -= read_lane_u32(hd, p);
         ++c;
         uint32_t w = read_lane_u32(ho, p) + 1;
-        const uint32_t level = read_lane_u32(seg, p);
+        const uint32_t others = read_lane_u32(seg_others, p);
         if (__builtin_expect(w % SEG == 0, 0)) {   // the queue's window is used up
           w -= SEG;
           if (mine == w / SEG) {
@@ -440,15 +443,16 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
         }
         const uint32_t n = read_lane_u32(raw, w);
         uint32_t to = p;
-        if (K > 1 && (level & (level - 1))) {
-          const uint32_t ahead = static_cast<uint32_t>(ballot(hd >= n)) & level & ~(1u << p);
-          to = static_cast<uint32_t>(__builtin_ctz(level)) + static_cast<uint32_t>(__builtin_popcount(ahead));
+        if (K > 1 && others) {
+          const uint32_t ahead = static_cast<uint32_t>(ballot(hd >= n)) & others;
+          to = read_lane_u32(seg_first, p) + static_cast<uint32_t>(__builtin_popcount(ahead));
           if (to > p) {
             const uint32_t d1 = dpp_move<0x101>(hd), o1 = dpp_move<0x101>(ho);   // row_shl:1, from the lane above
             const bool moves = lane - p < to - p;
             hd = moves ? d1 : hd;
             ho = moves ? o1 : ho;
-          } else if (to < p) {
+          }
+          if (to < p) {
             const uint32_t d1 = dpp_move<0x111>(hd), o1 = dpp_move<0x111>(ho);   // row_shr:1, from the lane below
             const bool moves = lane - to - 1 < p - to;
             hd = moves ? d1 : hd;
@@ -462,7 +466,8 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
       my_c = write_lane_u32(my_c, c, j);
       my_f = write_lane_u32(my_f, budget - rem, j);
       least = shortest();
-    }
+      takes = ballot(b1 > least) & todo;
+    } while (takes);
     if (i < n_gaps) {
       fill_count[g0 + i] = my_c;
       filled_ns[g0 + i] = static_cast<int64_t>(my_f);

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k_max", [1, 2, 3, 4, 7, 9, 16])
-@pytest.mark.parametrize("n_scen", [333, 16390])
+@pytest.mark.parametrize("n_scen", [333, 24600])
 def test_prio_walk_edges(k_max, n_scen):
     lens = [0, 1, 2, 3, 4, 5, 7, 8, 9, 12, 13, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 66]
     if n_scen < 1000:
