@@ -95,6 +95,8 @@ constexpr int PRED_CHUNK = PRED_THREADS * PRED_KPT;
 constexpr int PRED_ROWS = 512;                    // rows of a task kept in an LDS hash table for the lookup
 constexpr int PRED_HT = 2 * PRED_ROWS;
 
+constexpr uint32_t WIDE32 = 0xffffffffu;   // 32-bit predictions must be below this
+
 // The prediction read from a row's statistics: median, or mean = sum / count (Section 3.2: SK_j, SG_j).
 __device__ __forceinline__ int64_t predicted_of(const fikit_stats& st, uint32_t predictor) {
   if (predictor == FIKIT_PREDICT_P50) return st.p50;
@@ -110,6 +112,18 @@ struct PredTable {
   int64_t g[PRED_HT];
 };
 
+__device__ __forceinline__ bool find_row(uint64_t id, const fikit_row* __restrict__ rows, uint64_t r0, uint64_t nr, uint32_t predictor,
+                                         int64_t& e, int64_t& g) {
+  uint64_t lo = 0, hi = nr;
+  while (lo < hi) { const uint64_t mid = (lo + hi) >> 1; if (rows[r0 + mid].kernel_id < id) lo = mid + 1; else hi = mid; }
+  if (lo < nr && rows[r0 + lo].kernel_id == id) {
+    e = predicted_of(rows[r0 + lo].exec, predictor);
+    g = predicted_of(rows[r0 + lo].gap, predictor);
+    return true;
+  }
+  return false;
+}
+
 __device__ __forceinline__ bool predict_one(uint64_t id, bool in_lds, const PredTable& tb, const fikit_row* __restrict__ rows,
                                             uint64_t r0, uint64_t nr, uint32_t predictor, int64_t& e, int64_t& g) {
   if (in_lds) {
@@ -122,14 +136,7 @@ __device__ __forceinline__ bool predict_one(uint64_t id, bool in_lds, const Pred
     }
     return false;
   }
-  uint64_t lo = 0, hi = nr;
-  while (lo < hi) { const uint64_t mid = (lo + hi) >> 1; if (rows[r0 + mid].kernel_id < id) lo = mid + 1; else hi = mid; }
-  if (lo < nr && rows[r0 + lo].kernel_id == id) {
-    e = predicted_of(rows[r0 + lo].exec, predictor);
-    g = predicted_of(rows[r0 + lo].gap, predictor);
-    return true;
-  }
-  return false;
+  return find_row(id, rows, r0, nr, predictor, e, g);
 }
 
 // One workgroup per task that takes part in a scenario.  For every launch i of the task:
@@ -369,7 +376,16 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 // use, and whatever can be derived when a gap's result is staged (its count, its filled time, its opening
 // time) is not carried through the tries.
 
-constexpr uint32_t WIDE32 = 0xffffffffu;   // 32-bit predictions must be below this
+
+// The table of k_gf_predict32: both predictions of an ID in one 8-byte word (WIDE32: does not fit 32 bits).  16 KB, so that a
+// compute unit holds eight workgroups.
+struct PredTable32 {
+  uint64_t key[PRED_HT];
+  uint2 eg[PRED_HT];
+};
+__device__ __forceinline__ uint32_t clamp32(int64_t v) {   // (predictions are not negative)
+  return static_cast<uint64_t>(v) >= WIDE32 ? WIDE32 : static_cast<uint32_t>(v);
+}
 
 // Predicted values of every launch of the tasks that take part, in 32 bits (gridDim.y workgroups per task, each a
 // part of its launches: with few tasks one workgroup per task leaves most of the chip idle; see predict_parts):
@@ -383,7 +399,7 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
                const fikit_row* __restrict__ rows, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role,
                const int64_t* __restrict__ actual, uint32_t* __restrict__ lp_e, uint2* __restrict__ hp_eg,
                uint64_t* __restrict__ lp_total, uint32_t predictor, const uint32_t* __restrict__ pred_done, Ctrl* ctrl) {
-  __shared__ PredTable tb;
+  __shared__ PredTable32 tb;
   __shared__ uint64_t wave_tot[PRED_THREADS / WAVE];
   if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
   const uint32_t t = blockIdx.x;
@@ -408,12 +424,27 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
         if (old == ~0ull) break;
         h = (h + 1) & (PRED_HT - 1);
       }
-      tb.e[h] = predicted_of(row->exec, predictor);
-      tb.g[h] = predicted_of(row->gap, predictor);
+      tb.eg[h] = make_uint2(clamp32(predicted_of(row->exec, predictor)), clamp32(predicted_of(row->gap, predictor)));
     }
   }
   __syncthreads();
   bool unknown = false, wide = false, bad_actual = false;
+  auto predict = [&](uint64_t id) -> uint2 {
+    if (in_lds) {
+      uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (PRED_HT - 1);
+      for (int probe = 0; probe < PRED_HT; ++probe) {
+        const uint64_t k = tb.key[h];
+        if (k == id) return tb.eg[h];
+        if (k == ~0ull) break;
+        h = (h + 1) & (PRED_HT - 1);
+      }
+      unknown = true;
+      return make_uint2(0, 0);
+    }
+    int64_t e = 0, g = 0;
+    unknown |= !find_row(id, rows, r0, nr, predictor, e, g);
+    return make_uint2(clamp32(e), clamp32(g));
+  };
   uint64_t total = 0;
   const bool even = ((base & 1) == 0);   // 16-byte accesses to the workspace arrays need an even first index
   const bool ids_vec = (reinterpret_cast<uintptr_t>(ids + base) & 15) == 0;   // and those to the caller's IDs an aligned address
@@ -427,13 +458,11 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
       id0 = ids[base + i0];
       if (two) id1 = ids[base + i0 + 1];
     }
-    int64_t e0 = 0, g0 = 0, e1 = 0, g1 = 0;
-    unknown |= !predict_one(id0, in_lds, tb, rows, r0, nr, predictor, e0, g0);
-    if (two) unknown |= !predict_one(id1, in_lds, tb, rows, r0, nr, predictor, e1, g1);
-    wide |= static_cast<uint64_t>(e0) >= WIDE32 || static_cast<uint64_t>(g0) >= WIDE32 || static_cast<uint64_t>(e1) >= WIDE32 ||
-            static_cast<uint64_t>(g1) >= WIDE32;
-    const uint32_t a0 = static_cast<uint32_t>(e0), b0 = static_cast<uint32_t>(g0), a1 = static_cast<uint32_t>(e1),
-                   b1 = static_cast<uint32_t>(g1);
+    const uint2 p0 = predict(id0);
+    uint2 p1 = make_uint2(0, 0);
+    if (two) p1 = predict(id1);
+    const uint32_t a0 = p0.x, b0 = p0.y, a1 = p1.x, b1 = p1.y;
+    wide |= a0 == WIDE32 || b0 == WIDE32 || a1 == WIDE32 || b1 == WIDE32;
     total += static_cast<uint64_t>(a0) + a1;
     uint32_t h0w = a0, h1w = a1;   // first word of the high-priority entries
     if (actual && (rl & ROLE_HP)) {

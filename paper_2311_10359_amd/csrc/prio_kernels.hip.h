@@ -338,7 +338,7 @@ k_pf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 // lanes with the shortest request: gaps that take nothing cost nothing.
 // What bounds it: with few scenarios the chain of one decision (compare, first lane, three lane reads, compare, lane write:
 // about 260 cycles), with many the issue of its 25 to 35 instructions.  4096 scenarios of 1023 gaps and three queues of 2048:
-// 0.87 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
+// 0.94 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
 template <int SEG>
 __global__ void __launch_bounds__(WW_THREADS)
 k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint64_t* __restrict__ lp_off,
