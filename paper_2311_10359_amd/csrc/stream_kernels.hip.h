@@ -212,7 +212,9 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
   }
   __syncthreads();
   const uint32_t D = sm.ndist;
-  if (sm.fallback || D > SU_DMAX || sm.filled != m) {
+  // (the rows are staged in the space of the unit's own launches, and in a task of more than UNIT_RUNS_MAX tiles a unit may be
+  // a single launch)
+  if (sm.fallback || D > SU_DMAX || sm.filled != m || D > 2 * (m >> 4)) {
     // the whole task goes to the general path (k_long_general_values hands its per-launch values over)
     if (tid == 0 && atomicExch(&A.mflag[t], 0u) == 1u) {
       A.gflag[t] = 1;

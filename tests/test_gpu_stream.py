@@ -57,7 +57,44 @@ def test_frequent_ids(lens, n_ids, heavy, times, sorts):
     assert ("k_onesweep_pass" in names) == sorts, sorted(names)
 
 
+def with_rare(seed, tasks):
+    """Tasks of (launches, frequent IDs, IDs launched once to `most` times): the frequent ones about equally often, the rare ones
+    at random places and at the task's last launches."""
+    rng = np.random.default_rng(seed)
+    lens = [n for n, _, _, _ in tasks]
+    kids = []
+    for t, (n, frequent, rare, most) in enumerate(tasks):
+        kid = rng.integers(0, frequent, n)
+        times = rng.integers(1, most + 1, rare)
+        at = rng.choice(n, int(times.sum()), replace=False)
+        kid[at] = np.repeat(frequent + np.arange(rare), times)
+        if rare:
+            kid[-1] = frequent + rare - 1
+        kids.append(kid + 100_000 * t)
+    kid = np.concatenate(kids).astype(np.uint32)
+    n = kid.size
+    rec = np.zeros(n, dtype=traces.LAUNCH_DTYPE)
+    rec["name_id"], rec["grid"], rec["block"] = kid * 7919, 1, 64
+    ex = np.maximum(1, np.rint(rng.lognormal(8.5, 1.0, n))).astype(np.int64) + kid % 97
+    gp = np.rint(rng.lognormal(9.0, 1.0, n)).astype(np.int64)
+    rec["start_ns"] = np.cumsum(ex + gp) - (ex + gp)
+    rec["end_ns"] = rec["start_ns"] + ex
+    off = np.zeros(len(lens) + 1, dtype=np.uint64)
+    np.cumsum(lens, out=off[1:])
+    return rec, off
+
+
+@pytest.mark.parametrize("tasks", [
+    [(4_300_000, 30, 40, 1), (900, 100, 0, 1)],                       # a short task's rows lie behind the small buckets' ones
+    [(900, 100, 0, 1), (4_300_000, 100, 300, 20)],                    # ... and the small buckets end the workspace's arrays
+])
+def test_rare_ids_beside_frequent_ones_in_more_tiles_than_a_unit_can_list(tasks):
+    """Buckets of one launch or a few in a task whose buckets are all streamed: their rows need more room than their launches."""
+    print(f"tasks {tasks}", flush=True)
+    check_profile(*with_rare(len(tasks) + tasks[0][0], tasks))
+
+
 def test_more_tiles_than_a_unit_can_list():
-    """A task of more than 1024 tiles: all of its buckets are streamed, small ones too."""
+    """A task of more than 1024 tiles: all of its buckets are streamed, large and small."""
     rec, off = skewed(5, [4_200_000, 900], 300, 0.1, "lognormal")
     check_profile(rec, off)
