@@ -366,6 +366,8 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   uint32_t* udcount = utask + L.max_units;
   uint32_t* urow = udcount + L.max_units;
   uint32_t* ubuckets = urow + L.max_units;
+  uint32_t* bucket_size = reinterpret_cast<uint32_t*>(ws + L.bsize);
+  uint32_t* ustage = bucket_size;   // (one word per unit slot too, which k_msd_units has done with)
   uint32_t* wflag = reinterpret_cast<uint32_t*>(ws + L.wflag);
   const bool few_tasks = n_tasks <= BEGIN_TASKS;
   if (few_tasks) {
@@ -446,7 +448,6 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     n_msd_tiles = h.n_big_tiles;
     if (n_msd_tiles == 0 || n_msd_tiles > L.max_ptiles) return FIKIT_HIP_ERROR;
     tr.mark("k_tile_partition");
-    uint32_t* bucket_size = reinterpret_cast<uint32_t*>(ws + L.bsize);
     hipLaunchKernelGGL(k_msd_clear, dim3(blocks_for(n_units, 256)), dim3(256), 0, st, bucket_size, n_units, ctrl);
     FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tile_partition), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   static_cast<int>(sizeof(PartSmem))));
@@ -459,6 +460,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     ua.pred_role = nullptr;   // (units are parts of tasks: their task's predictions are left to the gap fill)
     ua.ustart = ustart; ua.ulen = ulen; ua.utask = utask; ua.ubuckets = ubuckets; ua.tile_prefix = mtiles; ua.bound = bound;
     ua.tile_len = PT_TILE; ua.part_id = k1; ua.part_kg = part_kg; ua.mflag = mflag; ua.dcount = udcount;
+    ua.staged = dcount; ua.ustage = ustage;   // (a long task's row count is 0 until k_msd_task_rows: the sum of what was staged)
     // (first, because its largest units take longest; a unit has more than FUSE_MAX launches, or is one of the
     // MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
     tr.mark("k_unit_stream");
@@ -494,8 +496,8 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     hipLaunchKernelGGL(k_gather_rows, dim3(xcd_grid(n_tasks)), dim3(256), 0, st, d_task_offsets, d_task_row_offsets, gflag, is_long,
                        n_units > 0 ? 1 : 0, e1, g1, n_tasks, d_rows_out, row_capacity, general_done, ctrl);
     if (n_units > 0)
-      hipLaunchKernelGGL(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, ustart, ulen, utask,
-                         udcount, urow, mflag, d_task_row_offsets, e1, g1, static_cast<uint32_t>(n_units), d_rows_out, row_capacity,
+      hipLaunchKernelGGL(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, d_task_offsets, ulen,
+                         utask, udcount, urow, ustage, mflag, d_task_row_offsets, e1, g1, static_cast<uint32_t>(n_units), d_rows_out, row_capacity,
                          general_done, ctrl);
   };
   tr.mark("row_offsets");

@@ -339,23 +339,24 @@ k_msd_task_rows(uint32_t n_tasks, const uint32_t* __restrict__ long_prefix, cons
 
 // Moves a unit's staged rows to their final place.
 __global__ void __launch_bounds__(256)
-k_gather_units(const uint32_t* __restrict__ ustart, const uint32_t* __restrict__ ulen, const uint32_t* __restrict__ utask,
-               const uint32_t* __restrict__ udcount, const uint32_t* __restrict__ urow, const uint32_t* __restrict__ mflag,
+k_gather_units(const uint64_t* __restrict__ off, const uint32_t* __restrict__ ulen, const uint32_t* __restrict__ utask,
+               const uint32_t* __restrict__ udcount, const uint32_t* __restrict__ urow, const uint32_t* __restrict__ ustage,
+               const uint32_t* __restrict__ mflag,
                const uint64_t* __restrict__ row_off, const int64_t* __restrict__ stage_a, const int64_t* __restrict__ stage_b,
                uint32_t n_units, fikit_row* __restrict__ rows, uint64_t capacity, uint64_t general_done, const Ctrl* ctrl) {
   if (!rows_final(ctrl, capacity, general_done)) return;
   const uint32_t u = xcd_item(blockIdx.x, n_units);
   if (u >= n_units) return;
-  const uint32_t m = ulen[u];
-  if (m == 0) return;
+  if (ulen[u] == 0) return;
   const uint32_t t = utask[u];
   if (!mflag[t]) return;
   const uint32_t D = udcount[u];
   uint64_t* out = reinterpret_cast<uint64_t*>(rows + row_off[t] + urow[u]);
-  const uint64_t base = ustart[u];
+  const uint64_t base = off[t];
+  const uint32_t m = static_cast<uint32_t>(off[t + 1] - base), row0 = ustage[u];
   for (uint32_t x = threadIdx.x; x < D * 16; x += 256) {
     const uint32_t j = x >> 4, f = x & 15;
-    out[x] = staged_row(const_cast<int64_t*>(stage_a), const_cast<int64_t*>(stage_b), base, m, j)[f];
+    out[x] = staged_row(const_cast<int64_t*>(stage_a), const_cast<int64_t*>(stage_b), base, m, row0 + j)[f];
   }
 }
 

@@ -35,7 +35,7 @@ struct StreamSmem {
   uint8_t fine[4][SU_DMAX];     // ... and the shift that cuts it into bins
   uint16_t slot_of[SU_DMAX];    // rank -> slot
   uint32_t aux[SU_WAVES];
-  uint32_t ndist, fallback, filled, again;
+  uint32_t ndist, fallback, filled, again, first_row;
   union {
     uint32_t hist[SU_HIST];
     struct { uint64_t ckey[SU_DMAX]; uint16_t cslot[SU_DMAX]; } tmp;
@@ -212,14 +212,14 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
   }
   __syncthreads();
   const uint32_t D = sm.ndist;
-  // (the rows are staged in the space of the unit's own launches, and in a task of more than UNIT_RUNS_MAX tiles a unit may be
-  // a single launch)
-  if (sm.fallback || D > SU_DMAX || sm.filled != m || D > 2 * (m >> 4)) {
-    // the whole task goes to the general path (k_long_general_values hands its per-launch values over)
-    if (tid == 0 && atomicExch(&A.mflag[t], 0u) == 1u) {
-      A.gflag[t] = 1;
-      atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->n_general), 1ull);
-    }
+  const uint64_t task_start = A.off[t];
+  const uint32_t task_len = static_cast<uint32_t>(A.off[t + 1] - task_start);
+  const bool fits = !sm.fallback && D <= SU_DMAX && sm.filled == m;
+  if (tid == 0) { sm.first_row = fits ? atomicAdd(&A.staged[t], D) : 0u; A.ustage[unit] = sm.first_row; }
+  __syncthreads();
+  const uint32_t row0 = sm.first_row;
+  if (!fits || row0 + D > stage_room(task_len)) {
+    if (tid == 0) unit_to_general(A, t);
     return;
   }
 
@@ -356,7 +356,7 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
 
   if (tid < D) {
     const uint32_t s = sm.slot_of[tid];
-    uint64_t* row = staged_row(A.stage_a, A.stage_b, base, m, tid);
+    uint64_t* row = staged_row(A.stage_a, A.stage_b, task_start, task_len, row0 + tid);
     const uint32_t gc = sm.gcnt[s];
     row[0] = sm.ht_key[s]; row[1] = t;
     row[2] = sm.cnt[s]; row[3] = sm.esum[s]; row[4] = sm.emin[s]; row[5] = sm.emax[s];

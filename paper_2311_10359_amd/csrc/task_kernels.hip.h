@@ -22,8 +22,8 @@
 //      means in LDS, the workgroup writes those predictions per launch itself, so that the gap fill does not have
 //      to read the Kernel IDs again and look each one up.
 //
-// Rows are staged in the task's own slice of two workspace arrays and moved to their final
-// place once every task's row count is known.  A task that does not fit (too many distinct IDs)
+// Rows are staged in the task's own slice of two workspace arrays (the units of a long task share its slice) and moved to
+// their final place once every task's row count is known.  A task that does not fit (too many distinct IDs)
 // writes its per-launch values to the workspace arrays instead and is flagged for the general
 // sort-based path.
 #pragma once
@@ -108,13 +108,15 @@ struct FusedSmem {
   uint32_t maxe, maxg;
   uint32_t ndist;
   uint32_t fallback;
+  uint32_t first_row;        // units: rows of the task that are staged before this unit's
   struct { uint64_t esum[HE], gsum[HE]; uint32_t emin[HE], emax[HE], gmin[HE], gmax[HE], nogap[HE]; } early;   // by slot
   uint16_t rslot[ESTATS ? DMAX : 1];   // rank -> slot
 };
 
 constexpr uint32_t NONE32 = 0xffffffffu;   // "no idle time after this launch" in the 32-bit value registers
 
-// Where row j of a task is staged: the task's slice of stage_a, then its slice of stage_b.
+// Where row j of a task is staged: the task's slice of stage_a, then its slice of stage_b, which hold stage_room rows.
+__device__ __forceinline__ uint32_t stage_room(uint32_t m) { return 2 * (m >> 4); }
 __device__ __forceinline__ uint64_t* staged_row(int64_t* stage_a, int64_t* stage_b, uint64_t base, uint32_t m, uint32_t j) {
   const uint32_t cap1 = m >> 4;  // rows of 16 words that fit in m words
   return j < cap1 ? reinterpret_cast<uint64_t*>(stage_a + base) + static_cast<uint64_t>(j) * 16
@@ -191,7 +193,7 @@ struct FusedArgs {
   int64_t* g0;
   uint64_t* key0;              // ... with their IDs, in the same order
   // units: groups of consecutive ID buckets of a long task, whose launches lie bucket-ordered inside every tile
-  const uint32_t* ustart;      // where the unit would start if the task were in bucket order: names its staging slice
+  const uint32_t* ustart;      // where the unit would start if the task were in bucket order (k_unit_stream packs its launches there)
   const uint32_t* ulen;
   const uint32_t* utask;
   const uint32_t* ubuckets;    // first bucket | (bucket after the last) << 16
@@ -201,9 +203,11 @@ struct FusedArgs {
   const uint64_t* part_id;     // tile-ordered IDs
   const uint2* part_kg;        // tile-ordered (execution time, idle time or NONE32)
   uint32_t* mflag;             // cleared when a unit sends its task to the general path
+  uint32_t* staged;            // per task: rows staged by its units so far (0 at the start) ...
+  uint32_t* ustage;            // ... and per unit: rows of its task that were staged before its own
   // both
-  int64_t* stage_a;            // rows are staged in the task's / unit's own slice of these two arrays
-  int64_t* stage_b;            // (for units they are also the source of exec and gap values)
+  int64_t* stage_a;            // rows are staged in the task's own slice of these two arrays
+  int64_t* stage_b;
   uint32_t* dcount;            // rows per task / per unit
   uint32_t* gflag;             // task takes the general path
   Ctrl* ctrl;
@@ -245,6 +249,13 @@ __device__ __forceinline__ void early_stats(Smem& sm, uint32_t s, uint32_t e, ui
   }
 }
 
+// The whole task of a unit goes to the general path (k_long_general_values hands its per-launch values over).  One thread.
+__device__ __forceinline__ void unit_to_general(const FusedArgs& A, uint32_t t) {
+  if (atomicExch(&A.mflag[t], 0u) != 1u) return;
+  A.gflag[t] = 1;
+  atomicAdd(reinterpret_cast<unsigned long long*>(&A.ctrl->n_general), 1ull);
+}
+
 template <int NT, int KPT, int DMAX, int HIST_WORDS, int LB, bool UNITS, int WPE, bool ESTATS = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 k_task_fused(const FusedArgs A) {
@@ -257,16 +268,19 @@ k_task_fused(const FusedArgs A) {
   if (blockIdx.x >= *A.count) return;
   const uint32_t unit = A.list[blockIdx.x];
   uint32_t t;          // owning task
-  uint64_t base;       // first launch / first sorted position
+  uint64_t base;       // first launch of the task
   uint64_t len64;
+  uint32_t task_len;   // (the rows' staging slice)
   if (UNITS) {
-    len64 = A.ulen[unit];
-    base = A.ustart[unit];
     t = A.utask[unit];
+    len64 = A.ulen[unit];
+    base = A.off[t];
+    task_len = static_cast<uint32_t>(A.off[t + 1] - base);
   } else {
     t = unit;
     base = A.off[t];
     len64 = A.off[t + 1] - base;
+    task_len = static_cast<uint32_t>(len64);
   }
   if (len64 == 0 || len64 > A.max_len) return;   // (cannot happen for a listed item)
   const uint32_t m = static_cast<uint32_t>(len64);
@@ -525,13 +539,9 @@ k_task_fused(const FusedArgs A) {
   if (lane_id() == 0) { atomicMax(&sm.maxe, my_maxe); atomicMax(&sm.maxg, my_maxg); }
   __syncthreads();
   const uint32_t D = sm.ndist;
-  if (sm.fallback || D > DMAX || D > 2 * (m >> 4)) {
+  if (sm.fallback || D > DMAX || (!UNITS && D > stage_room(m))) {
     if (UNITS) {
-      // the whole task goes to the general path (k_long_general_values hands its per-launch values over)
-      if (tid == 0 && atomicExch(&A.mflag[t], 0u) == 1u) {
-        gflag[t] = 1;
-        atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->n_general), 1ull);
-      }
+      if (tid == 0) unit_to_general(A, t);
       return;
     }
     // general path: hand over the per-launch values (recomputed at full width)
@@ -548,6 +558,11 @@ k_task_fused(const FusedArgs A) {
     if (tid == 0) { gflag[t] = 1; atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->n_general), 1ull); }
     return;
   }
+
+  // Units take the room for their rows from their task's, not from that of their own launches: a bucket of rarely launched
+  // kernels has more rows than its launches would leave room for.  (The answer is waited for where the rows are staged.)
+  uint32_t rows_before = 0;
+  if (UNITS && tid == 0) rows_before = atomicAdd(&A.staged[t], D);
 
   // digit width of the radix selection: 16-bit counters, two per word, shared by 4 * D (ID, percentile) pairs
   int B = 31 - __builtin_clz(static_cast<uint32_t>(HIST_WORDS * 2) / (4 * D));
@@ -660,12 +675,18 @@ k_task_fused(const FusedArgs A) {
       }
     }
   }
+  if (UNITS && tid == 0) { sm.first_row = rows_before; A.ustage[unit] = rows_before; }
   __syncthreads();
+  const uint32_t row0 = UNITS ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(sm.first_row))) : 0u;
+  if (UNITS && row0 + D > stage_room(task_len)) {
+    if (tid == 0) unit_to_general(A, t);
+    return;
+  }
   // (predictions: a thread stages at most one row, DMAX <= NT, and keeps that ID's means for after the barrier)
   const bool emit = !UNITS && A.pred_role != nullptr;
   uint32_t mean_e = 0, mean_g = 0;
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
+    uint64_t* row = staged_row(stage_a, stage_b, base, task_len, row0 + j);
     const uint32_t ec = sm.rcnt[j];
     uint32_t gc, emin, emax, gmin, gmax;
     uint64_t esum, gsum;
@@ -908,7 +929,7 @@ k_task_fused(const FusedArgs A) {
         const uint32_t arr = q >= D ? 1u : 0u, j = q - arr * D;
         const uint2 se = sel[q];
         const uint32_t b50 = sel_b50(se.y), b95 = sel_b95(se.y);
-        uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
+        uint64_t* row = staged_row(stage_a, stage_b, base, task_len, row0 + j);
         if (b50 == SEL_NO_BIN || !(se.y & SEL_LISTED)) {   // (not listed: bins one value wide where the scale is one to one)
           if (gl == 0) {
             const uint32_t v50 = b50 == SEL_NO_BIN ? 0 : value_of_scale(se.x + b50);
@@ -1034,7 +1055,7 @@ k_task_fused(const FusedArgs A) {
     __syncthreads();
   }
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
+    uint64_t* row = staged_row(stage_a, stage_b, base, task_len, row0 + j);
     const uint4 pf = sm.pref[j];
     row[6] = pf.x; row[7] = pf.y;
     row[12] = pf.z; row[13] = pf.w;

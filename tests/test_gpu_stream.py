@@ -3,6 +3,7 @@ profile against the CPU oracle, and whether the sort was needed."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2311_10359_amd import binding, traces
 from parity_util import check_profile
 
@@ -84,14 +85,47 @@ def with_rare(seed, tasks):
     return rec, off
 
 
+def sorted_with(rec, off):
+    """Compares the profile with the oracle's; was a task sorted?"""
+    binding.fikit_trace_enable(True)
+    try:
+        check_profile(rec, off)
+        return "k_onesweep_pass" in binding.fikit_trace_read()
+    finally:
+        binding.fikit_trace_enable(False)
+
+
 @pytest.mark.parametrize("tasks", [
-    [(4_300_000, 30, 40, 1), (900, 100, 0, 1)],                       # a short task's rows lie behind the small buckets' ones
-    [(900, 100, 0, 1), (4_300_000, 100, 300, 20)],                    # ... and the small buckets end the workspace's arrays
+    [(4_300_000, 30, 40, 1), (900, 100, 0, 1)],                       # more tiles than a unit can list: all buckets are streamed,
+    [(900, 100, 0, 1), (4_300_000, 100, 300, 20)],                    # also those of a single launch (here behind a short task's)
+    [(50_000, 10, 5, 1)],                                             # a bucket of one launch between two of which neither
+    [(100_000, 20, 5, 1), (20_000, 40, 9, 2), (700, 30, 0, 1)],       # can take it in
+    [(131_072, 30, 5, 1), (131_073, 30, 5, 1)],
+    [(1_000_000, 20, 5, 1), (300_000, 3, 200, 15)],                   # ... beside streamed ones
 ])
-def test_rare_ids_beside_frequent_ones_in_more_tiles_than_a_unit_can_list(tasks):
-    """Buckets of one launch or a few in a task whose buckets are all streamed: their rows need more room than their launches."""
+def test_rare_ids_beside_frequent_ones(tasks):
+    """Buckets with more rows than their launches would leave room for: the rows' room is the task's, nothing is sorted."""
     print(f"tasks {tasks}", flush=True)
-    check_profile(*with_rare(len(tasks) + tasks[0][0], tasks))
+    assert not sorted_with(*with_rare(len(tasks) + tasks[0][0], tasks))
+
+
+def test_more_rows_than_the_task_has_room_for():
+    """Nine units of 256 IDs each in 16,644 launches: 2304 rows, room for 2080.  The task is sorted."""
+    names = np.arange(400_000, dtype=np.uint32)
+    rec = np.zeros(names.size, dtype=traces.LAUNCH_DTYPE)
+    rec["name_id"], rec["grid"], rec["block"] = names, 1, 64
+    top = oracle.profile(rec, np.array([0, names.size], dtype=np.uint64))[0] >> np.uint64(56)
+    kid = []
+    for unit, launches in enumerate([256, 3841] * 4 + [256]):
+        mine = names[top == 20 * unit + 3][:256]
+        assert mine.size == 256
+        kid.append(np.resize(mine, launches))
+    kid = np.random.default_rng(3).permutation(np.concatenate(kid))
+    rec = np.zeros(kid.size, dtype=traces.LAUNCH_DTYPE)
+    rec["name_id"], rec["grid"], rec["block"] = kid, 1, 64
+    rec["start_ns"] = np.arange(kid.size) * 1000
+    rec["end_ns"] = rec["start_ns"] + 1 + kid % 997
+    assert sorted_with(rec, np.array([0, kid.size], dtype=np.uint64))
 
 
 def test_more_tiles_than_a_unit_can_list():
