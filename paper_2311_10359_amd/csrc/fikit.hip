@@ -188,15 +188,22 @@ int status_from_bits(uint32_t bits) {
 struct Mailbox {
   static constexpr size_t BYTES = 256;
   unsigned char* at = nullptr;
-  ~Mailbox() { if (at) (void)hipHostFree(at); }
+  // (another thread may be capturing a graph, which an allocation or a release in the default mode would break)
+  struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~Relaxed() { if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  };
+  ~Mailbox() {
+    if (!at) return;
+    const Relaxed relaxed;
+    (void)hipHostFree(at);
+  }
   unsigned char* get() {
     if (!at) {
-      // (another thread may be capturing a graph, which an allocation in the default mode would break)
-      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+      const Relaxed relaxed;
       void* p = nullptr;
       if (hipHostMalloc(&p, BYTES, hipHostMallocPortable) == hipSuccess) at = static_cast<unsigned char*>(p);
-      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
       (void)hipGetLastError();
     }
     return at;
