@@ -38,7 +38,7 @@ ALGO_BYTES_PER_RECORD = {
     "k_onesweep_pass": 24 + 24,
     "k_unit_fused": 16,
 }
-GAPFILL_KERNELS = ("k_gf_predict", "k_gf_walk", "k_gf_predict32", "k_gf_walk_lanes")
+GAPFILL_KERNELS = ("k_gf_predict32", "k_gf_walk_wave", "k_gf_walk_lanes")
 
 
 def source_hash():
@@ -451,7 +451,7 @@ def main():
     avg_ms = dom_ms / dom_cnt
     if dom in ALGO_BYTES_PER_RECORD:
         algo_bytes = ALGO_BYTES_PER_RECORD[dom] * units[dom]
-        if one_call and n_scen >= 4096 and dom.startswith("k_task_fused_"):
+        if one_call and n_scen and dom.startswith("k_task_fused_"):
             # one call: the task kernels also write the predictions that the gap fill reads (4 bytes per launch of a
             # task used as queue, 8 per launch of a task used as trace), which k_gf_predict32 writes otherwise
             lo, hi = {"k_task_fused_small": (0, 4096), "k_task_fused_mid": (4096, 8192), "k_task_fused_medium": (8192, 16384)}[dom]
@@ -460,14 +460,11 @@ def main():
             is_hp[hp] = True
             is_lp[lp] = True
             algo_bytes += 8 * int(lens[in_class & is_hp].sum()) + 4 * int(lens[in_class & is_lp].sum())
-    elif dom == "k_gf_predict":      # IDs read; prefix sums, idle times and gap-open times written (8 bytes each)
-        algo_bytes = 8 * (n_hp + n_lp) + 8 * n_lp + 16 * n_hp
     elif dom == "k_gf_predict32":    # IDs read; 32-bit execution times (queue) and (execution, idle) pairs (trace) written
         algo_bytes = 8 * (n_hp + n_lp) + 4 * n_lp + 8 * n_hp
     else:                            # every scenario reads its trace and its queue once and writes 12 bytes per gap
-        per_hp, per_lp = (8, 8) if dom == "k_gf_walk" else (8, 4)
-        algo_bytes = per_hp * n_hp * (n_scen // max(1, len(np.unique(hp)))) \
-            + per_lp * n_lp * (n_scen // max(1, len(np.unique(lp)))) + 12 * n_gaps
+        algo_bytes = 8 * n_hp * (n_scen // max(1, len(np.unique(hp)))) \
+            + 4 * n_lp * (n_scen // max(1, len(np.unique(lp)))) + 12 * n_gaps
     achieved = algo_bytes / (avg_ms * 1e-3) / 1e9
     # (stored counters of a workload with scenarios are of the one-call step)
     counters = stored_counters(name if one_call or not n_scen else name + " (two calls)") \

@@ -727,11 +727,12 @@ void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64
 
 // The walk on 32-bit predictions in one of its modes; `result`: completion times, or delays in the replay modes.
 template <int MODE>
-int walk_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_task_offsets, const uint32_t* d_hp_task,
+int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_task_offsets, const uint32_t* d_hp_task,
                  const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets, uint64_t n_gaps, int64_t margin,
                  int64_t min_gap, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* result, uint64_t* d_lp_placed,
                  bool set_attributes) {
   if (n_scenarios >= GF_LANES_MIN_SCENARIOS && n_gaps < MAX_ELEMS) {
+    tr.mark(MODE == LW_PLAN ? "k_gf_walk_lanes" : MODE == LW_REPLAY ? "k_gf_replay_lanes" : "k_gf_replay_feedback_lanes");
     if (set_attributes)
       FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gf_walk_lanes<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(sizeof(LaneWalkSmem))));
@@ -740,6 +741,7 @@ int walk_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_task
                        d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
                        d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, b.ctrl);
   } else {
+    tr.mark(MODE == LW_PLAN ? "k_gf_walk_wave" : MODE == LW_REPLAY ? "k_gf_replay_wave" : "k_gf_replay_feedback_wave");
     hipLaunchKernelGGL(k_gf_walk_wave<MODE>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st, d_task_offsets,
                        d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,
                        d_filled_ns, result, d_lp_placed, b.ctrl);
@@ -759,9 +761,9 @@ int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const u
   hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                      n_tasks, d_rows, d_task_row_offsets, b.role, static_cast<const int64_t*>(nullptr), b.lp_e, b.hp_eg, b.lp_total,
                      static_cast<uint32_t>(h_params->predictor), done, b.ctrl);
-  tr.mark("k_gf_walk");
-  return walk_enqueue<LW_PLAN>(st, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
-                               h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, set_attributes);
+  return walk_enqueue<LW_PLAN>(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps,
+                               h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
+                               set_attributes);
 }
 
 // The 64-bit kernels, which do the call if a prediction did not fit 32 bits (they check Ctrl::wide).
@@ -1070,9 +1072,8 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                      n_tasks, d_rows, d_task_row_offsets, b.role, d_actual_gap_ns, b.lp_e, b.hp_eg, b.lp_total,
                      static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), b.ctrl);
-  tr.mark(h_params->feedback ? "k_gf_replay_feedback" : "k_gf_replay");
   auto walk = h_params->feedback ? walk_enqueue<LW_REPLAY_FEEDBACK> : walk_enqueue<LW_REPLAY>;
-  if (int rc = walk(st, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
+  if (int rc = walk(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
                     h_params->min_gap_ns, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, true))
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&]() -> int {
@@ -1163,7 +1164,6 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
                        n_tasks, d_rows, d_task_row_offsets, role, static_cast<const int64_t*>(nullptr), lp_e, hp_eg, lp_total,
                        static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), ctrl);
     const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
-    tr.mark("k_pf_walk");
     int rc = FIKIT_OK;
 #define FIKIT_PF_WALK(W)                                                                                                   \
   rc = launch_prio_walk<W>(st, d_task_offsets, d_hp_task, d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, d_gap_offsets, \
@@ -1181,12 +1181,13 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
     //   3 tasks  64: 0.80 / 2.2   4096: 1.07 / 2.34   8192: 1.74 / 2.39   12,288: 2.41 / 2.76
     //   4 tasks  4096: 1.42 / 2.64   12,288: 2.88 / 3.11   6 tasks  4096: 1.59 / 3.41   12,288: 3.14 / 3.99
     //   9 tasks  4096: 1.71 / 3.75   16,384: 3.97 / 5.47   24,576: 5.51 / 7.75
-    const bool waves = n_scenarios <= (widest <= 1 || widest > 8 ? 24576u : 12288u);
+    const bool waves = widest <= 16 && n_scenarios <= (widest <= 1 || widest > 8 ? 24576u : 12288u);
+    tr.mark(waves ? "k_pf_walk_wave" : "k_pf_walk");
     if (waves && widest <= 1) FIKIT_PF_WAVE(64);
     else if (waves && widest <= 2) FIKIT_PF_WAVE(32);
     else if (waves && widest <= 4) FIKIT_PF_WAVE(16);
     else if (waves && widest <= 8) FIKIT_PF_WAVE(8);
-    else if (waves && widest <= 16) FIKIT_PF_WAVE(4);
+    else if (waves) FIKIT_PF_WAVE(4);
     else if (widest <= 1) FIKIT_PF_WALK(1);
     else if (widest <= 2) FIKIT_PF_WALK(2);
     else if (widest <= 4) FIKIT_PF_WALK(4);
