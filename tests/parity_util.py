@@ -1,5 +1,7 @@
 """Shared helpers of the GPU parity tests: run the HIP library and the CPU oracle on the same
 seeded inputs and compare every output bit for bit."""
+from contextlib import contextmanager
+
 import numpy as np
 import torch
 
@@ -7,6 +9,22 @@ import oracle
 from paper_2311_10359_amd import binding, traces
 
 DEV = "cuda:0"
+
+
+# From this many scenarios on the gap fill and the replay step through a scenario with one lane, below it with a wave.
+LANES_MIN_SCENARIOS = 32768
+
+
+@contextmanager
+def kernels_of():
+    """A set that holds, after the block, the names under which the library timed the launches of the calls in it."""
+    names = set()
+    binding.fikit_trace_enable(True)
+    try:
+        yield names
+        names.update(binding.fikit_trace_read())
+    finally:
+        binding.fikit_trace_enable(False)
 
 
 def run_profile_gpu(rec, off, **kw):

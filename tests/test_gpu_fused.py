@@ -1,14 +1,14 @@
 """fikit_profile_gapfill (the two calls of the hot path as one) against the oracle: every output of the profile and of
-the gap fill, bit for bit, where the profile's own kernels write the predictions (many scenarios, tasks that one
-workgroup holds) and where they do not (few scenarios, long tasks, tasks left to the sort, predictions beyond 32 bits)."""
+the gap fill, bit for bit, where the profile's own kernels write the predictions (tasks that one workgroup holds) and where
+they do not (long tasks, tasks left to the sort, predictions beyond 32 bits)."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2311_10359_amd import binding, traces
-from parity_util import DEV, assert_profile_equal
-from test_gpu_parity import all_pairs, mixed_trace, ragged_trace
+from parity_util import DEV, LANES_MIN_SCENARIOS, assert_profile_equal, kernels_of
+from test_gpu_parity import RAGGED_LENS, all_pairs, mixed_trace, ragged_trace
 
 pytestmark = pytest.mark.gpu
 
@@ -33,23 +33,26 @@ def check_fused(rec, off, hp, lp, margin, min_gap, predictor=0, o_prof=None):
 
 
 def test_batched_workload_shape():
-    """The benchmark's shape at a reduced size: a high-priority trace and a low-priority queue per scenario, one lane
-    per scenario; launches beyond 4096 and 8192 so that all three shapes of the task kernel write predictions."""
+    """The benchmark's shape at a reduced size: a high-priority trace and a low-priority queue per scenario (so few that a wave
+    takes each); launches beyond 4096 and 8192 so that all three shapes of the task kernel write predictions."""
     for hp_l, lp_l in ((300, 1200), (4100, 8300)):
         cfg = traces.config(4, n_tasks=8400 if hp_l == 300 else 8200, hp_launches=hp_l, lp_launches=lp_l)
         rec, off = traces.build(cfg, threads=4)
         hp, lp = traces.scenarios(cfg)
-        assert hp.size >= 4096
         o = check_fused(rec, off, hp, lp, cfg.margin_ns, cfg.min_gap_ns)
         check_fused(rec, off, hp, lp, 0, 100000, predictor=binding.FIKIT_PREDICT_MEAN, o_prof=o)
 
 
 def test_shared_tasks_in_both_roles():
-    """Every ordered pair of 72 tasks (a task against itself included): tasks are trace and queue at once."""
-    cfg = traces.config(4, n_tasks=72, hp_launches=301, lp_launches=1203)
+    """Every ordered pair of 182 tasks (a task against itself included), which the lane walk takes: tasks are trace and queue at
+    once."""
+    cfg = traces.config(4, n_tasks=182, hp_launches=201, lp_launches=803)
     rec, off = traces.build(cfg, threads=4)
     hp, lp = all_pairs(range(cfg.n_tasks))
-    o = check_fused(rec, off, hp, lp, cfg.margin_ns, cfg.min_gap_ns)
+    assert hp.size >= LANES_MIN_SCENARIOS
+    with kernels_of() as names:
+        o = check_fused(rec, off, hp, lp, cfg.margin_ns, cfg.min_gap_ns)
+    assert "k_gf_walk_lanes" in names and "k_gf_walk_wave" not in names
     check_fused(rec, off, hp, lp, 40000, 0, predictor=binding.FIKIT_PREDICT_MEAN, o_prof=o)
 
 
@@ -63,15 +66,14 @@ def test_mixed_task_shapes():
 
 
 def test_ragged_and_empty_tasks():
-    lens = [0, 1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 100, 127, 129, 255, 257, 500, 1000, 1001, 2047,
-            0, 5, 6, 40, 41, 42, 43, 44] + [11 * k + 1 for k in range(32)]
+    lens = RAGGED_LENS
     rec, off = ragged_trace(4242, lens, 9)
     hp, lp = all_pairs(range(len(lens)))
     check_fused(rec, off, hp, lp, 300, 0)
 
 
 def test_few_scenarios_and_none():
-    """Fewer scenarios than the one-lane kernels are used for: the call is the two calls; no scenario: the profile."""
+    """A few scenarios; no scenario: the profile."""
     cfg = traces.config(1, n_tasks=8, launches=3000)
     rec, off = traces.build(cfg, threads=4)
     hp, lp = traces.scenarios(cfg)

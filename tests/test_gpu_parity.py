@@ -8,7 +8,7 @@ import torch
 
 import oracle
 from paper_2311_10359_amd import binding, traces
-from parity_util import DEV, assert_profile_equal, check_gapfill, check_profile, run_profile_gpu
+from parity_util import DEV, LANES_MIN_SCENARIOS, assert_profile_equal, check_gapfill, check_profile, kernels_of, run_profile_gpu
 from test_oracle_pins import make_records
 
 pytestmark = pytest.mark.gpu
@@ -115,31 +115,43 @@ def all_pairs(tasks):
     return np.repeat(t, t.size), np.tile(t, t.size)
 
 
+# Empty, one-launch and odd-length tasks; all pairs are more scenarios than are walked by wave.
+RAGGED_LENS = [0, 1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 100, 127, 129, 255, 257, 500, 1000, 1001, 2047,
+               0, 5, 6, 40, 41, 42, 43, 44] + [11 * k + 1 for k in range(32)] + list(range(118))
+
+
 def test_many_scenarios_take_one_lane_each():
     """Thousands of scenarios over shared tasks (every ordered pair, a task against itself included):
     the one-lane-per-scenario kernels, with and without a margin and a minimum gap."""
-    cfg = traces.config(4, n_tasks=72, hp_launches=301, lp_launches=1203)
+    cfg = traces.config(4, n_tasks=182, hp_launches=101, lp_launches=403)
     rec, off = traces.build(cfg, threads=4)
     prof, d_off, o_prof = check_profile(rec, off)
     hp, lp = all_pairs(range(cfg.n_tasks))
-    assert hp.size >= 4096
-    for margin, min_gap in ((cfg.margin_ns, cfg.min_gap_ns), (0, 100000), (40000, 0)):
-        print(f"{hp.size} scenarios, margin {margin}, min gap {min_gap}", flush=True)
-        check_gapfill(prof, d_off, off, o_prof, hp, lp, margin, min_gap)
-    check_gapfill(prof, d_off, off, o_prof, hp, lp, cfg.margin_ns, cfg.min_gap_ns, predictor=binding.FIKIT_PREDICT_MEAN)
+    assert hp.size >= LANES_MIN_SCENARIOS
+    with kernels_of() as names:
+        for margin, min_gap in ((cfg.margin_ns, cfg.min_gap_ns), (0, 100000), (40000, 0)):
+            print(f"{hp.size} scenarios, margin {margin}, min gap {min_gap}", flush=True)
+            check_gapfill(prof, d_off, off, o_prof, hp, lp, margin, min_gap)
+        check_gapfill(prof, d_off, off, o_prof, hp, lp, cfg.margin_ns, cfg.min_gap_ns, predictor=binding.FIKIT_PREDICT_MEAN)
+    assert "k_gf_walk_lanes" in names and "k_gf_walk_wave" not in names
 
 
 def test_many_scenarios_ragged_tasks_and_unaligned_outputs():
     """Empty, one-launch and odd-length tasks in both roles; result buffers that are not 16-byte aligned."""
-    lens = [0, 1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 100, 127, 129, 255, 257, 500, 1000, 1001, 2047,
-            0, 5, 6, 40, 41, 42, 43, 44] + [11 * k + 1 for k in range(32)]
+    lens = RAGGED_LENS
     rec, off = ragged_trace(4242, lens, 9)
     prof, d_off, o_prof = check_profile(rec, off)
     hp, lp = all_pairs(range(len(lens)))
-    assert hp.size >= 4096
+    assert hp.size >= LANES_MIN_SCENARIOS
     print(f"{hp.size} scenarios over {len(lens)} ragged tasks", flush=True)
-    check_gapfill(prof, d_off, off, o_prof, hp, lp, 300, 0)
-    check_gapfill(prof, d_off, off, o_prof, hp, lp, 0, 5000)
+    few = hp < 64                                             # ... and so few that a wave takes each
+    with kernels_of() as names:
+        check_gapfill(prof, d_off, off, o_prof, hp, lp, 300, 0)
+        check_gapfill(prof, d_off, off, o_prof, hp, lp, 0, 5000)
+    assert "k_gf_walk_lanes" in names and "k_gf_walk_wave" not in names
+    with kernels_of() as names:
+        check_gapfill(prof, d_off, off, o_prof, hp[few], lp[few], 300, 0)
+    assert "k_gf_walk_wave" in names
     # the same through buffers that start 4 / 8 bytes past a 16-byte boundary
     go = traces.gap_offsets(off, hp)
     n_gaps = int(go[-1])
@@ -237,7 +249,7 @@ def test_mixed_task_shapes(seed):
 
 
 def test_mixed_task_shapes_many_scenarios():
-    """The same variety through the one-lane-per-scenario kernels: every ordered pair of 64 tasks."""
+    """The same variety with every ordered pair of 64 tasks."""
     rec, off, lens = mixed_trace(21, 64, max_len=4097, wide=False)
     print(f"{rec.shape[0]} records, task lengths {lens[:16]} ...", flush=True)
     prof, d_off, o_prof = check_profile(rec, off)
@@ -248,14 +260,14 @@ def test_mixed_task_shapes_many_scenarios():
 
 def test_gapfill_ids_at_an_address_that_is_not_16_byte_aligned():
     """The IDs may sit at any 8-byte aligned address (a view that starts one element into a buffer)."""
-    cfg = traces.config(4, n_tasks=8200, hp_launches=30, lp_launches=50)      # 4100 scenarios: one lane each
+    cfg = traces.config(4, n_tasks=8200, hp_launches=30, lp_launches=50)      # 4100 scenarios
     rec, off = traces.build(cfg, threads=4)
     prof, d_off, o_prof = check_profile(rec, off)
     shifted = torch.empty(prof.ids.numel() + 1, dtype=torch.int64, device=DEV)
     shifted[1:].copy_(prof.ids)
     assert shifted[1:].data_ptr() % 16 == 8
     hp, lp = traces.scenarios(cfg)
-    for pick in (slice(None), slice(0, 50)):                                  # ... and one wave each
+    for pick in (slice(None), slice(0, 50)):
         check_gapfill(prof._replace(ids=shifted[1:]), d_off, off, o_prof, hp[pick], lp[pick], cfg.margin_ns, cfg.min_gap_ns)
 
 

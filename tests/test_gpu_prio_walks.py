@@ -2,8 +2,10 @@
 one launch shorter and longer than a window, many equal durations, levels shared and not, against the CPU oracle."""
 import numpy as np
 import pytest
+import torch
 
-from parity_util import check_profile
+from paper_2311_10359_amd import binding, traces
+from parity_util import DEV, check_profile, kernels_of
 from test_gpu_prio import check_prio, prio_lists
 from test_gpu_walk import trace_of
 
@@ -24,3 +26,22 @@ def test_prio_walk_edges(k_max, n_scen):
             hp, lo, lt, lq = prio_lists(np.random.default_rng(seed), len(lens), n_scen, k_max, same_level)
             print(f"{n_scen} scenarios, up to {k_max} tasks, durations {execs}, same level {same_level}", flush=True)
             check_prio(prof, d_off, off, o_prof, hp, lo, lt, lq, 3, 5)
+
+
+@pytest.mark.parametrize("k_max", [1, 2, 3, 7, 16])
+def test_prio_groups_of_lanes_on_long_queues(k_max):
+    """So many scenarios that a group of lanes takes each: queues that pass through the kernel's rings many times, traces whose
+    results do too, result buffers off a 16-byte boundary."""
+    lens = [0, 1, 17, 64, 95, 127, 128, 129, 191, 257, 311, 400, 513]
+    rec, off = trace_of(k_max, lens, [100, 250, 40], [0, 90, 900, 4000])
+    prof, d_off, o_prof = check_profile(rec, off)
+    hp, lo, lt, lq = prio_lists(np.random.default_rng(k_max), len(lens), 24600, k_max, 0.5)
+    n_gaps = int(traces.gap_offsets(off, hp)[-1])
+    out = binding.PrioFill(torch.empty(n_gaps + 1, dtype=torch.int32, device=DEV)[1:],
+                           torch.empty(n_gaps + 1, dtype=torch.int64, device=DEV)[1:],
+                           torch.empty(lt.size, dtype=torch.int64, device=DEV), torch.empty(lt.size, dtype=torch.int64, device=DEV))
+    with kernels_of() as names:
+        for buffers in (None, out):
+            print(f"{hp.size} scenarios of up to {k_max} tasks, {n_gaps} gaps", flush=True)
+            check_prio(prof, d_off, off, o_prof, hp, lo, lt, lq, 3, 5, out=buffers)
+    assert "k_pf_walk" in names and "k_pf_walk_wave" not in names

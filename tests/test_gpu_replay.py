@@ -9,8 +9,8 @@ import torch
 
 import oracle
 from paper_2311_10359_amd import binding, traces
-from parity_util import DEV, check_profile
-from test_gpu_parity import all_pairs, mixed_trace, ragged_trace
+from parity_util import DEV, LANES_MIN_SCENARIOS, check_profile, kernels_of
+from test_gpu_parity import RAGGED_LENS, all_pairs, mixed_trace, ragged_trace
 from test_oracle_pins import replay_inputs
 
 pytestmark = pytest.mark.gpu
@@ -94,27 +94,38 @@ def test_replay_small_configs(name):
         check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, margin, min_gap)
 
 
+REPLAY_BY_LANE, REPLAY_BY_WAVE = {"k_gf_replay_lanes", "k_gf_replay_feedback_lanes"}, {"k_gf_replay_wave", "k_gf_replay_feedback_wave"}
+
+
 def test_replay_many_scenarios():
-    cfg = traces.config(4, n_tasks=72, hp_launches=301, lp_launches=1203)
+    cfg = traces.config(4, n_tasks=182, hp_launches=101, lp_launches=403)
     rec, off = traces.build(cfg, threads=4)
     prof, d_off, o_prof = check_profile(rec, off)
     d_gap, gap = check_measure(rec, off)
     hp, lp = all_pairs(range(cfg.n_tasks))
-    for margin, min_gap in ((cfg.margin_ns, cfg.min_gap_ns), (0, 100000), (40000, 0)):
-        print(f"{hp.size} scenarios, margin {margin}, min gap {min_gap}", flush=True)
-        check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, margin, min_gap)
-    check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, cfg.margin_ns, cfg.min_gap_ns, predictor=binding.FIKIT_PREDICT_MEAN)
+    assert hp.size >= LANES_MIN_SCENARIOS
+    with kernels_of() as names:
+        for margin, min_gap in ((cfg.margin_ns, cfg.min_gap_ns), (0, 100000), (40000, 0)):
+            print(f"{hp.size} scenarios, margin {margin}, min gap {min_gap}", flush=True)
+            check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, margin, min_gap)
+        check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, cfg.margin_ns, cfg.min_gap_ns, predictor=binding.FIKIT_PREDICT_MEAN)
+    assert REPLAY_BY_LANE <= names and not REPLAY_BY_WAVE & names
 
 
 def test_replay_ragged_tasks_and_unaligned_outputs():
-    lens = [0, 1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 100, 127, 129, 255, 257, 500, 1000, 1001, 2047,
-            0, 5, 6, 40, 41, 42, 43, 44] + [11 * k + 1 for k in range(32)]
+    lens = RAGGED_LENS
     rec, off = ragged_trace(4242, lens, 9)
     prof, d_off, o_prof = check_profile(rec, off)
     d_gap, gap = check_measure(rec, off)
     hp, lp = all_pairs(range(len(lens)))
-    check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 300, 0)
-    check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 0, 5000)
+    few = hp < 64                                             # so few that a wave takes each
+    with kernels_of() as names:
+        check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 300, 0)
+        check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 0, 5000)
+    assert REPLAY_BY_LANE <= names and not REPLAY_BY_WAVE & names
+    with kernels_of() as names:
+        check_replay(prof, d_off, off, o_prof, d_gap, gap, hp[few], lp[few], 300, 0)
+    assert REPLAY_BY_WAVE <= names
     n_gaps = int(traces.gap_offsets(off, hp)[-1])
     out = binding.Replay(torch.empty(n_gaps + 1, dtype=torch.int32, device=DEV)[1:],
                          torch.empty(n_gaps + 1, dtype=torch.int64, device=DEV)[1:],

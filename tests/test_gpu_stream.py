@@ -4,8 +4,8 @@ import numpy as np
 import pytest
 
 import oracle
-from paper_2311_10359_amd import binding, traces
-from parity_util import check_profile
+from paper_2311_10359_amd import traces
+from parity_util import check_profile, kernels_of
 
 pytestmark = pytest.mark.gpu
 LONG = 1 << 18      # tasks from this length on are not sorted for a frequent ID
@@ -49,12 +49,8 @@ def skewed(seed, lens, n_ids, heavy, times):
 def test_frequent_ids(lens, n_ids, heavy, times, sorts):
     print(f"lengths {lens}, {n_ids} IDs, share of the first {heavy}, {times}", flush=True)
     rec, off = skewed(len(lens) + n_ids, lens, n_ids, heavy, times)
-    binding.fikit_trace_enable(True)
-    try:
+    with kernels_of() as names:
         check_profile(rec, off)
-        names = binding.fikit_trace_read()
-    finally:
-        binding.fikit_trace_enable(False)
     assert ("k_onesweep_pass" in names) == sorts, sorted(names)
 
 
@@ -87,12 +83,9 @@ def with_rare(seed, tasks):
 
 def sorted_with(rec, off):
     """Compares the profile with the oracle's; was a task sorted?"""
-    binding.fikit_trace_enable(True)
-    try:
+    with kernels_of() as names:
         check_profile(rec, off)
-        return "k_onesweep_pass" in binding.fikit_trace_read()
-    finally:
-        binding.fikit_trace_enable(False)
+    return "k_onesweep_pass" in names
 
 
 @pytest.mark.parametrize("tasks", [

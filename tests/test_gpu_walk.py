@@ -1,10 +1,10 @@
-"""The walk of the gap fill and of the replay where its windows begin and end: queues and traces one launch shorter and longer
+"""The walks of the gap fill and of the replay where their windows begin and end: queues and traces one launch shorter and longer
 than a window, gaps that take several windows, and running sums of the queue that pass 32 bits, against the CPU oracle."""
 import numpy as np
 import pytest
 
 from paper_2311_10359_amd import traces
-from parity_util import check_gapfill, check_profile
+from parity_util import LANES_MIN_SCENARIOS, check_gapfill, check_profile, kernels_of
 from test_gpu_parity import all_pairs
 from test_gpu_replay import check_measure, check_replay
 
@@ -35,14 +35,17 @@ def trace_of(seed, lens, exec_choices, gap_choices):
     ([1 << 31, (1 << 32) - 2, 5], [0, 9, 1 << 31, (1 << 32) - 2]),   # running sums past 32 bits
     ([1 << 26, 3 << 25, 1], [1 << 27, 1 << 30, 2]),             # ... after many launches
 ])
-@pytest.mark.parametrize("copies", [1, 3])                      # 676 scenarios; 6084 in the second form
+@pytest.mark.parametrize("copies", [1, 3, 7])                   # 676 and 6084 scenarios: a wave each; 33,124: a lane each
 def test_walk_edges(exec_choices, gap_choices, copies):
     lens = [1, 2, 3, 8, 15, 16, 17, 31, 32, 33, 61, 62, 63, 64, 65, 125, 126, 127, 128, 129, 189, 190, 255, 256, 257, 700] * copies
     rec, off = trace_of(copies + len(gap_choices), lens, exec_choices, gap_choices)
     prof, d_off, o_prof = check_profile(rec, off)
     hp, lp = all_pairs(range(len(lens)))
-    for margin, min_gap in ((0, 0), (3, 50)):
-        print(f"{hp.size} scenarios, durations {exec_choices}, margin {margin}", flush=True)
-        check_gapfill(prof, d_off, off, o_prof, hp, lp, margin, min_gap)
+    with kernels_of() as names:
+        for margin, min_gap in ((0, 0), (3, 50)):
+            print(f"{hp.size} scenarios, durations {exec_choices}, margin {margin}", flush=True)
+            check_gapfill(prof, d_off, off, o_prof, hp, lp, margin, min_gap)
+    walks = names & {"k_gf_walk_lanes", "k_gf_walk_wave"}
+    assert walks == {"k_gf_walk_lanes" if hp.size >= LANES_MIN_SCENARIOS else "k_gf_walk_wave"}
     d_gap, gap = check_measure(rec, off)
     check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 3, 0)

@@ -8,16 +8,17 @@ import pytest
 import torch
 
 from paper_2311_10359_amd import binding, traces
+from test_gpu_parity import all_pairs
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def run_both(cfg, margin, min_gap, predictor=binding.FIKIT_PREDICT_P50):
+def run_both(cfg, margin, min_gap, predictor=binding.FIKIT_PREDICT_P50, pairs=traces.scenarios):
     rec, off = traces.build(cfg, threads=4)
     d_off = binding.to_device_u64(off, DEV)
     prof = binding.fikit_profile(binding.to_device_records(rec, DEV), d_off)
-    hp, lp = traces.scenarios(cfg)
+    hp, lp = pairs(cfg)
     go = traces.gap_offsets(off, hp)
     d_hp, d_lp, d_go = binding.to_device_u32(hp, DEV), binding.to_device_u32(lp, DEV), binding.to_device_u64(go, DEV)
     want = binding.fikit_gapfill(prof.ids, d_off, prof.rows, prof.task_row_offsets, d_hp, d_lp, d_go, margin_ns=margin,
@@ -43,10 +44,14 @@ def run_both(cfg, margin, min_gap, predictor=binding.FIKIT_PREDICT_P50):
 
 
 def test_two_calls_in_a_row_the_second_smaller():
-    # many scenarios (one lane per scenario): 4096 scenarios of 64 + 190 launches = 1,040,384 launches
+    # 4096 scenarios of 64 + 190 launches = 1,040,384 launches
     big = traces.config(4, n_tasks=8192, hp_launches=64, lp_launches=190)
     small = traces.config(4, n_tasks=40, hp_launches=500, lp_launches=1500)
     assert run_both(big, 500, 0) > 0
+    assert run_both(small, 500, 0) > 0
+    # so many scenarios that a lane takes each
+    all_of = traces.config(4, n_tasks=182, hp_launches=101, lp_launches=403)
+    assert run_both(all_of, 500, 0, pairs=lambda cfg: all_pairs(range(cfg.n_tasks))) > 0
     assert run_both(small, 500, 0) > 0
     # few scenarios sharing traces (one wave per scenario), the paper's 0.1 ms threshold, the mean predictor
     grid = traces.config(1, n_tasks=8, launches=20000)
