@@ -468,7 +468,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     ua.ustart = ustart; ua.ulen = ulen; ua.utask = utask; ua.ubuckets = ubuckets; ua.tile_prefix = mtiles; ua.bound = bound;
     ua.tile_len = PT_TILE; ua.part_id = k1; ua.part_kg = part_kg; ua.mflag = mflag; ua.dcount = udcount;
     ua.staged = dcount; ua.ustage = ustage;   // (a long task's row count is 0 until k_msd_task_rows: the sum of what was staged)
-    // (first, because its largest units take longest; a unit has more than FUSE_MAX launches, or is one of the
+    // (first, because its largest units take longest; a streamed unit has more than FUSE_MAX launches, or is one of the
     // MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
     tr.mark("k_unit_stream");
     FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -659,8 +659,15 @@ int fikit_profile(const fikit_launch* d_records, uint64_t n_records, const uint6
 // The per-launch arrays of the gap fill are read in 64-byte pieces that may reach past the last launch.
 constexpr uint64_t GF_PAD = 256;
 // From this many scenarios on, one lane steps through a scenario (k_gf_walk_lanes), below it a wave (k_gf_walk_wave).  The
-// lanes take about 3.3 ms for traces of 4096 and queues of 16,384 launches, however many they are (to 65,536); the waves 0.1 ms
-// per 1024 scenarios of that shape once the chip is full (1.44 ms against 3.2 ms at 16,384).
+// lanes' time hardly depends on how many there are (to 65,536); the waves' grows with them, and with the gaps that take
+// something.  Traces of 4096 and queues of 16,384 launches: the lanes 3.3 ms, the waves 0.1 ms per 1024 scenarios once the chip
+// is full (1.44 ms against 3.2 ms at 16,384).  Calls over shorter tasks, waves / lanes in ms (gap fill; replay with feedback):
+//   1024 gaps that take about one kernel each   16,384: 0.41 / 0.52; 0.48 / 0.55   24,000: 0.52 / 0.54; 0.60 / 0.56
+//                                               32,000: 0.63 / 0.55; 0.75 / 0.56
+//   512 gaps that take about ten each           16,384: 0.55 / 1.30; 0.61 / 1.22   32,000: 0.91 / 1.32; 1.05 / 1.25
+//   2048 gaps of which few take anything        16,384: 0.20 / 0.79; 0.20 / 0.84   32,000: 0.29 / 0.81; 0.29 / 0.85
+// The line lies where the waves of the longest of these shapes stop being ahead; what gaps take is not known when it is drawn,
+// and from about 24,000 scenarios on gaps of one kernel each are better off with the lanes.
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
 
 }  // extern "C"
@@ -1181,6 +1188,13 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
     //   3 tasks  64: 0.80 / 2.2   4096: 1.07 / 2.34   8192: 1.74 / 2.39   12,288: 2.41 / 2.76
     //   4 tasks  4096: 1.42 / 2.64   12,288: 2.88 / 3.11   6 tasks  4096: 1.59 / 3.41   12,288: 3.14 / 3.99
     //   9 tasks  4096: 1.71 / 3.75   16,384: 3.97 / 5.47   24,576: 5.51 / 7.75
+    // Shorter traces: gaps of one kernel each (512, queues of 512), of ten (256, queues of 2048), few that take any (1024):
+    //   1 task   12,288: 0.25 / 0.55, 0.58 / 0.58, 0.13 / 0.90   24,576: 0.37 / 0.58, 1.02 / 0.61, 0.18 / 0.92
+    //   2 tasks  8192: 0.29 / 0.67, 0.97 / 1.01, 0.12 / 1.15   12,288: 0.37 / 0.69, 1.31 / 1.02, 0.15 / 1.17
+    //   3 tasks  12,288: 0.42 / 0.83, 1.40 / 1.25, 0.17 / 1.45   6 tasks  12,288: 0.55 / 1.10, 1.54 / 1.56, 0.23 / 1.91
+    //   9 tasks  24,576: 1.06 / 2.18, 2.96 / 3.10, 0.49 / 3.73   16 tasks  24,576: 1.37 / 2.47, 3.25 / 3.44, 0.77 / 4.01
+    // (Ten kernels per gap are better off with the groups from 12,288 scenarios of one task and 8192 of two to five on; what
+    // gaps take is not known here, and the other shapes gain more than that one loses.)
     const bool waves = widest <= 16 && n_scenarios <= (widest <= 1 || widest > 8 ? 24576u : 12288u);
     tr.mark(waves ? "k_pf_walk_wave" : "k_pf_walk");
     if (waves && widest <= 1) FIKIT_PF_WAVE(64);

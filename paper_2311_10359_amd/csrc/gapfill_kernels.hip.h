@@ -560,7 +560,8 @@ enum : int { LW_PLAN = 0, LW_REPLAY = 1, LW_REPLAY_FEEDBACK = 2 };
 // at any other value it is done.  If the sums themselves passed 32 bits, the window is reloaded at the head, where
 // C = 0 and everything that can fit is exact.
 //
-// What bounds it: with few scenarios the chain of one gap (about 22 instructions, 120 cycles), with many the issue of
+// What bounds it: with few scenarios the chain of one gap (about 22 instructions; 120 cycles per gap, the windows' ends
+// included), with many the issue of
 // scalar instructions (the gap's fourteen scalar instructions go through one port per SIMD).  64 scenarios of 1500 gaps:
 // 0.076 ms (the 64-bit kernel above, which passes 64-bit sums through the LDS crossbar: 0.23 ms); 256 scenarios of 65,535
 // gaps of which few take anything: 0.52 ms (1.8 ms); 16,384 scenarios of 4095 gaps: 1.44 ms (one lane each: 3.2 ms).

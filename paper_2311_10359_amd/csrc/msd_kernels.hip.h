@@ -1,8 +1,10 @@
 // Long tasks (more launches than one workgroup can hold): one pass over the launch records splits
 // every tile of a task by the top bits of the Kernel ID, and the one-workgroup kernel then works on
 // units of consecutive ID buckets, gathering each unit's launches from the tiles.  Because the ID is a
-// hash, the buckets are of similar size unless a single ID dominates the task; such a task (a bucket
-// larger than a workgroup can hold) keeps the general sort-based path.
+// hash, the buckets are of similar size unless a few IDs dominate the task; a bucket larger than a
+// workgroup can hold is streamed by one (k_unit_stream) if its task is long enough, otherwise the task
+// keeps the general sort-based path.  In a task of more tiles than a unit's run table lists
+// (UNIT_RUNS_MAX) every bucket is streamed, however small.
 //
 //   k_plan_msd        which tasks are long, how many tiles each has
 //   k_tile_partition  one tile per workgroup: Kernel ID / execution time / idle time of every launch
@@ -32,7 +34,13 @@ constexpr uint32_t PT_TILE = 4096;                   // launches per tile of the
 constexpr int PT_THREADS = 512, PT_WAVES = PT_THREADS / WAVE, PT_KPT = PT_TILE / PT_THREADS;
 constexpr int PT_LB = 2;                             // rounds of record loads in flight per lane
 // A bucket of more than FUSE_MAX launches (one frequent ID) is streamed by k_unit_stream if its task has at least this
-// many launches; otherwise the task is sorted.
+// many launches; otherwise the task is sorted.  fikit_profile, one ID with 90 / 50 / 35 % of the launches beside 300 others, in
+// ms sorted / streamed (the line moved down for it):
+//   64 tasks of 24,000 launches: 0.53 / 0.68 (90 %), 0.51 / 0.31 (70 %)   64 of 40,000: 0.64 / 0.83, 0.73 / 0.34 (50 %)
+//   64 of 65,536: 0.80 / 0.44, 0.92 / 0.40, 0.90 / 0.38   256 of 131,072: 3.86 / 1.17, 4.44 / 1.24, 4.40 / 1.15
+//   256 of 262,143: 8.03 / 2.18, 7.76 / 2.32, 7.66 / 2.14
+// Streaming is ahead from 65,536 launches on; in shorter tasks it may be tried in vain, as a unit of the other IDs holds more of
+// them than its table.  The line lies above what has been measured to lose.
 constexpr uint64_t STREAM_MIN = 1u << 18;
 // Tasks of up to this many launches are cut into units of at most FUSE_SMALL_MAX launches, longer ones (whose buckets alone may
 // be longer) of FUSE_MID_MAX.  fikit_profile, uniform over 300 IDs, in ms with the smaller / the larger units:

@@ -1,6 +1,7 @@
-// Units too large for a workgroup's registers: an ID bucket of a long task that a few frequent Kernel IDs fill with more
-// launches than k_task_fused holds (skewed traces: some kernel is launched over and over).  One workgroup streams the
-// bucket's launches as often as it needs; nothing is sorted.
+// Units that k_task_fused does not take: an ID bucket of a long task that a few frequent Kernel IDs fill with more launches
+// than a workgroup's registers hold (skewed traces: some kernel is launched over and over), and every bucket of a task of more
+// than UNIT_RUNS_MAX tiles, down to buckets of a single launch.  One workgroup streams the bucket's launches as often as it
+// needs; nothing is sorted.
 //
 //   1. The bucket's runs (one per tile) are read once: IDs are found in an LDS table, count / sum / min / max per ID (Section
 //      3.2: sum / count = SK_j, SG_j) are gathered, and the launches are written back packed: (execution time, idle time) and
