@@ -130,8 +130,8 @@ __device__ __forceinline__ bool predict_one(uint64_t id, bool in_lds, const Pred
     uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (PRED_HT - 1);
     for (int probe = 0; probe < PRED_HT; ++probe) {
       const uint64_t k = tb.key[h];
+      if (k == ~0ull) return false;   // (first: the ID looked for may be that value, and no row's is)
       if (k == id) { e = tb.e[h]; g = tb.g[h]; return true; }
-      if (k == ~0ull) return false;
       h = (h + 1) & (PRED_HT - 1);
     }
     return false;
@@ -434,8 +434,8 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
       uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (PRED_HT - 1);
       for (int probe = 0; probe < PRED_HT; ++probe) {
         const uint64_t k = tb.key[h];
+        if (k == ~0ull) break;   // (first: the ID looked for may be that value, and no row's is)
         if (k == id) return tb.eg[h];
-        if (k == ~0ull) break;
         h = (h + 1) & (PRED_HT - 1);
       }
       unknown = true;

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2311_10359_amd import binding
+from paper_2311_10359_amd import binding, traces
 from parity_util import DEV, check_gapfill, check_profile
 from test_gpu_parity import ragged_trace
 
@@ -56,6 +56,29 @@ def test_rows_of_a_refused_call_are_not_written(n_tasks):
         with pytest.raises(binding.FikitError) as e:
             binding.fikit_profile_merge(want.rows, tro, want.rows, b_off, rows_out=out)
         assert e.value.status == status and bool((out == 0x5a).all())
+
+
+def test_an_id_of_all_ones_without_a_row_is_unknown():
+    """2^64 - 1 marks a free slot of the look-up tables: as a launch's ID it must not be found there."""
+    rec, off = ragged_trace(3, [40, 50, 60], 5)
+    prof, d_off, _ = check_profile(rec, off)
+    hp, lp = np.array([0, 2], dtype=np.uint32), np.array([1, 1], dtype=np.uint32)
+    d_hp, d_lp, d_go = binding.to_device_u32(hp, DEV), binding.to_device_u32(lp, DEV), binding.to_device_u64(traces.gap_offsets(off, hp), DEV)
+    _, d_gap = binding.fikit_measure(binding.to_device_records(rec, DEV), d_off)
+    lists = [binding.to_device_u64(np.array([0, 1, 2], dtype=np.uint64), DEV), d_lp, binding.to_device_u32(np.array([1, 2], dtype=np.uint32), DEV)]
+    wide_lists = [binding.to_device_u64(np.array([0, 1, 71], dtype=np.uint64), DEV), binding.to_device_u32(np.full(71, 1, dtype=np.uint32), DEV),
+                  binding.to_device_u32(np.full(71, 3, dtype=np.uint32), DEV)]
+    for at in (3, 45):                                  # in a trace, in the queue
+        ids = prof.ids.clone()
+        ids[at] = -1
+        args = (ids, d_off, prof.rows, prof.task_row_offsets)
+        for call in (lambda: binding.fikit_gapfill(*args, d_hp, d_lp, d_go, margin_ns=0, min_gap_ns=0),
+                     lambda: binding.fikit_gapfill_replay(*args, d_gap, d_hp, d_lp, d_go, margin_ns=0, min_gap_ns=0, feedback=True),
+                     lambda: binding.fikit_prio_fill(*args, d_hp, *lists, d_go, margin_ns=0, min_gap_ns=0),
+                     lambda: binding.fikit_prio_fill(*args, d_hp, *wide_lists, d_go, margin_ns=0, min_gap_ns=0)):
+            with pytest.raises(binding.FikitError) as e:
+                call()
+            assert e.value.status == binding.FIKIT_UNKNOWN_ID
 
 
 def test_calls_of_several_threads():
