@@ -244,6 +244,15 @@ __device__ __forceinline__ uint32_t xcd_item(uint32_t block, uint32_t n) {
   return (block % N_XCD) * per + block / N_XCD;
 }
 
+// Another map, for tasks that are taken in order but whose lengths may repeat with a short period (a trace, its queue, the
+// next trace ...): a die then gets all the long ones, and so does a shader engine inside it, since those take a die's
+// workgroups in turn as well.  Every eight consecutive items are rotated among the dies, by one die more for every 32 eights,
+// so that each die works through each place of a period for a while.  Launch n workgroups.
+__device__ __forceinline__ uint32_t rotated_item(uint32_t block, uint32_t n) {
+  const uint32_t group = block / N_XCD;
+  return group < n / N_XCD ? group * N_XCD + (block + group / 32) % N_XCD : block;
+}
+
 // Largest t in [0, n_tasks) with off[t] <= pos, skipping empty tasks to the one that owns pos
 // (requires pos < off[n_tasks]).
 __device__ __forceinline__ uint32_t task_of(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t pos) {

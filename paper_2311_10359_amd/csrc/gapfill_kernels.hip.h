@@ -153,7 +153,7 @@ k_gf_predict(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off,
   // only bits that earlier kernels set: the decision must be the same for the whole workgroup
   if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
   if (!ctrl->wide) return;
-  const uint32_t t = blockIdx.x;   // (one workgroup per task)
+  const uint32_t t = rotated_item(blockIdx.x, n_tasks);   // (one workgroup per task)
   const uint32_t rl = role[t];
   if (rl == 0) return;
   const uint64_t base = off[t], len = off[t + 1] - base;
@@ -391,6 +391,9 @@ __device__ __forceinline__ uint32_t clamp32(int64_t v) {   // (predictions are n
 // part of its launches: with few tasks one workgroup per task leaves most of the chip idle; see predict_parts):
 //   lp_e[i]  execution time, for tasks used as low-priority queue; lp_total[t] their sum (zero at the start)
 //   hp_eg[i] (execution time, idle time), for tasks used as high-priority trace
+// With the tasks in plain order the lengths' pattern decides: 16,384 tasks of 4096 and 16,384 launches in turn 652 us, the same
+// in two halves 511 us; in rotated order (rotated_item) 496 and 501 us.  One task of 15,000 launches in eight, the others of
+// 500: 599 -> 216 us.
 // For the replay against actual idle times (actual != nullptr) the first word of hp_eg[i] holds the idle
 // time that really followed launch i instead (clamped to WIDE32, which no filled time can reach).
 // pred_done (may be null): tasks whose predictions exist already and are left alone.
@@ -402,7 +405,7 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
   __shared__ PredTable32 tb;
   __shared__ uint64_t wave_tot[PRED_THREADS / WAVE];
   if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
-  const uint32_t t = blockIdx.x;
+  const uint32_t t = rotated_item(blockIdx.x, n_tasks);
   const uint64_t part0 = static_cast<uint64_t>(blockIdx.y) * (2 * PRED_THREADS);   // first launch of this workgroup's part
   const uint32_t rl = role[t];
   if (rl == 0) return;
