@@ -434,11 +434,12 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
   bool unknown = false, wide = false, bad_actual = false;
   auto predict = [&](uint64_t id) -> uint2 {
     if (in_lds) {
+      unknown |= id == ~0ull;   // (no row's ID then, but what a free slot holds)
       uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (PRED_HT - 1);
       for (int probe = 0; probe < PRED_HT; ++probe) {
         const uint64_t k = tb.key[h];
-        if (k == ~0ull) break;   // (first: the ID looked for may be that value, and no row's is)
         if (k == id) return tb.eg[h];
+        if (k == ~0ull) break;
         h = (h + 1) & (PRED_HT - 1);
       }
       unknown = true;
