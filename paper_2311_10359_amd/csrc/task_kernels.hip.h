@@ -561,8 +561,14 @@ k_task_fused(const FusedArgs A) {
 
   // Units take the room for their rows from their task's, not from that of their own launches: a bucket of rarely launched
   // kernels has more rows than its launches would leave room for.  (The answer is waited for where the rows are staged.)
+  // (for an address that is the same in the whole wave the compiler reads the answer of the atomic into a scalar at once, and
+  // the workgroup waits for it at the next barrier: 1 us of a unit's 40)
   uint32_t rows_before = 0;
-  if (UNITS && tid == 0) rows_before = atomicAdd(&A.staged[t], D);
+  if (UNITS && tid == 0) {
+    uint32_t which = t;
+    asm volatile("" : "+v"(which));
+    rows_before = atomicAdd(&A.staged[which], D);
+  }
 
   // digit width of the radix selection: 16-bit counters, two per word, shared by 4 * D (ID, percentile) pairs
   int B = 31 - __builtin_clz(static_cast<uint32_t>(HIST_WORDS * 2) / (4 * D));
