@@ -468,17 +468,6 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     ua.ustart = ustart; ua.ulen = ulen; ua.utask = utask; ua.ubuckets = ubuckets; ua.tile_prefix = mtiles; ua.bound = bound;
     ua.tile_len = PT_TILE; ua.part_id = k1; ua.part_kg = part_kg; ua.mflag = mflag; ua.dcount = udcount;
     ua.staged = dcount; ua.ustage = ustage;   // (a long task's row count is 0 until k_msd_task_rows: the sum of what was staged)
-    // (first, because its largest units take longest; a streamed unit has more than FUSE_MAX launches, or is one of the
-    // MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
-    tr.mark("k_unit_stream");
-    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  static_cast<int>(sizeof(StreamSmem))));
-    const uint64_t stream_most = n / (FUSE_MAX + 1) + n / (static_cast<uint64_t>(UNIT_RUNS_MAX) * PT_TILE) * MSD_SLOTS;
-    if (n >= STREAM_MIN) {
-      ua.list = lists + 3 * n_units; ua.count = &ctrl->n_class[3];
-      hipLaunchKernelGGL(k_unit_stream, dim3(static_cast<uint32_t>(stream_most < n_units ? stream_most : n_units)), dim3(SU_THREADS),
-                         sizeof(StreamSmem), st, ua, static_cast<uint32_t>(n_units), reinterpret_cast<uint2*>(e0), g0);
-    }
     // (how many units of a class there can be: two neighbours of a task are longer than FUSE_SMALL_MAX together, or one
     // of them would have taken the other's first bucket)
     auto at_most = [&](uint64_t most) { return dim3(static_cast<uint32_t>(most < n_units ? most : n_units)); };
@@ -491,6 +480,17 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     tr.mark("k_unit_fused_medium");
     ua.list = lists + 2 * n_units; ua.count = &ctrl->n_class[2]; ua.max_len = FUSE_MAX;
     hipLaunchKernelGGL(medium_u, at_most(n / (FUSE_MID_MAX + 1)), dim3(FUSE_M_THREADS), medium_lds, st, ua);
+    // (last, so that a task that another unit has left to the sort, for holding too many IDs, is not streamed in vain; a streamed
+    // unit has more than FUSE_MAX launches, or is one of the MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
+    tr.mark("k_unit_stream");
+    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  static_cast<int>(sizeof(StreamSmem))));
+    const uint64_t stream_most = n / (FUSE_MAX + 1) + n / (static_cast<uint64_t>(UNIT_RUNS_MAX) * PT_TILE) * MSD_SLOTS;
+    if (n >= STREAM_MIN) {
+      ua.list = lists + 3 * n_units; ua.count = &ctrl->n_class[3];
+      hipLaunchKernelGGL(k_unit_stream, dim3(static_cast<uint32_t>(stream_most < n_units ? stream_most : n_units)), dim3(SU_THREADS),
+                         sizeof(StreamSmem), st, ua, static_cast<uint32_t>(n_units), reinterpret_cast<uint2*>(e0), g0);
+    }
     tr.mark("plan");
     hipLaunchKernelGGL(k_msd_task_rows, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, n_tasks, is_long, mflag, udcount, urow, dcount);
     FIKIT_HIP(hipGetLastError());

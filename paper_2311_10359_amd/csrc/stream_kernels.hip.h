@@ -75,7 +75,7 @@ __device__ __forceinline__ void su_find(const uint32_t* hist, uint32_t bins, uin
   inside = __shfl(in, leader, WAVE);
 }
 
-// Slot of an ID in the table (entered if it is new), or SU_HT if the table is full.
+// Slot of an ID in the table (entered if it is new), or SU_HT if the table holds too many.
 __device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
   uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (SU_HT - 1);
   if (id == HT_EMPTY) return SU_HT;
@@ -84,10 +84,11 @@ __device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
     if (k == id) return h;
     if (k == HT_EMPTY) {
       const uint64_t old = atomicCAS(reinterpret_cast<unsigned long long*>(&sm.ht_key[h]), HT_EMPTY, id);
-      if (old == HT_EMPTY) { atomicAdd(&sm.ndist, 1u); return h; }
+      if (old == HT_EMPTY) return atomicAdd(&sm.ndist, 1u) < SU_DMAX ? h : SU_HT;
       if (old == id) return h;
     }
     h = (h + 1) & (SU_HT - 1);
+    if ((probe & 7) == 7 && __hip_atomic_load(&sm.ndist, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > SU_DMAX) break;
   }
   return SU_HT;
 }
@@ -115,7 +116,11 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
     sm.ht_key[s] = HT_EMPTY; sm.esum[s] = 0; sm.gsum[s] = 0; sm.cnt[s] = 0; sm.gcnt[s] = 0;
     sm.emin[s] = ~0u; sm.emax[s] = 0; sm.gmin[s] = ~0u; sm.gmax[s] = 0;
   }
-  if (tid == 0) { sm.ndist = 0; sm.fallback = 0; sm.filled = 0; }
+  // (the other units have run: a task that one of them has left to the sort needs nothing here)
+  if (tid == 0) {
+    sm.ndist = 0; sm.filled = 0;
+    sm.fallback = __hip_atomic_load(&A.mflag[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0u : 1u;
+  }
   __syncthreads();
 
   // ---- 1. gather the bucket's runs --------------------------------------------------------------------------------
@@ -164,6 +169,7 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
             if (have > most) { most = have; dom_id = cand; }
           }
           if (most > 0) dom_slot = su_slot(sm, dom_id);
+          if (ballot(dom_slot == SU_HT)) dom_slot = SU_HT;   // (the lane that entered one too many knows; the same for the wave)
         }
 #pragma unroll
         for (uint32_t r = 0; r < SU_RUNS; ++r) {

@@ -270,7 +270,7 @@ k_task_fused(const FusedArgs A) {
   uint32_t t;          // owning task
   uint64_t base;       // first launch of the task
   uint64_t len64;
-  uint32_t task_len;   // (the rows' staging slice)
+  uint32_t task_len = 0;   // (units: their rows' staging slice)
   if (UNITS) {
     t = A.utask[unit];
     len64 = A.ulen[unit];
@@ -280,7 +280,6 @@ k_task_fused(const FusedArgs A) {
     t = unit;
     base = A.off[t];
     len64 = A.off[t + 1] - base;
-    task_len = static_cast<uint32_t>(len64);
   }
   if (len64 == 0 || len64 > A.max_len) return;   // (cannot happen for a listed item)
   const uint32_t m = static_cast<uint32_t>(len64);
@@ -392,6 +391,8 @@ k_task_fused(const FusedArgs A) {
               if (old == id) { placed = true; break; }
             }
             h = (h + 1) & (HT - 1);
+            // (a table that already holds too many is not searched to its end: a unit that fails costs what its reads do)
+            if ((probe & 7) == 7 && __hip_atomic_load(&sm.ndist, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > DMAX) break;
           }
         }
         if (!placed) atomicOr(&sm.fallback, 1u);
@@ -692,7 +693,7 @@ k_task_fused(const FusedArgs A) {
   const bool emit = !UNITS && A.pred_role != nullptr;
   uint32_t mean_e = 0, mean_g = 0;
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, task_len, row0 + j);
+    uint64_t* row = staged_row(stage_a, stage_b, base, UNITS ? task_len : m, row0 + j);
     const uint32_t ec = sm.rcnt[j];
     uint32_t gc, emin, emax, gmin, gmax;
     uint64_t esum, gsum;
@@ -935,7 +936,7 @@ k_task_fused(const FusedArgs A) {
         const uint32_t arr = q >= D ? 1u : 0u, j = q - arr * D;
         const uint2 se = sel[q];
         const uint32_t b50 = sel_b50(se.y), b95 = sel_b95(se.y);
-        uint64_t* row = staged_row(stage_a, stage_b, base, task_len, row0 + j);
+        uint64_t* row = staged_row(stage_a, stage_b, base, UNITS ? task_len : m, row0 + j);
         if (b50 == SEL_NO_BIN || !(se.y & SEL_LISTED)) {   // (not listed: bins one value wide where the scale is one to one)
           if (gl == 0) {
             const uint32_t v50 = b50 == SEL_NO_BIN ? 0 : value_of_scale(se.x + b50);
@@ -1061,7 +1062,7 @@ k_task_fused(const FusedArgs A) {
     __syncthreads();
   }
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, task_len, row0 + j);
+    uint64_t* row = staged_row(stage_a, stage_b, base, UNITS ? task_len : m, row0 + j);
     const uint4 pf = sm.pref[j];
     row[6] = pf.x; row[7] = pf.y;
     row[12] = pf.z; row[13] = pf.w;

@@ -44,6 +44,8 @@ def skewed(seed, lens, n_ids, heavy, times):
     ([16385, 5000, LONG + 777, 300], 90, 0.3, "wide", False),    # beside tasks of every other shape
     ([500000, 600, 300001], 4096, 0.2, "lognormal", False),
     ([700001], 60000, 0.4, "lognormal", True),                   # more IDs in a bucket than its table holds
+    ([300000, 900, 290000], 30000, 0.4, "lognormal", True),      # ... in the buckets beside it only
+    ([4100000], 100000, 0.1, "ties", True),                      # ... in it, not in the ones beside it
     ([LONG, LONG], 50, 0.5, "beyond", True),
 ])
 def test_frequent_ids(lens, n_ids, heavy, times, sorts):
