@@ -471,12 +471,14 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     // (how many units of a class there can be: two neighbours of a task are longer than FUSE_SMALL_MAX together, or one
     // of them would have taken the other's first bucket)
     auto at_most = [&](uint64_t most) { return dim3(static_cast<uint32_t>(most < n_units ? most : n_units)); };
-    tr.mark("k_unit_fused_small");
-    ua.list = lists; ua.count = &ctrl->n_class[0]; ua.max_len = FUSE_SMALL_MAX;
-    hipLaunchKernelGGL(small_u, at_most(2 * (n / FUSE_SMALL_MAX) + n_long), dim3(FUSE_S_THREADS), small_lds, st, ua);
+    // (the launch whose units hold most launches per ID of their tables first: a task that holds too many IDs is given up there,
+    // and the other launches' units leave it alone)
     tr.mark("k_unit_fused_mid");
     ua.list = lists + n_units; ua.count = &ctrl->n_class[1]; ua.max_len = FUSE_MID_MAX;
     hipLaunchKernelGGL(mid_u, at_most(n / (FUSE_SMALL_MAX + 1)), dim3(512), mid_lds, st, ua);
+    tr.mark("k_unit_fused_small");
+    ua.list = lists; ua.count = &ctrl->n_class[0]; ua.max_len = FUSE_SMALL_MAX;
+    hipLaunchKernelGGL(small_u, at_most(2 * (n / FUSE_SMALL_MAX) + n_long), dim3(FUSE_S_THREADS), small_lds, st, ua);
     tr.mark("k_unit_fused_medium");
     ua.list = lists + 2 * n_units; ua.count = &ctrl->n_class[2]; ua.max_len = FUSE_MAX;
     hipLaunchKernelGGL(medium_u, at_most(n / (FUSE_MID_MAX + 1)), dim3(FUSE_M_THREADS), medium_lds, st, ua);

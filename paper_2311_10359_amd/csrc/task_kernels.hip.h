@@ -109,6 +109,7 @@ struct FusedSmem {
   uint32_t ndist;
   uint32_t fallback;
   uint32_t first_row;        // units: rows of the task that are staged before this unit's
+  uint32_t given_up;         // units: the task goes to the general path
   struct { uint64_t esum[HE], gsum[HE]; uint32_t emin[HE], emax[HE], gmin[HE], gmax[HE], nogap[HE]; } early;   // by slot
   uint16_t rslot[ESTATS ? DMAX : 1];   // rank -> slot
 };
@@ -323,6 +324,8 @@ k_task_fused(const FusedArgs A) {
     const uint32_t ub = A.ubuckets[unit], d0 = ub & 0xffffu, d1 = ub >> 16;
     const uint32_t tp = A.tile_prefix[t], tiles_t = A.tile_prefix[t + 1] - tp;
     const uint64_t task_start = A.off[t];
+    // (another unit may have given the task up; looked at when the run table stands, so that nothing waits for it)
+    const uint32_t alive = tid == 0 ? __hip_atomic_load(&A.mflag[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1u;
     const uint16_t* b_lo = A.bound + static_cast<uint64_t>(tp) * (256 + 1) + static_cast<uint64_t>(d0) * tiles_t;
     const uint16_t* b_hi = A.bound + static_cast<uint64_t>(tp) * (256 + 1) + static_cast<uint64_t>(d1) * tiles_t;
     uint32_t carry = 0;
@@ -338,8 +341,9 @@ k_task_fused(const FusedArgs A) {
       }
       carry += total;
     }
-    if (tid == 0) run_before[tiles_t] = carry;
+    if (tid == 0) { run_before[tiles_t] = carry; sm.given_up = alive ? 0u : 1u; }
     __syncthreads();
+    if (sm.given_up) return;   // (the same for all threads: nothing else writes the word)
     if (carry != m) {   // (cannot happen: the unit's length is the sum of these runs)
       if (tid == 0) atomicOr(&ctrl->status, ERR_OFFSETS);
       return;
