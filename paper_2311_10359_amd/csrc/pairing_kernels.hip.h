@@ -11,7 +11,9 @@ constexpr int PAIR_THREADS = 256;
 // One workgroup per scenario: checks the scenario, sums the time filled in its gaps (8 B read per gap) and raises the largest
 // filled time seen for its high-priority task.  Bound by HBM once enough bytes are in flight: a lane has up to eight 16-byte
 // reads out at a time.  16,384 scenarios of 2047 gaps: 62 us = 4.3 TB/s (four 8-byte reads at a time: 75 us).  A wave per
-// scenario is no faster (call 99 us against 97 us; 16,384 of 127 gaps 76 us against 77 us).  The atomic returns nothing, so
+// scenario is no faster (call 99 us against 97 us; 16,384 of 127 gaps 76 us against 77 us).  Up to 256 gaps a lane reads one of
+// them: eight guarded reads are then most of the instructions (200,000 scenarios of 3 gaps, call 273 us with them, 227 us without;
+// of 30 gaps 253 and 225 us).  The atomic returns nothing, so
 // nothing waits for it; looking at the word first does wait, at a word that all scenarios of a task share (158 us).
 __global__ void __launch_bounds__(PAIR_THREADS)
 k_pair_sum(const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task, uint64_t n_scen, uint32_t n_tasks,
@@ -33,31 +35,35 @@ k_pair_sum(const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp
   constexpr int READS = 8;
   uint64_t acc[2] = {0, 0};      // (sums wrap like the oracle's additions)
   const uint64_t* f = reinterpret_cast<const uint64_t*>(filled_ns);
-  // pairs from the first gap on that lies on a 16-byte address; the gap before them and the one behind by one lane
-  const uint64_t p0 = g0 < g1 && (reinterpret_cast<uintptr_t>(f + g0) & 15) ? g0 + 1 : g0;
-  const uint64_t pairs = (g1 - p0) / 2;
-  const ulonglong2* v = reinterpret_cast<const ulonglong2*>(f + p0);
-  uint64_t i = tid;
-  for (; i + (READS - 1) * PAIR_THREADS < pairs; i += READS * PAIR_THREADS) {
-    ulonglong2 x[READS];
+  if (g1 - g0 <= PAIR_THREADS) {   // few gaps: one read per lane, and few instructions
+    if (tid < g1 - g0) acc[0] = f[g0 + tid];
+  } else {
+    // pairs from the first gap on that lies on a 16-byte address; the gap before them and the one behind by one lane
+    const uint64_t p0 = (reinterpret_cast<uintptr_t>(f + g0) & 15) ? g0 + 1 : g0;
+    const uint64_t pairs = (g1 - p0) / 2;
+    const ulonglong2* v = reinterpret_cast<const ulonglong2*>(f + p0);
+    uint64_t i = tid;
+    for (; i + (READS - 1) * PAIR_THREADS < pairs; i += READS * PAIR_THREADS) {
+      ulonglong2 x[READS];
 #pragma unroll
-    for (int k = 0; k < READS; ++k) x[k] = v[i + k * PAIR_THREADS];
+      for (int k = 0; k < READS; ++k) x[k] = v[i + k * PAIR_THREADS];
 #pragma unroll
-    for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
-  }
-  {
-    ulonglong2 x[READS];
-#pragma unroll
-    for (int k = 0; k < READS; ++k) {
-      x[k] = make_ulonglong2(0, 0);
-      if (i + k * PAIR_THREADS < pairs) x[k] = v[i + k * PAIR_THREADS];
+      for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
     }
+    {
+      ulonglong2 x[READS];
 #pragma unroll
-    for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
-  }
-  if (tid == 0) {
-    if (p0 > g0) acc[0] += f[g0];
-    if (p0 + 2 * pairs < g1) acc[1] += f[g1 - 1];
+      for (int k = 0; k < READS; ++k) {
+        x[k] = make_ulonglong2(0, 0);
+        if (i + k * PAIR_THREADS < pairs) x[k] = v[i + k * PAIR_THREADS];
+      }
+#pragma unroll
+      for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
+    }
+    if (tid == 0) {
+      if (p0 > g0) acc[0] += f[g0];
+      if (p0 + 2 * pairs < g1) acc[1] += f[g1 - 1];
+    }
   }
   uint64_t total = wave_sum_u64(acc[0] + acc[1]);
   if (lane_id() == 0) part[tid >> 6] = total;

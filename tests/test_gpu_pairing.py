@@ -86,7 +86,7 @@ def test_pairing_argument_errors():
 @pytest.mark.parametrize("shift", [0, 1])
 def test_pairing_sums_at_odd_gaps_and_addresses(shift):
     rng = np.random.default_rng(21 + shift)
-    lens = np.array([0, 1, 2, 3, 511, 512, 513, 4094, 4095, 4096, 4097, 8191, 8193, 20001])
+    lens = np.array([0, 1, 2, 3, 255, 256, 257, 258, 511, 512, 513, 4094, 4095, 4096, 4097, 8191, 8193, 20001])
     go = np.concatenate([[0], np.cumsum(lens)]).astype(np.uint64)
     hp, lp = (rng.integers(0, 5, lens.size).astype(np.uint32) for _ in range(2))
     fn = rng.integers(0, 10**12, int(go[-1]))
