@@ -36,7 +36,7 @@ ALGO_BYTES_PER_RECORD = {
     "k_task_fused_medium": 64 + 8,
     "k_tile_partition": 64 + 8 + 16,
     "k_onesweep_pass": 24 + 24,
-    "k_unit_fused": 16,
+    "k_unit_sorted": 16,
 }
 GAPFILL_KERNELS = ("k_gf_predict32", "k_gf_walk_wave", "k_gf_walk_lanes")
 
@@ -436,16 +436,16 @@ def main():
     n_hp = int(sum(cfg.launches(int(t)) for t in np.unique(hp))) if n_scen else 0
     n_lp = int(sum(cfg.launches(int(t)) for t in np.unique(lp))) if n_scen else 0
     units = {"k_task_fused_small": n_small, "k_task_fused_mid": n_mid, "k_task_fused_medium": n_medium,
-             "k_tile_partition": n_long, "k_unit_fused": n_long,
+             "k_tile_partition": n_long, "k_unit_sorted": n_long,
              # (the launches of the long tasks: right where they all take the general path, as in workload 2, the only
              # workload in which this kernel can lead)
              "k_onesweep_pass": n_long}
     # the three launches over the units of partitioned tasks count as one kernel (the split between
     # them depends on the data)
     kernels = {k: v for k, v in trace.items() if k in ALGO_BYTES_PER_RECORD or k in GAPFILL_KERNELS}
-    unit_parts = [v for k, v in trace.items() if k.startswith("k_unit_fused_")]
+    unit_parts = [v for k, v in trace.items() if k.startswith("k_unit_sorted_")]
     if unit_parts:
-        kernels["k_unit_fused"] = (sum(v[0] for v in unit_parts), max(v[1] for v in unit_parts))
+        kernels["k_unit_sorted"] = (sum(v[0] for v in unit_parts), max(v[1] for v in unit_parts))
     dom = max(kernels, key=lambda k: kernels[k][0])
     dom_ms, dom_cnt = kernels[dom]
     avg_ms = dom_ms / dom_cnt

@@ -58,6 +58,10 @@ __device__ __forceinline__ uint32_t popc_below(uint64_t mask) {
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
+__device__ __forceinline__ uint32_t popc64(uint64_t m) { return static_cast<uint32_t>(__popcll(m)); }
+__host__ __device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__host__ __device__ __forceinline__ uint32_t max_u32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+
 template <typename T>
 __device__ __forceinline__ T shfl(T v, int src) { return __shfl(v, src, WAVE); }
 
@@ -73,6 +77,10 @@ __device__ __forceinline__ uint64_t read_lane_u64(uint64_t v, uint32_t src) {
   const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), static_cast<int>(src)));
   const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v >> 32)), static_cast<int>(src)));
   return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
+__device__ __forceinline__ uint32_t read_lane_u32(uint32_t v, uint32_t src) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(src)));
 }
 
 // A 16-byte load that tells the caches that its data will not be used again.
@@ -117,6 +125,13 @@ __device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, int d) {
 // (no LDS traffic); call it with all 64 lanes active.
 __device__ __forceinline__ uint32_t from_next_lane(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(v), static_cast<int>(v), 0x130, 0xf, 0xf, false));   // wave_shl:1
+}
+
+// Inside a row of 16 lanes values move by data-parallel-primitive swaps (pairs, quads) and mirrors (8, 16 lanes: once all
+// lanes of each half hold the half's result, mirroring exchanges the halves); every lane has a source lane in these patterns.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true));
 }
 
 // Wave-wide reductions over all 64 lanes (result in every lane).

@@ -14,6 +14,7 @@
 #include "stats_kernels.hip.h"
 #include "task_kernels.hip.h"
 #include "msd_kernels.hip.h"
+#include "unit_kernels.hip.h"
 #include "stream_kernels.hip.h"
 #include "prio_kernels.hip.h"
 #include "pairing_kernels.hip.h"
@@ -241,6 +242,17 @@ int read_ctrl(const Ctrl* d_ctrl, Ctrl* h, hipStream_t st) {
   return r.wait();
 }
 
+template <int NT, int KPT, int DMAX, int WPE>
+int launch_units(dim3 grid, const FusedArgs& args, hipStream_t st) {
+  if (grid.x == 0) return FIKIT_OK;
+  constexpr size_t lds = sizeof(UnitSmem<NT, KPT, DMAX>);
+  static_assert(lds <= 160 * 1024, "fits a compute unit's LDS");
+  auto kernel = k_unit_sorted<NT, KPT, DMAX, WPE>;
+  FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+  hipLaunchKernelGGL(kernel, dim3(xcd_grid(grid.x)), dim3(NT), lds, st, args);
+  return FIKIT_OK;
+}
+
 template <int W>
 int launch_prio_walk(hipStream_t st, const uint64_t* off, const uint32_t* hp_task, const uint64_t* lp_off,
                      const uint32_t* lp_task, const uint32_t* lp_prio, uint64_t n_scen, const uint64_t* gap_off,
@@ -398,21 +410,15 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   }
   uint16_t* bound = reinterpret_cast<uint16_t*>(hist);
   uint2* part_kg = reinterpret_cast<uint2*>(k2);
-  auto small = k_task_fused<FUSE_S_THREADS, FUSE_SMALL_MAX / FUSE_S_THREADS, 256, 7168, FUSE_S_LB, false, FUSE_S_WPE>;
-  auto medium = k_task_fused<FUSE_M_THREADS, FUSE_MAX / FUSE_M_THREADS, FUSE_M_DMAX, FUSE_M_HIST, 2, false, 4, FUSE_M_ESTATS>;
-  auto mid = k_task_fused<512, 16, 256, 7168, 2, false, 4>;
-  auto small_u = k_task_fused<FUSE_S_THREADS, FUSE_SMALL_MAX / FUSE_S_THREADS, 256, 7168, 4, true, FUSE_S_WPE>;
-  auto mid_u = k_task_fused<512, 16, 256, 7168, 4, true, 4>;
-  auto medium_u = k_task_fused<FUSE_M_THREADS, FUSE_MAX / FUSE_M_THREADS, FUSE_M_DMAX, FUSE_M_HIST, 2, true, 4, FUSE_M_ESTATS>;
+  auto small = k_task_fused<FUSE_S_THREADS, FUSE_SMALL_MAX / FUSE_S_THREADS, 256, 7168, FUSE_S_LB, FUSE_S_WPE>;
+  auto medium = k_task_fused<FUSE_M_THREADS, FUSE_MAX / FUSE_M_THREADS, FUSE_M_DMAX, FUSE_M_HIST, 2, 4, FUSE_M_ESTATS>;
+  auto mid = k_task_fused<512, 16, 256, 7168, 2, 4>;
   constexpr size_t mid_lds = sizeof(FusedSmem<512, 256, 7168>);
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(mid), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(mid_lds)));
-  FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(mid_u), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(mid_lds)));
   constexpr size_t small_lds = sizeof(FusedSmem<FUSE_S_THREADS, 256, 7168>),
                    medium_lds = sizeof(FusedSmem<FUSE_M_THREADS, FUSE_M_DMAX, FUSE_M_HIST, FUSE_M_ESTATS>);
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(small), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(small_lds)));
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(medium), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(medium_lds)));
-  FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(small_u), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(small_lds)));
-  FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(medium_u), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(medium_lds)));
   FusedArgs fa{};
   fa.rec = d_records; fa.off = d_task_offsets; fa.ids = ids; fa.e0 = e0; fa.g0 = g0; fa.key0 = k1;
   fa.stage_a = e1; fa.stage_b = g1; fa.dcount = dcount; fa.gflag = gflag; fa.ctrl = ctrl;
@@ -473,15 +479,15 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     auto at_most = [&](uint64_t most) { return dim3(static_cast<uint32_t>(most < n_units ? most : n_units)); };
     // (the launch whose units hold most launches per ID of their tables first: a task that holds too many IDs is given up there,
     // and the other launches' units leave it alone)
-    tr.mark("k_unit_fused_mid");
-    ua.list = lists + n_units; ua.count = &ctrl->n_class[1]; ua.max_len = FUSE_MID_MAX;
-    hipLaunchKernelGGL(mid_u, at_most(n / (FUSE_SMALL_MAX + 1)), dim3(512), mid_lds, st, ua);
-    tr.mark("k_unit_fused_small");
-    ua.list = lists; ua.count = &ctrl->n_class[0]; ua.max_len = FUSE_SMALL_MAX;
-    hipLaunchKernelGGL(small_u, at_most(2 * (n / FUSE_SMALL_MAX) + n_long), dim3(FUSE_S_THREADS), small_lds, st, ua);
-    tr.mark("k_unit_fused_medium");
-    ua.list = lists + 2 * n_units; ua.count = &ctrl->n_class[2]; ua.max_len = FUSE_MAX;
-    hipLaunchKernelGGL(medium_u, at_most(n / (FUSE_MID_MAX + 1)), dim3(FUSE_M_THREADS), medium_lds, st, ua);
+    tr.mark("k_unit_sorted_mid");
+    ua.list = lists + n_units; ua.count = &ctrl->n_class[1];
+    if (int rc = launch_units<512, FUSE_MID_MAX / 512, UNIT_DMAX, 4>(at_most(n / (FUSE_SMALL_MAX + 1)), ua, st)) return rc;
+    tr.mark("k_unit_sorted_small");
+    ua.list = lists; ua.count = &ctrl->n_class[0];
+    if (int rc = launch_units<512, FUSE_SMALL_MAX / 512, UNIT_DMAX, 6>(at_most(2 * (n / FUSE_SMALL_MAX) + n_long), ua, st)) return rc;
+    tr.mark("k_unit_sorted_large");
+    ua.list = lists + 2 * n_units; ua.count = &ctrl->n_class[2];
+    if (int rc = launch_units<1024, FUSE_MAX / 1024, UNIT_DMAX_LARGE, 4>(at_most(n / (FUSE_MID_MAX + 1)), ua, st)) return rc;
     // (last, so that a task that another unit has left to the sort, for holding too many IDs, is not streamed in vain; a streamed
     // unit has more than FUSE_MAX launches, or is one of the MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
     tr.mark("k_unit_stream");

@@ -583,16 +583,11 @@ __device__ __forceinline__ uint32_t wave_incl_scan_sat_u32(uint32_t v) {
   return v;
 }
 
-__device__ __forceinline__ uint32_t read_lane_u32(uint32_t v, uint32_t src) {
-  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(src)));
-}
 __device__ int llvm_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 __device__ __forceinline__ uint32_t write_lane_u32(uint32_t v, uint32_t value, uint32_t dst) {   // v with lane dst replaced
   return static_cast<uint32_t>(llvm_writelane(static_cast<int>(value), static_cast<int>(dst), static_cast<int>(v)));
 }
-__device__ __forceinline__ uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
 __device__ __forceinline__ uint32_t sat32(uint64_t v) { return v > WIDE32 ? WIDE32 : static_cast<uint32_t>(v); }
-__device__ __forceinline__ uint32_t popc64(uint64_t m) { return static_cast<uint32_t>(__popcll(m)); }
 
 // (completion_out receives the delay in the replay modes).
 template <int MODE>

@@ -1,5 +1,5 @@
 // Long tasks (more launches than one workgroup can hold): one pass over the launch records splits
-// every tile of a task by the top bits of the Kernel ID, and the one-workgroup kernel then works on
+// every tile of a task by the top bits of the Kernel ID, and one workgroup each then works on
 // units of consecutive ID buckets, gathering each unit's launches from the tiles.  Because the ID is a
 // hash, the buckets are of similar size unless a few IDs dominate the task; a bucket larger than a
 // workgroup can hold is streamed by one (k_unit_stream) if its task is long enough, otherwise the task
@@ -14,7 +14,7 @@
 //                     Nothing depends on another tile: no counters, no waiting, one read of the records.
 //   k_msd_units       bucket sizes of a task (summed over its tiles) -> units of at most FUSE_MID_MAX
 //                     launches (FUSE_SMALL_MAX in shorter tasks; or one larger bucket)
-//   k_task_fused      (task_kernels.hip.h, unit form) reads a unit's launches as one run per tile
+//   k_unit_sorted     (unit_kernels.hip.h) reads a unit's launches as one run per tile and makes its rows
 //   k_msd_task_rows / k_gather_units   row counts and final placement of the units' rows
 //   k_long_general_values   per-launch values of long tasks that had to be left to the general path
 #pragma once

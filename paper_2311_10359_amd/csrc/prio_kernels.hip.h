@@ -62,15 +62,7 @@ struct PrioWalkSmem {   // [entry][column]: a lane's durations in its own column
   uint32_t out_f[PW_OUT_CAP][PW_THREADS / W];
 };
 
-// Largest value among the W adjacent lanes of a group, in all of them.  Inside a row of 16 lanes the
-// values move by data-parallel-primitive swaps (pairs, quads) and mirrors (8, 16 lanes: once all lanes of
-// each half hold the half's result, mirroring exchanges the halves); every lane has a source lane in
-// these patterns.  All 64 lanes must call.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ uint32_t max_u32(uint32_t a, uint32_t b) { return a > b ? a : b; }
+// Largest value among the W adjacent lanes of a group, in all of them.  All 64 lanes must call.
 template <int W>
 __device__ __forceinline__ uint32_t group_max_u32(uint32_t v) {
   if (W >= 2) v = max_u32(v, dpp_move<0xB1>(v));    // quad_perm [1,0,3,2]

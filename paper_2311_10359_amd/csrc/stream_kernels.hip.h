@@ -1,4 +1,4 @@
-// Units that k_task_fused does not take: an ID bucket of a long task that a few frequent Kernel IDs fill with more launches
+// Units that k_unit_sorted does not take: an ID bucket of a long task that a few frequent Kernel IDs fill with more launches
 // than a workgroup's registers hold (skewed traces: some kernel is launched over and over), and every bucket of a task of more
 // than UNIT_RUNS_MAX tiles, down to buckets of a single launch.  One workgroup streams the bucket's launches as often as it
 // needs; nothing is sorted.
@@ -7,7 +7,7 @@
 //      3.2: sum / count = SK_j, SG_j) are gathered, and the launches are written back packed: (execution time, idle time) and
 //      the ID's table slot, 10 bytes each.
 //   2. Nearest-rank p50 / p95 (statistics of the same samples): a histogram per (ID, array) over the ID's own value range, on
-//      the scale of k_task_fused, gives the bin of each wanted rank; the samples of that bin only are counted again by their
+//      the scale of pick_group, gives the bin of each wanted rank; the samples of that bin only are counted again by their
 //      offset in the bin, finer and finer until a bin is one value wide.  Two passes over the packed launches as a rule.
 //
 // What bounds it: a compute unit's share of memory (the largest bucket is one workgroup's), and in the first pass the

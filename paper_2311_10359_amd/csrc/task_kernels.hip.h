@@ -30,6 +30,7 @@
 
 #include "common.hip.h"
 #include "profile_kernels.hip.h"
+#include "select_kernels.hip.h"
 
 namespace fikit {
 
@@ -108,13 +109,9 @@ struct FusedSmem {
   uint32_t maxe, maxg;
   uint32_t ndist;
   uint32_t fallback;
-  uint32_t first_row;        // units: rows of the task that are staged before this unit's
-  uint32_t given_up;         // units: the task goes to the general path
   struct { uint64_t esum[HE], gsum[HE]; uint32_t emin[HE], emax[HE], gmin[HE], gmax[HE], nogap[HE]; } early;   // by slot
   uint16_t rslot[ESTATS ? DMAX : 1];   // rank -> slot
 };
-
-constexpr uint32_t NONE32 = 0xffffffffu;   // "no idle time after this launch" in the 32-bit value registers
 
 // Where row j of a task is staged: the task's slice of stage_a, then its slice of stage_b, which hold stage_room rows.
 __device__ __forceinline__ uint32_t stage_room(uint32_t m) { return 2 * (m >> 4); }
@@ -144,16 +141,6 @@ constexpr int SEL_B50_AT = 7, SEL_B95_AT = 19;
 __device__ __forceinline__ uint32_t sel_shift(uint32_t y) { return y & SEL_SHIFT_MASK; }
 __device__ __forceinline__ uint32_t sel_b50(uint32_t y) { return (y >> SEL_B50_AT) & SEL_BIN_MASK; }
 __device__ __forceinline__ uint32_t sel_b95(uint32_t y) { return (y >> SEL_B95_AT) & SEL_BIN_MASK; }
-
-// The scale on which the fast percentile path lays out its bins: the bit pattern of the value as a float, without
-// its lowest 12 bits, i.e. the exponent and the leading 12 bits of the value.  Conversion rounds to nearest, which is
-// monotone, so ranks found on the scale are ranks of the values; values below 2^SCALE_EXACT_BITS map one to one and
-// come back exactly with value_of_scale.  Durations of one kernel spread over a range in proportion to their size
-// (the workloads draw them lognormal): bins of equal width on this scale then hold similar numbers of samples, where
-// bins of equal width in nanoseconds would crowd most samples into the lowest few.
-constexpr uint32_t SCALE_EXACT_BITS = 12, SCALE_DROP = 12;
-__device__ __forceinline__ uint32_t scale_of(uint32_t v) { return __float_as_uint(__uint2float_rn(v)) >> SCALE_DROP; }
-__device__ __forceinline__ uint32_t value_of_scale(uint32_t t) { return static_cast<uint32_t>(__uint_as_float(t << SCALE_DROP)); }
 
 // log2 of the number of bins the fast percentile path cuts an ID's value range into: about one bin
 // per WINDOW_SAMPLES_PER_BIN samples (the bin that holds a wanted rank is ranked directly afterwards), at least 2,
@@ -186,7 +173,7 @@ struct FusedArgs {
   // whole tasks read from launch records
   const fikit_launch* rec;
   const uint64_t* off;
-  const uint32_t* list;        // work list of this launch: task numbers / unit numbers ...
+  const uint32_t* list;        // work list of this launch: task numbers or unit numbers ...
   const uint32_t* count;       // ... and its length (workgroups beyond it have nothing to do)
   uint32_t max_len;            // capacity of this kernel shape (launches)
   uint64_t* ids;               // receives the IDs in launch order
@@ -257,7 +244,7 @@ __device__ __forceinline__ void unit_to_general(const FusedArgs& A, uint32_t t) 
   atomicAdd(reinterpret_cast<unsigned long long*>(&A.ctrl->n_general), 1ull);
 }
 
-template <int NT, int KPT, int DMAX, int HIST_WORDS, int LB, bool UNITS, int WPE, bool ESTATS = false>
+template <int NT, int KPT, int DMAX, int HIST_WORDS, int LB, int WPE, bool ESTATS = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 k_task_fused(const FusedArgs A) {
   using Smem = FusedSmem<NT, DMAX, HIST_WORDS, ESTATS>;
@@ -267,21 +254,8 @@ k_task_fused(const FusedArgs A) {
   Ctrl* ctrl = A.ctrl;
   if (ctrl->status & ERR_OFFSETS) return;
   if (blockIdx.x >= *A.count) return;
-  const uint32_t unit = A.list[blockIdx.x];
-  uint32_t t;          // owning task
-  uint64_t base;       // first launch of the task
-  uint64_t len64;
-  uint32_t task_len = 0;   // (units: their rows' staging slice)
-  if (UNITS) {
-    t = A.utask[unit];
-    len64 = A.ulen[unit];
-    base = A.off[t];
-    task_len = static_cast<uint32_t>(A.off[t + 1] - base);
-  } else {
-    t = unit;
-    base = A.off[t];
-    len64 = A.off[t + 1] - base;
-  }
+  const uint32_t t = A.list[blockIdx.x];
+  const uint64_t base = A.off[t], len64 = A.off[t + 1] - base;
   if (len64 == 0 || len64 > A.max_len) return;   // (cannot happen for a listed item)
   const uint32_t m = static_cast<uint32_t>(len64);
   const fikit_launch* __restrict__ rec = A.rec;
@@ -312,100 +286,7 @@ k_task_fused(const FusedArgs A) {
   const uint32_t lane = lane_id();
 #pragma unroll
   for (int r = 0; r < KPT; ++r) { ev[r] = 0; gv[r] = NONE32; sl[r] = 0; }
-  if (UNITS) {
-    // The unit's launches lie in one run per tile of its task: between the boundaries of its first bucket and of
-    // the bucket after its last.  Run table in LDS (the space of the identity memo, which units do not use):
-    // where each run starts in the tile-ordered arrays, and how many of the unit's launches precede it.
-    uint32_t* run_at = reinterpret_cast<uint32_t*>(&sm.u);
-    uint32_t* run_before = run_at + UNIT_RUNS_MAX;          // [tiles + 1]
-    uint16_t* run_of = reinterpret_cast<uint16_t*>(run_before + UNIT_RUNS_MAX + 4);   // [m]: the run that holds each launch
-    static_assert(sizeof(sm.u) >= (2 * UNIT_RUNS_MAX + 4) * 4 + 2 * NT * KPT, "run tables of a unit");
-    static_assert(UNIT_RUNS_MAX <= 0x10000, "runs are numbered in 16 bits");
-    const uint32_t ub = A.ubuckets[unit], d0 = ub & 0xffffu, d1 = ub >> 16;
-    const uint32_t tp = A.tile_prefix[t], tiles_t = A.tile_prefix[t + 1] - tp;
-    const uint64_t task_start = A.off[t];
-    // (another unit may have given the task up; looked at when the run table stands, so that nothing waits for it)
-    const uint32_t alive = tid == 0 ? __hip_atomic_load(&A.mflag[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1u;
-    const uint16_t* b_lo = A.bound + static_cast<uint64_t>(tp) * (256 + 1) + static_cast<uint64_t>(d0) * tiles_t;
-    const uint16_t* b_hi = A.bound + static_cast<uint64_t>(tp) * (256 + 1) + static_cast<uint64_t>(d1) * tiles_t;
-    uint32_t carry = 0;
-    for (uint32_t j0 = 0; j0 < tiles_t; j0 += NT) {   // (trip count is the same for every thread)
-      const uint32_t j = j0 + tid;
-      uint32_t lo = 0, c = 0;
-      if (j < tiles_t) { lo = b_lo[j]; c = static_cast<uint32_t>(b_hi[j]) - lo; }
-      uint32_t total;
-      const uint32_t ex = block_excl_scan<NT>(c, sm.aux, total);
-      if (j < tiles_t) {
-        run_at[j] = static_cast<uint32_t>(task_start) + j * A.tile_len + lo;
-        run_before[j] = carry + ex;
-      }
-      carry += total;
-    }
-    if (tid == 0) { run_before[tiles_t] = carry; sm.given_up = alive ? 0u : 1u; }
-    __syncthreads();
-    if (sm.given_up) return;   // (the same for all threads: nothing else writes the word)
-    if (carry != m) {   // (cannot happen: the unit's length is the sum of these runs)
-      if (tid == 0) atomicOr(&ctrl->status, ERR_OFFSETS);
-      return;
-    }
-    // every run writes its number over the launches it holds, so that a launch finds its run with one look
-    for (uint32_t j = tid; j < tiles_t; j += NT) {
-      const uint32_t hi = run_before[j + 1];
-      for (uint32_t i = run_before[j]; i < hi; ++i) run_of[i] = static_cast<uint16_t>(j);
-    }
-    __syncthreads();
-    // all of a thread's launches are located first and then read together, so that their loads are in flight at once
-    uint32_t at[KPT];
-#pragma unroll
-    for (int r = 0; r < KPT; ++r) {
-      const uint32_t i = r * NT + tid;
-      at[r] = 0;
-      if (i < m) {
-        const uint32_t j = run_of[i];
-        at[r] = run_at[j] + (i - run_before[j]);
-      }
-    }
-    uint64_t idq[KPT];
-#pragma unroll
-    for (int r = 0; r < KPT; ++r) {
-      idq[r] = 0;
-      if (r * NT + tid < m) {
-        idq[r] = A.part_id[at[r]];
-        const uint2 kg = A.part_kg[at[r]];
-        ev[r] = kg.x;
-        gv[r] = kg.y;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < KPT; ++r) {
-      const uint32_t i = r * NT + tid;
-      if (i < m) {
-        const uint64_t id = idq[r];
-        my_maxe = ev[r] > my_maxe ? ev[r] : my_maxe;
-        if (gv[r] != NONE32) my_maxg = gv[r] > my_maxg ? gv[r] : my_maxg;
-        uint32_t h = (static_cast<uint32_t>(id >> 32) ^ static_cast<uint32_t>(id)) & (HT - 1);
-        bool placed = false;
-        if (id != HT_EMPTY) {
-          for (int probe = 0; probe < HT; ++probe) {
-            const uint64_t k = __hip_atomic_load(&sm.ht_key[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (k == id) { placed = true; break; }
-            if (k == HT_EMPTY) {
-              const uint64_t old = atomicCAS(reinterpret_cast<unsigned long long*>(&sm.ht_key[h]), HT_EMPTY, id);
-              if (old == HT_EMPTY) { atomicAdd(&sm.ndist, 1u); placed = true; break; }
-              if (old == id) { placed = true; break; }
-            }
-            h = (h + 1) & (HT - 1);
-            // (a table that already holds too many is not searched to its end: a unit that fails costs what its reads do)
-            if ((probe & 7) == 7 && __hip_atomic_load(&sm.ndist, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > DMAX) break;
-          }
-        }
-        if (!placed) atomicOr(&sm.fallback, 1u);
-        if (ESTATS) early_stats(sm, h, ev[r], gv[r]);
-        else atomicAdd(&sm.ht_cnt[h], 1u);
-        sl[r] = h;
-      }
-    }
-  } else {
+  {
   // LB rounds of loads are issued before the first of them is used, to keep more bytes in flight
 #pragma unroll
   for (int r0 = 0; r0 < KPT; r0 += LB) {
@@ -544,11 +425,7 @@ k_task_fused(const FusedArgs A) {
   if (lane_id() == 0) { atomicMax(&sm.maxe, my_maxe); atomicMax(&sm.maxg, my_maxg); }
   __syncthreads();
   const uint32_t D = sm.ndist;
-  if (sm.fallback || D > DMAX || (!UNITS && D > stage_room(m))) {
-    if (UNITS) {
-      if (tid == 0) unit_to_general(A, t);
-      return;
-    }
+  if (sm.fallback || D > DMAX || D > stage_room(m)) {
     // general path: hand over the per-launch values (recomputed at full width)
     // (every thread reads back the IDs it wrote itself)
     for (uint32_t i = tid; i < m; i += NT) {
@@ -562,17 +439,6 @@ k_task_fused(const FusedArgs A) {
     }
     if (tid == 0) { gflag[t] = 1; atomicAdd(reinterpret_cast<unsigned long long*>(&ctrl->n_general), 1ull); }
     return;
-  }
-
-  // Units take the room for their rows from their task's, not from that of their own launches: a bucket of rarely launched
-  // kernels has more rows than its launches would leave room for.  (The answer is waited for where the rows are staged.)
-  // (for an address that is the same in the whole wave the compiler reads the answer of the atomic into a scalar at once, and
-  // the workgroup waits for it at the next barrier: 1 us of a unit's 40)
-  uint32_t rows_before = 0;
-  if (UNITS && tid == 0) {
-    uint32_t which = t;
-    asm volatile("" : "+v"(which));
-    rows_before = atomicAdd(&A.staged[which], D);
   }
 
   // digit width of the radix selection: 16-bit counters, two per word, shared by 4 * D (ID, percentile) pairs
@@ -686,18 +552,12 @@ k_task_fused(const FusedArgs A) {
       }
     }
   }
-  if (UNITS && tid == 0) { sm.first_row = rows_before; A.ustage[unit] = rows_before; }
   __syncthreads();
-  const uint32_t row0 = UNITS ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(sm.first_row))) : 0u;
-  if (UNITS && row0 + D > stage_room(task_len)) {
-    if (tid == 0) unit_to_general(A, t);
-    return;
-  }
   // (predictions: a thread stages at most one row, DMAX <= NT, and keeps that ID's means for after the barrier)
-  const bool emit = !UNITS && A.pred_role != nullptr;
+  const bool emit = A.pred_role != nullptr;
   uint32_t mean_e = 0, mean_g = 0;
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, UNITS ? task_len : m, row0 + j);
+    uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
     const uint32_t ec = sm.rcnt[j];
     uint32_t gc, emin, emax, gmin, gmax;
     uint64_t esum, gsum;
@@ -940,7 +800,7 @@ k_task_fused(const FusedArgs A) {
         const uint32_t arr = q >= D ? 1u : 0u, j = q - arr * D;
         const uint2 se = sel[q];
         const uint32_t b50 = sel_b50(se.y), b95 = sel_b95(se.y);
-        uint64_t* row = staged_row(stage_a, stage_b, base, UNITS ? task_len : m, row0 + j);
+        uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
         if (b50 == SEL_NO_BIN || !(se.y & SEL_LISTED)) {   // (not listed: bins one value wide where the scale is one to one)
           if (gl == 0) {
             const uint32_t v50 = b50 == SEL_NO_BIN ? 0 : value_of_scale(se.x + b50);
@@ -969,7 +829,7 @@ k_task_fused(const FusedArgs A) {
         }
       }
       if (emit) emit_predictions();
-      if (tid == 0) dcount[unit] = D;
+      if (tid == 0) dcount[t] = D;
       return;
     }
   }
@@ -1066,14 +926,14 @@ k_task_fused(const FusedArgs A) {
     __syncthreads();
   }
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, UNITS ? task_len : m, row0 + j);
+    uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
     const uint4 pf = sm.pref[j];
     row[6] = pf.x; row[7] = pf.y;
     row[12] = pf.z; row[13] = pf.w;
     if (emit_p50) { pred_e[j] = pf.x; pred_g[j] = pf.z; }
   }
   if (emit) emit_predictions();
-  if (tid == 0) dcount[unit] = D;
+  if (tid == 0) dcount[t] = D;
 }
 
 // May rows be written?  Not for a call that has failed, with more rows than there is room for, or with tasks that are left to

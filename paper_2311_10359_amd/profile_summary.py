@@ -83,12 +83,13 @@ def per_dispatch(path: str):
 
 
 def kernel_label(name: str) -> str:
-    """The name bench.py's per-kernel timing uses for a kernel (template instances of the task kernel by shape)."""
+    """The name bench.py's per-kernel timing uses for a kernel (template instances of the task and unit kernels by shape)."""
     n = name.replace("fikit::", "")
-    if n.startswith("k_task_fused<"):
-        a = [x.strip() for x in n[len("k_task_fused<"):].rstrip(">").split(",")]
-        shape = {("512", "8"): "small", ("512", "16"): "mid", ("1024", "16"): "medium"}.get((a[0], a[1]), "x".join(a[:2]))
-        return ("k_unit_fused_" if a[5] == "true" else "k_task_fused_") + shape
+    for kernel, largest in (("k_task_fused", "medium"), ("k_unit_sorted", "large")):
+        if n.startswith(kernel + "<"):
+            a = [x.strip() for x in n[len(kernel) + 1:].rstrip(">").split(",")]
+            shape = {("512", "8"): "small", ("512", "16"): "mid", ("1024", "16"): largest}.get((a[0], a[1]), "x".join(a[:2]))
+            return kernel + "_" + shape
     return n.split("<")[0]
 
 
