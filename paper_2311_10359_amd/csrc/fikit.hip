@@ -1263,12 +1263,12 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
   if (n_tasks == 0) return FIKIT_OK;
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  uint64_t n_gaps = 0;
-  if (n_scenarios > 0) {
+  if (n_scenarios > 0 && !d_filled_ns) {   // (allowed if there are no gaps, which only the device knows)
+    uint64_t n_gaps = 0;
     Reads r(st);
     if (int rc = r.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
     if (int rc = r.wait()) return rc;
-    if (n_gaps >= MAX_ELEMS || (n_gaps > 0 && !d_filled_ns)) return FIKIT_INVALID_ARG;
+    if (n_gaps > 0) return FIKIT_INVALID_ARG;
   }
   unsigned char* ws = static_cast<unsigned char*>(d_workspace);
   Carver c;
@@ -1279,11 +1279,12 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
 
   Tracer tr(st);
   tr.mark("pair_setup");
-  hipLaunchKernelGGL(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks, top_filled, soonest, best_scenario, ctrl);
+  hipLaunchKernelGGL(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks,
+                     n_scenarios > 0 ? d_gap_offsets + n_scenarios : static_cast<const uint64_t*>(nullptr), top_filled, soonest, best_scenario, ctrl);
   if (n_scenarios > 0) {
     tr.mark("k_pair_sum");
     hipLaunchKernelGGL(k_pair_sum, dim3(static_cast<uint32_t>(n_scenarios)), dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task,
-                       n_scenarios, n_tasks, d_gap_offsets, n_gaps, d_filled_ns, d_scenario_filled_ns, top_filled, ctrl);
+                       n_scenarios, n_tasks, d_gap_offsets, d_filled_ns, d_scenario_filled_ns, top_filled, ctrl);
     tr.mark("k_pair_pick");
     hipLaunchKernelGGL(k_pair_soonest, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_hp_task, n_scenarios,
                        d_scenario_filled_ns, d_lp_completion_ns, top_filled, soonest, ctrl);

@@ -98,3 +98,16 @@ def test_pairing_sums_at_odd_gaps_and_addresses(shift):
     exp = oracle.pairing_best(hp, lp, 5, go, fn, comp)
     assert np.array_equal(got.scenario_filled_ns.cpu().numpy(), exp[0])
     assert np.array_equal(binding.u64_to_numpy(got.best_scenario), exp[1])
+
+
+def test_pairing_refuses_too_many_gaps_before_it_writes():
+    hp, lp = np.array([0, 1], np.uint32), np.array([1, 0], np.uint32)
+    out = binding.Pairing(*(torch.full((n,), 77, dtype=d, device=DEV)
+                            for n, d in ((2, torch.int64), (2, torch.int64), (2, torch.int32), (2, torch.int64))))
+    for last in (2**32 - 2**24, 2**32, 2**63):
+        with pytest.raises(binding.FikitError) as e:
+            binding.fikit_pairing_best(binding.to_device_u32(hp, DEV), binding.to_device_u32(lp, DEV), 2,
+                                       binding.to_device_u64(np.array([0, 2, last], np.uint64), DEV),
+                                       torch.arange(5, device=DEV), torch.tensor([1, 2], device=DEV), out=out)
+        assert e.value.status == binding.FIKIT_INVALID_ARG
+        assert all(bool((x == 77).all()) for x in (out.scenario_filled_ns, out.best_scenario, out.best_lp, out.best_filled_ns))
