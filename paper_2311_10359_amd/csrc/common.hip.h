@@ -44,7 +44,8 @@ struct Ctrl {
   uint32_t n_class[6];    // length of the work lists: small, mid, medium tasks or units, and units that are streamed (huge from
                           // the list's front, others from its back); priority queues: [3] holds the largest number of
                           // low-priority tasks of a scenario
-  uint32_t reserved[2];
+  uint32_t taken;         // large and streamed units: how many have been taken
+  uint32_t reserved;
 };
 static_assert(sizeof(Ctrl) == 80, "control block");
 

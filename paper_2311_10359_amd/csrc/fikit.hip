@@ -486,20 +486,16 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     tr.mark("k_unit_sorted_small");
     ua.list = lists; ua.count = &ctrl->n_class[0];
     if (int rc = launch_units<512, FUSE_SMALL_MAX / 512, UNIT_DMAX, 6>(at_most(2 * (n / FUSE_SMALL_MAX) + n_long), ua, st)) return rc;
-    tr.mark("k_unit_sorted_large");
-    ua.list = lists + 2 * n_units; ua.count = &ctrl->n_class[2];
-    if (int rc = launch_units<1024, FUSE_MAX / 1024, UNIT_DMAX_LARGE, 4>(at_most(n / (FUSE_MID_MAX + 1)), ua, st)) return rc;
-    // (last, so that a task that another unit has left to the sort, for holding too many IDs, is not streamed in vain; a streamed
-    // unit has more than FUSE_MAX launches, or is one of the MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
-    tr.mark("k_unit_stream");
-    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_stream), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  static_cast<int>(sizeof(StreamSmem))));
-    const uint64_t stream_most = n / (FUSE_MAX + 1) + n / (static_cast<uint64_t>(UNIT_RUNS_MAX) * PT_TILE) * MSD_SLOTS;
-    if (n >= STREAM_MIN) {
-      ua.list = lists + 3 * n_units; ua.count = &ctrl->n_class[3];
-      hipLaunchKernelGGL(k_unit_stream, dim3(static_cast<uint32_t>(stream_most < n_units ? stream_most : n_units)), dim3(SU_THREADS),
-                         sizeof(StreamSmem), st, ua, static_cast<uint32_t>(n_units), reinterpret_cast<uint2*>(e0), g0);
-    }
+    // (streamed units last, so that a task that another unit has left to the sort, for holding too many IDs, is not streamed in vain;
+    // a streamed unit has more than FUSE_MAX launches, or is one of the MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
+    tr.mark("k_unit_large");
+    FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_large), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  static_cast<int>(UNIT_LARGE_LDS)));
+    const uint64_t large_most = n / (FUSE_MID_MAX + 1) + n / (static_cast<uint64_t>(UNIT_RUNS_MAX) * PT_TILE) * MSD_SLOTS;
+    ua.list = lists + 2 * n_units;
+    hipLaunchKernelGGL(k_unit_large, dim3(static_cast<uint32_t>(large_most < UNIT_LARGE_WORKGROUPS ? large_most : UNIT_LARGE_WORKGROUPS)),
+                       dim3(SU_THREADS), UNIT_LARGE_LDS, st, ua, lists + 3 * n_units, static_cast<uint32_t>(n_units),
+                       reinterpret_cast<uint2*>(e0), g0);
     tr.mark("plan");
     hipLaunchKernelGGL(k_msd_task_rows, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, n_tasks, is_long, mflag, udcount, urow, dcount);
     FIKIT_HIP(hipGetLastError());

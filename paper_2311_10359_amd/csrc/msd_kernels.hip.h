@@ -74,6 +74,7 @@ __global__ void k_msd_clear(uint32_t* __restrict__ bucket_size, uint64_t count, 
   const uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < count) bucket_size[i] = 0;
   if (i < 6) ctrl->n_class[i] = 0;
+  if (i == 6) ctrl->taken = 0;
 }
 
 struct PartSmem {

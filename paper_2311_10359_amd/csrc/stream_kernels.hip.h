@@ -7,16 +7,22 @@
 //      3.2: sum / count = SK_j, SG_j) are gathered, and the launches are written back packed: (execution time, idle time) and
 //      the ID's table slot, 10 bytes each.
 //   2. Nearest-rank p50 / p95 (statistics of the same samples): a histogram per (ID, array) over the ID's own value range, on
-//      the scale of pick_group, gives the bin of each wanted rank; the samples of that bin only are counted again by their
-//      offset in the bin, finer and finer until a bin is one value wide.  Two passes over the packed launches as a rule.
+//      the scale of pick_group and with as many bins as the ID has samples, gives the bin of each wanted rank.  The samples of
+//      that bin only are then listed and ranked if they are few, else counted by their offset in the bin, again if a bin of that
+//      is still more than one value wide.  Two passes over the packed launches as a rule.
 //
 // What bounds it: a compute unit's share of memory (the largest bucket is one workgroup's), and in the first pass the
 // same-address LDS atomics that one frequent ID causes: every wave therefore keeps the sums of the ID it meets most in
-// registers.
+// registers.  A bucket of 227,000 launches of which one ID has nearly all takes 250 us in step 1 and 150 us in each pass of step 2.
+// (The launches of other IDs taken from all of a wave's runs together, or once there are 64 of them: no change.)  With bins shared
+// out evenly and no lists three or four passes were needed: the streamed units of 64 tasks of 1,048,576 launches, Zipf over 4096
+// IDs, 975 us, now 690; 16 tasks of 1,000,000 with equal execution times (nothing to search then) 2020 -> 1152 us for the call.
 #pragma once
 
 #include "common.hip.h"
+#include "select_kernels.hip.h"
 #include "task_kernels.hip.h"
+#include "unit_kernels.hip.h"
 
 namespace fikit {
 
@@ -30,10 +36,15 @@ constexpr uint32_t SU_BITS_MAX = 11;
 struct StreamSmem {
   uint64_t ht_key[SU_HT], esum[SU_HT], gsum[SU_HT];
   uint32_t cnt[SU_HT], gcnt[SU_HT], emin[SU_HT], emax[SU_HT], gmin[SU_HT], gmax[SU_HT];
-  uint4 sel[2][SU_HT];          // by array and slot: low end of the ID's window (on the scale), shift | rank << 8, the bins of p50 and p95
+  uint4 sel[2][SU_HT];          // by array and slot: low end of the ID's window (a value or on the scale), how it is cut and the rank (su_bin), the bins of p50 and p95
+  uint16_t room[2][SU_HT];      // by array and slot: first word of its histogram
   uint32_t base[4][SU_DMAX];    // by 2 * array + percentile and rank: where the bin searched next begins (a value) ...
   uint32_t rest[4][SU_DMAX];    // ... the wanted rank among the samples from there on ...
-  uint8_t fine[4][SU_DMAX];     // ... and the shift that cuts it into bins
+  uint32_t width[4][SU_DMAX];   // ... how many values further it ends ...
+  uint32_t has[4][SU_DMAX];     // ... its samples ...
+  uint8_t fine[4][SU_DMAX];     // ... the shift that cuts it into bins, or SU_LISTED ...
+  uint16_t part[4][SU_DMAX];    // ... first word of those bins or of the list (its length is the word before it) ...
+  uint8_t log2n[4][SU_DMAX];    // ... and log2 of the bins
   uint16_t slot_of[SU_DMAX];    // rank -> slot
   uint32_t aux[SU_WAVES];
   uint32_t ndist, fallback, filled, again, first_row;
@@ -43,17 +54,31 @@ struct StreamSmem {
   } u;
 };
 static_assert(sizeof(StreamSmem) <= 160 * 1024, "fits a compute unit's LDS");
+using LargeSmem = UnitSmem<SU_THREADS, FUSE_MAX / SU_THREADS, UNIT_DMAX_LARGE>;
+constexpr size_t UNIT_LARGE_LDS = sizeof(StreamSmem) > sizeof(LargeSmem) ? sizeof(StreamSmem) : sizeof(LargeSmem);
+static_assert(UNIT_LARGE_LDS + 16 <= 160 * 1024, "fits a compute unit's LDS, with the ticket");
 constexpr uint32_t SU_NO_BIN = ~0u;
+constexpr uint32_t SU_LIST = 31, SU_LISTED = 0xffu;      // samples of a bin that are listed and ranked, not counted again
+static_assert(SU_HIST <= 0xffffu && 4 * SU_DMAX * (SU_LIST + 1) > SU_HIST, "places in the histograms fit 16 bits; lists may have to be shorter");
 
-// log2 of the bins each of n histograms may have.
-__device__ __forceinline__ uint32_t su_bins_log2(uint32_t n) {
-  const uint32_t b = 31u - __builtin_clz(SU_HIST / n);
-  return b < SU_BITS_MAX ? b : SU_BITS_MAX;
+__device__ __forceinline__ uint32_t su_log2_above(uint32_t v) { return v > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(v - 1)) : 0u; }   // 2^this >= v
+
+// Shares the histogram space among items, thread i's being 2^want words unless that is more than the space holds: then the
+// largest are cut, all to the same size.  Every thread calls, with SU_NONE for no item; gives the first word and the log2 granted.
+constexpr uint32_t SU_NONE = 32;
+__device__ __forceinline__ uint32_t su_share(uint32_t want, uint32_t* aux, uint32_t& granted) {
+  for (uint32_t most = SU_BITS_MAX;; --most) {
+    granted = want < most ? want : most;
+    uint32_t total;
+    const uint32_t at = block_excl_scan<SU_THREADS>(want == SU_NONE ? 0u : 1u << granted, aux, total);
+    if (total <= SU_HIST || most == 0) return at;   // (at most SU_THREADS items: one word each always fits)
+  }
 }
+static_assert(4 * SU_DMAX <= SU_THREADS && SU_THREADS <= SU_HIST, "a thread per item");
 
-// The bin of hist[0 .. bins) that holds the rank k (0-based; the bins' counts sum to more than k), and the rank inside it.  Called by
-// whole waves with the same arguments; the results are in all lanes.
-__device__ __forceinline__ void su_find(const uint32_t* hist, uint32_t bins, uint32_t k, uint32_t& bin, uint32_t& inside) {
+// The bin of hist[0 .. bins) that holds the rank k (0-based; the bins' counts sum to more than k), the rank inside it and its
+// samples.  Called by whole waves with the same arguments; the results are in all lanes.
+__device__ __forceinline__ void su_find(const uint32_t* hist, uint32_t bins, uint32_t k, uint32_t& bin, uint32_t& inside, uint32_t& count) {
   const uint32_t lane = lane_id();
   const uint32_t per = bins > WAVE ? bins / WAVE : 1u;   // (bins is a power of two)
   uint32_t mine = 0;
@@ -62,17 +87,25 @@ __device__ __forceinline__ void su_find(const uint32_t* hist, uint32_t bins, uin
   const uint32_t incl = wave_incl_scan_u32(mine);
   const uint64_t holds = ballot(k < incl);
   const int leader = holds ? __builtin_ctzll(holds) : WAVE - 1;
-  uint32_t at = 0, in = 0;
+  uint32_t at = 0, in = 0, has = 0;
   if (static_cast<int>(lane) == leader) {
     uint32_t cum = incl - mine;
     for (uint32_t b = 0; b < per; ++b) {
       const uint32_t c = hist[lane * per + b];
-      if (k < cum + c) { at = lane * per + b; in = k - cum; break; }
+      if (k < cum + c) { at = lane * per + b; in = k - cum; has = c; break; }
       cum += c;
     }
   }
   bin = __shfl(at, leader, WAVE);
   inside = __shfl(in, leader, WAVE);
+  count = __shfl(has, leader, WAVE);
+}
+
+__device__ __forceinline__ uint32_t su_scale(uint32_t v) { return pick_scale(__uint2float_rn(v)); }
+// The bin of a value by its ID's window (StreamSmem::sel), whose word y is shift | linear << 7 | rank << 8.
+constexpr uint32_t SU_LINEAR = 0x80u;
+__device__ __forceinline__ uint32_t su_bin(const uint4& window, uint32_t v) {
+  return ((window.y & SU_LINEAR ? v : su_scale(v)) - window.x) >> (window.y & 31u);
 }
 
 // Slot of an ID in the table (entered if it is new), or SU_HT if the table holds too many.
@@ -93,18 +126,10 @@ __device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
   return SU_HT;
 }
 
-// Work list: A.list[0 .. count[0]) from the front (the largest units first), then A.list[list_end - 1 - x] for x < count[1].
 // pack_kg, pack_slot: two 8-byte arrays that only the sort would use.  A unit writes the slices of both that belong to its own
 // launches (ustart, ulen) and nothing else: other tasks may have handed their values over to the sort there already.
-__global__ void __launch_bounds__(SU_THREADS)
-k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_all, int64_t* __restrict__ pack_slot_all) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  StreamSmem& sm = *reinterpret_cast<StreamSmem*>(smem_raw);
-  Ctrl* ctrl = A.ctrl;
-  if (ctrl->status & ERR_OFFSETS) return;
-  const uint32_t front = A.count[0], back = A.count[1];
-  if (blockIdx.x >= front + back) return;
-  const uint32_t unit = blockIdx.x < front ? A.list[blockIdx.x] : A.list[list_end - 1 - (blockIdx.x - front)];
+__device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit, uint2* __restrict__ pack_kg_all,
+                                              int64_t* __restrict__ pack_slot_all, StreamSmem& sm) {
   const uint32_t m = A.ulen[unit], t = A.utask[unit];
   const uint64_t base = A.ustart[unit];
   uint2* __restrict__ pack_kg = pack_kg_all + base;
@@ -245,15 +270,25 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
     }
     __syncthreads();
   }
-  const uint32_t B1 = su_bins_log2(2 * D), B2 = su_bins_log2(4 * D);
-  if (tid < 2 * D) {
-    const uint32_t arr = tid >= D ? 1u : 0u, j = tid - arr * D, s = sm.slot_of[j];
+  {
+    const bool mine = tid < 2 * D;
+    const uint32_t arr = mine && tid >= D ? 1u : 0u, j = mine ? tid - arr * D : 0u, s = sm.slot_of[j];
     const uint32_t n = arr ? sm.gcnt[s] : sm.cnt[s];
-    const uint32_t lo = scale_of(arr ? sm.gmin[s] : sm.emin[s]), range = n ? scale_of(arr ? sm.gmax[s] : sm.emax[s]) - lo : 0u;
-    const uint32_t bits = range ? 32 - __builtin_clz(range) : 0u;
-    sm.sel[arr][s] = make_uint4(lo, (bits > B1 ? bits - B1 : 0u) | (j << 8), SU_NO_BIN, SU_NO_BIN);
+    uint32_t bins_log2;
+    const uint32_t at = su_share(mine ? su_log2_above(n) : SU_NONE, sm.aux, bins_log2);
+    if (mine) {
+      // (equal steps of the value where the range is narrow, as in pick_group)
+      const uint32_t lo = n ? (arr ? sm.gmin[s] : sm.emin[s]) : 0u, by_value = n ? (arr ? sm.gmax[s] : sm.emax[s]) - lo : 0u;
+      const uint32_t by_scale = su_scale(lo + by_value) - su_scale(lo);
+      const bool linear = (by_value >> bins_log2) == 0 || (by_scale >> bins_log2) == 0;
+      sm.sel[arr][s] = make_uint4(linear ? lo : su_scale(lo), cut_shift(linear ? by_value : by_scale, bins_log2) | (linear ? SU_LINEAR : 0u) | (j << 8),
+                                  SU_NO_BIN, SU_NO_BIN);
+      sm.room[arr][s] = static_cast<uint16_t>(at);
+      sm.log2n[arr][j] = static_cast<uint8_t>(bins_log2);
+    }
   }
-  for (uint32_t i = tid; i < ((2 * D) << B1); i += SU_THREADS) sm.u.hist[i] = 0;
+  for (uint32_t i = tid; i < SU_HIST; i += SU_THREADS) sm.u.hist[i] = 0;
+  if (tid == 0) sm.again = 0;
   __syncthreads();
 
   // ---- 2. nearest-rank percentiles -------------------------------------------------------------------------------
@@ -270,10 +305,10 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
     for (uint32_t u = 0; u < SU_KPT; ++u) {
       if (i0 + u * SU_THREADS + tid < m) {
         const uint4 se = sm.sel[0][sl[u]];
-        atomicAdd(&sm.u.hist[((se.y >> 8) << B1) + ((scale_of(kg[u].x) - se.x) >> (se.y & 0xffu))], 1u);
+        atomicAdd(&sm.u.hist[sm.room[0][sl[u]] + su_bin(se, kg[u].x)], 1u);
         if (kg[u].y != NONE32) {
           const uint4 sg = sm.sel[1][sl[u]];
-          atomicAdd(&sm.u.hist[((D + (sg.y >> 8)) << B1) + ((scale_of(kg[u].y) - sg.x) >> (sg.y & 0xffu))], 1u);
+          atomicAdd(&sm.u.hist[sm.room[1][sl[u]] + su_bin(sg, kg[u].y)], 1u);
         }
       }
     }
@@ -287,39 +322,59 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
       continue;
     }
     const uint32_t k = static_cast<uint32_t>(rank_index(ap & 1u ? 95 : 50, n));
-    uint32_t bin, inside;
-    su_find(sm.u.hist + ((arr * D + j) << B1), 1u << B1, k, bin, inside);
+    uint32_t bin, inside, has;
+    su_find(sm.u.hist + sm.room[arr][s], 1u << sm.log2n[arr][j], k, bin, inside, has);
     if (lane == 0) {
       const uint4 sel = sm.sel[arr][s];
-      const uint32_t sh = sel.y & 0xffu, t_lo = sel.x + (bin << sh), t_end = t_lo + (1u << sh);
-      // The values of the bin: the scale's float rounds to nearest, so the lowest of them may lie half a unit in the
-      // last place below the bin's own low end.
-      const uint32_t v_lo = value_of_scale(t_lo), mn = arr ? sm.gmin[s] : sm.emin[s], mx = arr ? sm.gmax[s] : sm.emax[s];
-      uint32_t vb = v_lo - (v_lo >> 23) - (v_lo ? 1u : 0u);
-      vb = vb < mn ? mn : vb;
-      uint32_t vt = t_end < scale_of(~0u) ? value_of_scale(t_end) : ~0u;
-      vt = vt > mx ? mx : vt;
-      const uint32_t width = vt - vb, bits = width ? 32 - __builtin_clz(width) : 0u;
-      sm.base[ap][j] = vb;
+      const uint32_t sh = sel.y & 31u, mn = arr ? sm.gmin[s] : sm.emin[s], mx = arr ? sm.gmax[s] : sm.emax[s], t = sel.x + (bin << sh);
+      // the values of the bin, both ends included
+      const bool linear = (sel.y & SU_LINEAR) != 0;
+      const uint32_t first = linear ? t : max_u32(pick_scale_low(t), mn);
+      const uint32_t last = linear ? (mx - t < 1u << sh ? mx : t + (1u << sh) - 1) : min_u32(pick_scale_low(t + (1u << sh)) - 1, mx);
+      sm.base[ap][j] = first;
       sm.rest[ap][j] = inside;
-      sm.fine[ap][j] = static_cast<uint8_t>(bits > B2 ? bits - B2 : 0u);
-      (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) = bin;
+      sm.width[ap][j] = last - first;
+      sm.has[ap][j] = has;
+      if (last != first) {   // (else found)
+        (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) = bin;
+        atomicOr(&sm.again, 1u);
+      }
     }
   }
   __syncthreads();
-  for (;;) {
-    for (uint32_t i = tid; i < ((4 * D) << B2); i += SU_THREADS) sm.u.hist[i] = 0;
+  while (sm.again) {   // (the same for all threads: changed behind the barriers of su_share and in front of the loop's last)
+    // Room for every bin that is searched: a list if its samples are few, bins one value wide if there are so many words, fewer
+    // and wider ones if not.
+    {
+      const uint32_t ap = tid / SU_DMAX, j = tid % SU_DMAX, arr = ap >> 1, s = j < D ? sm.slot_of[j] : 0u;
+      const bool searched = j < D && (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) != SU_NO_BIN;
+      const uint32_t width = searched ? sm.width[ap][j] : 0u, has = searched ? sm.has[ap][j] : 0u;
+      const bool list = searched && has <= SU_LIST && width != 0;
+      uint32_t granted;
+      const uint32_t at = su_share(!searched ? SU_NONE : list ? su_log2_above(has + 1) : width < 1u << SU_BITS_MAX ? su_log2_above(width + 1) : SU_BITS_MAX,
+                                   sm.aux, granted);
+      if (searched) {
+        sm.part[ap][j] = static_cast<uint16_t>(at);
+        sm.log2n[ap][j] = static_cast<uint8_t>(granted);
+        sm.fine[ap][j] = static_cast<uint8_t>(list && has < 1u << granted ? SU_LISTED : cut_shift(width, granted));
+      }
+    }
+    for (uint32_t i = tid; i < SU_HIST; i += SU_THREADS) sm.u.hist[i] = 0;
     if (tid == 0) sm.again = 0;
     __syncthreads();
-    // a sample of a bin that is searched: counted by its offset from where the search has got to
+    // a sample of a bin that is searched: listed, or counted by its offset from where the search has got to
     auto count = [&](uint32_t arr, uint32_t v, uint32_t slot) {
       const uint4 sel = sm.sel[arr][slot];
-      const uint32_t bin = (scale_of(v) - sel.x) >> (sel.y & 0xffu), j = sel.y >> 8;
+      const uint32_t bin = su_bin(sel, v), j = sel.y >> 8;
 #pragma unroll
       for (uint32_t p = 0; p < 2; ++p) {
         if (bin == (p ? sel.w : sel.z)) {
-          const uint32_t ap = 2 * arr + p, d = (v - sm.base[ap][j]) >> sm.fine[ap][j];
-          if (v >= sm.base[ap][j] && d < (1u << B2)) atomicAdd(&sm.u.hist[((ap * D + j) << B2) + d], 1u);
+          const uint32_t ap = 2 * arr + p, past = v - sm.base[ap][j], sh = sm.fine[ap][j];
+          uint32_t* mine = sm.u.hist + sm.part[ap][j];
+          if (past <= sm.width[ap][j]) {
+            if (sh == SU_LISTED) mine[1 + (atomicAdd(&mine[0], 1u) & SU_LIST)] = v;
+            else atomicAdd(&mine[past >> sh], 1u);
+          }
         }
       }
     };
@@ -345,20 +400,31 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
       const uint32_t ap = q / D, j = q - ap * D, arr = ap >> 1, s = sm.slot_of[j];
       const uint32_t searched = ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z;
       if (searched == SU_NO_BIN) continue;
-      uint32_t bin, inside;
-      su_find(sm.u.hist + ((ap * D + j) << B2), 1u << B2, sm.rest[ap][j], bin, inside);
+      const uint32_t* mine = sm.u.hist + sm.part[ap][j];
+      const uint32_t sh = sm.fine[ap][j];
+      uint32_t bin = 0, inside = 0, has = 0;
+      if (sh == SU_LISTED) {   // a lane per sample counts the smaller ones; the wanted one is the largest with at most `rest` of them
+        const uint32_t n = mine[0], v = lane < n ? mine[1 + lane] : 0u;
+        uint32_t smaller = 0;
+        for (uint32_t i = 0; i < n; ++i) smaller += mine[1 + i] < v ? 1u : 0u;
+        bin = wave_max_u32(lane < n && smaller <= sm.rest[ap][j] ? v : 0u) - sm.base[ap][j];
+      } else {
+        su_find(mine, 1u << sm.log2n[ap][j], sm.rest[ap][j], bin, inside, has);
+        bin <<= sh;
+      }
       if (lane == 0) {
-        const uint32_t sh = sm.fine[ap][j];
-        sm.base[ap][j] += bin << sh;
-        sm.rest[ap][j] = inside;
-        sm.fine[ap][j] = static_cast<uint8_t>(sh > B2 ? sh - B2 : 0u);
-        if (sh == 0) (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) = SU_NO_BIN;   // one value wide: found
-        else atomicOr(&sm.again, 1u);
+        sm.base[ap][j] += bin;
+        if (sh == 0 || sh == SU_LISTED) {   // found
+          (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) = SU_NO_BIN;
+        } else {
+          sm.rest[ap][j] = inside;
+          sm.width[ap][j] = min_u32(sm.width[ap][j] - bin, (1u << sh) - 1);
+          sm.has[ap][j] = has;
+          atomicOr(&sm.again, 1u);
+        }
       }
     }
     __syncthreads();
-    if (!sm.again) break;
-    __syncthreads();   // (again is cleared at the top)
   }
 
   if (tid < D) {
@@ -373,6 +439,34 @@ k_unit_stream(const FusedArgs A, uint32_t list_end, uint2* __restrict__ pack_kg_
     row[14] = 0; row[15] = 0;
   }
   if (tid == 0) A.dcount[unit] = D;
+}
+
+// The streamed units and, beside them, the units of more than FUSE_MID_MAX launches: both need a compute unit's whole LDS, and the
+// longest streamed units leave most of the chip to the others (64 tasks of 1,048,576 launches, Zipf over 4096 IDs: 915 us
+// in a launch each, 726 us together; workgroups that stay also save the 30 us that 33,000 without a unit take to come and go).
+// Workgroups stay, one per compute unit, and take units in order from a counter: streamed ones from the front of their list (the largest first), then
+// from its back, then the others.
+constexpr uint64_t UNIT_LARGE_WORKGROUPS = 256;
+__global__ void __launch_bounds__(SU_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_unit_large(const FusedArgs A, const uint32_t* __restrict__ streamed, uint32_t streamed_end, uint2* __restrict__ pack_kg_all,
+             int64_t* __restrict__ pack_slot_all) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ uint32_t ticket;
+  if (A.ctrl->status & ERR_OFFSETS) return;
+  const uint32_t large = A.ctrl->n_class[2], front = A.ctrl->n_class[3], back = A.ctrl->n_class[4];
+  for (;;) {
+    if (threadIdx.x == 0) ticket = atomicAdd(&A.ctrl->taken, 1u);
+    __syncthreads();
+    const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(ticket)));
+    if (at >= front + back + large) return;
+    if (at < front + back)
+      unit_streamed(A, at < front ? streamed[at] : streamed[streamed_end - 1 - (at - front)], pack_kg_all, pack_slot_all,
+                    *reinterpret_cast<StreamSmem*>(smem_raw));
+    else
+      unit_sorted<SU_THREADS, FUSE_MAX / SU_THREADS, UNIT_DMAX_LARGE>(A, A.list[at - (front + back)],
+                                                                      *reinterpret_cast<LargeSmem*>(smem_raw));
+    __syncthreads();   // (the next unit's tables take the place of this one's)
+  }
 }
 
 }  // namespace fikit

@@ -50,25 +50,15 @@ struct UnitSmem {
   uint32_t ndist, fallback, first_row, given_up, n_shared, shared_launches, more;
 };
 
-template <int NT, int KPT, int DMAX, int WPE>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
-k_unit_sorted(const FusedArgs A) {
+template <int NT, int KPT, int DMAX>
+__device__ __forceinline__ void unit_sorted(const FusedArgs& A, uint32_t unit, UnitSmem<NT, KPT, DMAX>& sm) {
   using Smem = UnitSmem<NT, KPT, DMAX>;
   constexpr uint32_t HT = Smem::HT, CAP = Smem::CAP, NW = Smem::NW;
   constexpr int PLACE_AT = 10;   // a launch's slot and place in one word
   static_assert(HT <= 1u << PLACE_AT && CAP <= PICK_SAMPLES && CAP <= 1u << (32 - PLACE_AT), "slot and place of a launch");
   static_assert(UNIT_RUNS_MAX <= 0x10000, "runs are numbered in 16 bits");
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  Smem& sm = *reinterpret_cast<Smem*>(smem_raw);
   Ctrl* ctrl = A.ctrl;
-  if (ctrl->status & ERR_OFFSETS) return;
-  // (neighbours in the list, whose runs lie next to each other in every tile, run on the same die and share its L2: with lists of
-  // the percentile step made cheaper as well, 2184 -> 1891 us for the units of 8192 launches of 256 tasks of 1,048,576)
-  const uint32_t units = *A.count;
-  if (blockIdx.x >= xcd_grid(units)) return;
-  const uint32_t item = xcd_item(blockIdx.x, units);
-  if (item >= units) return;
-  const uint32_t unit = A.list[item], t = A.utask[unit], m = A.ulen[unit];
+  const uint32_t t = A.utask[unit], m = A.ulen[unit];
   if (m == 0 || m > CAP) return;   // (cannot happen for a listed unit)
   const uint64_t base = A.off[t];
   const uint32_t task_len = static_cast<uint32_t>(A.off[t + 1] - base);
@@ -331,6 +321,20 @@ k_unit_sorted(const FusedArgs A) {
   if (m - sm.shared_launches >= (D - n_shared) * 128) rows(std::integral_constant<uint32_t, 32>{});
   else rows(std::integral_constant<uint32_t, 16>{});
   if (tid == 0) A.dcount[unit] = D;
+}
+
+template <int NT, int KPT, int DMAX, int WPE>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
+k_unit_sorted(const FusedArgs A) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  if (A.ctrl->status & ERR_OFFSETS) return;
+  // (neighbours in the list, whose runs lie next to each other in every tile, run on the same die and share its L2: with lists of
+  // the percentile step made cheaper as well, 2184 -> 1891 us for the units of 8192 launches of 256 tasks of 1,048,576)
+  const uint32_t units = *A.count;
+  if (blockIdx.x >= xcd_grid(units)) return;
+  const uint32_t item = xcd_item(blockIdx.x, units);
+  if (item >= units) return;
+  unit_sorted(A, A.list[item], *reinterpret_cast<UnitSmem<NT, KPT, DMAX>*>(smem_raw));
 }
 
 }  // namespace fikit

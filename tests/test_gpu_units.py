@@ -53,5 +53,5 @@ def test_ids_at_the_edges_of_groups_waves_and_shares(kind):
     off = np.concatenate([[0], np.cumsum([r.size for r in recs])]).astype(np.uint64)
     with kernels_of() as names:
         check_profile(np.concatenate(recs), off)
-    assert {"k_unit_sorted_small", "k_unit_sorted_mid", "k_unit_sorted_large"} <= names, sorted(names)
+    assert {"k_unit_sorted_small", "k_unit_sorted_mid", "k_unit_large"} <= names, sorted(names)
     assert "k_onesweep_pass" not in names, sorted(names)
