@@ -280,4 +280,13 @@ __device__ __forceinline__ uint32_t task_of(const uint64_t* __restrict__ off, ui
   return lo;
 }
 
+// May rows be written?  Not for a call that has failed, with more rows than there is room for, or with tasks that are left to
+// the general path (general_done: how many of those have been counted): the host enqueues the gathers before it knows.
+__device__ __forceinline__ bool rows_final(const Ctrl* ctrl, uint64_t capacity, uint64_t general_done) {
+  return !ctrl->status && ctrl->n_general == general_done && ctrl->n_rows <= capacity;
+}
+
+// May a gap fill that was enqueued behind a profile in the same call run (prof null: there is none)?
+__device__ __forceinline__ bool may_follow(const Ctrl* prof, uint64_t capacity) { return !prof || rows_final(prof, capacity, 0); }
+
 }  // namespace fikit

@@ -322,12 +322,16 @@ struct PredEmit {
   uint32_t predictor;
 };
 
-// fikit_profile; with `emit` the kernels that hold a whole task in one workgroup also write the task's predictions (*all_emitted:
-// that was every task that has launches).
+// fikit_profile; with `emit` the kernels that hold a whole task in one workgroup also write the task's predictions.  `begin` (may be
+// null): the first checks of a gap fill that follows, which share a launch with the profile's if both are few.  ahead(tracer,
+// reads, ctrl, any long tasks) enqueues what follows once the rows are final, and what it wants read back, before the host knows
+// whether they are: *was_ahead says that they were (see may_follow).
+template <typename Ahead>
 int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_t* d_task_offsets,
                 uint32_t n_tasks, uint64_t* d_ids_out, fikit_row* d_rows_out, uint64_t row_capacity,
                 uint64_t* d_task_row_offsets, uint64_t* h_n_rows, void* d_workspace, size_t workspace_bytes,
-                void* hip_stream, const PredEmit* emit, bool* all_emitted) {
+                void* hip_stream, const PredEmit* emit, const GfBegin* begin, Ahead ahead, bool* was_ahead) {
+  *was_ahead = false;
   if (!h_n_rows) return FIKIT_INVALID_ARG;
   *h_n_rows = 0;
   if (!d_task_offsets || !d_task_row_offsets || !d_workspace) return FIKIT_INVALID_ARG;
@@ -391,8 +395,11 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   uint32_t* wflag = reinterpret_cast<uint32_t*>(ws + L.wflag);
   const bool few_tasks = n_tasks <= BEGIN_TASKS;
   if (few_tasks) {
-    hipLaunchKernelGGL(k_profile_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n, FUSE_SMALL_MAX, FUSE_MID_MAX,
-                       FUSE_MAX, PT_TILE, gflag, dcount, lists, is_long, mtiles, wflag, ctrl);
+    const ProfileBegin pb{n, FUSE_SMALL_MAX, FUSE_MID_MAX, FUSE_MAX, PT_TILE, gflag, dcount, lists, is_long, mtiles, wflag, ctrl};
+    if (begin)
+      hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, pb, *begin);
+    else
+      hipLaunchKernelGGL(k_profile_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, pb);
   } else {
     hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
     hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
@@ -512,17 +519,30 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
                          utask, udcount, urow, ustage, mflag, d_task_row_offsets, e1, g1, static_cast<uint32_t>(n_units), d_rows_out, row_capacity,
                          general_done, ctrl);
   };
-  tr.mark("row_offsets");
-  if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets, ctrl, st)) return rc;
-  gather_rows(0);
+  const bool any_long = n_units > 0;
+  if (!any_long && n_tasks <= ROWS_ONE_TASKS) {
+    tr.mark("k_gather_rows");
+    hipLaunchKernelGGL(k_rows_one, dim3(n_tasks), dim3(256), 0, st, d_task_offsets, dcount, e1, g1, n_tasks, d_task_row_offsets, d_rows_out,
+                       row_capacity, ctrl);
+  } else {
+    tr.mark("row_offsets");
+    if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets, ctrl, st)) return rc;
+    gather_rows(0);
+  }
   FIKIT_HIP(hipGetLastError());
-  tr.mark("host_sync");
-  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+  {
+    Reads reads(st);
+    if (int rc = ahead(tr, reads, ctrl, any_long)) return rc;
+    tr.mark("host_sync");
+    if (int rc = reads.add(&h, ctrl, sizeof(Ctrl))) return rc;
+    if (int rc = reads.wait()) return rc;
+  }
   if (int rc = status_from_bits(h.status)) return rc;
-  if (all_emitted) *all_emitted = emit && h.n_general == 0 && h.n_long == 0;
   if (h.n_general == 0) {
     *h_n_rows = h.n_rows;
-    return h.n_rows > row_capacity ? FIKIT_ROW_CAPACITY : FIKIT_OK;
+    if (h.n_rows > row_capacity) return FIKIT_ROW_CAPACITY;
+    *was_ahead = true;
+    return FIKIT_OK;
   }
   const uint64_t n_general = h.n_general;
   if (n_units > 0) {
@@ -658,8 +678,10 @@ int fikit_profile(const fikit_launch* d_records, uint64_t n_records, const uint6
                   uint32_t n_tasks, uint64_t* d_ids_out, fikit_row* d_rows_out, uint64_t row_capacity,
                   uint64_t* d_task_row_offsets, uint64_t* h_n_rows, void* d_workspace, size_t workspace_bytes,
                   void* hip_stream) {
+  bool was_ahead;
   return profile_run(d_records, n_records, d_task_offsets, n_tasks, d_ids_out, d_rows_out, row_capacity, d_task_row_offsets,
-                     h_n_rows, d_workspace, workspace_bytes, hip_stream, nullptr, nullptr);
+                     h_n_rows, d_workspace, workspace_bytes, hip_stream, nullptr, nullptr,
+                     [](Tracer&, Reads&, const Ctrl*, bool) { return FIKIT_OK; }, &was_ahead);
 }
 
 // The per-launch arrays of the gap fill are read in 64-byte pieces that may reach past the last launch.
@@ -726,13 +748,19 @@ uint32_t predict_parts(uint64_t n_ids, uint32_t n_tasks) {
   return static_cast<uint32_t>(parts > 64 ? 64 : parts);
 }
 
+bool gapfill_checks_are_few(uint32_t n_tasks, uint64_t n_scenarios) { return n_tasks <= GF_BEGIN_ITEMS && n_scenarios <= GF_BEGIN_ITEMS; }
+GfBegin gapfill_begin(const GapfillBuffers& b, const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios,
+                      const uint64_t* d_gap_offsets, uint64_t n_gaps, uint32_t* done) {
+  return GfBegin{d_hp_task, d_lp_task, static_cast<uint32_t>(n_scenarios), d_gap_offsets, n_gaps, b.role, b.lp_total, done, b.ctrl};
+}
+
 // What every gap fill starts with: a cleared control block, checked arguments, task roles.
 void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t* d_task_offsets, uint64_t n_ids, uint32_t n_tasks,
                            const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets,
                            uint64_t n_gaps, uint32_t* done) {
-  if (n_tasks <= GF_BEGIN_ITEMS && n_scenarios <= GF_BEGIN_ITEMS) {
-    hipLaunchKernelGGL(k_gf_begin, dim3(1), dim3(GF_BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n_ids, d_hp_task, d_lp_task,
-                       static_cast<uint32_t>(n_scenarios), d_gap_offsets, n_gaps, b.role, b.lp_total, done, b.ctrl);
+  if (gapfill_checks_are_few(n_tasks, n_scenarios)) {
+    hipLaunchKernelGGL(k_gf_begin, dim3(1), dim3(GF_BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n_ids,
+                       gapfill_begin(b, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, done));
     return;
   }
   hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, done, n_tasks);
@@ -740,12 +768,13 @@ void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64
                      n_tasks, n_ids, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, b.role, b.ctrl);
 }
 
-// The walk on 32-bit predictions in one of its modes; `result`: completion times, or delays in the replay modes.
+// The walk on 32-bit predictions in one of its modes; `result`: completion times, or delays in the replay modes.  prof (may be
+// null): the profile that it follows in the same call.
 template <int MODE>
 int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_task_offsets, const uint32_t* d_hp_task,
                  const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets, uint64_t n_gaps, int64_t margin,
                  int64_t min_gap, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* result, uint64_t* d_lp_placed,
-                 bool set_attributes) {
+                 bool set_attributes, const Ctrl* prof, uint64_t row_capacity) {
   if (n_scenarios >= GF_LANES_MIN_SCENARIOS && n_gaps < MAX_ELEMS) {
     tr.mark(MODE == LW_PLAN ? "k_gf_walk_lanes" : MODE == LW_REPLAY ? "k_gf_replay_lanes" : "k_gf_replay_feedback_lanes");
     if (set_attributes)
@@ -754,12 +783,12 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
     const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
     hipLaunchKernelGGL(k_gf_walk_lanes<MODE>, dim3(blocks_for(n_scenarios, LW_THREADS)), dim3(LW_THREADS), sizeof(LaneWalkSmem), st,
                        d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
-                       d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, b.ctrl);
+                       d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, prof, row_capacity, b.ctrl);
   } else {
     tr.mark(MODE == LW_PLAN ? "k_gf_walk_wave" : MODE == LW_REPLAY ? "k_gf_replay_wave" : "k_gf_replay_feedback_wave");
     hipLaunchKernelGGL(k_gf_walk_wave<MODE>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st, d_task_offsets,
                        d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,
-                       d_filled_ns, result, d_lp_placed, b.ctrl);
+                       d_filled_ns, result, d_lp_placed, prof, row_capacity, b.ctrl);
   }
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
@@ -772,15 +801,16 @@ int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const u
                     const uint64_t* d_task_offsets, uint32_t n_tasks, const fikit_row* d_rows, const uint64_t* d_task_row_offsets,
                     const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
                     const uint64_t* d_gap_offsets, uint64_t n_gaps, uint32_t* d_fill_count, int64_t* d_filled_ns,
-                    int64_t* d_lp_completion_ns, uint64_t* d_lp_placed, bool set_attributes, const uint32_t* done, bool all_done) {
+                    int64_t* d_lp_completion_ns, uint64_t* d_lp_placed, bool set_attributes, const uint32_t* done, bool all_done, const Ctrl* prof = nullptr,
+                    uint64_t row_capacity = 0) {
   tr.mark("k_gf_predict32");
   if (!all_done)
     hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                        n_tasks, d_rows, d_task_row_offsets, b.role, static_cast<const int64_t*>(nullptr), b.lp_e, b.hp_eg, b.lp_total,
-                       static_cast<uint32_t>(h_params->predictor), done, b.ctrl);
+                       static_cast<uint32_t>(h_params->predictor), done, prof, row_capacity, b.ctrl);
   return walk_enqueue<LW_PLAN>(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps,
                                h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
-                               set_attributes);
+                               set_attributes, prof, row_capacity);
 }
 
 // The 64-bit kernels, which do the call if a prediction did not fit 32 bits (they check Ctrl::wide).
@@ -798,12 +828,9 @@ int gapfill_wide_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t
   return FIKIT_OK;
 }
 
-// Ends a gap fill: its status, and the 64-bit kernels first if they are needed.
+// Ends a gap fill whose control block has been read: its status, and the 64-bit kernels first if they are needed.
 template <typename Wide>
-int finish_gapfill(hipStream_t st, Tracer& tr, const Ctrl* ctrl, Wide enqueue_wide) {
-  tr.mark("host_sync");
-  Ctrl h{};
-  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+int finish_gapfill(hipStream_t st, Tracer& tr, const Ctrl* ctrl, Ctrl h, Wide enqueue_wide) {
   if (int rc = status_from_bits(h.status)) return rc;
   if (!h.wide) return FIKIT_OK;
   tr.mark("gf_wide");
@@ -811,6 +838,13 @@ int finish_gapfill(hipStream_t st, Tracer& tr, const Ctrl* ctrl, Wide enqueue_wi
   tr.mark("host_sync");
   if (int rc = read_ctrl(ctrl, &h, st)) return rc;
   return status_from_bits(h.status);
+}
+template <typename Wide>
+int finish_gapfill(hipStream_t st, Tracer& tr, const Ctrl* ctrl, Wide enqueue_wide) {
+  tr.mark("host_sync");
+  Ctrl h{};
+  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+  return finish_gapfill(st, tr, ctrl, h, enqueue_wide);
 }
 
 }  // namespace
@@ -913,22 +947,40 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
   PredEmit emit{};
   emit.role = b.role; emit.lp_e = b.lp_e; emit.hp_eg = b.hp_eg; emit.lp_total = b.lp_total; emit.done = done;
   emit.predictor = static_cast<uint32_t>(h_params->predictor);
-  {
+  const bool few = n_tasks <= BEGIN_TASKS && gapfill_checks_are_few(n_tasks, n_scenarios) && n_records > 0;
+  const GfBegin begin = gapfill_begin(b, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, done);
+  if (!few) {
     Tracer tr(st);
     tr.mark("gf_setup");
     gapfill_check_enqueue(st, b, d_task_offsets, n_records, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, done);
     FIKIT_HIP(hipGetLastError());
   }
-  bool all_emitted = false;
+  auto fill = [&](Tracer& tr, bool all_done, const Ctrl* prof) {
+    return gapfill_enqueue(st, tr, b, d_ids_out, n_records, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task,
+                           d_lp_task, n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns, d_lp_completion_ns,
+                           d_lp_placed, true, done, all_done, prof, row_capacity);
+  };
+  // The fill is enqueued behind the rows and the host waits once (one pair of 1000 launches: 69 us with
+  // two waits and the small kernels apart, 57 us).  Where no
+  // task is long, either all have their predictions from the profile's kernels, or some are left to the general path and the
+  // fill leaves at once: it is enqueued again then.
+  Ctrl h{};
+  bool was_ahead = false;
   if (int rc = profile_run(d_records, n_records, d_task_offsets, n_tasks, d_ids_out, d_rows_out, row_capacity, d_task_row_offsets,
-                           h_n_rows, ws, prof_bytes, hip_stream, &emit, &all_emitted))
+                           h_n_rows, ws, prof_bytes, hip_stream, &emit, few ? &begin : nullptr,
+                           [&](Tracer& tr, Reads& reads, const Ctrl* prof, bool any_long) {
+                             if (int rc = fill(tr, !any_long, prof)) return rc;
+                             return reads.add(&h, b.ctrl, sizeof(Ctrl));
+                           },
+                           &was_ahead))
     return rc;
   Tracer tr(st);
-  if (int rc = gapfill_enqueue(st, tr, b, d_ids_out, n_records, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task,
-                               d_lp_task, n_scenarios, h_params, d_gap_offsets, n_gaps, d_fill_count, d_filled_ns,
-                               d_lp_completion_ns, d_lp_placed, true, done, all_emitted))
-    return rc;
-  return finish_gapfill(st, tr, b.ctrl, [&] {
+  if (!was_ahead) {
+    if (int rc = fill(tr, false, nullptr)) return rc;
+    tr.mark("host_sync");
+    if (int rc = read_ctrl(b.ctrl, &h, st)) return rc;
+  }
+  return finish_gapfill(st, tr, b.ctrl, h, [&] {
     return gapfill_wide_enqueue(st, b, d_ids_out, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task, d_lp_task,
                                 n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, nullptr);
   });
@@ -1089,10 +1141,11 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   tr.mark("k_gf_predict32");
   hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                      n_tasks, d_rows, d_task_row_offsets, b.role, d_actual_gap_ns, b.lp_e, b.hp_eg, b.lp_total,
-                     static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), b.ctrl);
+                     static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr),
+                     static_cast<const Ctrl*>(nullptr), static_cast<uint64_t>(0), b.ctrl);
   auto walk = h_params->feedback ? walk_enqueue<LW_REPLAY_FEEDBACK> : walk_enqueue<LW_REPLAY>;
   if (int rc = walk(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
-                    h_params->min_gap_ns, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, true))
+                    h_params->min_gap_ns, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, true, nullptr, 0))
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&]() -> int {
     hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
@@ -1180,7 +1233,8 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
     tr.mark("k_gf_predict32");
     hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                        n_tasks, d_rows, d_task_row_offsets, role, static_cast<const int64_t*>(nullptr), lp_e, hp_eg, lp_total,
-                       static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr), ctrl);
+                       static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr),
+                       static_cast<const Ctrl*>(nullptr), static_cast<uint64_t>(0), ctrl);
     const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
     int rc = FIKIT_OK;
 #define FIKIT_PF_WALK(W)                                                                                                   \

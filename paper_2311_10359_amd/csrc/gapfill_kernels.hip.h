@@ -65,10 +65,26 @@ __global__ void k_gf_check(const uint64_t* __restrict__ off, uint32_t n_tasks, u
 // chip's other units save.
 constexpr uint32_t GF_BEGIN_ITEMS = 2048;
 constexpr int GF_BEGIN_THREADS = 1024;
-__global__ void __launch_bounds__(GF_BEGIN_THREADS)
-k_gf_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const uint32_t* __restrict__ hp_task,
-           const uint32_t* __restrict__ lp_task, uint32_t n_scen, const uint64_t* __restrict__ gap_off, uint64_t n_gaps,
-           uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t* __restrict__ done, Ctrl* ctrl) {
+struct GfBegin {
+  const uint32_t *hp_task, *lp_task;
+  uint32_t n_scen;
+  const uint64_t* gap_off;
+  uint64_t n_gaps;
+  uint32_t* role;
+  uint64_t* lp_total;
+  uint32_t* done;
+  Ctrl* ctrl;
+};
+__device__ __forceinline__ void gf_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const GfBegin& a) {
+  const uint32_t* __restrict__ hp_task = a.hp_task;
+  const uint32_t* __restrict__ lp_task = a.lp_task;
+  const uint64_t* __restrict__ gap_off = a.gap_off;
+  const uint64_t n_gaps = a.n_gaps;
+  const uint32_t n_scen = a.n_scen;
+  uint32_t* __restrict__ role = a.role;
+  uint64_t* __restrict__ lp_total = a.lp_total;
+  uint32_t* __restrict__ done = a.done;
+  Ctrl* ctrl = a.ctrl;
   __shared__ uint32_t status;
   const uint32_t tid = threadIdx.x, items = n_tasks > n_scen ? n_tasks : n_scen;
   if (tid == 0) status = 0;
@@ -82,6 +98,9 @@ k_gf_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, c
   __syncthreads();
   if (tid < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[tid] = tid == 0 ? status : 0u;
 }
+
+__global__ void __launch_bounds__(GF_BEGIN_THREADS)
+k_gf_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const GfBegin a) { gf_begin(off, n_tasks, n_ids, a); }
 
 // The status a finished call would return, from the error bits its kernels left (fikit_gapfill_static).
 __device__ __forceinline__ int32_t gf_status(uint32_t bits) {
@@ -396,15 +415,17 @@ __device__ __forceinline__ uint32_t clamp32(int64_t v) {   // (predictions are n
 // 500: 599 -> 216 us.
 // For the replay against actual idle times (actual != nullptr) the first word of hp_eg[i] holds the idle
 // time that really followed launch i instead (clamped to WIDE32, which no filled time can reach).
-// pred_done (may be null): tasks whose predictions exist already and are left alone.
+// pred_done (may be null): tasks whose predictions exist already and are left alone.  prof (may be null, as in the walks): the
+// profile in the same call that this was enqueued behind.
 __global__ void __launch_bounds__(PRED_THREADS)
 k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, uint32_t n_tasks,
                const fikit_row* __restrict__ rows, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role,
                const int64_t* __restrict__ actual, uint32_t* __restrict__ lp_e, uint2* __restrict__ hp_eg,
-               uint64_t* __restrict__ lp_total, uint32_t predictor, const uint32_t* __restrict__ pred_done, Ctrl* ctrl) {
+               uint64_t* __restrict__ lp_total, uint32_t predictor, const uint32_t* __restrict__ pred_done, const Ctrl* prof,
+               uint64_t row_capacity, Ctrl* ctrl) {
   __shared__ PredTable32 tb;
   __shared__ uint64_t wave_tot[PRED_THREADS / WAVE];
-  if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
+  if ((ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) || !may_follow(prof, row_capacity)) return;
   const uint32_t t = rotated_item(blockIdx.x, n_tasks);
   const uint64_t part0 = static_cast<uint64_t>(blockIdx.y) * (2 * PRED_THREADS);   // first launch of this workgroup's part
   const uint32_t rl = role[t];
@@ -596,8 +617,8 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
                uint64_t n_scen, const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e,
                const uint2* __restrict__ hp_eg, const uint64_t* __restrict__ lp_total, int64_t margin, int64_t min_gap,
                uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
-               uint64_t* __restrict__ placed_out, const Ctrl* ctrl) {
-  if (ctrl->status || ctrl->wide) return;
+               uint64_t* __restrict__ placed_out, const Ctrl* prof, uint64_t row_capacity, const Ctrl* ctrl) {
+  if (ctrl->status || ctrl->wide || !may_follow(prof, row_capacity)) return;
   const uint32_t lane = lane_id();
   // (everything that is the same in the whole wave is kept in scalar registers: the scenario number has to be seen as one)
   const uint32_t s = static_cast<uint32_t>(
@@ -789,10 +810,10 @@ k_gf_walk_lanes(const uint64_t* __restrict__ off, const uint32_t* __restrict__ h
                 uint64_t n_scen, const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e,
                 const uint2* __restrict__ hp_eg, const uint64_t* __restrict__ lp_total, int64_t margin, int64_t min_gap,
                 uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
-                uint64_t* __restrict__ placed_out, uint32_t vec_ok, const Ctrl* ctrl) {
+                uint64_t* __restrict__ placed_out, uint32_t vec_ok, const Ctrl* prof, uint64_t row_capacity, const Ctrl* ctrl) {
   extern __shared__ __align__(16) unsigned char lw_raw[];
   LaneWalkSmem& sm = *reinterpret_cast<LaneWalkSmem*>(lw_raw);
-  if (ctrl->status || ctrl->wide) return;
+  if (ctrl->status || ctrl->wide || !may_follow(prof, row_capacity)) return;
   const uint32_t tid = threadIdx.x;
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * LW_THREADS + tid;
   const bool valid = s < n_scen;

@@ -70,10 +70,22 @@ __global__ void k_classify(const uint64_t* __restrict__ off, uint32_t n_tasks, u
 // tiles is known a host round trip earlier.  With more tasks the calls are so long that it no longer matters.
 constexpr uint32_t BEGIN_TASKS = 2048;
 constexpr int BEGIN_THREADS = 1024;
-__global__ void __launch_bounds__(BEGIN_THREADS)
-k_profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n, uint32_t len_small, uint32_t len_mid, uint32_t len_max,
-                uint32_t tile, uint32_t* __restrict__ gflag, uint32_t* __restrict__ dcount, uint32_t* __restrict__ lists,
-                uint32_t* __restrict__ long_prefix, uint32_t* __restrict__ tile_prefix, uint32_t* __restrict__ wflag, Ctrl* ctrl) {
+struct ProfileBegin {
+  uint64_t n;
+  uint32_t len_small, len_mid, len_max, tile;
+  uint32_t *gflag, *dcount, *lists, *long_prefix, *tile_prefix, *wflag;
+  Ctrl* ctrl;
+};
+__device__ __forceinline__ void profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBegin& a) {
+  const uint64_t n = a.n;
+  const uint32_t len_small = a.len_small, len_mid = a.len_mid, len_max = a.len_max, tile = a.tile;
+  uint32_t* __restrict__ gflag = a.gflag;
+  uint32_t* __restrict__ dcount = a.dcount;
+  uint32_t* __restrict__ lists = a.lists;
+  uint32_t* __restrict__ long_prefix = a.long_prefix;
+  uint32_t* __restrict__ tile_prefix = a.tile_prefix;
+  uint32_t* __restrict__ wflag = a.wflag;
+  Ctrl* ctrl = a.ctrl;
   __shared__ uint32_t lds[16], listed[3], bad;
   const uint32_t tid = threadIdx.x;
   if (tid < 3) listed[tid] = 0;
@@ -122,6 +134,8 @@ k_profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n, 
     *ctrl = c;
   }
 }
+__global__ void __launch_bounds__(BEGIN_THREADS)
+k_profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBegin a) { profile_begin(off, n_tasks, a); }
 
 // Execution time and idle time of every launch as they stand in the trace (Section 3.2, "Measuring the
 // execution and idle time of kernel"); task boundaries are put right by k_measure_task_ends afterwards.

@@ -110,3 +110,32 @@ def test_runs_and_errors():
                                       binding.to_device_u32(hp, DEV), binding.to_device_u32(lp, DEV),
                                       binding.to_device_u64(go, DEV), margin_ns=0, min_gap_ns=0)
     assert e.value.status == -4
+
+
+@pytest.mark.parametrize("n_tasks", [3, 1025, 2049])
+@pytest.mark.parametrize("long_task", [False, True])
+def test_the_fill_runs_ahead_of_the_host_only_behind_a_finished_profile(n_tasks, long_task):
+    """The fill is enqueued before the host knows how the profile ended: it must leave its outputs alone where the rows do not fit
+    or a record is bad, and be done again where a task was left to the sort."""
+    rng = np.random.default_rng(n_tasks)
+    lens = rng.integers(1, 40, n_tasks)
+    lens[0], lens[1] = 3000, 17000 if long_task else 900
+    rec, off = ragged_trace(11, lens.tolist(), 9)
+    hp, lp = rng.integers(0, n_tasks, 50).astype(np.uint32), rng.integers(0, n_tasks, 50).astype(np.uint32)
+    hp[0], lp[0], hp[1], lp[1] = 0, 1, 1, 0
+    o = check_fused(rec, off, hp, lp, 100, 0)
+    many = rec.copy()
+    many["name_id"][:3000] = np.arange(3000)      # more IDs than a workgroup holds
+    check_fused(many, off, hp, lp, 100, 0)
+    go = traces.gap_offsets(off, hp)
+    bad = rec.copy()
+    bad["end_ns"][700] = bad["start_ns"][700] - 1
+    for r, capacity, status in ((rec, len(o[1]) - 1, binding.FIKIT_ROW_CAPACITY), (bad, len(o[1]) + 8, binding.FIKIT_BAD_RECORD)):
+        out = binding.GapFill(*(torch.full((k,), 77, dtype=d, device=DEV)
+                                for k, d in ((int(go[-1]), torch.int32), (int(go[-1]), torch.int64), (50, torch.int64), (50, torch.int64))))
+        with pytest.raises(binding.FikitError) as e:
+            binding.fikit_profile_gapfill(binding.to_device_records(r, DEV), binding.to_device_u64(off, DEV), binding.to_device_u32(hp, DEV),
+                                          binding.to_device_u32(lp, DEV), binding.to_device_u64(go, DEV), margin_ns=100, min_gap_ns=0,
+                                          rows_out=torch.empty((capacity, 128), dtype=torch.uint8, device=DEV), out=out)
+        assert e.value.status == status
+        assert all(bool((x == 77).all()) for x in out)
