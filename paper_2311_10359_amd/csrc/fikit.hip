@@ -710,13 +710,14 @@ constexpr uint64_t gapfill_ws_bytes(uint64_t n_ids, uint64_t n_tasks) {
 }
 
 struct GapfillBuffers {
+  uint64_t n_ids;
   Ctrl* ctrl;
   uint32_t* role;
   uint64_t* lp_total;
   int64_t *pe, *pg, *open;   // 64-bit predictions (k_gf_predict)
   uint32_t* lp_e;            // 32-bit predictions (k_gf_predict32): they share the space of pe and pg
   uint2* hp_eg;
-  GapfillBuffers(unsigned char* ws, uint64_t n_ids, uint32_t n_tasks) {
+  GapfillBuffers(unsigned char* ws, uint64_t n_launches, uint32_t n_tasks) : n_ids(n_launches) {
     Carver c;
     ctrl = reinterpret_cast<Ctrl*>(ws + c.take(256));
     role = reinterpret_cast<uint32_t*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 4));
@@ -748,6 +749,20 @@ uint32_t predict_parts(uint64_t n_ids, uint32_t n_tasks) {
   return static_cast<uint32_t>(parts > 64 ? 64 : parts);
 }
 
+// The waves' order of the scenarios is made if there are more than two for each of the chip's SIMDs (up to there the longest trace
+// alone decides, wherever it runs: 1500 even scenarios 82 us without the lists, 84 us with them) and the lists fit `bytes` at `at`
+// (64 per scenario).
+constexpr uint64_t GF_ORDER_MIN_SCENARIOS = 2048 + 1;
+static_assert(GF_ORDER_MIN_SCENARIOS > GF_BEGIN_ITEMS, "k_gf_begin makes no lists");
+GfOrder scenario_order(Ctrl* ctrl, void* at, uint64_t bytes, uint64_t n_scenarios) {
+  static_assert(GF_LANES_MIN_SCENARIOS <= 1u << 16, "scenarios are listed by 16-bit numbers");
+  if (n_scenarios < GF_ORDER_MIN_SCENARIOS || n_scenarios >= GF_LANES_MIN_SCENARIOS || n_scenarios * GF_BUCKETS * 2 > bytes)
+    return GfOrder{nullptr, nullptr};
+  return GfOrder{reinterpret_cast<uint32_t*>(ctrl + 1), static_cast<uint16_t*>(at)};
+}
+// (in the space of the 64-bit opening times, which the 32-bit kernels leave unused)
+GfOrder gapfill_order(const GapfillBuffers& b, uint64_t n_scenarios) { return scenario_order(b.ctrl, b.open, b.n_ids * 8, n_scenarios); }
+
 bool gapfill_checks_are_few(uint32_t n_tasks, uint64_t n_scenarios) { return n_tasks <= GF_BEGIN_ITEMS && n_scenarios <= GF_BEGIN_ITEMS; }
 GfBegin gapfill_begin(const GapfillBuffers& b, const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios,
                       const uint64_t* d_gap_offsets, uint64_t n_gaps, uint32_t* done) {
@@ -765,7 +780,7 @@ void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64
   }
   hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, done, n_tasks);
   hipLaunchKernelGGL(k_gf_check, dim3(blocks_for(n_scenarios > n_tasks ? n_scenarios : n_tasks, 256)), dim3(256), 0, st, d_task_offsets,
-                     n_tasks, n_ids, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, b.role, b.ctrl);
+                     n_tasks, n_ids, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, b.role, gapfill_order(b, n_scenarios), b.ctrl);
 }
 
 // The walk on 32-bit predictions in one of its modes; `result`: completion times, or delays in the replay modes.  prof (may be
@@ -787,8 +802,8 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
   } else {
     tr.mark(MODE == LW_PLAN ? "k_gf_walk_wave" : MODE == LW_REPLAY ? "k_gf_replay_wave" : "k_gf_replay_feedback_wave");
     hipLaunchKernelGGL(k_gf_walk_wave<MODE>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st, d_task_offsets,
-                       d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,
-                       d_filled_ns, result, d_lp_placed, prof, row_capacity, b.ctrl);
+                       d_hp_task, d_lp_task, static_cast<uint32_t>(n_scenarios), d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
+                       d_fill_count, d_filled_ns, result, d_lp_placed, prof, row_capacity, gapfill_order(b, n_scenarios), b.ctrl);
   }
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
@@ -1212,6 +1227,9 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   int64_t* pg = reinterpret_cast<int64_t*>(ws + c.take(n_ids * 8 + GF_PAD));
   uint32_t* lp_e = reinterpret_cast<uint32_t*>(pe);
   uint2* hp_eg = reinterpret_cast<uint2*>(pg);
+  // (behind the 32-bit execution times, in the half of their space that the 64-bit ones would take; an even number of launches in)
+  const uint64_t listed_at = (n_ids + 1) / 2 * 8;
+  const GfOrder order = scenario_order(ctrl, reinterpret_cast<unsigned char*>(pe) + listed_at + GF_PAD, n_ids * 8 - listed_at, n_scenarios);
 
   Tracer tr(st);
   tr.mark("pf_setup");
@@ -1219,7 +1237,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
                      static_cast<uint32_t*>(nullptr), n_tasks);
   hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
   hipLaunchKernelGGL(k_pf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
-                     d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, n_entries, d_gap_offsets, role, ctrl);
+                     d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, n_entries, d_gap_offsets, role, order, ctrl);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};
@@ -1245,7 +1263,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   hipLaunchKernelGGL(k_pf_walk_wave<K>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st,            \
                      d_task_offsets, d_hp_task, d_lp_offsets, d_lp_task, d_lp_prio, static_cast<uint32_t>(n_scenarios),       \
                      d_gap_offsets, lp_e, hp_eg, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,        \
-                     d_lp_placed, d_lp_placed_ns, ctrl)
+                     d_lp_placed, d_lp_placed_ns, order, ctrl)
     // One wave per scenario up to this many scenarios, beyond it a group of lanes per scenario.  The waves' time grows with
     // the scenarios, the groups' hardly does; traces of 1024 launches, queues of 2048, waves / groups in ms for the call:
     //   1 task   4096: 0.35 / 1.22   16,384: 0.94 / 1.42   24,576: 1.34 / 1.54

@@ -13,6 +13,42 @@
 
 namespace fikit {
 
+// Scenarios in the order in which the walks' waves take them, the longest traces first: buckets of half an octave of the
+// high-priority trace's length (bucket 0 the longest), in no order inside.  With several waves per SIMD, what a SIMD has to do is the
+// sum of the traces it happens to get, and the longest may start last: 6000 traces of 1 to 2800 launches needed 93 cycles of a SIMD
+// per gap, even ones 53.  The kernel that checks the scenarios fills the lists, which costs it 2 us; scenarios of one bucket are
+// taken as they are numbered.  Calls in us as numbered / longest first: gap fill of these 6000 490 / 442, of 90 x 96 ragged pairs
+// 390 / 355; replay of 3000 traces of up to 4000 launches 562 / 530; priority queues, 4096 traces of up to 1600 launches and three
+// queues each 1010 / 866; even lengths 332 / 332 (90 x 96 pairs) and 369 / 371 (16,384 scenarios).
+struct GfOrder {
+  uint32_t* count;    // [GF_BUCKETS] scenarios of each bucket, in the words behind the control block (which k_gf_clear clears too);
+                      // null: as they are numbered
+  uint16_t* list;     // [GF_BUCKETS][n_scen]
+};
+constexpr uint32_t GF_BUCKETS = 32;
+constexpr uint32_t GF_BLOCK_WORDS = 64;   // the control block and the words behind it
+static_assert(sizeof(Ctrl) + GF_BUCKETS * 4 <= GF_BLOCK_WORDS * 4, "the buckets' counts lie behind the control block");
+__device__ __forceinline__ uint32_t gf_bucket(uint64_t launches) {
+  // exponent and first bit of the fraction; 16 launches and fewer are the last bucket, 2^19.5 and more the first
+  const uint32_t octaves = __float_as_uint(static_cast<float>(launches)) >> 22, least = (127 + 4) * 2;
+  const uint32_t k = octaves > least ? octaves - least : 0u;
+  return GF_BUCKETS - 1 - (k < GF_BUCKETS - 1 ? k : GF_BUCKETS - 1);
+}
+// Puts scenario s on its list (called by all threads of a workgroup; cnt: LDS).  One reservation per workgroup and bucket.
+__device__ __forceinline__ void gf_order(const GfOrder& order, uint64_t n_scen, uint64_t s, bool valid, uint64_t launches, uint32_t* cnt) {
+  const uint32_t tid = threadIdx.x;
+  __syncthreads();
+  if (tid < GF_BUCKETS) cnt[tid] = 0;
+  __syncthreads();
+  const uint32_t b = valid ? gf_bucket(launches) : 0u;
+  uint32_t at = 0;
+  if (valid) at = atomicAdd(&cnt[b], 1u);
+  __syncthreads();
+  if (tid < GF_BUCKETS && cnt[tid]) cnt[tid] = atomicAdd(&order.count[tid], cnt[tid]);
+  __syncthreads();
+  if (valid) order.list[b * n_scen + cnt[b] + at] = static_cast<uint16_t>(s);
+}
+
 // Start values of a call: the control block, and per task no role, no queue total and (done may be null) no predictions.
 __device__ __forceinline__ void gf_clear_task(uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t* __restrict__ done,
                                               uint32_t t) {
@@ -23,7 +59,7 @@ __device__ __forceinline__ void gf_clear_task(uint32_t* __restrict__ role, uint6
 __global__ void k_gf_clear(Ctrl* ctrl, uint32_t* __restrict__ role, uint64_t* __restrict__ lp_total, uint32_t* __restrict__ done,
                            uint32_t n_tasks) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[t] = 0;
+  if (t < GF_BLOCK_WORDS) reinterpret_cast<uint32_t*>(ctrl)[t] = 0;
   if (t < n_tasks) gf_clear_task(role, lp_total, done, t);
 }
 
@@ -55,10 +91,16 @@ __device__ __forceinline__ uint32_t gf_check_item(const uint64_t* __restrict__ o
 }
 __global__ void k_gf_check(const uint64_t* __restrict__ off, uint32_t n_tasks, uint64_t n_ids, const uint32_t* __restrict__ hp_task,
                            const uint32_t* __restrict__ lp_task, uint64_t n_scen, const uint64_t* __restrict__ gap_off,
-                           uint64_t n_gaps, uint32_t* __restrict__ role, Ctrl* ctrl) {
+                           uint64_t n_gaps, uint32_t* __restrict__ role, const GfOrder order, Ctrl* ctrl) {
+  __shared__ uint32_t cnt[GF_BUCKETS];
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const uint32_t wrong = gf_check_item(off, n_tasks, n_ids, hp_task, lp_task, n_scen, gap_off, n_gaps, role, s);
   if (wrong) atomicOr(&ctrl->status, wrong);
+  if (order.count) {
+    const bool valid = !wrong && s < n_scen;   // (with an error nothing is walked)
+    const uint32_t hp = valid ? hp_task[s] : 0u;
+    gf_order(order, n_scen, s, valid, off[hp + 1] - off[hp], cnt);
+  }
 }
 
 // Both of the above in one workgroup, for so few tasks and scenarios that a second launch costs more (4.5 us) than the
@@ -610,19 +652,38 @@ __device__ __forceinline__ uint32_t write_lane_u32(uint32_t v, uint32_t value, u
 }
 __device__ __forceinline__ uint32_t sat32(uint64_t v) { return v > WIDE32 ? WIDE32 : static_cast<uint32_t>(v); }
 
+// The wave's scenario: its own number, or what order holds at that place.  (Everything that is the same in the whole wave is kept in
+// scalar registers: the scenario number has to be seen as one.)
+__device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint32_t n_scen) {
+  const uint32_t place = static_cast<uint32_t>(
+      __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (WW_THREADS / WAVE) + threadIdx.x / WAVE)));
+  if (!order.count || place >= n_scen) return place;
+  const uint32_t lane = lane_id();
+  const uint32_t upto = wave_incl_scan_u32(lane < GF_BUCKETS ? order.count[lane] : 0u);
+  const uint32_t bucket = popc64(ballot(lane < GF_BUCKETS && upto <= place));
+  const uint32_t longest = popc64(ballot(lane < GF_BUCKETS && upto == 0));
+  if (popc64(ballot(lane < GF_BUCKETS && upto == n_scen)) + longest == GF_BUCKETS) return place;   // (one bucket holds them all)
+  if (bucket >= GF_BUCKETS) return n_scen;   // (cannot happen: every scenario is on a list)
+  // the longest buckets decide when the launch ends: their instructions are issued first
+  const uint32_t behind = bucket - longest;
+  if (behind == 0) __builtin_amdgcn_s_setprio(3);
+  else if (behind == 1) __builtin_amdgcn_s_setprio(2);
+  else if (behind == 2) __builtin_amdgcn_s_setprio(1);
+  const uint32_t before = bucket ? read_lane_u32(upto, bucket - 1) : 0u;
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(order.list[bucket * n_scen + (place - before)])));
+}
+
 // (completion_out receives the delay in the replay modes).
 template <int MODE>
 __global__ void __launch_bounds__(WW_THREADS)
 k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
-               uint64_t n_scen, const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e,
+               uint32_t n_scen, const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e,
                const uint2* __restrict__ hp_eg, const uint64_t* __restrict__ lp_total, int64_t margin, int64_t min_gap,
                uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
-               uint64_t* __restrict__ placed_out, const Ctrl* prof, uint64_t row_capacity, const Ctrl* ctrl) {
+               uint64_t* __restrict__ placed_out, const Ctrl* prof, uint64_t row_capacity, const GfOrder order, const Ctrl* ctrl) {
   if (ctrl->status || ctrl->wide || !may_follow(prof, row_capacity)) return;
   const uint32_t lane = lane_id();
-  // (everything that is the same in the whole wave is kept in scalar registers: the scenario number has to be seen as one)
-  const uint32_t s = static_cast<uint32_t>(
-      __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (WW_THREADS / WAVE) + threadIdx.x / WAVE)));
+  const uint32_t s = scenario_of_wave(order, n_scen);
   if (s >= n_scen) return;
   const uint32_t hp = hp_task[s], lp = lp_task[s];
   const uint32_t h0 = static_cast<uint32_t>(off[hp]), H = static_cast<uint32_t>(off[hp + 1]) - h0;

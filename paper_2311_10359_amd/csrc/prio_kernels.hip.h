@@ -14,8 +14,9 @@ constexpr uint32_t PF_MAX_LP = FIKIT_PRIO_MAX_LP;   // low-priority tasks of one
 __global__ void k_pf_scenarios(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* __restrict__ hp_task,
                                const uint64_t* __restrict__ lp_off, const uint32_t* __restrict__ lp_task,
                                const uint32_t* __restrict__ lp_prio, uint64_t n_scen, uint64_t n_entries,
-                               const uint64_t* __restrict__ gap_off, uint32_t* __restrict__ role, Ctrl* ctrl) {
-  if (ctrl->status & ERR_OFFSETS) return;
+                               const uint64_t* __restrict__ gap_off, uint32_t* __restrict__ role, const GfOrder order, Ctrl* ctrl) {
+  __shared__ uint32_t cnt[GF_BUCKETS];
+  if (ctrl->status & ERR_OFFSETS) return;   // (bits of an earlier kernel: the same for all threads)
   const uint64_t s = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   uint32_t k_here = 0;
   if (s < n_scen) {
@@ -43,6 +44,11 @@ __global__ void k_pf_scenarios(const uint64_t* __restrict__ off, uint32_t n_task
       // (the age of a waiting request is counted in 32 bits: one tick per list entry, then one per kernel issued)
       if (launches + (e1 - e0) >= (1ull << 32)) atomicOr(&ctrl->status, ERR_LP_LIMIT);
     }
+  }
+  if (order.count) {
+    const uint32_t hp = s < n_scen ? hp_task[s] : n_tasks;
+    const bool valid = hp < n_tasks;   // (with an error nothing is walked)
+    gf_order(order, n_scen, s, valid, valid ? off[hp + 1] - off[hp] : 0, cnt);
   }
   const uint32_t k_wave = wave_max_u32(k_here);
   if (lane_id() == 0 && k_wave) atomicMax(&ctrl->n_class[3], k_wave);
@@ -337,13 +343,12 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
                const uint32_t* __restrict__ lp_task, const uint32_t* __restrict__ lp_prio, uint32_t n_scen,
                const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e, const uint2* __restrict__ hp_eg,
                int64_t margin, int64_t min_gap, uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns,
-               uint64_t* __restrict__ placed_out, int64_t* __restrict__ placed_ns_out, const Ctrl* ctrl) {
+               uint64_t* __restrict__ placed_out, int64_t* __restrict__ placed_ns_out, const GfOrder order, const Ctrl* ctrl) {
   constexpr uint32_t K = WAVE / SEG;
   static_assert(K <= 16, "the requests fit a row of lanes");
   if (ctrl->status || ctrl->wide) return;
   const uint32_t lane = lane_id(), mine = lane / SEG, place = lane % SEG;   // the queue this lane belongs to
-  const uint32_t s = static_cast<uint32_t>(
-      __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (WW_THREADS / WAVE) + threadIdx.x / WAVE)));
+  const uint32_t s = scenario_of_wave(order, n_scen);
   if (s >= n_scen) return;
   const uint32_t hp = hp_task[s];
   const uint32_t h0 = static_cast<uint32_t>(off[hp]), H = static_cast<uint32_t>(off[hp + 1]) - h0;

@@ -6,6 +6,7 @@ import pytest
 from paper_2311_10359_amd import traces
 from parity_util import LANES_MIN_SCENARIOS, check_gapfill, check_profile, kernels_of
 from test_gpu_parity import all_pairs
+from test_gpu_prio import check_prio
 from test_gpu_replay import check_measure, check_replay
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,28 @@ def test_walk_edges(exec_choices, gap_choices, copies):
     assert walks == {"k_gf_walk_lanes" if hp.size >= LANES_MIN_SCENARIOS else "k_gf_walk_wave"}
     d_gap, gap = check_measure(rec, off)
     check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 3, 0)
+
+
+@pytest.mark.parametrize("n_scen,launches", [(2048, 40000), (2049, 8 * 2049 - 1), (2049, 8 * 2049), (2049, 16 * 2049), (5000, 90000), (32767, 8 * 32767)])
+def test_walk_order(n_scen, launches):
+    """Waves take the scenarios by buckets of their traces' lengths: below and from the number of scenarios on from which they do, with
+    lists that just fit and that do not, traces of no launch to a few thousand, and all of one bucket."""
+    rng = np.random.default_rng(n_scen + launches)
+    share = np.exp(rng.uniform(0, 6, 300))
+    lens = (0.9 * launches * share / share.sum()).astype(np.int64)
+    lens[:4] = 0, 1, 16, 17
+    lens[-1] += launches - lens.sum()
+    rec, off = trace_of(n_scen, list(lens), [100, 250], [0, 90, 400, 900])
+    prof, d_off, o_prof = check_profile(rec, off)
+    few = np.flatnonzero(lens < 3000)
+    hp, lp = rng.choice(few, n_scen).astype(np.uint32), rng.choice(few, n_scen).astype(np.uint32)
+    with kernels_of() as names:
+        check_gapfill(prof, d_off, off, o_prof, hp, lp, 3, 0)
+    assert "k_gf_walk_wave" in names
+    d_gap, gap = check_measure(rec, off)
+    check_replay(prof, d_off, off, o_prof, d_gap, gap, hp, lp, 3, 0)
+    check_gapfill(prof, d_off, off, o_prof, np.full(n_scen, hp[0]), lp, 3, 0)
+    if n_scen <= 12288:
+        entries = np.arange(n_scen + 1, dtype=np.uint64) * 2
+        both = np.stack([lp, rng.choice(few, n_scen).astype(np.uint32)], axis=1).ravel()
+        check_prio(prof, d_off, off, o_prof, hp, entries, both, np.full(2 * n_scen, 3, dtype=np.uint32), 3, 0)
