@@ -688,8 +688,8 @@ int fikit_profile(const fikit_launch* d_records, uint64_t n_records, const uint6
 constexpr uint64_t GF_PAD = 256;
 // From this many scenarios on, one lane steps through a scenario (k_gf_walk_lanes), below it a wave (k_gf_walk_wave).  The
 // lanes' time hardly depends on how many there are (to 65,536); the waves' grows with them, and with the gaps that take
-// something.  Traces of 4096 and queues of 16,384 launches: the lanes 3.3 ms, the waves 0.1 ms per 1024 scenarios once the chip
-// is full (1.44 ms against 3.2 ms at 16,384).  Calls over shorter tasks, waves / lanes in ms (gap fill; replay with feedback):
+// something.  Traces of 4096 and queues of 16,384 launches: the lanes 3.3 ms, the waves 0.08 ms per 1024 scenarios once the chip
+// is full (1.18 ms against 3.2 ms at 16,384).  Calls over shorter tasks, waves / lanes in ms (gap fill; replay with feedback):
 //   1024 gaps that take about one kernel each   16,384: 0.41 / 0.52; 0.48 / 0.55   24,000: 0.52 / 0.54; 0.60 / 0.56
 //                                               32,000: 0.63 / 0.55; 0.75 / 0.56
 //   512 gaps that take about ten each           16,384: 0.55 / 1.30; 0.61 / 1.22   32,000: 0.91 / 1.32; 1.05 / 1.25

@@ -627,11 +627,14 @@ enum : int { LW_PLAN = 0, LW_REPLAY = 1, LW_REPLAY_FEEDBACK = 2 };
 // at any other value it is done.  If the sums themselves passed 32 bits, the window is reloaded at the head, where
 // C = 0 and everything that can fit is exact.
 //
-// What bounds it: with few scenarios the chain of one gap (about 22 instructions; 120 cycles per gap, the windows' ends
-// included), with many the issue of
-// scalar instructions (the gap's fourteen scalar instructions go through one port per SIMD).  64 scenarios of 1500 gaps:
-// 0.076 ms (the 64-bit kernel above, which passes 64-bit sums through the LDS crossbar: 0.23 ms); 256 scenarios of 65,535
-// gaps of which few take anything: 0.52 ms (1.8 ms); 16,384 scenarios of 4095 gaps: 1.44 ms (one lane each: 3.2 ms).
+// What bounds it: with few scenarios the chain of one gap (eight steps that pass between the vector and the scalar unit; 100
+// cycles per gap, the windows' ends included), with many the issue of
+// scalar instructions (the gap's fourteen scalar instructions go through one port per SIMD).  A gap that takes the window's
+// rest and ends inside the next window has a way of its own: with kernels of a fifth of a gap that is every twelfth gap, and the
+// general loop goes through twice its instructions for it (ms with the loop / now: 64 scenarios of 1500 gaps 0.076 / 0.063, 16,384 of
+// 4095 gaps 1.43 / 1.18, 6000 ragged ones of up to 2800 0.25 / 0.22, replay of 6000 of 2047 gaps with feedback 0.44 / 0.376).
+// The 64-bit kernel above, which passes 64-bit sums through the LDS crossbar, takes 0.23 ms for the first of these, one lane each
+// 3.2 ms for the second.  The loop written in assembly with a quarter fewer instructions per gap is no faster (call 97 / 99 us).
 constexpr int WW_THREADS = 256;
 constexpr uint32_t WW_WIN = WAVE - 1;
 constexpr int WW_BLOCKS = 4;   // blocks of 64 gaps per round (their reads are one round ahead)
@@ -759,12 +762,14 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
           // the entries that end before that.
           const uint32_t limit = read_lane_u32(lim, k);
           uint32_t o2 = popc64(ballot(win < limit));
+          bool over = false;   // (with feedback: nothing is issued after these)
           if (MODE == LW_REPLAY_FEEDBACK) {
             const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
             const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
+            over = o3 <= o2;
             o2 = o3 < o2 ? o3 : o2;
           }
-          const uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
+          uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
           // the common case: the gap ends inside the window, at an entry whose running sum is exact
           uint32_t c = o2 - o, f = C2 - C;
           if (__builtin_expect(sum2 != WIDE32, 1)) {
@@ -772,9 +777,28 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
           } else {
             // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
             uint32_t left = read_lane_u32(b1[j], k);
-            c = f = 0;
             const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
-            for (;;) {
+            bool ended = false;
+            if (o2 == WW_WIN && !over && wb + WW_WIN < L) {
+              // nearly all of these: the gap takes the rest of the window (c and f so far) and ends inside the next one
+              left -= f;
+              wb += WW_WIN;
+              set_window(r1);
+              r1 = entry(wb + WW_WIN + lane);
+              o2 = popc64(ballot(win < left));
+              if (MODE == LW_REPLAY_FEEDBACK) {
+                const uint32_t o3 = popc64(ballot(win < actual - f)) + 1;
+                o2 = o3 < o2 ? o3 : o2;
+              }
+              C2 = read_lane_u32(before, o2);
+              sum2 = read_lane_u32(win, o2);
+              ended = sum2 != WIDE32;
+              o = ended ? o2 : 0u; C = ended ? C2 : 0u; sum = sum2;
+              c += o; f += C;
+            } else {
+              c = f = 0;
+            }
+            if (!ended) for (;;) {
               if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
               o2 = popc64(ballot(win < C + left));
               bool stop = false;
