@@ -2,6 +2,8 @@
 // Algorithm 2 (BestPrioFit) over the priority queues Q1..Q9.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hip.h"
 #include "gapfill_kernels.hip.h"
 
@@ -337,6 +339,15 @@ k_pf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 // What bounds it: with few scenarios the chain of one decision (compare, first lane, three lane reads, compare, lane write:
 // about 260 cycles), with many the issue of its 25 to 35 instructions.  4096 scenarios of 1023 gaps and three queues of 2048:
 // 0.94 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
+// Up to this many scenarios (every wave has a SIMD to itself) a scenario whose levels hold one or two requests, and one of them two,
+// goes through a level in scalars: the chain of a decision is then one lane read instead of eight steps between the two units.  It is as
+// many instructions, most of them for the scalar port, and with four waves per SIMD that loses.  Traces of 1024 launches, queues of
+// 2048, ms for the call through the lanes / in scalars:
+//   64 scenarios    2 tasks 0.63 / 0.45   3: 0.79 / 0.58   6: 1.11 / 0.75   9: 1.15 / 0.88
+//   1024 scenarios  2 tasks 0.66 / 0.48   3: 0.82 / 0.62   6: 1.33 / 0.86   9: 1.40 / 1.02
+//   4096 scenarios  2 tasks 0.86 / 0.91   3: 1.06 / 1.23   6: 1.64 / 1.52   9: 1.73 / 1.61
+// A queue that is alone: 1000 scenarios 0.25 / 0.28.
+constexpr uint32_t PF_PAIRS_SCENARIOS = 1024;
 template <int SEG>
 __global__ void __launch_bounds__(WW_THREADS)
 k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint64_t* __restrict__ lp_off,
@@ -403,73 +414,105 @@ k_pf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
     return read_lane_u32(m, 0);
   };
   uint32_t least = shortest();
+  auto next_window = [&](uint32_t& w) {   // a queue's window is used up: w stands at its end
+    w -= SEG;
+    if (mine == w / SEG) {
+      issued_ns += raw;
+      start += SEG;
+      raw = start + place < len ? next : WIDE32;
+      const uint32_t at = start + SEG + place;
+      next = queue[at < len ? at : 0u];   // (a queue with a window to use up is not empty)
+    }
+  };
 
   const uint2* __restrict__ trace = hp_eg + h0;
   auto idle_time = [&](uint32_t i) { return trace[i < n_gaps ? i : 0u].y; };
   uint32_t G0 = n_gaps ? idle_time(lane) : 0u, G1 = n_gaps ? idle_time(WAVE + lane) : 0u;
   uint32_t i0 = 0;
-  for (; i0 < n_gaps && least != WIDE32; i0 += WAVE) {
-    const uint32_t i = i0 + lane, G = G0;
-    G0 = G1;
-    G1 = idle_time(i + 2 * WAVE);
-    const uint32_t b1 = (i < n_gaps && G >= gap_floor) ? G - margin32 + 1 : 0u;   // one more than what may be filled
-    uint32_t my_c = 0, my_f = 0;
-    // (one way out of every loop, at its end: see k_gf_walk_wave)
-    uint64_t takes = ballot(b1 > least);
-    if (takes) do {
-      const uint32_t j = static_cast<uint32_t>(__builtin_ctzll(takes));
-      const uint64_t todo = (~1ull) << j;
-      const uint32_t budget = read_lane_u32(b1, j) - 1;
-      uint32_t rem = budget, c = 0;
-      uint64_t fit = ballot(hd <= rem);   // (never empty here)
-      do {
-        const uint32_t p = static_cast<uint32_t>(__builtin_ctzll(fit));
-        rem -= read_lane_u32(hd, p);
-        ++c;
-        uint32_t w = read_lane_u32(ho, p) + 1;
-        const uint32_t others = read_lane_u32(seg_others, p);
-        if (__builtin_expect(w % SEG == 0, 0)) {   // the queue's window is used up
-          w -= SEG;
-          if (mine == w / SEG) {
-            issued_ns += raw;
-            start += SEG;
-            raw = start + place < len ? next : WIDE32;
-            const uint32_t at = start + SEG + place;
-            next = queue[at < len ? at : 0u];   // (a queue with a window to use up is not empty)
+  auto gaps = [&](auto levels) {
+    constexpr bool PAIRS = decltype(levels)::value;
+    for (; i0 < n_gaps && least != WIDE32; i0 += WAVE) {
+      const uint32_t i = i0 + lane, G = G0;
+      G0 = G1;
+      G1 = idle_time(i + 2 * WAVE);
+      const uint32_t b1 = (i < n_gaps && G >= gap_floor) ? G - margin32 + 1 : 0u;   // one more than what may be filled
+      uint32_t my_c = 0, my_f = 0;
+      // (one way out of every loop, at its end: see k_gf_walk_wave)
+      uint64_t takes = ballot(b1 > least);
+      if (takes) do {
+        const uint32_t j = static_cast<uint32_t>(__builtin_ctzll(takes));
+        const uint64_t todo = (~1ull) << j;
+        const uint32_t budget = read_lane_u32(b1, j) - 1;
+        uint32_t rem = budget, c = 0;
+        uint64_t fit = ballot(hd <= rem);   // (never empty here)
+        do {
+          const uint32_t p = static_cast<uint32_t>(__builtin_ctzll(fit));
+          const uint32_t others = read_lane_u32(seg_others, p);
+          if constexpr (PAIRS) {
+            // in scalars: what stands before the level does not fit and will not in this gap, so that the level goes on until its
+            // shorter request does not fit either (a level of one: the other never fits)
+            const uint32_t first = read_lane_u32(seg_first, p), second = first + (others ? 1u : 0u);
+            uint32_t d0 = others ? read_lane_u32(hd, first) : WIDE32, w0 = read_lane_u32(ho, first);
+            uint32_t d1 = read_lane_u32(hd, second), w1 = read_lane_u32(ho, second);
+            do {
+              const bool longer = d0 <= rem;
+              const uint32_t dy = longer ? d1 : d0, wy = longer ? w1 : w0;   // the one that goes on waiting
+              uint32_t w = (longer ? w0 : w1) + 1;
+              rem -= longer ? d0 : d1;
+              ++c;
+              if (__builtin_expect(w % SEG == 0, 0)) next_window(w);
+              const uint32_t n = read_lane_u32(raw, w);
+              const bool behind = dy >= n;
+              d0 = behind ? dy : n; w0 = behind ? wy : w;
+              d1 = behind ? n : dy; w1 = behind ? w : wy;
+            } while (d1 <= rem);
+            hd = write_lane_u32(hd, d0, first);   // (of a level of one: overwritten below)
+            ho = write_lane_u32(ho, w0, first);
+            hd = write_lane_u32(hd, d1, second);
+            ho = write_lane_u32(ho, w1, second);
+            fit = ballot(hd <= rem);
+          } else {
+            rem -= read_lane_u32(hd, p);
+            ++c;
+            uint32_t w = read_lane_u32(ho, p) + 1;
+            if (__builtin_expect(w % SEG == 0, 0)) next_window(w);
+            const uint32_t n = read_lane_u32(raw, w);
+            uint32_t to = p;
+            if (K > 1 && others) {
+              const uint32_t ahead = static_cast<uint32_t>(ballot(hd >= n)) & others;
+              to = read_lane_u32(seg_first, p) + static_cast<uint32_t>(__builtin_popcount(ahead));
+              if (to > p) {
+                const uint32_t d1 = dpp_move<0x101>(hd), o1 = dpp_move<0x101>(ho);   // row_shl:1, from the lane above
+                const bool moves = lane - p < to - p;
+                hd = moves ? d1 : hd;
+                ho = moves ? o1 : ho;
+              }
+              if (to < p) {
+                const uint32_t d1 = dpp_move<0x111>(hd), o1 = dpp_move<0x111>(ho);   // row_shr:1, from the lane below
+                const bool moves = lane - to - 1 < p - to;
+                hd = moves ? d1 : hd;
+                ho = moves ? o1 : ho;
+              }
+            }
+            hd = write_lane_u32(hd, n, to);
+            ho = write_lane_u32(ho, w, to);
+            fit = ballot(hd <= rem);
           }
-        }
-        const uint32_t n = read_lane_u32(raw, w);
-        uint32_t to = p;
-        if (K > 1 && others) {
-          const uint32_t ahead = static_cast<uint32_t>(ballot(hd >= n)) & others;
-          to = read_lane_u32(seg_first, p) + static_cast<uint32_t>(__builtin_popcount(ahead));
-          if (to > p) {
-            const uint32_t d1 = dpp_move<0x101>(hd), o1 = dpp_move<0x101>(ho);   // row_shl:1, from the lane above
-            const bool moves = lane - p < to - p;
-            hd = moves ? d1 : hd;
-            ho = moves ? o1 : ho;
-          }
-          if (to < p) {
-            const uint32_t d1 = dpp_move<0x111>(hd), o1 = dpp_move<0x111>(ho);   // row_shr:1, from the lane below
-            const bool moves = lane - to - 1 < p - to;
-            hd = moves ? d1 : hd;
-            ho = moves ? o1 : ho;
-          }
-        }
-        hd = write_lane_u32(hd, n, to);
-        ho = write_lane_u32(ho, w, to);
-        fit = ballot(hd <= rem);
-      } while (fit);
-      my_c = write_lane_u32(my_c, c, j);
-      my_f = write_lane_u32(my_f, budget - rem, j);
-      least = shortest();
-      takes = ballot(b1 > least) & todo;
-    } while (takes);
-    if (i < n_gaps) {
-      fill_count[g0 + i] = my_c;
-      filled_ns[g0 + i] = static_cast<int64_t>(my_f);
+        } while (fit);
+        my_c = write_lane_u32(my_c, c, j);
+        my_f = write_lane_u32(my_f, budget - rem, j);
+        least = shortest();
+        takes = ballot(b1 > least) & todo;
+      } while (takes);
+      if (i < n_gaps) {
+        fill_count[g0 + i] = my_c;
+        filled_ns[g0 + i] = static_cast<int64_t>(my_f);
+      }
     }
-  }
+  };
+  if (K > 1 && n_scen <= PF_PAIRS_SCENARIOS && ballot((seg_others & (seg_others - 1)) != 0) == 0 && ballot(seg_others != 0))
+    gaps(std::true_type{});
+  else gaps(std::false_type{});
   for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queues ran empty)
     fill_count[g0 + i] = 0;
     filled_ns[g0 + i] = 0;

@@ -45,3 +45,18 @@ def test_prio_groups_of_lanes_on_long_queues(k_max):
             print(f"{hp.size} scenarios of up to {k_max} tasks, {n_gaps} gaps", flush=True)
             check_prio(prof, d_off, off, o_prof, hp, lo, lt, lq, 3, 5, out=buffers)
     assert "k_pf_walk" in names and "k_pf_walk_wave" not in names
+
+
+@pytest.mark.parametrize("n_scen", [1024, 1025])
+@pytest.mark.parametrize("k", [2, 3, 5, 16])
+def test_prio_levels_of_one_or_two_requests(n_scen, k):
+    """Both sides of the number of scenarios up to which such levels are gone through in scalars."""
+    lens = [0, 1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 129, 200]
+    rec, off = trace_of(k, lens, [100, 250, 250, 40], [0, 90, 400, 2000])
+    prof, d_off, o_prof = check_profile(rec, off)
+    rng = np.random.default_rng(k)
+    hp = rng.integers(0, len(lens), n_scen).astype(np.uint32)
+    lo = np.arange(n_scen + 1, dtype=np.uint64) * k
+    lt = rng.integers(0, len(lens), n_scen * k).astype(np.uint32)
+    lq = np.concatenate([1 + rng.permutation(k) // 2 for _ in range(n_scen)]).astype(np.uint32)
+    check_prio(prof, d_off, off, o_prof, hp, lo, lt, lq, 3, 5)
