@@ -493,8 +493,9 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     tr.mark("k_unit_sorted_small");
     ua.list = lists; ua.count = &ctrl->n_class[0];
     if (int rc = launch_units<512, FUSE_SMALL_MAX / 512, UNIT_DMAX, 6>(at_most(2 * (n / FUSE_SMALL_MAX) + n_long), ua, st)) return rc;
-    // (streamed units last, so that a task that another unit has left to the sort, for holding too many IDs, is not streamed in vain;
-    // a streamed unit has more than FUSE_MAX launches, or is one of the MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
+    // (streamed units behind these, so that a task that one of them has left to the sort, for holding too many IDs, is not streamed
+    // in vain; units of more than FUSE_MID_MAX launches run beside them, see unit_streamed; a streamed unit has more than FUSE_MAX
+    // launches, or is one of the MSD_SLOTS buckets of a task of more than UNIT_RUNS_MAX tiles)
     tr.mark("k_unit_large");
     FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_unit_large), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   static_cast<int>(UNIT_LARGE_LDS)));

@@ -47,7 +47,7 @@ struct StreamSmem {
   uint8_t log2n[4][SU_DMAX];    // ... and log2 of the bins
   uint16_t slot_of[SU_DMAX];    // rank -> slot
   uint32_t aux[SU_WAVES];
-  uint32_t ndist, fallback, filled, again, first_row;
+  uint32_t ndist, fallback, filled, again, first_row, given_up;
   union {
     uint32_t hist[SU_HIST];
     struct { uint64_t ckey[SU_DMAX]; uint16_t cslot[SU_DMAX]; } tmp;
@@ -128,6 +128,11 @@ __device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
 
 // pack_kg, pack_slot: two 8-byte arrays that only the sort would use.  A unit writes the slices of both that belong to its own
 // launches (ustart, ulen) and nothing else: other tasks may have handed their values over to the sort there already.
+// Another unit may give the task up to the sort at any time (the launches of smaller units have run, but units of more than
+// FUSE_MID_MAX launches and other streamed ones run beside it): the task's flag is looked at along the way, and the unit leaves.
+// fikit_profile, us, flag looked at at the start only / along the way, with 600 IDs in a bucket of 12,000 launches beside one ID with
+// most of the others: a task of 300,000 launches 1500 / 1185, 16 of them 1830 / 1520, 64 of 1,000,000 11,150 / 9550; profiles of
+// which no task is given up are the same.
 __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit, uint2* __restrict__ pack_kg_all,
                                               int64_t* __restrict__ pack_slot_all, StreamSmem& sm) {
   const uint32_t m = A.ulen[unit], t = A.utask[unit];
@@ -141,11 +146,10 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
     sm.ht_key[s] = HT_EMPTY; sm.esum[s] = 0; sm.gsum[s] = 0; sm.cnt[s] = 0; sm.gcnt[s] = 0;
     sm.emin[s] = ~0u; sm.emax[s] = 0; sm.gmin[s] = ~0u; sm.gmax[s] = 0;
   }
-  // (the other units have run: a task that one of them has left to the sort needs nothing here)
-  if (tid == 0) {
-    sm.ndist = 0; sm.filled = 0;
-    sm.fallback = __hip_atomic_load(&A.mflag[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0u : 1u;
-  }
+  auto given_up = [&]() -> uint32_t {   // (nothing waits for the answer where it is asked)
+    return __hip_atomic_load(&A.mflag[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0u : 1u;
+  };
+  if (tid == 0) { sm.ndist = 0; sm.filled = 0; sm.fallback = given_up(); }
   __syncthreads();
 
   // ---- 1. gather the bucket's runs --------------------------------------------------------------------------------
@@ -176,6 +180,8 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
         longest = rc[r] > longest ? rc[r] : longest;
       }
       for (uint32_t x0 = 0; x0 < longest; x0 += WAVE) {
+        if (__hip_atomic_load(&sm.fallback, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
+        const uint32_t leave = tid == 0 ? given_up() : 0u;
         const uint32_t x = x0 + lane;
         uint64_t id[SU_RUNS];
         uint2 kg[SU_RUNS];
@@ -226,6 +232,7 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
             }
           }
         }
+        if (leave) atomicOr(&sm.fallback, 1u);
       }
     }
     if (dom_slot != SU_HT) {   // (the same in the whole wave)
@@ -247,8 +254,9 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
   const uint64_t task_start = A.off[t];
   const uint32_t task_len = static_cast<uint32_t>(A.off[t + 1] - task_start);
   const bool fits = !sm.fallback && D <= SU_DMAX && sm.filled == m;
-  if (tid == 0) { sm.first_row = fits ? atomicAdd(&A.staged[t], D) : 0u; A.ustage[unit] = sm.first_row; }
+  if (tid == 0) { sm.given_up = given_up(); sm.first_row = fits ? atomicAdd(&A.staged[t], D) : 0u; A.ustage[unit] = sm.first_row; }
   __syncthreads();
+  if (sm.given_up) return;   // (the same for all threads)
   const uint32_t row0 = sm.first_row;
   if (!fits || row0 + D > stage_room(task_len)) {
     if (tid == 0) unit_to_general(A, t);
@@ -292,6 +300,7 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
   __syncthreads();
 
   // ---- 2. nearest-rank percentiles -------------------------------------------------------------------------------
+  const uint32_t leave = tid == 0 ? given_up() : 0u;
   for (uint32_t i0 = 0; i0 < m; i0 += SU_KPT * SU_THREADS) {
     uint2 kg[SU_KPT];
     uint32_t sl[SU_KPT];
@@ -313,7 +322,9 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
       }
     }
   }
+  if (leave) sm.given_up = 1;
   __syncthreads();
+  if (sm.given_up) return;
   for (uint32_t q = w; q < 4 * D; q += SU_WAVES) {   // (2 * array + percentile, rank); a wave each
     const uint32_t ap = q / D, j = q - ap * D, arr = ap >> 1, s = sm.slot_of[j];
     const uint32_t n = arr ? sm.gcnt[s] : sm.cnt[s];

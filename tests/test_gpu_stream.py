@@ -127,3 +127,35 @@ def test_more_tiles_than_a_unit_can_list():
     """A task of more than 1024 tiles: all of its buckets are streamed, large and small."""
     rec, off = skewed(5, [4_200_000, 900], 300, 0.1, "lognormal")
     check_profile(rec, off)
+
+
+def names_by_bucket(n=400_000):
+    """Kernel names (their number) by the bucket that their IDs fall into."""
+    names = np.arange(n, dtype=np.uint32)
+    rec = np.zeros(n, dtype=traces.LAUNCH_DTYPE)
+    rec["name_id"], rec["grid"], rec["block"] = names, 1, 64
+    top = oracle.profile(rec, np.array([0, n], dtype=np.uint64))[0] >> np.uint64(56)
+    return [names[top == b] for b in range(256)]
+
+
+def trace_of(kids, ex, gap):
+    """One task per array of kernel names."""
+    kid = np.concatenate(kids)
+    rec = np.zeros(kid.size, dtype=traces.LAUNCH_DTYPE)
+    rec["name_id"], rec["grid"], rec["block"] = kid, 1, 64
+    rec["start_ns"] = np.cumsum(ex + gap) - (ex + gap)
+    rec["end_ns"] = rec["start_ns"] + ex
+    return rec, np.concatenate([[0], np.cumsum([k.size for k in kids])]).astype(np.uint64)
+
+
+@pytest.mark.parametrize("ids,sorts", [(512, False), (600, True)])
+def test_task_that_a_large_unit_gives_up_while_it_is_streamed(ids, sorts):
+    """A bucket of 12,000 launches holds as many IDs as its unit's table, or more; another bucket of the task is streamed beside it."""
+    by, rng = names_by_bucket(), np.random.default_rng(ids)
+    assert by[9].size >= ids
+    others = np.concatenate([by[b][:1] for b in range(0, 256, 3) if b not in (6, 9)])
+    kids = [rng.permutation(np.concatenate([np.full(230_000, by[6][0]), np.resize(by[9][:ids], 12_000), rng.choice(others, 58_000)]))
+            for _ in range(3)]
+    n = sum(k.size for k in kids)
+    rec, off = trace_of(kids, np.maximum(1, np.rint(rng.lognormal(8.5, 1.5, n))).astype(np.int64), rng.integers(0, 30_000, n))
+    assert sorted_with(rec, off) == sorts
