@@ -1175,6 +1175,32 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   });
 }
 
+}  // extern "C"
+
+namespace {
+
+// One wave per scenario up to this many scenarios, beyond it a group of lanes per scenario.  The waves' time grows with
+// the scenarios, the groups' hardly does; traces of 1024 launches, queues of 2048, waves / groups in ms for the call:
+//   1 task   4096: 0.35 / 1.22   16,384: 0.94 / 1.42   24,576: 1.34 / 1.54
+//   2 tasks  4096: 0.87 / 1.81   8192: 1.41 / 1.87   12,288: 1.93 / 1.96
+//   3 tasks  64: 0.80 / 2.2   4096: 1.07 / 2.34   8192: 1.74 / 2.39   12,288: 2.41 / 2.76
+//   4 tasks  4096: 1.42 / 2.64   12,288: 2.88 / 3.11   6 tasks  4096: 1.59 / 3.41   12,288: 3.14 / 3.99
+//   9 tasks  4096: 1.71 / 3.75   16,384: 3.97 / 5.47   24,576: 5.51 / 7.75
+// Shorter traces: gaps of one kernel each (512, queues of 512), of ten (256, queues of 2048), few that take any (1024):
+//   1 task   12,288: 0.25 / 0.55, 0.58 / 0.58, 0.13 / 0.90   24,576: 0.37 / 0.58, 1.02 / 0.61, 0.18 / 0.92
+//   2 tasks  8192: 0.29 / 0.67, 0.97 / 1.01, 0.12 / 1.15   12,288: 0.37 / 0.69, 1.31 / 1.02, 0.15 / 1.17
+//   3 tasks  12,288: 0.42 / 0.83, 1.40 / 1.25, 0.17 / 1.45   6 tasks  12,288: 0.55 / 1.10, 1.54 / 1.56, 0.23 / 1.91
+//   9 tasks  24,576: 1.06 / 2.18, 2.96 / 3.10, 0.49 / 3.73   16 tasks  24,576: 1.37 / 2.47, 3.25 / 3.44, 0.77 / 4.01
+// (Ten kernels per gap are better off with the groups from 12,288 scenarios of one task and 8192 of two to five on; what
+// gaps take is not known here, and the other shapes gain more than that one loses.)
+bool prio_by_wave(uint64_t widest, uint64_t n_scenarios) {
+  return widest <= 16 && n_scenarios <= (widest <= 1 || widest > 8 ? 24576u : 12288u);
+}
+
+}  // namespace
+
+extern "C" {
+
 size_t fikit_prio_fill_workspace_bytes(uint64_t n_ids, uint32_t n_tasks, uint64_t n_scenarios) {
   (void)n_scenarios;
   if (n_ids >= MAX_ELEMS) return 0;
@@ -1230,7 +1256,11 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   uint2* hp_eg = reinterpret_cast<uint2*>(pg);
   // (behind the 32-bit execution times, in the half of their space that the 64-bit ones would take; an even number of launches in)
   const uint64_t listed_at = (n_ids + 1) / 2 * 8;
-  const GfOrder order = scenario_order(ctrl, reinterpret_cast<unsigned char*>(pe) + listed_at + GF_PAD, n_ids * 8 - listed_at, n_scenarios);
+  // The waves' order is made where waves will walk.  The widest scenario, which decides that, is not known yet: the average one stands
+  // in for it (30,000 scenarios of one task: 557 us with lists that nobody reads, 555 without).
+  const GfOrder order = prio_by_wave((n_entries + n_scenarios - 1) / n_scenarios, n_scenarios)
+                            ? scenario_order(ctrl, reinterpret_cast<unsigned char*>(pe) + listed_at + GF_PAD, n_ids * 8 - listed_at, n_scenarios)
+                            : GfOrder{nullptr, nullptr};
 
   Tracer tr(st);
   tr.mark("pf_setup");
@@ -1265,21 +1295,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
                      d_task_offsets, d_hp_task, d_lp_offsets, d_lp_task, d_lp_prio, static_cast<uint32_t>(n_scenarios),       \
                      d_gap_offsets, lp_e, hp_eg, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,        \
                      d_lp_placed, d_lp_placed_ns, order, ctrl)
-    // One wave per scenario up to this many scenarios, beyond it a group of lanes per scenario.  The waves' time grows with
-    // the scenarios, the groups' hardly does; traces of 1024 launches, queues of 2048, waves / groups in ms for the call:
-    //   1 task   4096: 0.35 / 1.22   16,384: 0.94 / 1.42   24,576: 1.34 / 1.54
-    //   2 tasks  4096: 0.87 / 1.81   8192: 1.41 / 1.87   12,288: 1.93 / 1.96
-    //   3 tasks  64: 0.80 / 2.2   4096: 1.07 / 2.34   8192: 1.74 / 2.39   12,288: 2.41 / 2.76
-    //   4 tasks  4096: 1.42 / 2.64   12,288: 2.88 / 3.11   6 tasks  4096: 1.59 / 3.41   12,288: 3.14 / 3.99
-    //   9 tasks  4096: 1.71 / 3.75   16,384: 3.97 / 5.47   24,576: 5.51 / 7.75
-    // Shorter traces: gaps of one kernel each (512, queues of 512), of ten (256, queues of 2048), few that take any (1024):
-    //   1 task   12,288: 0.25 / 0.55, 0.58 / 0.58, 0.13 / 0.90   24,576: 0.37 / 0.58, 1.02 / 0.61, 0.18 / 0.92
-    //   2 tasks  8192: 0.29 / 0.67, 0.97 / 1.01, 0.12 / 1.15   12,288: 0.37 / 0.69, 1.31 / 1.02, 0.15 / 1.17
-    //   3 tasks  12,288: 0.42 / 0.83, 1.40 / 1.25, 0.17 / 1.45   6 tasks  12,288: 0.55 / 1.10, 1.54 / 1.56, 0.23 / 1.91
-    //   9 tasks  24,576: 1.06 / 2.18, 2.96 / 3.10, 0.49 / 3.73   16 tasks  24,576: 1.37 / 2.47, 3.25 / 3.44, 0.77 / 4.01
-    // (Ten kernels per gap are better off with the groups from 12,288 scenarios of one task and 8192 of two to five on; what
-    // gaps take is not known here, and the other shapes gain more than that one loses.)
-    const bool waves = widest <= 16 && n_scenarios <= (widest <= 1 || widest > 8 ? 24576u : 12288u);
+    const bool waves = prio_by_wave(widest, n_scenarios);
     tr.mark(waves ? "k_pf_walk_wave" : "k_pf_walk");
     if (waves && widest <= 1) FIKIT_PF_WAVE(64);
     else if (waves && widest <= 2) FIKIT_PF_WAVE(32);

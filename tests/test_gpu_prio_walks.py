@@ -60,3 +60,33 @@ def test_prio_levels_of_one_or_two_requests(n_scen, k):
     lt = rng.integers(0, len(lens), n_scen * k).astype(np.uint32)
     lq = np.concatenate([1 + rng.permutation(k) // 2 for _ in range(n_scen)]).astype(np.uint32)
     check_prio(prof, d_off, off, o_prof, hp, lo, lt, lq, 3, 5)
+
+
+@pytest.mark.parametrize("n_scen,lists,rare,walk,listed", [
+    (2048, 1, 1, "wave", False), (2049, 1, 1, "wave", True),
+    (24576, 1, 1, "wave", True), (24577, 1, 1, "lanes", False),
+    (12288, 3, 3, "wave", True), (12289, 3, 3, "lanes", False), (12289, 9, 9, "wave", True),
+    (12289, 1, 3, "lanes", True), (12289, 3, 9, "wave", False),      # the widest scenario is not like the others
+])
+def test_prio_order_is_made_where_waves_walk(n_scen, lists, rare, walk, listed):
+    """Scenarios are listed by their traces' lengths for walks that read the lists, as far as the average scenario tells."""
+    lens = [0, 1, 2, 16, 17, 24, 40] + [14_000] * 32               # (the long ones make room for the lists; nobody uses them)
+    rec, off = trace_of(n_scen, lens, [100, 250, 40], [0, 90, 900])
+    prof, d_off, o_prof = check_profile(rec, off)
+    rng = np.random.default_rng(n_scen)
+    k = np.full(n_scen, lists)
+    k[5] = rare
+    k[10:10 + rare - lists] -= 1                                    # (as many entries on average as the others have)
+    lo = np.concatenate([[0], np.cumsum(k)]).astype(np.uint64)
+    hp, lt = rng.integers(0, 7, n_scen).astype(np.uint32), rng.integers(0, 7, int(lo[-1])).astype(np.uint32)
+    lq = rng.integers(1, 10, int(lo[-1])).astype(np.uint32)
+    with kernels_of() as names:
+        got, _ = check_prio(prof, d_off, off, o_prof, hp, lo, lt, lq, 3, 5)
+    assert ("k_pf_walk_wave" in names) == (walk == "wave") and ("k_pf_walk" in names) == (walk == "lanes")
+    ws = torch.zeros(binding.fikit_prio_fill_workspace_bytes(rec.size, len(lens), n_scen), dtype=torch.uint8, device=DEV)
+    again = binding.fikit_prio_fill(prof.ids, d_off, prof.rows, prof.task_row_offsets, binding.to_device_u32(hp, DEV),
+                                    binding.to_device_u64(lo, DEV), binding.to_device_u32(lt, DEV), binding.to_device_u32(lq, DEV),
+                                    binding.to_device_u64(traces.gap_offsets(off, hp), DEV), margin_ns=3, min_gap_ns=5, workspace_buf=ws)
+    assert all(torch.equal(a, b) for a, b in zip(again, got))
+    counts = ws[:256].view(torch.int32)[20:52]                      # (behind the control block: scenarios on each list)
+    assert int(counts.sum()) == (n_scen if listed else 0)
