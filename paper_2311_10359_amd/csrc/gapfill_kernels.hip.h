@@ -16,10 +16,12 @@ namespace fikit {
 // Scenarios in the order in which the walks' waves take them, the longest traces first: buckets of half an octave of the
 // high-priority trace's length (bucket 0 the longest), in no order inside.  With several waves per SIMD, what a SIMD has to do is the
 // sum of the traces it happens to get, and the longest may start last: 6000 traces of 1 to 2800 launches needed 93 cycles of a SIMD
-// per gap, even ones 53.  The kernel that checks the scenarios fills the lists, which costs it 2 us; scenarios of one bucket are
-// taken as they are numbered.  Calls in us as numbered / longest first: gap fill of these 6000 490 / 442, of 90 x 96 ragged pairs
-// 390 / 355; replay of 3000 traces of up to 4000 launches 562 / 530; priority queues, 4096 traces of up to 1600 launches and three
-// queues each 1010 / 866; even lengths 332 / 332 (90 x 96 pairs) and 369 / 371 (16,384 scenarios).
+// per gap, even ones 53.  The kernel that checks the scenarios fills the lists, which costs it 1 to 4 us; scenarios of one bucket are
+// taken as they are numbered.  Calls in us as numbered / longest first: gap fill of these 6000 431 / 397, of 20,000 of up to 1200
+// launches 437 / 392, of 2100 of up to 1000 151 / 150; replay of 3000 traces of up to 4000 launches 491 / 463; priority queues, 4096
+// traces of up to 1600 launches and three queues each 1249 / 1088; even lengths, 2100 scenarios 117 / 119, 6000 350 / 351, 30,000 407 /
+// 411.  The longest buckets' waves at a higher priority on their SIMD: 397, 392, 150, 464 and 1079 us for the ragged ones; not worth
+// standing before other streams' waves.
 struct GfOrder {
   uint32_t* count;    // [GF_BUCKETS] scenarios of each bucket, in the words behind the control block (which k_gf_clear clears too);
                       // null: as they are numbered
@@ -667,11 +669,6 @@ __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint3
   const uint32_t longest = popc64(ballot(lane < GF_BUCKETS && upto == 0));
   if (popc64(ballot(lane < GF_BUCKETS && upto == n_scen)) + longest == GF_BUCKETS) return place;   // (one bucket holds them all)
   if (bucket >= GF_BUCKETS) return n_scen;   // (cannot happen: every scenario is on a list)
-  // the longest buckets decide when the launch ends: their instructions are issued first
-  const uint32_t behind = bucket - longest;
-  if (behind == 0) __builtin_amdgcn_s_setprio(3);
-  else if (behind == 1) __builtin_amdgcn_s_setprio(2);
-  else if (behind == 2) __builtin_amdgcn_s_setprio(1);
   const uint32_t before = bucket ? read_lane_u32(upto, bucket - 1) : 0u;
   return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(order.list[bucket * n_scen + (place - before)])));
 }
