@@ -212,18 +212,21 @@ struct Mailbox {
 };
 thread_local Mailbox t_mailbox;
 
-// Up to four reads of device words; they have arrived once wait() returns.
+// Up to MOST reads of device words; they have arrived once wait() returns.
 struct Reads {
+  static constexpr int MOST = 4;
+  static constexpr size_t place(size_t bytes) { return (bytes + 15) / 16 * 16; }
   hipStream_t st;
   unsigned char* box = t_mailbox.get();
-  struct { void* to; size_t bytes, at; } item[4];
+  struct { void* to; size_t bytes, at; } item[MOST];
   int n = 0;
   size_t used = 0;
   explicit Reads(hipStream_t s) : st(s) {}
   int add(void* to, const void* from, size_t bytes) {
+    if (n == MOST || used + place(bytes) > Mailbox::BYTES) return FIKIT_HIP_ERROR;   // (cannot happen: see below)
     item[n].to = to; item[n].bytes = bytes; item[n].at = used;
     FIKIT_HIP(hipMemcpyAsync(box ? box + used : to, from, bytes, hipMemcpyDeviceToHost, st));
-    used += (bytes + 15) / 16 * 16;
+    used += place(bytes);
     ++n;
     return FIKIT_OK;
   }
@@ -234,7 +237,8 @@ struct Reads {
     return FIKIT_OK;
   }
 };
-static_assert(sizeof(Ctrl) + 3 * 16 <= Mailbox::BYTES, "what one wait brings fits");
+static_assert(2 * Reads::place(sizeof(Ctrl)) <= Mailbox::BYTES && 3 * Reads::place(8) <= Mailbox::BYTES,
+              "what one wait brings fits: two control blocks, or three counts");
 
 int read_ctrl(const Ctrl* d_ctrl, Ctrl* h, hipStream_t st) {
   Reads r(st);
@@ -819,11 +823,12 @@ int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const u
                     const uint64_t* d_gap_offsets, uint64_t n_gaps, uint32_t* d_fill_count, int64_t* d_filled_ns,
                     int64_t* d_lp_completion_ns, uint64_t* d_lp_placed, bool set_attributes, const uint32_t* done, bool all_done, const Ctrl* prof = nullptr,
                     uint64_t row_capacity = 0) {
-  tr.mark("k_gf_predict32");
-  if (!all_done)
+  if (!all_done) {
+    tr.mark("k_gf_predict32");
     hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                        n_tasks, d_rows, d_task_row_offsets, b.role, static_cast<const int64_t*>(nullptr), b.lp_e, b.hp_eg, b.lp_total,
                        static_cast<uint32_t>(h_params->predictor), done, prof, row_capacity, b.ctrl);
+  }
   return walk_enqueue<LW_PLAN>(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps,
                                h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
                                set_attributes, prof, row_capacity);

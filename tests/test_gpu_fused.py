@@ -139,3 +139,12 @@ def test_the_fill_runs_ahead_of_the_host_only_behind_a_finished_profile(n_tasks,
                                           rows_out=torch.empty((capacity, 128), dtype=torch.uint8, device=DEV), out=out)
         assert e.value.status == status
         assert all(bool((x == 77).all()) for x in out)
+
+
+@pytest.mark.parametrize("longest,launched", [(16384, False), (16385, True)])
+def test_trace_names_the_look_ups_only_where_they_run(longest, launched):
+    """The profile's kernels write the predictions of tasks that a workgroup holds; the look-ups run for longer ones."""
+    rec, off = ragged_trace(2, [longest, 300, 160], 9)
+    with kernels_of() as names:
+        check_fused(rec, off, np.array([0, 1], dtype=np.uint32), np.array([1, 2], dtype=np.uint32), 100, 0)
+    assert ("k_gf_predict32" in names) == launched
