@@ -27,6 +27,23 @@ def kernels_of():
         binding.fikit_trace_enable(False)
 
 
+def unit_sizes(ids, off):
+    """Launches of the units that long tasks (more than 16,384 launches) are cut into: neighbouring buckets of the IDs' first byte
+    as far as they fit together, 4096 launches in tasks of up to 131,072, otherwise 8192; a larger bucket alone."""
+    sizes = []
+    for a, b in zip(off[:-1].astype(np.int64), off[1:].astype(np.int64)):
+        if b - a <= 16384:
+            continue
+        most, open_unit = 4096 if b - a <= 131072 else 8192, 0
+        for n in np.bincount((ids[a:b] >> np.uint64(56)).astype(np.int64)):
+            if open_unit and open_unit + n > most:
+                sizes.append(open_unit)
+                open_unit = 0
+            open_unit += int(n)
+        sizes.append(open_unit)
+    return np.array([s for s in sizes if s])
+
+
 def run_profile_gpu(rec, off, **kw):
     d_rec = binding.to_device_records(rec, DEV)
     d_off = binding.to_device_u64(off, DEV)

@@ -159,3 +159,49 @@ def test_task_that_a_large_unit_gives_up_while_it_is_streamed(ids, sorts):
     n = sum(k.size for k in kids)
     rec, off = trace_of(kids, np.maximum(1, np.rint(rng.lognormal(8.5, 1.5, n))).astype(np.int64), rng.integers(0, 30_000, n))
     assert sorted_with(rec, off) == sorts
+
+
+def by_turn(kid):
+    """How often each launch's kernel has been launched before it."""
+    order = np.argsort(kid, kind="stable")
+    first = np.r_[0, np.flatnonzero(np.diff(kid[order])) + 1]
+    turn = np.empty(kid.size, dtype=np.int64)
+    turn[order] = np.arange(kid.size) - np.repeat(first, np.diff(np.r_[first, kid.size]))
+    return turn
+
+
+def crowded(rng, launches, kind):
+    """A task of LONG launches whose bucket 30 holds one ID per entry of `launches`; IDs of other buckets fill it up."""
+    by = names_by_bucket()
+    others = np.concatenate([by[b][:1] for b in range(0, 256, 2) if b != 30])
+    rest = LONG + 5 - sum(launches)
+    kid = rng.permutation(np.concatenate([np.repeat(by[30][:len(launches)], launches), rng.choice(others, rest - 1)]))
+    kid = np.append(kid, others[:1])                         # (the task's last launch, which has no idle time)
+    if kind == "lognormal":
+        ex = np.maximum(1, np.rint(rng.lognormal(9 + kid % 5, 0.3 + 0.4 * (kid % 4)))).astype(np.int64)
+        return trace_of([kid], ex, ex[::-1])
+    # nearly all of an ID's values lie in one bin between its least and its largest
+    turn = by_turn(kid)
+    v = np.where(turn == 0, 10, np.where(turn == 1, 4_000_000_000, 1_000_000 + turn * 6151 % 200_000))
+    return trace_of([kid], v, v)
+
+
+@pytest.mark.parametrize("kind", ["lognormal", "clustered"])
+@pytest.mark.parametrize("launches", [
+    [40_000] + [2048, 2049, 3000, 4095, 4096, 4097, 2048, 5000, 33, 1],      # few IDs with as many bins as there can be
+    [20_000] * 12,
+    [30_000] + [33] * 255,                                                   # as many IDs as the table holds, with short lists ...
+    [30_000] + [20 + i % 44 for i in range(255)],                            # ... and with some too long for one
+    [17_000] + [300] * 255,
+])
+def test_streamed_bucket_wants_more_room_than_there_is(launches, kind):
+    """The bins that a streamed bucket's IDs want do not fit their 24,576 words; clustered, the bins of the second round do not
+    either, nor the lists of 31 samples each (255 IDs of 33 launches: 1020 lists of 32 words): the largest are cut to fit."""
+    log2_above = lambda n: int(n - 1).bit_length()
+    assert 2 * sum(1 << min(11, log2_above(n)) for n in launches) > 24576 and sum(launches) > 16384
+    rec, off = crowded(np.random.default_rng(len(launches)), launches, kind)
+    with kernels_of() as names:
+        _, _, (ids, _, _) = check_profile(rec, off)
+    assert "k_onesweep_pass" not in names, sorted(names)
+    in_30 = ids[ids >> np.uint64(56) == 30]
+    assert np.unique(in_30).size == len(launches) and in_30.size == sum(launches)

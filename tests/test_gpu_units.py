@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2311_10359_amd import traces
-from parity_util import check_profile, kernels_of
+from parity_util import check_profile, kernels_of, unit_sizes
 
 pytestmark = pytest.mark.gpu
 EDGES = [1, 2, 3, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025]
@@ -52,6 +52,8 @@ def test_ids_at_the_edges_of_groups_waves_and_shares(kind):
     recs = [task(rng, c, kind, 10_000 * i) for i, c in enumerate(counts)]
     off = np.concatenate([[0], np.cumsum([r.size for r in recs])]).astype(np.uint64)
     with kernels_of() as names:
-        check_profile(np.concatenate(recs), off)
-    assert {"k_unit_sorted_small", "k_unit_sorted_mid", "k_unit_large"} <= names, sorted(names)
+        _, _, (ids, _, _) = check_profile(np.concatenate(recs), off)
     assert "k_onesweep_pass" not in names, sorted(names)
+    sizes = unit_sizes(ids, off)                             # units of every shape there is, up to the largest
+    assert [int(((lo < sizes) & (sizes <= hi)).sum()) >= 3 for lo, hi in ((0, 4096), (4096, 8192), (8192, 16384))] == [True] * 3
+    assert 4096 in sizes and 8192 in sizes and sizes.max() <= 16384
