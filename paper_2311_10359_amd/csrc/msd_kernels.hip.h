@@ -2,7 +2,7 @@
 // every tile of a task by the top bits of the Kernel ID, and one workgroup each then works on
 // units of consecutive ID buckets, gathering each unit's launches from the tiles.  Because the ID is a
 // hash, the buckets are of similar size unless a few IDs dominate the task; a bucket larger than a
-// workgroup can hold is streamed by one (k_unit_stream) if its task is long enough, otherwise the task
+// workgroup can hold is streamed by one (k_unit_large) if its task is long enough, otherwise the task
 // keeps the general sort-based path.  In a task of more tiles than a unit's run table lists
 // (UNIT_RUNS_MAX) every bucket is streamed, however small.
 //
@@ -15,6 +15,7 @@
 //   k_msd_units       bucket sizes of a task (summed over its tiles) -> units of at most FUSE_MID_MAX
 //                     launches (FUSE_SMALL_MAX in shorter tasks; or one larger bucket)
 //   k_unit_sorted     (unit_kernels.hip.h) reads a unit's launches as one run per tile and makes its rows
+//   k_unit_large      (stream_kernels.hip.h) the same for units of more than FUSE_MID_MAX launches, and the streamed ones
 //   k_msd_task_rows / k_gather_units   row counts and final placement of the units' rows
 //   k_long_general_values   per-launch values of long tasks that had to be left to the general path
 #pragma once
@@ -27,13 +28,13 @@
 namespace fikit {
 
 // Top ID bits that name a launch's bucket.  All tasks use as many: neighbouring buckets are packed into one unit anyway, and
-// the finer the buckets, the fewer IDs share one with a frequent ID (k_unit_stream).
+// the finer the buckets, the fewer IDs share one with a frequent ID (unit_streamed).
 constexpr uint32_t MSD_BITS = 8;
 constexpr uint32_t MSD_SLOTS = 1u << MSD_BITS;       // buckets, and unit slots reserved per long task
 constexpr uint32_t PT_TILE = 4096;                   // launches per tile of the partition pass
 constexpr int PT_THREADS = 512, PT_WAVES = PT_THREADS / WAVE, PT_KPT = PT_TILE / PT_THREADS;
 constexpr int PT_LB = 2;                             // rounds of record loads in flight per lane
-// A bucket of more than FUSE_MAX launches (one frequent ID) is streamed by k_unit_stream if its task has at least this
+// A bucket of more than FUSE_MAX launches (one frequent ID) is streamed (unit_streamed) if its task has at least this
 // many launches; otherwise the task is sorted.  fikit_profile, one ID with 90 / 50 / 35 % of the launches beside 300 others, in
 // ms sorted / streamed (the line moved down for it):
 //   64 tasks of 24,000 launches: 0.53 / 0.68 (90 %), 0.51 / 0.31 (70 %)   64 of 40,000: 0.64 / 0.83, 0.73 / 0.34 (50 %)

@@ -81,18 +81,18 @@ __device__ __forceinline__ void each_sample(const uint32_t* v, uint32_t n, uint3
 
 // Histograms have two 16-bit counters to a word (an ID has at most PICK_SAMPLES samples).
 __device__ __forceinline__ void count_in(uint32_t* hist, uint32_t bin) { atomicAdd(&hist[bin >> 1], 1u << ((bin << 4) & 31u)); }
-__host__ __device__ __forceinline__ uint32_t cut_shift(uint32_t width, uint32_t bins_log2) {   // so that width >> shift is below 2^bins_log2
+__device__ __forceinline__ uint32_t cut_shift(uint32_t width, uint32_t bins_log2) {   // so that width >> shift is below 2^bins_log2
   return width >> bins_log2 ? 32u - static_cast<uint32_t>(__builtin_clz(width)) - bins_log2 : 0u;
 }
 
 // scale_of with 0 just below 1.
 constexpr uint32_t SCALE_ZERO = (0x3f800000u >> SCALE_DROP) - 1;
-__host__ __device__ __forceinline__ uint32_t pick_scale(float rounded) {
+__device__ __forceinline__ uint32_t pick_scale(float rounded) {
   return max_u32(__builtin_bit_cast(uint32_t, rounded) >> SCALE_DROP, SCALE_ZERO);
 }
 // The smallest value whose pick_scale is t or more.  From 2^24 on the values just below a step's own value round up to it: half a
 // float's spacing, which is half as wide below a power of two.
-__host__ __device__ __forceinline__ uint32_t pick_scale_low(uint32_t t) {
+__device__ __forceinline__ uint32_t pick_scale_low(uint32_t t) {
   if (t <= SCALE_ZERO) return 0u;
   const uint32_t bits = t << SCALE_DROP, e = (bits >> 23) - 127u;
   if (bits > 0x4f800000u) return NONE32;   // (beyond 2^32)
@@ -106,19 +106,19 @@ struct Window {
   static constexpr uint32_t BINS_LOG2 = GW == 32 ? 8 : 7;
   uint32_t min, max, from, shift;
   bool linear;
-  __host__ __device__ __forceinline__ Window(uint32_t min_, uint32_t max_) : min(min_), max(max_) {
+  __device__ __forceinline__ Window(uint32_t min_, uint32_t max_) : min(min_), max(max_) {
     const uint32_t scale_lo = pick_scale(static_cast<float>(min)), by_scale = pick_scale(static_cast<float>(max)) - scale_lo;
     linear = ((max - min) >> BINS_LOG2) == 0 || (by_scale >> BINS_LOG2) == 0;
     from = linear ? min : scale_lo;
     shift = cut_shift(linear ? max - min : by_scale, BINS_LOG2);
   }
-  __host__ __device__ __forceinline__ uint32_t bin(uint32_t x) const { return ((linear ? x : pick_scale(static_cast<float>(x))) - from) >> shift; }
+  __device__ __forceinline__ uint32_t bin(uint32_t x) const { return ((linear ? x : pick_scale(static_cast<float>(x))) - from) >> shift; }
   // the values of a bin that holds samples
-  __host__ __device__ __forceinline__ uint32_t low(uint32_t b) const {
+  __device__ __forceinline__ uint32_t low(uint32_t b) const {
     const uint32_t t = from + (b << shift);
     return max_u32(linear ? t : pick_scale_low(t), min);
   }
-  __host__ __device__ __forceinline__ uint32_t high(uint32_t b) const {
+  __device__ __forceinline__ uint32_t high(uint32_t b) const {
     const uint32_t t = from + ((b + 1) << shift);
     return linear ? (max - from < (b + 1) << shift ? max : t - 1) : min_u32(pick_scale_low(t) - 1, max);
   }

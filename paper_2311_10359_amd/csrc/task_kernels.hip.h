@@ -182,7 +182,7 @@ struct FusedArgs {
   int64_t* g0;
   uint64_t* key0;              // ... with their IDs, in the same order
   // units: groups of consecutive ID buckets of a long task, whose launches lie bucket-ordered inside every tile
-  const uint32_t* ustart;      // where the unit would start if the task were in bucket order (k_unit_stream packs its launches there)
+  const uint32_t* ustart;      // where the unit would start if the task were in bucket order (unit_streamed packs its launches there)
   const uint32_t* ulen;
   const uint32_t* utask;
   const uint32_t* ubuckets;    // first bucket | (bucket after the last) << 16
@@ -287,7 +287,6 @@ k_task_fused(const FusedArgs A) {
   const uint32_t lane = lane_id();
 #pragma unroll
   for (int r = 0; r < KPT; ++r) { ev[r] = 0; gv[r] = NONE32; sl[r] = 0; }
-  {
   // LB rounds of loads are issued before the first of them is used, to keep more bytes in flight
 #pragma unroll
   for (int r0 = 0; r0 < KPT; r0 += LB) {
@@ -417,7 +416,6 @@ k_task_fused(const FusedArgs A) {
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-  }
   }
   if (bad) atomicOr(&ctrl->status, ERR_BAD_RECORD);
   if (wide) atomicOr(&sm.fallback, 1u);
