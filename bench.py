@@ -38,6 +38,7 @@ ALGO_BYTES_PER_RECORD = {
     "k_onesweep_pass": 24 + 24,
     "k_unit_sorted": 16,
 }
+UNIT_KERNELS = ("k_unit_sorted_small", "k_unit_sorted_mid", "k_unit_large")   # by size of the unit; the last streams units too
 GAPFILL_KERNELS = ("k_gf_predict32", "k_gf_walk_wave", "k_gf_walk_lanes")
 
 
@@ -74,7 +75,8 @@ def stored_traffic(data, kernel):
     """HBM bytes per launch of one kernel from the stored counter readings."""
     if not data:
         return None
-    return data.get("kernels", {}).get(kernel, {}).get("hbm_bytes_per_launch")
+    parts = [data.get("kernels", {}).get(k, {}).get("hbm_bytes_per_launch") for k in (UNIT_KERNELS if kernel == "k_unit_sorted" else (kernel,))]
+    return sum(p for p in parts if p is not None) if any(p is not None for p in parts) else None
 
 
 def stored_call_traffic(data):
@@ -440,10 +442,10 @@ def main():
              # (the launches of the long tasks: right where they all take the general path, as in workload 2, the only
              # workload in which this kernel can lead)
              "k_onesweep_pass": n_long}
-    # the three launches over the units of partitioned tasks count as one kernel (the split between
-    # them depends on the data)
+    # the three launches over the units of partitioned tasks (UNIT_KERNELS) count as one kernel: the split between
+    # them depends on the data
     kernels = {k: v for k, v in trace.items() if k in ALGO_BYTES_PER_RECORD or k in GAPFILL_KERNELS}
-    unit_parts = [v for k, v in trace.items() if k.startswith("k_unit_sorted_")]
+    unit_parts = [trace[k] for k in UNIT_KERNELS if k in trace]
     if unit_parts:
         kernels["k_unit_sorted"] = (sum(v[0] for v in unit_parts), max(v[1] for v in unit_parts))
     dom = max(kernels, key=lambda k: kernels[k][0])

@@ -85,10 +85,10 @@ def per_dispatch(path: str):
 def kernel_label(name: str) -> str:
     """The name bench.py's per-kernel timing uses for a kernel (template instances of the task and unit kernels by shape)."""
     n = name.replace("fikit::", "")
-    for kernel, largest in (("k_task_fused", "medium"), ("k_unit_sorted", "large")):
+    for kernel in ("k_task_fused", "k_unit_sorted"):   # (units of the largest shape run in k_unit_large)
         if n.startswith(kernel + "<"):
             a = [x.strip() for x in n[len(kernel) + 1:].rstrip(">").split(",")]
-            shape = {("512", "8"): "small", ("512", "16"): "mid", ("1024", "16"): largest}.get((a[0], a[1]), "x".join(a[:2]))
+            shape = {("512", "8"): "small", ("512", "16"): "mid", ("1024", "16"): "medium"}.get((a[0], a[1]), "x".join(a[:2]))
             return kernel + "_" + shape
     return n.split("<")[0]
 
