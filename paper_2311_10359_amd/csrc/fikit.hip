@@ -695,12 +695,12 @@ constexpr uint64_t GF_PAD = 256;
 // lanes' time hardly depends on how many there are (to 65,536); the waves' grows with them, and with the gaps that take
 // something.  Traces of 4096 and queues of 16,384 launches: the lanes 3.3 ms, the waves 0.08 ms per 1024 scenarios once the chip
 // is full (1.18 ms against 3.2 ms at 16,384).  Calls over shorter tasks, waves / lanes in ms (gap fill; replay with feedback):
-//   1024 gaps that take about one kernel each   16,384: 0.41 / 0.52; 0.48 / 0.55   24,000: 0.52 / 0.54; 0.60 / 0.56
-//                                               32,000: 0.63 / 0.55; 0.75 / 0.56
-//   512 gaps that take about ten each           16,384: 0.55 / 1.30; 0.61 / 1.22   32,000: 0.91 / 1.32; 1.05 / 1.25
-//   2048 gaps of which few take anything        16,384: 0.20 / 0.79; 0.20 / 0.84   32,000: 0.29 / 0.81; 0.29 / 0.85
-// The line lies where the waves of the longest of these shapes stop being ahead; what gaps take is not known when it is drawn,
-// and from about 24,000 scenarios on gaps of one kernel each are better off with the lanes.
+//   1024 gaps that take about one kernel each   16,384: 0.53 / 0.71; 0.64 / 0.74   24,000: 0.74 / 0.82; 0.89 / 0.86
+//                                               32,000: 0.94 / 0.95; 1.14 / 0.99
+//   512 gaps that take about ten each           16,384: 0.58 / 1.08; 0.65 / 1.12   32,000: 1.05 / 1.33; 1.19 / 1.38
+//   2048 gaps of which few take anything        16,384: 0.39 / 1.11; 0.44 / 1.17   32,000: 0.72 / 1.58; 0.80 / 1.48
+// The line lies where the first of these shapes has the waves and the lanes level; with feedback it has from about 24,000 scenarios
+// on, but what gaps take is not known when the line is drawn.
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
 
 }  // extern "C"

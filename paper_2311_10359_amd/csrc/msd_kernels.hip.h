@@ -37,16 +37,16 @@ constexpr int PT_LB = 2;                             // rounds of record loads i
 // A bucket of more than FUSE_MAX launches (one frequent ID) is streamed (unit_streamed) if its task has at least this
 // many launches; otherwise the task is sorted.  fikit_profile, one ID with 90 / 50 / 35 % of the launches beside 300 others, in
 // ms sorted / streamed (the line moved down for it):
-//   64 tasks of 24,000 launches: 0.53 / 0.68 (90 %), 0.51 / 0.31 (70 %)   64 of 40,000: 0.64 / 0.83, 0.73 / 0.34 (50 %)
-//   64 of 65,536: 0.80 / 0.44, 0.92 / 0.40, 0.90 / 0.38   256 of 131,072: 3.86 / 1.17, 4.44 / 1.24, 4.40 / 1.15
-//   256 of 262,143: 8.03 / 2.18, 7.76 / 2.32, 7.66 / 2.14
-// Streaming is ahead from 65,536 launches on; in shorter tasks it may be tried in vain, as a unit of the other IDs holds more of
-// them than its table.  The line lies above what has been measured to lose.
+//   64 tasks of 24,000 launches: 0.53 / 0.31 (90 %), 0.53 / 0.28 (70 %)   64 of 40,000: 0.65 / 0.38, 0.76 / 0.28 (50 %)
+//   64 of 65,536: 0.82 / 0.43, 0.94 / 0.33, 0.91 / 0.31   256 of 131,072: 3.90 / 1.15, 4.53 / 1.07, 4.47 / 1.03
+//   256 of 262,143: 8.29 / 2.16, 7.91 / 2.00, 7.76 / 1.97
+// Streaming is ahead in all of these.  The line was drawn when it still lost at 24,000 and 40,000 launches, above those; in shorter
+// tasks it may also be tried in vain, as a unit of the other IDs holds more of them than its table.
 constexpr uint64_t STREAM_MIN = 1u << 18;
 // Tasks of up to this many launches are cut into units of at most FUSE_SMALL_MAX launches, longer ones (whose buckets alone may
 // be longer) of FUSE_MID_MAX.  fikit_profile, uniform over 300 IDs, in ms with the smaller / the larger units:
-//   1024 tasks of 65,536 launches: 2.62 / 2.79   1000 of 100,000: 3.03 / 3.98   50 of 131,072: 0.298 / 0.386
-//   256 of 262,144: 2.03 / 2.01   16 of 1,048,576: 0.66 / 0.63
+//   1024 tasks of 65,536 launches: 1.88 / 1.98   1000 of 100,000: 2.62 / 2.71   50 of 131,072: 0.260 / 0.288
+//   256 of 262,144: 1.92 / 1.82   16 of 1,048,576: 0.60 / 0.60
 constexpr uint64_t UNIT_SMALL_TASK = 1u << 17;
 constexpr uint32_t STREAM_HUGE = 1u << 16;           // streamed units beyond this are started first
 constexpr uint32_t PT_ROWS = MSD_SLOTS + 1;          // rows of a task's boundary table: bucket 0 .. 256 (= the tile's end)

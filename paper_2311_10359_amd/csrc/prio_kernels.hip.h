@@ -343,10 +343,14 @@ k_pf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 // goes through a level in scalars: the chain of a decision is then one lane read instead of eight steps between the two units.  It is as
 // many instructions, most of them for the scalar port, and with four waves per SIMD that loses.  Traces of 1024 launches, queues of
 // 2048, ms for the call through the lanes / in scalars:
-//   64 scenarios    2 tasks 0.63 / 0.45   3: 0.79 / 0.58   6: 1.11 / 0.75   9: 1.15 / 0.88
-//   1024 scenarios  2 tasks 0.66 / 0.48   3: 0.82 / 0.62   6: 1.33 / 0.86   9: 1.40 / 1.02
-//   4096 scenarios  2 tasks 0.86 / 0.91   3: 1.06 / 1.23   6: 1.64 / 1.52   9: 1.73 / 1.61
-// A queue that is alone: 1000 scenarios 0.25 / 0.28.
+//   64 scenarios    2 tasks 0.61 / 0.48   3: 0.83 / 0.59   6: 1.51 / 0.96   9: 1.46 / 1.09
+//   1024 scenarios  2 tasks 0.63 / 0.50   3: 0.85 / 0.62   6: 1.53 / 0.98   9: 1.48 / 1.11
+//   1536 scenarios  2 tasks 0.65 / 0.59   3: 0.88 / 0.75   6: 1.53 / 1.00   9: 1.47 / 1.12
+//   2048 scenarios  2 tasks 0.66 / 0.60   3: 0.90 / 0.77   6: 1.54 / 1.00   9: 1.48 / 1.13
+//   3072 scenarios  2 tasks 0.73 / 0.74   3: 0.96 / 0.97   6: 1.70 / 1.29   9: 1.63 / 1.43
+//   4096 scenarios  2 tasks 0.84 / 0.91   3: 1.09 / 1.18   6: 1.85 / 1.58   9: 1.75 / 1.64
+// The line is the one up to which scalars cannot lose; beyond it, to 2048 scenarios and with six tasks and more to 4096, they are
+// ahead too, which it leaves alone.  A queue that is alone goes through the lanes: 1000 scenarios 0.25 ms, in scalars 0.28.
 constexpr uint32_t PF_PAIRS_SCENARIOS = 1024;
 template <int SEG>
 __global__ void __launch_bounds__(WW_THREADS)
