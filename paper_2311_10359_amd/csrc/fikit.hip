@@ -702,6 +702,14 @@ constexpr uint64_t GF_PAD = 256;
 // The line lies where the first of these shapes has the waves and the lanes level; with feedback it has from about 24,000 scenarios
 // on, but what gaps take is not known when the line is drawn.
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
+// Up to this many scenarios of tasks of so many launches on average, a workgroup takes each: one of its waves walks, all copy what
+// repeats (256 scenarios of 65,535 gaps: a copy of 64,000 gaps takes 140,000 cycles by four waves, the call 382 us; by eight 355, by
+// sixteen 341).  A workgroup costs 2 us more to start and to end, which 64 scenarios of 1500 gaps feel (75.8 -> 78 us).
+constexpr uint64_t GF_TEAM_SCENARIOS = 1024, GF_TEAM_LAUNCHES = 8192;
+constexpr int GF_TEAM_WAVES = 8;
+// Below this average few traces are long enough for the search, and the walk without it has 54 registers instead of 67: one pair of 1000
+// launches 60.0 -> 58.8 us, 64 scenarios of 1500 and 3000 launches 79.3 -> 78.5 us; 6000 of 3100 on average gain by the search (396 -> 377).
+constexpr uint64_t GF_REPEAT_LAUNCHES = REPEAT_GAPS + REPEAT_ENTRIES;
 
 }  // extern "C"
 
@@ -791,8 +799,8 @@ void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64
 // The walk on 32-bit predictions in one of its modes; `result`: completion times, or delays in the replay modes.  prof (may be
 // null): the profile that it follows in the same call.
 template <int MODE>
-int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_task_offsets, const uint32_t* d_hp_task,
-                 const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets, uint64_t n_gaps, int64_t margin,
+int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_task_offsets, uint32_t n_tasks,
+                 const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets, uint64_t n_gaps, int64_t margin,
                  int64_t min_gap, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* result, uint64_t* d_lp_placed,
                  bool set_attributes, const Ctrl* prof, uint64_t row_capacity) {
   if (n_scenarios >= GF_LANES_MIN_SCENARIOS && n_gaps < MAX_ELEMS) {
@@ -806,9 +814,15 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
                        d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, prof, row_capacity, b.ctrl);
   } else {
     tr.mark(MODE == LW_PLAN ? "k_gf_walk_wave" : MODE == LW_REPLAY ? "k_gf_replay_wave" : "k_gf_replay_feedback_wave");
-    hipLaunchKernelGGL(k_gf_walk_wave<MODE>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st, d_task_offsets,
-                       d_hp_task, d_lp_task, static_cast<uint32_t>(n_scenarios), d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
-                       d_fill_count, d_filled_ns, result, d_lp_placed, prof, row_capacity, gapfill_order(b, n_scenarios), b.ctrl);
+    const uint64_t launches = b.n_ids / n_tasks;   // of a task on average
+    const bool teams = MODE != LW_REPLAY_FEEDBACK && n_scenarios <= GF_TEAM_SCENARIOS && launches >= GF_TEAM_LAUNCHES;
+    auto kernel = &k_gf_walk_wave<MODE, 0>;
+    if constexpr (MODE != LW_REPLAY_FEEDBACK)
+      kernel = teams ? &k_gf_walk_wave<MODE, GF_TEAM_WAVES> : launches >= GF_REPEAT_LAUNCHES ? &k_gf_walk_wave<MODE, 1> : kernel;
+    hipLaunchKernelGGL(kernel, dim3(teams ? static_cast<uint32_t>(n_scenarios) : blocks_for(n_scenarios, WW_THREADS / WAVE)),
+                       dim3(teams ? GF_TEAM_WAVES * WAVE : WW_THREADS), 0, st, d_task_offsets, d_hp_task, d_lp_task,
+                       static_cast<uint32_t>(n_scenarios), d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,
+                       d_filled_ns, result, d_lp_placed, prof, row_capacity, gapfill_order(b, n_scenarios), b.ctrl);
   }
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
@@ -829,7 +843,7 @@ int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const u
                        n_tasks, d_rows, d_task_row_offsets, b.role, static_cast<const int64_t*>(nullptr), b.lp_e, b.hp_eg, b.lp_total,
                        static_cast<uint32_t>(h_params->predictor), done, prof, row_capacity, b.ctrl);
   }
-  return walk_enqueue<LW_PLAN>(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps,
+  return walk_enqueue<LW_PLAN>(st, tr, b, d_task_offsets, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps,
                                h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
                                set_attributes, prof, row_capacity);
 }
@@ -1165,7 +1179,7 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
                      static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr),
                      static_cast<const Ctrl*>(nullptr), static_cast<uint64_t>(0), b.ctrl);
   auto walk = h_params->feedback ? walk_enqueue<LW_REPLAY_FEEDBACK> : walk_enqueue<LW_REPLAY>;
-  if (int rc = walk(st, tr, b, d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
+  if (int rc = walk(st, tr, b, d_task_offsets, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, h_params->margin_ns,
                     h_params->min_gap_ns, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, true, nullptr, 0))
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&]() -> int {

@@ -673,17 +673,146 @@ __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint3
   return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(order.list[bucket * n_scen + (place - before)])));
 }
 
-// (completion_out receives the delay in the replay modes).
-template <int MODE>
-__global__ void __launch_bounds__(WW_THREADS)
+// ---- what repeats is copied -------------------------------------------------------------------------------------------
+//
+// A service runs the same kernels pass after pass, so its predicted idle times repeat, and so do the queue's entries.  A gap's
+// result follows from the queue's next entries and the idle time alone.  If the walk stands before gap a and entry ja, stood before
+// gap a - D and entry ja - dq earlier, and from there on the idle times equal those D gaps earlier and the entries those dq entries
+// earlier, everything that follows is what followed then: a unit of D gaps issues the same dq entries again.  The walk looks for
+// such a place at multiples of the trace's period; from it on the inputs are compared, all of them, and the results copied.  No
+// step of this waits for the one before, so it runs at the rate of the memory instead of at the length of a chain.
+//
+// Traces of passes reach such a place after two to five periods as a rule: whatever the queue's first entry was, it soon stands at one
+// that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 368 (the
+// slowest wave walks 21,000 gaps), 16,384 of 4095 7740 / 7360 (the walk 1170 / 775: 1100 gaps walked, 2600 copied, and the queue's
+// 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 377.  Kernels drawn at random, which never repeat, pay for the search:
+// 7790 / 7840, 397 / 396, and 675 / 710 for the 256 long ones, whose rounds of gaps that take nothing are short.
+// The loop without the search beside the one with it (as a second copy of the code): 83 registers instead of 67, the short traces 75 ->
+// 81 us and the random ones 7790 -> 8050.
+struct Repeat {
+  uint32_t a, ja;         // the place
+  uint32_t D, dq;         // gaps and entries of a unit (the unit before the place is the one that is copied)
+  uint32_t x0;            // gaps from here on have no result yet
+  uint32_t units, X;      // units compared and copied (0: there is nothing to copy), and the gap at which they end
+};
+struct RepeatSums {
+  uint32_t c;             // entries issued
+  uint64_t used, line;    // time filled; predicted time line (replay: delay)
+  uint32_t bad_x, bad_y;  // the first gap and the first entry found to differ
+};
+constexpr uint32_t NOT_BAD = ~0u;
+constexpr int REPEAT_BLOCKS = 2;   // blocks of 64 gaps and of 256 entries per stripe (four: 30 registers more, no faster)
+
+// Four entries of a queue, which starts anywhere.
+struct __attribute__((packed, aligned(4))) FourEntries { uint32_t e[4]; };
+
+// One of `parts` waves: its share of the units, in stripes of BLOCKS times 64 gaps and 256 entries.  The sums are the lane's own.
+template <int MODE, int BLOCKS>
+__device__ __forceinline__ RepeatSums repeat_part(const Repeat& r, uint32_t part, uint32_t parts, uint32_t H, const uint2* __restrict__ trace,
+                                                  const uint32_t* __restrict__ queue, uint32_t* fill_count, int64_t* filled_ns) {
+  RepeatSums sum{0, 0, 0, NOT_BAD, NOT_BAD};
+  const uint32_t lane = lane_id();
+  const uint32_t end = r.X + 1 == H ? H : r.X;   // (the trace's last launch has no gap, but its time counts)
+  // (of what lies before x0 only the idle times are compared)
+  const uint32_t stride = 64 * BLOCKS * parts, step = stride % r.D;
+  uint32_t at[BLOCKS];                           // place in the unit
+#pragma unroll
+  for (uint32_t k = 0; k < BLOCKS; ++k) at[k] = (64 * (BLOCKS * part + k) + lane) % r.D;
+  const uint2* __restrict__ unit = trace + (r.a - r.D);
+  const uint32_t* unit_c = fill_count + (r.a - r.D);
+  const int64_t* unit_f = filled_ns + (r.a - r.D);
+  for (uint32_t x1 = r.a + 64 * BLOCKS * part; x1 < end; x1 += stride) {
+    uint2 t[BLOCKS];
+    uint32_t g[BLOCKS], c[BLOCKS], f[BLOCKS];
+#pragma unroll
+    for (uint32_t k = 0; k < BLOCKS; ++k) {
+      t[k] = trace[min_u32(x1 + 64 * k + lane, H - 1)];
+      g[k] = unit[at[k]].y;
+      c[k] = unit_c[at[k]];
+      f[k] = static_cast<uint32_t>(unit_f[at[k]]);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < BLOCKS; ++k) {
+      const uint32_t x = x1 + 64 * k + lane;
+      const bool gap = x < r.X, open = x >= r.x0;
+      if (gap && t[k].y != g[k]) sum.bad_x = min_u32(sum.bad_x, x);
+      if (gap && open) {
+        fill_count[x] = c[k];
+        filled_ns[x] = f[k];
+        sum.c += c[k];
+        sum.used += f[k];
+      }
+      if (MODE == LW_PLAN) {
+        sum.line += (open && x < end ? static_cast<uint64_t>(t[k].x) : 0ull) + (open && gap ? static_cast<uint64_t>(t[k].y) : 0ull);
+      } else {
+        sum.line += open && gap && f[k] > t[k].x ? f[k] - t[k].x : 0u;
+      }
+      at[k] += step;
+      at[k] -= at[k] >= r.D ? r.D : 0u;
+    }
+  }
+  if (r.dq == 0) return sum;
+  // (the entry behind the last unit's belongs to it too: it is the one that no longer fits)
+  const uint32_t last = r.ja + r.units * r.dq;
+  for (uint32_t y1 = r.ja + 256 * BLOCKS * part; y1 <= last; y1 += 4 * stride) {
+    FourEntries now[BLOCKS], then[BLOCKS];
+    uint32_t from[BLOCKS];
+#pragma unroll
+    for (uint32_t k = 0; k < BLOCKS; ++k) {
+      from[k] = min_u32(y1 + 256 * k + 4 * lane, last);   // (up to three entries behind it are read, and their place is in the workspace)
+      now[k] = *reinterpret_cast<const FourEntries*>(queue + from[k]);
+      then[k] = *reinterpret_cast<const FourEntries*>(queue + (from[k] - r.dq));
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < BLOCKS; ++k)
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e)
+        if (from[k] + e <= last && now[k].e[e] != then[k].e[e]) sum.bad_y = min_u32(sum.bad_y, from[k] + e);
+  }
+  return sum;
+}
+// How many units hold, by the first places that differ (the first entry behind a unit belongs to that unit too).
+__device__ __forceinline__ uint32_t units_that_hold(const Repeat& r, uint32_t bad_x, uint32_t bad_y) {
+  uint32_t units = r.units;
+  if (bad_x != NOT_BAD) units = min_u32(units, (bad_x - r.a) / r.D);
+  if (bad_y != NOT_BAD) units = min_u32(units, bad_y > r.ja ? (bad_y - r.ja - 1) / r.dq : 0u);
+  return units;
+}
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {   // (v is the same in all lanes: kept in a scalar register)
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+}
+__device__ __forceinline__ uint32_t wave_total_u32(uint32_t v) { return read_lane_u32(wave_incl_scan_u32(v), WAVE - 1); }
+
+// Where it is worth the search.  The search costs a wave 1 to 2 us until there is a period and 0.4 us a note; 64 traces of 1500 gaps
+// (a call of 75 us) gain nothing by it, 6000 of up to 2800 gaps 393 -> 367 us.  A queue of a few passes is soon used up, or hardly moves.
+constexpr uint32_t REPEAT_GAPS = 2048, REPEAT_ENTRIES = 1024;
+// A wave by itself copies a gap in 9 to 16 cycles and walks one that takes nothing in 5, one that takes something in 100 and more: a unit
+// is copied if at least every eighth of its gaps takes something (three traces of 12,192 gaps whose queue hardly moves, all copied
+// 181 us, walked 157).  Eight waves copy one in 2 cycles, and copy whatever repeats.
+constexpr uint32_t REPEAT_WORTH = 8;
+constexpr uint32_t REPEAT_LEAST = 128;     // a shorter period counts as a multiple of it, so that a round has few places to look at
+constexpr uint32_t REPEAT_NOTES = 32;      // places noted; the period is doubled at every eighth, so that they reach over 120 periods
+constexpr uint32_t REPEAT_MISSES = 4;      // starts of a period, and repeats, that may turn out to be none
+// Gaps from a start without a period after which another start is looked for, and how often; then the search ends.  What comes before
+// the first pass may be 2048 launches long, and a pass 4096.
+constexpr uint32_t REPEAT_ANCHOR = 2048, REPEAT_ANCHORS = 2;
+
+// (completion_out receives the delay in the replay modes).  TEAM waves per scenario, of which the first walks and all copy what
+// repeats; 0: one wave, and nothing is looked for.
+template <int MODE, int TEAM>
+__global__ void __launch_bounds__(TEAM <= 1 ? WW_THREADS : TEAM * WAVE)
 k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
                uint32_t n_scen, const uint64_t* __restrict__ gap_off, const uint32_t* __restrict__ lp_e,
                const uint2* __restrict__ hp_eg, const uint64_t* __restrict__ lp_total, int64_t margin, int64_t min_gap,
-               uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
+               uint32_t* fill_count, int64_t* filled_ns, int64_t* __restrict__ completion_out,
                uint64_t* __restrict__ placed_out, const Ctrl* prof, uint64_t row_capacity, const GfOrder order, const Ctrl* ctrl) {
+  // (with feedback the decisions follow the idle times that occurred, which do not repeat)
+  constexpr bool REPEATS = TEAM > 0;
+  static_assert(!REPEATS || MODE != LW_REPLAY_FEEDBACK, "decisions that do not repeat");
   if (ctrl->status || ctrl->wide || !may_follow(prof, row_capacity)) return;
   const uint32_t lane = lane_id();
-  const uint32_t s = scenario_of_wave(order, n_scen);
+  const uint32_t wave = TEAM <= 1 ? 0u : static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x / WAVE)));
+  const uint32_t s = TEAM <= 1 ? scenario_of_wave(order, n_scen) : blockIdx.x;
   if (s >= n_scen) return;
   const uint32_t hp = hp_task[s], lp = lp_task[s];
   const uint32_t h0 = static_cast<uint32_t>(off[hp]), H = static_cast<uint32_t>(off[hp + 1]) - h0;
@@ -714,18 +843,31 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   };
   bool done = L == 0;    // the whole queue has been issued
   uint32_t f_last = 0;   // time filled in the gap that took the last of it
-  if (!done) { load_window(0); sum = read_lane_u32(win, 0); }
+  if (!done && wave == 0) { load_window(0); sum = read_lane_u32(win, 0); }
 
   uint64_t time_line = 0, consumed = 0, delay = 0;   // (per lane; summed over the lanes at the end)
+  // The search for what repeats.  Two idle times in a row that equal those at the anchor may be the start of the next pass, and are
+  // if 64 are equal.  From then on the wave notes, once a period, where the queue stands and what it holds there (a lane per note:
+  // the gap, the entry, a sum over the next 64 entries).
+  uint32_t misses = n_gaps < REPEAT_GAPS || L < REPEAT_ENTRIES ? REPEAT_MISSES : 0u;
+  uint32_t period = 0, next_place = 0, notes = 0, note_i = 0, note_j = 0, note_sum = 0;
+  uint32_t anchor = 0;   // (what is needed until there is a period is kept in lanes too: scalar registers are few)
+  enum : uint32_t { A_GAP, A_ENTRY, A_G0, A_G1, A_NEXT, A_COUNT };
+  auto anchor_of = [&](uint32_t what) { return read_lane_u32(anchor, what); };
+  auto sum_of = [&](uint32_t e) { return wave_total_u32(e * ((2 * lane + 1) * 0x9e3779b1u)); };
+
+  uint32_t i0 = 0;
+  for (;;) {
+  Repeat rep{0, 0, 0, 0, 0, 0, 0};
+  if (wave == 0) {
   // (launches are read without a branch too, so that what is in flight can be counted: the lane behind the trace's end
   // reads its last launch again, and nothing of it is used)
   uint2 ahead[WW_BLOCKS];
 #pragma unroll
-  for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(64 * j + lane, H - 1)] : make_uint2(0, 0);
+  for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(i0 + 64 * j + lane, H - 1)] : make_uint2(0, 0);
 #pragma unroll
   for (uint32_t j = 0; j < WW_BLOCKS; ++j) asm volatile("" : "+v"(ahead[j].x), "+v"(ahead[j].y));   // (the loop starts with nothing in flight)
-  uint32_t i0 = 0;
-  for (; i0 < H && !done; i0 += 64 * WW_BLOCKS) {
+  while (i0 < H && !done) {
     uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
 #pragma unroll
     for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
@@ -741,6 +883,41 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
     const bounded out_c = bounded_at(fill_count + g0 + i0, 4 * gaps_here), out_f = bounded_at(filled_ns + g0 + i0, 8 * gaps_here);
 #pragma unroll
     for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
+    const bool looking = REPEATS && misses < REPEAT_MISSES && n_gaps > i0 + 64 * WW_BLOCKS;   // (what lies behind the round can be copied)
+    uint32_t found = 0;   // where the next pass may start (what has to be compared is read now and looked at behind the round)
+    uint32_t pass0 = 0, pass1 = 0, anchor_q = 0;
+    if (looking && !period) {
+      if (i0 >= anchor_of(A_NEXT)) {
+        const uint32_t n = anchor_of(A_COUNT);
+        anchor = write_lane_u32(anchor, i0, A_GAP);
+        anchor = write_lane_u32(anchor, wb + o, A_ENTRY);
+        anchor = write_lane_u32(anchor, read_lane_u32(G[0], 0), A_G0);
+        anchor = write_lane_u32(anchor, read_lane_u32(G[0], 1), A_G1);
+        anchor = write_lane_u32(anchor, n + 1 < REPEAT_ANCHORS ? i0 + REPEAT_ANCHOR : i0 + 2 * REPEAT_ANCHOR, A_NEXT);
+        anchor = write_lane_u32(anchor, n + 1, A_COUNT);
+        if (n == REPEAT_ANCHORS) misses = REPEAT_MISSES;
+      }
+      const uint32_t from = anchor_of(A_GAP), g0 = anchor_of(A_G0), g1 = anchor_of(A_G1);
+      uint64_t alike[WW_BLOCKS], any = 0;
+#pragma unroll
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+        alike[j] = ballot(G[j] == g0) & ~(j == 0 && i0 == from ? 1ull | 1ull << 63 : 1ull << 63);
+        any |= alike[j];
+      }
+      if (any) {
+#pragma unroll
+        for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+          alike[j] &= ballot(from_next_lane(G[j]) == g1);
+          if (!found && alike[j]) found = i0 + 64 * j + static_cast<uint32_t>(__builtin_ctzll(alike[j]));
+        }
+        if (found) {
+          pass0 = trace[from + lane].y;
+          pass1 = trace[min_u32(found + lane, H - 1)].y;
+          anchor_q = entry(anchor_of(A_ENTRY) + lane);
+        }
+      }
+    }
+    uint32_t count[WW_BLOCKS];
 #pragma unroll
     for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
       const uint32_t i = i0 + 64 * j + lane;
@@ -838,8 +1015,112 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
       }
       store_below(out_c, 256u * j + 4u * lane, my_c);
       store_below(out_f, 512u * j + 8u * lane, my_f, 0u);
+      count[j] = my_c;
+    }
+    const uint32_t first = i0;
+    i0 += 64 * WW_BLOCKS;
+    if (looking && !done) {
+      if (found) {
+        if (ballot(found + lane < H && pass0 == pass1) == ~0ull) {
+          const uint32_t from = anchor_of(A_GAP);
+          note_i = from; note_j = anchor_of(A_ENTRY); note_sum = sum_of(anchor_q); notes = 1;
+          period = found - from;
+          if (period < REPEAT_LEAST) period *= (REPEAT_LEAST + period - 1) / period;
+          next_place = from + period;   // (not before this round: a pass that starts in it is found in it)
+        } else {
+          ++misses;
+        }
+      }
+      if (period && next_place <= i0) {
+        while (next_place + period <= i0) next_place += period;
+        uint32_t behind = 0;   // entries issued from the place on
+#pragma unroll
+        for (uint32_t j = 0; j < WW_BLOCKS; ++j) behind += first + 64 * j + lane >= next_place ? count[j] : 0u;
+        const uint32_t here_j = wb + o - wave_total_u32(behind), here_sum = sum_of(entry(here_j + lane));
+        const uint64_t alike = ballot(lane < notes && note_sum == here_sum);
+        if (alike) {
+          const uint32_t n = 63u - static_cast<uint32_t>(__builtin_clzll(alike));
+          rep.a = next_place; rep.ja = here_j;
+          rep.D = rep.a - read_lane_u32(note_i, n); rep.dq = rep.ja - read_lane_u32(note_j, n);
+          rep.x0 = i0;
+          const uint32_t wanted = (n_gaps - rep.a + rep.D - 1) / rep.D;
+          const uint32_t there = rep.dq ? (L - 1 - rep.ja) / rep.dq : wanted;   // (units whose entries lie in the queue, with the one behind)
+          rep.units = min_u32(wanted, there);
+          rep.X = rep.units == wanted ? n_gaps : rep.a + rep.units * rep.D;
+          if (rep.X <= rep.x0) rep.units = 0;
+          if (there == 0) misses = REPEAT_MISSES;   // (the queue ends first)
+          if (TEAM == 1 && rep.dq < rep.D / REPEAT_WORTH) { rep.units = 0; misses = REPEAT_MISSES; }
+        }
+        const uint32_t n = notes;
+        note_i = write_lane_u32(note_i, next_place, n);
+        note_j = write_lane_u32(note_j, here_j, n);
+        note_sum = write_lane_u32(note_sum, here_sum, n);
+        ++notes;
+        period <<= (notes & 7) == 0 ? 1 : 0;     // (what comes back after c periods comes back after 2 c)
+        misses = notes == REPEAT_NOTES ? REPEAT_MISSES : misses;
+        next_place += period;
+        if (rep.units) break;
+      }
     }
   }
+  }
+  if (!REPEATS) break;
+  __shared__ struct { Repeat rep; RepeatSums sum; } team;
+  if (TEAM > 1) {
+    if (threadIdx.x == 0) team.rep = rep;
+    __syncthreads();
+    rep = team.rep;
+    rep = Repeat{uniform(rep.a), uniform(rep.ja), uniform(rep.D), uniform(rep.dq), uniform(rep.x0), uniform(rep.units), uniform(rep.X)};
+  }
+  if (!rep.units) break;
+  uint32_t queue_at = wb + o;   // (the window is read again behind the copy: it needs the registers)
+  for (;;) {
+    if (TEAM > 1) {
+      if (threadIdx.x == 0) team.sum = RepeatSums{0, 0, 0, NOT_BAD, NOT_BAD};
+      __syncthreads();
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // (the unit that is copied has been stored by the walk)
+    RepeatSums part = repeat_part<MODE, REPEAT_BLOCKS>(rep, wave, TEAM, H, trace, queue, fill_count + g0, filled_ns + g0);
+    if (TEAM > 1) {
+      if (part.bad_x != NOT_BAD) atomicMin(&team.sum.bad_x, part.bad_x);
+      if (part.bad_y != NOT_BAD) atomicMin(&team.sum.bad_y, part.bad_y);
+      part.c = wave_total_u32(part.c);
+      if (lane == 0) atomicAdd(&team.sum.c, part.c);
+      if (wave != 0) {
+        part.used = wave_sum_u64(part.used); part.line = wave_sum_u64(part.line);
+        if (lane == 0) {
+          atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.used), static_cast<unsigned long long>(part.used));
+          atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.line), static_cast<unsigned long long>(part.line));
+        }
+      }
+      __syncthreads();
+      part.bad_x = uniform(team.sum.bad_x); part.bad_y = uniform(team.sum.bad_y); part.c = uniform(team.sum.c);
+      if (wave == 0 && lane == 0) { part.used += team.sum.used; part.line += team.sum.line; }
+      __syncthreads();
+    } else {
+      part.bad_x = ballot(part.bad_x != NOT_BAD) ? uniform(wave_min_u32(part.bad_x)) : NOT_BAD;
+      part.bad_y = ballot(part.bad_y != NOT_BAD) ? uniform(wave_min_u32(part.bad_y)) : NOT_BAD;
+      part.c = wave_total_u32(part.c);
+    }
+    const uint32_t hold = units_that_hold(rep, part.bad_x, part.bad_y);
+    if (hold == rep.units) {
+      if (MODE == LW_PLAN) time_line += part.line; else delay += part.line;
+      consumed += part.used;
+      i0 = rep.X;
+      next_place = rep.X + period;
+      queue_at = rep.X == n_gaps ? queue_at + part.c : rep.ja + rep.units * rep.dq;
+      break;
+    }
+    // something differs: what holds is copied once more, for the sums; the walk goes on behind it and looks for another period
+    ++misses; period = 0; anchor = 0;
+    rep.units = hold;
+    rep.X = rep.a + hold * rep.D;
+    if (rep.X <= rep.x0) break;
+  }
+  if (i0 == n_gaps) { wb = queue_at; o = 0; break; }   // (the last launch's time has been added too)
+  if (wave == 0) { load_window(queue_at); sum = read_lane_u32(win, 0); }
+  }
+  if (wave != 0) return;
   for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queue ran empty)
     fill_count[g0 + i] = 0;
     filled_ns[g0 + i] = 0;
