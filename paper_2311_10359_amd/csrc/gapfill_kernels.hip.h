@@ -683,7 +683,7 @@ __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint3
 // step of this waits for the one before, so it runs at the rate of the memory instead of at the length of a chain.
 //
 // Traces of passes reach such a place after two to five periods as a rule: whatever the queue's first entry was, it soon stands at one
-// that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 368 (the
+// that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 345 (the
 // slowest wave walks 21,000 gaps), 16,384 of 4095 7740 / 7360 (the walk 1170 / 775: 1100 gaps walked, 2600 copied, and the queue's
 // 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 377.  Kernels drawn at random, which never repeat, pay for the search:
 // 7790 / 7840, 397 / 396, and 675 / 710 for the 256 long ones, whose rounds of gaps that take nothing are short.
@@ -791,7 +791,7 @@ constexpr uint32_t REPEAT_GAPS = 2048, REPEAT_ENTRIES = 1024;
 // 181 us, walked 157).  Eight waves copy one in 2 cycles, and copy whatever repeats.
 constexpr uint32_t REPEAT_WORTH = 8;
 constexpr uint32_t REPEAT_LEAST = 128;     // a shorter period counts as a multiple of it, so that a round has few places to look at
-constexpr uint32_t REPEAT_NOTES = 32;      // places noted; the period is doubled at every eighth, so that they reach over 120 periods
+constexpr uint32_t REPEAT_NOTES = 48;      // places noted; the period is doubled at every 16th (at every eighth: 256 long traces 345 -> 367 us)
 constexpr uint32_t REPEAT_MISSES = 4;      // starts of a period, and repeats, that may turn out to be none
 // Gaps from a start without a period after which another start is looked for, and how often; then the search ends.  What comes before
 // the first pass may be 2048 launches long, and a pass 4096.
@@ -1056,7 +1056,7 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
         note_j = write_lane_u32(note_j, here_j, n);
         note_sum = write_lane_u32(note_sum, here_sum, n);
         ++notes;
-        period <<= (notes & 7) == 0 ? 1 : 0;     // (what comes back after c periods comes back after 2 c)
+        period <<= (notes & 15) == 0 ? 1 : 0;     // (what comes back after c periods comes back after 2 c)
         misses = notes == REPEAT_NOTES ? REPEAT_MISSES : misses;
         next_place += period;
         if (rep.units) break;
