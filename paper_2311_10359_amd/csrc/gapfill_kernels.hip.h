@@ -750,6 +750,7 @@ __device__ __forceinline__ RepeatSums repeat_part(const Repeat& r, uint32_t part
       at[k] += step;
       at[k] -= at[k] >= r.D ? r.D : 0u;
     }
+    if (ballot(sum.bad_x != NOT_BAD)) return sum;   // (the sums are of no use, and what comes behind is looked at again)
   }
   if (r.dq == 0) return sum;
   // (the entry behind the last unit's belongs to it too: it is the one that no longer fits)
@@ -768,6 +769,7 @@ __device__ __forceinline__ RepeatSums repeat_part(const Repeat& r, uint32_t part
 #pragma unroll
       for (uint32_t e = 0; e < 4; ++e)
         if (from[k] + e <= last && now[k].e[e] != then[k].e[e]) sum.bad_y = min_u32(sum.bad_y, from[k] + e);
+    if (ballot(sum.bad_y != NOT_BAD)) return sum;
   }
   return sum;
 }
@@ -792,7 +794,7 @@ constexpr uint32_t REPEAT_GAPS = 2048, REPEAT_ENTRIES = 1024;
 constexpr uint32_t REPEAT_WORTH = 8;
 constexpr uint32_t REPEAT_LEAST = 128;     // a shorter period counts as a multiple of it, so that a round has few places to look at
 constexpr uint32_t REPEAT_NOTES = 48;      // places noted; the period is doubled at every 16th (at every eighth: 256 long traces 345 -> 367 us)
-constexpr uint32_t REPEAT_MISSES = 4;      // starts of a period, and repeats, that may turn out to be none
+constexpr uint32_t REPEAT_MISSES = 4;      // starts of a period (counted once) and repeats (twice) that may turn out to be none
 // Gaps from a start without a period after which another start is looked for, and how often; then the search ends.  What comes before
 // the first pass may be 2048 launches long, and a pass 4096.
 constexpr uint32_t REPEAT_ANCHOR = 2048, REPEAT_ANCHORS = 2;
@@ -1057,7 +1059,7 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
         note_sum = write_lane_u32(note_sum, here_sum, n);
         ++notes;
         period <<= (notes & 15) == 0 ? 1 : 0;     // (what comes back after c periods comes back after 2 c)
-        misses = notes == REPEAT_NOTES ? REPEAT_MISSES : misses;
+        misses = notes >= REPEAT_NOTES ? REPEAT_MISSES : misses;
         next_place += period;
         if (rep.units) break;
       }
@@ -1112,7 +1114,7 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
       break;
     }
     // something differs: what holds is copied once more, for the sums; the walk goes on behind it and looks for another period
-    ++misses; period = 0; anchor = 0;
+    misses += 2; period = 0; anchor = 0;
     rep.units = hold;
     rep.X = rep.a + hold * rep.D;
     if (rep.X <= rep.x0) break;
