@@ -657,6 +657,13 @@ __device__ __forceinline__ uint32_t write_lane_u32(uint32_t v, uint32_t value, u
 }
 __device__ __forceinline__ uint32_t sat32(uint64_t v) { return v > WIDE32 ? WIDE32 : static_cast<uint32_t>(v); }
 
+// Before the loop over the gaps that take something: it is 116 to 148 bytes long and runs as one wave's chain, so that it matters where
+// the instructions lie in the 32 bytes that are fetched at a time.  From the middle of such a piece on is the best place in all of its
+// forms; where the compiler happens to put it costs up to 7 %.  Gap fills in us, 256 scenarios of 65,535 gaps that never repeat, for
+// starts at byte 0, 4, 8, 12, 16, 20, 24: by a wave 1532, 1564, 1473, 1489, 1466, 1487, 1558; by eight 1560, 1579, 1502, 1491, 1500, 1524, 1584.
+// (The instructions that fill the piece are run once per block of 64 gaps.)
+__device__ __forceinline__ void place_loop() { asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0"); }
+
 // The wave's scenario: its own number, or what order holds at that place.  (Everything that is the same in the whole wave is kept in
 // scalar registers: the scenario number has to be seen as one.)
 __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint32_t n_scen) {
@@ -685,10 +692,10 @@ __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint3
 // Traces of passes reach such a place after two to five periods as a rule: whatever the queue's first entry was, it soon stands at one
 // that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 345 (the
 // slowest wave walks 21,000 gaps), 16,384 of 4095 7740 / 7360 (the walk 1170 / 775: 1100 gaps walked, 2600 copied, and the queue's
-// 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 377.  Kernels drawn at random, which never repeat, pay for the search:
-// 7790 / 7840, 397 / 396, and 675 / 710 for the 256 long ones, whose rounds of gaps that take nothing are short.
-// The loop without the search beside the one with it (as a second copy of the code): 83 registers instead of 67, the short traces 75 ->
-// 81 us and the random ones 7790 -> 8050.
+// 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 377.  Kernels drawn at random never repeat and pay for the search:
+// about 0.3 us a round while it lasts (24 rounds as a rule), then one comparison a round.
+// The rounds without the search as a second copy of the code: 82 to 86 registers instead of 67 to 71, and both copies' loops are compiled
+// worse (256 traces of 65,535 gaps that never repeat 1518 -> 1648 us, the step of 16,384 7760 -> 7960).
 struct Repeat {
   uint32_t a, ja;         // the place
   uint32_t D, dq;         // gaps and entries of a unit (the unit before the place is the one that is copied)
@@ -799,6 +806,114 @@ constexpr uint32_t REPEAT_MISSES = 4;      // starts of a period (counted once) 
 // the first pass may be 2048 launches long, and a pass 4096.
 constexpr uint32_t REPEAT_ANCHOR = 2048, REPEAT_ANCHORS = 2;
 
+// The search, by the wave that walks.  Two idle times in a row that equal those at the anchor may be the start of the next pass, and are
+// if 64 are equal.  From then on the wave notes, once a period, where the queue stands and what it holds there (a lane per note:
+// the gap, the entry, a sum over the next 64 entries).
+struct RepeatSearch {
+  // Rounds that start before this gap are looked at; 0: the search is over.  (One comparison per round is what a trace pays that never
+  // repeats, or that is too short.)
+  uint32_t until;
+  uint32_t misses = 0;
+  uint32_t period = 0, next_place = 0, notes = 0, note_i = 0, note_j = 0, note_sum = 0;
+  uint32_t anchor = 0;                                   // (what is needed until there is a period is kept in lanes too: scalar registers are few)
+  // Where a round's gaps may be the start of the next pass (0: nowhere), and what has to be compared for it.
+  struct Start { uint32_t at, pass0, pass1, anchor_q; };
+
+  enum : uint32_t { A_GAP, A_ENTRY, A_G0, A_G1, A_NEXT, A_COUNT };
+  __device__ __forceinline__ uint32_t anchor_of(uint32_t what) const { return read_lane_u32(anchor, what); }
+  __device__ __forceinline__ static uint32_t sum_of(uint32_t e) { return wave_total_u32(e * ((2 * lane_id() + 1) * 0x9e3779b1u)); }
+
+  __device__ __forceinline__ void miss(uint32_t times) {
+    misses += times;
+    until = misses >= REPEAT_MISSES ? 0u : until;
+  }
+
+  // The round's idle times (G) are at hand, its gaps not walked yet: what has to be compared is read now and looked at behind the round.
+  template <typename Entry>
+  __device__ __forceinline__ Start look(uint32_t i0, uint32_t queue_at, uint32_t H, const uint2* __restrict__ trace,
+                                        const uint32_t (&G)[WW_BLOCKS], Entry entry) {
+    Start start{0, 0, 0, 0};
+    if (period) return start;
+    if (i0 >= anchor_of(A_NEXT)) {
+      const uint32_t n = anchor_of(A_COUNT);
+      anchor = write_lane_u32(anchor, i0, A_GAP);
+      anchor = write_lane_u32(anchor, queue_at, A_ENTRY);
+      anchor = write_lane_u32(anchor, read_lane_u32(G[0], 0), A_G0);
+      anchor = write_lane_u32(anchor, read_lane_u32(G[0], 1), A_G1);
+      anchor = write_lane_u32(anchor, n + 1 < REPEAT_ANCHORS ? i0 + REPEAT_ANCHOR : i0 + 2 * REPEAT_ANCHOR, A_NEXT);
+      anchor = write_lane_u32(anchor, n + 1, A_COUNT);
+      if (n == REPEAT_ANCHORS) { until = 0; return start; }
+    }
+    const uint32_t from = anchor_of(A_GAP), g0 = anchor_of(A_G0), g1 = anchor_of(A_G1);
+    uint64_t alike[WW_BLOCKS], any = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+      // (two ballots: lanes are read from their neighbours, so all have to take part)
+      alike[j] = ballot(G[j] == g0) & ballot(from_next_lane(G[j]) == g1) & ~(j == 0 && i0 == from ? 1ull | 1ull << 63 : 1ull << 63);
+      any |= alike[j];
+    }
+    if (any) {
+#pragma unroll
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j)
+        if (!start.at && alike[j]) start.at = i0 + 64 * j + static_cast<uint32_t>(__builtin_ctzll(alike[j]));
+      const uint32_t lane = lane_id();
+      start.pass0 = trace[from + lane].y;
+      start.pass1 = trace[min_u32(start.at + lane, H - 1)].y;
+      start.anchor_q = entry(anchor_of(A_ENTRY) + lane);
+    }
+    return start;
+  }
+
+  // Behind the round that started at gap `first`: count: entries that its gaps took, queue_at: where the queue stands.  Returns what can
+  // be compared and copied (units == 0: nothing).
+  template <int TEAM, typename Entry>
+  __device__ __forceinline__ Repeat note(const Start& start, uint32_t first, uint32_t queue_at, uint32_t H, uint32_t L, uint32_t n_gaps,
+                                         const uint32_t (&count)[WW_BLOCKS], Entry entry) {
+    Repeat rep{0, 0, 0, 0, 0, 0, 0};
+    const uint32_t lane = lane_id(), end = first + 64 * WW_BLOCKS;
+    if (start.at) {
+      if (ballot(start.at + lane < H && start.pass0 == start.pass1) == ~0ull) {
+        const uint32_t from = anchor_of(A_GAP);
+        note_i = from; note_j = anchor_of(A_ENTRY); note_sum = sum_of(start.anchor_q); notes = 1;
+        period = start.at - from;
+        if (period < REPEAT_LEAST) period *= (REPEAT_LEAST + period - 1) / period;
+        next_place = from + period;   // (not before this round: a pass that starts in it is found in it)
+      } else {
+        miss(1);
+      }
+    }
+    if (!period || next_place > end) return rep;
+    while (next_place + period <= end) next_place += period;
+    uint32_t behind = 0;   // entries issued from the place on
+#pragma unroll
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) behind += first + 64 * j + lane >= next_place ? count[j] : 0u;
+    const uint32_t here_j = queue_at - wave_total_u32(behind), here_sum = sum_of(entry(here_j + lane));
+    const uint64_t alike = ballot(lane < notes && note_sum == here_sum);
+    if (alike) {
+      const uint32_t n = 63u - static_cast<uint32_t>(__builtin_clzll(alike));
+      rep.a = next_place; rep.ja = here_j;
+      rep.D = rep.a - read_lane_u32(note_i, n); rep.dq = rep.ja - read_lane_u32(note_j, n);
+      rep.x0 = end;
+      const uint32_t wanted = (n_gaps - rep.a + rep.D - 1) / rep.D;
+      const uint32_t there = rep.dq ? (L - 1 - rep.ja) / rep.dq : wanted;   // (units whose entries lie in the queue, with the one behind)
+      rep.units = min_u32(wanted, there);
+      rep.X = rep.units == wanted ? n_gaps : rep.a + rep.units * rep.D;
+      if (rep.X <= rep.x0) rep.units = 0;
+      if (there == 0) until = 0;   // (the queue ends first)
+      if (TEAM == 1 && rep.dq < rep.D / REPEAT_WORTH) { rep.units = 0; until = 0; }
+    }
+    const uint32_t n = notes;
+    note_i = write_lane_u32(note_i, next_place, n);
+    note_j = write_lane_u32(note_j, here_j, n);
+    note_sum = write_lane_u32(note_sum, here_sum, n);
+    ++notes;
+    period <<= (notes & 15) == 0 ? 1 : 0;     // (what comes back after c periods comes back after 2 c)
+    until = notes >= REPEAT_NOTES ? 0u : until;
+    next_place += period;
+    return rep;
+  }
+};
+
 // (completion_out receives the delay in the replay modes).  TEAM waves per scenario, of which the first walks and all copy what
 // repeats; 0: one wave, and nothing is looked for.
 template <int MODE, int TEAM>
@@ -848,279 +963,205 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   if (!done && wave == 0) { load_window(0); sum = read_lane_u32(win, 0); }
 
   uint64_t time_line = 0, consumed = 0, delay = 0;   // (per lane; summed over the lanes at the end)
-  // The search for what repeats.  Two idle times in a row that equal those at the anchor may be the start of the next pass, and are
-  // if 64 are equal.  From then on the wave notes, once a period, where the queue stands and what it holds there (a lane per note:
-  // the gap, the entry, a sum over the next 64 entries).
-  uint32_t misses = n_gaps < REPEAT_GAPS || L < REPEAT_ENTRIES ? REPEAT_MISSES : 0u;
-  uint32_t period = 0, next_place = 0, notes = 0, note_i = 0, note_j = 0, note_sum = 0;
-  uint32_t anchor = 0;   // (what is needed until there is a period is kept in lanes too: scalar registers are few)
-  enum : uint32_t { A_GAP, A_ENTRY, A_G0, A_G1, A_NEXT, A_COUNT };
-  auto anchor_of = [&](uint32_t what) { return read_lane_u32(anchor, what); };
-  auto sum_of = [&](uint32_t e) { return wave_total_u32(e * ((2 * lane + 1) * 0x9e3779b1u)); };
+  RepeatSearch search;
+  search.until = REPEATS && n_gaps >= REPEAT_GAPS && L >= REPEAT_ENTRIES ? n_gaps - 64 * WW_BLOCKS : 0u;   // (what lies behind the round can be copied)
 
   uint32_t i0 = 0;
   for (;;) {
-  Repeat rep{0, 0, 0, 0, 0, 0, 0};
-  if (wave == 0) {
-  // (launches are read without a branch too, so that what is in flight can be counted: the lane behind the trace's end
-  // reads its last launch again, and nothing of it is used)
-  uint2 ahead[WW_BLOCKS];
+    Repeat rep{0, 0, 0, 0, 0, 0, 0};
+    if (wave == 0) {
+      // (launches are read without a branch too, so that what is in flight can be counted: the lane behind the trace's end
+      // reads its last launch again, and nothing of it is used)
+      uint2 ahead[WW_BLOCKS];
 #pragma unroll
-  for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(i0 + 64 * j + lane, H - 1)] : make_uint2(0, 0);
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(i0 + 64 * j + lane, H - 1)] : make_uint2(0, 0);
 #pragma unroll
-  for (uint32_t j = 0; j < WW_BLOCKS; ++j) asm volatile("" : "+v"(ahead[j].x), "+v"(ahead[j].y));   // (the loop starts with nothing in flight)
-  while (i0 < H && !done) {
-    uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
-#pragma unroll
-    for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
-      E[j] = ahead[j].x; G[j] = ahead[j].y;
-      b1[j] = (i0 + 64 * j + lane < n_gaps && G[j] >= gap_floor) ? G[j] - margin32 + 1 : 0u;
-      if (MODE == LW_REPLAY_FEEDBACK) b1[j] = E[j] == 0 ? 0u : b1[j];   // (the next request is there at once: nothing is issued)
-      asm volatile("" : "+v"(E[j]), "+v"(G[j]), "+v"(b1[j]));           // (waited for here, before the next round's reads go out)
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // (the results of a round are stored without a branch, so that the wait for the next round's reads can leave them in
-    // flight: lanes behind the last gap fall outside the buffer)
-    const uint32_t left = n_gaps - min_u32(i0, n_gaps), gaps_here = min_u32(left, 64 * WW_BLOCKS);
-    const bounded out_c = bounded_at(fill_count + g0 + i0, 4 * gaps_here), out_f = bounded_at(filled_ns + g0 + i0, 8 * gaps_here);
-#pragma unroll
-    for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
-    const bool looking = REPEATS && misses < REPEAT_MISSES && n_gaps > i0 + 64 * WW_BLOCKS;   // (what lies behind the round can be copied)
-    uint32_t found = 0;   // where the next pass may start (what has to be compared is read now and looked at behind the round)
-    uint32_t pass0 = 0, pass1 = 0, anchor_q = 0;
-    if (looking && !period) {
-      if (i0 >= anchor_of(A_NEXT)) {
-        const uint32_t n = anchor_of(A_COUNT);
-        anchor = write_lane_u32(anchor, i0, A_GAP);
-        anchor = write_lane_u32(anchor, wb + o, A_ENTRY);
-        anchor = write_lane_u32(anchor, read_lane_u32(G[0], 0), A_G0);
-        anchor = write_lane_u32(anchor, read_lane_u32(G[0], 1), A_G1);
-        anchor = write_lane_u32(anchor, n + 1 < REPEAT_ANCHORS ? i0 + REPEAT_ANCHOR : i0 + 2 * REPEAT_ANCHOR, A_NEXT);
-        anchor = write_lane_u32(anchor, n + 1, A_COUNT);
-        if (n == REPEAT_ANCHORS) misses = REPEAT_MISSES;
-      }
-      const uint32_t from = anchor_of(A_GAP), g0 = anchor_of(A_G0), g1 = anchor_of(A_G1);
-      uint64_t alike[WW_BLOCKS], any = 0;
-#pragma unroll
-      for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
-        alike[j] = ballot(G[j] == g0) & ~(j == 0 && i0 == from ? 1ull | 1ull << 63 : 1ull << 63);
-        any |= alike[j];
-      }
-      if (any) {
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j) asm volatile("" : "+v"(ahead[j].x), "+v"(ahead[j].y));   // (the loop starts with nothing in flight)
+      while (i0 < H && !done) {
+        uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
 #pragma unroll
         for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
-          alike[j] &= ballot(from_next_lane(G[j]) == g1);
-          if (!found && alike[j]) found = i0 + 64 * j + static_cast<uint32_t>(__builtin_ctzll(alike[j]));
+          E[j] = ahead[j].x; G[j] = ahead[j].y;
+          b1[j] = (i0 + 64 * j + lane < n_gaps && G[j] >= gap_floor) ? G[j] - margin32 + 1 : 0u;
+          if (MODE == LW_REPLAY_FEEDBACK) b1[j] = E[j] == 0 ? 0u : b1[j];   // (the next request is there at once: nothing is issued)
+          asm volatile("" : "+v"(E[j]), "+v"(G[j]), "+v"(b1[j]));           // (waited for here, before the next round's reads go out)
         }
-        if (found) {
-          pass0 = trace[from + lane].y;
-          pass1 = trace[min_u32(found + lane, H - 1)].y;
-          anchor_q = entry(anchor_of(A_ENTRY) + lane);
-        }
-      }
-    }
-    uint32_t count[WW_BLOCKS];
+        __builtin_amdgcn_sched_barrier(0);
+        // (the results of a round are stored without a branch, so that the wait for the next round's reads can leave them in
+        // flight: lanes behind the last gap fall outside the buffer)
+        const uint32_t left = n_gaps - min_u32(i0, n_gaps), gaps_here = min_u32(left, 64 * WW_BLOCKS);
+        const bounded out_c = bounded_at(fill_count + g0 + i0, 4 * gaps_here), out_f = bounded_at(filled_ns + g0 + i0, 8 * gaps_here);
 #pragma unroll
-    for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
-      const uint32_t i = i0 + 64 * j + lane;
-      const bool has_gap = i < n_gaps;
-      uint32_t my_c = 0, my_f = 0;
-      if (!done) {
-        uint32_t k = 0, lim = __builtin_elementwise_add_sat(b1[j], C);
-        uint64_t takes = ballot(lim > sum);
-        // (one way out of the loop, at its end, and the rare case inside it: otherwise the compiler carries flags and copies
-        // through every gap)
-        if (takes) do {
-          k = static_cast<uint32_t>(__builtin_ctzll(takes));
-          uint64_t todo = (~1ull) << k;
-          // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
-          // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
-          // the entries that end before that.
-          const uint32_t limit = read_lane_u32(lim, k);
-          uint32_t o2 = popc64(ballot(win < limit));
-          bool over = false;   // (with feedback: nothing is issued after these)
-          if (MODE == LW_REPLAY_FEEDBACK) {
-            const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
-            const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
-            over = o3 <= o2;
-            o2 = o3 < o2 ? o3 : o2;
-          }
-          uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
-          // the common case: the gap ends inside the window, at an entry whose running sum is exact
-          uint32_t c = o2 - o, f = C2 - C;
-          if (__builtin_expect(sum2 != WIDE32, 1)) {
-            o = o2; C = C2; sum = sum2;
-          } else {
-            // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
-            uint32_t left = read_lane_u32(b1[j], k);
-            const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
-            bool ended = false;
-            if (o2 == WW_WIN && !over && wb + WW_WIN < L) {
-              // nearly all of these: the gap takes the rest of the window (c and f so far) and ends inside the next one
-              left -= f;
-              wb += WW_WIN;
-              set_window(r1);
-              r1 = entry(wb + WW_WIN + lane);
-              o2 = popc64(ballot(win < left));
-              if (MODE == LW_REPLAY_FEEDBACK) {
-                const uint32_t o3 = popc64(ballot(win < actual - f)) + 1;
-                o2 = o3 < o2 ? o3 : o2;
-              }
-              C2 = read_lane_u32(before, o2);
-              sum2 = read_lane_u32(win, o2);
-              ended = sum2 != WIDE32;
-              o = ended ? o2 : 0u; C = ended ? C2 : 0u; sum = sum2;
-              c += o; f += C;
+        for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
+        const bool looking = REPEATS && i0 < search.until;
+        RepeatSearch::Start start{0, 0, 0, 0};
+        if (looking) start = search.look(i0, wb + o, H, trace, G, entry);
+        uint32_t count[WW_BLOCKS];
+#pragma unroll
+        for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+          const uint32_t i = i0 + 64 * j + lane;
+          const bool has_gap = i < n_gaps;
+          uint32_t my_c = 0, my_f = 0;
+          if (!done) {
+            uint32_t k = 0, lim = __builtin_elementwise_add_sat(b1[j], C);
+            uint64_t takes = ballot(lim > sum);
+            // (one way out of the loop, at its end, and the rare case inside it: otherwise the compiler carries flags and copies
+            // through every gap)
+            if (takes) {
+              place_loop();
+              do {
+                k = static_cast<uint32_t>(__builtin_ctzll(takes));
+                uint64_t todo = (~1ull) << k;
+                // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
+                // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
+                // the entries that end before that.
+                const uint32_t limit = read_lane_u32(lim, k);
+                uint32_t o2 = popc64(ballot(win < limit));
+                bool over = false;   // (with feedback: nothing is issued after these)
+                if (MODE == LW_REPLAY_FEEDBACK) {
+                  const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
+                  const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
+                  over = o3 <= o2;
+                  o2 = o3 < o2 ? o3 : o2;
+                }
+                uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
+                // the common case: the gap ends inside the window, at an entry whose running sum is exact
+                uint32_t c = o2 - o, f = C2 - C;
+                if (__builtin_expect(sum2 != WIDE32, 1)) {
+                  o = o2; C = C2; sum = sum2;
+                } else {
+                  // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
+                  uint32_t left = read_lane_u32(b1[j], k);
+                  const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
+                  bool ended = false;
+                  if (o2 == WW_WIN && !over && wb + WW_WIN < L) {
+                    // nearly all of these: the gap takes the rest of the window (c and f so far) and ends inside the next one
+                    left -= f;
+                    wb += WW_WIN;
+                    set_window(r1);
+                    r1 = entry(wb + WW_WIN + lane);
+                    o2 = popc64(ballot(win < left));
+                    if (MODE == LW_REPLAY_FEEDBACK) {
+                      const uint32_t o3 = popc64(ballot(win < actual - f)) + 1;
+                      o2 = o3 < o2 ? o3 : o2;
+                    }
+                    C2 = read_lane_u32(before, o2);
+                    sum2 = read_lane_u32(win, o2);
+                    ended = sum2 != WIDE32;
+                    o = ended ? o2 : 0u; C = ended ? C2 : 0u; sum = sum2;
+                    c += o; f += C;
+                  } else {
+                    c = f = 0;
+                  }
+                  if (!ended) for (;;) {
+                    if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
+                    o2 = popc64(ballot(win < C + left));
+                    bool stop = false;
+                    if (MODE == LW_REPLAY_FEEDBACK) {
+                      const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
+                      stop = o3 <= o2;
+                      o2 = stop ? o3 : o2;
+                    }
+                    const uint32_t C3 = read_lane_u32(before, o2);
+                    c += o2 - o; f += C3 - C; left -= C3 - C;
+                    o = o2; C = C3;
+                    if (wb + o >= L) { done = true; break; }
+                    bool again = false;
+                    if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
+                      wb += WW_WIN; o = 0; C = 0;
+                      set_window(r1);
+                      r1 = entry(wb + WW_WIN + lane);
+                      again = !stop;
+                    }
+                    sum = read_lane_u32(win, o);
+                    if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
+                    if (!again) break;
+                  }
+                  if (done) { f_last = f; todo = 0; }
+                }
+                my_c = write_lane_u32(my_c, c, k);
+                my_f = write_lane_u32(my_f, f, k);
+                lim = __builtin_elementwise_add_sat(b1[j], C);
+                takes = ballot(lim > sum) & todo;
+              } while (takes);
+            }
+            if (MODE == LW_PLAN) {
+              consumed += my_f;
+              // predicted time line: all launches of the block and the idle times after them, or, if the queue ran empty in
+              // gap k, up to the launch before it
+              const bool ran = !done || lane <= k, idled = !done || lane < k;
+              time_line += (i < H && ran ? static_cast<uint64_t>(E[j]) : 0ull) + (has_gap && idled ? static_cast<uint64_t>(G[j]) : 0ull);
             } else {
-              c = f = 0;
+              delay += my_f > E[j] ? my_f - E[j] : 0u;
             }
-            if (!ended) for (;;) {
-              if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
-              o2 = popc64(ballot(win < C + left));
-              bool stop = false;
-              if (MODE == LW_REPLAY_FEEDBACK) {
-                const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
-                stop = o3 <= o2;
-                o2 = stop ? o3 : o2;
-              }
-              const uint32_t C3 = read_lane_u32(before, o2);
-              c += o2 - o; f += C3 - C; left -= C3 - C;
-              o = o2; C = C3;
-              if (wb + o >= L) { done = true; break; }
-              bool again = false;
-              if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
-                wb += WW_WIN; o = 0; C = 0;
-                set_window(r1);
-                r1 = entry(wb + WW_WIN + lane);
-                again = !stop;
-              }
-              sum = read_lane_u32(win, o);
-              if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
-              if (!again) break;
-            }
-            if (done) { f_last = f; todo = 0; }
           }
-          my_c = write_lane_u32(my_c, c, k);
-          my_f = write_lane_u32(my_f, f, k);
-          lim = __builtin_elementwise_add_sat(b1[j], C);
-          takes = ballot(lim > sum) & todo;
-        } while (takes);
-        if (MODE == LW_PLAN) {
-          consumed += my_f;
-          // predicted time line: all launches of the block and the idle times after them, or, if the queue ran empty in
-          // gap k, up to the launch before it
-          const bool ran = !done || lane <= k, idled = !done || lane < k;
-          time_line += (i < H && ran ? static_cast<uint64_t>(E[j]) : 0ull) + (has_gap && idled ? static_cast<uint64_t>(G[j]) : 0ull);
-        } else {
-          delay += my_f > E[j] ? my_f - E[j] : 0u;
+          store_below(out_c, 256u * j + 4u * lane, my_c);
+          store_below(out_f, 512u * j + 8u * lane, my_f, 0u);
+          count[j] = my_c;
         }
-      }
-      store_below(out_c, 256u * j + 4u * lane, my_c);
-      store_below(out_f, 512u * j + 8u * lane, my_f, 0u);
-      count[j] = my_c;
-    }
-    const uint32_t first = i0;
-    i0 += 64 * WW_BLOCKS;
-    if (looking && !done) {
-      if (found) {
-        if (ballot(found + lane < H && pass0 == pass1) == ~0ull) {
-          const uint32_t from = anchor_of(A_GAP);
-          note_i = from; note_j = anchor_of(A_ENTRY); note_sum = sum_of(anchor_q); notes = 1;
-          period = found - from;
-          if (period < REPEAT_LEAST) period *= (REPEAT_LEAST + period - 1) / period;
-          next_place = from + period;   // (not before this round: a pass that starts in it is found in it)
-        } else {
-          ++misses;
+        const uint32_t first = i0;
+        i0 += 64 * WW_BLOCKS;
+        if (looking && !done) {
+          rep = search.note<TEAM>(start, first, wb + o, H, L, n_gaps, count, entry);
+          if (rep.units) break;
         }
-      }
-      if (period && next_place <= i0) {
-        while (next_place + period <= i0) next_place += period;
-        uint32_t behind = 0;   // entries issued from the place on
-#pragma unroll
-        for (uint32_t j = 0; j < WW_BLOCKS; ++j) behind += first + 64 * j + lane >= next_place ? count[j] : 0u;
-        const uint32_t here_j = wb + o - wave_total_u32(behind), here_sum = sum_of(entry(here_j + lane));
-        const uint64_t alike = ballot(lane < notes && note_sum == here_sum);
-        if (alike) {
-          const uint32_t n = 63u - static_cast<uint32_t>(__builtin_clzll(alike));
-          rep.a = next_place; rep.ja = here_j;
-          rep.D = rep.a - read_lane_u32(note_i, n); rep.dq = rep.ja - read_lane_u32(note_j, n);
-          rep.x0 = i0;
-          const uint32_t wanted = (n_gaps - rep.a + rep.D - 1) / rep.D;
-          const uint32_t there = rep.dq ? (L - 1 - rep.ja) / rep.dq : wanted;   // (units whose entries lie in the queue, with the one behind)
-          rep.units = min_u32(wanted, there);
-          rep.X = rep.units == wanted ? n_gaps : rep.a + rep.units * rep.D;
-          if (rep.X <= rep.x0) rep.units = 0;
-          if (there == 0) misses = REPEAT_MISSES;   // (the queue ends first)
-          if (TEAM == 1 && rep.dq < rep.D / REPEAT_WORTH) { rep.units = 0; misses = REPEAT_MISSES; }
-        }
-        const uint32_t n = notes;
-        note_i = write_lane_u32(note_i, next_place, n);
-        note_j = write_lane_u32(note_j, here_j, n);
-        note_sum = write_lane_u32(note_sum, here_sum, n);
-        ++notes;
-        period <<= (notes & 15) == 0 ? 1 : 0;     // (what comes back after c periods comes back after 2 c)
-        misses = notes >= REPEAT_NOTES ? REPEAT_MISSES : misses;
-        next_place += period;
-        if (rep.units) break;
       }
     }
-  }
-  }
-  if (!REPEATS) break;
-  __shared__ struct { Repeat rep; RepeatSums sum; } team;
-  if (TEAM > 1) {
-    if (threadIdx.x == 0) team.rep = rep;
-    __syncthreads();
-    rep = team.rep;
-    rep = Repeat{uniform(rep.a), uniform(rep.ja), uniform(rep.D), uniform(rep.dq), uniform(rep.x0), uniform(rep.units), uniform(rep.X)};
-  }
-  if (!rep.units) break;
-  uint32_t queue_at = wb + o;   // (the window is read again behind the copy: it needs the registers)
-  for (;;) {
+    if (!REPEATS) break;
+    __shared__ struct { Repeat rep; RepeatSums sum; } team;
     if (TEAM > 1) {
-      if (threadIdx.x == 0) team.sum = RepeatSums{0, 0, 0, NOT_BAD, NOT_BAD};
+      if (threadIdx.x == 0) team.rep = rep;
       __syncthreads();
+      rep = team.rep;
+      rep = Repeat{uniform(rep.a), uniform(rep.ja), uniform(rep.D), uniform(rep.dq), uniform(rep.x0), uniform(rep.units), uniform(rep.X)};
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // (the unit that is copied has been stored by the walk)
-    RepeatSums part = repeat_part<MODE, REPEAT_BLOCKS>(rep, wave, TEAM, H, trace, queue, fill_count + g0, filled_ns + g0);
-    if (TEAM > 1) {
-      if (part.bad_x != NOT_BAD) atomicMin(&team.sum.bad_x, part.bad_x);
-      if (part.bad_y != NOT_BAD) atomicMin(&team.sum.bad_y, part.bad_y);
-      part.c = wave_total_u32(part.c);
-      if (lane == 0) atomicAdd(&team.sum.c, part.c);
-      if (wave != 0) {
-        part.used = wave_sum_u64(part.used); part.line = wave_sum_u64(part.line);
-        if (lane == 0) {
-          atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.used), static_cast<unsigned long long>(part.used));
-          atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.line), static_cast<unsigned long long>(part.line));
-        }
+    if (!rep.units) break;
+    uint32_t queue_at = wb + o;   // (the window is read again behind the copy: it needs the registers)
+    for (;;) {
+      if (TEAM > 1) {
+        if (threadIdx.x == 0) team.sum = RepeatSums{0, 0, 0, NOT_BAD, NOT_BAD};
+        __syncthreads();
       }
-      __syncthreads();
-      part.bad_x = uniform(team.sum.bad_x); part.bad_y = uniform(team.sum.bad_y); part.c = uniform(team.sum.c);
-      if (wave == 0 && lane == 0) { part.used += team.sum.used; part.line += team.sum.line; }
-      __syncthreads();
-    } else {
-      part.bad_x = ballot(part.bad_x != NOT_BAD) ? uniform(wave_min_u32(part.bad_x)) : NOT_BAD;
-      part.bad_y = ballot(part.bad_y != NOT_BAD) ? uniform(wave_min_u32(part.bad_y)) : NOT_BAD;
-      part.c = wave_total_u32(part.c);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // (the unit that is copied has been stored by the walk)
+      RepeatSums part = repeat_part<MODE, REPEAT_BLOCKS>(rep, wave, TEAM, H, trace, queue, fill_count + g0, filled_ns + g0);
+      if (TEAM > 1) {
+        if (part.bad_x != NOT_BAD) atomicMin(&team.sum.bad_x, part.bad_x);
+        if (part.bad_y != NOT_BAD) atomicMin(&team.sum.bad_y, part.bad_y);
+        part.c = wave_total_u32(part.c);
+        if (lane == 0) atomicAdd(&team.sum.c, part.c);
+        if (wave != 0) {
+          part.used = wave_sum_u64(part.used); part.line = wave_sum_u64(part.line);
+          if (lane == 0) {
+            atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.used), static_cast<unsigned long long>(part.used));
+            atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.line), static_cast<unsigned long long>(part.line));
+          }
+        }
+        __syncthreads();
+        part.bad_x = uniform(team.sum.bad_x); part.bad_y = uniform(team.sum.bad_y); part.c = uniform(team.sum.c);
+        if (wave == 0 && lane == 0) { part.used += team.sum.used; part.line += team.sum.line; }
+        __syncthreads();
+      } else {
+        part.bad_x = ballot(part.bad_x != NOT_BAD) ? uniform(wave_min_u32(part.bad_x)) : NOT_BAD;
+        part.bad_y = ballot(part.bad_y != NOT_BAD) ? uniform(wave_min_u32(part.bad_y)) : NOT_BAD;
+        part.c = wave_total_u32(part.c);
+      }
+      const uint32_t hold = units_that_hold(rep, part.bad_x, part.bad_y);
+      if (hold == rep.units) {
+        if (MODE == LW_PLAN) time_line += part.line; else delay += part.line;
+        consumed += part.used;
+        i0 = rep.X;
+        search.next_place = rep.X + search.period;
+        queue_at = rep.X == n_gaps ? queue_at + part.c : rep.ja + rep.units * rep.dq;
+        break;
+      }
+      // something differs: what holds is copied once more, for the sums; the walk goes on behind it and looks for another period
+      search.miss(2); search.period = 0; search.anchor = 0;
+      rep.units = hold;
+      rep.X = rep.a + hold * rep.D;
+      if (rep.X <= rep.x0) break;
     }
-    const uint32_t hold = units_that_hold(rep, part.bad_x, part.bad_y);
-    if (hold == rep.units) {
-      if (MODE == LW_PLAN) time_line += part.line; else delay += part.line;
-      consumed += part.used;
-      i0 = rep.X;
-      next_place = rep.X + period;
-      queue_at = rep.X == n_gaps ? queue_at + part.c : rep.ja + rep.units * rep.dq;
-      break;
-    }
-    // something differs: what holds is copied once more, for the sums; the walk goes on behind it and looks for another period
-    misses += 2; period = 0; anchor = 0;
-    rep.units = hold;
-    rep.X = rep.a + hold * rep.D;
-    if (rep.X <= rep.x0) break;
-  }
-  if (i0 == n_gaps) { wb = queue_at; o = 0; break; }   // (the last launch's time has been added too)
-  if (wave == 0) { load_window(queue_at); sum = read_lane_u32(win, 0); }
+    if (i0 == n_gaps) { wb = queue_at; o = 0; break; }   // (the last launch's time has been added too)
+    if (wave == 0) { load_window(queue_at); sum = read_lane_u32(win, 0); }
   }
   if (wave != 0) return;
   for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queue ran empty)
