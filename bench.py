@@ -39,7 +39,7 @@ ALGO_BYTES_PER_RECORD = {
     "k_unit_sorted": 16,
 }
 UNIT_KERNELS = ("k_unit_sorted_small", "k_unit_sorted_mid", "k_unit_large")   # by size of the unit; the last streams units too
-GAPFILL_KERNELS = ("k_gf_predict32", "k_gf_walk_wave", "k_gf_walk_lanes")
+GAPFILL_KERNELS = ("k_gf_predict32", "k_gf_walk_wave", "k_gf_walk_team", "k_gf_walk_lanes")
 
 
 def source_hash():

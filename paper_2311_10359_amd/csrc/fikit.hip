@@ -703,9 +703,13 @@ constexpr uint64_t GF_PAD = 256;
 // on, but what gaps take is not known when the line is drawn.
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
 // Up to this many scenarios of tasks of so many launches on average, a workgroup takes each: one of its waves walks, all copy what
-// repeats (256 scenarios of 65,535 gaps: a copy of 64,000 gaps takes 140,000 cycles by four waves, the call 382 us; by eight 355, by
-// sixteen 341).  A workgroup costs 2 us more to start and to end, which 64 scenarios of 1500 gaps feel (75.8 -> 78 us).
-constexpr uint64_t GF_TEAM_SCENARIOS = 1024, GF_TEAM_LAUNCHES = 8192;
+// repeats.  Three workgroups of eight waves are on a compute unit at a time, so the 769th waits until a scenario is through (traces
+// and queues of 16,384 launches that never repeat, in us by a wave / by a workgroup each: 768 scenarios 441 / 455, 784 429 / 563, 1024
+// 447 / 700).  Shorter traces are copied fast enough by one wave, and the walk by the first of several is 2 to 4 % slower (256 scenarios,
+// queues four times as long as the traces, repeating: 4096 launches 222 / 223, 8192 249 / 231, 16,384 310 / 263, 32,768 439 / 273; never
+// repeating: 334 / 341, 618 / 634, 1195 / 1228, 2320 / 2387).  Of 256 scenarios of 65,535 gaps, four waves take 382 us, eight 355, sixteen
+// 341, but of workgroups of sixteen waves only 256 would be there at a time.
+constexpr uint64_t GF_TEAM_SCENARIOS = 768, GF_TEAM_LAUNCHES = 16384;
 constexpr int GF_TEAM_WAVES = 8;
 // Below this average few traces are long enough for the search, and the walk without it has 54 registers instead of 67: one pair of 1000
 // launches 60.0 -> 58.8 us, 64 scenarios of 1500 and 3000 launches 79.3 -> 78.5 us; 6000 of 3100 on average gain by the search (396 -> 377).
@@ -800,8 +804,8 @@ void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64
 // null): the profile that it follows in the same call.
 template <int MODE>
 int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_task_offsets, uint32_t n_tasks,
-                 const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets, uint64_t n_gaps, int64_t margin,
-                 int64_t min_gap, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* result, uint64_t* d_lp_placed,
+                 const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets,
+                 uint64_t n_gaps, int64_t margin, int64_t min_gap, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* result, uint64_t* d_lp_placed,
                  bool set_attributes, const Ctrl* prof, uint64_t row_capacity) {
   if (n_scenarios >= GF_LANES_MIN_SCENARIOS && n_gaps < MAX_ELEMS) {
     tr.mark(MODE == LW_PLAN ? "k_gf_walk_lanes" : MODE == LW_REPLAY ? "k_gf_replay_lanes" : "k_gf_replay_feedback_lanes");
@@ -813,9 +817,10 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
                        d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
                        d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, prof, row_capacity, b.ctrl);
   } else {
-    tr.mark(MODE == LW_PLAN ? "k_gf_walk_wave" : MODE == LW_REPLAY ? "k_gf_replay_wave" : "k_gf_replay_feedback_wave");
     const uint64_t launches = b.n_ids / n_tasks;   // of a task on average
     const bool teams = MODE != LW_REPLAY_FEEDBACK && n_scenarios <= GF_TEAM_SCENARIOS && launches >= GF_TEAM_LAUNCHES;
+    tr.mark(MODE == LW_PLAN ? (teams ? "k_gf_walk_team" : "k_gf_walk_wave")
+                            : MODE == LW_REPLAY ? (teams ? "k_gf_replay_team" : "k_gf_replay_wave") : "k_gf_replay_feedback_wave");
     auto kernel = &k_gf_walk_wave<MODE, 0>;
     if constexpr (MODE != LW_REPLAY_FEEDBACK)
       kernel = teams ? &k_gf_walk_wave<MODE, GF_TEAM_WAVES> : launches >= GF_REPEAT_LAUNCHES ? &k_gf_walk_wave<MODE, 1> : kernel;

@@ -787,10 +787,74 @@ __device__ __forceinline__ uint32_t units_that_hold(const Repeat& r, uint32_t ba
   if (bad_y != NOT_BAD) units = min_u32(units, bad_y > r.ja ? (bad_y - r.ja - 1) / r.dq : 0u);
   return units;
 }
+// Something differed: what holds is left, to be copied once more for the sums.  False if all of it holds.
+__device__ __forceinline__ bool repeat_shorten(Repeat& r, const RepeatSums& part) {
+  const uint32_t hold = units_that_hold(r, part.bad_x, part.bad_y);
+  if (hold == r.units) return false;
+  r.units = hold;
+  r.X = r.a + hold * r.D;
+  return true;
+}
 __device__ __forceinline__ uint32_t uniform(uint32_t v) {   // (v is the same in all lanes: kept in a scalar register)
   return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
 }
 __device__ __forceinline__ uint32_t wave_total_u32(uint32_t v) { return read_lane_u32(wave_incl_scan_u32(v), WAVE - 1); }
+
+struct RepeatTeam {   // (in LDS)
+  Repeat rep;         // what the walking wave has found; no units: the others leave
+  RepeatSums sum;
+};
+// All waves of a scenario: what repeats is compared and copied.  Returns the number of entries issued and the first places that differ;
+// `used` and `line` are the lane's own, and the other waves' sums are added to lane 0 of the first.
+template <int MODE, int TEAM>
+__device__ __forceinline__ RepeatSums repeat_copy(const Repeat& rep, uint32_t wave, uint32_t H, const uint2* __restrict__ trace,
+                                                  const uint32_t* __restrict__ queue, uint32_t* fill_count, int64_t* filled_ns,
+                                                  RepeatTeam* team) {
+  const uint32_t lane = lane_id();
+  if (TEAM > 1) {
+    if (threadIdx.x == 0) team->sum = RepeatSums{0, 0, 0, NOT_BAD, NOT_BAD};
+    __syncthreads();
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // (the unit that is copied has been stored by the walk)
+  RepeatSums part = repeat_part<MODE, REPEAT_BLOCKS>(rep, wave, TEAM, H, trace, queue, fill_count, filled_ns);
+  if (TEAM > 1) {
+    if (part.bad_x != NOT_BAD) atomicMin(&team->sum.bad_x, part.bad_x);
+    if (part.bad_y != NOT_BAD) atomicMin(&team->sum.bad_y, part.bad_y);
+    part.c = wave_total_u32(part.c);
+    if (lane == 0) atomicAdd(&team->sum.c, part.c);
+    if (wave != 0) {
+      part.used = wave_sum_u64(part.used); part.line = wave_sum_u64(part.line);
+      if (lane == 0) {
+        atomicAdd(reinterpret_cast<unsigned long long*>(&team->sum.used), static_cast<unsigned long long>(part.used));
+        atomicAdd(reinterpret_cast<unsigned long long*>(&team->sum.line), static_cast<unsigned long long>(part.line));
+      }
+    }
+    __syncthreads();
+    part.bad_x = uniform(team->sum.bad_x); part.bad_y = uniform(team->sum.bad_y); part.c = uniform(team->sum.c);
+    if (wave == 0 && lane == 0) { part.used += team->sum.used; part.line += team->sum.line; }
+    __syncthreads();
+  } else {
+    part.bad_x = ballot(part.bad_x != NOT_BAD) ? uniform(wave_min_u32(part.bad_x)) : NOT_BAD;
+    part.bad_y = ballot(part.bad_y != NOT_BAD) ? uniform(wave_min_u32(part.bad_y)) : NOT_BAD;
+    part.c = wave_total_u32(part.c);
+  }
+  return part;
+}
+// The waves of a scenario that do not walk: they copy what the walking wave finds until it finds no more.
+template <int MODE, int TEAM>
+__device__ __forceinline__ void repeat_helper(uint32_t wave, uint32_t H, const uint2* __restrict__ trace, const uint32_t* __restrict__ queue,
+                                              uint32_t* fill_count, int64_t* filled_ns, RepeatTeam* team) {
+  for (;;) {
+    __syncthreads();
+    Repeat rep = team->rep;
+    rep = Repeat{uniform(rep.a), uniform(rep.ja), uniform(rep.D), uniform(rep.dq), uniform(rep.x0), uniform(rep.units), uniform(rep.X)};
+    if (!rep.units) return;
+    while (rep.X > rep.x0) {   // (as the walking wave does)
+      const RepeatSums part = repeat_copy<MODE, TEAM>(rep, wave, H, trace, queue, fill_count, filled_ns, team);
+      if (!repeat_shorten(rep, part)) break;
+    }
+  }
+}
 
 // Where it is worth the search.  The search costs a wave 1 to 2 us until there is a period and 0.4 us a note; 64 traces of 1500 gaps
 // (a call of 75 us) gain nothing by it, 6000 of up to 2800 gaps 393 -> 367 us.  A queue of a few passes is soon used up, or hardly moves.
@@ -958,9 +1022,15 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
     r1 = entry(at + WW_WIN + lane);
     set_window(r0);
   };
+  __shared__ RepeatTeam team;
+  if (TEAM > 1 && wave != 0) { repeat_helper<MODE, TEAM>(wave, H, trace, queue, fill_count + g0, filled_ns + g0, &team); return; }
+  auto share = [&](const Repeat& rep) {
+    if (threadIdx.x == 0) team.rep = rep;
+    __syncthreads();
+  };
   bool done = L == 0;    // the whole queue has been issued
   uint32_t f_last = 0;   // time filled in the gap that took the last of it
-  if (!done && wave == 0) { load_window(0); sum = read_lane_u32(win, 0); }
+  if (!done) { load_window(0); sum = read_lane_u32(win, 0); }
 
   uint64_t time_line = 0, consumed = 0, delay = 0;   // (per lane; summed over the lanes at the end)
   RepeatSearch search;
@@ -969,184 +1039,148 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
   uint32_t i0 = 0;
   for (;;) {
     Repeat rep{0, 0, 0, 0, 0, 0, 0};
-    if (wave == 0) {
-      // (launches are read without a branch too, so that what is in flight can be counted: the lane behind the trace's end
-      // reads its last launch again, and nothing of it is used)
-      uint2 ahead[WW_BLOCKS];
+    // (launches are read without a branch too, so that what is in flight can be counted: the lane behind the trace's end
+    // reads its last launch again, and nothing of it is used)
+    uint2 ahead[WW_BLOCKS];
 #pragma unroll
-      for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(i0 + 64 * j + lane, H - 1)] : make_uint2(0, 0);
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = H ? trace[min_u32(i0 + 64 * j + lane, H - 1)] : make_uint2(0, 0);
 #pragma unroll
-      for (uint32_t j = 0; j < WW_BLOCKS; ++j) asm volatile("" : "+v"(ahead[j].x), "+v"(ahead[j].y));   // (the loop starts with nothing in flight)
-      while (i0 < H && !done) {
-        uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
+    for (uint32_t j = 0; j < WW_BLOCKS; ++j) asm volatile("" : "+v"(ahead[j].x), "+v"(ahead[j].y));   // (the loop starts with nothing in flight)
+    while (i0 < H && !done) {
+      uint32_t E[WW_BLOCKS], G[WW_BLOCKS], b1[WW_BLOCKS];   // (replay: E is the idle time that occurred)
 #pragma unroll
-        for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
-          E[j] = ahead[j].x; G[j] = ahead[j].y;
-          b1[j] = (i0 + 64 * j + lane < n_gaps && G[j] >= gap_floor) ? G[j] - margin32 + 1 : 0u;
-          if (MODE == LW_REPLAY_FEEDBACK) b1[j] = E[j] == 0 ? 0u : b1[j];   // (the next request is there at once: nothing is issued)
-          asm volatile("" : "+v"(E[j]), "+v"(G[j]), "+v"(b1[j]));           // (waited for here, before the next round's reads go out)
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // (the results of a round are stored without a branch, so that the wait for the next round's reads can leave them in
-        // flight: lanes behind the last gap fall outside the buffer)
-        const uint32_t left = n_gaps - min_u32(i0, n_gaps), gaps_here = min_u32(left, 64 * WW_BLOCKS);
-        const bounded out_c = bounded_at(fill_count + g0 + i0, 4 * gaps_here), out_f = bounded_at(filled_ns + g0 + i0, 8 * gaps_here);
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+        E[j] = ahead[j].x; G[j] = ahead[j].y;
+        b1[j] = (i0 + 64 * j + lane < n_gaps && G[j] >= gap_floor) ? G[j] - margin32 + 1 : 0u;
+        if (MODE == LW_REPLAY_FEEDBACK) b1[j] = E[j] == 0 ? 0u : b1[j];   // (the next request is there at once: nothing is issued)
+        asm volatile("" : "+v"(E[j]), "+v"(G[j]), "+v"(b1[j]));           // (waited for here, before the next round's reads go out)
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // (the results of a round are stored without a branch, so that the wait for the next round's reads can leave them in
+      // flight: lanes behind the last gap fall outside the buffer)
+      const uint32_t left = n_gaps - min_u32(i0, n_gaps), gaps_here = min_u32(left, 64 * WW_BLOCKS);
+      const bounded out_c = bounded_at(fill_count + g0 + i0, 4 * gaps_here), out_f = bounded_at(filled_ns + g0 + i0, 8 * gaps_here);
 #pragma unroll
-        for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
-        const bool looking = REPEATS && i0 < search.until;
-        RepeatSearch::Start start{0, 0, 0, 0};
-        if (looking) start = search.look(i0, wb + o, H, trace, G, entry);
-        uint32_t count[WW_BLOCKS];
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j) ahead[j] = trace[min_u32(i0 + 64 * (WW_BLOCKS + j) + lane, H - 1)];
+      const bool looking = REPEATS && i0 < search.until;
+      RepeatSearch::Start start{0, 0, 0, 0};
+      if (looking) start = search.look(i0, wb + o, H, trace, G, entry);
+      uint32_t count[WW_BLOCKS];
 #pragma unroll
-        for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
-          const uint32_t i = i0 + 64 * j + lane;
-          const bool has_gap = i < n_gaps;
-          uint32_t my_c = 0, my_f = 0;
-          if (!done) {
-            uint32_t k = 0, lim = __builtin_elementwise_add_sat(b1[j], C);
-            uint64_t takes = ballot(lim > sum);
-            // (one way out of the loop, at its end, and the rare case inside it: otherwise the compiler carries flags and copies
-            // through every gap)
-            if (takes) {
-              place_loop();
-              do {
-                k = static_cast<uint32_t>(__builtin_ctzll(takes));
-                uint64_t todo = (~1ull) << k;
-                // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
-                // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
-                // the entries that end before that.
-                const uint32_t limit = read_lane_u32(lim, k);
-                uint32_t o2 = popc64(ballot(win < limit));
-                bool over = false;   // (with feedback: nothing is issued after these)
-                if (MODE == LW_REPLAY_FEEDBACK) {
-                  const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
-                  const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
-                  over = o3 <= o2;
-                  o2 = o3 < o2 ? o3 : o2;
-                }
-                uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
-                // the common case: the gap ends inside the window, at an entry whose running sum is exact
-                uint32_t c = o2 - o, f = C2 - C;
-                if (__builtin_expect(sum2 != WIDE32, 1)) {
-                  o = o2; C = C2; sum = sum2;
+      for (uint32_t j = 0; j < WW_BLOCKS; ++j) {
+        const uint32_t i = i0 + 64 * j + lane;
+        const bool has_gap = i < n_gaps;
+        uint32_t my_c = 0, my_f = 0;
+        if (!done) {
+          uint32_t k = 0, lim = __builtin_elementwise_add_sat(b1[j], C);
+          uint64_t takes = ballot(lim > sum);
+          // (one way out of the loop, at its end, and the rare case inside it: otherwise the compiler carries flags and copies
+          // through every gap)
+          if (takes) {
+            place_loop();
+            do {
+              k = static_cast<uint32_t>(__builtin_ctzll(takes));
+              uint64_t todo = (~1ull) << k;
+              // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
+              // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
+              // the entries that end before that.
+              const uint32_t limit = read_lane_u32(lim, k);
+              uint32_t o2 = popc64(ballot(win < limit));
+              bool over = false;   // (with feedback: nothing is issued after these)
+              if (MODE == LW_REPLAY_FEEDBACK) {
+                const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
+                const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
+                over = o3 <= o2;
+                o2 = o3 < o2 ? o3 : o2;
+              }
+              uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
+              // the common case: the gap ends inside the window, at an entry whose running sum is exact
+              uint32_t c = o2 - o, f = C2 - C;
+              if (__builtin_expect(sum2 != WIDE32, 1)) {
+                o = o2; C = C2; sum = sum2;
+              } else {
+                // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
+                uint32_t left = read_lane_u32(b1[j], k);
+                const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
+                bool ended = false;
+                if (o2 == WW_WIN && !over && wb + WW_WIN < L) {
+                  // nearly all of these: the gap takes the rest of the window (c and f so far) and ends inside the next one
+                  left -= f;
+                  wb += WW_WIN;
+                  set_window(r1);
+                  r1 = entry(wb + WW_WIN + lane);
+                  o2 = popc64(ballot(win < left));
+                  if (MODE == LW_REPLAY_FEEDBACK) {
+                    const uint32_t o3 = popc64(ballot(win < actual - f)) + 1;
+                    o2 = o3 < o2 ? o3 : o2;
+                  }
+                  C2 = read_lane_u32(before, o2);
+                  sum2 = read_lane_u32(win, o2);
+                  ended = sum2 != WIDE32;
+                  o = ended ? o2 : 0u; C = ended ? C2 : 0u; sum = sum2;
+                  c += o; f += C;
                 } else {
-                  // the rest: the gap reaches the window's end or the queue's, or the window has to be reloaded first
-                  uint32_t left = read_lane_u32(b1[j], k);
-                  const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
-                  bool ended = false;
-                  if (o2 == WW_WIN && !over && wb + WW_WIN < L) {
-                    // nearly all of these: the gap takes the rest of the window (c and f so far) and ends inside the next one
-                    left -= f;
-                    wb += WW_WIN;
+                  c = f = 0;
+                }
+                if (!ended) for (;;) {
+                  if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
+                  o2 = popc64(ballot(win < C + left));
+                  bool stop = false;
+                  if (MODE == LW_REPLAY_FEEDBACK) {
+                    const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
+                    stop = o3 <= o2;
+                    o2 = stop ? o3 : o2;
+                  }
+                  const uint32_t C3 = read_lane_u32(before, o2);
+                  c += o2 - o; f += C3 - C; left -= C3 - C;
+                  o = o2; C = C3;
+                  if (wb + o >= L) { done = true; break; }
+                  bool again = false;
+                  if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
+                    wb += WW_WIN; o = 0; C = 0;
                     set_window(r1);
                     r1 = entry(wb + WW_WIN + lane);
-                    o2 = popc64(ballot(win < left));
-                    if (MODE == LW_REPLAY_FEEDBACK) {
-                      const uint32_t o3 = popc64(ballot(win < actual - f)) + 1;
-                      o2 = o3 < o2 ? o3 : o2;
-                    }
-                    C2 = read_lane_u32(before, o2);
-                    sum2 = read_lane_u32(win, o2);
-                    ended = sum2 != WIDE32;
-                    o = ended ? o2 : 0u; C = ended ? C2 : 0u; sum = sum2;
-                    c += o; f += C;
-                  } else {
-                    c = f = 0;
+                    again = !stop;
                   }
-                  if (!ended) for (;;) {
-                    if (static_cast<uint64_t>(C) + left > WIDE32) load_window(wb + o);
-                    o2 = popc64(ballot(win < C + left));
-                    bool stop = false;
-                    if (MODE == LW_REPLAY_FEEDBACK) {
-                      const uint32_t o3 = popc64(ballot(win < sat32(static_cast<uint64_t>(C) + (actual - f)))) + 1;
-                      stop = o3 <= o2;
-                      o2 = stop ? o3 : o2;
-                    }
-                    const uint32_t C3 = read_lane_u32(before, o2);
-                    c += o2 - o; f += C3 - C; left -= C3 - C;
-                    o = o2; C = C3;
-                    if (wb + o >= L) { done = true; break; }
-                    bool again = false;
-                    if (o == WW_WIN) {   // the window is used up: the next one, in which this gap goes on
-                      wb += WW_WIN; o = 0; C = 0;
-                      set_window(r1);
-                      r1 = entry(wb + WW_WIN + lane);
-                      again = !stop;
-                    }
-                    sum = read_lane_u32(win, o);
-                    if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
-                    if (!again) break;
-                  }
-                  if (done) { f_last = f; todo = 0; }
+                  sum = read_lane_u32(win, o);
+                  if (sum == WIDE32 && C != 0) { load_window(wb + o); sum = read_lane_u32(win, 0); again = !stop; }
+                  if (!again) break;
                 }
-                my_c = write_lane_u32(my_c, c, k);
-                my_f = write_lane_u32(my_f, f, k);
-                lim = __builtin_elementwise_add_sat(b1[j], C);
-                takes = ballot(lim > sum) & todo;
-              } while (takes);
-            }
-            if (MODE == LW_PLAN) {
-              consumed += my_f;
-              // predicted time line: all launches of the block and the idle times after them, or, if the queue ran empty in
-              // gap k, up to the launch before it
-              const bool ran = !done || lane <= k, idled = !done || lane < k;
-              time_line += (i < H && ran ? static_cast<uint64_t>(E[j]) : 0ull) + (has_gap && idled ? static_cast<uint64_t>(G[j]) : 0ull);
-            } else {
-              delay += my_f > E[j] ? my_f - E[j] : 0u;
-            }
+                if (done) { f_last = f; todo = 0; }
+              }
+              my_c = write_lane_u32(my_c, c, k);
+              my_f = write_lane_u32(my_f, f, k);
+              lim = __builtin_elementwise_add_sat(b1[j], C);
+              takes = ballot(lim > sum) & todo;
+            } while (takes);
           }
-          store_below(out_c, 256u * j + 4u * lane, my_c);
-          store_below(out_f, 512u * j + 8u * lane, my_f, 0u);
-          count[j] = my_c;
+          if (MODE == LW_PLAN) {
+            consumed += my_f;
+            // predicted time line: all launches of the block and the idle times after them, or, if the queue ran empty in
+            // gap k, up to the launch before it
+            const bool ran = !done || lane <= k, idled = !done || lane < k;
+            time_line += (i < H && ran ? static_cast<uint64_t>(E[j]) : 0ull) + (has_gap && idled ? static_cast<uint64_t>(G[j]) : 0ull);
+          } else {
+            delay += my_f > E[j] ? my_f - E[j] : 0u;
+          }
         }
-        const uint32_t first = i0;
-        i0 += 64 * WW_BLOCKS;
-        if (looking && !done) {
-          rep = search.note<TEAM>(start, first, wb + o, H, L, n_gaps, count, entry);
-          if (rep.units) break;
-        }
+        store_below(out_c, 256u * j + 4u * lane, my_c);
+        store_below(out_f, 512u * j + 8u * lane, my_f, 0u);
+        count[j] = my_c;
+      }
+      const uint32_t first = i0;
+      i0 += 64 * WW_BLOCKS;
+      if (looking && !done) {
+        rep = search.note<TEAM>(start, first, wb + o, H, L, n_gaps, count, entry);
+        if (rep.units) break;
       }
     }
-    if (!REPEATS) break;
-    __shared__ struct { Repeat rep; RepeatSums sum; } team;
-    if (TEAM > 1) {
-      if (threadIdx.x == 0) team.rep = rep;
-      __syncthreads();
-      rep = team.rep;
-      rep = Repeat{uniform(rep.a), uniform(rep.ja), uniform(rep.D), uniform(rep.dq), uniform(rep.x0), uniform(rep.units), uniform(rep.X)};
-    }
-    if (!rep.units) break;
+    if (!REPEATS || !rep.units) break;
+    if (TEAM > 1) share(rep);
     uint32_t queue_at = wb + o;   // (the window is read again behind the copy: it needs the registers)
-    for (;;) {
-      if (TEAM > 1) {
-        if (threadIdx.x == 0) team.sum = RepeatSums{0, 0, 0, NOT_BAD, NOT_BAD};
-        __syncthreads();
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // (the unit that is copied has been stored by the walk)
-      RepeatSums part = repeat_part<MODE, REPEAT_BLOCKS>(rep, wave, TEAM, H, trace, queue, fill_count + g0, filled_ns + g0);
-      if (TEAM > 1) {
-        if (part.bad_x != NOT_BAD) atomicMin(&team.sum.bad_x, part.bad_x);
-        if (part.bad_y != NOT_BAD) atomicMin(&team.sum.bad_y, part.bad_y);
-        part.c = wave_total_u32(part.c);
-        if (lane == 0) atomicAdd(&team.sum.c, part.c);
-        if (wave != 0) {
-          part.used = wave_sum_u64(part.used); part.line = wave_sum_u64(part.line);
-          if (lane == 0) {
-            atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.used), static_cast<unsigned long long>(part.used));
-            atomicAdd(reinterpret_cast<unsigned long long*>(&team.sum.line), static_cast<unsigned long long>(part.line));
-          }
-        }
-        __syncthreads();
-        part.bad_x = uniform(team.sum.bad_x); part.bad_y = uniform(team.sum.bad_y); part.c = uniform(team.sum.c);
-        if (wave == 0 && lane == 0) { part.used += team.sum.used; part.line += team.sum.line; }
-        __syncthreads();
-      } else {
-        part.bad_x = ballot(part.bad_x != NOT_BAD) ? uniform(wave_min_u32(part.bad_x)) : NOT_BAD;
-        part.bad_y = ballot(part.bad_y != NOT_BAD) ? uniform(wave_min_u32(part.bad_y)) : NOT_BAD;
-        part.c = wave_total_u32(part.c);
-      }
-      const uint32_t hold = units_that_hold(rep, part.bad_x, part.bad_y);
-      if (hold == rep.units) {
+    while (rep.X > rep.x0) {
+      const RepeatSums part = repeat_copy<MODE, TEAM>(rep, 0, H, trace, queue, fill_count + g0, filled_ns + g0, &team);
+      if (!repeat_shorten(rep, part)) {
         if (MODE == LW_PLAN) time_line += part.line; else delay += part.line;
         consumed += part.used;
         i0 = rep.X;
@@ -1154,16 +1188,13 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
         queue_at = rep.X == n_gaps ? queue_at + part.c : rep.ja + rep.units * rep.dq;
         break;
       }
-      // something differs: what holds is copied once more, for the sums; the walk goes on behind it and looks for another period
-      search.miss(2); search.period = 0; search.anchor = 0;
-      rep.units = hold;
-      rep.X = rep.a + hold * rep.D;
-      if (rep.X <= rep.x0) break;
+      search.miss(2); search.period = 0; search.anchor = 0;   // (the walk goes on behind what holds and looks for another period)
     }
     if (i0 == n_gaps) { wb = queue_at; o = 0; break; }   // (the last launch's time has been added too)
-    if (wave == 0) { load_window(queue_at); sum = read_lane_u32(win, 0); }
+    load_window(queue_at);
+    sum = read_lane_u32(win, 0);
   }
-  if (wave != 0) return;
+  if (TEAM > 1) share(Repeat{0, 0, 0, 0, 0, 0, 0});
   for (uint32_t i = i0 + lane; i < n_gaps; i += WAVE) {   // (after the queue ran empty)
     fill_count[g0 + i] = 0;
     filled_ns[g0 + i] = 0;

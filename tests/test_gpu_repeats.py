@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 
 # Up to so many scenarios, if the tasks have so many launches on average, a workgroup takes each, otherwise a wave.  Repeats are looked
 # for in traces of REPEAT_GAPS gaps and more, if the tasks have REPEAT_LAUNCHES launches on average.
-TEAM_SCENARIOS, TEAM_LAUNCHES, REPEAT_GAPS, REPEAT_LAUNCHES = 1024, 8192, 2048, 3072
+TEAM_SCENARIOS, TEAM_LAUNCHES, REPEAT_GAPS, REPEAT_LAUNCHES = 768, 16384, 2048, 3072
+
+WALKS, REPLAYS = {"k_gf_walk_wave", "k_gf_walk_team", "k_gf_walk_lanes"}, {"k_gf_replay_wave", "k_gf_replay_team", "k_gf_replay_lanes"}
 
 
 def passes(rng, period, launches, ids, odd_at=(), first=0):
@@ -70,5 +72,21 @@ def test_what_repeats_is_copied(times, team):
         print(f"{hs.size} scenarios, {times}, margin {margin}", flush=True)
         with kernels_of() as names:
             check_gapfill(prof, d_off, off, o_prof, hs, ls, margin, min_gap)
-        assert "k_gf_walk_wave" in names
-        check_replay(prof, d_off, off, o_prof, d_gap, gap, hs, ls, margin, min_gap)
+        assert names & WALKS == {"k_gf_walk_team" if team else "k_gf_walk_wave"}
+        with kernels_of() as names:
+            check_replay(prof, d_off, off, o_prof, d_gap, gap, hs, ls, margin, min_gap)
+        assert names & REPLAYS == {"k_gf_replay_team" if team else "k_gf_replay_wave"}
+
+
+@pytest.mark.parametrize("n_scen,launches,team", [
+    (TEAM_SCENARIOS, TEAM_LAUNCHES, True), (TEAM_SCENARIOS + 1, TEAM_LAUNCHES, False), (3, TEAM_LAUNCHES, True), (3, TEAM_LAUNCHES - 1, False)])
+def test_a_workgroup_takes_a_scenario_while_all_fit(n_scen, launches, team):
+    rng = np.random.default_rng(launches)
+    rec, off = tasks_of(rng, [passes(rng, 200, launches, 20), passes(rng, 160, launches, 20)], rng.integers(100, 4000, 23), rng.integers(0, 3000, 23))
+    prof, d_off, o_prof = check_profile(rec, off)
+    d_gap, gap = check_measure(rec, off)
+    hs, ls = np.zeros(n_scen, np.uint32), np.ones(n_scen, np.uint32)
+    with kernels_of() as names:
+        check_gapfill(prof, d_off, off, o_prof, hs, ls, 0, 0)
+        check_replay(prof, d_off, off, o_prof, d_gap, gap, hs, ls, 0, 0)
+    assert names & (WALKS | REPLAYS) == ({"k_gf_walk_team", "k_gf_replay_team"} if team else {"k_gf_walk_wave", "k_gf_replay_wave"})
