@@ -10,9 +10,9 @@ from test_gpu_replay import check_measure, check_replay
 
 pytestmark = pytest.mark.gpu
 
-# Up to so many scenarios, if the tasks have so many launches on average, a workgroup takes each, otherwise a wave.  Repeats are looked
-# for in traces of REPEAT_GAPS gaps and more, if the tasks have REPEAT_LAUNCHES launches on average.
-TEAM_SCENARIOS, TEAM_LAUNCHES, REPEAT_GAPS, REPEAT_LAUNCHES = 768, 16384, 2048, 3072
+# Up to so many scenarios, if they have so many gaps on average, a workgroup takes each, otherwise a wave.  Repeats are looked
+# for in traces of REPEAT_GAPS gaps and more.
+TEAM_SCENARIOS, TEAM_GAPS, REPEAT_GAPS = 768, 16384, 2048
 
 WALKS, REPLAYS = {"k_gf_walk_wave", "k_gf_walk_team", "k_gf_walk_lanes"}, {"k_gf_replay_wave", "k_gf_replay_team", "k_gf_replay_lanes"}
 
@@ -60,12 +60,12 @@ def test_what_repeats_is_copied(times, team):
     lp = [passes(rng, p, n, ids, odd, 0) for p, n, odd in (
         (1, 5000, ()), (13, 3000, ()), (63, 6000, ()), (160, 9000, ()), (160, 9000, (700, 3000)), (160, 400, ()), (161, 1000, (999,)), (64, 64, ()),
         (600, 9000, ()), (4000, 4000, ()), (1, 1, ()))]
-    most = TEAM_LAUNCHES * (len(hp) + len(lp) + 1) if team else 1   # (of a task that no scenario uses)
-    rec, off = tasks_of(rng, hp + lp + [passes(rng, 50, most, ids)], exec_of, gap_of)
+    if team:   # (a trace that alone brings the average there)
+        hp.append(passes(rng, 50, TEAM_GAPS * (len(hp) + 1) + 1, ids))
+    rec, off = tasks_of(rng, hp + lp, exec_of, gap_of)
     prof, d_off, o_prof = check_profile(rec, off)
     h, l = (a.ravel().astype(np.uint32) for a in np.meshgrid(range(len(hp)), range(len(hp), len(hp) + len(lp)), indexing="ij"))
-    assert h.size <= TEAM_SCENARIOS < 6 * h.size and (int(off[-1]) // (off.size - 1) >= TEAM_LAUNCHES) == team
-    assert int(off[-1]) // (off.size - 1) >= REPEAT_LAUNCHES
+    assert h.size <= TEAM_SCENARIOS < 6 * h.size
     d_gap, gap = check_measure(rec, off)
     for copies, margin, min_gap in ((1, 0, 0), (1, 50, 500)) + ((6, 20, 0),) * (not team):
         hs, ls = np.tile(h, copies), np.tile(l, copies)
@@ -78,11 +78,15 @@ def test_what_repeats_is_copied(times, team):
         assert names & REPLAYS == {"k_gf_replay_team" if team else "k_gf_replay_wave"}
 
 
-@pytest.mark.parametrize("n_scen,launches,team", [
-    (TEAM_SCENARIOS, TEAM_LAUNCHES, True), (TEAM_SCENARIOS + 1, TEAM_LAUNCHES, False), (3, TEAM_LAUNCHES, True), (3, TEAM_LAUNCHES - 1, False)])
-def test_a_workgroup_takes_a_scenario_while_all_fit(n_scen, launches, team):
-    rng = np.random.default_rng(launches)
-    rec, off = tasks_of(rng, [passes(rng, 200, launches, 20), passes(rng, 160, launches, 20)], rng.integers(100, 4000, 23), rng.integers(0, 3000, 23))
+# Tasks that no scenario uses do not count: neither a long one beside short scenarios nor short ones beside long scenarios.
+@pytest.mark.parametrize("n_scen,gaps,unused,team", [
+    (TEAM_SCENARIOS, TEAM_GAPS, [], True), (TEAM_SCENARIOS + 1, TEAM_GAPS, [], False),
+    (3, TEAM_GAPS, [], True), (3, TEAM_GAPS - 1, [], False),
+    (3, 100, [3 * TEAM_GAPS], False), (3, TEAM_GAPS, [100] * 40, True)])
+def test_a_workgroup_takes_a_scenario_while_all_fit(n_scen, gaps, unused, team):
+    rng = np.random.default_rng(gaps)
+    rec, off = tasks_of(rng, [passes(rng, 200, gaps + 1, 20), passes(rng, 160, gaps + 1, 20)] + [passes(rng, 50, n, 20) for n in unused],
+                        rng.integers(100, 4000, 23), rng.integers(0, 3000, 23))
     prof, d_off, o_prof = check_profile(rec, off)
     d_gap, gap = check_measure(rec, off)
     hs, ls = np.zeros(n_scen, np.uint32), np.ones(n_scen, np.uint32)
