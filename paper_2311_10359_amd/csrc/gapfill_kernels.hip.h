@@ -865,7 +865,9 @@ constexpr uint32_t REPEAT_GAPS = 2048, REPEAT_ENTRIES = 1024;
 constexpr uint32_t REPEAT_WORTH = 8;
 constexpr uint32_t REPEAT_LEAST = 128;     // a shorter period counts as a multiple of it, so that a round has few places to look at
 constexpr uint32_t REPEAT_NOTES = 48;      // places noted; the period is doubled at every 16th (at every eighth: 256 long traces 345 -> 367 us)
-constexpr uint32_t REPEAT_MISSES = 4;      // starts of a period (counted once) and repeats (twice) that may turn out to be none
+// Starts of a period (counted once) and repeats (twice) that may turn out to be none; one that held for REPEAT_ANCHOR gaps has paid for
+// the search, and the count starts again.
+constexpr uint32_t REPEAT_MISSES = 4;
 // Gaps from a start without a period after which another start is looked for, and how often; then the search ends.  What comes before
 // the first pass may be 2048 launches long, and a pass 4096.
 constexpr uint32_t REPEAT_ANCHOR = 2048, REPEAT_ANCHORS = 2;
@@ -1178,6 +1180,7 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
     if (!REPEATS || !rep.units) break;
     if (TEAM > 1) share(rep);
     uint32_t queue_at = wb + o;   // (the window is read again behind the copy: it needs the registers)
+    const uint32_t units = rep.units;
     while (rep.X > rep.x0) {
       const RepeatSums part = repeat_copy<MODE, TEAM>(rep, 0, H, trace, queue, fill_count + g0, filled_ns + g0, &team);
       if (!repeat_shorten(rep, part)) {
@@ -1188,7 +1191,11 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
         queue_at = rep.X == n_gaps ? queue_at + part.c : rep.ja + rep.units * rep.dq;
         break;
       }
-      search.miss(2); search.period = 0; search.anchor = 0;   // (the walk goes on behind what holds and looks for another period)
+    }
+    if (rep.units != units) {   // something differed: the walk goes on behind what held and looks for another period
+      if (i0 < rep.x0 + REPEAT_ANCHOR) search.miss(2);
+      else search.misses = 0;
+      search.period = 0; search.anchor = 0;
     }
     if (i0 == n_gaps) { wb = queue_at; o = 0; break; }   // (the last launch's time has been added too)
     load_window(queue_at);

@@ -4,8 +4,9 @@ move, by a workgroup per scenario and by a wave, against the CPU oracle."""
 import numpy as np
 import pytest
 
-from paper_2311_10359_amd import traces
+from paper_2311_10359_amd import binding, traces
 from parity_util import check_gapfill, check_profile, kernels_of
+from repeat_model import follow
 from test_gpu_replay import check_measure, check_replay
 
 pytestmark = pytest.mark.gpu
@@ -94,3 +95,42 @@ def test_a_workgroup_takes_a_scenario_while_all_fit(n_scen, gaps, unused, team):
         check_gapfill(prof, d_off, off, o_prof, hs, ls, 0, 0)
         check_replay(prof, d_off, off, o_prof, d_gap, gap, hs, ls, 0, 0)
     assert names & (WALKS | REPLAYS) == ({"k_gf_walk_team", "k_gf_replay_team"} if team else {"k_gf_walk_wave", "k_gf_replay_wave"})
+
+
+def walk_ms(prof, d_off, off, o_prof, hs, ls):
+    """Least time of the walk of a gap fill in four calls, whose results are checked."""
+    ms = []
+    for _ in range(4):
+        binding.fikit_trace_enable(True)
+        try:
+            check_gapfill(prof, d_off, off, o_prof, hs, ls, 0, 0)
+            times = binding.fikit_trace_read()
+        finally:
+            binding.fikit_trace_enable(False)
+        ms += [t for name, (t, _) in times.items() if name in WALKS]
+    assert len(ms) == 4
+    return min(ms)
+
+
+@pytest.mark.parametrize("team", [True, False])
+def test_what_repeats_is_not_walked(team):
+    """A trace that repeats, one that does but for a launch in every 15,000, and one that does not: copying shows in the time (measured:
+    0.29, 3.5 and 7.9 ms by a workgroup, 0.88, 3.6 and 7.6 by a wave; 0.98 and 0.63 of the first two are copied).  Short scenarios beside
+    them bring the average down to the walk by wave."""
+    rng, n, ids = np.random.default_rng(11), 120000, 200
+    e, g = rng.integers(1000, 12000, ids + 3), rng.integers(0, 30000, ids + 3)
+    order = rng.permutation(ids)
+    whole = np.resize(order, n)
+    odd = whole.copy()
+    odd[15000::15000] = ids + np.arange(odd[15000::15000].size) % 3
+    short = np.resize(order, 100)
+    kids = [whole, odd, rng.permutation(whole), passes(rng, 160, 3 * n, ids), short]
+    rec, off = tasks_of(rng, kids, e, g)
+    prof, d_off, o_prof = check_profile(rec, off)
+    few = 0 if team else 40
+    ms = []
+    for trace in (0, 1, 2):
+        hs, ls = np.array([trace] * 4 + [4] * few, np.uint32), np.array([3] * 4 + [4] * few, np.uint32)
+        ms.append(walk_ms(prof, d_off, off, o_prof, hs, ls))
+    print(f"walk in ms: {ms}", flush=True)
+    assert ms[0] < 0.4 * ms[2] and ms[1] < 0.6 * ms[2], ms
