@@ -10,7 +10,7 @@ import numpy as np
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2311_10359_amd", "csrc")
 
 
-def constants():
+def limits():
     """REPEAT_* and GF_* limits of the walk by their names in the source."""
     got = {}
     for name in ("gapfill_kernels.hip.h", "fikit.hip"):
@@ -22,18 +22,18 @@ def constants():
     return got
 
 
-C = constants()
+LIMITS = limits()
 ROUND, BLOCK = 256, 64
 
 
 def follow(G, q, counts, team):
-    """G: idle time after each launch of the trace, q: the queue's durations, counts: entries that each gap took.  Counter of what
-    happens, with `copied` gaps."""
-    seen = Counter()
+    """G: idle time after each launch of the trace, q: the queue's durations, counts: entries that each gap took.  Returns a Counter of
+    what happens, with the number of `copied` gaps, and the first repeat that is compared: gap, entry, gaps and entries of a unit."""
+    seen, repeat = Counter(), None
     n_gaps, L = len(counts), len(q)
     J = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)      # where the queue stands before each gap
     gaps, q = G[:n_gaps], np.asarray(q)
-    until = n_gaps - ROUND if n_gaps >= C["REPEAT_GAPS"] and L >= C["REPEAT_ENTRIES"] else 0
+    until = n_gaps - ROUND if n_gaps >= LIMITS["REPEAT_GAPS"] and L >= LIMITS["REPEAT_ENTRIES"] else 0
 
     def next_entries(j):
         return q[np.minimum(np.arange(j, j + BLOCK), L - 1)]
@@ -45,10 +45,10 @@ def follow(G, q, counts, team):
         if not period:
             if first >= next_anchor:
                 anchor, tries = first, tries + 1
-                if tries > C["REPEAT_ANCHORS"]:
+                if tries > LIMITS["REPEAT_ANCHORS"]:
                     seen["no_period"] += 1
                     break
-                next_anchor = first + C["REPEAT_ANCHOR"] * (1 if tries < C["REPEAT_ANCHORS"] else 2)
+                next_anchor = first + LIMITS["REPEAT_ANCHOR"] * (1 if tries < LIMITS["REPEAT_ANCHORS"] else 2)
             x = np.arange(first, first + ROUND)
             hit = (G[x] == G[anchor]) & (G[x + 1] == G[anchor + 1]) & ((x - first) % BLOCK != BLOCK - 1) & (x != anchor)
             if hit.any():
@@ -59,14 +59,14 @@ def follow(G, q, counts, team):
         if start is not None:
             if start + BLOCK <= len(G) and np.array_equal(G[anchor:anchor + BLOCK], G[start:start + BLOCK]):
                 period = start - anchor
-                if period < C["REPEAT_LEAST"]:
-                    period *= -(-C["REPEAT_LEAST"] // period)
+                if period < LIMITS["REPEAT_LEAST"]:
+                    period *= -(-LIMITS["REPEAT_LEAST"] // period)
                     seen["short_period"] += 1
                 place, notes = anchor + period, [(anchor, int(J[anchor]))]
             else:
                 seen["false_start"] += 1
                 misses += 1
-                if misses >= C["REPEAT_MISSES"]:
+                if misses >= LIMITS["REPEAT_MISSES"]:
                     until = 0
         if not period or place > i0:
             continue
@@ -87,7 +87,7 @@ def follow(G, q, counts, team):
             if there == 0:
                 seen["queue_ends"] += 1
                 until = 0
-            if not team and dq < D // C["REPEAT_WORTH"]:
+            if not team and dq < D // LIMITS["REPEAT_WORTH"]:
                 seen["not_worth"] += 1
                 units = until = 0
             if units:
@@ -96,13 +96,14 @@ def follow(G, q, counts, team):
         if len(notes) % 16 == 0:
             seen["doubled"] += 1
             period *= 2
-        if len(notes) >= C["REPEAT_NOTES"]:
+        if len(notes) >= LIMITS["REPEAT_NOTES"]:
             seen["all_notes"] += 1
             until = 0
         place += period
         if not units:
             continue
         # what is compared
+        repeat = repeat or (a, ja, D, dq)
         at = np.arange(a, X)
         bad = np.flatnonzero(gaps[at] != gaps[a - D + (at - a) % D])
         bad_x = int(at[bad[0]]) if bad.size else None
@@ -119,9 +120,9 @@ def follow(G, q, counts, team):
                 if n < hold:
                     seen["cut_by_gap_and_entry"] += cut == "gap"
                     hold, cut = n, "entry"
-                    seen["entry_at_place"] += bad_y == ja
-                    seen["entry_behind_unit"] += bad_y > ja and (bad_y - ja) % dq == 0
-                    seen["entry_last_of_unit"] += bad_y > ja and (bad_y - ja) % dq == dq - 1
+                    if a + hold * D > i0:
+                        seen["entry_behind_unit"] += (bad_y - ja) % dq == 0
+                        seen["entry_last_of_unit"] += (bad_y - ja) % dq == dq - 1
         end = n_gaps if hold == wanted else a + hold * D
         copied = max(0, end - i0)
         if copied:
@@ -137,8 +138,8 @@ def follow(G, q, counts, team):
         else:
             seen["nothing_held_" + (cut or "")] += 1
         if cut:
-            misses = misses + 2 if copied < C["REPEAT_ANCHOR"] else 0
-            if misses >= C["REPEAT_MISSES"]:
+            misses = misses + 2 if copied < LIMITS["REPEAT_ANCHOR"] else 0
+            if misses >= LIMITS["REPEAT_MISSES"]:
                 until = 0
                 seen["gave_up"] += 1
             period, anchor, tries, next_anchor = 0, 0, 0, 0
@@ -146,4 +147,4 @@ def follow(G, q, counts, team):
             i0 = end
             if period:
                 place = end + period
-    return seen
+    return seen, repeat

@@ -1,19 +1,21 @@
 """The walk where inputs repeat and results are copied: periods around the sizes of a block, a round and the shortest period that is
 noted, traces and queues that stop repeating somewhere, a first pass unlike the others, queues that end inside a copied unit or never
-move, by a workgroup per scenario and by a wave, against the CPU oracle."""
+move, by a workgroup per scenario and by a wave, against the CPU oracle.  Which ways through the search and the copy these inputs take
+is checked in test_repeat_model.py."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2311_10359_amd import binding, traces
 from parity_util import check_gapfill, check_profile, kernels_of
-from repeat_model import follow
+from repeat_model import LIMITS, follow
 from test_gpu_replay import check_measure, check_replay
 
 pytestmark = pytest.mark.gpu
 
 # Up to so many scenarios, if they have so many gaps on average, a workgroup takes each, otherwise a wave.  Repeats are looked
 # for in traces of REPEAT_GAPS gaps and more.
-TEAM_SCENARIOS, TEAM_GAPS, REPEAT_GAPS = 768, 16384, 2048
+TEAM_SCENARIOS, TEAM_GAPS, REPEAT_GAPS = LIMITS["GF_TEAM_SCENARIOS"], LIMITS["GF_TEAM_GAPS"], LIMITS["REPEAT_GAPS"]
 
 WALKS, REPLAYS = {"k_gf_walk_wave", "k_gf_walk_team", "k_gf_walk_lanes"}, {"k_gf_replay_wave", "k_gf_replay_team", "k_gf_replay_lanes"}
 
@@ -40,9 +42,8 @@ def tasks_of(rng, kids, exec_of, gap_of):
     return rec, np.concatenate([[0], np.cumsum([k.size for k in kids])]).astype(np.uint64)
 
 
-@pytest.mark.parametrize("times", ["few", "many", "stuck", "zeros", "wide_sums"])
-@pytest.mark.parametrize("team", [True, False])
-def test_what_repeats_is_copied(times, team):
+def grid(times, team):
+    """Traces and queues in all pairs: kernel numbers of the tasks, durations and idle times, high- and low-priority tasks."""
     rng = np.random.default_rng(sum(map(ord, times)))
     ids = 23
     exec_of, gap_of = rng.integers(100, 4000, ids + 3), rng.integers(0, 3000, ids + 3)
@@ -52,8 +53,9 @@ def test_what_repeats_is_copied(times, team):
         exec_of[::4] = 1 << 20
     elif times == "zeros":
         exec_of[::2], gap_of[::3] = 0, 0
+        gap_of *= 2
     elif times == "wide_sums":
-        exec_of, gap_of = exec_of << 19, gap_of << 19
+        exec_of, gap_of = exec_of << 19, np.minimum(4 * gap_of, 8191) << 19
     hp = [passes(rng, p, n, ids, odd, first) for p, n, odd, first in (
         (1, 2500, (), 0), (2, 2900, (600,), 0), (7, 4097, (), 0), (63, REPEAT_GAPS, (), 0), (64, REPEAT_GAPS + 1, (), 0),
         (65, REPEAT_GAPS + 2, (1300, 1301), 0), (127, 3000, (), 0), (128, 3000, (2999,), 0), (129, 3000, (2998,), 0), (200, 5000, (), 0), (200, 5000, (900, 2100, 3300, 4400), 0),
@@ -63,12 +65,48 @@ def test_what_repeats_is_copied(times, team):
         (600, 9000, ()), (4000, 4000, ()), (1, 1, ()))]
     if team:   # (a trace that alone brings the average there)
         hp.append(passes(rng, 50, TEAM_GAPS * (len(hp) + 1) + 1, ids))
-    rec, off = tasks_of(rng, hp + lp, exec_of, gap_of)
-    prof, d_off, o_prof = check_profile(rec, off)
     h, l = (a.ravel().astype(np.uint32) for a in np.meshgrid(range(len(hp)), range(len(hp), len(hp) + len(lp)), indexing="ij"))
-    assert h.size <= TEAM_SCENARIOS < 6 * h.size
+    return hp + lp, exec_of, gap_of, h, l
+
+
+def stops(team):
+    """One trace of kernels that are all different, long enough for many repeats, and queues of which one entry differs: inside the fourth
+    unit that is compared, its last one, the one behind it; passes so long that places repeat only after the period has been doubled; one
+    that never repeats.  The same with a trace that stops repeating soon, and with one that goes on repeating behind a launch.  As grid()."""
+    rng, ids, n = np.random.default_rng(3), 200, 30000
+    exec_of, gap_of = rng.integers(1000, 12000, ids + 3), rng.integers(0, 30000, ids + 3)
+    whole, queue = np.resize(rng.permutation(ids), n), passes(rng, 160, 3 * n, ids)
+    rec, off = tasks_of(rng, [whole, queue], exec_of, gap_of)
+    o_ids, o_rows, o_tro = oracle.profile(rec, off)
+    pair = np.array([0], np.uint32), np.array([1], np.uint32)
+    counts = oracle.gapfill(o_ids, off, o_rows, o_tro, *pair, 0, 0, traces.gap_offsets(off, pair[0]))[0]
+    a, ja, D, dq = follow(gap_of[whole], exec_of[queue], counts, team)[1]
+
+    def but_for(kid, at):
+        kid = kid.copy()
+        kid[at] = ids
+        return kid
+
+    odd, late = but_for(whole, a + 5 * D + 3), but_for(whole, n // 2)
+    queues = [queue] + [but_for(queue, ja + at) for at in (3 * dq + dq // 2, 4 * dq - 1, 4 * dq)]
+    queues += [passes(rng, 6007, 3 * n, ids), passes(rng, 7001, 3 * n, ids), rng.integers(0, ids, 3 * n)]
+    kids = [whole, odd, late] + queues
+    h, l = np.repeat([0, 1, 2], len(queues)), np.tile(3 + np.arange(len(queues)), 3)
+    if not team:   # (short scenarios, which bring the average down to the walk by wave)
+        kids.append(np.resize(whole, 100))
+        h, l = (np.concatenate([x, np.full(2 * x.size, len(kids) - 1)]) for x in (h, l))
+    return kids, exec_of, gap_of, h.astype(np.uint32), l.astype(np.uint32)
+
+
+@pytest.mark.parametrize("times", ["few", "many", "stuck", "zeros", "wide_sums", "stops"])
+@pytest.mark.parametrize("team", [True, False])
+def test_what_repeats_is_copied(times, team):
+    kids, exec_of, gap_of, h, l = stops(team) if times == "stops" else grid(times, team)
+    rec, off = tasks_of(np.random.default_rng(1), kids, exec_of, gap_of)
+    prof, d_off, o_prof = check_profile(rec, off)
+    assert h.size <= TEAM_SCENARIOS
     d_gap, gap = check_measure(rec, off)
-    for copies, margin, min_gap in ((1, 0, 0), (1, 50, 500)) + ((6, 20, 0),) * (not team):
+    for copies, margin, min_gap in ((1, 0, 0), (1, 50, 500)) + ((-(-(TEAM_SCENARIOS + 1) // h.size), 20, 0),) * (not team):
         hs, ls = np.tile(h, copies), np.tile(l, copies)
         print(f"{hs.size} scenarios, {times}, margin {margin}", flush=True)
         with kernels_of() as names:
