@@ -702,20 +702,20 @@ constexpr uint64_t GF_PAD = 256;
 // The line lies where the first of these shapes has the waves and the lanes level; with feedback it has from about 24,000 scenarios
 // on, but what gaps take is not known when the line is drawn.
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
-// Up to this many scenarios of so many gaps on average, a workgroup takes each: one of its waves walks, all copy what
+// Up to this many scenarios of traces of so many launches on average, a workgroup takes each: one of its waves walks, all copy what
 // repeats.  Three workgroups of eight waves are on a compute unit at a time, so the 769th waits until a scenario is through (traces
 // and queues of 16,384 launches that never repeat, in us by a wave / by a workgroup each: 768 scenarios 441 / 455, 784 429 / 563, 1024
-// 447 / 700).  Shorter traces are copied fast enough by one wave, and the walk by the first of several is 2 to 4 % slower (256 scenarios,
-// queues four times as long as the traces, repeating: 4096 launches 222 / 223, 8192 249 / 231, 16,384 310 / 263, 32,768 439 / 273; never
-// repeating: 334 / 341, 618 / 634, 1195 / 1228, 2320 / 2387).  Of 256 scenarios of 65,535 gaps, four waves take 382 us, eight 355, sixteen
-// 341, but of workgroups of sixteen waves only 256 would be there at a time.
-constexpr uint64_t GF_TEAM_SCENARIOS = 768, GF_TEAM_GAPS = 16384;
+// 447 / 700).  Shorter traces are copied fast enough by one wave, and the walk by the first of several is 2 to 4 % slower (queues four times
+// as long as the traces, repeating, 16 scenarios: 4096 launches 195 / 185, 8192 190 / 154, 16,384 265 / 176, 32,768 381 / 201; 256
+// scenarios: 222 / 223, 249 / 231, 310 / 263, 439 / 273; never repeating: 334 / 341, 618 / 634, 1195 / 1228, 2320 / 2387).  Of 256 scenarios of
+// 65,535 gaps, four waves take 382 us, eight 355, sixteen 341, but of workgroups of sixteen waves only 256 would be there at a time.
+constexpr uint64_t GF_TEAM_SCENARIOS = 768, GF_TEAM_LAUNCHES = 8192;
 constexpr int GF_TEAM_WAVES = 8;
 // From this average on some traces are long enough for the search (if lengths are spread up to twice the average).  The walk with it
 // has 67 registers instead of 54, which many scenarios feel.  Without / with it in us: 12,000 scenarios of 1000 gaps 312 / 318, 30,000
 // 252 / 256, 12,000 ragged ones of 700 on average 369 / 373; 64 of 1500 gaps 73 / 73; 6000 ragged ones of 1400 on average 390 / 356 (if they
 // repeat) and 377 / 380 (if not), 12,000 of 2100 563 / 449 and 559 / 563.
-constexpr uint64_t GF_REPEAT_GAPS = REPEAT_GAPS / 2;
+constexpr uint64_t GF_REPEAT_LAUNCHES = REPEAT_GAPS / 2;
 
 }  // extern "C"
 
@@ -819,14 +819,14 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
                        d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
                        d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, prof, row_capacity, b.ctrl);
   } else {
-    // gaps of a scenario on average; in a step, where the host does not read their number, launches of a task
-    const uint64_t gaps = n_gaps != ANY_GAPS ? n_gaps / n_scenarios : b.n_ids / n_tasks;
-    const bool teams = MODE != LW_REPLAY_FEEDBACK && n_scenarios <= GF_TEAM_SCENARIOS && gaps >= GF_TEAM_GAPS;
+    // launches of a trace on average; in a step, where the host does not read the number of gaps, of a task
+    const uint64_t launches = n_gaps != ANY_GAPS ? n_gaps / n_scenarios + 1 : b.n_ids / n_tasks;
+    const bool teams = MODE != LW_REPLAY_FEEDBACK && n_scenarios <= GF_TEAM_SCENARIOS && launches >= GF_TEAM_LAUNCHES;
     tr.mark(MODE == LW_PLAN ? (teams ? "k_gf_walk_team" : "k_gf_walk_wave")
                             : MODE == LW_REPLAY ? (teams ? "k_gf_replay_team" : "k_gf_replay_wave") : "k_gf_replay_feedback_wave");
     auto kernel = &k_gf_walk_wave<MODE, 0>;
     if constexpr (MODE != LW_REPLAY_FEEDBACK)
-      kernel = teams ? &k_gf_walk_wave<MODE, GF_TEAM_WAVES> : gaps >= GF_REPEAT_GAPS ? &k_gf_walk_wave<MODE, 1> : kernel;
+      kernel = teams ? &k_gf_walk_wave<MODE, GF_TEAM_WAVES> : launches >= GF_REPEAT_LAUNCHES ? &k_gf_walk_wave<MODE, 1> : kernel;
     hipLaunchKernelGGL(kernel, dim3(teams ? static_cast<uint32_t>(n_scenarios) : blocks_for(n_scenarios, WW_THREADS / WAVE)),
                        dim3(teams ? GF_TEAM_WAVES * WAVE : WW_THREADS), 0, st, d_task_offsets, d_hp_task, d_lp_task,
                        static_cast<uint32_t>(n_scenarios), d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,

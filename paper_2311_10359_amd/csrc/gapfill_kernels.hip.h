@@ -658,11 +658,16 @@ __device__ __forceinline__ uint32_t write_lane_u32(uint32_t v, uint32_t value, u
 __device__ __forceinline__ uint32_t sat32(uint64_t v) { return v > WIDE32 ? WIDE32 : static_cast<uint32_t>(v); }
 
 // Before the loop over the gaps that take something: it is 116 to 148 bytes long and runs as one wave's chain, so that it matters where
-// the instructions lie in the 32 bytes that are fetched at a time.  From the middle of such a piece on is the best place in all of its
-// forms; where the compiler happens to put it costs up to 7 %.  Gap fills in us, 256 scenarios of 65,535 gaps that never repeat, for
+// the instructions lie in the 32 bytes that are fetched at a time.  Between byte 8 and 16 of such a piece is the best place in all of
+// its forms; where the compiler happens to put it costs up to 7 %.  Gap fills in us, 256 scenarios of 65,535 gaps that never repeat, for
 // starts at byte 0, 4, 8, 12, 16, 20, 24: by a wave 1532, 1564, 1473, 1489, 1466, 1487, 1558; by eight 1560, 1579, 1502, 1491, 1500, 1524, 1584.
-// (The instructions that fill the piece are run once per block of 64 gaps.)
-__device__ __forceinline__ void place_loop() { asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0"); }
+// The instructions that fill the piece are run once per block of 64 gaps, so there should be few (where nearly every gap takes
+// something, 256 long scenarios by eight waves: 358 us with three, 361 with four).
+template <int TEAM>
+__device__ __forceinline__ void place_loop() {
+  if constexpr (TEAM > 1) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+  else asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0");
+}
 
 // The wave's scenario: its own number, or what order holds at that place.  (Everything that is the same in the whole wave is kept in
 // scalar registers: the scenario number has to be seen as one.)
@@ -1036,7 +1041,8 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
 
   uint64_t time_line = 0, consumed = 0, delay = 0;   // (per lane; summed over the lanes at the end)
   RepeatSearch search;
-  search.until = REPEATS && n_gaps >= REPEAT_GAPS && L >= REPEAT_ENTRIES ? n_gaps - 64 * WW_BLOCKS : 0u;   // (what lies behind the round can be copied)
+  // (what lies behind a round can be copied)
+  search.until = REPEATS && n_gaps >= REPEAT_GAPS && L >= REPEAT_ENTRIES ? n_gaps - 64 * WW_BLOCKS : 0u;
 
   uint32_t i0 = 0;
   for (;;) {
@@ -1079,7 +1085,7 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
           // (one way out of the loop, at its end, and the rare case inside it: otherwise the compiler carries flags and copies
           // through every gap)
           if (takes) {
-            place_loop();
+            place_loop<TEAM>();
             do {
               k = static_cast<uint32_t>(__builtin_ctzll(takes));
               uint64_t todo = (~1ull) << k;

@@ -13,9 +13,9 @@ from test_gpu_replay import check_measure, check_replay
 
 pytestmark = pytest.mark.gpu
 
-# Up to so many scenarios, if they have so many gaps on average, a workgroup takes each, otherwise a wave.  Repeats are looked
+# Up to so many scenarios, if their traces have so many launches on average, a workgroup takes each, otherwise a wave.  Repeats are looked
 # for in traces of REPEAT_GAPS gaps and more.
-TEAM_SCENARIOS, TEAM_GAPS, REPEAT_GAPS = LIMITS["GF_TEAM_SCENARIOS"], LIMITS["GF_TEAM_GAPS"], LIMITS["REPEAT_GAPS"]
+TEAM_SCENARIOS, TEAM_LAUNCHES, REPEAT_GAPS = LIMITS["GF_TEAM_SCENARIOS"], LIMITS["GF_TEAM_LAUNCHES"], LIMITS["REPEAT_GAPS"]
 
 WALKS, REPLAYS = {"k_gf_walk_wave", "k_gf_walk_team", "k_gf_walk_lanes"}, {"k_gf_replay_wave", "k_gf_replay_team", "k_gf_replay_lanes"}
 
@@ -64,7 +64,7 @@ def grid(times, team):
         (1, 5000, ()), (13, 3000, ()), (63, 6000, ()), (160, 9000, ()), (160, 9000, (700, 3000)), (160, 400, ()), (161, 1000, (999,)), (64, 64, ()),
         (600, 9000, ()), (4000, 4000, ()), (1, 1, ()))]
     if team:   # (a trace that alone brings the average there)
-        hp.append(passes(rng, 50, TEAM_GAPS * (len(hp) + 1) + 1, ids))
+        hp.append(passes(rng, 50, TEAM_LAUNCHES * (len(hp) + 1), ids))
     h, l = (a.ravel().astype(np.uint32) for a in np.meshgrid(range(len(hp)), range(len(hp), len(hp) + len(lp)), indexing="ij"))
     return hp + lp, exec_of, gap_of, h, l
 
@@ -94,7 +94,7 @@ def stops(team):
     h, l = np.repeat([0, 1, 2], len(queues)), np.tile(3 + np.arange(len(queues)), 3)
     if not team:   # (short scenarios, which bring the average down to the walk by wave)
         kids.append(np.resize(whole, 100))
-        h, l = (np.concatenate([x, np.full(2 * x.size, len(kids) - 1)]) for x in (h, l))
+        h, l = (np.concatenate([x, np.full(3 * x.size, len(kids) - 1)]) for x in (h, l))
     return kids, exec_of, gap_of, h.astype(np.uint32), l.astype(np.uint32)
 
 
@@ -118,13 +118,13 @@ def test_what_repeats_is_copied(times, team):
 
 
 # Tasks that no scenario uses do not count: neither a long one beside short scenarios nor short ones beside long scenarios.
-@pytest.mark.parametrize("n_scen,gaps,unused,team", [
-    (TEAM_SCENARIOS, TEAM_GAPS, [], True), (TEAM_SCENARIOS + 1, TEAM_GAPS, [], False),
-    (3, TEAM_GAPS, [], True), (3, TEAM_GAPS - 1, [], False),
-    (3, 100, [3 * TEAM_GAPS], False), (3, TEAM_GAPS, [100] * 40, True)])
-def test_a_workgroup_takes_a_scenario_while_all_fit(n_scen, gaps, unused, team):
-    rng = np.random.default_rng(gaps)
-    rec, off = tasks_of(rng, [passes(rng, 200, gaps + 1, 20), passes(rng, 160, gaps + 1, 20)] + [passes(rng, 50, n, 20) for n in unused],
+@pytest.mark.parametrize("n_scen,launches,unused,team", [
+    (TEAM_SCENARIOS, TEAM_LAUNCHES, [], True), (TEAM_SCENARIOS + 1, TEAM_LAUNCHES, [], False),
+    (3, TEAM_LAUNCHES, [], True), (3, TEAM_LAUNCHES - 1, [], False),
+    (3, 100, [3 * TEAM_LAUNCHES], False), (3, TEAM_LAUNCHES, [100] * 40, True)])
+def test_a_workgroup_takes_a_scenario_while_all_fit(n_scen, launches, unused, team):
+    rng = np.random.default_rng(launches)
+    rec, off = tasks_of(rng, [passes(rng, 200, launches, 20), passes(rng, 160, launches, 20)] + [passes(rng, 50, n, 20) for n in unused],
                         rng.integers(100, 4000, 23), rng.integers(0, 3000, 23))
     prof, d_off, o_prof = check_profile(rec, off)
     d_gap, gap = check_measure(rec, off)

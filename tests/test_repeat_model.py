@@ -43,5 +43,5 @@ def test_the_inputs_take_every_way(team):
 
 
 def test_the_limits_are_read_from_the_source():
-    assert {"GF_TEAM_SCENARIOS", "GF_TEAM_GAPS", "GF_REPEAT_GAPS", "REPEAT_GAPS", "REPEAT_ENTRIES", "REPEAT_WORTH", "REPEAT_LEAST", "REPEAT_NOTES",
+    assert {"GF_TEAM_SCENARIOS", "GF_TEAM_LAUNCHES", "GF_REPEAT_LAUNCHES", "REPEAT_GAPS", "REPEAT_ENTRIES", "REPEAT_WORTH", "REPEAT_LEAST", "REPEAT_NOTES",
             "REPEAT_MISSES", "REPEAT_ANCHOR", "REPEAT_ANCHORS"} <= set(LIMITS)
