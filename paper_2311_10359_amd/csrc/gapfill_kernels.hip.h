@@ -695,10 +695,10 @@ __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint3
 // step of this waits for the one before, so it runs at the rate of the memory instead of at the length of a chain.
 //
 // Traces of passes reach such a place after two to five periods as a rule: whatever the queue's first entry was, it soon stands at one
-// that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 345 (the
-// slowest wave walks 21,000 gaps), 16,384 of 4095 7740 / 7360 (the walk 1170 / 775: 1100 gaps walked, 2600 copied, and the queue's
-// 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 377.  Kernels drawn at random never repeat and pay for the search:
-// about 0.3 us a round while it lasts (24 rounds as a rule), then one comparison a round.
+// that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 347 (the
+// slowest wave walks 21,000 gaps), 16,384 of 4095 7565 / 7130 (the walk 1170 / 775: 1100 gaps walked, 2600 copied, and the queue's
+// 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 379.  Kernels drawn at random never repeat and pay for the search: about
+// 0.3 us a round while it lasts (24 rounds as a rule), then one comparison a round (the same calls 635 / 656, 7755 / 7775, 386 / 387).
 // The rounds without the search as a second copy of the code: 82 to 86 registers instead of 67 to 71, and both copies' loops are compiled
 // worse (256 traces of 65,535 gaps that never repeat 1518 -> 1648 us, the step of 16,384 7760 -> 7960).
 struct Repeat {
@@ -862,7 +862,7 @@ __device__ __forceinline__ void repeat_helper(uint32_t wave, uint32_t H, const u
 }
 
 // Where it is worth the search.  The search costs a wave 1 to 2 us until there is a period and 0.4 us a note; 64 traces of 1500 gaps
-// (a call of 75 us) gain nothing by it, 6000 of up to 2800 gaps 393 -> 367 us.  A queue of a few passes is soon used up, or hardly moves.
+// (a call of 73 us) gain nothing by it, 6000 of up to 2800 gaps 396 -> 379 us.  A queue of a few passes is soon used up, or hardly moves.
 constexpr uint32_t REPEAT_GAPS = 2048, REPEAT_ENTRIES = 1024;
 // A wave by itself copies a gap in 9 to 16 cycles and walks one that takes nothing in 5, one that takes something in 100 and more: a unit
 // is copied if at least every eighth of its gaps takes something (three traces of 12,192 gaps whose queue hardly moves, all copied
