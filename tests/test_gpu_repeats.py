@@ -59,10 +59,10 @@ def grid(times, team):
     hp = [passes(rng, p, n, ids, odd, first) for p, n, odd, first in (
         (1, 2500, (), 0), (2, 2900, (600,), 0), (7, 4097, (), 0), (63, REPEAT_GAPS, (), 0), (64, REPEAT_GAPS + 1, (), 0),
         (65, REPEAT_GAPS + 2, (1300, 1301), 0), (127, 3000, (), 0), (128, 3000, (2999,), 0), (129, 3000, (2998,), 0), (200, 5000, (), 0), (200, 5000, (900, 2100, 3300, 4400), 0),
-        (255, 2500, (), 0), (256, 2561, (1280,), 0), (257, 2571, (), 0), (600, 6000, (), 300), (200, 8000, (5000,), 2300), (3000, 5900, (), 0))]
+        (255, 2500, (), 0), (256, 2561, (1280,), 0), (257, 2571, (), 0), (600, 6000, (), 300), (200, 8000, (5000,), 2300), (3000, 5900, (), 0), (7, 0, (), 0), (7, 1, (), 0))]
     lp = [passes(rng, p, n, ids, odd, 0) for p, n, odd in (
         (1, 5000, ()), (13, 3000, ()), (63, 6000, ()), (160, 9000, ()), (160, 9000, (700, 3000)), (160, 400, ()), (161, 1000, (999,)), (64, 64, ()),
-        (600, 9000, ()), (4000, 4000, ()), (1, 1, ()))]
+        (600, 9000, ()), (4000, 4000, ()), (1, 1, ()), (1, 0, ()))]
     if team:   # (a trace that alone brings the average there)
         hp.append(passes(rng, 50, TEAM_LAUNCHES * (len(hp) + 1), ids))
     h, l = (a.ravel().astype(np.uint32) for a in np.meshgrid(range(len(hp)), range(len(hp), len(hp) + len(lp)), indexing="ij"))
