@@ -29,14 +29,15 @@
  * Conventions
  *   - d_* arguments are device pointers, h_* are host pointers.  The caller owns every buffer,
  *     including the workspace; the library allocates no device memory and its results depend
- *     on nothing but a call's arguments (the only things it keeps between calls are 256 bytes of
+ *     on nothing but a call's arguments (the only things it keeps between calls are 320 bytes of
  *     pinned host memory per calling thread, through which counts and status come back and which
  *     are freed when the thread ends, the measurement aid fikit_trace_*, the bound of
  *     fikit_set_wait_limit and the scratch address of fikit_gapfill_static).  Inputs are left
  *     untouched.
  *   - All work is enqueued on `hip_stream` (a hipStream_t passed as void*; NULL = the default
- *     stream).  Every call but fikit_gapfill_static synchronises that stream before it returns, so
- *     outputs and the returned status are final on return.
+ *     stream).  Every call but fikit_gapfill_static waits until its work there is done
+ *     before it returns, so outputs and the returned status are final on return, for every stream,
+ *     copy and thread.
  *   - Return value: FIKIT_OK or a negative fikit_status.  Nothing aborts or throws.  After an
  *     error the contents of the output buffers are unspecified.
  *   - Everything is integer arithmetic (nanoseconds, counts); results are exact.
@@ -255,7 +256,7 @@ size_t fikit_measure_workspace_bytes(void);
  *               task's next launch - end_ns), or -1 for the last launch of a run or task.
  *   d_workspace 256-byte aligned, at least fikit_measure_workspace_bytes() bytes.
  *
- * Buffers are the caller's; the call synchronises the stream.  Errors: INVALID_ARG,
+ * Buffers are the caller's; the call waits for its work.  Errors: INVALID_ARG,
  * WORKSPACE_TOO_SMALL, BAD_RECORD, HIP_ERROR.
  */
 int fikit_measure(const fikit_launch* d_records, uint64_t n_records, const uint64_t* d_task_offsets,
@@ -372,7 +373,7 @@ size_t fikit_pairing_workspace_bytes(uint32_t n_tasks);
  *                      2^32 - 1 and 0.
  *   d_workspace        256-byte aligned, at least fikit_pairing_workspace_bytes(n_tasks) bytes.
  *
- * Buffers are the caller's; the call synchronises the stream.
+ * Buffers are the caller's; the call waits for its work.
  * Errors: INVALID_ARG (also: task index out of range, gap offsets not monotone),
  * WORKSPACE_TOO_SMALL, HIP_ERROR.
  */
@@ -404,7 +405,7 @@ size_t fikit_profile_merge_workspace_bytes(uint32_t n_tasks);
  *   d_task_row_offsets_out [n_tasks+1], h_n_rows   as in fikit_profile (also on FIKIT_ROW_CAPACITY).
  *   d_workspace        256-byte aligned, at least fikit_profile_merge_workspace_bytes(n_tasks) bytes.
  *
- * The output must not overlap the inputs.  Buffers are the caller's; the call synchronises the stream.
+ * The output must not overlap the inputs.  Buffers are the caller's; the call waits for its work.
  * Errors: INVALID_ARG, WORKSPACE_TOO_SMALL, ROW_CAPACITY, HIP_ERROR.
  */
 int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_offsets_a,

@@ -10,6 +10,22 @@ __global__ void k_clear_ctrl(Ctrl* ctrl) {
   if (threadIdx.x < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[threadIdx.x] = 0;
 }
 
+// Words for the host: stored in its memory, and behind them, once they are there, the number that it waits for.  One wave.
+constexpr int REPORT_READS = 4;
+struct Report {
+  const uint32_t* from[REPORT_READS];
+  uint32_t* to[REPORT_READS];
+  uint32_t words[REPORT_READS];
+};
+__global__ void __launch_bounds__(WAVE)
+k_report(const Report r, uint32_t* seen, uint32_t number) {
+#pragma unroll
+  for (int i = 0; i < REPORT_READS; ++i)
+    if (threadIdx.x < r.words[i]) r.to[i][threadIdx.x] = r.from[i][threadIdx.x];
+  __threadfence_system();
+  if (threadIdx.x == 0) __hip_atomic_store(seen, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Fills `count` 32-bit words with `value` (used instead of memset so that a caller may capture
 // the stream into a graph).
 __global__ void k_fill_u32(uint32_t* __restrict__ p, uint64_t count, uint32_t value) {
