@@ -1424,26 +1424,29 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
   unsigned char* ws = static_cast<unsigned char*>(d_workspace);
   Carver c;
   Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + c.take(256));
-  long long* soonest = reinterpret_cast<long long*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 8));
-  long long* top_filled = reinterpret_cast<long long*>(d_best_filled_ns);
+  long long* top_filled = reinterpret_cast<long long*>(ws + c.take(static_cast<uint64_t>(n_tasks) * 8));
   unsigned long long* best_scenario = reinterpret_cast<unsigned long long*>(d_best_scenario);
 
   Tracer tr(st);
   tr.mark("pair_setup");
   hipLaunchKernelGGL(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks,
-                     n_scenarios > 0 ? d_gap_offsets + n_scenarios : static_cast<const uint64_t*>(nullptr), top_filled, soonest, best_scenario, ctrl);
+                     n_scenarios > 0 ? d_gap_offsets + n_scenarios : static_cast<const uint64_t*>(nullptr), top_filled, best_scenario,
+                     d_best_lp, d_best_filled_ns, ctrl);
   if (n_scenarios > 0) {
     tr.mark("k_pair_sum");
-    hipLaunchKernelGGL(k_pair_sum, dim3(static_cast<uint32_t>(n_scenarios)), dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task,
-                       n_scenarios, n_tasks, d_gap_offsets, d_filled_ns, d_scenario_filled_ns, top_filled, ctrl);
+    const bool waves = n_scenarios >= PAIR_WAVES;
+    const uint64_t most = waves ? PAIR_STAY : n_scenarios;
+    const uint64_t groups = waves ? (n_scenarios + PAIR_THREADS / WAVE - 1) / (PAIR_THREADS / WAVE) : n_scenarios;
+    hipLaunchKernelGGL(waves ? k_pair_sum<WAVE> : k_pair_sum<PAIR_THREADS>, dim3(static_cast<uint32_t>(groups < most ? groups : most)),
+                       dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task, static_cast<uint32_t>(n_scenarios), n_tasks, d_gap_offsets,
+                       d_filled_ns, d_scenario_filled_ns, top_filled, ctrl);
     tr.mark("k_pair_pick");
-    hipLaunchKernelGGL(k_pair_soonest, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_hp_task, n_scenarios,
-                       d_scenario_filled_ns, d_lp_completion_ns, top_filled, soonest, ctrl);
-    hipLaunchKernelGGL(k_pair_first, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_hp_task, n_scenarios,
-                       d_scenario_filled_ns, d_lp_completion_ns, top_filled, soonest, best_scenario, ctrl);
+    hipLaunchKernelGGL(k_pair_pick, dim3(blocks_for(n_scenarios, PAIR_THREADS)), dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task, n_scenarios,
+                       n_tasks, d_scenario_filled_ns, d_lp_completion_ns, top_filled, best_scenario, d_best_lp, d_best_filled_ns, ctrl);
+    if (n_tasks > PAIR_LAST_TASKS)
+      hipLaunchKernelGGL(k_pair_finish, dim3(blocks_for(n_tasks, PAIR_THREADS)), dim3(PAIR_THREADS), 0, st, n_tasks, d_lp_task,
+                         d_scenario_filled_ns, best_scenario, d_best_lp, d_best_filled_ns, ctrl);
   }
-  hipLaunchKernelGGL(k_pair_finish, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks, d_lp_task, best_scenario,
-                     d_best_lp, top_filled, ctrl);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};

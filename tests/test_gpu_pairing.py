@@ -53,6 +53,15 @@ def test_pairing_random_inputs_with_many_ties():
     assert (got[3] == 0).all()
 
 
+@pytest.mark.parametrize("n_scen", [8191, 8192, 8193, 16384, 20001])      # workgroups, then waves: a full round, one more, a ragged one
+@pytest.mark.parametrize("n_tasks,values", [(1, 1), (512, 4), (513, 4)])   # the last workgroup writes the results, then a launch
+def test_pairing_by_waves(n_scen, n_tasks, values):
+    rng = np.random.default_rng(n_scen + n_tasks)
+    hp, lp, go, fn, comp = random_pairing(rng, n_tasks, n_scen, 150, values)
+    print(f"{n_tasks} tasks, {n_scen} scenarios, {fn.size} gaps", flush=True)
+    check_pairing(hp, lp, n_tasks, go, fn, comp)
+
+
 def test_pairing_of_a_grid_of_gap_fills():
     cfg = traces.config(1, n_tasks=24, launches=4000)          # 12 x 12 combinations
     rec, off = traces.build(cfg, threads=4)
