@@ -92,7 +92,8 @@ struct ProfileBegin {
   uint32_t *gflag, *dcount, *lists, *long_prefix, *tile_prefix, *wflag;
   Ctrl* ctrl;
 };
-__device__ __forceinline__ void profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBegin& a) {
+// (off: the task offsets, in LDS)
+__device__ __forceinline__ void profile_begin(const uint64_t* off, uint32_t n_tasks, const ProfileBegin& a) {
   const uint64_t n = a.n;
   const uint32_t len_small = a.len_small, len_mid = a.len_mid, len_max = a.len_max, tile = a.tile;
   uint32_t* __restrict__ gflag = a.gflag;
@@ -150,9 +151,6 @@ __device__ __forceinline__ void profile_begin(const uint64_t* __restrict__ off, 
     *ctrl = c;
   }
 }
-__global__ void __launch_bounds__(BEGIN_THREADS)
-k_profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBegin a) { profile_begin(off, n_tasks, a); }
-
 // Execution time and idle time of every launch as they stand in the trace (Section 3.2, "Measuring the
 // execution and idle time of kernel"); task boundaries are put right by k_measure_task_ends afterwards.
 __global__ void __launch_bounds__(256)

@@ -957,12 +957,21 @@ k_gather_rows(const uint64_t* __restrict__ off, const uint64_t* __restrict__ row
   }
 }
 
-// The first checks of a profile and of the gap fill that follows it in the same call.
-static_assert(BEGIN_THREADS == GF_BEGIN_THREADS, "one workgroup for both");
+// The first checks of a profile, and of a profile and the gap fill that follows it in the same call.
+static_assert(BEGIN_THREADS == GF_BEGIN_THREADS && BEGIN_TASKS == GF_BEGIN_ITEMS, "one workgroup for both");
+__global__ void __launch_bounds__(BEGIN_THREADS)
+k_profile_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBegin p) {
+  __shared__ BeginOffsets sm;
+  begin_offsets(sm, off, n_tasks);
+  profile_begin(sm.off, n_tasks, p);
+}
 __global__ void __launch_bounds__(BEGIN_THREADS)
 k_step_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBegin p, const GfBegin g) {
-  profile_begin(off, n_tasks, p);
-  gf_begin(off, n_tasks, p.n, g);
+  __shared__ BeginOffsets sm;
+  const GfFirst first(g);
+  begin_offsets(sm, off, n_tasks);
+  profile_begin(sm.off, n_tasks, p);
+  gf_begin(sm, n_tasks, p.n, g, first);
 }
 
 // Row offsets, their total and the rows themselves in one launch, for few tasks of which none is long: every workgroup adds up the
