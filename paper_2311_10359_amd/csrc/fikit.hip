@@ -118,7 +118,7 @@ int scan_u32(uint32_t* d_data, uint64_t count, uint32_t* d_sums, uint64_t* d_tot
 // 64-bit offsets and their total (ctrl->n_rows) from `count` 32-bit row counts, the last of which is 0; see k_row_offsets.
 int row_offsets_enqueue(const uint32_t* d_counts, uint64_t count, uint32_t* d_sums, uint64_t* d_out, Ctrl* ctrl, hipStream_t st) {
   if (count <= ROW_SCAN_ONE) {
-    hipLaunchKernelGGL(k_row_offsets, dim3(1), dim3(1024), 0, st, d_counts, count, d_out, ctrl);
+    hipLaunchKernelGGL(k_row_offsets, dim3(blocks_for(count, ROW_SCAN_TILE)), dim3(1024), 0, st, d_counts, count, d_out, ctrl);
   } else {
     const uint32_t nb = blocks_for(count, SCAN_TILE);
     hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums);
@@ -176,7 +176,7 @@ struct Tracer {
 };
 
 int status_from_bits(uint32_t bits) {
-  if (bits & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS | ERR_ACTUAL_GAP | ERR_LP_LIST | ERR_ROWS)) return FIKIT_INVALID_ARG;
+  if (bits & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS | ERR_ACTUAL_GAP | ERR_LP_LIST | ERR_ROWS | ERR_TOO_MANY)) return FIKIT_INVALID_ARG;
   if (bits & ERR_BAD_RECORD) return FIKIT_BAD_RECORD;
   if (bits & ERR_UNKNOWN_ID) return FIKIT_UNKNOWN_ID;
   if (bits & ERR_LP_LIMIT) return FIKIT_UNSUPPORTED;
@@ -1476,13 +1476,15 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   if (workspace_bytes < fikit_profile_merge_workspace_bytes(n_tasks)) return FIKIT_WORKSPACE_TOO_SMALL;
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  uint64_t na = 0, nb = 0;
-  Reads counts(st);
-  if (int rc = counts.add(&na, d_task_row_offsets_a + n_tasks, 8)) return rc;
-  if (int rc = counts.add(&nb, d_task_row_offsets_b + n_tasks, 8)) return rc;
-  if (int rc = counts.wait()) return rc;
-  if (na >= MAX_ELEMS || nb >= MAX_ELEMS || na + nb >= MAX_ELEMS) return FIKIT_INVALID_ARG;
-  if ((na > 0 && !d_rows_a) || (nb > 0 && !d_rows_b)) return FIKIT_INVALID_ARG;
+  // The numbers of rows live on the device, whose first kernel looks at them; the host only waits for them where a table may be missing.
+  if (!d_rows_a || !d_rows_b) {
+    uint64_t na = 0, nb = 0;
+    Reads counts(st);
+    if (int rc = counts.add(&na, d_task_row_offsets_a + n_tasks, 8)) return rc;
+    if (int rc = counts.add(&nb, d_task_row_offsets_b + n_tasks, 8)) return rc;
+    if (int rc = counts.wait()) return rc;
+    if ((na > 0 && !d_rows_a) || (nb > 0 && !d_rows_b)) return FIKIT_INVALID_ARG;
+  }
 
   unsigned char* ws = static_cast<unsigned char*>(d_workspace);
   Carver c;
@@ -1493,25 +1495,20 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   Tracer tr(st);
   tr.mark("merge_count");
   const uint32_t grid = n_tasks < 65536u ? n_tasks : 65536u;
-  // Tables of few rows on average: the kernel with the small LDS tables, and the tasks that do not fit them by list.
-  const bool small = (na + nb) / n_tasks <= MERGE_IDS_SMALL / 2;
-  const uint64_t most_large = small ? (na + nb) / (MERGE_IDS_SMALL + 1) : 0;
-  const uint32_t list_grid = static_cast<uint32_t>(most_large < grid ? most_large : grid);
-  // (the list lives where nothing else does at that time: in the row offsets before they exist, in the row counts after)
-  auto pass = [&](auto all, auto small_all, auto listed, uint32_t* list) {
-    hipLaunchKernelGGL(small ? small_all : all, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
-                       d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, na, nb, row_capacity,
-                       small ? list : static_cast<uint32_t*>(nullptr), ctrl);
-    if (list_grid > 0)
-      hipLaunchKernelGGL(listed, dim3(list_grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b,
-                         d_task_row_offsets_b, n_tasks, dcount, d_task_row_offsets_out, d_rows_out, na, nb, row_capacity, list, ctrl);
+  // The kernel with the small LDS tables takes every task, and puts those that do not fit them on a list for the one with the larger
+  // tables; or that one takes all (k_merge_begin).  (The list lives where nothing else does at that time: in the row offsets before they exist, in the row counts after.)
+  const uint32_t large_grid = n_tasks < MERGE_LARGE_WORKGROUPS ? n_tasks : MERGE_LARGE_WORKGROUPS;
+  auto pass = [&](auto small, auto large, uint32_t* list) {
+    hipLaunchKernelGGL(small, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,
+                       n_tasks, dcount, d_task_row_offsets_out, d_rows_out, row_capacity, list, ctrl);
+    hipLaunchKernelGGL(large, dim3(large_grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,
+                       n_tasks, dcount, d_task_row_offsets_out, d_rows_out, row_capacity, list, ctrl);
   };
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  pass(k_merge<0, MERGE_IDS, false>, k_merge<0, MERGE_IDS_SMALL, false>, k_merge<0, MERGE_IDS, true>,
-       reinterpret_cast<uint32_t*>(d_task_row_offsets_out));
+  hipLaunchKernelGGL(k_merge_begin, dim3(1), dim3(64), 0, st, d_task_row_offsets_a + n_tasks, d_task_row_offsets_b + n_tasks, n_tasks, MAX_ELEMS, ctrl);
+  pass(k_merge<0, MERGE_IDS_SMALL, false>, k_merge<0, MERGE_IDS, true>, reinterpret_cast<uint32_t*>(d_task_row_offsets_out));
   if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets_out, ctrl, st)) return rc;
   tr.mark("k_merge_rows");   // (does nothing if a check failed or the rows are too many)
-  pass(k_merge<1, MERGE_IDS, false>, k_merge<1, MERGE_IDS_SMALL, false>, k_merge<1, MERGE_IDS, true>, dcount);
+  pass(k_merge<1, MERGE_IDS_SMALL, false>, k_merge<1, MERGE_IDS, true>, dcount);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};

@@ -13,6 +13,7 @@ constexpr int MERGE_THREADS = 256;
 // of 20,000 tasks of 90 + 90 rows: 269 us with three, 182 us with seven; 146 us, 4.7 TB/s, since a lane moves 16 bytes and rows
 // that go nowhere are not read).  Tables beyond the larger number are searched in memory.
 constexpr uint32_t MERGE_IDS = 3072, MERGE_IDS_SMALL = 1024;
+constexpr uint32_t MERGE_LARGE_WORKGROUPS = 12 * 256;   // of the larger tables, four for each that the chip holds; they take the tasks in turn
 
 template <uint32_t IDS>
 struct MergeSmem {
@@ -73,25 +74,44 @@ __device__ __forceinline__ void merge_write_round(const MergeSmem<IDS>& sm, cons
   }
 }
 
+// The control block, and what the host would have to wait for before anything runs (20,000 tasks of 90 + 90 rows, call 271 us with that
+// wait, 262 us without): whether there are more rows than can be merged (`most` or more of both together), and which tables
+// take the tasks (Ctrl::wide).  With MERGE_IDS_SMALL rows in both tables of a task together on average, most fit the small ones, and the
+// few that do not are listed; beyond it the list would hold too many, and the larger tables take all tasks (us with the list / without: 1000
+// tasks of 2000 + 2000 rows 484 / 460, 3000 of 1100 + 1100 664 / 594; 3000 of 700 + 700 368 / 376, 7945 of 349 + 349 427 / 449, the last
+// two and the ones without the list with the host's wait, 8 us).
+__global__ void k_merge_begin(const uint64_t* __restrict__ n_a, const uint64_t* __restrict__ n_b, uint32_t n_tasks, uint64_t most, Ctrl* ctrl) {
+  const uint64_t a = *n_a, b = *n_b;
+  const uint32_t i = threadIdx.x;
+  Ctrl c{};
+  c.status = a >= most || b >= most || a + b >= most ? ERR_TOO_MANY : 0u;
+  c.wide = (a + b) / n_tasks > MERGE_IDS_SMALL ? 1u : 0u;
+  if (i == 0) *ctrl = c;
+}
+
 // MODE 0: checks both inputs of a task (task field, IDs strictly ascending) and counts the rows of the
 // union into dcount[t].  MODE 1: writes the union's rows at row_off[t].. in ID order.
 // One workgroup per task; rank of an ID in the union = IDs below it in a + IDs below it in b - IDs below
 // it that are in both (a running count of the matched rows seen so far).
-// LIST: the tasks of list[0 .. ctrl->n_class[MODE]) only.  Otherwise all tasks; if list is not null, those with more than IDS
-// rows in a table are put on it instead.
-template <int MODE, uint32_t IDS, bool LIST>
+// LARGE: with larger tables, either the tasks of list[0 .. ctrl->n_class[MODE]) or all (Ctrl::wide).  Otherwise all tasks or none; those
+// with more than IDS rows in a table are put on the list instead.
+template <int MODE, uint32_t IDS, bool LARGE>
 __global__ void __launch_bounds__(MERGE_THREADS, IDS == MERGE_IDS_SMALL ? 7 : 3)
 k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, const fikit_row* __restrict__ b,
         const uint64_t* __restrict__ b_off, uint32_t n_tasks, uint32_t* dcount,
-        const uint64_t* row_off, fikit_row* __restrict__ out, uint64_t n_a, uint64_t n_b, uint64_t capacity,
-        uint32_t* list, Ctrl* ctrl) {
+        const uint64_t* row_off, fikit_row* __restrict__ out, uint64_t capacity, uint32_t* list, Ctrl* ctrl) {
   __shared__ MergeSmem<IDS> sm;
-  if (MODE == 1 && (ctrl->status || ctrl->n_rows > capacity)) return;   // (enqueued before the host knows)
+  // (MODE 0: only the bit of k_merge_begin: the others are set by workgroups of this launch)
+  if (MODE == 0 ? (ctrl->status & ERR_TOO_MANY) != 0 : (ctrl->status || ctrl->n_rows > capacity)) return;   // (enqueued before the host knows)
+  const bool all = ctrl->wide != 0;
+  if (MODE == 0 && !LARGE && blockIdx.x == 0 && threadIdx.x == 0) dcount[n_tasks] = 0;   // (the scan leaves the total here)
+  if (!LARGE && all) return;
+  const uint64_t n_a = a_off[n_tasks], n_b = b_off[n_tasks];
   const uint32_t tid = threadIdx.x;
-  const uint32_t items = LIST ? ctrl->n_class[MODE] : n_tasks;
+  const uint32_t items = LARGE && !all ? ctrl->n_class[MODE] : n_tasks;
   for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
     // (the rows are written from the last task to the first: what the counting pass read last is still in the cache)
-    const uint32_t t = LIST ? list[item] : MODE == 1 ? items - 1 - item : item;
+    const uint32_t t = LARGE && !all ? list[item] : MODE == 1 ? items - 1 - item : item;
     const uint64_t a0 = a_off[t], a1 = a_off[t + 1], b0 = b_off[t], b1 = b_off[t + 1];
     // (n_a, n_b: the rows there are; with this every row read is in bounds, whatever the other offsets say)
     if (a1 < a0 || b1 < b0 || a1 > n_a || b1 > n_b || a1 - a0 >= (1ull << 32) || b1 - b0 >= (1ull << 32) || (t == 0 && (a0 != 0 || b0 != 0))) {
@@ -102,7 +122,7 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
     const fikit_row* ra = a + a0;
     const fikit_row* rb = b + b0;
     const bool in_lds = na <= IDS && nb <= IDS;
-    if (!LIST && list && !in_lds) {   // (the same for all threads)
+    if (!LARGE && !in_lds) {   // (the same for all threads)
       if (tid == 0) list[atomicAdd(&ctrl->n_class[MODE], 1u)] = t;
       continue;
     }
@@ -169,7 +189,6 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
       if (tid == 0) dcount[t] = na + nb - matched;
     }
   }
-  if (MODE == 0 && !LIST && blockIdx.x == 0 && tid == 0) dcount[n_tasks] = 0;   // (the scan leaves the total here)
 }
 
 }  // namespace fikit

@@ -69,26 +69,35 @@ __global__ void k_widen_offsets(const uint32_t* __restrict__ in, uint64_t count,
 
 // Row offsets from row counts (count = tasks + 1 entries, the last 0), and the number of rows.  Not for a call that has
 // failed, nor while tasks are left to the general path, whose rows are not counted yet: the host enqueues this before it
-// knows.  One workgroup for as many tasks as it sums up faster than three dependent launches do (about 14 us): 8192 counts
-// take it 4.8 us, 20,000 take it 21 us.
-constexpr uint64_t ROW_SCAN_ONE = 8192;
+// knows.  A workgroup takes ROW_SCAN_TILE counts and sums up those before them for itself, so that nothing waits for another
+// workgroup: what the last one reads, 1 MiB at ROW_SCAN_ONE, takes it less time than two further launches that wait for each other
+// (us between events, one launch / three, those one more: 20,001 counts 25 / 27, 131,073 24 / 29, 262,144 24 / 31).
+constexpr uint64_t ROW_SCAN_ONE = 1u << 18;
+constexpr uint32_t ROW_SCAN_TILE = 8192;
 __global__ void __launch_bounds__(1024)
 k_row_offsets(const uint32_t* __restrict__ dcount, uint64_t count, uint64_t* __restrict__ out, Ctrl* ctrl) {
-  constexpr int ITEMS = 8;
+  constexpr int ITEMS = ROW_SCAN_TILE / 1024, READS = 8;
   __shared__ uint32_t lds[16];
   if (ctrl->status || ctrl->n_general) return;
-  uint32_t carry = 0;
-  for (uint64_t t0 = 0; t0 < count; t0 += 1024 * ITEMS) {
-    const uint64_t t = t0 + static_cast<uint64_t>(threadIdx.x) * ITEMS;
-    uint32_t v[ITEMS], sum = 0, total;
+  const uint32_t first = blockIdx.x * ROW_SCAN_TILE;
+  const uint4* __restrict__ quads = reinterpret_cast<const uint4*>(dcount);
+  uint32_t before = 0;
+  for (uint32_t q0 = threadIdx.x; q0 < first / 4; q0 += READS * 1024) {
+    uint4 v[READS];
 #pragma unroll
-    for (int k = 0; k < ITEMS; ++k) { v[k] = t + k < count ? dcount[t + k] : 0u; sum += v[k]; }
-    uint32_t run = carry + block_excl_scan_1024(sum, lds, total);
+    for (int k = 0; k < READS; ++k) v[k] = q0 + k * 1024 < first / 4 ? quads[q0 + k * 1024] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int k = 0; k < ITEMS; ++k) { if (t + k < count) out[t + k] = run; run += v[k]; }
-    carry += total;
+    for (int k = 0; k < READS; ++k) before += v[k].x + v[k].y + v[k].z + v[k].w;
   }
-  if (threadIdx.x == 0) ctrl->n_rows = carry;
+  const uint64_t t = first + static_cast<uint64_t>(threadIdx.x) * ITEMS;
+  uint32_t v[ITEMS], sum = 0, earlier, total;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) { v[k] = t + k < count ? dcount[t + k] : 0u; sum += v[k]; }
+  (void)block_excl_scan_1024(before, lds, earlier);
+  uint32_t run = earlier + block_excl_scan_1024(sum, lds, total);
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) { if (t + k < count) out[t + k] = run; run += v[k]; }
+  if (threadIdx.x == 0 && blockIdx.x + 1 == gridDim.x) ctrl->n_rows = earlier + total;
 }
 __global__ void __launch_bounds__(SCAN_BLOCK)
 k_row_offsets_apply(const uint32_t* __restrict__ dcount, uint64_t count, const uint32_t* __restrict__ block_sums,

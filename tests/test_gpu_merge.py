@@ -85,6 +85,43 @@ def test_merge_random_tables(n_tasks, max_ids, pool):
     check_merge(a, ao, a, ao)
 
 
+@pytest.mark.parametrize("most_small,large", [(8, (1024, 1025, 1500)), (8, (3072, 3073)), (500, (1100, 4000)), (700, (1025,)), (1400, ())])
+def test_merge_of_small_tables_beside_large_ones(most_small, large):
+    # (few large tables are listed; with many rows on average all tasks take the larger tables)
+    rng = np.random.default_rng(most_small + len(large))
+    n_tasks = 40
+    pool = [np.unique(rng.integers(0, 2**64, 12000, dtype=np.uint64)) for _ in range(n_tasks)]
+    sizes = rng.integers(0, most_small + 1, n_tasks)
+    a, b = [], []
+    for t in range(n_tasks):
+        n = int(sizes[t]) if t not in (3, 17, 39)[:len(large)] else large[(3, 17, 39).index(t)]
+        for out, k in ((a, n), (b, n // 2)):
+            ids = np.sort(rng.choice(pool[t], k, replace=False))
+            r = np.zeros(k, dtype=oracle.ROW_DTYPE)
+            r["kernel_id"], r["task"] = ids, t
+            for blk in ("exec", "gap"):
+                r[blk]["count"] = rng.integers(1, 9, k)
+                r[blk]["sum"] = rng.integers(0, 2**62, k)
+                for f in ("min", "max", "p50", "p95"):
+                    r[blk][f] = rng.integers(0, 10**6, k)
+            out.append(r)
+    offs = [np.concatenate([[0], np.cumsum([r.size for r in side])]).astype(np.uint64) for side in (a, b)]
+    check_merge(np.concatenate(a), offs[0], np.concatenate(b), offs[1])
+
+
+@pytest.mark.parametrize("n_tasks", [8190, 8191, 8192, 16383, 16384, 20000])   # row counts around whole tiles of the scan
+def test_row_offsets_of_many_tasks(n_tasks):
+    rng = np.random.default_rng(n_tasks)
+    sizes = rng.integers(0, 4, n_tasks)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    rows = np.zeros(int(off[-1]), dtype=oracle.ROW_DTYPE)
+    rows["kernel_id"] = np.arange(rows.size)
+    rows["task"] = np.repeat(np.arange(n_tasks), sizes)
+    for blk in ("exec", "gap"):
+        rows[blk]["count"] = 1
+    check_merge(rows, off, rows[:0], np.zeros(n_tasks + 1, dtype=np.uint64))
+
+
 def test_merge_of_runs_feeds_the_gap_fill():
     cfg = traces.config(4, n_tasks=40, hp_launches=500, lp_launches=1500)
     rec, off = traces.build(cfg, threads=4)
