@@ -92,6 +92,11 @@ __device__ __forceinline__ uint4 load_once(const uint4* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+typedef uint64_t u64x2_native __attribute__((ext_vector_type(2), aligned(8)));
+// Stores that tell the caches the same of what they write.
+__device__ __forceinline__ void store_once(uint64_t* p, uint64_t v) { __builtin_nontemporal_store(v, p); }
+__device__ __forceinline__ void store_once(int64_t* p, int64_t v) { __builtin_nontemporal_store(v, p); }
+
 // Stores to `bytes` bytes from p on (the same in the whole wave): what a lane writes behind them is dropped by the
 // hardware, without a branch.
 typedef __amdgpu_buffer_rsrc_t bounded;
