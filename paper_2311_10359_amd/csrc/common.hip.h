@@ -93,9 +93,17 @@ __device__ __forceinline__ uint4 load_once(const uint4* p) {
 }
 
 typedef uint64_t u64x2_native __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ ulonglong2 load_once(const ulonglong2* p) {
+  const u64x2_native v = __builtin_nontemporal_load(reinterpret_cast<const u64x2_native*>(p));
+  return make_ulonglong2(v.x, v.y);
+}
 // Stores that tell the caches the same of what they write.
 __device__ __forceinline__ void store_once(uint64_t* p, uint64_t v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void store_once(int64_t* p, int64_t v) { __builtin_nontemporal_store(v, p); }
+__device__ __forceinline__ void store_once(ulonglong2* p, ulonglong2 v) {
+  const u64x2_native w = {v.x, v.y};
+  __builtin_nontemporal_store(w, reinterpret_cast<u64x2_native*>(p));
+}
 
 // Stores to `bytes` bytes from p on (the same in the whole wave): what a lane writes behind them is dropped by the
 // hardware, without a branch.

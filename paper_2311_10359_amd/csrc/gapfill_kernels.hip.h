@@ -550,7 +550,7 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
     uint64_t id0 = 0, id1 = 0;
     const bool two = i0 + 1 < len;
     if (ids_vec && two) {
-      const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(ids + base + i0);
+      const ulonglong2 v = load_once(reinterpret_cast<const ulonglong2*>(ids + base + i0));   // (2 % of the kernel)
       id0 = v.x; id1 = v.y;
     } else {
       id0 = ids[base + i0];

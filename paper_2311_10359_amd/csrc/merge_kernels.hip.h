@@ -56,7 +56,8 @@ __device__ __forceinline__ uint64_t merge_field(uint32_t f, uint64_t x, uint64_t
 
 // Writes the planned rows of a round (sm.place / sm.partner, `rows` of them, taken from src[first ..]): eight
 // lanes per row, two 8-byte fields each, so that a wave reads and writes whole rows side by side.  Rows that go nowhere
-// (they went out with their partner) are not read.
+// (they went out with their partner) are not read.  Neither is needed again, and the caches keep what the next tasks' searches read: 20,000
+// tasks of 90 + 90 rows, call 262 us with ordinary reads and writes, 242 with the hint on the writes, 231 with it on both.
 template <uint32_t IDS>
 __device__ __forceinline__ void merge_write_round(const MergeSmem<IDS>& sm, const fikit_row* __restrict__ src, uint32_t first,
                                                   uint32_t rows, const fikit_row* __restrict__ other, fikit_row* __restrict__ out) {
@@ -65,12 +66,12 @@ __device__ __forceinline__ void merge_write_round(const MergeSmem<IDS>& sm, cons
   for (uint32_t r = tid >> 3; r < rows; r += MERGE_THREADS / 8) {      // (the eight lanes of a row stay together)
     const uint32_t place = sm.place[r], partner = sm.partner[r];
     if (place == MERGE_NONE) continue;
-    ulonglong2 v = reinterpret_cast<const ulonglong2*>(src + first + r)[f];
+    ulonglong2 v = load_once(reinterpret_cast<const ulonglong2*>(src + first + r) + f);
     ulonglong2 y = make_ulonglong2(0, 0);
-    if (partner != MERGE_NONE) y = reinterpret_cast<const ulonglong2*>(other + partner)[f];
+    if (partner != MERGE_NONE) y = load_once(reinterpret_cast<const ulonglong2*>(other + partner) + f);
     const uint64_t cx = shfl_u64(v.x, count_lane), cy = shfl_u64(y.x, count_lane);
     if (partner != MERGE_NONE) v = make_ulonglong2(merge_field(2 * f, v.x, y.x, cx, cy), merge_field(2 * f + 1, v.y, y.y, cx, cy));
-    reinterpret_cast<ulonglong2*>(out + place)[f] = v;
+    store_once(reinterpret_cast<ulonglong2*>(out + place) + f, v);
   }
 }
 
