@@ -513,7 +513,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     hipLaunchKernelGGL(k_tile_partition, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(PT_THREADS), sizeof(PartSmem), st, d_records,
                        d_task_offsets, n_tasks, mtiles, is_long, ids, k1, part_kg, bound, bucket_size, wflag, ctrl);
     tr.mark("k_msd_units");
-    hipLaunchKernelGGL(k_msd_units, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, d_task_offsets, n_tasks, is_long, mtiles, bucket_size, wflag,
+    hipLaunchKernelGGL(k_msd_units, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, d_task_offsets, n_tasks, is_long, mtiles, bucket_size, ustage, wflag,
                        ustart, ulen, utask, udcount, ubuckets, mflag, gflag, lists, static_cast<uint32_t>(n_units), ctrl);
     FusedArgs ua = fa;
     ua.pred_role = nullptr;   // (units are parts of tasks: their task's predictions are left to the gap fill)

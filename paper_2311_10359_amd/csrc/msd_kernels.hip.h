@@ -49,6 +49,7 @@ constexpr uint64_t STREAM_MIN = 1u << 18;
 //   256 of 262,144: 1.92 / 1.82   16 of 1,048,576: 0.60 / 0.60
 constexpr uint64_t UNIT_SMALL_TASK = 1u << 17;
 constexpr uint32_t STREAM_HUGE = 1u << 16;           // streamed units beyond this are started first
+constexpr uint32_t STREAM_LONGEST = 1u << 17;        // and counted beyond this (see k_unit_large)
 constexpr uint32_t PT_ROWS = MSD_SLOTS + 1;          // rows of a task's boundary table: bucket 0 .. 256 (= the tile's end)
 static_assert(PT_TILE <= 0xffffu, "bucket boundaries inside a tile are stored in 16 bits");
 static_assert(MSD_SLOTS == 256, "the scans over a task's slots are those of a 256-thread block");
@@ -219,7 +220,7 @@ k_tile_partition(const fikit_launch* __restrict__ rec, const uint64_t* __restric
 // together write the unit slots and the work lists.  bucket_size: the task's bucket sizes as the tiles added them up.
 __global__ void __launch_bounds__(MSD_SLOTS)
 k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* __restrict__ long_prefix,
-            const uint32_t* __restrict__ tile_prefix, const uint32_t* __restrict__ bucket_size, const uint32_t* __restrict__ wflag,
+            const uint32_t* __restrict__ tile_prefix, const uint32_t* bucket_size, uint32_t* ustage, const uint32_t* __restrict__ wflag,
             uint32_t* __restrict__ ustart, uint32_t* __restrict__ ulen, uint32_t* __restrict__ utask,
             uint32_t* __restrict__ udcount, uint32_t* __restrict__ ubuckets, uint32_t* __restrict__ mflag,
             uint32_t* __restrict__ gflag, uint32_t* __restrict__ lists, uint32_t list_stride, Ctrl* ctrl) {
@@ -277,6 +278,7 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
   const uint32_t u = o * MSD_SLOTS + d;
   utask[u] = t;
   udcount[u] = 0;
+  ustage[u] = ~0u;   // (SU_UNPLACED; in the place of this thread's own bucket size)
   const bool live = d < used;
   const uint32_t first = live ? ufirst[d] : 0u, past = live ? after[first] : 0u;
   const uint32_t l = live ? bstart[past] - bstart[first] : 0u;
@@ -287,6 +289,7 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
   // unit bumped on its own would serialise the whole launch on one address)
   // (list 3: streamed units, huge ones from its front and the others from its back)
   const bool streamed = live && (l > FUSE_MAX || tiles_t > UNIT_RUNS_MAX);
+  if (streamed && l > STREAM_LONGEST) atomicAdd(&ctrl->n_class[5], 1u);
   const uint32_t c = !live ? 5u : streamed ? (l > STREAM_HUGE ? 3u : 4u) : (l <= FUSE_SMALL_MAX ? 0u : (l <= FUSE_MID_MAX ? 1u : 2u));
   __syncthreads();   // (aux is reused)
   for (uint32_t k = 0; k < 5; ++k) {

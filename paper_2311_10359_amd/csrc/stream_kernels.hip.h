@@ -133,12 +133,19 @@ __device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
 // fikit_profile, us, flag looked at at the start only / along the way, with 600 IDs in a bucket of 12,000 launches beside one ID with
 // most of the others: a task of 300,000 launches 1500 / 1185, 16 of them 1830 / 1520, 64 of 1,000,000 11,150 / 9550; profiles of
 // which no task is given up are the same.
+// PART: what of the launches is looked at.
+enum : int { SU_BOTH = 0, SU_EXEC = 1, SU_IDLE = 2 };
+constexpr uint32_t SU_UNPLACED = ~0u;
+template <int PART>
 __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit, uint2* __restrict__ pack_kg_all,
                                               int64_t* __restrict__ pack_slot_all, StreamSmem& sm) {
+  constexpr bool EXEC = PART != SU_IDLE, IDLE = PART != SU_EXEC;
   const uint32_t m = A.ulen[unit], t = A.utask[unit];
   const uint64_t base = A.ustart[unit];
+  // (the two parts of a unit pack for themselves, into a half of its slices each)
   uint2* __restrict__ pack_kg = pack_kg_all + base;
-  uint16_t* __restrict__ pack_slot = reinterpret_cast<uint16_t*>(pack_slot_all + base);
+  uint32_t* __restrict__ pack_v = reinterpret_cast<uint32_t*>(pack_kg) + (PART == SU_IDLE ? m : 0u);
+  uint16_t* __restrict__ pack_slot = reinterpret_cast<uint16_t*>(pack_slot_all + base) + (PART == SU_IDLE ? 2 * static_cast<uint64_t>(m) : 0u);
   const uint32_t tid = threadIdx.x, lane = lane_id();
   const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(tid / WAVE)));
 
@@ -208,26 +215,30 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
             const uint32_t e = kg[r].x, g = kg[r].y;
             uint32_t s = dom_slot;
             if (id[r] == dom_id && dom_slot != SU_HT) {
-              ++dom_c; dom_es += e;
-              dom_en = e < dom_en ? e : dom_en; dom_ex = e > dom_ex ? e : dom_ex;
-              if (g != NONE32) {
+              if (EXEC) {
+                ++dom_c; dom_es += e;
+                dom_en = e < dom_en ? e : dom_en; dom_ex = e > dom_ex ? e : dom_ex;
+              }
+              if (IDLE && g != NONE32) {
                 ++dom_gc; dom_gs += g;
                 dom_gn = g < dom_gn ? g : dom_gn; dom_gx = g > dom_gx ? g : dom_gx;
               }
             } else {
               s = su_slot(sm, id[r]);
               if (s == SU_HT) { atomicOr(&sm.fallback, 1u); s = 0; }
-              atomicAdd(&sm.cnt[s], 1u);
-              atomicAdd(reinterpret_cast<unsigned long long*>(&sm.esum[s]), static_cast<unsigned long long>(e));
-              atomicMin(&sm.emin[s], e); atomicMax(&sm.emax[s], e);
-              if (g != NONE32) {
+              if (EXEC) {
+                atomicAdd(&sm.cnt[s], 1u);
+                atomicAdd(reinterpret_cast<unsigned long long*>(&sm.esum[s]), static_cast<unsigned long long>(e));
+                atomicMin(&sm.emin[s], e); atomicMax(&sm.emax[s], e);
+              }
+              if (IDLE && g != NONE32) {
                 atomicAdd(&sm.gcnt[s], 1u);
                 atomicAdd(reinterpret_cast<unsigned long long*>(&sm.gsum[s]), static_cast<unsigned long long>(g));
                 atomicMin(&sm.gmin[s], g); atomicMax(&sm.gmax[s], g);
               }
             }
             if (rto[r] + x < m) {   // (always: the unit's length is the sum of its runs)
-              pack_kg[rto[r] + x] = kg[r];
+              if (PART == SU_BOTH) pack_kg[rto[r] + x] = kg[r]; else pack_v[rto[r] + x] = EXEC ? e : g;
               pack_slot[rto[r] + x] = static_cast<uint16_t>(s);
             }
           }
@@ -239,10 +250,12 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
       const uint32_t c = wave_sum_u32(dom_c), gc = wave_sum_u32(dom_gc);
       const uint64_t es = wave_sum_u64(dom_es), gs = wave_sum_u64(dom_gs);
       const uint32_t ex = wave_max_u32(dom_ex), gx = wave_max_u32(dom_gx), en = ~wave_max_u32(~dom_en), gn = ~wave_max_u32(~dom_gn);
-      if (lane == 0 && c) {
+      if (EXEC && lane == 0 && c) {
         atomicAdd(&sm.cnt[dom_slot], c);
         atomicAdd(reinterpret_cast<unsigned long long*>(&sm.esum[dom_slot]), static_cast<unsigned long long>(es));
         atomicMin(&sm.emin[dom_slot], en); atomicMax(&sm.emax[dom_slot], ex);
+      }
+      if (IDLE && lane == 0 && gc) {
         atomicAdd(&sm.gcnt[dom_slot], gc);
         atomicAdd(reinterpret_cast<unsigned long long*>(&sm.gsum[dom_slot]), static_cast<unsigned long long>(gs));
         atomicMin(&sm.gmin[dom_slot], gn); atomicMax(&sm.gmax[dom_slot], gx);
@@ -254,7 +267,20 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
   const uint64_t task_start = A.off[t];
   const uint32_t task_len = static_cast<uint32_t>(A.off[t + 1] - task_start);
   const bool fits = !sm.fallback && D <= SU_DMAX && sm.filled == m;
-  if (tid == 0) { sm.given_up = given_up(); sm.first_row = fits ? atomicAdd(&A.staged[t], D) : 0u; A.ustage[unit] = sm.first_row; }
+  if (tid == 0) {
+    sm.given_up = given_up();
+    if (PART == SU_BOTH) {
+      sm.first_row = fits ? atomicAdd(&A.staged[t], D) : 0u;
+      A.ustage[unit] = sm.first_row;
+    } else {   // the rows are where the part that came first has put them (if both come at once, the other's room is left empty)
+      uint32_t at = __hip_atomic_load(&A.ustage[unit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (at == SU_UNPLACED && fits) {
+        const uint32_t room = atomicAdd(&A.staged[t], D), held = atomicCAS(&A.ustage[unit], SU_UNPLACED, room);
+        at = held == SU_UNPLACED ? room : held;
+      }
+      sm.first_row = fits ? at : 0u;
+    }
+  }
   __syncthreads();
   if (sm.given_up) return;   // (the same for all threads)
   const uint32_t row0 = sm.first_row;
@@ -279,8 +305,9 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
     __syncthreads();
   }
   {
-    const bool mine = tid < 2 * D;
-    const uint32_t arr = mine && tid >= D ? 1u : 0u, j = mine ? tid - arr * D : 0u, s = sm.slot_of[j];
+    const bool mine = tid < (PART == SU_BOTH ? 2 * D : D);
+    const uint32_t second = mine && tid >= D ? 1u : 0u, arr = PART == SU_BOTH ? second : PART == SU_EXEC ? 0u : 1u;
+    const uint32_t j = mine ? tid - second * D : 0u, s = sm.slot_of[j];
     const uint32_t n = arr ? sm.gcnt[s] : sm.cnt[s];
     uint32_t bins_log2;
     const uint32_t at = su_share(mine ? su_log2_above(n) : SU_NONE, sm.aux, bins_log2);
@@ -307,15 +334,20 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
 #pragma unroll
     for (uint32_t u = 0; u < SU_KPT; ++u) {
       const uint32_t i = i0 + u * SU_THREADS + tid;
-      kg[u] = make_uint2(0, 0); sl[u] = 0;
-      if (i < m) { kg[u] = pack_kg[i]; sl[u] = pack_slot[i]; }
+      kg[u] = make_uint2(0, NONE32); sl[u] = 0;
+      if (i < m) {
+        if (PART == SU_BOTH) kg[u] = pack_kg[i]; else (EXEC ? kg[u].x : kg[u].y) = pack_v[i];
+        sl[u] = pack_slot[i];
+      }
     }
 #pragma unroll
     for (uint32_t u = 0; u < SU_KPT; ++u) {
       if (i0 + u * SU_THREADS + tid < m) {
-        const uint4 se = sm.sel[0][sl[u]];
-        atomicAdd(&sm.u.hist[sm.room[0][sl[u]] + su_bin(se, kg[u].x)], 1u);
-        if (kg[u].y != NONE32) {
+        if (EXEC) {
+          const uint4 se = sm.sel[0][sl[u]];
+          atomicAdd(&sm.u.hist[sm.room[0][sl[u]] + su_bin(se, kg[u].x)], 1u);
+        }
+        if (IDLE && kg[u].y != NONE32) {
           const uint4 sg = sm.sel[1][sl[u]];
           atomicAdd(&sm.u.hist[sm.room[1][sl[u]] + su_bin(sg, kg[u].y)], 1u);
         }
@@ -325,7 +357,8 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
   if (leave) sm.given_up = 1;
   __syncthreads();
   if (sm.given_up) return;
-  for (uint32_t q = w; q < 4 * D; q += SU_WAVES) {   // (2 * array + percentile, rank); a wave each
+  const uint32_t q_first = EXEC ? 0u : 2 * D, q_past = IDLE ? 4 * D : 2 * D;
+  for (uint32_t q = q_first + w; q < q_past; q += SU_WAVES) {   // (2 * array + percentile, rank); a wave each
     const uint32_t ap = q / D, j = q - ap * D, arr = ap >> 1, s = sm.slot_of[j];
     const uint32_t n = arr ? sm.gcnt[s] : sm.cnt[s];
     if (n == 0) {
@@ -358,7 +391,7 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
     // and wider ones if not.
     {
       const uint32_t ap = tid / SU_DMAX, j = tid % SU_DMAX, arr = ap >> 1, s = j < D ? sm.slot_of[j] : 0u;
-      const bool searched = j < D && (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) != SU_NO_BIN;
+      const bool searched = j < D && (arr ? IDLE : EXEC) && (ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z) != SU_NO_BIN;
       const uint32_t width = searched ? sm.width[ap][j] : 0u, has = searched ? sm.has[ap][j] : 0u;
       const bool list = searched && has <= SU_LIST && width != 0;
       uint32_t granted;
@@ -395,19 +428,22 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
 #pragma unroll
       for (uint32_t u = 0; u < SU_KPT; ++u) {
         const uint32_t i = i0 + u * SU_THREADS + tid;
-        kg[u] = make_uint2(0, 0); sl[u] = 0;
-        if (i < m) { kg[u] = pack_kg[i]; sl[u] = pack_slot[i]; }
+        kg[u] = make_uint2(0, NONE32); sl[u] = 0;
+        if (i < m) {
+          if (PART == SU_BOTH) kg[u] = pack_kg[i]; else (EXEC ? kg[u].x : kg[u].y) = pack_v[i];
+          sl[u] = pack_slot[i];
+        }
       }
 #pragma unroll
       for (uint32_t u = 0; u < SU_KPT; ++u) {
         if (i0 + u * SU_THREADS + tid < m) {
-          count(0, kg[u].x, sl[u]);
-          if (kg[u].y != NONE32) count(1, kg[u].y, sl[u]);
+          if (EXEC) count(0, kg[u].x, sl[u]);
+          if (IDLE && kg[u].y != NONE32) count(1, kg[u].y, sl[u]);
         }
       }
     }
     __syncthreads();
-    for (uint32_t q = w; q < 4 * D; q += SU_WAVES) {
+    for (uint32_t q = q_first + w; q < q_past; q += SU_WAVES) {
       const uint32_t ap = q / D, j = q - ap * D, arr = ap >> 1, s = sm.slot_of[j];
       const uint32_t searched = ap & 1u ? sm.sel[arr][s].w : sm.sel[arr][s].z;
       if (searched == SU_NO_BIN) continue;
@@ -441,13 +477,17 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
   if (tid < D) {
     const uint32_t s = sm.slot_of[tid];
     uint64_t* row = staged_row(A.stage_a, A.stage_b, task_start, task_len, row0 + tid);
-    const uint32_t gc = sm.gcnt[s];
-    row[0] = sm.ht_key[s]; row[1] = t;
-    row[2] = sm.cnt[s]; row[3] = sm.esum[s]; row[4] = sm.emin[s]; row[5] = sm.emax[s];
-    row[6] = sm.base[0][tid]; row[7] = sm.base[1][tid];
-    row[8] = gc; row[9] = sm.gsum[s]; row[10] = gc ? sm.gmin[s] : 0; row[11] = gc ? sm.gmax[s] : 0;
-    row[12] = sm.base[2][tid]; row[13] = sm.base[3][tid];
-    row[14] = 0; row[15] = 0;
+    if (EXEC) {
+      row[0] = sm.ht_key[s]; row[1] = t;
+      row[2] = sm.cnt[s]; row[3] = sm.esum[s]; row[4] = sm.emin[s]; row[5] = sm.emax[s];
+      row[6] = sm.base[0][tid]; row[7] = sm.base[1][tid];
+      row[14] = 0; row[15] = 0;
+    }
+    if (IDLE) {
+      const uint32_t gc = sm.gcnt[s];
+      row[8] = gc; row[9] = sm.gsum[s]; row[10] = gc ? sm.gmin[s] : 0; row[11] = gc ? sm.gmax[s] : 0;
+      row[12] = sm.base[2][tid]; row[13] = sm.base[3][tid];
+    }
   }
   if (tid == 0) A.dcount[unit] = D;
 }
@@ -456,8 +496,14 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
 // longest streamed units leave most of the chip to the others (64 tasks of 1,048,576 launches, Zipf over 4096 IDs: 915 us
 // in a launch each, 726 us together; workgroups that stay also save the 30 us that 33,000 without a unit take to come and go).
 // Workgroups stay, one per compute unit, and take units in order from a counter: streamed ones from the front of their list (the largest first), then
-// from its back, then the others.
+// from its back, then the others.  One of the front's is taken by
+// two workgroups, one for the execution times and one for the idle times, where that leaves a compute unit to each: all of them, or only those of
+// more than STREAM_LONGEST launches, or none.  What a unit of 227,000 launches takes decides the launch then, and the memory of one
+// compute unit decides that; both workgroups find and rank the IDs, and nothing is waited for, but all of it together is a third more
+// work.  This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only the
+// longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000 1700 / 1391.
 constexpr uint64_t UNIT_LARGE_WORKGROUPS = 256;
+constexpr uint32_t SU_SPLIT_PARTS = 192;
 __global__ void __launch_bounds__(SU_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_unit_large(const FusedArgs A, const uint32_t* __restrict__ streamed, uint32_t streamed_end, uint2* __restrict__ pack_kg_all,
              int64_t* __restrict__ pack_slot_all) {
@@ -465,17 +511,27 @@ k_unit_large(const FusedArgs A, const uint32_t* __restrict__ streamed, uint32_t 
   __shared__ uint32_t ticket;
   if (A.ctrl->status & ERR_OFFSETS) return;
   const uint32_t large = A.ctrl->n_class[2], front = A.ctrl->n_class[3], back = A.ctrl->n_class[4];
+  const uint32_t longest = A.ctrl->n_class[5];   // units of more than STREAM_LONGEST
+  const uint32_t split_above = 2 * front <= UNIT_LARGE_WORKGROUPS ? 0u : 2 * longest <= SU_SPLIT_PARTS ? STREAM_LONGEST : ~0u;
   for (;;) {
     if (threadIdx.x == 0) ticket = atomicAdd(&A.ctrl->taken, 1u);
     __syncthreads();
     const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(ticket)));
-    if (at >= front + back + large) return;
-    if (at < front + back)
-      unit_streamed(A, at < front ? streamed[at] : streamed[streamed_end - 1 - (at - front)], pack_kg_all, pack_slot_all,
-                    *reinterpret_cast<StreamSmem*>(smem_raw));
-    else
-      unit_sorted<SU_THREADS, FUSE_MAX / SU_THREADS, UNIT_DMAX_LARGE>(A, A.list[at - (front + back)],
-                                                                      *reinterpret_cast<LargeSmem*>(smem_raw));
+    StreamSmem& stream = *reinterpret_cast<StreamSmem*>(smem_raw);
+    if (at < 2 * front) {   // (two places for each of the front's units)
+      const uint32_t unit = streamed[at / 2];
+      if (A.ulen[unit] > split_above) {
+        if (at & 1) unit_streamed<SU_IDLE>(A, unit, pack_kg_all, pack_slot_all, stream);
+        else unit_streamed<SU_EXEC>(A, unit, pack_kg_all, pack_slot_all, stream);
+      } else if (!(at & 1)) {
+        unit_streamed<SU_BOTH>(A, unit, pack_kg_all, pack_slot_all, stream);
+      }
+    } else {
+      const uint32_t next = at - 2 * front;
+      if (next >= back + large) return;
+      if (next < back) unit_streamed<SU_BOTH>(A, streamed[streamed_end - 1 - next], pack_kg_all, pack_slot_all, stream);
+      else unit_sorted<SU_THREADS, FUSE_MAX / SU_THREADS, UNIT_DMAX_LARGE>(A, A.list[next - back], *reinterpret_cast<LargeSmem*>(smem_raw));
+    }
     __syncthreads();   // (the next unit's tables take the place of this one's)
   }
 }
