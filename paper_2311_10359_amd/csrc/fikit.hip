@@ -67,12 +67,14 @@ ProfileLayout profile_layout(uint64_t n, uint32_t n_tasks) {
   L.max_tiles = n / TILE + big_tasks;
   L.ctrl = c.take(256);
   L.k0 = c.take(n * 8);
-  L.k1 = c.take(n * 8);      // long tasks: tile-ordered IDs; general path: keys (sorted in the end)
-  L.k2 = c.take(n * 8 + 8);  // long tasks: tile-ordered values; general path: second key buffer, then segment starts
-  L.e0 = c.take(n * 8);
-  L.e1 = c.take(n * 8);      // also: first half of the staged rows of one-workgroup tasks
-  L.g0 = c.take(n * 8);
-  L.g1 = c.take(n * 8);      // also: second half of the staged rows
+  // (six arrays of one size: rows of one-workgroup tasks are staged in them, see Staging)
+  const uint64_t words = n * 8 + 8;
+  L.k1 = c.take(words);      // long tasks: tile-ordered IDs; general path: keys (sorted in the end)
+  L.k2 = c.take(words);      // long tasks: tile-ordered values; general path: second key buffer, then segment starts
+  L.e0 = c.take(words);
+  L.e1 = c.take(words);      // also: first half of the staged rows of long tasks
+  L.g0 = c.take(words);
+  L.g1 = c.take(words);      // also: second half of them
   L.tiles = c.take((static_cast<uint64_t>(n_tasks) + 1) * 4);
   uint64_t long_tasks = n / (static_cast<uint64_t>(FUSE_MAX) + 1);
   if (long_tasks > n_tasks) long_tasks = n_tasks;
@@ -104,6 +106,7 @@ ProfileLayout profile_layout(uint64_t n, uint32_t n_tasks) {
   L.total = c.at;
   return L;
 }
+static_assert(STAGING_ARRAYS == 6, "k1 .. g1");
 
 // In-place exclusive prefix sum of `count` 32-bit words; the grand total goes to *d_total (may be null).
 int scan_u32(uint32_t* d_data, uint64_t count, uint32_t* d_sums, uint64_t* d_total, hipStream_t st) {
@@ -467,6 +470,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(medium), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(medium_lds)));
   FusedArgs fa{};
   fa.rec = d_records; fa.off = d_task_offsets; fa.ids = ids; fa.e0 = e0; fa.g0 = g0; fa.key0 = k1;
+  fa.staging = Staging{k1, (L.k2 - L.k1) / 8};
   fa.stage_a = e1; fa.stage_b = g1; fa.dcount = dcount; fa.gflag = gflag; fa.ctrl = ctrl;
   if (emit) {
     fa.pred_role = emit->role; fa.pred_lp_e = emit->lp_e; fa.pred_hp_eg = emit->hp_eg; fa.pred_lp_total = emit->lp_total;
@@ -552,7 +556,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   auto gather_rows = [&](uint64_t general_done) {
     tr.mark("k_gather_rows");
     hipLaunchKernelGGL(k_gather_rows, dim3(xcd_grid(n_tasks)), dim3(256), 0, st, d_task_offsets, d_task_row_offsets, gflag, is_long,
-                       n_units > 0 ? 1 : 0, e1, g1, n_tasks, d_rows_out, row_capacity, general_done, ctrl);
+                       n_units > 0 ? 1 : 0, fa.staging, n_tasks, d_rows_out, row_capacity, general_done, ctrl);
     if (n_units > 0)
       hipLaunchKernelGGL(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, d_task_offsets, ulen,
                          utask, udcount, urow, ustage, mflag, d_task_row_offsets, e1, g1, static_cast<uint32_t>(n_units), d_rows_out, row_capacity,
@@ -561,7 +565,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   const bool any_long = n_units > 0;
   if (!any_long && n_tasks <= ROWS_ONE_TASKS) {
     tr.mark("k_gather_rows");
-    hipLaunchKernelGGL(k_rows_one, dim3(n_tasks), dim3(256), 0, st, d_task_offsets, dcount, e1, g1, n_tasks, d_task_row_offsets, d_rows_out,
+    hipLaunchKernelGGL(k_rows_one, dim3(n_tasks), dim3(256), 0, st, d_task_offsets, dcount, fa.staging, n_tasks, d_task_row_offsets, d_rows_out,
                        row_capacity, ctrl);
   } else {
     tr.mark("row_offsets");

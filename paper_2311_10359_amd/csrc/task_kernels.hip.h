@@ -114,12 +114,40 @@ struct FusedSmem {
   uint16_t rslot[ESTATS ? DMAX : 1];   // rank -> slot
 };
 
-// Where row j of a task is staged: the task's slice of stage_a, then its slice of stage_b, which hold stage_room rows.
+// Where row j of a long task is staged: the task's slice of stage_a, then its slice of stage_b, which hold stage_room rows.
 __device__ __forceinline__ uint32_t stage_room(uint32_t m) { return 2 * (m >> 4); }
 __device__ __forceinline__ uint64_t* staged_row(int64_t* stage_a, int64_t* stage_b, uint64_t base, uint32_t m, uint32_t j) {
   const uint32_t cap1 = m >> 4;  // rows of 16 words that fit in m words
   return j < cap1 ? reinterpret_cast<uint64_t*>(stage_a + base) + static_cast<uint64_t>(j) * 16
                   : reinterpret_cast<uint64_t*>(stage_b + base) + static_cast<uint64_t>(j - cap1) * 16;
+}
+
+// Rows of a task that one workgroup profiles whole are staged in eight words instead of a row's sixteen (what is below 2^32 there,
+// two to a word), in the task's slices of as many arrays as they need (STAGING_ARRAYS of the per-launch arrays, which lie `stride`
+// words apart): three rows to four launches.  A task with more is sorted, which short traces of many kernels should not be.  Staged as whole rows in two arrays, one to
+// eight launches, / now, us: profile of 8200 tasks of 64 launches, 10 kernels, 862 / 191, of 3000 of 1500, 250 kernels, 1462 / 282; step of
+// 1000 pairs of 300 and 500, 60 and 100 kernels 550 / 120, of one pair of 100, 20 and 30 kernels 176 / 44.
+constexpr uint32_t ROW_WORDS = 8, STAGING_ARRAYS = 6;
+enum : uint32_t { RW_ID, RW_COUNTS, RW_EXEC_SUM, RW_GAP_SUM, RW_EXEC_RANGE, RW_GAP_RANGE, RW_EXEC_PICKS, RW_GAP_PICKS };
+struct Staging {
+  uint64_t* first;
+  uint64_t stride;
+};
+__device__ __forceinline__ uint32_t staging_room(uint32_t m) { return STAGING_ARRAYS * (m / ROW_WORDS); }
+__device__ __forceinline__ uint64_t* staged_words(const Staging& s, uint64_t base, uint32_t m, uint32_t j) {
+  const uint32_t each = m / ROW_WORDS, k = j < each ? 0u : j / each;
+  return s.first + (k * s.stride + base + static_cast<uint64_t>(j - k * each) * ROW_WORDS);
+}
+__device__ __forceinline__ uint64_t two_words(uint32_t lo, uint32_t hi) { return static_cast<uint64_t>(hi) << 32 | lo; }
+// Field f (of sixteen) of the row that is staged at w.
+__device__ __forceinline__ uint64_t row_field(const uint64_t* w, uint32_t task, uint32_t f) {
+  // (per field: its word, and 1 the lower half, 2 the upper half, 0 all of it)
+  constexpr uint64_t WORD = 0x0077553166442100ull, PART = 0x0021210221210100ull;   // (the lowest digit is field 0's)
+  const uint32_t part = static_cast<uint32_t>(PART >> (4 * f)) & 3u;
+  const uint64_t v = w[static_cast<uint32_t>(WORD >> (4 * f)) & 7u];
+  if (f == 1) return task;
+  if (f >= 14) return 0;
+  return part == 0 ? v : part == 1 ? static_cast<uint32_t>(v) : v >> 32;
 }
 
 __device__ __forceinline__ uint32_t rotl32(uint32_t x, int k) { return (x << k) | (x >> (32 - k)); }
@@ -181,6 +209,7 @@ struct FusedArgs {
   int64_t* e0;                 // per-launch values handed to the general path when a task does not fit
   int64_t* g0;
   uint64_t* key0;              // ... with their IDs, in the same order
+  Staging staging;             // a task's rows
   // units: groups of consecutive ID buckets of a long task, whose launches lie bucket-ordered inside every tile
   const uint32_t* ustart;      // where the unit would start if the task were in bucket order (unit_streamed packs its launches there)
   const uint32_t* ulen;
@@ -194,9 +223,9 @@ struct FusedArgs {
   uint32_t* mflag;             // cleared when a unit sends its task to the general path
   uint32_t* staged;            // per task: rows staged by its units so far (0 at the start) ...
   uint32_t* ustage;            // ... and per unit: rows of its task that were staged before its own
-  // both
   int64_t* stage_a;            // rows are staged in the task's own slice of these two arrays
   int64_t* stage_b;
+  // both
   uint32_t* dcount;            // rows per task / per unit
   uint32_t* gflag;             // task takes the general path
   Ctrl* ctrl;
@@ -263,8 +292,6 @@ k_task_fused(const FusedArgs A) {
   uint64_t* __restrict__ ids = A.ids;
   int64_t* __restrict__ e0 = A.e0;
   int64_t* __restrict__ g0 = A.g0;
-  int64_t* __restrict__ stage_a = A.stage_a;
-  int64_t* __restrict__ stage_b = A.stage_b;
   uint32_t* __restrict__ dcount = A.dcount;
   uint32_t* __restrict__ gflag = A.gflag;
   const uint32_t tid = threadIdx.x;
@@ -280,8 +307,10 @@ k_task_fused(const FusedArgs A) {
   __syncthreads();
 
   // ---- 1. read, identify, measure ------------------------------------------------------------
-  uint32_t ev[KPT], gv[KPT];   // execution time, idle time (NONE32 for the task's last launch)
-  uint32_t sl[KPT];            // ID-table slot, later the rank of the launch's ID
+  // (vectors, which stay in registers also where the compiler unrolls a loop over them late; it puts an array into memory then)
+  typedef uint32_t per_launch __attribute__((ext_vector_type(KPT)));
+  per_launch ev, gv;           // execution time, idle time (NONE32 for the task's last launch)
+  per_launch sl;               // ID-table slot, later the rank of the launch's ID
   uint32_t my_maxe = 0, my_maxg = 0;
   bool bad = false, wide = false;
   const uint32_t lane = lane_id();
@@ -424,7 +453,7 @@ k_task_fused(const FusedArgs A) {
   if (lane_id() == 0) { atomicMax(&sm.maxe, my_maxe); atomicMax(&sm.maxg, my_maxg); }
   __syncthreads();
   const uint32_t D = sm.ndist;
-  if (sm.fallback || D > DMAX || D > stage_room(m)) {
+  if (sm.fallback || D > DMAX || D > staging_room(m)) {
     // general path: hand over the per-launch values (recomputed at full width)
     // (every thread reads back the IDs it wrote itself)
     for (uint32_t i = tid; i < m; i += NT) {
@@ -556,7 +585,7 @@ k_task_fused(const FusedArgs A) {
   const bool emit = A.pred_role != nullptr;
   uint32_t mean_e = 0, mean_g = 0;
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
+    uint64_t* row = staged_words(A.staging, base, m, j);
     const uint32_t ec = sm.rcnt[j];
     uint32_t gc, emin, emax, gmin, gmax;
     uint64_t esum, gsum;
@@ -571,12 +600,10 @@ k_task_fused(const FusedArgs A) {
       esum = sm.u.acc.esum[j]; emin = sm.u.acc.emin[j]; emax = sm.u.acc.emax[j];
       gsum = sm.u.acc.gsum[j]; gmin = sm.u.acc.gmin[j]; gmax = sm.u.acc.gmax[j];
     }
-    row[0] = sm.rkey[j];
-    row[1] = t;
-    row[2] = ec; row[3] = esum; row[4] = emin; row[5] = emax;
-    row[8] = gc; row[9] = gsum;
-    row[10] = gc ? gmin : 0; row[11] = gc ? gmax : 0;
-    row[14] = 0; row[15] = 0;
+    row[RW_ID] = sm.rkey[j];
+    row[RW_COUNTS] = two_words(ec, gc);
+    row[RW_EXEC_SUM] = esum; row[RW_GAP_SUM] = gsum;
+    row[RW_EXEC_RANGE] = two_words(emin, emax); row[RW_GAP_RANGE] = two_words(gc ? gmin : 0, gc ? gmax : 0);
     if (emit && A.predictor != FIKIT_PREDICT_P50) {
       mean_e = ec ? static_cast<uint32_t>(esum / ec) : 0u;
       mean_g = gc ? static_cast<uint32_t>(gsum / gc) : 0u;
@@ -799,13 +826,13 @@ k_task_fused(const FusedArgs A) {
         const uint32_t arr = q >= D ? 1u : 0u, j = q - arr * D;
         const uint2 se = sel[q];
         const uint32_t b50 = sel_b50(se.y), b95 = sel_b95(se.y);
-        uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
+        uint32_t* picks = reinterpret_cast<uint32_t*>(staged_words(A.staging, base, m, j) + (arr ? RW_GAP_PICKS : RW_EXEC_PICKS));   // p50, p95
         if (b50 == SEL_NO_BIN || !(se.y & SEL_LISTED)) {   // (not listed: bins one value wide where the scale is one to one)
           if (gl == 0) {
             const uint32_t v50 = b50 == SEL_NO_BIN ? 0 : value_of_scale(se.x + b50);
-            row[arr ? 12 : 6] = v50;
+            picks[0] = v50;
             if (emit_p50) (arr ? pred_g : pred_e)[j] = v50;
-            row[arr ? 13 : 7] = b50 == SEL_NO_BIN ? 0 : value_of_scale(se.x + b95);
+            picks[1] = b50 == SEL_NO_BIN ? 0 : value_of_scale(se.x + b95);
           }
           continue;
         }
@@ -815,15 +842,15 @@ k_task_fused(const FusedArgs A) {
         for (uint32_t x = gl; x < ca; x += GS) {
           const uint32_t v = la[x];
           const uint32_t rank = list_rank(la, ca, v, x);
-          if (rank == k50) { row[arr ? 12 : 6] = v; if (emit_p50) (arr ? pred_g : pred_e)[j] = v; }
-          if (cb == 0 && rank == k95) row[arr ? 13 : 7] = v;
+          if (rank == k50) { picks[0] = v; if (emit_p50) (arr ? pred_g : pred_e)[j] = v; }
+          if (cb == 0 && rank == k95) picks[1] = v;
         }
         if (cb) {
           const uint32_t* lb = lists + loff[(2 * arr + 1) * DMAX + j];
           for (uint32_t x = gl; x < cb; x += GS) {
             const uint32_t v = lb[x];
             const uint32_t rank = list_rank(lb, cb, v, x);
-            if (rank == k95) row[arr ? 13 : 7] = v;
+            if (rank == k95) picks[1] = v;
           }
         }
       }
@@ -925,10 +952,10 @@ k_task_fused(const FusedArgs A) {
     __syncthreads();
   }
   for (uint32_t j = tid; j < D; j += NT) {
-    uint64_t* row = staged_row(stage_a, stage_b, base, m, j);
+    uint64_t* row = staged_words(A.staging, base, m, j);
     const uint4 pf = sm.pref[j];
-    row[6] = pf.x; row[7] = pf.y;
-    row[12] = pf.z; row[13] = pf.w;
+    row[RW_EXEC_PICKS] = two_words(pf.x, pf.y);
+    row[RW_GAP_PICKS] = two_words(pf.z, pf.w);
     if (emit_p50) { pred_e[j] = pf.x; pred_g[j] = pf.z; }
   }
   if (emit) emit_predictions();
@@ -938,8 +965,7 @@ k_task_fused(const FusedArgs A) {
 // Moves a task's staged rows to their final place once the row offsets are known.
 __global__ void __launch_bounds__(256)
 k_gather_rows(const uint64_t* __restrict__ off, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ gflag,
-              const uint32_t* __restrict__ long_prefix, int have_long, const int64_t* __restrict__ stage_a,
-              const int64_t* __restrict__ stage_b, uint32_t n_tasks, fikit_row* __restrict__ rows, uint64_t capacity,
+              const uint32_t* __restrict__ long_prefix, int have_long, const Staging staging, uint32_t n_tasks, fikit_row* __restrict__ rows, uint64_t capacity,
               uint64_t general_done, const Ctrl* ctrl) {
   if (!rows_final(ctrl, capacity, general_done)) return;
   const uint32_t t = xcd_item(blockIdx.x, n_tasks);
@@ -953,7 +979,7 @@ k_gather_rows(const uint64_t* __restrict__ off, const uint64_t* __restrict__ row
   uint64_t* out = reinterpret_cast<uint64_t*>(rows + r0);
   for (uint32_t x = threadIdx.x; x < D * 16; x += 256) {
     const uint32_t j = x >> 4, f = x & 15;
-    out[x] = staged_row(const_cast<int64_t*>(stage_a), const_cast<int64_t*>(stage_b), base, m, j)[f];
+    out[x] = row_field(staged_words(staging, base, m, j), t, f);
   }
 }
 
@@ -978,8 +1004,7 @@ k_step_begin(const uint64_t* __restrict__ off, uint32_t n_tasks, const ProfileBe
 // row counts before its task's for itself (a launch less, 4.5 us).
 constexpr uint32_t ROWS_ONE_TASKS = 1024;
 __global__ void __launch_bounds__(256)
-k_rows_one(const uint64_t* __restrict__ off, const uint32_t* __restrict__ counts, const int64_t* __restrict__ stage_a,
-           const int64_t* __restrict__ stage_b, uint32_t n_tasks, uint64_t* __restrict__ row_off, fikit_row* __restrict__ rows,
+k_rows_one(const uint64_t* __restrict__ off, const uint32_t* __restrict__ counts, const Staging staging, uint32_t n_tasks, uint64_t* __restrict__ row_off, fikit_row* __restrict__ rows,
            uint64_t capacity, Ctrl* ctrl) {
   __shared__ uint64_t part[2][4];
   const uint32_t t = blockIdx.x, tid = threadIdx.x, w = tid / WAVE;
@@ -1006,7 +1031,7 @@ k_rows_one(const uint64_t* __restrict__ off, const uint32_t* __restrict__ counts
   const uint32_t m = static_cast<uint32_t>(off[t + 1] - base);
   uint64_t* out = reinterpret_cast<uint64_t*>(rows + before);
   for (uint32_t x = tid; x < D * 16; x += 256)
-    out[x] = staged_row(const_cast<int64_t*>(stage_a), const_cast<int64_t*>(stage_b), base, m, x >> 4)[x & 15];
+    out[x] = row_field(staged_words(staging, base, m, x >> 4), t, x & 15);
 }
 
 }  // namespace fikit
