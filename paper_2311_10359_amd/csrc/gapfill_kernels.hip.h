@@ -186,6 +186,7 @@ constexpr int PRED_KPT = 8;                       // consecutive launches per th
 constexpr int PRED_CHUNK = PRED_THREADS * PRED_KPT;
 constexpr int PRED_ROWS = 512;                    // rows of a task kept in an LDS hash table for the lookup
 constexpr int PRED_HT = 2 * PRED_ROWS;
+constexpr int PRED_READS = 2;                     // pairs of launches that a lane reads at a time (k_gf_predict32)
 
 constexpr uint32_t WIDE32 = 0xffffffffu;   // 32-bit predictions must be below this
 
@@ -488,6 +489,9 @@ __device__ __forceinline__ uint32_t clamp32(int64_t v) {   // (predictions are n
 // 500: 599 -> 216 us.
 // For the replay against actual idle times (actual != nullptr) the first word of hp_eg[i] holds the idle
 // time that really followed launch i instead (clamped to WIDE32, which no filled time can reach).
+// Bound by the memory that reads and writes by turns, once a lane has PRED_READS pairs of IDs on their way and both halves of an odd task's
+// pairs come in one read: 6000 ragged scenarios 146 us with one read per pair where the task starts at an even place and two where not,
+// 133 so; 6000 of 2048 and 8192 launches 195 / 186 = 5.5 TB/s (four pairs 139 and 184 us, one 152 and 211).
 // pred_done (may be null): tasks whose predictions exist already and are left alone.  prof (may be null, as in the walks): the
 // profile in the same call that this was enqueued behind.
 __global__ void __launch_bounds__(PRED_THREADS)
@@ -544,18 +548,15 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
     return make_uint2(clamp32(e), clamp32(g));
   };
   uint64_t total = 0;
-  const bool even = ((base & 1) == 0);   // 16-byte accesses to the workspace arrays need an even first index
-  const bool ids_vec = (reinterpret_cast<uintptr_t>(ids + base) & 15) == 0;   // and those to the caller's IDs an aligned address
-  for (uint64_t i0 = part0 + 2 * static_cast<uint64_t>(tid); i0 < len; i0 += static_cast<uint64_t>(gridDim.y) * (2 * PRED_THREADS)) {
-    uint64_t id0 = 0, id1 = 0;
-    const bool two = i0 + 1 < len;
-    if (ids_vec && two) {
-      const ulonglong2 v = load_once(reinterpret_cast<const ulonglong2*>(ids + base + i0));   // (2 % of the kernel)
-      id0 = v.x; id1 = v.y;
-    } else {
-      id0 = ids[base + i0];
-      if (two) id1 = ids[base + i0 + 1];
-    }
+  // Pairs of launches start at even elements, so that they are read as 16 bytes and written as 8 and 16; an odd first launch goes by itself.
+  // (IDs that lie on 8 bytes only are read one by one, and the results written so where they do not match.)
+  const bool ids_vec = (reinterpret_cast<uintptr_t>(ids) & 15) == 0;
+  const uint32_t lead = static_cast<uint32_t>(base & 1);
+  const uint64_t step = static_cast<uint64_t>(gridDim.y) * (2 * PRED_THREADS);
+  uint64_t i0 = lead + part0 + 2 * static_cast<uint64_t>(tid);
+  const bool hp_role = (rl & ROLE_HP) != 0, lp_role = (rl & ROLE_LP) != 0, with_actual = actual && hp_role;
+  // what is left of a launch pair once its IDs and idle times are there
+  auto finish = [&](uint64_t i, bool two, uint64_t id0, uint64_t id1, int64_t x0, int64_t x1) {
     const uint2 p0 = predict(id0);
     uint2 p1 = make_uint2(0, 0);
     if (two) p1 = predict(id1);
@@ -563,21 +564,43 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
     wide |= a0 == WIDE32 || b0 == WIDE32 || a1 == WIDE32 || b1 == WIDE32;
     total += static_cast<uint64_t>(a0) + a1;
     uint32_t h0w = a0, h1w = a1;   // first word of the high-priority entries
-    if (actual && (rl & ROLE_HP)) {
+    if (with_actual) {
       // (the task's last launch has no idle time after it and its entry is never used as a gap)
-      const int64_t x0 = i0 + 1 < len ? actual[base + i0] : 0, x1 = i0 + 2 < len ? actual[base + i0 + 1] : 0;
+      x0 = i + 1 < len ? x0 : 0; x1 = i + 2 < len ? x1 : 0;
       bad_actual |= x0 < 0 || x1 < 0;
       h0w = static_cast<uint64_t>(x0) >= WIDE32 ? WIDE32 : static_cast<uint32_t>(x0);
       h1w = static_cast<uint64_t>(x1) >= WIDE32 ? WIDE32 : static_cast<uint32_t>(x1);
     }
-    if (even && two) {
-      if (rl & ROLE_LP) *reinterpret_cast<uint2*>(lp_e + base + i0) = make_uint2(a0, a1);
-      if (rl & ROLE_HP) *reinterpret_cast<uint4*>(hp_eg + base + i0) = make_uint4(h0w, b0, h1w, b1);
+    if (two) {
+      if (lp_role) *reinterpret_cast<uint2*>(lp_e + base + i) = make_uint2(a0, a1);
+      if (hp_role) *reinterpret_cast<uint4*>(hp_eg + base + i) = make_uint4(h0w, b0, h1w, b1);
     } else {
-      if (rl & ROLE_LP) { lp_e[base + i0] = a0; if (two) lp_e[base + i0 + 1] = a1; }
-      if (rl & ROLE_HP) { hp_eg[base + i0] = make_uint2(h0w, b0); if (two) hp_eg[base + i0 + 1] = make_uint2(h1w, b1); }
+      if (lp_role) { lp_e[base + i] = a0; if (two) lp_e[base + i + 1] = a1; }
+      if (hp_role) { hp_eg[base + i] = make_uint2(h0w, b0); if (two) hp_eg[base + i + 1] = make_uint2(h1w, b1); }
+    }
+  };
+  if (ids_vec) {
+    for (; i0 + (PRED_READS - 1) * step + 1 < len; i0 += PRED_READS * step) {
+      ulonglong2 v[PRED_READS];
+      int64_t x[PRED_READS][2];
+#pragma unroll
+      for (int u = 0; u < PRED_READS; ++u) v[u] = load_once(reinterpret_cast<const ulonglong2*>(ids + base + i0 + u * step));
+#pragma unroll
+      for (int u = 0; u < PRED_READS; ++u) {
+        x[u][0] = x[u][1] = 0;
+        if (with_actual) { x[u][0] = actual[base + i0 + u * step]; x[u][1] = actual[base + i0 + u * step + 1]; }
+      }
+#pragma unroll
+      for (int u = 0; u < PRED_READS; ++u) finish(i0 + u * step, true, v[u].x, v[u].y, x[u][0], x[u][1]);
     }
   }
+  auto plain = [&](uint64_t i, bool two) {
+    const uint64_t id0 = ids[base + i], id1 = two ? ids[base + i + 1] : 0;
+    const int64_t x0 = with_actual ? actual[base + i] : 0, x1 = with_actual && two ? actual[base + i + 1] : 0;
+    finish(i, two, id0, id1, x0, x1);
+  };
+  for (; i0 < len; i0 += step) plain(i0, i0 + 1 < len);
+  if (lead && part0 == 0 && tid == PRED_THREADS - 1) plain(0, false);
   total = wave_sum_u64(total);
   if (lane_id() == 0) wave_tot[tid >> 6] = total;
   __syncthreads();
@@ -1119,17 +1142,12 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
               k = static_cast<uint32_t>(__builtin_ctzll(takes));
               uint64_t todo = (~1ull) << k;
               // How far the queue gets: the entries (consumed ones too) that end within what may be filled; with feedback
-              // an entry is issued only while the time filled before it is below the actual gap, so at most one more than
-              // the entries that end before that.
+              // an entry is issued only while the time filled before it is below the actual gap.
               const uint32_t limit = read_lane_u32(lim, k);
-              uint32_t o2 = popc64(ballot(win < limit));
-              bool over = false;   // (with feedback: nothing is issued after these)
-              if (MODE == LW_REPLAY_FEEDBACK) {
-                const uint32_t arrived = read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k);
-                const uint32_t o3 = popc64(ballot(win < arrived)) + 1;
-                over = o3 <= o2;
-                o2 = o3 < o2 ? o3 : o2;
-              }
+              uint64_t ends = ballot(win < limit);
+              const uint32_t arrived = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(__builtin_elementwise_add_sat(E[j], C), k) : 0u;
+              if (MODE == LW_REPLAY_FEEDBACK) ends &= ballot(before < arrived);   // (both are true up to some entry)
+              uint32_t o2 = popc64(ends);
               uint32_t C2 = read_lane_u32(before, o2), sum2 = read_lane_u32(win, o2);   // (o2 >= 1: the head fits)
               // the common case: the gap ends inside the window, at an entry whose running sum is exact
               uint32_t c = o2 - o, f = C2 - C;
@@ -1140,6 +1158,8 @@ k_gf_walk_wave(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp
                 uint32_t left = read_lane_u32(b1[j], k);
                 const uint32_t actual = MODE == LW_REPLAY_FEEDBACK ? read_lane_u32(E[j], k) : 0u;
                 bool ended = false;
+                // (with feedback: nothing is issued after these)
+                const bool over = MODE == LW_REPLAY_FEEDBACK && popc64(ballot(win < arrived)) < o2;
                 if (o2 == WW_WIN && !over && wb + WW_WIN < L) {
                   // nearly all of these: the gap takes the rest of the window (c and f so far) and ends inside the next one
                   left -= f;
