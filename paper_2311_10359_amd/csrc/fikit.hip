@@ -899,7 +899,7 @@ int gapfill_wide_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t
                          const fikit_row* d_rows, const uint64_t* d_task_row_offsets, const uint32_t* d_hp_task,
                          const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
                          const uint64_t* d_gap_offsets, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* d_lp_completion_ns,
-                         uint64_t* d_lp_placed, int32_t* d_status) {
+                         uint64_t* d_lp_placed, int32_t* d_status = nullptr) {
   hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
                      d_task_row_offsets, b.role, b.pe, b.pg, b.open, static_cast<uint32_t>(h_params->predictor), b.ctrl);
   hipLaunchKernelGGL(k_gf_walk, dim3(blocks_for(n_scenarios, 256 / WAVE)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
@@ -976,7 +976,7 @@ int fikit_gapfill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint32_
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&] {
     return gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task, n_scenarios,
-                                h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, nullptr);
+                                h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed);
   });
 }
 
@@ -1063,7 +1063,7 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
   }
   return finish_gapfill(st, tr, b.ctrl, h, [&] {
     return gapfill_wide_enqueue(st, b, d_ids_out, d_task_offsets, n_tasks, d_rows_out, d_task_row_offsets, d_hp_task, d_lp_task,
-                                n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed, nullptr);
+                                n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed);
   });
 }
 
@@ -1141,10 +1141,16 @@ int fikit_gapfill_static(const uint64_t* d_ids, uint64_t n_ids, const uint64_t* 
                                  d_lp_placed, false, nullptr, false))
       return rc;
     // (whether a prediction needs 64 bits is only known on the device, and nothing is waited for here)
-    if (int rc = gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
-                                      n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
-                                      d_status))
+    if (n_scenarios <= GF_WIDE_SCENARIOS) {
+      hipLaunchKernelGGL(k_gf_wide, dim3(static_cast<uint32_t>(n_scenarios)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, d_rows,
+                         d_task_row_offsets, b.role, d_hp_task, d_lp_task, d_gap_offsets, b.pe, b.pg, b.open,
+                         static_cast<uint32_t>(h_params->predictor), h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,
+                         d_lp_completion_ns, d_lp_placed, d_status, b.ctrl);
+    } else if (int rc = gapfill_wide_enqueue(st, b, d_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
+                                             n_scenarios, h_params, d_gap_offsets, d_fill_count, d_filled_ns, d_lp_completion_ns, d_lp_placed,
+                                             d_status)) {
       return rc;
+    }
   }
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;

@@ -232,23 +232,16 @@ __device__ __forceinline__ bool predict_one(uint64_t id, bool in_lds, const Pred
   return find_row(id, rows, r0, nr, predictor, e, g);
 }
 
-// One workgroup per task that takes part in a scenario.  For every launch i of the task:
+// One workgroup and one task that takes part in a scenario (rl: as what).  For every launch i of the task:
 //   as low-priority queue:   pe[i]   = sum of predicted execution times of launches 0..i
 //   as high-priority trace:  pg[i]   = predicted idle time after launch i
 //                            open[i] = predicted time at which launch i ends (its gap opens):
 //                                      sum_{k<=i} E_k + sum_{k<i} G_k   (not written if open is null)
 // Prefix sums run thread -> wave -> workgroup, with a running carry from chunk to chunk.
-__global__ void __launch_bounds__(PRED_THREADS) __attribute__((amdgpu_waves_per_eu(5, 8)))
-k_gf_predict(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, uint32_t n_tasks,
-             const fikit_row* __restrict__ rows, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role,
-             int64_t* __restrict__ pe, int64_t* __restrict__ pg, int64_t* __restrict__ open, uint32_t predictor, Ctrl* ctrl) {
-  __shared__ PredTable tb;
-  // only bits that earlier kernels set: the decision must be the same for the whole workgroup
-  if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
-  if (!ctrl->wide) return;
-  const uint32_t t = rotated_item(blockIdx.x, n_tasks);   // (one workgroup per task)
-  const uint32_t rl = role[t];
-  if (rl == 0) return;
+__device__ __forceinline__ void gf_predict_task(PredTable& tb, uint32_t t, uint32_t rl, const uint64_t* __restrict__ ids,
+                                                const uint64_t* __restrict__ off, const fikit_row* __restrict__ rows,
+                                                const uint64_t* __restrict__ row_off, int64_t* __restrict__ pe, int64_t* __restrict__ pg,
+                                                int64_t* __restrict__ open, uint32_t predictor, Ctrl* ctrl) {
   const uint64_t base = off[t], len = off[t + 1] - base;
   const uint64_t r0 = row_off[t], nr = row_off[t + 1] - r0;
   const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
@@ -342,23 +335,29 @@ k_gf_predict(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off,
   }
   if (unknown) atomicOr(&ctrl->status, ERR_UNKNOWN_ID);
 }
+// One workgroup per task.
+__global__ void __launch_bounds__(PRED_THREADS) __attribute__((amdgpu_waves_per_eu(5, 8)))
+k_gf_predict(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, uint32_t n_tasks,
+             const fikit_row* __restrict__ rows, const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role,
+             int64_t* __restrict__ pe, int64_t* __restrict__ pg, int64_t* __restrict__ open, uint32_t predictor, Ctrl* ctrl) {
+  __shared__ PredTable tb;
+  // only bits that earlier kernels set: the decision must be the same for the whole workgroup
+  if (ctrl->status & (ERR_OFFSETS | ERR_TASK_INDEX | ERR_GAP_OFFSETS)) return;
+  if (!ctrl->wide) return;
+  const uint32_t t = rotated_item(blockIdx.x, n_tasks), rl = role[t];
+  if (rl) gf_predict_task(tb, t, rl, ids, off, rows, row_off, pe, pg, open, predictor, ctrl);
+}
 
 // The walk on 64-bit prefix sums, one wave per scenario: for calls with a prediction that does not fit 32 bits.
 __device__ __forceinline__ int64_t lane_value(int64_t v, uint32_t idx) {   // (idx: the same in all lanes)
   return static_cast<int64_t>(read_lane_u64(static_cast<uint64_t>(v), idx));
 }
 
-__global__ void __launch_bounds__(256)
-k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
-          uint64_t n_scen, const uint64_t* __restrict__ gap_off, const int64_t* __restrict__ pe,
-          const int64_t* __restrict__ pg, const int64_t* __restrict__ open, int64_t margin, int64_t min_gap,
-          uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
-          uint64_t* __restrict__ placed_out, int32_t* __restrict__ status_out, const Ctrl* ctrl) {
-  // (status_out may be null: the call's status, which no kernel changes from here on)
-  if (status_out && blockIdx.x == 0 && threadIdx.x == 0) *status_out = gf_status(ctrl->status);
-  if (ctrl->status || !ctrl->wide) return;
-  const uint64_t s = static_cast<uint64_t>(blockIdx.x) * (256 / WAVE) + threadIdx.x / WAVE;
-  if (s >= n_scen) return;  // whole waves leave together
+__device__ __forceinline__ void gf_walk_scenario(uint64_t s, const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task,
+                                                 const uint32_t* __restrict__ lp_task, const uint64_t* __restrict__ gap_off, const int64_t* pe,
+                                                 const int64_t* pg, const int64_t* open, int64_t margin, int64_t min_gap,
+                                                 uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns,
+                                                 int64_t* __restrict__ completion_out, uint64_t* __restrict__ placed_out) {
   const uint32_t lane = lane_id();
 
   const uint32_t hp = hp_task[s], lp = lp_task[s];
@@ -446,6 +445,47 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
     completion_out[s] = completion;
     placed_out[s] = p;
   }
+}
+__global__ void __launch_bounds__(256)
+k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task,
+          uint64_t n_scen, const uint64_t* __restrict__ gap_off, const int64_t* __restrict__ pe,
+          const int64_t* __restrict__ pg, const int64_t* __restrict__ open, int64_t margin, int64_t min_gap,
+          uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns, int64_t* __restrict__ completion_out,
+          uint64_t* __restrict__ placed_out, int32_t* __restrict__ status_out, const Ctrl* ctrl) {
+  // (status_out may be null: the call's status, which no kernel changes from here on)
+  if (status_out && blockIdx.x == 0 && threadIdx.x == 0) *status_out = gf_status(ctrl->status);
+  if (ctrl->status || !ctrl->wide) return;
+  const uint64_t s = static_cast<uint64_t>(blockIdx.x) * (256 / WAVE) + threadIdx.x / WAVE;
+  if (s >= n_scen) return;  // whole waves leave together
+  gf_walk_scenario(s, off, hp_task, lp_task, gap_off, pe, pg, open, margin, min_gap, fill_count, filled_ns, completion_out, placed_out);
+}
+
+// Both in one launch, for a call of few scenarios that enqueues them before it knows whether they are needed (fikit_gapfill_static): the
+// workgroup of a scenario looks its two tasks up (what several scenarios share is written by all of their workgroups, each the same values)
+// and one of its waves walks.  Also where the call's status is published, which nothing before or in this launch changes by then: an ID
+// without a row has been found by k_gf_predict32.  A launch that finds nothing to do costs 2.2 us of the chip's time and 3 of the
+// host's: static calls in us, two launches / one: 64 scenarios of 1500 gaps 69.8 / 68.4, a few of 100 gaps 22 / 19.4; with predictions beyond
+// 32 bits one scenario 260 / 233, 64 of 16 tasks 322 / 280, 256 of 32 tasks 329 / 282, 900 of 60 tasks 345 / 439, which decides the line.
+constexpr uint64_t GF_WIDE_SCENARIOS = 256;
+__global__ void __launch_bounds__(PRED_THREADS)
+k_gf_wide(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, const fikit_row* __restrict__ rows,
+          const uint64_t* __restrict__ row_off, const uint32_t* __restrict__ role, const uint32_t* __restrict__ hp_task,
+          const uint32_t* __restrict__ lp_task, const uint64_t* __restrict__ gap_off, int64_t* pe, int64_t* pg, int64_t* open,
+          uint32_t predictor, int64_t margin, int64_t min_gap, uint32_t* __restrict__ fill_count, int64_t* __restrict__ filled_ns,
+          int64_t* __restrict__ completion_out, uint64_t* __restrict__ placed_out, int32_t* __restrict__ status_out, Ctrl* ctrl) {
+  __shared__ PredTable tb;
+  const uint32_t status = ctrl->status;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *status_out = gf_status(status);
+  if (status || !ctrl->wide) return;
+  const uint64_t s = blockIdx.x;
+  const uint32_t hp = hp_task[s], lp = lp_task[s];
+  gf_predict_task(tb, hp, role[hp], ids, off, rows, row_off, pe, pg, open, predictor, ctrl);
+  __syncthreads();   // (the table is built anew)
+  if (lp != hp) gf_predict_task(tb, lp, role[lp], ids, off, rows, row_off, pe, pg, open, predictor, ctrl);
+  __threadfence_block();
+  __syncthreads();
+  if (threadIdx.x < WAVE)
+    gf_walk_scenario(s, off, hp_task, lp_task, gap_off, pe, pg, open, margin, min_gap, fill_count, filled_ns, completion_out, placed_out);
 }
 
 // ---------------------------------------------------------------------------------------------
