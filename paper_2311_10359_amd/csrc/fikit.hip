@@ -72,7 +72,7 @@ ProfileLayout profile_layout(uint64_t n, uint32_t n_tasks) {
   L.k1 = c.take(words);      // long tasks: tile-ordered IDs; general path: keys (sorted in the end)
   L.k2 = c.take(words);      // long tasks: tile-ordered values; general path: second key buffer, then segment starts
   L.e0 = c.take(words);
-  L.e1 = c.take(words);      // also: first half of the staged rows of long tasks
+  L.e1 = c.take(words);      // also: first half of the rows that a long task's units stage
   L.g0 = c.take(words);
   L.g1 = c.take(words);      // also: second half of them
   L.tiles = c.take((static_cast<uint64_t>(n_tasks) + 1) * 4);

@@ -6,7 +6,7 @@
 // what is left" is the same as "advance the queue pointer to the last position whose running sum
 // of durations does not exceed (consumed so far) + (gap - margin)".  Predictions are looked up once per
 // launch (k_gf_predict32) and are 32-bit numbers of nanoseconds; calls with a prediction that does not fit take
-// the 64-bit kernels (k_gf_predict, k_gf_walk).
+// the 64-bit kernels (k_gf_predict, k_gf_walk; k_gf_wide where both are one launch).
 #pragma once
 
 #include "common.hip.h"
@@ -589,7 +589,7 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
   };
   uint64_t total = 0;
   // Pairs of launches start at even elements, so that they are read as 16 bytes and written as 8 and 16; an odd first launch goes by itself.
-  // (IDs that lie on 8 bytes only are read one by one, and the results written so where they do not match.)
+  // (IDs that lie on 8 bytes only are read one by one.)
   const bool ids_vec = (reinterpret_cast<uintptr_t>(ids) & 15) == 0;
   const uint32_t lead = static_cast<uint32_t>(base & 1);
   const uint64_t step = static_cast<uint64_t>(gridDim.y) * (2 * PRED_THREADS);
@@ -615,8 +615,8 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
       if (lp_role) *reinterpret_cast<uint2*>(lp_e + base + i) = make_uint2(a0, a1);
       if (hp_role) *reinterpret_cast<uint4*>(hp_eg + base + i) = make_uint4(h0w, b0, h1w, b1);
     } else {
-      if (lp_role) { lp_e[base + i] = a0; if (two) lp_e[base + i + 1] = a1; }
-      if (hp_role) { hp_eg[base + i] = make_uint2(h0w, b0); if (two) hp_eg[base + i + 1] = make_uint2(h1w, b1); }
+      if (lp_role) lp_e[base + i] = a0;
+      if (hp_role) hp_eg[base + i] = make_uint2(h0w, b0);
     }
   };
   if (ids_vec) {

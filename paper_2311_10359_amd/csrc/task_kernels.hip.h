@@ -22,9 +22,9 @@
 //      means in LDS, the workgroup writes those predictions per launch itself, so that the gap fill does not have
 //      to read the Kernel IDs again and look each one up.
 //
-// Rows are staged in the task's own slice of two workspace arrays (the units of a long task share its slice) and moved to
-// their final place once every task's row count is known.  A task that does not fit (too many distinct IDs)
-// writes its per-launch values to the workspace arrays instead and is flagged for the general
+// Rows are staged, eight words each, in the task's own slices of up to six workspace arrays (Staging; the units of a long
+// task share its slices) and moved to their final place once every task's row count is known.  A task that does not fit (too
+// many distinct IDs) writes its per-launch values to the workspace arrays instead and is flagged for the general
 // sort-based path.
 #pragma once
 
