@@ -67,14 +67,13 @@ ProfileLayout profile_layout(uint64_t n, uint32_t n_tasks) {
   L.max_tiles = n / TILE + big_tasks;
   L.ctrl = c.take(256);
   L.k0 = c.take(n * 8);
-  // (six arrays of one size: rows of one-workgroup tasks are staged in them, see Staging)
-  const uint64_t words = n * 8 + 8;
-  L.k1 = c.take(words);      // long tasks: tile-ordered IDs; general path: keys (sorted in the end)
-  L.k2 = c.take(words);      // long tasks: tile-ordered values; general path: second key buffer, then segment starts
-  L.e0 = c.take(words);
-  L.e1 = c.take(words);      // also: first half of the rows that a long task's units stage
-  L.g0 = c.take(words);
-  L.g1 = c.take(words);      // also: second half of them
+  // (six arrays, evenly spaced: rows of one-workgroup tasks are staged in them, see Staging)
+  L.k1 = c.take(n * 8);      // long tasks: tile-ordered IDs; general path: keys (sorted in the end)
+  L.e0 = c.take(n * 8);
+  L.e1 = c.take(n * 8);      // also: first half of the rows that a long task's units stage
+  L.g0 = c.take(n * 8);
+  L.g1 = c.take(n * 8);      // also: second half of them
+  L.k2 = c.take(n * 8 + 8);  // long tasks: tile-ordered values; general path: second key buffer, then segment starts (one word more)
   L.tiles = c.take((static_cast<uint64_t>(n_tasks) + 1) * 4);
   uint64_t long_tasks = n / (static_cast<uint64_t>(FUSE_MAX) + 1);
   if (long_tasks > n_tasks) long_tasks = n_tasks;
@@ -106,7 +105,7 @@ ProfileLayout profile_layout(uint64_t n, uint32_t n_tasks) {
   L.total = c.at;
   return L;
 }
-static_assert(STAGING_ARRAYS == 6, "k1 .. g1");
+static_assert(STAGING_ARRAYS == 6, "k1 .. k2");
 
 // In-place exclusive prefix sum of `count` 32-bit words; the grand total goes to *d_total (may be null).
 int scan_u32(uint32_t* d_data, uint64_t count, uint32_t* d_sums, uint64_t* d_total, hipStream_t st) {
@@ -472,7 +471,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(medium), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(medium_lds)));
   FusedArgs fa{};
   fa.rec = d_records; fa.off = d_task_offsets; fa.ids = ids; fa.e0 = e0; fa.g0 = g0; fa.key0 = k1;
-  fa.staging = Staging{k1, (L.k2 - L.k1) / 8};
+  fa.staging = Staging{k1, (L.e0 - L.k1) / 8};
   fa.stage_a = e1; fa.stage_b = g1; fa.dcount = dcount; fa.gflag = gflag; fa.ctrl = ctrl;
   if (emit) {
     fa.pred_role = emit->role; fa.pred_lp_e = emit->lp_e; fa.pred_hp_eg = emit->hp_eg; fa.pred_lp_total = emit->lp_total;
