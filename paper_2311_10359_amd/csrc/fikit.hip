@@ -223,10 +223,17 @@ thread_local Mailbox t_mailbox;
 // One small kernel stores the words in the mailbox and the number of the wait behind them; the host looks at that number for a
 // while, and lets the runtime wait for the stream if it takes longer.  A kernel and this take 8.7 us; the same words copied
 // to pinned memory and the stream waited for 13.6 us with one copy, 16.2 us with two (a call that looks at two counts first: 14.3
-// against 6.5 us).  The runtime does not know that the stream is empty then: a device synchronisation right behind the call takes 12 to
-// 45 us instead of 3, any other use gains (pairs of 1000 launches in turn 58.8 us per step with copies, 53.2 with a report and the
-// runtime's wait, 48.5 so).  Stores of the kernels before have left the caches of their dies when this kernel starts, as for any kernel
+// against 6.5 us).  Stores of the kernels before have left the caches of their dies when this kernel starts, as for any kernel
 // that follows in the stream, so outputs are final for every stream, copy and thread.
+//
+// The runtime does not know then that the stream is empty, and a device synchronisation right behind the call would pay for that: 12 to
+// 28 us, against 3 behind a wait of its own.  So behind the last report of a call it is asked whether the stream is empty: it
+// puts a marker there, which passes while the host looks at the report, and such a synchronisation takes 3.5 to 5 us.  Calls in us that copy
+// and wait / do not ask / ask, each followed by a device synchronisation: a pair of 1000 launches 60.6 / 59.0 / 52.1, 16,384 scenarios'
+// pairing 94 to 98 / 92 / 87, 256 scenarios of 65,536 launches 361 / 370 / 347, priority queues of 4096 scenarios 1055 / 1061 / 1038; the first call on
+// new inputs 90 / 96 / 76, 115 / 124 / 108, 364 / 368 / 351; one behind the other 57 / 48 / 47 to 51, 93 / 81 / 83, 359 / 340 / 342, 1055 /
+// 1029 / 1033.  Asked at the waits inside a call too, 256 scenarios one behind the other take 353 us; asked once the report is there, a
+// pair 64; an event recorded instead, a pair 47, and 51 with the synchronisation, but 256 scenarios 366 us with it.
 struct Reads {
   static constexpr int MOST = 4;
   static constexpr int64_t LOOK_NS = 1000000;   // (the runtime's wait adds 4 us, which a call of this length no longer feels)
@@ -244,7 +251,8 @@ struct Reads {
     ++n;
     return FIKIT_OK;
   }
-  int wait() {
+  // (last: nothing of the call follows)
+  int wait(bool last) {
     if (!box) {
       for (int i = 0; i < n; ++i) FIKIT_HIP(hipMemcpyAsync(item[i].to, item[i].from, item[i].bytes, hipMemcpyDeviceToHost, st));
       FIKIT_HIP(hipStreamSynchronize(st));
@@ -260,6 +268,10 @@ struct Reads {
     }
     hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, r, seen, number);
     FIKIT_HIP(hipGetLastError());
+    if (last) {
+      (void)hipStreamQuery(st);   // (the answer is that it is not, which would stand as the last error)
+      (void)hipGetLastError();
+    }
     auto arrived = [&] { return __atomic_load_n(seen, __ATOMIC_ACQUIRE) == number; };
     const auto from = std::chrono::steady_clock::now();
     for (uint32_t looks = 1; !arrived(); ++looks) {
@@ -278,10 +290,10 @@ static_assert(2 * Reads::place(sizeof(Ctrl)) <= Mailbox::BYTES && 3 * Reads::pla
               "what one wait brings fits: two control blocks, or three counts");
 static_assert(Reads::MOST == REPORT_READS && sizeof(Ctrl) % 4 == 0, "what a report holds");
 
-int read_ctrl(const Ctrl* d_ctrl, Ctrl* h, hipStream_t st) {
+int read_ctrl(const Ctrl* d_ctrl, Ctrl* h, hipStream_t st, bool last = true) {
   Reads r(st);
   if (int rc = r.add(h, d_ctrl, sizeof(Ctrl))) return rc;
-  return r.wait();
+  return r.wait(last);
 }
 
 template <int NT, int KPT, int DMAX, int WPE>
@@ -454,7 +466,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   uint64_t n_class[3] = {n < n_tasks ? n : n_tasks, n / (FUSE_SMALL_MAX + 1), n / (FUSE_MID_MAX + 1)};
   if (n > FUSE_MAX) {
     tr.mark("host_sync");
-    if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+    if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
     if (int rc = status_from_bits(h.status)) return rc;
     for (int k = 0; k < 3; ++k) n_class[k] = h.n_class[k];
   }
@@ -507,7 +519,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
       if (int rc = scan_u32(is_long, static_cast<uint64_t>(n_tasks) + 1, sums, nullptr, st)) return rc;
       if (int rc = scan_u32(mtiles, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_big_tiles, st)) return rc;
       tr.mark("host_sync");
-      if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+      if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
     }
     n_msd_tiles = h.n_big_tiles;
     if (n_msd_tiles == 0 || n_msd_tiles > L.max_ptiles) return FIKIT_HIP_ERROR;
@@ -579,7 +591,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     if (int rc = ahead(tr, reads, ctrl, any_long)) return rc;
     tr.mark("host_sync");
     if (int rc = reads.add(&h, ctrl, sizeof(Ctrl))) return rc;
-    if (int rc = reads.wait()) return rc;
+    if (int rc = reads.wait(true)) return rc;
   }
   if (int rc = status_from_bits(h.status)) return rc;
   if (h.n_general == 0) {
@@ -604,7 +616,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
                        d_task_offsets, n_tasks, gflag, tiles, ctrl);
     if (int rc = scan_u32(tiles, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_big_tiles, st)) return rc;
     tr.mark("host_sync");
-    if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+    if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
     if (int rc = status_from_bits(h.status)) return rc;
     const uint64_t n_big_tiles = h.n_big_tiles;
     if (n_big_tiles > L.max_tiles) return FIKIT_HIP_ERROR;  // cannot happen for valid offsets
@@ -655,7 +667,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
       hipLaunchKernelGGL(k_popcount_words, dim3(blocks_for(L.n_words, 256)), dim3(256), 0, st, bits, L.n_words, word_prefix);
       if (int rc = scan_u32(word_prefix, L.n_words, sums, &ctrl->n_heads, st)) return rc;
       tr.mark("host_sync");
-      if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+      if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
       return status_from_bits(h.status);   // (a wait of the sort that ran out)
     };
     if (n_big_tiles > 0)
@@ -680,7 +692,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   hipLaunchKernelGGL(k_widen_offsets, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, dcount,
                      static_cast<uint64_t>(n_tasks) + 1, d_task_row_offsets);
   tr.mark("host_sync");
-  if (int rc = read_ctrl(ctrl, &h, st)) return rc;
+  if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
   const uint64_t n_rows = h.n_rows;
   *h_n_rows = n_rows;
   if (n_rows > row_capacity) return FIKIT_ROW_CAPACITY;
@@ -961,7 +973,7 @@ int fikit_gapfill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint32_
   Reads counts(st);
   if (int rc = counts.add(&n_ids, d_task_offsets + n_tasks, 8)) return rc;
   if (int rc = counts.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
-  if (int rc = counts.wait()) return rc;
+  if (int rc = counts.wait(false)) return rc;
   if (n_ids >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if (n_ids > 0 && (!d_ids || !d_rows)) return FIKIT_INVALID_ARG;
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
@@ -1019,7 +1031,7 @@ int fikit_profile_gapfill(const fikit_launch* d_records, uint64_t n_records, con
   if (!d_fill_count || !d_filled_ns || n_scenarios >= GF_LANES_MIN_SCENARIOS) {
     Reads r(st);
     if (int rc = r.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
-    if (int rc = r.wait()) return rc;
+    if (int rc = r.wait(false)) return rc;
     if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
   }
 
@@ -1216,7 +1228,7 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   Reads counts(st);
   if (int rc = counts.add(&n_ids, d_task_offsets + n_tasks, 8)) return rc;
   if (int rc = counts.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
-  if (int rc = counts.wait()) return rc;
+  if (int rc = counts.wait(false)) return rc;
   if (n_ids >= MAX_ELEMS || n_gaps >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if (n_ids > 0 && (!d_ids || !d_rows || !d_actual_gap_ns)) return FIKIT_INVALID_ARG;
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
@@ -1310,7 +1322,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   if (int rc = counts.add(&n_ids, d_task_offsets + n_tasks, 8)) return rc;
   if (int rc = counts.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
   if (int rc = counts.add(&n_entries, d_lp_offsets + n_scenarios, 8)) return rc;
-  if (int rc = counts.wait()) return rc;
+  if (int rc = counts.wait(false)) return rc;
   if (n_ids >= MAX_ELEMS || n_gaps >= MAX_ELEMS || n_entries >= MAX_ELEMS) return FIKIT_INVALID_ARG;
   if (n_ids > 0 && (!d_ids || !d_rows)) return FIKIT_INVALID_ARG;
   if (n_gaps > 0 && (!d_fill_count || !d_filled_ns)) return FIKIT_INVALID_ARG;
@@ -1344,7 +1356,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
   Ctrl h{};
-  if (int rc = read_ctrl(ctrl, &h, st)) return rc;   // the widest scenario decides how many lanes share one
+  if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;   // the widest scenario decides how many lanes share one
   if (int rc = status_from_bits(h.status)) return rc;
   const uint32_t widest = h.n_class[3];
   // Up to 64 low-priority tasks per scenario: a wave or a group of lanes per scenario on 32-bit predictions; the 64-bit
@@ -1429,7 +1441,7 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
     uint64_t n_gaps = 0;
     Reads r(st);
     if (int rc = r.add(&n_gaps, d_gap_offsets + n_scenarios, 8)) return rc;
-    if (int rc = r.wait()) return rc;
+    if (int rc = r.wait(false)) return rc;
     if (n_gaps > 0) return FIKIT_INVALID_ARG;
   }
   unsigned char* ws = static_cast<unsigned char*>(d_workspace);
@@ -1493,7 +1505,7 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
     Reads counts(st);
     if (int rc = counts.add(&na, d_task_row_offsets_a + n_tasks, 8)) return rc;
     if (int rc = counts.add(&nb, d_task_row_offsets_b + n_tasks, 8)) return rc;
-    if (int rc = counts.wait()) return rc;
+    if (int rc = counts.wait(false)) return rc;
     if ((na > 0 && !d_rows_a) || (nb > 0 && !d_rows_b)) return FIKIT_INVALID_ARG;
   }
 
