@@ -275,14 +275,24 @@ __device__ __forceinline__ void unit_to_general(const FusedArgs& A, uint32_t t) 
 }
 
 // Workgroups that start together and have the same to do stay together: all of them read, then all of them rank, and the memory
-// waits.  The largest shape, of which a compute unit holds one, has its first workgroups start spread over most of what a task takes
-// (70 us), if so many tasks follow that it pays.  us per call without / with it: profile of 1024 tasks of 16,384 launches
-// 411 / 392, 2048 751 / 697, 4096 1399 / 1300, 8192 of 10,000 launches 1832 / 1725; step of 16,384 pairs 7173 / 7015 (spread over half or one
-// and a half times as much: less); 6000 tasks of 1 to 16,000 launches, which do not stay together, 1626 / 1629.  The smaller shapes, of which
-// a compute unit holds two or three, gain nothing.
-constexpr uint32_t FUSE_SPREAD_TASKS = 1024, FUSE_SPREAD_WORKGROUPS = 256, FUSE_SPREAD_STEPS = 55;   // (a step is 2048 cycles)
-__device__ __forceinline__ void spread_start(uint32_t block) {
-  const uint32_t steps = ((block * 40503u) & 0xffffu) * FUSE_SPREAD_STEPS >> 16;   // (multiples of the golden ratio)
+// waits.  The largest shape, of which a compute unit holds one, has its first workgroups start spread over half of what a
+// task takes or a little more, so by its own length (47 us for one of FUSE_MAX launches).  Tasks of many kernels
+// rank for so long that they gain little, and the later start is lost to them; with fewer than eight tasks per
+// compute unit that shows, and the spread is shortened in proportion.  us per call of fikit_profile, no spread / this one:
+//   kernels per task            20            100            200            300
+//   1024 tasks of  8200    246 / 242      270 / 268      304 / 303      337 / 337
+//   1024 of       16,384   389 / 375      420 / 417      461 / 462      505 / 513
+//   2048 of        8200    432 / 408      483 / 464      544 / 543      607 / 611
+//   2048 of       16,384   699 / 653      766 / 718      841 / 822      942 / 947
+//   4096 of        8200    795 / 755      890 / 854     1021 / 1003    1161 / 1157
+//   4096 of       16,384  1290 / 1200    1424 / 1326    1577 / 1536    1800 / 1796
+// (47 us for all: 1024 tasks of 8200 launches 251, 286, 331 and 369 us, 4096 of them and 300 kernels 1174; not shortened: 1024 of 16,384 launches and
+// 300 kernels 527.)  Tasks of all lengths, which do not stay together: 4000 of 1 to 18,000 launches, 100 kernels, 1519 / 1515.  The smaller
+// shapes, of which a compute unit holds two or three, gain nothing.
+constexpr uint32_t FUSE_SPREAD_TASKS = 1024, FUSE_SPREAD_ALL = 2048, FUSE_SPREAD_WORKGROUPS = 256, FUSE_SPREAD_STEPS = 55;   // (a step is 2048 cycles)
+__device__ __forceinline__ void spread_start(uint32_t block, uint32_t launches, uint32_t tasks) {
+  const uint32_t most = FUSE_SPREAD_STEPS * launches / FUSE_MAX * min_u32(tasks, FUSE_SPREAD_ALL) / FUSE_SPREAD_ALL;
+  const uint32_t steps = ((block * 40503u) & 0xffffu) * most >> 16;   // (multiples of the golden ratio)
   for (uint32_t k = 0; k < steps; ++k) __builtin_amdgcn_s_sleep(32);
 }
 
@@ -297,11 +307,11 @@ k_task_fused(const FusedArgs A) {
   if (ctrl->status & ERR_OFFSETS) return;
   const uint32_t tasks = *A.count;
   if (blockIdx.x >= tasks) return;
-  if (NT == FUSE_M_THREADS && blockIdx.x < FUSE_SPREAD_WORKGROUPS && tasks >= FUSE_SPREAD_TASKS) spread_start(blockIdx.x);
   const uint32_t t = A.list[blockIdx.x];
   const uint64_t base = A.off[t], len64 = A.off[t + 1] - base;
   if (len64 == 0 || len64 > A.max_len) return;   // (cannot happen for a listed item)
   const uint32_t m = static_cast<uint32_t>(len64);
+  if (NT == FUSE_M_THREADS && blockIdx.x < FUSE_SPREAD_WORKGROUPS && tasks >= FUSE_SPREAD_TASKS) spread_start(blockIdx.x, m, tasks);
   const fikit_launch* __restrict__ rec = A.rec;
   uint64_t* __restrict__ ids = A.ids;
   int64_t* __restrict__ e0 = A.e0;
