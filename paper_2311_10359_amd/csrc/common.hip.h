@@ -43,10 +43,10 @@ struct Ctrl {
   uint64_t n_long;        // tasks too long for the one-workgroup path
   uint64_t n_heads;       // rows found by the general path
   uint32_t n_class[6];    // length of the work lists: small, mid, medium tasks or units, and units that are streamed (huge from
-                          // the list's front, others from its back), and how many of these are longest; priority queues: [3] holds the largest number of
-                          // low-priority tasks of a scenario
+                          // the list's front, others from its back), and how many of these are longest; priority queues: [3]
+                          // holds the largest number of low-priority tasks of a scenario
   uint32_t taken;         // large and streamed units: how many have been taken
-  uint32_t reserved;
+  uint32_t n_large;       // ... and the launches of all of them
 };
 static_assert(sizeof(Ctrl) == 80, "control block");
 

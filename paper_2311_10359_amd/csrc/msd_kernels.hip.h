@@ -291,6 +291,8 @@ k_msd_units(const uint64_t* __restrict__ off, uint32_t n_tasks, const uint32_t* 
   const bool streamed = live && (l > FUSE_MAX || tiles_t > UNIT_RUNS_MAX);
   if (streamed && l > STREAM_LONGEST) atomicAdd(&ctrl->n_class[5], 1u);
   const uint32_t c = !live ? 5u : streamed ? (l > STREAM_HUGE ? 3u : 4u) : (l <= FUSE_SMALL_MAX ? 0u : (l <= FUSE_MID_MAX ? 1u : 2u));
+  const uint32_t in_large = wave_sum_u32(c >= 2 && c <= 4 ? l : 0u);   // (k_unit_large's part of the launches, of which there are fewer than 2^32)
+  if (in_large && lane_id() == 0) atomicAdd(&ctrl->n_large, in_large);
   __syncthreads();   // (aux is reused)
   for (uint32_t k = 0; k < 5; ++k) {
     uint32_t total;

@@ -495,13 +495,18 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
 // The streamed units and, beside them, the units of more than FUSE_MID_MAX launches: both need a compute unit's whole LDS, and the
 // longest streamed units leave most of the chip to the others (64 tasks of 1,048,576 launches, Zipf over 4096 IDs: 915 us
 // in a launch each, 726 us together; workgroups that stay also save the 30 us that 33,000 without a unit take to come and go).
-// Workgroups stay, one per compute unit, and take units in order from a counter: streamed ones from the front of their list (the largest first), then
-// from its back, then the others.  One of the front's is taken by
-// two workgroups, one for the execution times and one for the idle times, where that leaves a compute unit to each: all of them, or only those of
-// more than STREAM_LONGEST launches, or none.  What a unit of 227,000 launches takes decides the launch then, and the memory of one
-// compute unit decides that; both workgroups find and rank the IDs, and nothing is waited for, but all of it together is a third more
-// work.  This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only the
-// longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000 1700 / 1391.
+// Workgroups stay, one per compute unit, and take units in order from a counter: streamed ones from the front of their list (the
+// largest first), then from its back, then the others.
+//
+// One of the front's is taken by two workgroups, one for the execution times and one for the idle times, where that leaves a
+// compute unit to each: all of them, or only those of more than STREAM_LONGEST launches, or none.  What a unit of 227,000 launches
+// takes decides the launch then, and the memory of one compute unit decides that; both workgroups find and rank the IDs, and
+// nothing is waited for, but all of it together is a third more work.  So no unit is taken so that is not longer, by a quarter, than
+// what there is for each workgroup to do: the other units fill the chip then, and the third more is all that comes of it.
+// This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only the
+// longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000 1700 /
+// 1391; 60 of 400,000, two IDs with 0.3 of the launches each and 30 others 273 / 242.  Left whole for what else there is: 100 tasks of
+// 300,000, one ID with 0.3 of the launches and 20 others 378 / 418, 40 of 2,000,000, two IDs with 0.1 each and 200 others 655 / 747.
 constexpr uint64_t UNIT_LARGE_WORKGROUPS = 256;
 constexpr uint32_t SU_SPLIT_PARTS = 192;
 __global__ void __launch_bounds__(SU_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
@@ -512,7 +517,9 @@ k_unit_large(const FusedArgs A, const uint32_t* __restrict__ streamed, uint32_t 
   if (A.ctrl->status & ERR_OFFSETS) return;
   const uint32_t large = A.ctrl->n_class[2], front = A.ctrl->n_class[3], back = A.ctrl->n_class[4];
   const uint32_t longest = A.ctrl->n_class[5];   // units of more than STREAM_LONGEST
-  const uint32_t split_above = 2 * front <= UNIT_LARGE_WORKGROUPS ? 0u : 2 * longest <= SU_SPLIT_PARTS ? STREAM_LONGEST : ~0u;
+  const uint32_t for_each = A.ctrl->n_large / static_cast<uint32_t>(UNIT_LARGE_WORKGROUPS);
+  const uint32_t split_above = max_u32(2 * front <= UNIT_LARGE_WORKGROUPS ? 0u : 2 * longest <= SU_SPLIT_PARTS ? STREAM_LONGEST : ~0u,
+                                       for_each + for_each / 4);
   for (;;) {
     if (threadIdx.x == 0) ticket = atomicAdd(&A.ctrl->taken, 1u);
     __syncthreads();

@@ -1,0 +1,66 @@
+"""Streamed units beside so many others that the chip is full without cutting them in two: against the CPU oracle, beside one that
+is cut, and what the launch takes."""
+import statistics
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2311_10359_amd import binding, traces
+from parity_util import DEV, assert_profile_equal
+
+pytestmark = pytest.mark.gpu
+LONG = 300_000
+
+
+def task(rng, launches, share, others):
+    """A kernel with `share` of the launches, and others with the same number each."""
+    kid = np.where(rng.random(launches) < share, 0, 1 + rng.integers(0, others, launches))
+    rec = np.zeros(launches, dtype=traces.LAUNCH_DTYPE)
+    rec["name_id"], rec["grid"], rec["block"] = kid * 7919, 1, 64
+    ex, gap = (np.rint(rng.lognormal(m, 1.1, launches)).astype(np.int64) for m in (8.5, 9.6))
+    rec["start_ns"] = np.cumsum(ex + gap) - (ex + gap)
+    rec["end_ns"] = rec["start_ns"] + ex
+    return rec
+
+
+def together(parts):
+    """Tasks (records, how often) one behind the other on the GPU, their offsets, and what the oracle says of all."""
+    recs, lens, ids, rows, counts, at = [], [], [], [], [], 0
+    for rec, times in parts:
+        off = np.array([0, rec.size], dtype=np.uint64)
+        o_ids, o_rows, _ = oracle.profile(rec, off)
+        recs.append(binding.to_device_records(rec, DEV).repeat(times, 1))
+        lens += [rec.size] * times
+        ids.append(np.tile(o_ids, times))
+        r = np.tile(o_rows, times)
+        r["task"] = np.repeat(np.arange(at, at + times, dtype=np.uint32), o_rows.size)
+        rows.append(r)
+        counts += [o_rows.size] * times
+        at += times
+    ends = [np.concatenate([[0], np.cumsum(x)]).astype(np.uint64) for x in (lens, counts)]
+    return torch.cat(recs), ends[0], (np.concatenate(ids), np.concatenate(rows), ends[1])
+
+
+@pytest.mark.parametrize("parts", [[(LONG, 0.3, 20, 100)], [(LONG, 0.3, 20, 60), (4_000_000, 0.6, 30, 1)], [(LONG, 0.3, 600, 100)]])
+def test_units_left_whole(parts):
+    rng = np.random.default_rng(len(parts))
+    d_rec, off, want = together([(task(rng, *p[:3]), p[3]) for p in parts])
+    assert_profile_equal(binding.fikit_profile(d_rec, binding.to_device_u64(off, DEV)), *want)
+
+
+def test_no_work_is_done_twice_where_the_chip_is_full():
+    rec = task(np.random.default_rng(1), LONG, 0.3, 20)
+    took = {}
+    for tasks in (100, 130):             # (with 130 there are more such units than half the workgroups, and none is cut)
+        d_rec, off = binding.to_device_records(rec, DEV).repeat(tasks, 1), binding.to_device_u64(np.arange(tasks + 1, dtype=np.uint64) * LONG, DEV)
+        ms = []
+        for _ in range(12):
+            binding.fikit_trace_enable(True)
+            binding.fikit_profile(d_rec, off)
+            ms.append(binding.fikit_trace_read()["k_unit_large"][0])
+            binding.fikit_trace_enable(False)
+        took[tasks] = statistics.median(ms) / tasks
+    print({k: f"{v * 1e3:.2f} us per task" for k, v in took.items()}, flush=True)
+    assert took[100] < 1.05 * took[130]  # 1.11 with the units cut in two
