@@ -35,6 +35,14 @@ constexpr uint64_t MAX_ELEMS = (1ull << 32) - (1ull << 24);
     }                                             \
   } while (0)
 
+// Launches of this thread since the last wait of a call (see Reads::wait).
+thread_local uint32_t t_launches = 0;
+#define FIKIT_COUNT_LAUNCH(...)      \
+  do {                               \
+    ++t_launches;                    \
+    hipLaunchKernelGGL(__VA_ARGS__); \
+  } while (0)
+
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 inline uint32_t blocks_for(uint64_t items, uint32_t per_block) {
@@ -110,9 +118,9 @@ static_assert(STAGING_ARRAYS == 6, "k1 .. k2");
 // In-place exclusive prefix sum of `count` 32-bit words; the grand total goes to *d_total (may be null).
 int scan_u32(uint32_t* d_data, uint64_t count, uint32_t* d_sums, uint64_t* d_total, hipStream_t st) {
   const uint32_t nb = blocks_for(count, SCAN_TILE);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_data, count, d_sums);
-  hipLaunchKernelGGL(k_scan_spine, dim3(1), dim3(SCAN_BLOCK), 0, st, d_sums, static_cast<uint64_t>(nb), d_total);
-  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_data, count, d_sums);
+  FIKIT_COUNT_LAUNCH(k_scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_data, count, d_sums);
+  FIKIT_COUNT_LAUNCH(k_scan_spine, dim3(1), dim3(SCAN_BLOCK), 0, st, d_sums, static_cast<uint64_t>(nb), d_total);
+  FIKIT_COUNT_LAUNCH(k_scan_apply, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_data, count, d_sums);
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
 }
@@ -120,12 +128,12 @@ int scan_u32(uint32_t* d_data, uint64_t count, uint32_t* d_sums, uint64_t* d_tot
 // 64-bit offsets and their total (ctrl->n_rows) from `count` 32-bit row counts, the last of which is 0; see k_row_offsets.
 int row_offsets_enqueue(const uint32_t* d_counts, uint64_t count, uint32_t* d_sums, uint64_t* d_out, Ctrl* ctrl, hipStream_t st) {
   if (count <= ROW_SCAN_ONE) {
-    hipLaunchKernelGGL(k_row_offsets, dim3(blocks_for(count, ROW_SCAN_TILE)), dim3(1024), 0, st, d_counts, count, d_out, ctrl);
+    FIKIT_COUNT_LAUNCH(k_row_offsets, dim3(blocks_for(count, ROW_SCAN_TILE)), dim3(1024), 0, st, d_counts, count, d_out, ctrl);
   } else {
     const uint32_t nb = blocks_for(count, SCAN_TILE);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums);
-    hipLaunchKernelGGL(k_scan_spine, dim3(1), dim3(SCAN_BLOCK), 0, st, d_sums, static_cast<uint64_t>(nb), &ctrl->n_rows);
-    hipLaunchKernelGGL(k_row_offsets_apply, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums, d_out, ctrl);
+    FIKIT_COUNT_LAUNCH(k_scan_reduce, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums);
+    FIKIT_COUNT_LAUNCH(k_scan_spine, dim3(1), dim3(SCAN_BLOCK), 0, st, d_sums, static_cast<uint64_t>(nb), &ctrl->n_rows);
+    FIKIT_COUNT_LAUNCH(k_row_offsets_apply, dim3(nb), dim3(SCAN_BLOCK), 0, st, d_counts, count, d_sums, d_out, ctrl);
   }
   FIKIT_HIP(hipGetLastError());
   return FIKIT_OK;
@@ -226,17 +234,27 @@ thread_local Mailbox t_mailbox;
 // against 6.5 us).  Stores of the kernels before have left the caches of their dies when this kernel starts, as for any kernel
 // that follows in the stream, so outputs are final for every stream, copy and thread.
 //
-// The runtime does not know then that the stream is empty, and a device synchronisation right behind the call would pay for that: 12 to
-// 28 us, against 3 behind a wait of its own.  So behind the last report of a call it is asked whether the stream is empty: it
-// puts a marker there, which passes while the host looks at the report, and such a synchronisation takes 3.5 to 5 us.  Calls in us that copy
-// and wait / do not ask / ask, each followed by a device synchronisation: a pair of 1000 launches 60.6 / 59.0 / 52.1, 16,384 scenarios'
-// pairing 94 to 98 / 92 / 87, 256 scenarios of 65,536 launches 361 / 370 / 347, priority queues of 4096 scenarios 1055 / 1061 / 1038; the first call on
-// new inputs 90 / 96 / 76, 115 / 124 / 108, 364 / 368 / 351; one behind the other 57 / 48 / 47 to 51, 93 / 81 / 83, 359 / 340 / 342, 1055 /
-// 1029 / 1033.  Asked at the waits inside a call too, 256 scenarios one behind the other take 353 us; asked once the report is there, a
-// pair 64; an event recorded instead, a pair 47, and 51 with the synchronisation, but 256 scenarios 366 us with it.
+// The runtime does not know then that the stream is empty, and a synchronisation of the caller's right behind the call pays for that.  It
+// goes by the commands since its own last wait: up to RUNTIME_WAITS, the one of the wait among them, it waits itself, beyond them it
+// leaves it to its handler thread, which takes 20 us longer.  (A synchronisation behind N empty kernels and a report that has been seen: 9 us up to N = 6, 24 us
+// from 7 on; with an event recorded behind the report 5.6 us up to N = 5.)  So behind the last report of a call of few launches an event is
+// recorded, which nobody waits for; in a longer one the runtime is asked whether the stream is empty, which sets the handler to work,
+// but only once the host has looked for ASK_NS: asking takes 14 us, which then pass while the call does.
+// Calls in us, with copies and the runtime's wait / reports alone / now:    one behind the other     each with a device synchronisation
+//   fikit_measure, 1000 launches                                              28 / 27 / 26             31 / 35 / 29
+//   pairing of 16 scenarios                                                   33 / 27 / 27             36 / 36 / 30
+//   step of a pair of 1000 launches                                           57 / 48 / 48             60 / 59 / 50
+//   merge of 16 tasks of 20 rows (seven launches, over before it is asked)    50 / 38 / 38             53 / 46 / 46
+//   priority queues, one scenario of two                                     120 / 103 / 106          121 / 131 / 110
+//   merge of 20,000 tasks of 90 rows                                         287 / 235 / 234          290 / 246 / 237
+//   step of 256 scenarios of 65,536 launches                                 358 / 341 / 342          361 / 374 / 350
+//   priority queues, 4096 scenarios of three                                1060 / 1038 / 1041       1059 / 1067 / 1041
+// (asked at once in every call: fikit_measure 38 to 44, the small merge 51 to 55, the step of a pair 47 to 51 one behind the other.)
 struct Reads {
   static constexpr int MOST = 4;
   static constexpr int64_t LOOK_NS = 1000000;   // (the runtime's wait adds 4 us, which a call of this length no longer feels)
+  static constexpr int64_t ASK_NS = 30000;
+  static constexpr uint32_t RUNTIME_WAITS = 8;
   static constexpr size_t place(size_t bytes) { return (bytes + 15) / 16 * 16; }
   hipStream_t st;
   unsigned char* box = t_mailbox.get();
@@ -266,17 +284,34 @@ struct Reads {
       r.to[i] = reinterpret_cast<uint32_t*>(box + item[i].at);
       r.words[i] = static_cast<uint32_t>(item[i].bytes / 4);
     }
-    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, r, seen, number);
+    FIKIT_COUNT_LAUNCH(k_report, dim3(1), dim3(64), 0, st, r, seen, number);
     FIKIT_HIP(hipGetLastError());
+    bool ask = false;
     if (last) {
-      (void)hipStreamQuery(st);   // (the answer is that it is not, which would stand as the last error)
-      (void)hipGetLastError();
+      const bool few = t_launches + 2 <= RUNTIME_WAITS;   // (the event and the wait's own command)
+      t_launches = 0;
+      ask = !few;
+      if (few) {
+        hipEvent_t behind;
+        if (hipEventCreateWithFlags(&behind, hipEventDisableTiming) == hipSuccess) {
+          (void)hipEventRecord(behind, st);
+          (void)hipEventDestroy(behind);
+        }
+        (void)hipGetLastError();
+      }
     }
     auto arrived = [&] { return __atomic_load_n(seen, __ATOMIC_ACQUIRE) == number; };
     const auto from = std::chrono::steady_clock::now();
     for (uint32_t looks = 1; !arrived(); ++looks) {
       __builtin_ia32_pause();
-      if (looks % 64 == 0 && std::chrono::steady_clock::now() - from > std::chrono::nanoseconds(LOOK_NS)) {
+      if (looks % 64 != 0) continue;
+      const auto looked = std::chrono::steady_clock::now() - from;
+      if (ask && looked > std::chrono::nanoseconds(ASK_NS)) {
+        ask = false;
+        (void)hipStreamQuery(st);   // (the answer is that it is not, which would stand as the last error)
+        (void)hipGetLastError();
+      }
+      if (looked > std::chrono::nanoseconds(LOOK_NS)) {
         FIKIT_HIP(hipStreamSynchronize(st));
         if (!arrived()) return FIKIT_HIP_ERROR;
         break;
@@ -303,7 +338,7 @@ int launch_units(dim3 grid, const FusedArgs& args, hipStream_t st) {
   static_assert(lds <= 160 * 1024, "fits a compute unit's LDS");
   auto kernel = k_unit_sorted<NT, KPT, DMAX, WPE>;
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-  hipLaunchKernelGGL(kernel, dim3(xcd_grid(grid.x)), dim3(NT), lds, st, args);
+  FIKIT_COUNT_LAUNCH(kernel, dim3(xcd_grid(grid.x)), dim3(NT), lds, st, args);
   return FIKIT_OK;
 }
 
@@ -314,7 +349,7 @@ int launch_prio_walk(hipStream_t st, const uint64_t* off, const uint32_t* hp_tas
                      int64_t* filled_ns, uint64_t* placed, int64_t* placed_ns, uint32_t vec_ok, const Ctrl* ctrl) {
   FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_pf_walk<W>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 static_cast<int>(sizeof(PrioWalkSmem<W>))));
-  hipLaunchKernelGGL(k_pf_walk<W>, dim3(blocks_for(n_scen * W, PW_THREADS)), dim3(PW_THREADS), sizeof(PrioWalkSmem<W>), st, off,
+  FIKIT_COUNT_LAUNCH(k_pf_walk<W>, dim3(blocks_for(n_scen * W, PW_THREADS)), dim3(PW_THREADS), sizeof(PrioWalkSmem<W>), st, off,
                      hp_task, lp_off, lp_task, lp_prio, n_scen, gap_off, lp_e, hp_eg, margin, min_gap, fill_count, filled_ns,
                      placed, placed_ns, vec_ok, ctrl);
   return FIKIT_OK;
@@ -417,9 +452,9 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   tr.mark("setup");
   Ctrl h{};
   if (n == 0) {
-    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-    hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(2 * (static_cast<uint64_t>(n_tasks) + 1), 256)), dim3(256), 0, st,
+    FIKIT_COUNT_LAUNCH(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
+    FIKIT_COUNT_LAUNCH(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
+    FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(blocks_for(2 * (static_cast<uint64_t>(n_tasks) + 1), 256)), dim3(256), 0, st,
                        reinterpret_cast<uint32_t*>(d_task_row_offsets), 2 * (static_cast<uint64_t>(n_tasks) + 1), 0u);
     FIKIT_HIP(hipGetLastError());
     if (int rc = read_ctrl(ctrl, &h, st)) return rc;
@@ -451,13 +486,13 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   if (few_tasks) {
     const ProfileBegin pb{n, FUSE_SMALL_MAX, FUSE_MID_MAX, FUSE_MAX, PT_TILE, gflag, dcount, lists, is_long, mtiles, wflag, ctrl};
     if (begin)
-      hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, pb, *begin);
+      FIKIT_COUNT_LAUNCH(k_step_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, pb, *begin);
     else
-      hipLaunchKernelGGL(k_profile_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, pb);
+      FIKIT_COUNT_LAUNCH(k_profile_begin, dim3(1), dim3(BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, pb);
   } else {
-    hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-    hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
-    hipLaunchKernelGGL(k_classify, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
+    FIKIT_COUNT_LAUNCH(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n, ctrl);
+    FIKIT_COUNT_LAUNCH(k_classify, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
                        n_tasks, FUSE_SMALL_MAX, FUSE_MID_MAX, FUSE_MAX, gflag, dcount, lists, ctrl);
   }
   FIKIT_HIP(hipGetLastError());
@@ -492,17 +527,17 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   if (n_class[0]) {
     tr.mark("k_task_fused_small");
     fa.list = lists; fa.count = &ctrl->n_class[0]; fa.max_len = FUSE_SMALL_MAX;
-    hipLaunchKernelGGL(small, dim3(static_cast<uint32_t>(n_class[0])), dim3(FUSE_S_THREADS), small_lds, st, fa);
+    FIKIT_COUNT_LAUNCH(small, dim3(static_cast<uint32_t>(n_class[0])), dim3(FUSE_S_THREADS), small_lds, st, fa);
   }
   if (n_class[1]) {
     tr.mark("k_task_fused_mid");
     fa.list = lists + n_tasks; fa.count = &ctrl->n_class[1]; fa.max_len = FUSE_MID_MAX;
-    hipLaunchKernelGGL(mid, dim3(static_cast<uint32_t>(n_class[1])), dim3(512), mid_lds, st, fa);
+    FIKIT_COUNT_LAUNCH(mid, dim3(static_cast<uint32_t>(n_class[1])), dim3(512), mid_lds, st, fa);
   }
   if (n_class[2]) {
     tr.mark("k_task_fused_medium");
     fa.list = lists + 2 * static_cast<uint64_t>(n_tasks); fa.count = &ctrl->n_class[2]; fa.max_len = FUSE_MAX;
-    hipLaunchKernelGGL(medium, dim3(static_cast<uint32_t>(n_class[2])), dim3(FUSE_M_THREADS), medium_lds, st, fa);
+    FIKIT_COUNT_LAUNCH(medium, dim3(static_cast<uint32_t>(n_class[2])), dim3(FUSE_M_THREADS), medium_lds, st, fa);
   }
   FIKIT_HIP(hipGetLastError());
   uint64_t n_units = 0, n_msd_tiles = 0;
@@ -514,7 +549,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     if (n_units > L.max_units) return FIKIT_HIP_ERROR;   // cannot happen: a long task has more than FUSE_MAX launches
     if (!few_tasks) {
       tr.mark("plan");
-      hipLaunchKernelGGL(k_plan_msd, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
+      FIKIT_COUNT_LAUNCH(k_plan_msd, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, d_task_offsets,
                          n_tasks, gflag, is_long, mtiles, wflag);
       if (int rc = scan_u32(is_long, static_cast<uint64_t>(n_tasks) + 1, sums, nullptr, st)) return rc;
       if (int rc = scan_u32(mtiles, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_big_tiles, st)) return rc;
@@ -524,13 +559,13 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     n_msd_tiles = h.n_big_tiles;
     if (n_msd_tiles == 0 || n_msd_tiles > L.max_ptiles) return FIKIT_HIP_ERROR;
     tr.mark("k_tile_partition");
-    hipLaunchKernelGGL(k_msd_clear, dim3(blocks_for(n_units, 256)), dim3(256), 0, st, bucket_size, n_units, ctrl);
+    FIKIT_COUNT_LAUNCH(k_msd_clear, dim3(blocks_for(n_units, 256)), dim3(256), 0, st, bucket_size, n_units, ctrl);
     FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_tile_partition), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   static_cast<int>(sizeof(PartSmem))));
-    hipLaunchKernelGGL(k_tile_partition, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(PT_THREADS), sizeof(PartSmem), st, d_records,
+    FIKIT_COUNT_LAUNCH(k_tile_partition, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(PT_THREADS), sizeof(PartSmem), st, d_records,
                        d_task_offsets, n_tasks, mtiles, is_long, ids, k1, part_kg, bound, bucket_size, wflag, ctrl);
     tr.mark("k_msd_units");
-    hipLaunchKernelGGL(k_msd_units, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, d_task_offsets, n_tasks, is_long, mtiles, bucket_size, ustage, wflag,
+    FIKIT_COUNT_LAUNCH(k_msd_units, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, d_task_offsets, n_tasks, is_long, mtiles, bucket_size, ustage, wflag,
                        ustart, ulen, utask, udcount, ubuckets, mflag, gflag, lists, static_cast<uint32_t>(n_units), ctrl);
     FusedArgs ua = fa;
     ua.pred_role = nullptr;   // (units are parts of tasks: their task's predictions are left to the gap fill)
@@ -556,11 +591,11 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
                                   static_cast<int>(UNIT_LARGE_LDS)));
     const uint64_t large_most = n / (FUSE_MID_MAX + 1) + n / (static_cast<uint64_t>(UNIT_RUNS_MAX) * PT_TILE) * MSD_SLOTS;
     ua.list = lists + 2 * n_units;
-    hipLaunchKernelGGL(k_unit_large, dim3(static_cast<uint32_t>(large_most < UNIT_LARGE_WORKGROUPS ? large_most : UNIT_LARGE_WORKGROUPS)),
+    FIKIT_COUNT_LAUNCH(k_unit_large, dim3(static_cast<uint32_t>(large_most < UNIT_LARGE_WORKGROUPS ? large_most : UNIT_LARGE_WORKGROUPS)),
                        dim3(SU_THREADS), UNIT_LARGE_LDS, st, ua, lists + 3 * n_units, static_cast<uint32_t>(n_units),
                        reinterpret_cast<uint2*>(e0), g0);
     tr.mark("plan");
-    hipLaunchKernelGGL(k_msd_task_rows, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, n_tasks, is_long, mflag, udcount, urow, dcount);
+    FIKIT_COUNT_LAUNCH(k_msd_task_rows, dim3(n_tasks), dim3(MSD_SLOTS), 0, st, n_tasks, is_long, mflag, udcount, urow, dcount);
     FIKIT_HIP(hipGetLastError());
   }
 
@@ -568,17 +603,17 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   // when the host has waited: the kernels look at the control block and do nothing if there is one.
   auto gather_rows = [&](uint64_t general_done) {
     tr.mark("k_gather_rows");
-    hipLaunchKernelGGL(k_gather_rows, dim3(xcd_grid(n_tasks)), dim3(256), 0, st, d_task_offsets, d_task_row_offsets, gflag, is_long,
+    FIKIT_COUNT_LAUNCH(k_gather_rows, dim3(xcd_grid(n_tasks)), dim3(256), 0, st, d_task_offsets, d_task_row_offsets, gflag, is_long,
                        n_units > 0 ? 1 : 0, fa.staging, n_tasks, d_rows_out, row_capacity, general_done, ctrl);
     if (n_units > 0)
-      hipLaunchKernelGGL(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, d_task_offsets, ulen,
+      FIKIT_COUNT_LAUNCH(k_gather_units, dim3(xcd_grid(static_cast<uint32_t>(n_units))), dim3(256), 0, st, d_task_offsets, ulen,
                          utask, udcount, urow, ustage, mflag, d_task_row_offsets, e1, g1, static_cast<uint32_t>(n_units), d_rows_out, row_capacity,
                          general_done, ctrl);
   };
   const bool any_long = n_units > 0;
   if (!any_long && n_tasks <= ROWS_ONE_TASKS) {
     tr.mark("k_gather_rows");
-    hipLaunchKernelGGL(k_rows_one, dim3(n_tasks), dim3(256), 0, st, d_task_offsets, dcount, fa.staging, n_tasks, d_task_row_offsets, d_rows_out,
+    FIKIT_COUNT_LAUNCH(k_rows_one, dim3(n_tasks), dim3(256), 0, st, d_task_offsets, dcount, fa.staging, n_tasks, d_task_row_offsets, d_rows_out,
                        row_capacity, ctrl);
   } else {
     tr.mark("row_offsets");
@@ -603,7 +638,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   const uint64_t n_general = h.n_general;
   if (n_units > 0) {
     tr.mark("k_long_general_values");
-    hipLaunchKernelGGL(k_long_general_values, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(256), 0, st, d_records, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_long_general_values, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(256), 0, st, d_records, d_task_offsets,
                        n_tasks, mtiles, gflag, wflag, ids, k1, part_kg, e0, g0);
   }
   uint64_t n_heads = 0;
@@ -612,7 +647,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     // General path: per-launch values are in memory (written by whichever kernel gave the task up);
     // sort by ID, find the segment heads.
     tr.mark("plan");
-    hipLaunchKernelGGL(k_plan_tiles, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st,
+    FIKIT_COUNT_LAUNCH(k_plan_tiles, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st,
                        d_task_offsets, n_tasks, gflag, tiles, ctrl);
     if (int rc = scan_u32(tiles, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_big_tiles, st)) return rc;
     tr.mark("host_sync");
@@ -625,7 +660,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_leaf_sort), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   static_cast<int>(sizeof(LeafSmem))));
     tr.mark("k_leaf_sort");
-    hipLaunchKernelGGL(k_leaf_sort, dim3(xcd_grid(n_tasks)), dim3(LEAF_THREADS), sizeof(LeafSmem), st, d_task_offsets, n_tasks, gflag, k1,
+    FIKIT_COUNT_LAUNCH(k_leaf_sort, dim3(xcd_grid(n_tasks)), dim3(LEAF_THREADS), sizeof(LeafSmem), st, d_task_offsets, n_tasks, gflag, k1,
                        k1, e0, g0, ctrl);
     FIKIT_HIP(hipGetLastError());
     // Eight stable passes over the eight key bytes sort any keys.  Kernel IDs are hashes: a task's distinct IDs
@@ -643,16 +678,16 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
       int64_t *ein = e0, *eout = e1, *gin = g0, *gout = g1;
       const uint32_t nt = static_cast<uint32_t>(n_big_tiles);
       tr.mark("k_digit_hist");
-      hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_big_tiles * DIGIT_WORDS_PER_TILE, 1024)), dim3(256), 0, st, digit_counts,
+      FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(blocks_for(n_big_tiles * DIGIT_WORDS_PER_TILE, 1024)), dim3(256), 0, st, digit_counts,
                          n_big_tiles * DIGIT_WORDS_PER_TILE, 0u);
-      hipLaunchKernelGGL(k_digit_hist, dim3(nt), dim3(256), 0, st, d_task_offsets, n_tasks, tiles, kin, first_byte, digit_counts);
-      hipLaunchKernelGGL(k_digit_bases, dim3(n_tasks), dim3(256), 0, st, n_tasks, tiles, digit_counts);
+      FIKIT_COUNT_LAUNCH(k_digit_hist, dim3(nt), dim3(256), 0, st, d_task_offsets, n_tasks, tiles, kin, first_byte, digit_counts);
+      FIKIT_COUNT_LAUNCH(k_digit_bases, dim3(n_tasks), dim3(256), 0, st, n_tasks, tiles, digit_counts);
       for (int pass = 0; pass < SORT_PASSES_PER_ROUND; ++pass) {
         tr.mark("k_onesweep_pass");
-        hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_big_tiles * 512, 1024)), dim3(256), 0, st, reinterpret_cast<uint32_t*>(look),
+        FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(blocks_for(n_big_tiles * 512, 1024)), dim3(256), 0, st, reinterpret_cast<uint32_t*>(look),
                            n_big_tiles * 512, 0u);
-        hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n_tasks, 1024)), dim3(256), 0, st, tickets, static_cast<uint64_t>(n_tasks), 0u);
-        hipLaunchKernelGGL(k_onesweep_pass, dim3(onesweep_grid(nt)), dim3(TILE_THREADS), sizeof(TileSmem), st, d_task_offsets, n_tasks,
+        FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(blocks_for(n_tasks, 1024)), dim3(256), 0, st, tickets, static_cast<uint64_t>(n_tasks), 0u);
+        FIKIT_COUNT_LAUNCH(k_onesweep_pass, dim3(onesweep_grid(nt)), dim3(TILE_THREADS), sizeof(TileSmem), st, d_task_offsets, n_tasks,
                            tiles, digit_counts, pass, 8 * (first_byte + pass), nt, tickets, look, kin, kout, ein, eout, gin, gout, g_wait_limit, ctrl);
         FIKIT_HIP(hipGetLastError());
         uint64_t* tk = kin; kin = kout; kout = tk;
@@ -663,8 +698,8 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     };
     auto find_heads = [&]() -> int {
       tr.mark("heads");
-      hipLaunchKernelGGL(k_head_bits, dim3(blocks_for(n, 256)), dim3(256), 0, st, k1, n, d_task_offsets, n_tasks, gflag, bits, ctrl);
-      hipLaunchKernelGGL(k_popcount_words, dim3(blocks_for(L.n_words, 256)), dim3(256), 0, st, bits, L.n_words, word_prefix);
+      FIKIT_COUNT_LAUNCH(k_head_bits, dim3(blocks_for(n, 256)), dim3(256), 0, st, k1, n, d_task_offsets, n_tasks, gflag, bits, ctrl);
+      FIKIT_COUNT_LAUNCH(k_popcount_words, dim3(blocks_for(L.n_words, 256)), dim3(256), 0, st, bits, L.n_words, word_prefix);
       if (int rc = scan_u32(word_prefix, L.n_words, sums, &ctrl->n_heads, st)) return rc;
       tr.mark("host_sync");
       if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
@@ -674,7 +709,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
       if (int rc = sort_passes(4)) return rc;
     if (int rc = find_heads()) return rc;
     if (h.wide) {
-      hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->wide, static_cast<uint64_t>(1), 0u);
+      FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->wide, static_cast<uint64_t>(1), 0u);
       if (int rc = sort_passes(0)) return rc;   // all eight bytes, least significant first
       if (int rc = sort_passes(4)) return rc;
       if (int rc = find_heads()) return rc;
@@ -682,14 +717,14 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     }
     n_heads = h.n_heads;
     tr.mark("heads");
-    hipLaunchKernelGGL(k_general_row_counts, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, gflag,
+    FIKIT_COUNT_LAUNCH(k_general_row_counts, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, gflag,
                        bits, word_prefix, n, static_cast<uint32_t>(n_heads), dcount);
   }
 
   // Row offsets of every task, and the total.
   tr.mark("row_offsets");
   if (int rc = scan_u32(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, &ctrl->n_rows, st)) return rc;
-  hipLaunchKernelGGL(k_widen_offsets, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, dcount,
+  FIKIT_COUNT_LAUNCH(k_widen_offsets, dim3(blocks_for(static_cast<uint64_t>(n_tasks) + 1, 256)), dim3(256), 0, st, dcount,
                      static_cast<uint64_t>(n_tasks) + 1, d_task_row_offsets);
   tr.mark("host_sync");
   if (int rc = read_ctrl(ctrl, &h, st, false)) return rc;
@@ -700,24 +735,24 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
   gather_rows(n_general);
   if (n_heads > 0) {
     tr.mark("seg_starts");
-    hipLaunchKernelGGL(k_seg_starts, dim3(blocks_for(L.n_words, 256)), dim3(256), 0, st, bits, word_prefix, L.n_words, n, n_heads,
+    FIKIT_COUNT_LAUNCH(k_seg_starts, dim3(blocks_for(L.n_words, 256)), dim3(256), 0, st, bits, word_prefix, L.n_words, n, n_heads,
                        seg_start);
     tr.mark("k_stats_small");
-    hipLaunchKernelGGL(k_stats_small, dim3(blocks_for(n_heads, 4)), dim3(256), 0, st, seg_start, n_heads, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_stats_small, dim3(blocks_for(n_heads, 4)), dim3(256), 0, st, seg_start, n_heads, d_task_offsets,
                        n_tasks, k1, e0, g0, bits, word_prefix, n, dcount, d_rows_out);
     // rows with long segments: by work list (the staging areas e1 / g1 are free once the rows are gathered)
     tr.mark("k_stats_lists");
     uint32_t* rlist = reinterpret_cast<uint32_t*>(e1);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->n_class[0], static_cast<uint64_t>(2), 0u);
-    hipLaunchKernelGGL(k_stats_lists, dim3(blocks_for(n_heads, 256)), dim3(256), 0, st, seg_start, n_heads, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->n_class[0], static_cast<uint64_t>(2), 0u);
+    FIKIT_COUNT_LAUNCH(k_stats_lists, dim3(blocks_for(n_heads, 256)), dim3(256), 0, st, seg_start, n_heads, d_task_offsets,
                        n_tasks, rlist, ctrl);
     tr.mark("k_stats_big");
     const uint32_t big_grid = static_cast<uint32_t>(n_heads < 4096 ? n_heads : 4096);
     const uint32_t huge_grid = static_cast<uint32_t>(n_heads < 512 ? n_heads : 512);
-    hipLaunchKernelGGL(k_stats_big<BIG_THREADS>, dim3(big_grid), dim3(BIG_THREADS), 0, st, seg_start, n_heads, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_stats_big<BIG_THREADS>, dim3(big_grid), dim3(BIG_THREADS), 0, st, seg_start, n_heads, d_task_offsets,
                        n_tasks, k1, e0, g0, bits, word_prefix, n, dcount, d_rows_out, rlist, &ctrl->n_class[0], 0u);
     tr.mark("k_stats_huge");
-    hipLaunchKernelGGL(k_stats_big<HUGE_THREADS>, dim3(huge_grid), dim3(HUGE_THREADS), 0, st, seg_start, n_heads,
+    FIKIT_COUNT_LAUNCH(k_stats_big<HUGE_THREADS>, dim3(huge_grid), dim3(HUGE_THREADS), 0, st, seg_start, n_heads,
                        d_task_offsets, n_tasks, k1, e0, g0, bits, word_prefix, n, dcount, d_rows_out, rlist, &ctrl->n_class[1],
                        1u);
   }
@@ -844,12 +879,12 @@ void gapfill_check_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64
                            const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const uint64_t* d_gap_offsets,
                            uint64_t n_gaps, uint32_t* done) {
   if (gapfill_checks_are_few(n_tasks, n_scenarios)) {
-    hipLaunchKernelGGL(k_gf_begin, dim3(1), dim3(GF_BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n_ids,
+    FIKIT_COUNT_LAUNCH(k_gf_begin, dim3(1), dim3(GF_BEGIN_THREADS), 0, st, d_task_offsets, n_tasks, n_ids,
                        gapfill_begin(b, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, done));
     return;
   }
-  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, done, n_tasks);
-  hipLaunchKernelGGL(k_gf_check, dim3(blocks_for(n_scenarios > n_tasks ? n_scenarios : n_tasks, 256)), dim3(256), 0, st, d_task_offsets,
+  FIKIT_COUNT_LAUNCH(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, b.ctrl, b.role, b.lp_total, done, n_tasks);
+  FIKIT_COUNT_LAUNCH(k_gf_check, dim3(blocks_for(n_scenarios > n_tasks ? n_scenarios : n_tasks, 256)), dim3(256), 0, st, d_task_offsets,
                      n_tasks, n_ids, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, b.role, gapfill_order(b, n_scenarios), b.ctrl);
 }
 
@@ -866,7 +901,7 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
       FIKIT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_gf_walk_lanes<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(sizeof(LaneWalkSmem))));
     const uint32_t vec_ok = (aligned(d_fill_count, 16) && aligned(d_filled_ns, 16)) ? 1u : 0u;
-    hipLaunchKernelGGL(k_gf_walk_lanes<MODE>, dim3(blocks_for(n_scenarios, LW_THREADS)), dim3(LW_THREADS), sizeof(LaneWalkSmem), st,
+    FIKIT_COUNT_LAUNCH(k_gf_walk_lanes<MODE>, dim3(blocks_for(n_scenarios, LW_THREADS)), dim3(LW_THREADS), sizeof(LaneWalkSmem), st,
                        d_task_offsets, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap,
                        d_fill_count, d_filled_ns, result, d_lp_placed, vec_ok, prof, row_capacity, b.ctrl);
   } else {
@@ -878,7 +913,7 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
     auto kernel = &k_gf_walk_wave<MODE, 0>;
     if constexpr (MODE != LW_REPLAY_FEEDBACK)
       kernel = teams ? &k_gf_walk_wave<MODE, GF_TEAM_WAVES> : launches >= GF_REPEAT_LAUNCHES ? &k_gf_walk_wave<MODE, 1> : kernel;
-    hipLaunchKernelGGL(kernel, dim3(teams ? static_cast<uint32_t>(n_scenarios) : blocks_for(n_scenarios, WW_THREADS / WAVE)),
+    FIKIT_COUNT_LAUNCH(kernel, dim3(teams ? static_cast<uint32_t>(n_scenarios) : blocks_for(n_scenarios, WW_THREADS / WAVE)),
                        dim3(teams ? GF_TEAM_WAVES * WAVE : WW_THREADS), 0, st, d_task_offsets, d_hp_task, d_lp_task,
                        static_cast<uint32_t>(n_scenarios), d_gap_offsets, b.lp_e, b.hp_eg, b.lp_total, margin, min_gap, d_fill_count,
                        d_filled_ns, result, d_lp_placed, prof, row_capacity, gapfill_order(b, n_scenarios), b.ctrl);
@@ -898,7 +933,7 @@ int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const u
                     uint64_t row_capacity = 0) {
   if (!all_done) {
     tr.mark("k_gf_predict32");
-    hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                        n_tasks, d_rows, d_task_row_offsets, b.role, static_cast<const int64_t*>(nullptr), b.lp_e, b.hp_eg, b.lp_total,
                        static_cast<uint32_t>(h_params->predictor), done, prof, row_capacity, b.ctrl);
   }
@@ -913,9 +948,9 @@ int gapfill_wide_enqueue(hipStream_t st, const GapfillBuffers& b, const uint64_t
                          const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
                          const uint64_t* d_gap_offsets, uint32_t* d_fill_count, int64_t* d_filled_ns, int64_t* d_lp_completion_ns,
                          uint64_t* d_lp_placed, int32_t* d_status = nullptr) {
-  hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
+  FIKIT_COUNT_LAUNCH(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
                      d_task_row_offsets, b.role, b.pe, b.pg, b.open, static_cast<uint32_t>(h_params->predictor), b.ctrl);
-  hipLaunchKernelGGL(k_gf_walk, dim3(blocks_for(n_scenarios, 256 / WAVE)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
+  FIKIT_COUNT_LAUNCH(k_gf_walk, dim3(blocks_for(n_scenarios, 256 / WAVE)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
                      n_scenarios, d_gap_offsets, b.pe, b.pg, b.open, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,
                      d_lp_completion_ns, d_lp_placed, d_status, b.ctrl);
   FIKIT_HIP(hipGetLastError());
@@ -1146,7 +1181,7 @@ int fikit_gapfill_static(const uint64_t* d_ids, uint64_t n_ids, const uint64_t* 
   Tracer tr(st, false);   // (recording events would allocate)
   const GapfillBuffers b(ws, n_ids, n_tasks);
   if (n_scenarios == 0) {
-    hipLaunchKernelGGL(k_publish_ok, dim3(1), dim3(64), 0, st, d_status);
+    FIKIT_COUNT_LAUNCH(k_publish_ok, dim3(1), dim3(64), 0, st, d_status);
   } else {
     gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, nullptr);
     if (int rc = gapfill_enqueue(st, tr, b, d_ids, n_ids, d_task_offsets, n_tasks, d_rows, d_task_row_offsets, d_hp_task, d_lp_task,
@@ -1155,7 +1190,7 @@ int fikit_gapfill_static(const uint64_t* d_ids, uint64_t n_ids, const uint64_t* 
       return rc;
     // (whether a prediction needs 64 bits is only known on the device, and nothing is waited for here)
     if (n_scenarios <= GF_WIDE_SCENARIOS) {
-      hipLaunchKernelGGL(k_gf_wide, dim3(static_cast<uint32_t>(n_scenarios)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, d_rows,
+      FIKIT_COUNT_LAUNCH(k_gf_wide, dim3(static_cast<uint32_t>(n_scenarios)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, d_rows,
                          d_task_row_offsets, b.role, d_hp_task, d_lp_task, d_gap_offsets, b.pe, b.pg, b.open,
                          static_cast<uint32_t>(h_params->predictor), h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,
                          d_lp_completion_ns, d_lp_placed, d_status, b.ctrl);
@@ -1184,13 +1219,13 @@ int fikit_measure(const fikit_launch* d_records, uint64_t n_records, const uint6
   Ctrl* ctrl = static_cast<Ctrl*>(d_workspace);
   Tracer tr(st);
   tr.mark("k_measure");
-  hipLaunchKernelGGL(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_records,
+  FIKIT_COUNT_LAUNCH(k_clear_ctrl, dim3(1), dim3(64), 0, st, ctrl);
+  FIKIT_COUNT_LAUNCH(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_records,
                      ctrl);
   if (n_records > 0) {
-    hipLaunchKernelGGL(k_measure, dim3(blocks_for(n_records, 256)), dim3(256), 0, st, d_records, n_records, d_exec_ns, d_gap_ns,
+    FIKIT_COUNT_LAUNCH(k_measure, dim3(blocks_for(n_records, 256)), dim3(256), 0, st, d_records, n_records, d_exec_ns, d_gap_ns,
                        ctrl);
-    hipLaunchKernelGGL(k_measure_task_ends, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_gap_ns,
+    FIKIT_COUNT_LAUNCH(k_measure_task_ends, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_gap_ns,
                        ctrl);
   }
   FIKIT_HIP(hipGetLastError());
@@ -1239,7 +1274,7 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
   tr.mark("gf_setup");
   gapfill_check_enqueue(st, b, d_task_offsets, n_ids, n_tasks, d_hp_task, d_lp_task, n_scenarios, d_gap_offsets, n_gaps, nullptr);
   tr.mark("k_gf_predict32");
-  hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
+  FIKIT_COUNT_LAUNCH(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                      n_tasks, d_rows, d_task_row_offsets, b.role, d_actual_gap_ns, b.lp_e, b.hp_eg, b.lp_total,
                      static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr),
                      static_cast<const Ctrl*>(nullptr), static_cast<uint64_t>(0), b.ctrl);
@@ -1248,10 +1283,10 @@ int fikit_gapfill_replay(const uint64_t* d_ids, const uint64_t* d_task_offsets, 
                     h_params->min_gap_ns, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, true, nullptr, 0))
     return rc;
   return finish_gapfill(st, tr, b.ctrl, [&]() -> int {
-    hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
+    FIKIT_COUNT_LAUNCH(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
                        d_task_row_offsets, b.role, b.pe, b.pg, static_cast<int64_t*>(nullptr),
                        static_cast<uint32_t>(h_params->predictor), b.ctrl);
-    hipLaunchKernelGGL(k_gf_replay_wide, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
+    FIKIT_COUNT_LAUNCH(k_gf_replay_wide, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, d_hp_task, d_lp_task,
                        n_scenarios, d_gap_offsets, b.pe, b.pg, d_actual_gap_ns, h_params->margin_ns, h_params->min_gap_ns,
                        h_params->feedback ? 1u : 0u, d_fill_count, d_filled_ns, d_hp_delay_ns, d_lp_placed, b.ctrl);
     FIKIT_HIP(hipGetLastError());
@@ -1348,10 +1383,10 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
 
   Tracer tr(st);
   tr.mark("pf_setup");
-  hipLaunchKernelGGL(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, ctrl, role, lp_total,
+  FIKIT_COUNT_LAUNCH(k_gf_clear, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, ctrl, role, lp_total,
                      static_cast<uint32_t*>(nullptr), n_tasks);
-  hipLaunchKernelGGL(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
-  hipLaunchKernelGGL(k_pf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
+  FIKIT_COUNT_LAUNCH(k_validate_offsets, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, n_ids, ctrl);
+  FIKIT_COUNT_LAUNCH(k_pf_scenarios, dim3(blocks_for(n_scenarios, 256)), dim3(256), 0, st, d_task_offsets, n_tasks, d_hp_task,
                      d_lp_offsets, d_lp_task, d_lp_prio, n_scenarios, n_entries, d_gap_offsets, role, order, ctrl);
   FIKIT_HIP(hipGetLastError());
   tr.mark("host_sync");
@@ -1364,7 +1399,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   const bool groups = widest <= PF_MAX_LP;
   if (groups) {
     tr.mark("k_gf_predict32");
-    hipLaunchKernelGGL(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
+    FIKIT_COUNT_LAUNCH(k_gf_predict32, dim3(n_tasks, predict_parts(n_ids, n_tasks)), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets,
                        n_tasks, d_rows, d_task_row_offsets, role, static_cast<const int64_t*>(nullptr), lp_e, hp_eg, lp_total,
                        static_cast<uint32_t>(h_params->predictor), static_cast<const uint32_t*>(nullptr),
                        static_cast<const Ctrl*>(nullptr), static_cast<uint64_t>(0), ctrl);
@@ -1375,7 +1410,7 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
                            lp_e, hp_eg, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns, d_lp_placed, \
                            d_lp_placed_ns, vec_ok, ctrl)
 #define FIKIT_PF_WAVE(K)                                                                                                      \
-  hipLaunchKernelGGL(k_pf_walk_wave<K>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st,            \
+  FIKIT_COUNT_LAUNCH(k_pf_walk_wave<K>, dim3(blocks_for(n_scenarios, WW_THREADS / WAVE)), dim3(WW_THREADS), 0, st,            \
                      d_task_offsets, d_hp_task, d_lp_offsets, d_lp_task, d_lp_prio, static_cast<uint32_t>(n_scenarios),       \
                      d_gap_offsets, lp_e, hp_eg, h_params->margin_ns, h_params->min_gap_ns, d_fill_count, d_filled_ns,        \
                      d_lp_placed, d_lp_placed_ns, order, ctrl)
@@ -1399,13 +1434,13 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   }
   if (!groups) {
     // the 64-bit kernels, as if a prediction had not fitted
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->wide, static_cast<uint64_t>(1), 1u);
+    FIKIT_COUNT_LAUNCH(k_fill_u32, dim3(1), dim3(64), 0, st, &ctrl->wide, static_cast<uint64_t>(1), 1u);
   }
   return finish_gapfill(st, tr, ctrl, [&]() -> int {
-    hipLaunchKernelGGL(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
+    FIKIT_COUNT_LAUNCH(k_gf_predict, dim3(n_tasks), dim3(PRED_THREADS), 0, st, d_ids, d_task_offsets, n_tasks, d_rows,
                        d_task_row_offsets, role, pe, pg, static_cast<int64_t*>(nullptr), static_cast<uint32_t>(h_params->predictor),
                        ctrl);
-    hipLaunchKernelGGL(k_pf_walk_wide, dim3(blocks_for(n_scenarios, 64)), dim3(64), 0, st, d_task_offsets, d_hp_task, d_lp_offsets,
+    FIKIT_COUNT_LAUNCH(k_pf_walk_wide, dim3(blocks_for(n_scenarios, 64)), dim3(64), 0, st, d_task_offsets, d_hp_task, d_lp_offsets,
                        d_lp_task, d_lp_prio, n_scenarios, d_gap_offsets, pe, pg, h_params->margin_ns, h_params->min_gap_ns,
                        d_fill_count, d_filled_ns, d_lp_placed, d_lp_placed_ns, ctrl);
     FIKIT_HIP(hipGetLastError());
@@ -1452,7 +1487,7 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
 
   Tracer tr(st);
   tr.mark("pair_setup");
-  hipLaunchKernelGGL(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks,
+  FIKIT_COUNT_LAUNCH(k_pair_init, dim3(blocks_for(n_tasks, 256)), dim3(256), 0, st, n_tasks,
                      n_scenarios > 0 ? d_gap_offsets + n_scenarios : static_cast<const uint64_t*>(nullptr), top_filled, best_scenario,
                      d_best_lp, d_best_filled_ns, ctrl);
   if (n_scenarios > 0) {
@@ -1460,14 +1495,14 @@ int fikit_pairing_best(const uint32_t* d_hp_task, const uint32_t* d_lp_task, uin
     const bool waves = n_scenarios >= PAIR_WAVES;
     const uint64_t most = waves ? PAIR_STAY : n_scenarios;
     const uint64_t groups = waves ? (n_scenarios + PAIR_THREADS / WAVE - 1) / (PAIR_THREADS / WAVE) : n_scenarios;
-    hipLaunchKernelGGL(waves ? k_pair_sum<WAVE> : k_pair_sum<PAIR_THREADS>, dim3(static_cast<uint32_t>(groups < most ? groups : most)),
+    FIKIT_COUNT_LAUNCH(waves ? k_pair_sum<WAVE> : k_pair_sum<PAIR_THREADS>, dim3(static_cast<uint32_t>(groups < most ? groups : most)),
                        dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task, static_cast<uint32_t>(n_scenarios), n_tasks, d_gap_offsets,
                        d_filled_ns, d_scenario_filled_ns, top_filled, ctrl);
     tr.mark("k_pair_pick");
-    hipLaunchKernelGGL(k_pair_pick, dim3(blocks_for(n_scenarios, PAIR_THREADS)), dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task, n_scenarios,
+    FIKIT_COUNT_LAUNCH(k_pair_pick, dim3(blocks_for(n_scenarios, PAIR_THREADS)), dim3(PAIR_THREADS), 0, st, d_hp_task, d_lp_task, n_scenarios,
                        n_tasks, d_scenario_filled_ns, d_lp_completion_ns, top_filled, best_scenario, d_best_lp, d_best_filled_ns, ctrl);
     if (n_tasks > PAIR_LAST_TASKS)
-      hipLaunchKernelGGL(k_pair_finish, dim3(blocks_for(n_tasks, PAIR_THREADS)), dim3(PAIR_THREADS), 0, st, n_tasks, d_lp_task,
+      FIKIT_COUNT_LAUNCH(k_pair_finish, dim3(blocks_for(n_tasks, PAIR_THREADS)), dim3(PAIR_THREADS), 0, st, n_tasks, d_lp_task,
                          d_scenario_filled_ns, best_scenario, d_best_lp, d_best_filled_ns, ctrl);
   }
   FIKIT_HIP(hipGetLastError());
@@ -1522,12 +1557,12 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   // tables; or that one takes all (k_merge_begin).  (The list lives where nothing else does at that time: in the row offsets before they exist, in the row counts after.)
   const uint32_t large_grid = n_tasks < MERGE_LARGE_WORKGROUPS ? n_tasks : MERGE_LARGE_WORKGROUPS;
   auto pass = [&](auto small, auto large, uint32_t* list) {
-    hipLaunchKernelGGL(small, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,
+    FIKIT_COUNT_LAUNCH(small, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,
                        n_tasks, dcount, d_task_row_offsets_out, d_rows_out, row_capacity, list, ctrl);
-    hipLaunchKernelGGL(large, dim3(large_grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,
+    FIKIT_COUNT_LAUNCH(large, dim3(large_grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,
                        n_tasks, dcount, d_task_row_offsets_out, d_rows_out, row_capacity, list, ctrl);
   };
-  hipLaunchKernelGGL(k_merge_begin, dim3(1), dim3(64), 0, st, d_task_row_offsets_a + n_tasks, d_task_row_offsets_b + n_tasks, n_tasks, MAX_ELEMS, ctrl);
+  FIKIT_COUNT_LAUNCH(k_merge_begin, dim3(1), dim3(64), 0, st, d_task_row_offsets_a + n_tasks, d_task_row_offsets_b + n_tasks, n_tasks, MAX_ELEMS, ctrl);
   pass(k_merge<0, MERGE_IDS_SMALL, false>, k_merge<0, MERGE_IDS, true>, reinterpret_cast<uint32_t*>(d_task_row_offsets_out));
   if (int rc = row_offsets_enqueue(dcount, static_cast<uint64_t>(n_tasks) + 1, sums, d_task_row_offsets_out, ctrl, st)) return rc;
   tr.mark("k_merge_rows");   // (does nothing if a check failed or the rows are too many)
