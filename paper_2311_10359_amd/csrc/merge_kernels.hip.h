@@ -13,7 +13,7 @@ constexpr int MERGE_THREADS = 256;
 // of 20,000 tasks of 90 + 90 rows: 269 us with three, 182 us with seven; 146 us, 4.7 TB/s, since a lane moves 16 bytes and rows
 // that go nowhere are not read).  Tables beyond the larger number are searched in memory.
 constexpr uint32_t MERGE_IDS = 3072, MERGE_IDS_SMALL = 1024;
-constexpr uint32_t MERGE_LARGE_WORKGROUPS = 12 * 256;   // of the larger tables, four for each that the chip holds; they take the tasks in turn
+constexpr uint32_t MERGE_LARGE_WORKGROUPS = 3 * 256;   // of the larger tables: as many as the chip holds
 
 template <uint32_t IDS>
 struct MergeSmem {
@@ -96,6 +96,11 @@ __global__ void k_merge_begin(const uint64_t* __restrict__ n_a, const uint64_t* 
 // it that are in both (a running count of the matched rows seen so far).
 // LARGE: with larger tables, either the tasks of list[0 .. ctrl->n_class[MODE]) or all (Ctrl::wide).  Otherwise all tasks or none; those
 // with more than IDS rows in a table are put on the list instead.
+// The large kernel's workgroups stay and count the tasks they take in ctrl->n_class[2 + MODE]: in fixed turns, tasks that are long at
+// the pace of the turns meet in few workgroups, and ragged ones leave some workgroups behind (us per call, four workgroups for
+// each that the chip holds in fixed turns / as many as it holds, counted: 20,000 tasks of 100 and 1800 rows in turn 4374 / 2882, 6144 of 200 rows, of which
+// 200 in a row have 12,000 at two places, 3590 / 2370, 20,000 lognormal ones of 830 rows on average 5300 / 4660, 20,000 of 700
+// 2055 / 1975, 4000 of 700 467 / 457, 3072 of 700 371 / 376).
 template <int MODE, uint32_t IDS, bool LARGE>
 __global__ void __launch_bounds__(MERGE_THREADS, IDS == MERGE_IDS_SMALL ? 7 : 3)
 k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, const fikit_row* __restrict__ b,
@@ -110,7 +115,14 @@ k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, con
   const uint64_t n_a = a_off[n_tasks], n_b = b_off[n_tasks];
   const uint32_t tid = threadIdx.x;
   const uint32_t items = LARGE && !all ? ctrl->n_class[MODE] : n_tasks;
-  for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+  auto following = [&](uint32_t item) -> uint32_t {   // (called by all threads once a task is done)
+    if constexpr (!LARGE) return item + gridDim.x;
+    __syncthreads();   // (all have read the word that is written now, and the task's searches are over)
+    if (tid == 0) sm.aux[0] = atomicAdd(&ctrl->n_class[2 + MODE], 1u);
+    __syncthreads();
+    return gridDim.x + sm.aux[0];
+  };
+  for (uint32_t item = blockIdx.x; item < items; item = following(item)) {
     // (the rows are written from the last task to the first: what the counting pass read last is still in the cache)
     const uint32_t t = LARGE && !all ? list[item] : MODE == 1 ? items - 1 - item : item;
     const uint64_t a0 = a_off[t], a1 = a_off[t + 1], b0 = b_off[t], b1 = b_off[t + 1];
