@@ -34,7 +34,51 @@ __global__ void k_pair_init(uint32_t n_tasks, const uint64_t* __restrict__ n_gap
 // gaps are no more than the lanes, each reads one of them: eight guarded reads are then most of the instructions (200,000 scenarios of 3 gaps,
 // call 273 us with them, 227 us without; of 30 gaps 253 and 225 us, both with a workgroup each).  The atomic returns nothing, so
 // nothing waits for it; looking at the word first does wait, at a word that all scenarios of a task share (158 us).
+//
+// A scenario of many more gaps than the others (PAIR_LONG times the average and more than PAIR_LONG_LEAST) is left to the end by
+// its wave, and the workgroup's waves sum it up together: a wave alone decided the call.  us per call, a workgroup per
+// scenario / waves alone / now: 8192 scenarios of 1000 gaps, one of 100,000 65 / 78 / 60, one of 1,000,000 202 / 364 / 191, eight of
+// 1,000,000 212 / 388 / 207; 8192 of 100, 64 of 200,000 84 / 112 / 79; 20,000 of 500, one of 4,000,000 668 / 1356 / 645; 8192 of 20,000
+// 282 / 268 / 262.
 constexpr uint64_t PAIR_WAVES = 8192, PAIR_STAY = 2048;   // (PAIR_STAY workgroups of four waves fill the chip)
+constexpr uint64_t PAIR_LONG = 8, PAIR_LONG_LEAST = 8192;
+constexpr uint32_t PAIR_LONGS = 256;   // of a workgroup; what is beyond stays with its wave
+template <int G>
+__device__ __forceinline__ uint64_t pair_lane_sum(const uint64_t* __restrict__ f, uint64_t g0, uint64_t g1, uint32_t at) {
+  constexpr int READS = 8;
+  uint64_t acc[2] = {0, 0};      // (sums wrap like the oracle's additions)
+  if (g1 - g0 <= G) {   // few gaps: one read per lane, and few instructions
+    if (at < g1 - g0) acc[0] = f[g0 + at];
+  } else {
+    // pairs from the first gap on that lies on a 16-byte address; the gap before them and the one behind by one lane
+    const uint64_t p0 = (reinterpret_cast<uintptr_t>(f + g0) & 15) ? g0 + 1 : g0;
+    const uint32_t pairs = static_cast<uint32_t>((g1 - p0) / 2);
+    const ulonglong2* v = reinterpret_cast<const ulonglong2*>(f + p0);
+    uint32_t i = at;
+    for (; i + (READS - 1) * G < pairs; i += READS * G) {
+      ulonglong2 x[READS];
+#pragma unroll
+      for (int k = 0; k < READS; ++k) x[k] = v[i + k * G];
+#pragma unroll
+      for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
+    }
+    {
+      ulonglong2 x[READS];
+#pragma unroll
+      for (int k = 0; k < READS; ++k) {
+        x[k] = make_ulonglong2(0, 0);
+        if (i + k * G < pairs) x[k] = v[i + k * G];
+      }
+#pragma unroll
+      for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
+    }
+    if (at == 0) {
+      if (p0 > g0) acc[0] += f[g0];
+      if (p0 + 2 * static_cast<uint64_t>(pairs) < g1) acc[1] += f[g1 - 1];
+    }
+  }
+  return acc[0] + acc[1];
+}
 template <int G>
 __global__ void __launch_bounds__(PAIR_THREADS)
 k_pair_sum(const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp_task, uint32_t n_scen, uint32_t n_tasks,
@@ -42,69 +86,73 @@ k_pair_sum(const uint32_t* __restrict__ hp_task, const uint32_t* __restrict__ lp
            long long* __restrict__ top_filled, Ctrl* ctrl) {
   static_assert(G == WAVE || G == PAIR_THREADS, "a wave or a workgroup");
   __shared__ uint64_t part[PAIR_THREADS / WAVE];
+  __shared__ uint32_t n_longs, longs[G == WAVE ? PAIR_LONGS : 1];
   const uint32_t at = threadIdx.x % G, groups = gridDim.x * (PAIR_THREADS / G);
   uint32_t s = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (PAIR_THREADS / G) + threadIdx.x / G)));
   const uint64_t n_gaps = gap_off[n_scen];
-  if (n_gaps >= PAIR_MOST_GAPS || s >= n_scen) return;   // (k_pair_init has seen the number too)
-  uint32_t hp = hp_task[s], lp = lp_task[s];
-  uint64_t g0 = gap_off[s], g1 = gap_off[s + 1];
-  constexpr int READS = 8;
+  if (n_gaps >= PAIR_MOST_GAPS) return;   // (k_pair_init has seen the number too)
   const uint64_t* f = reinterpret_cast<const uint64_t*>(filled_ns);
-  for (;;) {
-    const uint32_t s_next = n_scen - s > groups ? s + groups : s;   // (the last one is looked up again)
-    const uint32_t hp_next = hp_task[s_next], lp_next = lp_task[s_next];
-    const uint64_t g0_next = gap_off[s_next], g1_next = gap_off[s_next + 1];
-    if (hp >= n_tasks || lp >= n_tasks) {   // (these are the same in all of the group's lanes)
-      if (at == 0) atomicOr(&ctrl->status, ERR_TASK_INDEX);
-    } else if (g1 < g0 || g1 > n_gaps || (s == 0 && g0 != 0)) {
-      if (at == 0) atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
-    } else {
-      uint64_t acc[2] = {0, 0};      // (sums wrap like the oracle's additions)
-      if (g1 - g0 <= G) {   // few gaps: one read per lane, and few instructions
-        if (at < g1 - g0) acc[0] = f[g0 + at];
+  // the workgroup's sum over its threads' (the words are free again behind the caller's next barrier)
+  auto all_of = [&](uint64_t mine) {
+    uint64_t total = wave_sum_u64(mine);
+    if (lane_id() == 0) part[threadIdx.x / WAVE] = total;
+    __syncthreads();
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < PAIR_THREADS / WAVE; ++w) total += part[w];
+    return total;
+  };
+  if (G == WAVE) {
+    if (threadIdx.x == 0) n_longs = 0;
+    __syncthreads();
+  }
+  if (s < n_scen) {   // (the same in the whole group)
+    const uint64_t average = n_gaps / n_scen, long_above = average * PAIR_LONG > PAIR_LONG_LEAST ? average * PAIR_LONG : PAIR_LONG_LEAST;
+    uint32_t hp = hp_task[s], lp = lp_task[s];
+    uint64_t g0 = gap_off[s], g1 = gap_off[s + 1];
+    // scenarios of one task that follow each other share an exchange (100,000 of 64 tasks in turn: sums 240 us with a workgroup
+    // each, 325 by waves that exchange every one, 37 so)
+    long long top = INT64_MIN;   // (what a task starts with)
+    for (;;) {
+      const uint32_t s_next = n_scen - s > groups ? s + groups : s;   // (the last one is looked up again)
+      const uint32_t hp_next = hp_task[s_next], lp_next = lp_task[s_next];
+      const uint64_t g0_next = gap_off[s_next], g1_next = gap_off[s_next + 1];
+      if (hp >= n_tasks || lp >= n_tasks) {   // (these are the same in all of the group's lanes)
+        if (at == 0) atomicOr(&ctrl->status, ERR_TASK_INDEX);
+      } else if (g1 < g0 || g1 > n_gaps || (s == 0 && g0 != 0)) {
+        if (at == 0) atomicOr(&ctrl->status, ERR_GAP_OFFSETS);
       } else {
-        // pairs from the first gap on that lies on a 16-byte address; the gap before them and the one behind by one lane
-        const uint64_t p0 = (reinterpret_cast<uintptr_t>(f + g0) & 15) ? g0 + 1 : g0;
-        const uint32_t pairs = static_cast<uint32_t>((g1 - p0) / 2);
-        const ulonglong2* v = reinterpret_cast<const ulonglong2*>(f + p0);
-        uint32_t i = at;
-        for (; i + (READS - 1) * G < pairs; i += READS * G) {
-          ulonglong2 x[READS];
-#pragma unroll
-          for (int k = 0; k < READS; ++k) x[k] = v[i + k * G];
-#pragma unroll
-          for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
+        uint32_t place = PAIR_LONGS;
+        if (G == WAVE && g1 - g0 > long_above) {
+          if (at == 0) place = atomicAdd(&n_longs, 1u);
+          place = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(place)));
         }
-        {
-          ulonglong2 x[READS];
-#pragma unroll
-          for (int k = 0; k < READS; ++k) {
-            x[k] = make_ulonglong2(0, 0);
-            if (i + k * G < pairs) x[k] = v[i + k * G];
-          }
-#pragma unroll
-          for (int k = 0; k < READS; ++k) { acc[0] += x[k].x; acc[1] += x[k].y; }
+        if (place < PAIR_LONGS) {
+          if (at == 0) longs[place] = s;
+        } else {
+          const uint64_t mine = pair_lane_sum<G>(f, g0, g1, at), total = G == WAVE ? wave_sum_u64(mine) : all_of(mine);
+          if (at == 0) scen_filled[s] = static_cast<int64_t>(total);
+          top = static_cast<long long>(total) > top ? static_cast<long long>(total) : top;
         }
-        if (at == 0) {
-          if (p0 > g0) acc[0] += f[g0];
-          if (p0 + 2 * static_cast<uint64_t>(pairs) < g1) acc[1] += f[g1 - 1];
+        if (hp_next != hp || s_next == s) {
+          if (at == 0 && top != INT64_MIN) atomicMax(&top_filled[hp], top);
+          top = INT64_MIN;
         }
       }
-      uint64_t total = wave_sum_u64(acc[0] + acc[1]);
-      if constexpr (G != WAVE) {   // (one scenario per workgroup: the words are written once)
-        if (lane_id() == 0) part[threadIdx.x / WAVE] = total;
-        __syncthreads();
-        total = 0;
-#pragma unroll
-        for (int w = 0; w < PAIR_THREADS / WAVE; ++w) total += part[w];
-      }
-      if (at == 0) {
-        scen_filled[s] = static_cast<int64_t>(total);
-        atomicMax(&top_filled[hp], static_cast<long long>(total));
-      }
+      if (G != WAVE || s_next == s) break;   // (one scenario per workgroup)
+      s = s_next; hp = hp_next; lp = lp_next; g0 = g0_next; g1 = g1_next;
     }
-    if (G != WAVE || s_next == s) return;
-    s = s_next; hp = hp_next; lp = lp_next; g0 = g0_next; g1 = g1_next;
+  }
+  if (G != WAVE) return;
+  __syncthreads();
+  for (uint32_t i = 0; i < min_u32(n_longs, PAIR_LONGS); ++i) {
+    const uint32_t scenario = longs[i];
+    const uint64_t total = all_of(pair_lane_sum<PAIR_THREADS>(f, gap_off[scenario], gap_off[scenario + 1], threadIdx.x));
+    if (threadIdx.x == 0) {
+      scen_filled[scenario] = static_cast<int64_t>(total);
+      atomicMax(&top_filled[hp_task[scenario]], static_cast<long long>(total));
+    }
+    __syncthreads();
   }
 }
 
