@@ -34,6 +34,20 @@ def test_few_scenarios_of_many_gaps(n_scen, base, longs, length):
     check_pairing(*with_gaps(rng, gaps, 300))
 
 
+@pytest.mark.parametrize("n_scen", [9, 255, 257, 5000, 8192, 30000])
+@pytest.mark.parametrize("tasks", [[0], list(range(64)), [511], list(range(600)), [5 + 512 * k for k in range(12)]])   # (the last: one place in a table for all)
+@pytest.mark.parametrize("order", ["falling", "rising", "mixed", "equal", "extreme"])
+def test_scenarios_that_tie(n_scen, tasks, order):
+    rng = np.random.default_rng(n_scen)
+    comp = {"falling": np.arange(n_scen)[::-1], "rising": np.arange(n_scen), "mixed": rng.permutation(n_scen), "equal": np.zeros(n_scen),
+            "extreme": np.where(np.arange(n_scen) < n_scen - 2, 2**63 - 1, -2**63)}[order].astype(np.int64)
+    gaps = rng.integers(0, 3, n_scen)
+    off = np.concatenate([[0], np.cumsum(gaps)]).astype(np.uint64)
+    filled = np.zeros(int(off[-1]), dtype=np.int64)
+    hp = np.asarray(tasks, dtype=np.uint32)[np.arange(n_scen) % len(tasks) if order == "mixed" else rng.integers(0, len(tasks), n_scen)]
+    check_pairing(hp, rng.integers(0, 600, n_scen).astype(np.uint32), max(600, max(tasks) + 1), off, filled, comp)
+
+
 def took_us(calls):
     took = [[] for _ in calls]
     for _ in range(25):
@@ -61,3 +75,10 @@ def test_one_long_scenario_costs_the_same_among_more_others():
     below, at = took_us([call_of(gaps[:-1], np.arange(WAVES - 1), 1000), call_of(gaps, np.arange(WAVES), 1000)])
     print(f"{below:.0f} us by workgroups, {at:.0f} us by waves", flush=True)
     assert at < 1.3 * below
+
+
+def test_order_of_tied_scenarios_does_not_matter():
+    gaps = np.full(2 * WAVES, 3)
+    falling, equal = took_us([call_of(gaps, np.arange(gaps.size)[::-1], 1), call_of(gaps, np.zeros(gaps.size), 1)])
+    print(f"falling completions {falling:.0f} us, equal ones {equal:.0f} us", flush=True)
+    assert falling < 1.4 * equal
