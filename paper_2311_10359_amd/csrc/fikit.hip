@@ -7,6 +7,7 @@
 #include <chrono>
 #include <cstring>
 #include <mutex>
+#include <thread>
 
 #include "common.hip.h"
 #include "gapfill_kernels.hip.h"
@@ -250,6 +251,10 @@ thread_local Mailbox t_mailbox;
 //   step of 256 scenarios of 65,536 launches                                 358 / 341 / 342          361 / 374 / 350
 //   priority queues, 4096 scenarios of three                                1060 / 1038 / 1041       1059 / 1067 / 1041
 // (asked at once in every call: fikit_measure 38 to 44, the small merge 51 to 55, the step of a pair 47 to 51 one behind the other.)
+//
+// The host gives way to other threads while it looks, which may have calls of their own to enqueue (us per step of a pair of 1000
+// launches, all threads together, runtime's wait / looking without giving way / so: 8 threads on 2 processors 48 / 51 to 54 / 48, 4 on 1
+// processor 66 / 54 / 32, 1 thread 64 / 51 / 51).
 struct Reads {
   static constexpr int MOST = 4;
   static constexpr int64_t LOOK_NS = 1000000;   // (the runtime's wait adds 4 us, which a call of this length no longer feels)
@@ -303,8 +308,9 @@ struct Reads {
     auto arrived = [&] { return __atomic_load_n(seen, __ATOMIC_ACQUIRE) == number; };
     const auto from = std::chrono::steady_clock::now();
     for (uint32_t looks = 1; !arrived(); ++looks) {
-      __builtin_ia32_pause();
+      __builtin_ia32_pause();   // (x86, as the hosts of these GPUs are)
       if (looks % 64 != 0) continue;
+      std::this_thread::yield();
       const auto looked = std::chrono::steady_clock::now() - from;
       if (ask && looked > std::chrono::nanoseconds(ASK_NS)) {
         ask = false;
