@@ -109,7 +109,8 @@ def test_merge_of_small_tables_beside_large_ones(most_small, large):
     check_merge(np.concatenate(a), offs[0], np.concatenate(b), offs[1])
 
 
-@pytest.mark.parametrize("n_tasks", [8190, 8191, 8192, 16383, 16384, 20000])   # row counts around whole tiles of the scan
+# row counts around whole tiles of the scan; more than one round of the counts before a tile; around the last count that one launch takes
+@pytest.mark.parametrize("n_tasks", [8190, 8191, 8192, 16383, 16384, 20000, 41003, 131072, 262142, 262143, 262144, 300001])
 def test_row_offsets_of_many_tasks(n_tasks):
     rng = np.random.default_rng(n_tasks)
     sizes = rng.integers(0, 4, n_tasks)
