@@ -235,13 +235,14 @@ thread_local Mailbox t_mailbox;
 // against 6.5 us).  Stores of the kernels before have left the caches of their dies when this kernel starts, as for any kernel
 // that follows in the stream, so outputs are final for every stream, copy and thread.
 //
-// The runtime does not know then that the stream is empty, and a synchronisation of the caller's right behind the call pays for that.  It
-// goes by the commands since its own last wait: up to RUNTIME_WAITS, the one of the wait among them, it waits itself, beyond them it
-// leaves it to its handler thread, which takes 20 us longer.  (A synchronisation behind N empty kernels and a report that has been seen: 9 us up to N = 6, 24 us
-// from 7 on; with an event recorded behind the report 5.6 us up to N = 5.)  So behind the last report of a call of few launches an event is
-// recorded, which nobody waits for; in a longer one the runtime is asked whether the stream is empty, which sets the handler to work,
-// but only once the host has looked for ASK_NS: asking takes 14 us, which then pass while the call does.
-// Calls in us, with copies and the runtime's wait / reports alone / now:    one behind the other     each with a device synchronisation
+// The runtime does not know then that the stream is empty, and a synchronisation of the caller's right behind the call pays for
+// that.  It goes by the commands since its own last wait: up to RUNTIME_WAITS, the one of the wait among them, it waits itself,
+// beyond them it leaves it to its handler thread, which takes 20 us longer.  (A synchronisation behind N empty kernels and a
+// report that has been seen: 9 us up to N = 6, 24 us from 7 on; with an event recorded behind the report 5.6 us up to N = 5.)  So
+// behind the last report of a call of few launches an event is recorded, which nobody waits for; in a longer one the runtime is
+// asked whether the stream is empty, which sets the handler to work, but only once the host has looked for ASK_NS: asking takes
+// 14 us, which then pass while the call does.
+// Calls in us, with copies and the runtime's wait / reports alone / now:    one behind the other     each with a synchronisation
 //   fikit_measure, 1000 launches                                              28 / 27 / 26             31 / 35 / 29
 //   pairing of 16 scenarios                                                   33 / 27 / 27             36 / 36 / 30
 //   step of a pair of 1000 launches                                           57 / 48 / 48             60 / 59 / 50
@@ -250,11 +251,12 @@ thread_local Mailbox t_mailbox;
 //   merge of 20,000 tasks of 90 rows                                         287 / 235 / 234          290 / 246 / 237
 //   step of 256 scenarios of 65,536 launches                                 358 / 341 / 342          361 / 374 / 350
 //   priority queues, 4096 scenarios of three                                1060 / 1038 / 1041       1059 / 1067 / 1041
-// (asked at once in every call: fikit_measure 38 to 44, the small merge 51 to 55, the step of a pair 47 to 51 one behind the other.)
+// (asked at once in every call: fikit_measure 38 to 44, the small merge 51 to 55, the step of a pair 47 to 51 one behind the
+// other.)
 //
 // The host gives way to other threads while it looks, which may have calls of their own to enqueue (us per step of a pair of 1000
-// launches, all threads together, runtime's wait / looking without giving way / so: 8 threads on 2 processors 48 / 51 to 54 / 48, 4 on 1
-// processor 66 / 54 / 32, 1 thread 64 / 51 / 51).
+// launches, all threads together, runtime's wait / looking without giving way / so: 8 threads on 2 processors 48 / 51 to 54 / 48,
+// 4 on 1 processor 66 / 54 / 32, 1 thread 64 / 51 / 51).
 struct Reads {
   static constexpr int MOST = 4;
   static constexpr int64_t LOOK_NS = 1000000;   // (the runtime's wait adds 4 us, which a call of this length no longer feels)
@@ -417,8 +419,8 @@ struct PredEmit {
   uint32_t predictor;
 };
 
-// fikit_profile; with `emit` the kernels that hold a whole task in one workgroup also write the task's predictions.  `begin` (may be
-// null): the first checks of a gap fill that follows, which share a launch with the profile's if both are few.  ahead(tracer,
+// fikit_profile; with `emit` the kernels that hold a whole task in one workgroup also write the task's predictions.  `begin` (may
+// be null): the first checks of a gap fill that follows, which share a launch with the profile's if both are few.  ahead(tracer,
 // reads, ctrl, any long tasks) enqueues what follows once the rows are final, and what it wants read back, before the host knows
 // whether they are: *was_ahead says that they were (see may_follow).
 template <typename Ahead>
@@ -796,17 +798,18 @@ constexpr uint64_t GF_PAD = 256;
 constexpr uint64_t GF_LANES_MIN_SCENARIOS = 32768;
 // Up to this many scenarios of traces of so many launches on average, a workgroup takes each: one of its waves walks, all copy what
 // repeats.  Three workgroups of eight waves are on a compute unit at a time, so the 769th waits until a scenario is through (traces
-// and queues of 16,384 launches that never repeat, in us by a wave / by a workgroup each: 768 scenarios 441 / 455, 784 429 / 563, 1024
-// 447 / 700).  Shorter traces are copied fast enough by one wave, and the walk by the first of several is 2 to 4 % slower (queues four times
-// as long as the traces, repeating, 16 scenarios: 4096 launches 195 / 185, 8192 190 / 154, 16,384 265 / 176, 32,768 381 / 201; 256
-// scenarios: 222 / 223, 249 / 231, 310 / 263, 439 / 273; never repeating: 334 / 341, 618 / 634, 1195 / 1228, 2320 / 2387).  Of 256 scenarios of
-// 65,535 gaps, four waves take 382 us, eight 355, sixteen 341, but of workgroups of sixteen waves only 256 would be there at a time.
+// and queues of 16,384 launches that never repeat, in us by a wave / by a workgroup each: 768 scenarios 441 / 455, 784 429 / 563,
+// 1024 447 / 700).  Shorter traces are copied fast enough by one wave, and the walk by the first of several is 2 to 4 % slower
+// (queues four times as long as the traces, repeating, 16 scenarios: 4096 launches 195 / 185, 8192 190 / 154, 16,384 265 / 176,
+// 32,768 381 / 201; 256 scenarios: 222 / 223, 249 / 231, 310 / 263, 439 / 273; never repeating: 334 / 341, 618 / 634, 1195 /
+// 1228, 2320 / 2387).  Of 256 scenarios of 65,535 gaps, four waves take 382 us, eight 355, sixteen 341, but of workgroups of
+// sixteen waves only 256 would be there at a time.
 constexpr uint64_t GF_TEAM_SCENARIOS = 768, GF_TEAM_LAUNCHES = 8192;
 constexpr int GF_TEAM_WAVES = 8;
-// From this average on some traces are long enough for the search (if lengths are spread up to twice the average).  The walk with it
-// has 67 registers instead of 54, which many scenarios feel.  Without / with it in us: 12,000 scenarios of 1000 gaps 312 / 318, 30,000
-// 252 / 256, 12,000 ragged ones of 700 on average 369 / 373; 64 of 1500 gaps 73 / 73; 6000 ragged ones of 1400 on average 390 / 356 (if they
-// repeat) and 377 / 380 (if not), 12,000 of 2100 563 / 449 and 559 / 563.
+// From this average on some traces are long enough for the search (if lengths are spread up to twice the average).  The walk with
+// it has 67 registers instead of 54, which many scenarios feel.  Without / with it in us: 12,000 scenarios of 1000 gaps 312 /
+// 318, 30,000 252 / 256, 12,000 ragged ones of 700 on average 369 / 373; 64 of 1500 gaps 73 / 73; 6000 ragged ones of 1400 on
+// average 390 / 356 (if they repeat) and 377 / 380 (if not), 12,000 of 2100 563 / 449 and 559 / 563.
 constexpr uint64_t GF_REPEAT_LAUNCHES = REPEAT_GAPS / 2;
 
 }  // extern "C"
@@ -928,9 +931,9 @@ int walk_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint
   return FIKIT_OK;
 }
 
-// Enqueues the predictions and the fill on `st` (gapfill_check_enqueue has been).  done (may be null): tasks whose predictions exist
-// already; all_done: those of all tasks do (a launch that would find nothing to do costs 5 us of a call of 74, and 20 us with 32,768
-// tasks).  Nothing is read back and nothing is allocated here.
+// Enqueues the predictions and the fill on `st` (gapfill_check_enqueue has been).  done (may be null): tasks whose predictions
+// exist already; all_done: those of all tasks do (a launch that would find nothing to do costs 5 us of a call of 74, and 20 us
+// with 32,768 tasks).  Nothing is read back and nothing is allocated here.
 int gapfill_enqueue(hipStream_t st, Tracer& tr, const GapfillBuffers& b, const uint64_t* d_ids, uint64_t n_ids,
                     const uint64_t* d_task_offsets, uint32_t n_tasks, const fikit_row* d_rows, const uint64_t* d_task_row_offsets,
                     const uint32_t* d_hp_task, const uint32_t* d_lp_task, uint64_t n_scenarios, const fikit_gapfill_params* h_params,
@@ -1381,8 +1384,8 @@ int fikit_prio_fill(const uint64_t* d_ids, const uint64_t* d_task_offsets, uint3
   uint2* hp_eg = reinterpret_cast<uint2*>(pg);
   // (behind the 32-bit execution times, in the half of their space that the 64-bit ones would take; an even number of launches in)
   const uint64_t listed_at = (n_ids + 1) / 2 * 8;
-  // The waves' order is made where waves will walk.  The widest scenario, which decides that, is not known yet: the average one stands
-  // in for it (30,000 scenarios of one task: 557 us with lists that nobody reads, 555 without).
+  // The waves' order is made where waves will walk.  The widest scenario, which decides that, is not known yet: the average one
+  // stands in for it (30,000 scenarios of one task: 557 us with lists that nobody reads, 555 without).
   const GfOrder order = prio_by_wave((n_entries + n_scenarios - 1) / n_scenarios, n_scenarios)
                             ? scenario_order(ctrl, reinterpret_cast<unsigned char*>(pe) + listed_at + GF_PAD, n_ids * 8 - listed_at, n_scenarios)
                             : GfOrder{nullptr, nullptr};
@@ -1540,7 +1543,8 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   if (workspace_bytes < fikit_profile_merge_workspace_bytes(n_tasks)) return FIKIT_WORKSPACE_TOO_SMALL;
 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  // The numbers of rows live on the device, whose first kernel looks at them; the host only waits for them where a table may be missing.
+  // The numbers of rows live on the device, whose first kernel looks at them; the host only waits for them where a table may be
+  // missing.
   if (!d_rows_a || !d_rows_b) {
     uint64_t na = 0, nb = 0;
     Reads counts(st);
@@ -1559,8 +1563,9 @@ int fikit_profile_merge(const fikit_row* d_rows_a, const uint64_t* d_task_row_of
   Tracer tr(st);
   tr.mark("merge_count");
   const uint32_t grid = n_tasks < 65536u ? n_tasks : 65536u;
-  // The kernel with the small LDS tables takes every task, and puts those that do not fit them on a list for the one with the larger
-  // tables; or that one takes all (k_merge_begin).  (The list lives where nothing else does at that time: in the row offsets before they exist, in the row counts after.)
+  // The kernel with the small LDS tables takes every task, and puts those that do not fit them on a list for the one with the
+  // larger tables; or that one takes all (k_merge_begin).  (The list lives where nothing else does at that time: in the row
+  // offsets before they exist, in the row counts after.)
   const uint32_t large_grid = n_tasks < MERGE_LARGE_WORKGROUPS ? n_tasks : MERGE_LARGE_WORKGROUPS;
   auto pass = [&](auto small, auto large, uint32_t* list) {
     FIKIT_COUNT_LAUNCH(small, dim3(grid), dim3(MERGE_THREADS), 0, st, d_rows_a, d_task_row_offsets_a, d_rows_b, d_task_row_offsets_b,

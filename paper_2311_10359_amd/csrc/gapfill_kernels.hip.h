@@ -14,14 +14,14 @@
 namespace fikit {
 
 // Scenarios in the order in which the walks' waves take them, the longest traces first: buckets of half an octave of the
-// high-priority trace's length (bucket 0 the longest), in no order inside.  With several waves per SIMD, what a SIMD has to do is the
-// sum of the traces it happens to get, and the longest may start last: 6000 traces of 1 to 2800 launches needed 93 cycles of a SIMD
-// per gap, even ones 53.  The kernel that checks the scenarios fills the lists, which costs it 1 to 4 us; scenarios of one bucket are
-// taken as they are numbered.  Calls in us as numbered / longest first: gap fill of these 6000 431 / 397, of 20,000 of up to 1200
-// launches 437 / 392, of 2100 of up to 1000 151 / 150; replay of 3000 traces of up to 4000 launches 491 / 463; priority queues, 4096
-// traces of up to 1600 launches and three queues each 1249 / 1088; even lengths, 2100 scenarios 117 / 119, 6000 350 / 351, 30,000 407 /
-// 411.  The longest buckets' waves at a higher priority on their SIMD: 397, 392, 150, 464 and 1079 us for the ragged ones; not worth
-// standing before other streams' waves.
+// high-priority trace's length (bucket 0 the longest), in no order inside.  With several waves per SIMD, what a SIMD has to do is
+// the sum of the traces it happens to get, and the longest may start last: 6000 traces of 1 to 2800 launches needed 93 cycles of
+// a SIMD per gap, even ones 53.  The kernel that checks the scenarios fills the lists, which costs it 1 to 4 us; scenarios of one
+// bucket are taken as they are numbered.  Calls in us as numbered / longest first: gap fill of these 6000 431 / 397, of 20,000 of
+// up to 1200 launches 437 / 392, of 2100 of up to 1000 151 / 150; replay of 3000 traces of up to 4000 launches 491 / 463;
+// priority queues, 4096 traces of up to 1600 launches and three queues each 1249 / 1088; even lengths, 2100 scenarios 117 / 119,
+// 6000 350 / 351, 30,000 407 / 411.  The longest buckets' waves at a higher priority on their SIMD: 397, 392, 150, 464 and 1079
+// us for the ragged ones; not worth standing before other streams' waves.
 struct GfOrder {
   uint32_t* count;    // [GF_BUCKETS] scenarios of each bucket, in the words behind the control block (which k_gf_clear clears too);
                       // null: as they are numbered
@@ -105,9 +105,10 @@ __global__ void k_gf_check(const uint64_t* __restrict__ off, uint32_t n_tasks, u
 }
 
 // Both of the above in one workgroup, for so few tasks and scenarios that a second launch costs more (4.5 us) than the
-// chip's other units save.  What it does takes no time; what it waits for does: everything is asked for at once (GfFirst, BeginOffsets),
-// and the roles are gathered in LDS.  (The offsets read where they are needed and the roles in memory, behind a
-// fence / now: 64 scenarios of 16 tasks, call 74.2 / 69.3 us; the first launch of a step of one scenario 11.4 / 7.0 us between events.)
+// chip's other units save.  What it does takes no time; what it waits for does: everything is asked for at once (GfFirst,
+// BeginOffsets), and the roles are gathered in LDS.  (The offsets read where they are needed and the roles in memory, behind a
+// fence / now: 64 scenarios of 16 tasks, call 74.2 / 69.3 us; the first launch of a step of one scenario 11.4 / 7.0 us between
+// events.)
 constexpr uint32_t GF_BEGIN_ITEMS = 2048;
 constexpr int GF_BEGIN_THREADS = 1024;
 struct GfBegin {
@@ -460,12 +461,13 @@ k_gf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
   gf_walk_scenario(s, off, hp_task, lp_task, gap_off, pe, pg, open, margin, min_gap, fill_count, filled_ns, completion_out, placed_out);
 }
 
-// Both in one launch, for a call of few scenarios that enqueues them before it knows whether they are needed (fikit_gapfill_static): the
-// workgroup of a scenario looks its two tasks up (what several scenarios share is written by all of their workgroups, each the same values)
-// and one of its waves walks.  Also where the call's status is published, which nothing before or in this launch changes by then: an ID
-// without a row has been found by k_gf_predict32.  A launch that finds nothing to do costs 2.2 us of the chip's time and 3 of the
-// host's: static calls in us, two launches / one: 64 scenarios of 1500 gaps 69.8 / 68.4, a few of 100 gaps 22 / 19.4; with predictions beyond
-// 32 bits one scenario 260 / 233, 64 of 16 tasks 322 / 280, 256 of 32 tasks 329 / 282, 900 of 60 tasks 345 / 439, which decides the line.
+// Both in one launch, for a call of few scenarios that enqueues them before it knows whether they are needed
+// (fikit_gapfill_static): the workgroup of a scenario looks its two tasks up (what several scenarios share is written by all of
+// their workgroups, each the same values) and one of its waves walks.  Also where the call's status is published, which nothing
+// before or in this launch changes by then: an ID without a row has been found by k_gf_predict32.  A launch that finds nothing to
+// do costs 2.2 us of the chip's time and 3 of the host's: static calls in us, two launches / one: 64 scenarios of 1500 gaps 69.8
+// / 68.4, a few of 100 gaps 22 / 19.4; with predictions beyond 32 bits one scenario 260 / 233, 64 of 16 tasks 322 / 280, 256 of
+// 32 tasks 329 / 282, 256 that share a queue of 400,000 launches 1939 / 1991, 900 of 60 tasks 345 / 439, which decides the line.
 constexpr uint64_t GF_WIDE_SCENARIOS = 256;
 __global__ void __launch_bounds__(PRED_THREADS)
 k_gf_wide(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ off, const fikit_row* __restrict__ rows,
@@ -529,9 +531,9 @@ __device__ __forceinline__ uint32_t clamp32(int64_t v) {   // (predictions are n
 // 500: 599 -> 216 us.
 // For the replay against actual idle times (actual != nullptr) the first word of hp_eg[i] holds the idle
 // time that really followed launch i instead (clamped to WIDE32, which no filled time can reach).
-// Bound by the memory that reads and writes by turns, once a lane has PRED_READS pairs of IDs on their way and both halves of an odd task's
-// pairs come in one read: 6000 ragged scenarios 146 us with one read per pair where the task starts at an even place and two where not,
-// 133 so; 6000 of 2048 and 8192 launches 195 / 186 = 5.5 TB/s (four pairs 139 and 184 us, one 152 and 211).
+// Bound by the memory that reads and writes by turns, once a lane has PRED_READS pairs of IDs on their way and both halves of an
+// odd task's pairs come in one read: 6000 ragged scenarios 146 us with one read per pair where the task starts at an even place
+// and two where not, 133 so; 6000 of 2048 and 8192 launches 195 / 186 = 5.5 TB/s (four pairs 139 and 184 us, one 152 and 211).
 // pred_done (may be null): tasks whose predictions exist already and are left alone.  prof (may be null, as in the walks): the
 // profile in the same call that this was enqueued behind.
 __global__ void __launch_bounds__(PRED_THREADS)
@@ -588,8 +590,8 @@ k_gf_predict32(const uint64_t* __restrict__ ids, const uint64_t* __restrict__ of
     return make_uint2(clamp32(e), clamp32(g));
   };
   uint64_t total = 0;
-  // Pairs of launches start at even elements, so that they are read as 16 bytes and written as 8 and 16; an odd first launch goes by itself.
-  // (IDs that lie on 8 bytes only are read one by one.)
+  // Pairs of launches start at even elements, so that they are read as 16 bytes and written as 8 and 16; an odd first launch goes
+  // by itself. (IDs that lie on 8 bytes only are read one by one.)
   const bool ids_vec = (reinterpret_cast<uintptr_t>(ids) & 15) == 0;
   const uint32_t lead = static_cast<uint32_t>(base & 1);
   const uint64_t step = static_cast<uint64_t>(gridDim.y) * (2 * PRED_THREADS);
@@ -725,10 +727,11 @@ enum : int { LW_PLAN = 0, LW_REPLAY = 1, LW_REPLAY_FEEDBACK = 2 };
 // cycles per gap, the windows' ends included), with many the issue of
 // scalar instructions (the gap's fourteen scalar instructions go through one port per SIMD).  A gap that takes the window's
 // rest and ends inside the next window has a way of its own: with kernels of a fifth of a gap that is every twelfth gap, and the
-// general loop goes through twice its instructions for it (ms with the loop / now: 64 scenarios of 1500 gaps 0.076 / 0.063, 16,384 of
-// 4095 gaps 1.43 / 1.18, 6000 ragged ones of up to 2800 0.25 / 0.22, replay of 6000 of 2047 gaps with feedback 0.44 / 0.376).
-// The 64-bit kernel above, which passes 64-bit sums through the LDS crossbar, takes 0.23 ms for the first of these, one lane each
-// 3.2 ms for the second.  The loop written in assembly with a quarter fewer instructions per gap is no faster (call 97 / 99 us).
+// general loop goes through twice its instructions for it (ms with the loop / now: 64 scenarios of 1500 gaps 0.076 / 0.063,
+// 16,384 of 4095 gaps 1.43 / 1.18, 6000 ragged ones of up to 2800 0.25 / 0.22, replay of 6000 of 2047 gaps with feedback 0.44 /
+// 0.376). The 64-bit kernel above, which passes 64-bit sums through the LDS crossbar, takes 0.23 ms for the first of these, one
+// lane each 3.2 ms for the second.  The loop written in assembly with a quarter fewer instructions per gap is no faster (call 97
+// / 99 us).
 constexpr int WW_THREADS = 256;
 constexpr uint32_t WW_WIN = WAVE - 1;
 constexpr int WW_BLOCKS = 4;   // blocks of 64 gaps per round (their reads are one round ahead)
@@ -749,20 +752,20 @@ __device__ __forceinline__ uint32_t write_lane_u32(uint32_t v, uint32_t value, u
 }
 __device__ __forceinline__ uint32_t sat32(uint64_t v) { return v > WIDE32 ? WIDE32 : static_cast<uint32_t>(v); }
 
-// Before the loop over the gaps that take something: it is 116 to 148 bytes long and runs as one wave's chain, so that it matters where
-// the instructions lie in the 32 bytes that are fetched at a time.  Between byte 8 and 16 of such a piece is the best place in all of
-// its forms; where the compiler happens to put it costs up to 7 %.  Gap fills in us, 256 scenarios of 65,535 gaps that never repeat, for
-// starts at byte 0, 4, 8, 12, 16, 20, 24: by a wave 1532, 1564, 1473, 1489, 1466, 1487, 1558; by eight 1560, 1579, 1502, 1491, 1500, 1524, 1584.
-// The instructions that fill the piece are run once per block of 64 gaps, so there should be few (where nearly every gap takes
-// something, 256 long scenarios by eight waves: 358 us with three, 361 with four).
+// Before the loop over the gaps that take something: it is 116 to 148 bytes long and runs as one wave's chain, so that it matters
+// where the instructions lie in the 32 bytes that are fetched at a time.  Between byte 8 and 16 of such a piece is the best place
+// in all of its forms; where the compiler happens to put it costs up to 7 %.  Gap fills in us, 256 scenarios of 65,535 gaps that
+// never repeat, for starts at byte 0, 4, 8, 12, 16, 20, 24: by a wave 1532, 1564, 1473, 1489, 1466, 1487, 1558; by eight 1560,
+// 1579, 1502, 1491, 1500, 1524, 1584. The instructions that fill the piece are run once per block of 64 gaps, so there should be
+// few (where nearly every gap takes something, 256 long scenarios by eight waves: 358 us with three, 361 with four).
 template <int TEAM>
 __device__ __forceinline__ void place_loop() {
   if constexpr (TEAM > 1) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
   else asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0");
 }
 
-// The wave's scenario: its own number, or what order holds at that place.  (Everything that is the same in the whole wave is kept in
-// scalar registers: the scenario number has to be seen as one.)
+// The wave's scenario: its own number, or what order holds at that place.  (Everything that is the same in the whole wave is kept
+// in scalar registers: the scenario number has to be seen as one.)
 __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint32_t n_scen) {
   const uint32_t place = static_cast<uint32_t>(
       __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * (WW_THREADS / WAVE) + threadIdx.x / WAVE)));
@@ -786,13 +789,14 @@ __device__ __forceinline__ uint32_t scenario_of_wave(const GfOrder& order, uint3
 // such a place at multiples of the trace's period; from it on the inputs are compared, all of them, and the results copied.  No
 // step of this waits for the one before, so it runs at the rate of the memory instead of at the length of a chain.
 //
-// Traces of passes reach such a place after two to five periods as a rule: whatever the queue's first entry was, it soon stands at one
-// that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps 705 / 347 (the
-// slowest wave walks 21,000 gaps), 16,384 of 4095 7565 / 7130 (the walk 1170 / 775: 1100 gaps walked, 2600 copied, and the queue's
-// 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 379.  Kernels drawn at random never repeat and pay for the search: about
-// 0.3 us a round while it lasts (24 rounds as a rule), then one comparison a round (the same calls 635 / 656, 7755 / 7775, 386 / 387).
-// The rounds without the search as a second copy of the code: 82 to 86 registers instead of 67 to 71, and both copies' loops are compiled
-// worse (256 traces of 65,535 gaps that never repeat 1518 -> 1648 us, the step of 16,384 7760 -> 7960).
+// Traces of passes reach such a place after two to five periods as a rule: whatever the queue's first entry was, it soon stands
+// at one that only few of a pass's gaps can take.  Calls in us, walked to the end / with the copy: 256 scenarios of 65,535 gaps
+// 705 / 347 (the slowest wave walks 21,000 gaps), 16,384 of 4095 7565 / 7130 (the walk 1170 / 775: 1100 gaps walked, 2600 copied,
+// and the queue's 13,000 entries compared), 6000 ragged ones of up to 2800 396 / 379.  Kernels drawn at random never repeat and
+// pay for the search: about 0.3 us a round while it lasts (24 rounds as a rule), then one comparison a round (the same calls 635
+// / 656, 7755 / 7775, 386 / 387). The rounds without the search as a second copy of the code: 82 to 86 registers instead of 67 to
+// 71, and both copies' loops are compiled worse (256 traces of 65,535 gaps that never repeat 1518 -> 1648 us, the step of 16,384
+// 7760 -> 7960).
 struct Repeat {
   uint32_t a, ja;         // the place
   uint32_t D, dq;         // gaps and entries of a unit (the unit before the place is the one that is copied)
@@ -901,8 +905,8 @@ struct RepeatTeam {   // (in LDS)
   Repeat rep;         // what the walking wave has found; no units: the others leave
   RepeatSums sum;
 };
-// All waves of a scenario: what repeats is compared and copied.  Returns the number of entries issued and the first places that differ;
-// `used` and `line` are the lane's own, and the other waves' sums are added to lane 0 of the first.
+// All waves of a scenario: what repeats is compared and copied.  Returns the number of entries issued and the first places that
+// differ; `used` and `line` are the lane's own, and the other waves' sums are added to lane 0 of the first.
 template <int MODE, int TEAM>
 __device__ __forceinline__ RepeatSums repeat_copy(const Repeat& rep, uint32_t wave, uint32_t H, const uint2* __restrict__ trace,
                                                   const uint32_t* __restrict__ queue, uint32_t* fill_count, int64_t* filled_ns,
@@ -953,28 +957,29 @@ __device__ __forceinline__ void repeat_helper(uint32_t wave, uint32_t H, const u
   }
 }
 
-// Where it is worth the search.  The search costs a wave 1 to 2 us until there is a period and 0.4 us a note; 64 traces of 1500 gaps
-// (a call of 73 us) gain nothing by it, 6000 of up to 2800 gaps 396 -> 379 us.  A queue of a few passes is soon used up, or hardly moves.
+// Where it is worth the search.  The search costs a wave 1 to 2 us until there is a period and 0.4 us a note; 64 traces of 1500
+// gaps (a call of 73 us) gain nothing by it, 6000 of up to 2800 gaps 396 -> 379 us.  A queue of a few passes is soon used up, or
+// hardly moves.
 constexpr uint32_t REPEAT_GAPS = 2048, REPEAT_ENTRIES = 1024;
-// A wave by itself copies a gap in 9 to 16 cycles and walks one that takes nothing in 5, one that takes something in 100 and more: a unit
-// is copied if at least every eighth of its gaps takes something (three traces of 12,192 gaps whose queue hardly moves, all copied
-// 181 us, walked 157).  Eight waves copy one in 2 cycles, and copy whatever repeats.
+// A wave by itself copies a gap in 9 to 16 cycles and walks one that takes nothing in 5, one that takes something in 100 and
+// more: a unit is copied if at least every eighth of its gaps takes something (three traces of 12,192 gaps whose queue hardly
+// moves, all copied 181 us, walked 157).  Eight waves copy one in 2 cycles, and copy whatever repeats.
 constexpr uint32_t REPEAT_WORTH = 8;
 constexpr uint32_t REPEAT_LEAST = 128;     // a shorter period counts as a multiple of it, so that a round has few places to look at
 constexpr uint32_t REPEAT_NOTES = 48;      // places noted; the period is doubled at every 16th (at every eighth: 256 long traces 345 -> 367 us)
-// Starts of a period (counted once) and repeats (twice) that may turn out to be none; one that held for REPEAT_ANCHOR gaps has paid for
-// the search, and the count starts again.
+// Starts of a period (counted once) and repeats (twice) that may turn out to be none; one that held for REPEAT_ANCHOR gaps has
+// paid for the search, and the count starts again.
 constexpr uint32_t REPEAT_MISSES = 4;
-// Gaps from a start without a period after which another start is looked for, and how often; then the search ends.  What comes before
-// the first pass may be 2048 launches long, and a pass 4096.
+// Gaps from a start without a period after which another start is looked for, and how often; then the search ends.  What comes
+// before the first pass may be 2048 launches long, and a pass 4096.
 constexpr uint32_t REPEAT_ANCHOR = 2048, REPEAT_ANCHORS = 2;
 
-// The search, by the wave that walks.  Two idle times in a row that equal those at the anchor may be the start of the next pass, and are
-// if 64 are equal.  From then on the wave notes, once a period, where the queue stands and what it holds there (a lane per note:
-// the gap, the entry, a sum over the next 64 entries).
+// The search, by the wave that walks.  Two idle times in a row that equal those at the anchor may be the start of the next pass,
+// and are if 64 are equal.  From then on the wave notes, once a period, where the queue stands and what it holds there (a lane
+// per note: the gap, the entry, a sum over the next 64 entries).
 struct RepeatSearch {
-  // Rounds that start before this gap are looked at; 0: the search is over.  (One comparison per round is what a trace pays that never
-  // repeats, or that is too short.)
+  // Rounds that start before this gap are looked at; 0: the search is over.  (One comparison per round is what a trace pays that
+  // never repeats, or that is too short.)
   uint32_t until;
   uint32_t misses = 0;
   uint32_t period = 0, next_place = 0, notes = 0, note_i = 0, note_j = 0, note_sum = 0;
@@ -991,7 +996,8 @@ struct RepeatSearch {
     until = misses >= REPEAT_MISSES ? 0u : until;
   }
 
-  // The round's idle times (G) are at hand, its gaps not walked yet: what has to be compared is read now and looked at behind the round.
+  // The round's idle times (G) are at hand, its gaps not walked yet: what has to be compared is read now and looked at behind the
+  // round.
   template <typename Entry>
   __device__ __forceinline__ Start look(uint32_t i0, uint32_t queue_at, uint32_t H, const uint2* __restrict__ trace,
                                         const uint32_t (&G)[WW_BLOCKS], Entry entry) {
@@ -1027,8 +1033,8 @@ struct RepeatSearch {
     return start;
   }
 
-  // Behind the round that started at gap `first`: count: entries that its gaps took, queue_at: where the queue stands.  Returns what can
-  // be compared and copied (units == 0: nothing).
+  // Behind the round that started at gap `first`: count: entries that its gaps took, queue_at: where the queue stands.  Returns
+  // what can be compared and copied (units == 0: nothing).
   template <int TEAM, typename Entry>
   __device__ __forceinline__ Repeat note(const Start& start, uint32_t first, uint32_t queue_at, uint32_t H, uint32_t L, uint32_t n_gaps,
                                          const uint32_t (&count)[WW_BLOCKS], Entry entry) {

@@ -56,8 +56,9 @@ __device__ __forceinline__ uint64_t merge_field(uint32_t f, uint64_t x, uint64_t
 
 // Writes the planned rows of a round (sm.place / sm.partner, `rows` of them, taken from src[first ..]): eight
 // lanes per row, two 8-byte fields each, so that a wave reads and writes whole rows side by side.  Rows that go nowhere
-// (they went out with their partner) are not read.  Neither is needed again, and the caches keep what the next tasks' searches read: 20,000
-// tasks of 90 + 90 rows, call 262 us with ordinary reads and writes, 242 with the hint on the writes, 231 with it on both.
+// (they went out with their partner) are not read.  Neither is needed again, and the caches keep what the next tasks' searches
+// read: 20,000 tasks of 90 + 90 rows, call 262 us with ordinary reads and writes, 242 with the hint on the writes, 231 with it on
+// both.
 template <uint32_t IDS>
 __device__ __forceinline__ void merge_write_round(const MergeSmem<IDS>& sm, const fikit_row* __restrict__ src, uint32_t first,
                                                   uint32_t rows, const fikit_row* __restrict__ other, fikit_row* __restrict__ out) {
@@ -75,12 +76,12 @@ __device__ __forceinline__ void merge_write_round(const MergeSmem<IDS>& sm, cons
   }
 }
 
-// The control block, and what the host would have to wait for before anything runs (20,000 tasks of 90 + 90 rows, call 271 us with that
-// wait, 262 us without): whether there are more rows than can be merged (`most` or more of both together), and which tables
-// take the tasks (Ctrl::wide).  With MERGE_IDS_SMALL rows in both tables of a task together on average, most fit the small ones, and the
-// few that do not are listed; beyond it the list would hold too many, and the larger tables take all tasks (us with the list / without: 1000
-// tasks of 2000 + 2000 rows 484 / 460, 3000 of 1100 + 1100 664 / 594; 3000 of 700 + 700 368 / 376, 7945 of 349 + 349 427 / 449, the last
-// two and the ones without the list with the host's wait, 8 us).
+// The control block, and what the host would have to wait for before anything runs (20,000 tasks of 90 + 90 rows, call 271 us
+// with that wait, 262 us without): whether there are more rows than can be merged (`most` or more of both together), and which
+// tables take the tasks (Ctrl::wide).  With MERGE_IDS_SMALL rows in both tables of a task together on average, most fit the small
+// ones, and the few that do not are listed; beyond it the list would hold too many, and the larger tables take all tasks (us with
+// the list / without: 1000 tasks of 2000 + 2000 rows 484 / 460, 3000 of 1100 + 1100 664 / 594; 3000 of 700 + 700 368 / 376, 7945
+// of 349 + 349 427 / 449, the last two and the ones without the list with the host's wait, 8 us).
 __global__ void k_merge_begin(const uint64_t* __restrict__ n_a, const uint64_t* __restrict__ n_b, uint32_t n_tasks, uint64_t most, Ctrl* ctrl) {
   const uint64_t a = *n_a, b = *n_b;
   const uint32_t i = threadIdx.x;
@@ -94,13 +95,13 @@ __global__ void k_merge_begin(const uint64_t* __restrict__ n_a, const uint64_t* 
 // union into dcount[t].  MODE 1: writes the union's rows at row_off[t].. in ID order.
 // One workgroup per task; rank of an ID in the union = IDs below it in a + IDs below it in b - IDs below
 // it that are in both (a running count of the matched rows seen so far).
-// LARGE: with larger tables, either the tasks of list[0 .. ctrl->n_class[MODE]) or all (Ctrl::wide).  Otherwise all tasks or none; those
-// with more than IDS rows in a table are put on the list instead.
-// The large kernel's workgroups stay and count the tasks they take in ctrl->n_class[2 + MODE]: in fixed turns, tasks that are long at
-// the pace of the turns meet in few workgroups, and ragged ones leave some workgroups behind (us per call, four workgroups for
-// each that the chip holds in fixed turns / as many as it holds, counted: 20,000 tasks of 100 and 1800 rows in turn 4374 / 2882, 6144 of 200 rows, of which
-// 200 in a row have 12,000 at two places, 3590 / 2370, 20,000 lognormal ones of 830 rows on average 5300 / 4660, 20,000 of 700
-// 2055 / 1975, 4000 of 700 467 / 457, 3072 of 700 371 / 376).
+// LARGE: with larger tables, either the tasks of list[0 .. ctrl->n_class[MODE]) or all (Ctrl::wide).  Otherwise all tasks or
+// none; those with more than IDS rows in a table are put on the list instead.
+// The large kernel's workgroups stay and count the tasks they take in ctrl->n_class[2 + MODE]: in fixed turns, tasks that are
+// long at the pace of the turns meet in few workgroups, and ragged ones leave some workgroups behind (us per call, four
+// workgroups for each that the chip holds in fixed turns / as many as it holds, counted: 20,000 tasks of 100 and 1800 rows in
+// turn 4374 / 2882, 6144 of 200 rows, of which 200 in a row have 12,000 at two places, 3590 / 2370, 20,000 lognormal ones of 830
+// rows on average 5300 / 4660, 20,000 of 700 2055 / 1975, 4000 of 700 467 / 457, 3072 of 700 371 / 376).
 template <int MODE, uint32_t IDS, bool LARGE>
 __global__ void __launch_bounds__(MERGE_THREADS, IDS == MERGE_IDS_SMALL ? 7 : 3)
 k_merge(const fikit_row* __restrict__ a, const uint64_t* __restrict__ a_off, const fikit_row* __restrict__ b,

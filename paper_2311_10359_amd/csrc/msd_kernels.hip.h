@@ -40,8 +40,10 @@ constexpr int PT_LB = 2;                             // rounds of record loads i
 //   64 tasks of 24,000 launches: 0.53 / 0.31 (90 %), 0.53 / 0.28 (70 %)   64 of 40,000: 0.65 / 0.38, 0.76 / 0.28 (50 %)
 //   64 of 65,536: 0.82 / 0.43, 0.94 / 0.33, 0.91 / 0.31   256 of 131,072: 3.90 / 1.15, 4.53 / 1.07, 4.47 / 1.03
 //   256 of 262,143: 8.29 / 2.16, 7.91 / 2.00, 7.76 / 1.97
-// Streaming is ahead in all of these.  The line was drawn when it still lost at 24,000 and 40,000 launches, above those; in shorter
-// tasks it may also be tried in vain, as a unit of the other IDs holds more of them than its table.
+// Streaming is ahead in all of these, and the tasks below the line are sorted all the same: it was drawn when streaming still
+// lost at 24,000 and 40,000 launches, and has not been moved since.  A task may also be tried in vain, as a unit of the other IDs
+// holds more of them than its table; that costs little (sorted / tried and sorted, one ID with half of the launches beside 20,000
+// others: 64 tasks of 40,000 1.23 / 1.28, 64 of 65,536 1.55 / 1.59, 256 of 131,072 8.24 / 8.45, 256 of 262,143 12.6 / 13.0).
 constexpr uint64_t STREAM_MIN = 1u << 18;
 // Tasks of up to this many launches are cut into units of at most FUSE_SMALL_MAX launches, longer ones (whose buckets alone may
 // be longer) of FUSE_MID_MAX.  fikit_profile, uniform over 300 IDs, in ms with the smaller / the larger units:
@@ -85,15 +87,14 @@ struct PartSmem {
   uint32_t aux[8];
 };
 
-// One tile (PT_TILE launches of one long task) per workgroup, its launches dealt to the waves in turns of 64, so that a round of the
-// workgroup's reads is one piece of memory.  What bounds it is the memory that reads and writes by turns: 256 tasks of 1,048,576
-// launches, 23.6 GB, 4.62 ms with a stretch of 512 launches per wave and ordinary stores, 4.45 ms with either the turns or stores that are
-// not kept in the caches, 4.27 ms = 5.5 TB/s with both (the units then gather 4 % slower, 2.04 against 1.95 ms; only the IDs
-// stored so: no change; the reads hinted the same way: no change).  The boundary table of a task is stored bucket-major,
-// tile-minor (bound[(first tile of the task) * PT_ROWS + bucket * tiles + tile]) so that a unit reads the two
-// boundaries it needs of all tiles as two contiguous vectors.  Execution and idle times travel as 32-bit numbers
-// (idle time NONE32 = the task's last launch has none); a task with a value that does not fit is flagged and left
-// to the general path.
+// One tile (PT_TILE launches of one long task) per workgroup, its launches dealt to the waves in turns of 64, so that a round of
+// the workgroup's reads is one piece of memory.  What bounds it is the memory that reads and writes by turns: 256 tasks of
+// 1,048,576 launches, 23.6 GB, 4.62 ms with a stretch of 512 launches per wave and ordinary stores, 4.45 ms with either the turns
+// or stores that are not kept in the caches, 4.27 ms = 5.5 TB/s with both (the units then gather 4 % slower, 2.04 against 1.95
+// ms; only the IDs stored so: no change; the reads hinted the same way: no change).  The boundary table of a task is stored
+// bucket-major, tile-minor (bound[(first tile of the task) * PT_ROWS + bucket * tiles + tile]) so that a unit reads the two
+// boundaries it needs of all tiles as two contiguous vectors.  Execution and idle times travel as 32-bit numbers (idle time
+// NONE32 = the task's last launch has none); a task with a value that does not fit is flagged and left to the general path.
 __global__ void __launch_bounds__(PT_THREADS)
 k_tile_partition(const fikit_launch* __restrict__ rec, const uint64_t* __restrict__ off, uint32_t n_tasks,
                  const uint32_t* __restrict__ tile_prefix, const uint32_t* __restrict__ long_prefix,

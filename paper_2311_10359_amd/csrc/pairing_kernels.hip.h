@@ -9,8 +9,8 @@ namespace fikit {
 constexpr int PAIR_THREADS = 256;
 constexpr uint64_t PAIR_MOST_GAPS = (1ull << 32) - (1ull << 24);   // a call with as many or more is refused
 
-// The control block and start values per task (no memset: the stream may be under graph capture): the values of a task that heads no
-// scenario.  The number of gaps is looked at here and not by the host, which would have to wait for it.
+// The control block and start values per task (no memset: the stream may be under graph capture): the values of a task that heads
+// no scenario.  The number of gaps is looked at here and not by the host, which would have to wait for it.
 __global__ void k_pair_init(uint32_t n_tasks, const uint64_t* __restrict__ n_gaps, long long* __restrict__ top_filled,
                             unsigned long long* __restrict__ best_scenario, uint32_t* __restrict__ best_lp,
                             int64_t* __restrict__ best_filled, Ctrl* ctrl) {
@@ -24,22 +24,23 @@ __global__ void k_pair_init(uint32_t n_tasks, const uint64_t* __restrict__ n_gap
   best_filled[t] = 0;
 }
 
-// G lanes per scenario (a workgroup or a wave), which take every so-manieth one: they check the scenario, sum the time filled in its
-// gaps (8 B read per gap) and raise the largest filled time seen for its high-priority task.  Bound by HBM once enough bytes are in
-// flight: a lane has up to eight 16-byte reads out at a time.  From PAIR_WAVES scenarios on a wave takes one: as many waves as
-// there are places for stay and look the next scenario up while they read, so that nothing but the reads themselves is waited for, and no
-// barrier is met (16,384 scenarios of 2047 gaps: a workgroup each 62 us = 4.3 TB/s, call 84.3 us; waves 57 us = 4.7 TB/s, call
-// 79.6 us; twice as many workgroups 83.3, half as many 81.6, sixteen reads at a time 81.1, reads that are not to be kept 83.5).
-// Below it, a workgroup's reads come back sooner than a wave's (40 scenarios of 4772 gaps: call 26.6 against 27.3 us).  Where the
-// gaps are no more than the lanes, each reads one of them: eight guarded reads are then most of the instructions (200,000 scenarios of 3 gaps,
-// call 273 us with them, 227 us without; of 30 gaps 253 and 225 us, both with a workgroup each).  The atomic returns nothing, so
-// nothing waits for it; looking at the word first does wait, at a word that all scenarios of a task share (158 us).
+// G lanes per scenario (a workgroup or a wave), which take every so-manieth one: they check the scenario, sum the time filled in
+// its gaps (8 B read per gap) and raise the largest filled time seen for its high-priority task.  Bound by HBM once enough bytes
+// are in flight: a lane has up to eight 16-byte reads out at a time.  From PAIR_WAVES scenarios on a wave takes one: as many
+// waves as there are places for stay and look the next scenario up while they read, so that nothing but the reads themselves is
+// waited for, and no barrier is met (16,384 scenarios of 2047 gaps: a workgroup each 62 us = 4.3 TB/s, call 84.3 us; waves 57 us
+// = 4.7 TB/s, call 79.6 us; twice as many workgroups 83.3, half as many 81.6, sixteen reads at a time 81.1, reads that are not to
+// be kept 83.5). Below it, a workgroup's reads come back sooner than a wave's (40 scenarios of 4772 gaps: call 26.6 against 27.3
+// us).  Where the gaps are no more than the lanes, each reads one of them: eight guarded reads are then most of the instructions
+// (200,000 scenarios of 3 gaps, call 273 us with them, 227 us without; of 30 gaps 253 and 225 us, both with a workgroup each).
+// The atomic returns nothing, so nothing waits for it; looking at the word first does wait, at a word that all scenarios of a
+// task share (158 us).
 //
 // A scenario of many more gaps than the others (PAIR_LONG times the average and more than PAIR_LONG_LEAST) is left to the end by
 // its wave, and the workgroup's waves sum it up together: a wave alone decided the call.  us per call, a workgroup per
-// scenario / waves alone / now: 8192 scenarios of 1000 gaps, one of 100,000 65 / 78 / 60, one of 1,000,000 202 / 364 / 191, eight of
-// 1,000,000 212 / 388 / 207; 8192 of 100, 64 of 200,000 84 / 112 / 79; 20,000 of 500, one of 4,000,000 668 / 1356 / 645; 8192 of 20,000
-// 282 / 268 / 262.
+// scenario / waves alone / now: 8192 scenarios of 1000 gaps, one of 100,000 65 / 78 / 60, one of 1,000,000 202 / 364 / 191, eight
+// of 1,000,000 212 / 388 / 207; 8192 of 100, 64 of 200,000 84 / 112 / 79; 20,000 of 500, one of 4,000,000 668 / 1356 / 645; 8192
+// of 20,000 282 / 268 / 262.
 constexpr uint64_t PAIR_WAVES = 8192, PAIR_STAY = 2048;   // (PAIR_STAY workgroups of four waves fill the chip)
 constexpr uint64_t PAIR_LONG = 8, PAIR_LONG_LEAST = 8192;
 constexpr uint32_t PAIR_LONGS = 256;   // of a workgroup; what is beyond stays with its wave
@@ -165,15 +166,15 @@ __device__ __forceinline__ void pair_result(uint32_t t, const uint32_t* __restri
   best_filled[t] = scen_filled[b];
 }
 
-// Among the scenarios of a task with the largest filled time the one whose partner completes earliest, and among those the first.  A
-// scenario takes the task's place from the one that holds it if it comes before that one; both are compared by the call's inputs, so
-// the word that changes hands is all that workgroups tell each other.  Few scenarios reach the largest filled time as a rule, and few
-// try.  Where nothing fits into any gap all of them do: with more than PAIR_FEW in a workgroup, its best one of each task is found
-// in LDS first, and only that one tries (pick in us, all try / so, and two rounds of atomic minima: 16,384 scenarios of one task that
-// all fill nothing, completions falling 315 / 10, 195, rising 175 / 10, 194; 100,000 of 64 tasks, falling 100 / 59, 38).
-// With up to PAIR_LAST_TASKS tasks the last workgroup to get here writes the results; with more, k_pair_finish does (one workgroup
-// takes 256 of them at a time, 1.5 us each).  Two launches for what took three (16,384 scenarios of 128 tasks: call 89.0 us with
-// three).
+// Among the scenarios of a task with the largest filled time the one whose partner completes earliest, and among those the
+// first.  A scenario takes the task's place from the one that holds it if it comes before that one; both are compared by the
+// call's inputs, so the word that changes hands is all that workgroups tell each other.  Few scenarios reach the largest filled
+// time as a rule, and few try.  Where nothing fits into any gap all of them do: with more than PAIR_FEW in a workgroup, its best
+// one of each task is found in LDS first, and only that one tries (pick in us, all try / so, and two rounds of atomic minima:
+// 16,384 scenarios of one task that all fill nothing, completions falling 315 / 10, 195, rising 175 / 10, 194; 100,000 of 64
+// tasks, falling 100 / 59, 38). With up to PAIR_LAST_TASKS tasks the last workgroup to get here writes the results; with more,
+// k_pair_finish does (one workgroup takes 256 of them at a time, 1.5 us each).  Two launches for what took three (16,384
+// scenarios of 128 tasks: call 89.0 us with three).
 constexpr uint32_t PAIR_LAST_TASKS = 512;
 constexpr uint32_t PAIR_FEW = 8, PAIR_SLOTS = 512, PAIR_PROBES = 8;
 constexpr uint32_t PAIR_NONE = ~0u;

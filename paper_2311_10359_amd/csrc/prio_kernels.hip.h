@@ -339,10 +339,10 @@ k_pf_walk(const uint64_t* __restrict__ off, const uint32_t* __restrict__ hp_task
 // What bounds it: with few scenarios the chain of one decision (compare, first lane, three lane reads, compare, lane write:
 // about 260 cycles), with many the issue of its 25 to 35 instructions.  4096 scenarios of 1023 gaps and three queues of 2048:
 // 0.94 ms (k_pf_walk, whose 256 waves leave most of the chip idle and which idles in half of its decisions: 2.16 ms).
-// Up to this many scenarios (every wave has a SIMD to itself) a scenario whose levels hold one or two requests, and one of them two,
-// goes through a level in scalars: the chain of a decision is then one lane read instead of eight steps between the two units.  It is as
-// many instructions, most of them for the scalar port, and with four waves per SIMD that loses.  Traces of 1024 launches, queues of
-// 2048, ms for the call through the lanes / in scalars:
+// Up to this many scenarios (every wave has a SIMD to itself) a scenario whose levels hold one or two requests, and one of them
+// two, goes through a level in scalars: the chain of a decision is then one lane read instead of eight steps between the two
+// units.  It is as many instructions, most of them for the scalar port, and with four waves per SIMD that loses.  Traces of 1024
+// launches, queues of 2048, ms for the call through the lanes / in scalars:
 //   64 scenarios    2 tasks 0.61 / 0.48   3: 0.83 / 0.59   6: 1.51 / 0.96   9: 1.46 / 1.09
 //   1024 scenarios  2 tasks 0.63 / 0.50   3: 0.85 / 0.62   6: 1.53 / 0.98   9: 1.48 / 1.11
 //   1536 scenarios  2 tasks 0.65 / 0.59   3: 0.88 / 0.75   6: 1.53 / 1.00   9: 1.47 / 1.12

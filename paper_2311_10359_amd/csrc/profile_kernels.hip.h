@@ -156,7 +156,8 @@ __device__ __forceinline__ void profile_begin(const uint64_t* off, uint32_t n_ta
 // Bound by HBM, which reads 64 bytes and writes 16 by turns.  A lane reads its own launch's times as 16 bytes and its run; the next
 // launch's are the next lane's, the wave's last lane has its neighbour's read by all as one place.  24,000,000 launches:
 // 399 us with the next launch read by every lane, 361 so, 341 us = 5.6 TB/s with the hint that neither what is read nor what is
-// written will be used again (only the writes 347, only the reads 361; two launches per lane 370 with both hints; 378 without, four 383).
+// written will be used again (only the writes 347, only the reads 361; two launches per lane 370 with both hints; 378 without,
+// four 383).
 __global__ void __launch_bounds__(256)
 k_measure(const fikit_launch* __restrict__ rec, uint64_t n, int64_t* __restrict__ exec_ns, int64_t* __restrict__ gap_ns,
           Ctrl* ctrl) {

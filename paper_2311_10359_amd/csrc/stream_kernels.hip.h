@@ -130,9 +130,9 @@ __device__ __forceinline__ uint32_t su_slot(StreamSmem& sm, uint64_t id) {
 // launches (ustart, ulen) and nothing else: other tasks may have handed their values over to the sort there already.
 // Another unit may give the task up to the sort at any time (the launches of smaller units have run, but units of more than
 // FUSE_MID_MAX launches and other streamed ones run beside it): the task's flag is looked at along the way, and the unit leaves.
-// fikit_profile, us, flag looked at at the start only / along the way, with 600 IDs in a bucket of 12,000 launches beside one ID with
-// most of the others: a task of 300,000 launches 1500 / 1185, 16 of them 1830 / 1520, 64 of 1,000,000 11,150 / 9550; profiles of
-// which no task is given up are the same.
+// fikit_profile, us, flag looked at at the start only / along the way, with 600 IDs in a bucket of 12,000 launches beside one ID
+// with most of the others: a task of 300,000 launches 1500 / 1185, 16 of them 1830 / 1520, 64 of 1,000,000 11,150 / 9550;
+// profiles of which no task is given up are the same.
 // PART: what of the launches is looked at.
 enum : int { SU_BOTH = 0, SU_EXEC = 1, SU_IDLE = 2 };
 constexpr uint32_t SU_UNPLACED = ~0u;
@@ -501,12 +501,13 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
 // One of the front's is taken by two workgroups, one for the execution times and one for the idle times, where that leaves a
 // compute unit to each: all of them, or only those of more than STREAM_LONGEST launches, or none.  What a unit of 227,000 launches
 // takes decides the launch then, and the memory of one compute unit decides that; both workgroups find and rank the IDs, and
-// nothing is waited for, but all of it together is a third more work.  So no unit is taken so that is not longer, by a quarter, than
-// what there is for each workgroup to do: the other units fill the chip then, and the third more is all that comes of it.
-// This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only the
-// longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000 1700 /
-// 1391; 60 of 400,000, two IDs with 0.3 of the launches each and 30 others 273 / 242.  Left whole for what else there is: 100 tasks of
-// 300,000, one ID with 0.3 of the launches and 20 others 378 / 418, 40 of 2,000,000, two IDs with 0.1 each and 200 others 655 / 747.
+// nothing is waited for, but all of it together is a third more work.  So no unit is taken so that is not longer, by a quarter,
+// than what there is for each workgroup to do: the other units fill the chip then, and the third more is all that comes of it.
+// This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only
+// the longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000
+// 1700 / 1391; 60 of 400,000, two IDs with 0.3 of the launches each and 30 others 273 / 242.  Left whole for what else there is:
+// 100 tasks of 300,000, one ID with 0.3 of the launches and 20 others 378 / 418, 40 of 2,000,000, two IDs with 0.1 each and 200
+// others 655 / 747.
 constexpr uint64_t UNIT_LARGE_WORKGROUPS = 256;
 constexpr uint32_t SU_SPLIT_PARTS = 192;
 __global__ void __launch_bounds__(SU_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))

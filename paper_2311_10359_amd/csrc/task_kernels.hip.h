@@ -124,9 +124,10 @@ __device__ __forceinline__ uint64_t* staged_row(int64_t* stage_a, int64_t* stage
 
 // Rows of a task that one workgroup profiles whole are staged in eight words instead of a row's sixteen (what is below 2^32 there,
 // two to a word), in the task's slices of as many arrays as they need (STAGING_ARRAYS of the per-launch arrays, which lie `stride`
-// words apart): three rows to four launches.  A task with more is sorted, which short traces of many kernels should not be.  Staged as whole rows in two arrays, one to
-// eight launches, / now, us: profile of 8200 tasks of 64 launches, 10 kernels, 862 / 191, of 3000 of 1500, 250 kernels, 1462 / 282; step of
-// 1000 pairs of 300 and 500, 60 and 100 kernels 550 / 120, of one pair of 100, 20 and 30 kernels 176 / 44.
+// words apart): six rows to every whole eight launches, none to a task of fewer than eight.  A task with more is sorted, which
+// short traces of many kernels should not be.  Staged as whole rows in two arrays, one to eight launches, / now, us: profile of
+// 8200 tasks of 64 launches, 10 kernels, 862 / 191, of 3000 of 1500, 250 kernels, 1462 / 282; step of 1000 pairs of 300 and 500,
+// 60 and 100 kernels 550 / 120, of one pair of 100, 20 and 30 kernels 176 / 44.
 constexpr uint32_t ROW_WORDS = 8, STAGING_ARRAYS = 6;
 enum : uint32_t { RW_ID, RW_COUNTS, RW_EXEC_SUM, RW_GAP_SUM, RW_EXEC_RANGE, RW_GAP_RANGE, RW_EXEC_PICKS, RW_GAP_PICKS };
 struct Staging {
@@ -286,9 +287,9 @@ __device__ __forceinline__ void unit_to_general(const FusedArgs& A, uint32_t t) 
 //   2048 of       16,384   699 / 653      766 / 718      841 / 822      942 / 947
 //   4096 of        8200    795 / 755      890 / 854     1021 / 1003    1161 / 1157
 //   4096 of       16,384  1290 / 1200    1424 / 1326    1577 / 1536    1800 / 1796
-// (47 us for all: 1024 tasks of 8200 launches 251, 286, 331 and 369 us, 4096 of them and 300 kernels 1174; not shortened: 1024 of 16,384 launches and
-// 300 kernels 527.)  Tasks of all lengths, which do not stay together: 4000 of 1 to 18,000 launches, 100 kernels, 1519 / 1515.  The smaller
-// shapes, of which a compute unit holds two or three, gain nothing.
+// (47 us for all: 1024 tasks of 8200 launches 251, 286, 331 and 369 us, 4096 of them and 300 kernels 1174; not shortened: 1024 of
+// 16,384 launches and 300 kernels 527.)  Tasks of all lengths, which do not stay together: 4000 of 1 to 18,000 launches, 100
+// kernels, 1519 / 1515.  The smaller shapes, of which a compute unit holds two or three, gain nothing.
 constexpr uint32_t FUSE_SPREAD_TASKS = 1024, FUSE_SPREAD_ALL = 2048, FUSE_SPREAD_WORKGROUPS = 256, FUSE_SPREAD_STEPS = 55;   // (a step is 2048 cycles)
 __device__ __forceinline__ void spread_start(uint32_t block, uint32_t launches, uint32_t tasks) {
   const uint32_t most = FUSE_SPREAD_STEPS * launches / FUSE_MAX * min_u32(tasks, FUSE_SPREAD_ALL) / FUSE_SPREAD_ALL;

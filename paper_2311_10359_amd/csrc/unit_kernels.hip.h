@@ -11,10 +11,10 @@
 // per sample pair in step 3; a workgroup's LDS (8 bytes per launch) decides how many units a compute unit overlaps.  Steps 1 and
 // 2 as before with registers instead of LDS and a barrier after each of some forty short steps took 1.1 to 2.2 times as long:
 // fikit_profile, us, before / now: 256 tasks of 1,048,576 launches, uniform over 1000 IDs 7840 / 6945 (its units 3240 / 2410);
-// 64 of them, Zipf over 4096 IDs 3580 / 2410 (1440 / 685 for the units, the rest from the streamed ones); 16 of 1,000,000, 1000 IDs,
-// times that hardly vary 1208 / 542; 64 of 131,072, 30 IDs, times in steps of 500 ns 809 / 375; 256 of 50,000 in passes over 300 IDs
-// 574 / 434; 64 of 20,000, 20 IDs 141 / 132.  The share from which on all waves work on an ID: with one wave for every ID the skewed
-// units take 1770 us, with all waves from one share on those of the 1000 IDs 2790 us.
+// 64 of them, Zipf over 4096 IDs 3580 / 2410 (1440 / 685 for the units, the rest from the streamed ones); 16 of 1,000,000, 1000
+// IDs, times that hardly vary 1208 / 542; 64 of 131,072, 30 IDs, times in steps of 500 ns 809 / 375; 256 of 50,000 in passes over
+// 300 IDs 574 / 434; 64 of 20,000, 20 IDs 141 / 132.  The share from which on all waves work on an ID: with one wave for every ID
+// the skewed units take 1770 us, with all waves from one share on those of the 1000 IDs 2790 us.
 #pragma once
 
 #include <type_traits>
