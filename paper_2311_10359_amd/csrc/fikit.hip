@@ -201,7 +201,7 @@ struct Mailbox {
   static constexpr size_t BYTES = 256, WAIT_AT = BYTES;
   unsigned char* at = nullptr;
   uint32_t waits = 0;      // of this thread so far
-  // (another thread may be capturing a graph, which an allocation or a release in the default mode would break)
+  // (another thread may be capturing a graph, which an allocation, a release, a question or a wait in the default mode would break)
   struct Relaxed {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
@@ -299,6 +299,7 @@ struct Reads {
       t_launches = 0;
       ask = !few;
       if (few) {
+        const Mailbox::Relaxed relaxed;
         hipEvent_t behind;
         if (hipEventCreateWithFlags(&behind, hipEventDisableTiming) == hipSuccess) {
           (void)hipEventRecord(behind, st);
@@ -316,10 +317,12 @@ struct Reads {
       const auto looked = std::chrono::steady_clock::now() - from;
       if (ask && looked > std::chrono::nanoseconds(ASK_NS)) {
         ask = false;
+        const Mailbox::Relaxed relaxed;
         (void)hipStreamQuery(st);   // (the answer is that it is not, which would stand as the last error)
         (void)hipGetLastError();
       }
       if (looked > std::chrono::nanoseconds(LOOK_NS)) {
+        const Mailbox::Relaxed relaxed;
         FIKIT_HIP(hipStreamSynchronize(st));
         if (!arrived()) return FIKIT_HIP_ERROR;
         break;

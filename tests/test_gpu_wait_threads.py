@@ -104,3 +104,49 @@ def test_threads_on_one_processor_give_way_while_they_wait():
     alone_us, shared_us = statistics.median(alone) * 1e6, statistics.median(shared) * 1e6
     print(f"{alone_us:.1f} us per call from one thread, {shared_us:.1f} from four", flush=True)
     assert shared_us < 0.85 * alone_us     # 0.6; 1.06 where a waiting thread keeps the processor
+
+
+@pytest.mark.parametrize("tasks,launches", [(2, 1000), (6, 20000), (64, 20000)])     # few launches, many, and some for longer
+@pytest.mark.parametrize("busy_cycles", [0, 5_000_000])                               # (a wait of some milliseconds)
+def test_calls_beside_a_capture(tasks, launches, busy_cycles):
+    caller = Caller(300, tasks=tasks, launches=launches)
+    x = torch.zeros(1000, device=DEV)
+    with torch.cuda.stream(caller.stream):
+        caller.call()
+    torch.cuda.synchronize()
+    capturing, called = threading.Event(), threading.Event()
+
+    def work(c):
+        assert capturing.wait(60)
+        try:
+            for _ in range(20):
+                if busy_cycles:
+                    torch.cuda._sleep(busy_cycles)
+                c.call()
+        finally:
+            called.set()
+
+    failed = []
+
+    def body():
+        try:
+            run_threads([caller], work)
+        except BaseException as e:
+            failed.append(e)
+
+    thread = threading.Thread(target=body)
+    thread.start()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        x.add_(1)
+        capturing.set()
+        assert called.wait(60)
+        x.add_(1)
+    thread.join(60)
+    assert not failed, failed
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(x, torch.full_like(x, 6))
+    with torch.cuda.stream(caller.stream):
+        caller.check()
