@@ -28,13 +28,13 @@ __global__ void k_pair_init(uint32_t n_tasks, const uint64_t* __restrict__ n_gap
 // its gaps (8 B read per gap) and raise the largest filled time seen for its high-priority task.  Bound by HBM once enough bytes
 // are in flight: a lane has up to eight 16-byte reads out at a time.  From PAIR_WAVES scenarios on a wave takes one: as many
 // waves as there are places for stay and look the next scenario up while they read, so that nothing but the reads themselves is
-// waited for, and no barrier is met (16,384 scenarios of 2047 gaps: a workgroup each 62 us = 4.3 TB/s, call 84.3 us; waves 57 us
-// = 4.7 TB/s, call 79.6 us; twice as many workgroups 83.3, half as many 81.6, sixteen reads at a time 81.1, reads that are not to
-// be kept 83.5). Below it, a workgroup's reads come back sooner than a wave's (40 scenarios of 4772 gaps: call 26.6 against 27.3
-// us).  Where the gaps are no more than the lanes, each reads one of them: eight guarded reads are then most of the instructions
-// (200,000 scenarios of 3 gaps, call 273 us with them, 227 us without; of 30 gaps 253 and 225 us, both with a workgroup each).
-// The atomic returns nothing, so nothing waits for it; looking at the word first does wait, at a word that all scenarios of a
-// task share (158 us).
+// waited for, and no barrier is met on the way (16,384 scenarios of 2047 gaps: a workgroup each 62 us = 4.3 TB/s, call 84.3 us;
+// waves 57 us = 4.7 TB/s, call 79.6 us; twice as many workgroups 83.3, half as many 81.6, sixteen reads at a time 81.1, reads
+// that are not to be kept 83.5). Below it, a workgroup's reads come back sooner than a wave's (40 scenarios of 4772 gaps: call
+// 26.6 against 27.3 us).  Where the gaps are no more than the lanes, each reads one of them: eight guarded reads are then most
+// of the instructions (200,000 scenarios of 3 gaps, call 273 us with them, 227 us without; of 30 gaps 253 and 225 us, both with
+// a workgroup each). The atomic returns nothing, so nothing waits for it; looking at the word first does wait, at a word that
+// all scenarios of a task share (158 us).
 //
 // A scenario of many more gaps than the others (PAIR_LONG times the average and more than PAIR_LONG_LEAST) is left to the end by
 // its wave, and the workgroup's waves sum it up together: a wave alone decided the call.  us per call, a workgroup per
