@@ -36,8 +36,9 @@ constexpr uint64_t MAX_ELEMS = (1ull << 32) - (1ull << 24);
     }                                             \
   } while (0)
 
-// Launches of this thread since the last wait of a call (see Reads::wait).
+// Launches of this thread since the last wait of a call, and how long it looked in the last one of many (see Reads::wait).
 thread_local uint32_t t_launches = 0;
+thread_local int64_t t_looked = 0;
 #define FIKIT_COUNT_LAUNCH(...)      \
   do {                               \
     ++t_launches;                    \
@@ -240,17 +241,19 @@ thread_local Mailbox t_mailbox;
 // beyond them it leaves it to its handler thread, which takes 20 us longer.  (A synchronisation behind N empty kernels and a
 // report that has been seen: 9 us up to N = 6, 24 us from 7 on; with an event recorded behind the report 5.6 us up to N = 5.)  So
 // behind the last report of a call of few launches an event is recorded, which nobody waits for; in a longer one the runtime is
-// asked whether the stream is empty, which sets the handler to work, but only once the host has looked for ASK_NS: asking takes
-// 14 us, which then pass while the call does.
+// asked whether the stream is empty, which sets the handler to work.  Asking takes 14 us of the host's time, which have to pass
+// while the call does: the runtime is asked at once if the thread's last such call had it look for ASK_AT_ONCE_NS, otherwise once
+// it has looked for ASK_NS (asked after 30 us in every call, those that end soon after are 12 to 14 us longer: merge of 22 tasks
+// of 724 rows 64 / 78, step of 15 and 25 short tasks 66 / 78).
 // Calls in us, with copies and the runtime's wait / reports alone / now:    one behind the other     each with a synchronisation
-//   fikit_measure, 1000 launches                                              28 / 27 / 26             31 / 35 / 29
-//   pairing of 16 scenarios                                                   33 / 27 / 27             36 / 36 / 30
-//   step of a pair of 1000 launches                                           57 / 48 / 48             60 / 59 / 50
-//   merge of 16 tasks of 20 rows (seven launches, over before it is asked)    50 / 38 / 38             53 / 46 / 46
-//   priority queues, one scenario of two                                     120 / 103 / 106          121 / 131 / 110
-//   merge of 20,000 tasks of 90 rows                                         287 / 235 / 234          290 / 246 / 237
-//   step of 256 scenarios of 65,536 launches                                 358 / 341 / 342          361 / 374 / 350
-//   priority queues, 4096 scenarios of three                                1060 / 1038 / 1041       1059 / 1067 / 1041
+//   fikit_measure, 1000 launches                                              30 / 26 / 27             33 / 36 / 30
+//   pairing of 16 scenarios                                                   33 / 27 / 28             36 / 36 / 30
+//   step of a pair of 1000 launches                                           59 / 48 / 48             61 / 60 / 52
+//   merge of 16 tasks of 20 rows (seven launches, over before it is asked)    51 / 34 / 35             54 / 47 / 47
+//   priority queues, one scenario of two                                     122 / 100 / 105          123 / 129 / 111
+//   merge of 20,000 tasks of 90 rows                                         286 / 233 / 233          296 / 245 / 241
+//   step of 256 scenarios of 65,536 launches                                 365 / 341 / 350          370 / 375 / 352
+//   priority queues, 4096 scenarios of three                                1057 / 1034 / 1042       1060 / 1071 / 1048
 // (asked at once in every call: fikit_measure 38 to 44, the small merge 51 to 55, the step of a pair 47 to 51 one behind the
 // other.)
 //
@@ -260,7 +263,7 @@ thread_local Mailbox t_mailbox;
 struct Reads {
   static constexpr int MOST = 4;
   static constexpr int64_t LOOK_NS = 1000000;   // (the runtime's wait adds 4 us, which a call of this length no longer feels)
-  static constexpr int64_t ASK_NS = 30000;
+  static constexpr int64_t ASK_NS = 150000, ASK_AT_ONCE_NS = 40000;
   static constexpr uint32_t RUNTIME_WAITS = 8;
   static constexpr size_t place(size_t bytes) { return (bytes + 15) / 16 * 16; }
   hipStream_t st;
@@ -293,41 +296,42 @@ struct Reads {
     }
     FIKIT_COUNT_LAUNCH(k_report, dim3(1), dim3(64), 0, st, r, seen, number);
     FIKIT_HIP(hipGetLastError());
-    bool ask = false;
-    if (last) {
-      const bool few = t_launches + 2 <= RUNTIME_WAITS;   // (the event and the wait's own command)
-      t_launches = 0;
-      ask = !few;
-      if (few) {
-        const Mailbox::Relaxed relaxed;
-        hipEvent_t behind;
-        if (hipEventCreateWithFlags(&behind, hipEventDisableTiming) == hipSuccess) {
-          (void)hipEventRecord(behind, st);
-          (void)hipEventDestroy(behind);
-        }
-        (void)hipGetLastError();
-      }
-    }
-    auto arrived = [&] { return __atomic_load_n(seen, __ATOMIC_ACQUIRE) == number; };
     const auto from = std::chrono::steady_clock::now();
+    auto looked = [&] { return std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() - from).count(); };
+    auto arrived = [&] { return __atomic_load_n(seen, __ATOMIC_ACQUIRE) == number; };
+    const bool few = t_launches + 2 <= RUNTIME_WAITS, many = last && !few;   // (the event and the wait's own command)
+    if (last) t_launches = 0;
+    if (last && few) {
+      const Mailbox::Relaxed relaxed;
+      hipEvent_t behind;
+      if (hipEventCreateWithFlags(&behind, hipEventDisableTiming) == hipSuccess) {
+        (void)hipEventRecord(behind, st);
+        (void)hipEventDestroy(behind);
+      }
+      (void)hipGetLastError();
+    }
+    bool to_ask = many;
+    auto ask = [&] {
+      to_ask = false;
+      const Mailbox::Relaxed relaxed;
+      (void)hipStreamQuery(st);   // (the answer is that it is not, which would stand as the last error)
+      (void)hipGetLastError();
+    };
+    if (many && t_looked >= ASK_AT_ONCE_NS) ask();
     for (uint32_t looks = 1; !arrived(); ++looks) {
       __builtin_ia32_pause();   // (x86, as the hosts of these GPUs are)
       if (looks % 64 != 0) continue;
       std::this_thread::yield();
-      const auto looked = std::chrono::steady_clock::now() - from;
-      if (ask && looked > std::chrono::nanoseconds(ASK_NS)) {
-        ask = false;
-        const Mailbox::Relaxed relaxed;
-        (void)hipStreamQuery(st);   // (the answer is that it is not, which would stand as the last error)
-        (void)hipGetLastError();
-      }
-      if (looked > std::chrono::nanoseconds(LOOK_NS)) {
+      const int64_t ns = looked();
+      if (to_ask && ns > ASK_NS) ask();
+      if (ns > LOOK_NS) {
         const Mailbox::Relaxed relaxed;
         FIKIT_HIP(hipStreamSynchronize(st));
         if (!arrived()) return FIKIT_HIP_ERROR;
         break;
       }
     }
+    if (many) t_looked = looked();
     for (int i = 0; i < n; ++i) std::memcpy(item[i].to, box + item[i].at, item[i].bytes);
     return FIKIT_OK;
   }
