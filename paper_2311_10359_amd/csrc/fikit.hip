@@ -255,7 +255,8 @@ thread_local Mailbox t_mailbox;
 //   step of 256 scenarios of 65,536 launches                                 365 / 341 / 350          370 / 375 / 352
 //   priority queues, 4096 scenarios of three                                1057 / 1034 / 1042       1060 / 1071 / 1048
 // (asked at once in every call: fikit_measure 38 to 44, the small merge 51 to 55, the step of a pair 47 to 51 one behind the
-// other.)
+// other.)  The sort's way through a profile ends in a report too: the runtime's wait at its end took the 20 us longer (4 tasks of
+// 98 launches of as many kernels 162 / 135, 144 with copies).
 //
 // The host gives way to other threads while it looks, which may have calls of their own to enqueue (us per step of a pair of 1000
 // launches, all threads together, runtime's wait / looking without giving way / so: 8 threads on 2 processors 48 / 51 to 54 / 48,
@@ -651,6 +652,7 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
     return FIKIT_OK;
   }
   const uint64_t n_general = h.n_general;
+  t_launches += Reads::RUNTIME_WAITS;   // (that was not the call's last wait)
   if (n_units > 0) {
     tr.mark("k_long_general_values");
     FIKIT_COUNT_LAUNCH(k_long_general_values, dim3(static_cast<uint32_t>(n_msd_tiles)), dim3(256), 0, st, d_records, d_task_offsets,
@@ -772,8 +774,8 @@ int profile_run(const fikit_launch* d_records, uint64_t n_records, const uint64_
                        1u);
   }
   FIKIT_HIP(hipGetLastError());
-  FIKIT_HIP(hipStreamSynchronize(st));
-  return FIKIT_OK;
+  Reads end(st);
+  return end.wait(true);
 }
 
 }  // namespace
