@@ -499,17 +499,20 @@ __device__ __forceinline__ void unit_streamed(const FusedArgs& A, uint32_t unit,
 // largest first), then from its back, then the others.
 //
 // One of the front's is taken by two workgroups, one for the execution times and one for the idle times, where that leaves a
-// compute unit to each: all of them, or only those of more than STREAM_LONGEST launches, or none.  What a unit of 227,000 launches
-// takes decides the launch then, and the memory of one compute unit decides that; both workgroups find and rank the IDs, and
-// nothing is waited for, but all of it together is a third more work.  So no unit is taken so that is not longer, by a quarter,
-// than what there is for each workgroup to do: the other units fill the chip then, and the third more is all that comes of it.
-// This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only
-// the longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000
-// 1700 / 1391; 60 of 400,000, two IDs with 0.3 of the launches each and 30 others 273 / 242.  Left whole for what else there is:
-// 100 tasks of 300,000, one ID with 0.3 of the launches and 20 others 378 / 418, 40 of 2,000,000, two IDs with 0.1 each and 200
-// others 655 / 747.
+// compute unit to each: all of them, or only those of more than STREAM_LONGEST launches, or none.  What a unit of 227,000
+// launches takes decides the launch then, and the memory of one compute unit decides that; both workgroups find and rank the
+// IDs, and nothing is waited for, but all of it together is a third more work.  Where a quarter of the launches and more is in
+// units that are not streamed, these fill the chip behind the streamed ones, and none of those is taken so that is not longer,
+// by a quarter, than what there is for each workgroup to do: the third more is all that would come of it.
+// This launch in us, whole / in parts: 4 tasks of 1,048,576 launches, Zipf over 4096 IDs, 678 / 423, 64 of them 757 / 631 (only the
+// longest), 96 of them 1001 / 1005; 16 tasks of 300,000 over 50 IDs 218 / 178, 30 of 1,000,000 649 / 517; one of 4,300,000 1700 /
+// 1391; 60 of 400,000, two IDs with 0.3 of the launches each and 30 others 273 / 242; 30 of 1,000,000 over 20 IDs alike 458 / 380,
+// 20 of 2,000,000 over 30 (all streamed, the others' order decides) 932 / 675.  Left whole for what else there is: 100 tasks of
+// 300,000, one ID with 0.3 of the launches and 20 others 373 / 418, 128 of 1,000,000, one with 0.1 and 300 others 656 / 724, 40 of
+// 2,000,000, two IDs with 0.1 each and 200 others 655 / 747.
 constexpr uint64_t UNIT_LARGE_WORKGROUPS = 256;
-constexpr uint32_t SU_SPLIT_PARTS = 192;
+constexpr uint32_t SU_SPLIT_PARTS = 192, SU_FILL_PART = 4;
+constexpr uint32_t LARGE_TYPICAL = (FUSE_MID_MAX + FUSE_MAX) / 2;   // launches of a unit that is not streamed
 __global__ void __launch_bounds__(SU_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_unit_large(const FusedArgs A, const uint32_t* __restrict__ streamed, uint32_t streamed_end, uint2* __restrict__ pack_kg_all,
              int64_t* __restrict__ pack_slot_all) {
@@ -518,9 +521,10 @@ k_unit_large(const FusedArgs A, const uint32_t* __restrict__ streamed, uint32_t 
   if (A.ctrl->status & ERR_OFFSETS) return;
   const uint32_t large = A.ctrl->n_class[2], front = A.ctrl->n_class[3], back = A.ctrl->n_class[4];
   const uint32_t longest = A.ctrl->n_class[5];   // units of more than STREAM_LONGEST
-  const uint32_t for_each = A.ctrl->n_large / static_cast<uint32_t>(UNIT_LARGE_WORKGROUPS);
+  const uint32_t launches = A.ctrl->n_large, for_each = launches / static_cast<uint32_t>(UNIT_LARGE_WORKGROUPS);
+  const bool filled = static_cast<uint64_t>(large) * LARGE_TYPICAL >= launches / SU_FILL_PART;
   const uint32_t split_above = max_u32(2 * front <= UNIT_LARGE_WORKGROUPS ? 0u : 2 * longest <= SU_SPLIT_PARTS ? STREAM_LONGEST : ~0u,
-                                       for_each + for_each / 4);
+                                       filled ? for_each + for_each / 4 : 0u);
   for (;;) {
     if (threadIdx.x == 0) ticket = atomicAdd(&A.ctrl->taken, 1u);
     __syncthreads();

@@ -43,7 +43,8 @@ def together(parts):
     return torch.cat(recs), ends[0], (np.concatenate(ids), np.concatenate(rows), ends[1])
 
 
-@pytest.mark.parametrize("parts", [[(LONG, 0.3, 20, 100)], [(LONG, 0.3, 20, 60), (4_000_000, 0.6, 30, 1)], [(LONG, 0.3, 600, 100)]])
+@pytest.mark.parametrize("parts", [[(LONG, 0.3, 20, 100)], [(LONG, 0.3, 20, 60), (4_000_000, 0.6, 30, 1)], [(LONG, 0.3, 600, 100)],
+                                   [(600_000, 0.25, 7, 40)], [(900_000, 0.1, 13, 20), (LONG, 0.4, 20, 9)]])     # (the last two: few units that are not streamed)
 def test_units_left_whole(parts):
     rng = np.random.default_rng(len(parts))
     d_rec, off, want = together([(task(rng, *p[:3]), p[3]) for p in parts])
