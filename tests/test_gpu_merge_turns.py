@@ -11,6 +11,7 @@ import oracle
 from paper_2311_10359_amd import binding
 from parity_util import DEV
 from test_gpu_merge import check_merge
+from timing_util import below
 
 pytestmark = pytest.mark.gpu
 
@@ -55,13 +56,16 @@ def test_two_lengths_in_turn_cost_what_both_cost_apart():
         row_off = torch.empty(sizes.size + 1, dtype=torch.int64, device=DEV)
         ws = binding.workspace(binding.fikit_profile_merge_workspace_bytes(sizes.size), DEV)
         calls[name] = lambda s=sides, o=out, r=row_off, w=ws: binding.fikit_profile_merge(*s, rows_out=o, task_row_offsets_out=r, workspace_buf=w)
-    took = {name: [] for name in calls}
-    for _ in range(15):
-        for name, call in calls.items():
-            torch.cuda.synchronize()
-            t = time.perf_counter()
-            call()
-            took[name].append(time.perf_counter() - t)
-    us = {name: statistics.median(t) * 1e6 for name, t in took.items()}
-    print({name: round(t) for name, t in us.items()}, flush=True)
-    assert us["in turn"] < 1.2 * (us["short"] + us["long"])
+
+    def compare():
+        took = {name: [] for name in calls}
+        for _ in range(15):
+            for name, call in calls.items():
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                call()
+                took[name].append(time.perf_counter() - t)
+        us = {name: statistics.median(t) * 1e6 for name, t in took.items()}
+        return us["in turn"], 1.2 * (us["short"] + us["long"])
+
+    assert below(compare)                  # 0.92; 1.3 in fixed turns

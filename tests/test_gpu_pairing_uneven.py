@@ -10,6 +10,7 @@ import torch
 from paper_2311_10359_amd import binding
 from parity_util import DEV
 from test_gpu_pairing import check_pairing
+from timing_util import below
 
 pytestmark = pytest.mark.gpu
 WAVES = 8192                  # from this many scenarios on a wave takes one, in rounds of as many
@@ -72,13 +73,21 @@ def call_of(gaps, comp, filled_up_to):
 def test_one_long_scenario_costs_the_same_among_more_others():
     gaps = np.full(WAVES, 1000)
     gaps[7] = 1_000_000
-    below, at = took_us([call_of(gaps[:-1], np.arange(WAVES - 1), 1000), call_of(gaps, np.arange(WAVES), 1000)])
-    print(f"{below:.0f} us by workgroups, {at:.0f} us by waves", flush=True)
-    assert at < 1.3 * below
+    calls = [call_of(gaps, np.arange(WAVES), 1000), call_of(gaps[:-1], np.arange(WAVES - 1), 1000)]     # by waves, by workgroups
+
+    def compare():
+        waves, workgroups = took_us(calls)
+        return waves, 1.3 * workgroups
+
+    assert below(compare)                  # 1.02; 2.2 by waves alone
 
 
 def test_order_of_tied_scenarios_does_not_matter():
     gaps = np.full(2 * WAVES, 3)
-    falling, equal = took_us([call_of(gaps, np.arange(gaps.size)[::-1], 1), call_of(gaps, np.zeros(gaps.size), 1)])
-    print(f"falling completions {falling:.0f} us, equal ones {equal:.0f} us", flush=True)
-    assert falling < 1.4 * equal
+    calls = [call_of(gaps, np.arange(gaps.size)[::-1], 1), call_of(gaps, np.zeros(gaps.size), 1)]       # falling completions, equal ones
+
+    def compare():
+        falling, equal = took_us(calls)
+        return falling, 1.4 * equal
+
+    assert below(compare)                  # 1.0; 1.65 to 2.2 if all of them try

@@ -10,6 +10,7 @@ import torch
 import oracle
 from paper_2311_10359_amd import binding, traces
 from parity_util import DEV, assert_profile_equal
+from timing_util import below
 
 pytestmark = pytest.mark.gpu
 
@@ -55,13 +56,16 @@ def test_spread_costs_nothing_where_it_gains_nothing():
         ws = binding.workspace(binding.fikit_profile_workspace_bytes(n, tasks), DEV)
         calls[tasks] = lambda a=d_rec, b=d_off, c=ids, d=rows, e=row_off, f=ws: binding.fikit_profile(
             a, b, ids_out=c, rows_out=d, task_row_offsets_out=e, workspace_buf=f)
-    took = {tasks: [] for tasks in calls}
-    for _ in range(40):
-        for tasks, call in calls.items():
-            torch.cuda.synchronize()
-            t = time.perf_counter()
-            call()
-            took[tasks].append((time.perf_counter() - t) / tasks)
-    below, above = (statistics.median(took[tasks]) for tasks in calls)
-    print(f"per task {below * 1e9:.0f} ns below, {above * 1e9:.0f} above", flush=True)
-    assert above < 1.04 * below            # 1.01 with the spread by what the tasks are, 1.07 to 1.09 with one of the same length for all
+
+    def compare():
+        took = {tasks: [] for tasks in calls}
+        for _ in range(40):
+            for tasks, call in calls.items():
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                call()
+                took[tasks].append((time.perf_counter() - t) / tasks)
+        under, on = (statistics.median(took[tasks]) for tasks in calls)
+        return on, 1.045 * under
+
+    assert below(compare)                  # 1.01 with the spread by what the tasks are, 1.07 to 1.09 with one of the same length for all

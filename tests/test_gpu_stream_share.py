@@ -9,6 +9,7 @@ import torch
 import oracle
 from paper_2311_10359_amd import binding, traces
 from parity_util import DEV, assert_profile_equal
+from timing_util import below
 
 pytestmark = pytest.mark.gpu
 LONG = 300_000
@@ -53,8 +54,8 @@ def test_units_left_whole(parts):
 
 def test_no_work_is_done_twice_where_the_chip_is_full():
     rec = task(np.random.default_rng(1), LONG, 0.3, 20)
-    took = {}
-    for tasks in (100, 130):             # (with 130 there are more such units than half the workgroups, and none is cut)
+
+    def per_task(tasks):
         d_rec, off = binding.to_device_records(rec, DEV).repeat(tasks, 1), binding.to_device_u64(np.arange(tasks + 1, dtype=np.uint64) * LONG, DEV)
         ms = []
         for _ in range(12):
@@ -62,6 +63,7 @@ def test_no_work_is_done_twice_where_the_chip_is_full():
             binding.fikit_profile(d_rec, off)
             ms.append(binding.fikit_trace_read()["k_unit_large"][0])
             binding.fikit_trace_enable(False)
-        took[tasks] = statistics.median(ms) / tasks
-    print({k: f"{v * 1e3:.2f} us per task" for k, v in took.items()}, flush=True)
-    assert took[100] < 1.05 * took[130]  # 1.11 with the units cut in two
+        return statistics.median(ms) / tasks
+
+    # with 130 there are more such units than half the workgroups, and none is cut; 1.01 to 1.03, 1.11 to 1.12 with the units cut in two
+    assert below(lambda: (per_task(100), 1.07 * per_task(130)))

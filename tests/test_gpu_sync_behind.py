@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2311_10359_amd import binding, traces
+from timing_util import below
 
 DEV = "cuda:0"
 
@@ -25,11 +26,14 @@ def test_nothing_is_left_behind_a_call(tasks, launches):
     hp, lp = traces.scenarios(cfg)
     d_rec, d_off = binding.to_device_records(rec, DEV), binding.to_device_u64(off, DEV)
     d_hp, d_lp, d_gaps = binding.to_device_u32(hp, DEV), binding.to_device_u32(lp, DEV), binding.to_device_u64(traces.gap_offsets(off, hp), DEV)
-    idle, behind = [], []
-    for _ in range(100):
-        binding.fikit_profile_gapfill(d_rec, d_off, d_hp, d_lp, d_gaps, margin_ns=cfg.margin_ns, min_gap_ns=cfg.min_gap_ns)
-        behind.append(synchronisation_us())
-        idle.append(synchronisation_us())
-    print(f"behind a call {statistics.median(behind):.1f} us, idle {statistics.median(idle):.1f} us", flush=True)
+
+    def compare():
+        idle, behind = [], []
+        for _ in range(100):
+            binding.fikit_profile_gapfill(d_rec, d_off, d_hp, d_lp, d_gaps, margin_ns=cfg.margin_ns, min_gap_ns=cfg.min_gap_ns)
+            behind.append(synchronisation_us())
+            idle.append(synchronisation_us())
+        return statistics.median(behind), 2 * statistics.median(idle) + 2
+
     # 2.9 us on an idle device; 3.5 to 4.2 where the runtime was told or asked of the call's end, 12 to 32 where it was not
-    assert statistics.median(behind) < 2 * statistics.median(idle) + 2
+    assert below(compare)

@@ -11,6 +11,7 @@ import torch
 
 import oracle
 from paper_2311_10359_amd import binding, traces
+from timing_util import below
 
 DEV = "cuda:0"
 
@@ -97,13 +98,15 @@ def test_threads_on_one_processor_give_way_while_they_wait():
     torch.cuda.synchronize()
     cpu = sorted(os.sched_getaffinity(0))[:1]
     calls = 200
-    alone, shared = [], []
-    for _ in range(5):
-        alone.append(run_threads(callers[:1], lambda c: [c.call() for _ in range(calls)], cpu) / calls)
-        shared.append(run_threads(callers, lambda c: [c.call() for _ in range(calls)], cpu) / (calls * len(callers)))
-    alone_us, shared_us = statistics.median(alone) * 1e6, statistics.median(shared) * 1e6
-    print(f"{alone_us:.1f} us per call from one thread, {shared_us:.1f} from four", flush=True)
-    assert shared_us < 0.85 * alone_us     # 0.6; 1.06 where a waiting thread keeps the processor
+
+    def compare():
+        alone, shared = [], []
+        for _ in range(5):
+            alone.append(run_threads(callers[:1], lambda c: [c.call() for _ in range(calls)], cpu) / calls)
+            shared.append(run_threads(callers, lambda c: [c.call() for _ in range(calls)], cpu) / (calls * len(callers)))
+        return statistics.median(shared) * 1e6, 0.85 * statistics.median(alone) * 1e6
+
+    assert below(compare)                  # 0.4 to 0.6; 0.98 to 1.06 where a waiting thread keeps the processor
 
 
 @pytest.mark.parametrize("tasks,launches", [(2, 1000), (6, 20000), (64, 20000)])     # few launches, many, and some for longer
