@@ -29,10 +29,11 @@
  * Conventions
  *   - d_* arguments are device pointers, h_* are host pointers.  The caller owns every buffer,
  *     including the workspace; the library allocates no device memory and its results depend
- *     on nothing but a call's arguments (the only things it keeps between calls are 320 bytes of
- *     pinned host memory per calling thread, through which counts and status come back and which
- *     are freed when the thread ends, the measurement aid fikit_trace_*, the bound of
- *     fikit_set_wait_limit and the scratch address of fikit_gapfill_static).  Inputs are left
+ *     on nothing but a call's arguments (the only things it keeps between calls are, per calling
+ *     thread, 320 bytes of pinned host memory, through which counts and status come back, an event
+ *     and two numbers about its last call's length, all given back when the thread ends, the
+ *     measurement aid fikit_trace_*, the bound of fikit_set_wait_limit and the scratch address of
+ *     fikit_gapfill_static).  Inputs are left
  *     untouched.
  *   - All work is enqueued on `hip_stream` (a hipStream_t passed as void*; NULL = the default
  *     stream).  Every call but fikit_gapfill_static waits until its work there is done

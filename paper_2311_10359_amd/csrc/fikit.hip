@@ -202,6 +202,8 @@ struct Mailbox {
   static constexpr size_t BYTES = 256, WAIT_AT = BYTES;
   unsigned char* at = nullptr;
   uint32_t waits = 0;      // of this thread so far
+  hipEvent_t end = nullptr;
+  int end_device = -1;
   // (another thread may be capturing a graph, which an allocation, a release, a question or a wait in the default mode would break)
   struct Relaxed {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -209,9 +211,22 @@ struct Mailbox {
     ~Relaxed() { if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode); }
   };
   ~Mailbox() {
-    if (!at) return;
+    if (!at && !end) return;
     const Relaxed relaxed;
-    (void)hipHostFree(at);
+    if (end) (void)hipEventDestroy(end);
+    if (at) (void)hipHostFree(at);
+  }
+  // The event that is recorded behind short calls, on the current device (null: there is none).  In the relaxed mode.
+  hipEvent_t end_event() {
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess) return nullptr;
+    if (end && end_device != device) {
+      (void)hipEventDestroy(end);
+      end = nullptr;
+    }
+    if (!end && hipEventCreateWithFlags(&end, hipEventDisableTiming) != hipSuccess) end = nullptr;
+    end_device = device;
+    return end;
   }
   unsigned char* get() {
     if (!at) {
@@ -304,11 +319,7 @@ struct Reads {
     if (last) t_launches = 0;
     if (last && few) {
       const Mailbox::Relaxed relaxed;
-      hipEvent_t behind;
-      if (hipEventCreateWithFlags(&behind, hipEventDisableTiming) == hipSuccess) {
-        (void)hipEventRecord(behind, st);
-        (void)hipEventDestroy(behind);
-      }
+      if (const hipEvent_t end = t_mailbox.end_event()) (void)hipEventRecord(end, st);   // (the thread's own: made anew it costs 1 us)
       (void)hipGetLastError();
     }
     bool to_ask = many;
